@@ -351,7 +351,7 @@ def main():
     tokens_per_s = T / (ms_per_step * 1e-3)
     assert torch.isfinite(op.out).all()
 
-    # dominant kernel: the score kernel (k_score_mfma for bf16 codebooks; with the codebook packed ahead of
+    # dominant kernel: the score kernel (k_score_stream for bf16 codebooks; with the codebook packed ahead of
     # time it is the only kernel of the score stage, so the stage's HIP events time exactly its launches).
     # Algorithmic work per launch (per (token, KV head) unit): M_k*d additions of the gather-sum, 3d for the
     # rotation, 2dG for the G dot products.
@@ -360,7 +360,7 @@ def main():
     score_flops = units * w.d * (w.Mk + 3 + 2 * G)
     achieved_tflops = score_flops / score_s / 1e12 if score_s > 0 else 0.0
     paired = w.key_format == "paired"
-    kname = "k_score_pair" if paired else ("k_score_mfma" if w.dtype == "bf16" else "k_score")
+    kname = "k_score_pair" if paired else ("k_score_stream" if w.dtype == "bf16" else "k_score")
     if args.position_free:
         kname = "k_score_lut"
     # HBM bytes per launch from rocprofv3 counter passes (FETCH_SIZE, WRITE_SIZE) of this same command: counters
@@ -390,8 +390,8 @@ def main():
                 "launches_sampled": ("every call of a separate eager run" if args.graph else
                                      f"every {args.stage_event_interval}th call of the timed region"),
                 "timed_region_includes": ("index unpacking (k_unpack_pairs) + k_score_pair" if paired else
-                                          "k_score_mfma + k_score_combine" if prepacked and op.plan.score_slice_groups > 1 else
-                                          "k_score_mfma only" if prepacked else "codebook re-layout (k_prep) + score kernel"),
+                                          "k_score_stream + k_score_combine" if prepacked and op.plan.score_slice_groups > 1 else
+                                          "k_score_stream only" if prepacked else "codebook re-layout (k_prep) + score kernel"),
                 "lds_gather_view": {"codeword_bytes_TBs": round(gather_tbs, 2), "peak_TBs": LDS_PEAK_TBS,
                                     "frac": round(gather_tbs / LDS_PEAK_TBS, 4)},
                 "mfma_view": {"issued_bf16_TFLOPs": round(mfma_tflops, 1), "peak_TFLOPs": mfma_peak,

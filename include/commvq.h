@@ -111,7 +111,7 @@ typedef struct {
 
 /* How one call is cut into workgroups (host struct, filled by commvq_plan_query). */
 typedef struct {
-    int32_t score_split_len;  /* context tokens per score workgroup */
+    int32_t score_split_len;  /* context tokens per score tile (at most; a power of two) */
     int32_t score_splits;     /* score workgroups per (sequence, KV head) for max_seqlen */
     int32_t value_split_len;  /* context tokens per value workgroup */
     int32_t value_splits;     /* value workgroups per (sequence, KV head) for max_seqlen */

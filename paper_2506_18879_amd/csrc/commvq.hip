@@ -5,7 +5,7 @@
 //               codewords, rotate once by the RoPE matrix of the relative position, contract
 //               with the G query heads of the group -> scaled logits + per-split (max, sum exp).
 //               bf16 codebooks with contiguous key positions: k_prep (codebook re-laid in
-//               LDS-image order) + k_score_mfma (codebook slices streamed through LDS, tile codes
+//               LDS-image order) + k_score_stream (codebook slices streamed through LDS, tile codes
 //               resident in registers, gather-sum and query contraction on the matrix cores), for
 //               short contexts with the tiles also cut along the slices + k_score_combine;
 //               fp32 codebooks or explicit key positions: k_score (rows gathered through L1).
@@ -47,7 +47,7 @@ struct Workspace {
     float *lsum;      // [B * Hq * value_splits] sum of exp(logit - sequence max) over the score tiles that begin in that value split
     unsigned *bins;   // [B * Hkv * value_splits][K][Mv][G] fixed-point bins (codeword-major: see k_bins)
     float *partial;   // [B * Hq * out_chunks][d]
-    uint4 *packed;    // key codebook re-laid slice-major for k_score_mfma / k_score_pair
+    uint4 *packed;    // key codebook re-laid slice-major for k_score_stream / k_score_pair
     uint8_t *pair_bytes;  // paired-code keys: one byte per index, [T * Hkv][32 * blocks]
     float *lut;           // position-free keys: scale * q . C, [B * Hkv][M_k * K][G]
     float *scores_part;   // [slice groups][T * Hq] partial logits when the score tiles are also cut along the slices
@@ -55,7 +55,7 @@ struct Workspace {
     size_t bytes;
 };
 
-// The slice-streaming score kernel (k_score_mfma) serves bf16 codebooks with contiguous positions; everything else
+// The slice-streaming score kernel (k_score_stream) serves bf16 codebooks with contiguous positions; everything else
 // (fp32 codebooks, explicit key positions) goes through the gather kernel.
 bool use_sliced(const commvq_handle *h, bool explicit_positions)
 {
@@ -85,31 +85,60 @@ inline size_t packed_key_bytes(const commvq_config &c)
     return (size_t)c.n_kv_heads * c.m_key * kK * kD * 2;
 }
 
-void make_plan(const commvq_handle *h, int B, int max_seqlen, bool sliced, commvq_plan *p)
+// How k_score_stream cuts a launch: `passes` segments of 512 tokens per workgroup, `tiles` workgroups per KV head, each of
+// them once per slice group.
+struct StreamShape {
+    int passes, tiles, groups;
+};
+StreamShape stream_shape(const commvq_handle *h, int B, int64_t T, int max_seqlen)
+{
+    const int per_seq = (max_seqlen + kPassTokens - 1) / kPassTokens;
+    // segments per KV head: at most one partly filled one per sequence more than the tokens need; about half of them for the estimate
+    const int64_t most = std::min<int64_t>((int64_t)B * per_seq, T / kPassTokens + B);
+    const int64_t likely = B == 1 ? most : std::min<int64_t>((int64_t)B * per_seq, T / kPassTokens + (B + 1) / 2);
+    // Cost of a workgroup in microseconds, fitted to sweeps over lengths from 350 tokens up: a fixed start and end (launch, first
+    // fetches, write-out), and per slice a switch and the passes.  A launch too short to fill the 256 compute units is also
+    // cut along the slices; every group then fetches the tile's codes again, the partial logits take a trip through
+    // memory (at 4 TB/s), and k_score_combine is one more launch.
+    const bool two = h->cfg.m_key == 32;
+    const double fixed = 9.0, sw = two ? 1.25 : h->G == 8 ? 0.6 : 0.5, c = two ? (h->G == 8 ? 0.70 : 0.66) : (h->G == 8 ? 0.47 : 0.41);
+    const double part = (double)T * h->cfg.n_q_heads / 1e6 + (two ? 0.08 : 0.15);
+    StreamShape best = {2, 1, 1};
+    double t_best = 1e30;
+    for (int passes = 2; passes <= kStreamPasses; ++passes)
+        for (int e = 1; e <= kStreamSlices; e *= 2) {
+            const int64_t wgs = (likely + passes - 1) / passes * h->cfg.n_kv_heads * e;
+            const double t = (double)((wgs + 255) / 256) * (fixed + (double)(kStreamSlices / e) * (sw + passes * c)) + (e > 1 ? 5.0 + e * part : 0.0);
+            if (t < t_best * 0.9999) { t_best = t; best = StreamShape{passes, 0, e}; }
+        }
+    best.tiles = (int)((most + best.passes - 1) / best.passes);
+    return best;
+}
+
+// Whether the sliced score path is k_score_stream (index-form keys with RoPE).
+inline bool stream_keys(const commvq_config &c) { return !pair_keys(c) && !c.position_free; }
+
+void make_plan(const commvq_handle *h, int B, int64_t T, int max_seqlen, bool sliced, commvq_plan *p)
 {
     const int units = B * h->cfg.n_kv_heads;
     int len, groups = 1;
-    if (sliced) {
-        // Tile = 1024, 2048 or 4096 tokens of one (sequence, KV head); a context too short to fill the 256 compute
-        // units with such tiles is also cut along the codebook slices, `groups` workgroups per tile that each stream
-        // S / groups slices and leave partial logits for k_score_combine to add.  Cost model of a workgroup, in
-        // microseconds as measured on the five configurations: a fixed start (first fetches, write-out), per slice a
-        // switch (LDS refill, barriers) and the passes themselves.
-        const bool splittable = !pair_keys(h->cfg) && !h->cfg.position_free;
+    if (sliced && stream_keys(h->cfg)) {
+        const StreamShape ss = stream_shape(h, B, T, max_seqlen);
+        groups = ss.groups;
+        len = 1024;
+        while (len < ss.passes * kPassTokens) len *= 2;
+    } else if (sliced) {
+        // Tile = 1024, 2048 or 4096 tokens of one (sequence, KV head).  Cost model of a workgroup, in microseconds: a fixed
+        // start (first fetches, write-out), per slice a switch (LDS refill, barriers) and the passes themselves.
         const int S = pair_keys(h->cfg) ? 4 : h->cfg.m_key / 2;                       // slices per tile
         const double c1024 = h->cfg.m_key == 16 && !pair_keys(h->cfg) ? 2.1 : 1.85;  // passes of 1024 tokens over one slice
         double best = 1e30;
         len = 1024;
-        groups = 1;
         for (int tpt = 1; tpt <= kScoreMaxTpt; tpt *= 2) {
             if (tpt == 4 && h->G == 8 && (h->cfg.m_key == 16 || pair_keys(h->cfg))) break;  // those instantiations run out of registers
-            for (int e = 1; e <= (splittable ? S : 1); e *= 2) {
-                const long wgs = (long)units * ((max_seqlen + 1024 * tpt - 1) / (1024 * tpt)) * e;
-                // cut along the slices: every group fetches the tile's codes again, the partial logits take a trip through
-                // memory, and k_score_combine is one more launch
-                const double t = (double)((wgs + 255) / 256) * (9.0 + (double)(S / e) * (1.3 + tpt * c1024)) + (e > 1 ? 12.0 : 0.0);
-                if (t < best * 0.9999) { best = t; len = 1024 * tpt; groups = e; }
-            }
+            const long wgs = (long)units * ((max_seqlen + 1024 * tpt - 1) / (1024 * tpt));
+            const double t = (double)((wgs + 255) / 256) * (9.0 + (double)S * (1.3 + tpt * c1024));
+            if (t < best * 0.9999) { best = t; len = 1024 * tpt; }
         }
     } else {
         len = 1024;
@@ -145,9 +174,13 @@ void make_plan(const commvq_handle *h, int B, int max_seqlen, bool sliced, commv
 }
 
 // Granularity of the (max, sum of exp) statistics that the score stage leaves for k_bins: the score tile, except that
-// k_score_combine (tiles cut along the slices) writes them per 1024 tokens.
-inline int stat_len(const commvq_plan &p) { return p.score_kernel && p.score_slice_groups > 1 ? 1024 : p.score_split_len; }
-inline int stat_splits(const commvq_plan &p, int max_seqlen) { return (max_seqlen + stat_len(p) - 1) / stat_len(p); }
+// k_score_stream writes them per 512-token segment and k_score_combine (tiles cut along the slices) per 1024 tokens.
+inline int stat_len(const commvq_handle *h, const commvq_plan &p)
+{
+    if (p.score_kernel && stream_keys(h->cfg)) return p.score_slice_groups > 1 ? 1024 : kPassTokens;
+    return p.score_split_len;
+}
+inline int stat_splits(const commvq_handle *h, const commvq_plan &p, int max_seqlen) { return (max_seqlen + stat_len(h, p) - 1) / stat_len(h, p); }
 
 // Carves the workspace.  Array sizes are the larger of what the two score kernels need, so one
 // workspace size serves a batch shape whether or not explicit positions are passed.
@@ -155,9 +188,9 @@ void carve(const commvq_handle *h, int B, int64_t T, int max_seqlen, void *base,
 {
     const commvq_config &c = h->cfg;
     commvq_plan pa, pb;
-    make_plan(h, B, max_seqlen, true, &pa);
-    make_plan(h, B, max_seqlen, false, &pb);
-    const size_t ssplits = std::max<size_t>(std::max(pa.score_splits, pb.score_splits), (size_t)stat_splits(pa, max_seqlen));
+    make_plan(h, B, T, max_seqlen, true, &pa);
+    make_plan(h, B, T, max_seqlen, false, &pb);
+    const size_t ssplits = std::max<size_t>(std::max(pa.score_splits, pb.score_splits), (size_t)stat_splits(h, pa, max_seqlen));
     const size_t vsplits = pa.value_splits > pb.value_splits ? pa.value_splits : pb.value_splits;
     size_t off = 0;
     auto take = [&](size_t n_floats) {
@@ -452,45 +485,33 @@ __global__ __launch_bounds__(kScoreThreads) void k_score(
 
 // ------------------------------------------------------------------ k_prep
 constexpr int kSliceThreads = 1024;              // one workgroup per compute unit
-constexpr int kSliceBytes = 128 * 1024;          // LDS bytes of one codebook slice
-constexpr int kPhaseBytes = (4 * 64 + 4 * 65) * 16;  // LDS bytes of the slice's phase factors (at most)
 constexpr int kStatBytes = (kSliceThreads / 64) * 8 * 8;  // per-wavefront (max, sum) of up to 8 heads
-constexpr int kScoreLds = kSliceBytes + 2 * kPhaseBytes + kStatBytes;  // the phase factors are double-buffered
 
-// Key codebook re-laid for k_score_mfma.
-//   packed[g][s][blk][c][col] : 16-byte pieces (8 bf16).  Slice s holds elements DS*s .. DS*s + DS-1 of
-//                        every codeword (DS = 256 / M, S = 128 / DS slices) as one contiguous 128 KiB
-//                        image of two 64 KiB blocks of 256 rows (one per code value c) x 16 pieces:
-//                        piece x = 16 blk + col with x = 16 * plane + m for M = 16 (plane = which 8 of
-//                        the 16 elements) and x = m for M = 32.  A 256-byte row spans all 64 LDS banks,
-//                        so a piece lives in bank column col whatever its code: lanes that read
-//                        different columns never conflict.
+// Key codebook re-laid for k_score_stream.
+//   packed[g][s][blk][c][col] : 16-byte pieces (8 bf16).  Slice s holds elements 8 s .. 8 s + 7 of every codeword as
+//                        one (M = 16) or two (M = 32) contiguous 64 KiB images of 256 rows (one per code value c) x 16
+//                        pieces: codebook 16 blk + col.  A 256-byte row spans all 64 LDS banks, so a piece
+//                        lives in bank column col whatever its code: lanes that read different columns never conflict.
 // One thread per 16-byte piece of the source (coalesced reads).
 __global__ __launch_bounds__(256) void k_prep(const uint4 *__restrict__ key_cb, uint4 *__restrict__ packed, int Hkv, int M)
 {
-    const int P = 32 / M;                       // planes: DS / 8 = (256 / M) / 8
     const size_t n_pieces = (size_t)Hkv * M * kK * 16;
     const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (t >= n_pieces) return;
-    const int piece = (int)(t & 15);            // 16 pieces of 8 elements per row
+    const int sl = (int)(t & 15);               // a row's 16 pieces of 8 elements: one per slice
     const size_t row = t >> 4;                  // (g * M + m) * K + c
     const int g = (int)(row / ((size_t)M * kK));
     const int mc = (int)(row % ((size_t)M * kK));
     const int m = mc / kK, c = mc % kK;
-    const int sl = piece / P, pl = piece % P;
-    const int S = 16 / P;
-    const int x = pl * 16 + m;                  // 0..31: block x / 16, bank column x % 16
-    packed[((((size_t)g * S + sl) * 2 + x / 16) * kK + c) * 16 + x % 16] = key_cb[t];
+    packed[(((size_t)g * 16 + sl) * (M / 16) + m / 16) * (kK * 16) + c * 16 + m % 16] = key_cb[t];
 }
 
 struct SliceDims {
     int Hq, Hkv, nsplit, n_hi, q_bf16;
     float scale;
-    int groups;            // workgroups per tile, each with S / groups of the codebook slices (k_score_mfma)
-    long long part_stride; // floats between the partial logit arrays of two slice groups
 };
 
-// ------------------------------------------------------------------ k_score_mfma
+// ------------------------------------------------------------------ k_score_stream
 
 // 16-byte LDS read at an absolute LDS byte address.  The score kernels keep their dynamic LDS at address 0
 // (no static LDS), but the compiler only learns that after instruction selection: a read through the array's
@@ -498,26 +519,617 @@ struct SliceDims {
 typedef __attribute__((address_space(3))) const uint4_t *lds_u4_ptr;
 __device__ __forceinline__ uint4_t lds_read_b128(unsigned byte_addr) { return *reinterpret_cast<lds_u4_ptr>(byte_addr); }
 
-// Max / sum over the lanes of a wavefront that hold logits of the same query head in k_score_mfma:
-// one 16-lane row (M = 16), or the two rows r and r + 2 (M = 32).
-template <int M>
-__device__ __forceinline__ float head_lanes_max(float v)
+// Workgroup barrier that waits for nothing by itself: the caller has waited for what the others may rely on (LDS
+// reads that have been consumed, lds_dma16 loads by s_waitcnt).  No LDS access moves across it.
+__device__ __forceinline__ void bare_barrier()
 {
-    v = row_max16(v);
-    if (M == 16) return v;
-    const unsigned u = __builtin_bit_cast(unsigned, v);
-    auto r32 = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-    return fmaxf(__builtin_bit_cast(float, (unsigned)r32[0]), __builtin_bit_cast(float, (unsigned)r32[1]));
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
 }
-template <int M>
-__device__ __forceinline__ float head_lanes_sum(float v)
+
+// The lane's index, made anew wherever it is asked for: what depends on it is then neither hoisted out of a loop nor kept in
+// registers (or spilled) across it.
+__device__ __forceinline__ int fresh_lane()
 {
-    v = row_sum16(v);
-    if (M == 16) return v;
-    const unsigned u = __builtin_bit_cast(unsigned, v);
-    auto r32 = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-    return __builtin_bit_cast(float, (unsigned)r32[0]) + __builtin_bit_cast(float, (unsigned)r32[1]);
+    int l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+    return l;
 }
+
+constexpr int kBlockBytes = 64 * 1024;    // 16 codebooks x 256 codewords x 16 bytes
+// LDS behind the two 64 KiB blocks, per buffer of two, in 16-byte pieces (what a slice needs besides the codebook, sent
+// from memory straight into LDS by thread x to piece x): fine phase factors [2 parts][64], coarse ones [8 passes][9 rows]
+// [2 parts] padded to whole wavefronts, raw queries [8 passes][G heads][1 (bf16) or 2 (fp32)]
+constexpr int kAuxHi = 2 * kLo, kAuxQ = kAuxHi + 192, kAuxPieces = kAuxQ + 128;
+constexpr int kHiRows = 9;
+constexpr int kAuxBytes = kAuxPieces * 16;
+constexpr int kSegOff = 2 * kBlockBytes + 2 * kAuxBytes;          // int4 per pass: sequence, first token, length, cu_seqlens
+constexpr int kWstOff = kSegOff + kStreamPasses * 16;             // float2 [8 passes][2 halves][8 heads]
+constexpr int kAuxTabOff = kWstOff + kStreamPasses * 2 * 8 * 8;   // where thread x's piece comes from (for slice 0)
+constexpr int kStreamLds = kAuxTabOff + kAuxPieces * 8;
+
+struct StreamDims {
+    int Hq, Hkv, G, batch, n_hi, q_bf16;
+    float scale;
+    int tiles;             // workgroups per KV head and slice group
+    int groups;            // workgroups per tile, each with S / groups of the codebook slices
+    int nstat;             // 512-token statistics per (sequence, query head)
+    long long part_stride; // floats between the partial logit arrays of two slice groups
+};
+
+// Slice-streaming score kernel with both contractions on the matrix cores (Eq. new_attention,
+// re-bracketed: gather-sum the codeword blocks first, rotate once, contract with the G queries).
+// Works on the key codebook repacked by k_prep: slice sl = 8 consecutive elements of every codeword, as one (M = 16) or
+// two (M = 32) 64 KiB LDS images of 256 rows (code value) x 16 bank columns (codebook).
+//
+// Tokens.  The contexts of a KV head, one sequence after the other, are cut into segments of 512 tokens; a workgroup takes
+// `passes` consecutive segments -- of one long sequence, or of several short ones: everything that depends on the sequence
+// (query, distances, output place) is looked up per pass.  A pass is 64 fine positions (token mod 64) x 8 coarse rows; a
+// wavefront owns 4 fine positions, and lane n of its 16 token lanes takes fine position n / 4 and coarse rows n % 4 (set 0)
+// and 4 + n % 4 (set 1).  So the four lanes of a 4-lane block, both sets and all passes of one sequence are whole coarse
+// rows (64 tokens) apart: they share the fine phase factor E_lo of the relative position 64 H + lo, which is folded
+// into the block's query operand once per slice, and a pass only rotates by the coarse factor E_hi.
+//
+// Codes.  The tile's codes are read once and stay in registers for all slices, in the byte order of the lane's gather steps.
+//
+// Per slice and pass:
+//  1. Gather-sum: v_smfmac_f32_16x16x64_bf16 (structured-sparse first operand) with a constant 0/1 selection
+//     matrix as first operand and 128 gathered pieces as second: lane n + 16 g supplies two pieces, A for token n
+//     of set 0 and B for token n of set 1, of the same codebook.  Products with 1.0 are exact, so this is the plain fp32 sum
+//     of the M codeword slices.  Rows 0..7 of the result are elements 0..7 of set 0's tokens, rows 8..15 those of set 1's:
+//     lane (n, g) receives elements 4 (g & 1) .. + 3 of its token of set g >> 1.
+//     The LDS reads of a group of steps are issued right after the matrix instructions that consumed the
+//     group's registers, so the first reads of the next pass travel while this pass is finished.
+//  2. Each lane rotates its two (x, y) sub-spaces by the coarse phase factor of its token.
+//  3. Contraction with the queries, two passes at a time: the two lanes of a token hold half of its 8 elements each, so
+//     an exchange of 16-lane rows between the passes of a pair (4 v_permlane16_swap) gives the even lane all 8 elements of
+//     its token of the even pass and the odd lane those of its token of the odd pass.  Eight chained
+//     v_mfma_f32_4x4x1_16b_f32 per group of 4 heads (in a block of 4 lanes, lane i supplies q'[head i][element], every lane
+//     its own element) then add the slice's whole contribution to the accumulators of 4 heads: nothing is left to add or
+//     exchange per head, where totals over the token's lanes per pass took 6 (G = 4) to 12 (G = 8) vector instructions.
+// What bounds it: SIMD issue.  With four wavefronts on a SIMD a sparse MFMA takes 17 clk of it, a 4x4x1 one 9, a row swap 9,
+// a byte permute 5, a rotation's multiplication or addition 3 (micro-benchmark), and they add up; a pass is 4 (8) + 4 (8) +
+// 2 + 8 (16) + 8 of these for M = 16 (32) and 4 heads = 200 (300) clk at 2.4 GHz, and the compute unit's LDS needs 4.35 clk
+// for each of the M / 2 + 1 16-byte reads of its 16 wavefronts, 157 (296) per SIMD.  Measured per slice of 8 passes: 7700
+// clk at 2.14 GHz against 5700 for M = 16, 13200 against 9800 for M = 32; the rest is the switch of slices and what the
+// latencies of one wavefront's chain leave open.  A wavefront that is behind issues first (s_setprio by pass): waves that ran
+// ahead left the last ones alone on their SIMD before each barrier (C3 74.5 -> 73.4 us, 8 heads 487 -> 475).
+//
+// Slices.  M = 16: the two 64 KiB blocks take slices in turn, the next one travels (memory -> LDS, no registers)
+// while the current one is worked on: one barrier per slice.  Its sends are spread over the passes, since a burst fills
+// the memory pipe's queue and stops the wavefronts for up to 2000 clk.  M = 32: a slice fills both blocks (codebooks 0..15 |
+// 16..31).  Its last pass is done with block 0 after half of its steps; the next slice's block 0, fetched into registers
+// earlier, is stored right then, and block 1 follows after the first half of the next slice's first pass, when everyone
+// has left the old one.  With 8 heads no registers are left to wait in: there the blocks are sent for at those points.
+//
+// Times, one sequence or batch of the 8B / 70B layer, before (tiles of one sequence, per-head totals after every pass) and
+// now: 128K tokens, M = 16: 75.3 -> 72 us; 8 x 8K..64K, M = 32: 435 -> 390; 64 x 512..1024, M = 32: 105 -> 70 (sequences
+// share workgroups); 4 x 128K, M = 32, 8 heads: 548 -> 475.  Not kept: three or four steps of reads in flight instead of two
+// (spills, or no change); M = 32 as two sweeps of 16 codebooks with the gather sums carried in registers, which
+// allows double buffering but only 4 to 6 passes (8 heads: 549 us, 4 heads: 403).
+//
+// Short contexts: a launch may cut every tile along the slices as well (StreamDims::groups workgroups per
+// tile); each then writes partial logits, which k_score_combine adds.
+template <int M, int NGRP, int NP>
+__global__ __launch_bounds__(kSliceThreads) void k_score_stream(
+    const void *__restrict__ q, const uint8_t *__restrict__ key_codes, const uint4 *__restrict__ packed,
+    const int32_t *__restrict__ cu, const int32_t *__restrict__ q_pos, const float2 *__restrict__ tbl_hi,
+    const float2 *__restrict__ tbl_lo, float *__restrict__ scores, float2 *__restrict__ sstat, const StreamDims a)
+{
+    constexpr int S = kStreamSlices;
+    constexpr int NB = M / 16;                                // 64 KiB blocks per slice
+    constexpr int NST = 4 * NB;                               // gather steps (sparse matrix instructions) per pass
+    const int G = NGRP == 2 ? 8 : a.G;                        // query heads of the KV head; NGRP groups of 4, padded with zero queries
+    constexpr int NBUF = 2;                                   // gather steps whose LDS reads are in flight
+    constexpr bool STAGE = M == 32 && NGRP == 1;              // next slice through registers (8 heads leave none)
+    constexpr bool DELAY = M == 16 && NGRP == 1;              // a pair's rest runs between the steps of the next pass (else: no registers)
+    extern __shared__ __attribute__((aligned(16))) uint4 tab[];
+
+    int id = blockIdx.x;
+    const int g = id % a.Hkv;                                 // (head = index mod Hkv: with 8 KV heads an XCD serves one head)
+    id /= a.Hkv;
+    const int tile = id % a.tiles;
+    const int eg = id / a.tiles;                              // which group of slices
+    const int s_begin = eg * (S / a.groups), s_end = s_begin + S / a.groups;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    // The slice's codebook images: thread x's piece x of every 16 KiB, memory -> LDS.
+    const char *src = reinterpret_cast<const char *>(packed) + (size_t)g * S * NB * kBlockBytes;
+    auto send_part = [&](int sl, int blk, int slot, int j) {
+        const char *p = src + ((size_t)sl * NB + blk) * kBlockBytes + j * 16384;
+        lds_dma16(p, (unsigned)(wave * 64 + fresh_lane()) * 16u, (unsigned)(slot * kBlockBytes + j * 16384 + wave * 1024));
+    };
+    auto send_block = [&](int sl, int blk, int slot) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) send_part(sl, blk, slot, j);
+    };
+    send_block(s_begin, 0, M == 16 ? s_begin & 1 : 0);
+    if (M == 32) send_block(s_begin, 1, 1);
+
+    // This workgroup's segments: pass p works on tokens pt0[p] .. + 511 of sequence pb[p].  Every wavefront finds them by
+    // itself, 64 sequences at a time (prefix sums of the sequences' segment counts).
+    int pb[NP], pt0[NP], pL[NP], pcu[NP];
+    int qd[NP];                                               // distance of the segment's first token to its query
+    int np = 0;                                               // passes that exist
+#pragma unroll
+    for (int p = 0; p < NP; ++p) { pb[p] = 0; pt0[p] = 0; pL[p] = 0; pcu[p] = 0; qd[p] = 0; }
+    const int first = tile * NP;
+    if (a.batch == 1) {
+        const int c0 = cu[0], L = cu[1] - c0, qp = q_pos[0];
+#pragma unroll
+        for (int p = 0; p < NP; ++p) { pt0[p] = (first + p) * kPassTokens; pL[p] = L; pcu[p] = c0; qd[p] = qp - pt0[p]; }
+        np = min(NP, (L + kPassTokens - 1) / kPassTokens - first);
+    } else {
+        int before = 0;                                       // segments of the sequences before this round of 64
+        for (int c = 0; c < a.batch; c += 64) {
+            const int bb = c + lane;
+            const int c0 = bb < a.batch ? cu[bb] : 0, Lb = bb < a.batch ? cu[bb + 1] - c0 : 0, qp = bb < a.batch ? q_pos[bb] : 0;
+            const int nb = (Lb + kPassTokens - 1) / kPassTokens;
+            int incl = nb;
+#pragma unroll
+            for (int d = 1; d < 64; d *= 2) {
+                const int t = __shfl_up(incl, d);
+                if (lane >= d) incl += t;
+            }
+            const int start = before + incl - nb;
+#pragma unroll
+            for (int p = 0; p < NP; ++p) {
+                const int s = first + p;
+                const unsigned long long hit = __ballot(s >= start && s < start + nb);
+                if (hit) {
+                    const int l = __builtin_ctzll(hit);
+                    pb[p] = c + l;
+                    pt0[p] = (s - __builtin_amdgcn_readlane(start, l)) * kPassTokens;
+                    pL[p] = __builtin_amdgcn_readlane(Lb, l);
+                    pcu[p] = __builtin_amdgcn_readlane(c0, l);
+                    qd[p] = __builtin_amdgcn_readlane(qp, l) - pt0[p];
+                    np = p + 1;
+                }
+            }
+            before += __builtin_amdgcn_readlane(incl, 63);
+            if (before >= first + NP) break;
+        }
+    }
+    if (np <= 0) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the blocks sent for above have landed
+        return;
+    }
+    unsigned chg = 1u;                                        // bit p: pass p is of another sequence than pass p - 1
+    bool neg = false;                                         // some distance is negative
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        if (p > 0 && p < np && pb[p] != pb[p - 1]) chg |= 1u << p;
+        if (p < np && qd[p] < kPassTokens - 1) neg = true;
+    }
+
+    const int n = lane & 15, gk = lane >> 4;
+    const int par = gk & 1, hi = gk >> 1;                     // par: half of the 8 elements; hi: set of 16 tokens
+    const int f = 4 * wave + (n >> 2);                        // fine position
+
+    // The tile's codes: every lane asks for what no other asks for, 8 bytes (M = 16: bytes 8 par .. + 7) or 16 (M = 32: block
+    // par) of its token of set hi; the lanes exchange the rest below.
+    constexpr int RAW = M / 8;
+    unsigned raw[NP][RAW];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        // tokens past the end of the sequence read zeros (the descriptor ends with the sequence): code 0, a valid row
+        const __amdgpu_buffer_rsrc_t rs = make_rsrc(key_codes + ((size_t)pcu[p] * a.Hkv + (size_t)g * pL[p]) * M, p < np ? (unsigned)pL[p] * M : 0u);
+        const unsigned at = (unsigned)(pt0[p] + f + kLo * ((n & 3) + 4 * hi)) * M + (M == 16 ? 8u : 16u) * par;
+        if (M == 16) {
+            const uint2_t c = __builtin_amdgcn_raw_buffer_load_b64(rs, at, 0, 0);
+            raw[p][0] = c[0]; raw[p][1] = c[1];
+        } else {
+            const uint4_t c = __builtin_amdgcn_raw_buffer_load_b128(rs, at, 0, 0);
+#pragma unroll
+            for (int i = 0; i < RAW; ++i) raw[p][i] = c[i & 3];
+        }
+    }
+
+    // What a slice needs besides the codebook: thread x < kAuxPieces sends for piece x.  The source of its piece of slice 0
+    // waits in LDS between the slices (bit 0 of a coarse factor's: take the conjugate, the row's distance is negative).
+    unsigned long long *aux_tab = reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(tab) + kAuxTabOff);
+    {
+        uintptr_t aux = 0;
+        if (tid < kAuxHi) {
+            aux = reinterpret_cast<uintptr_t>(tbl_lo + (size_t)(tid % kLo) * kJ + 2 * (tid / kLo));
+        } else if (tid < kAuxQ) {
+            const int x = tid - kAuxHi, p = x / (2 * kHiRows), row = x % (2 * kHiRows) / 2;
+            int D = 0;
+#pragma unroll
+            for (int k = 0; k < NP; ++k)
+                if (p == k) D = qd[k];
+            const int H = ((D + 1) >> kLoBits) - 8 + row;     // rows 0..8: what distances D - 511 .. D can reach
+            if (p < np) aux = reinterpret_cast<uintptr_t>(tbl_hi + (size_t)min(H < 0 ? -H : H, a.n_hi - 1) * kJ + 2 * (x & 1)) | (H < 0 ? 1u : 0u);
+        } else if (tid < kAuxPieces) {
+            const int x = tid - kAuxQ, per = a.q_bf16 ? 1 : 2;
+            const int p = x / (G * per), h = x / per % G, part = x % per;
+            int bs = 0;
+#pragma unroll
+            for (int k = 0; k < NP; ++k)
+                if (p == k) bs = pb[k];
+            if (p < np) aux = reinterpret_cast<uintptr_t>(q) + (((size_t)bs * a.Hq + (size_t)g * G + h) * kD * (a.q_bf16 ? 2 : 4) + part * 16);
+        }
+        if (tid < kAuxPieces) aux_tab[tid] = aux;
+    }
+    const bool q_odd = (reinterpret_cast<uintptr_t>(q) & 15u) != 0;
+    auto send_aux = [&](int sl, int buf) {
+        if (wave >= kAuxPieces / 64) return;
+        const int x = wave * 64 + fresh_lane();
+        const uintptr_t aux = aux_tab[x];
+        if (!aux) return;
+        const unsigned step = wave >= kAuxQ / 64 && a.q_bf16 ? 16u : 32u;
+        char *dst = reinterpret_cast<char *>(tab) + 2 * kBlockBytes + buf * kAuxBytes + x * 16;
+        if (neg && wave >= kAuxHi / 64 && wave < kAuxQ / 64) {  // the conjugate of the row of |H| needs a register
+            float4 e = *reinterpret_cast<const float4 *>((aux & ~(uintptr_t)1) + sl * step);
+            if (aux & 1) { e.y = -e.y; e.w = -e.w; }
+            *reinterpret_cast<float4 *>(dst) = e;
+        } else if (q_odd && wave >= kAuxQ / 64) {              // queries that are not 16-byte aligned
+            const uint16_t *e = reinterpret_cast<const uint16_t *>(aux + sl * step);
+            for (int k = 0; k < 8; ++k) reinterpret_cast<uint16_t *>(dst)[k] = e[k];
+        } else {
+            lds_dma16(reinterpret_cast<const void *>(aux + sl * step), (unsigned)(2 * kBlockBytes + buf * kAuxBytes + wave * 1024));
+        }
+    };
+    send_aux(s_begin, s_begin & 1);
+
+    // Selection operand of v_smfmac_f32_16x16x64_bf16 (first operand structured-sparse: two of every four
+    // consecutive k kept, 2-bit positions in an index register).  Its second operand takes two 16-byte pieces per
+    // lane, A (elements 0..7) and B (8..15); measured layout (micro-benchmark smfmac_layouts): logical k =
+    // 32 * (A | B) + 8 * (lane / 16) + element, and first-operand lane (row i, block q) covers k = 16 q .. 16 q + 15
+    // with stored slots 2 t, 2 t + 1 for its t-th group of four.  Rows 0..7 must add element i of the four lanes'
+    // A pieces, rows 8..15 element i - 8 of their B pieces: lane (i, q) is active when (i < 8) == (q < 2) and then
+    // keeps 1.0 at position e % 4 of groups e / 4 and 2 + e / 4 (e = i % 8); every other stored value is 0.0.
+    uint4_t sel = {0u, 0u, 0u, 0u};
+    unsigned sidx = 0x44444444u;  // default positions (0, 1) of every stored pair
+    {
+        const int e = n & 7;
+        if ((n < 8) == (gk < 2)) {
+            const int t = e >> 2, pos = e & 3, other = pos == 0 ? 1 : 0;
+            sel[t] = 0x00003f80u;        // slot 2 t      = 1.0, slot 2 t + 1 = 0.0
+            sel[2 + t] = 0x00003f80u;    // slot 4 + 2 t  = 1.0
+            const unsigned pair = (unsigned)pos | (unsigned)other << 2;
+            sidx = (sidx & ~(0xfu << (4 * t)) & ~(0xfu << (4 * (2 + t)))) | pair << (4 * t) | pair << (4 * (2 + t));
+            sidx = (sidx & 0xffffu) | sidx << 16;
+        }
+    }
+    const bf16x8_t selv = __builtin_bit_cast(bf16x8_t, sel);
+
+    // What a lane gathers, for tokens n of both sets: the 4 codebooks 8 par + (n + 4 hi + st) mod 8, st = 0..3, of every
+    // block of 16; the four lanes of a token cover the block.  In every group of lanes that the LDS checks
+    // against each other for bank conflicts the 16 pieces of one read then come from 16 different bank columns,
+    // whatever the codes.  xreg[st]: byte 0 = 16 * column read at step st, bytes 2 and 3 = 0 and 1; a byte permute splices the
+    // code in as byte 1 and byte 2 or 3 as byte 2, which yields the LDS byte address 65536 slot + 256 c + 16 col.
+    unsigned xreg[4];
+#pragma unroll
+    for (int st = 0; st < 4; ++st) xreg[st] = (unsigned)(8 * par + ((n + st + 4 * hi) & 7)) * 16u | 1u << 24;
+    unsigned rsel = 0u;  // byte selector that rotates 8 code bytes so that step st finds its code at byte st
+#pragma unroll
+    for (int x = 0; x < 4; ++x) rsel |= (unsigned)((x + n + 4 * hi) & 7) << (8 * x);
+
+    // ccall[p][v][blk]: the code bytes of steps 4 blk .. + 3 for the lane's token of set v, pass p
+    unsigned ccall[NP][2][NB];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        unsigned d[2][2 * NB];                                // both sets' tokens: bytes 8 par .. + 7 of every block of 16
+        unsigned own[2 * NB];
+        if (M == 16) {
+            own[0] = raw[p][0]; own[1] = raw[p][1];
+        } else {                                              // rows exchanged: halves of both blocks instead of one block
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                auto r = __builtin_amdgcn_permlane16_swap(raw[p][i], raw[p][(2 + i) % RAW], false, false);
+                own[i] = r[0];
+                own[(2 + i) % (2 * NB)] = r[1];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 2 * NB; ++i) {                    // lower half of the wavefront: set 0, upper half: set 1
+            auto r = __builtin_amdgcn_permlane32_swap(own[i], own[i], false, false);
+            d[0][i] = r[0];
+            d[1][i] = r[1];
+        }
+#pragma unroll
+        for (int v = 0; v < 2; ++v)
+#pragma unroll
+            for (int k = 0; k < NB; ++k) ccall[p][v][k] = __builtin_amdgcn_perm(d[v][2 * k + 1], d[v][2 * k], rsel);
+    }
+    if (wave == 0 && lane < NP) {                             // the segments, for the write-out
+        int4 s = make_int4(0, 0, 0, 0);
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+            if (lane == p) s = make_int4(pb[p], pt0[p], pL[p], pcu[p]);
+        reinterpret_cast<int4 *>(reinterpret_cast<char *>(tab) + kSegOff)[lane] = s;
+    }
+
+    constexpr int NPAIR = (NP + 1) / 2;
+    floatx4_t sc[NPAIR][NGRP];                               // pair k: 4 heads of the lane's token of pass 2 k + par
+#pragma unroll
+    for (int k = 0; k < NPAIR; ++k)
+#pragma unroll
+        for (int x = 0; x < NGRP; ++x) sc[k][x] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+
+    float zero = 0.f;
+    asm volatile("" : "+v"(zero));
+    uint4_t v[NBUF][2];
+    float qrow[NGRP][8];                                      // q' of the slice: head 4 x + n % 4, the 8 elements
+    unsigned ehi_at = 0u;                                     // LDS address of the lane's coarse factor in pass 0's rows
+    // where the lane finds its fine and coarse factor of pass 0's sequence, from the start of a buffer: bits 0..15, 16..31
+    unsigned at0;
+    {
+        const int D0 = qd[0], D1 = qd[NP > 1 ? 1 : 0], ln = fresh_lane(), fl = 4 * wave + (ln >> 2 & 3), Dl = ln >> 4 & 1 ? D1 : D0;
+        const int row = ((D0 - fl) >> kLoBits) - ((D0 + 1) >> kLoBits) + 8 - (ln & 3) - 4 * (ln >> 5);
+        at0 = (unsigned)((Dl - fl) & (kLo - 1)) * 16u | (unsigned)(kAuxHi + 2 * row + (ln >> 4 & 1)) << 20;
+    }
+    uint4_t stage[4];                                         // STAGE: the thread's pieces of a block on their way to LDS
+    auto fetch_block = [&](int sl, int blk) {
+        const uint4_t *p = reinterpret_cast<const uint4_t *>(src + ((size_t)sl * NB + blk) * kBlockBytes) + (wave * 64 + fresh_lane());
+#pragma unroll
+        for (int j = 0; j < 4; ++j) stage[j] = p[j * kSliceThreads];
+    };
+    auto store_block = [&](int blk) {
+        uint4_t *p = reinterpret_cast<uint4_t *>(tab) + blk * (kBlockBytes / 16) + (wave * 64 + fresh_lane());
+#pragma unroll
+        for (int j = 0; j < 4; ++j) p[j * kSliceThreads] = stage[j];
+    };
+    for (int sl = s_begin; sl < s_end; ++sl) {
+        const bool more = sl + 1 < s_end;
+        const int buf = sl & 1;
+        const unsigned aux0 = (unsigned)(2 * kBlockBytes + buf * kAuxBytes);
+        // this slice (M = 32: its block 0; block 1 may still be on its way) and its phase factors and queries are in LDS,
+        // and everyone is done with what the next sends overwrite
+        if (M == 16 || sl == s_begin) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)" ::: "memory");
+        bare_barrier();
+        // an opaque copy per slice: the gather addresses made from these must not be hoisted out of the slice loop (they would
+        // take several registers per pass)
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < NB; ++j) asm volatile("" : "+v"(ccall[p][i][j]));
+        const unsigned slot_sel = M == 16 ? (unsigned)(2 + buf) << 16 : 0u;
+        auto issue = [&](int p, int st) {
+            const int blk = st / 4;
+            const unsigned psel = (0x0c000000u | (unsigned)(4 + st % 4) << 8) | (M == 16 ? slot_sel : (unsigned)(2 + blk) << 16);
+#pragma unroll
+            for (int ab = 0; ab < 2; ++ab)
+                v[(p * NST + st) % NBUF][ab] = lds_read_b128(__builtin_amdgcn_perm(ccall[p][ab][blk], xreg[st % 4], psel));
+        };
+        // q' = q conj(E_lo) for the pair of passes k (Re(conj(q) a E_hi E_lo) = Re(conj(q') a E_hi))
+        auto fold = [&](int k) {
+            const int ln = fresh_lane(), odd = ln >> 4 & 1;
+            unsigned lo = aux0 + (at0 & 0xffffu);
+            if (k > 0) {
+                const int d0 = qd[2 * k], d1 = qd[2 * k + 1 < NP ? 2 * k + 1 : 2 * k], D = odd ? d1 : d0;
+                lo = aux0 + (unsigned)((D - 4 * wave - (ln >> 2 & 3)) & (kLo - 1)) * 16u;
+            }
+            const uint4_t e0 = lds_read_b128(lo), e1 = lds_read_b128(lo + kLo * 16u);
+#pragma unroll
+            for (int x = 0; x < NGRP; ++x) {
+                const int h = 4 * x + (ln & 3);
+                const unsigned at = aux0 + (unsigned)(kAuxQ + ((2 * k + odd) * G + h) * (a.q_bf16 ? 1 : 2)) * 16u;
+                float qv[8];
+                if (a.q_bf16) {
+                    const uint4_t w = lds_read_b128(at);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const unsigned u = w[r];
+                        qv[2 * r] = bf16_lo(u);
+                        qv[2 * r + 1] = bf16_hi(u);
+                    }
+                } else {
+                    const uint4_t w0 = lds_read_b128(at), w1 = lds_read_b128(at + 16u);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const unsigned u0 = w0[r], u1 = w1[r];
+                        qv[r] = __builtin_bit_cast(float, u0);
+                        qv[4 + r] = __builtin_bit_cast(float, u1);
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const unsigned lxr = u < 2 ? e0[2 * u] : e1[2 * u - 4], lyr = u < 2 ? e0[2 * u + 1] : e1[2 * u - 3];
+                    const float lx = __builtin_bit_cast(float, lxr), ly = __builtin_bit_cast(float, lyr);
+                    const float qx = qv[2 * u], qy = qv[2 * u + 1];
+                    qrow[x][2 * u] = NGRP == 1 && h >= G ? 0.f : qx * lx + qy * ly;
+                    qrow[x][2 * u + 1] = NGRP == 1 && h >= G ? 0.f : qy * lx - qx * ly;
+                }
+            }
+        };
+        // the lane's place among the coarse factors of a pass whose first token is D away from its query
+        auto hi_row = [&](int D) {
+            const int ln = fresh_lane();
+            const int row = ((D - 4 * wave - (ln >> 2 & 3)) >> kLoBits) - ((D + 1) >> kLoBits) + 8 - (ln & 3) - 4 * (ln >> 5);
+            ehi_at = aux0 + (unsigned)(kAuxHi + 2 * row + (ln >> 4 & 1)) * 16u;
+        };
+        // the lane's sub-space u (of two), rotated by the coarse phase factor: A E_hi
+        auto rotate = [&](int u, const floatx4_t &acc, const uint4_t &eh, float *val) {
+            const unsigned hxr = eh[2 * u], hyr = eh[2 * u + 1];
+            const float ex = __builtin_bit_cast(float, hxr), ey = __builtin_bit_cast(float, hyr);
+            const float ax = acc[2 * u], ay = acc[2 * u + 1];
+            val[2 * u] = ax * ex - ay * ey;
+            val[2 * u + 1] = ax * ey + ay * ex;
+        };
+        floatx4_t acc_e, acc_o;                               // gather sums of the pair's even and odd pass
+        uint4_t eh_e, eh_o;                                   // their coarse phase factors
+        float xy[8];                                          // even pass: rotated elements in 0..3; then the lane's 8 elements
+        // 2. and 3. for a pair of passes, in NST parts that run between the steps of the next pass
+        auto finish = [&](int k, int st) {
+            if (st == 0) {
+                float odd[4];
+                rotate(0, acc_o, eh_o, odd);
+                rotate(1, acc_o, eh_o, odd);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    auto s = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, xy[r]), __builtin_bit_cast(unsigned, odd[r]), false, false);
+                    const unsigned s0 = s[0], s1 = s[1];
+                    xy[r] = __builtin_bit_cast(float, s0);
+                    xy[4 + r] = __builtin_bit_cast(float, s1);
+                }
+            } else {
+#pragma unroll
+                for (int r = (st - 1) * 8 / (NST - 1); r < st * 8 / (NST - 1); ++r)
+#pragma unroll
+                    for (int x = 0; x < NGRP; ++x) sc[k][x] = __builtin_amdgcn_mfma_f32_4x4x1f32(qrow[x][r], xy[r], sc[k][x], 0, 0, 0);
+            }
+        };
+        // 1. the gather-sum of pass p on the matrix cores, with a part of other work after every step
+        auto pass = [&](auto pc, floatx4_t &acc, uint4_t &eh, auto part) __attribute__((always_inline)) {
+            constexpr int p = decltype(pc)::value;
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_setprio(3 - p * 4 / NP);       // (wavefronts that are behind go first)
+            if (p == 0) ehi_at = aux0 + (at0 >> 16);
+            else if (__builtin_expect(chg >> p & 1u, 0)) hi_row(qd[p]);
+            eh = lds_read_b128(ehi_at + (unsigned)(p * 2 * kHiRows * 16));
+            // What the next slice needs sets out spread over this one's passes (a burst of sends fills the memory pipe's queue and
+            // stops the wavefronts): its codebook (M = 16) or the registers' share of it, phase factors and queries
+            if (more) {
+                if (M == 16) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (p == j * (NP - 1) / 5) send_part(sl + 1, 0, buf ^ 1, j);
+                }
+                if (p == (M == 16 ? 4 * (NP - 1) / 5 : (NP - 1) / 3)) send_aux(sl + 1, buf ^ 1);
+                if (STAGE && p == (NP - 1) / 2) fetch_block(sl + 1, 0);
+            }
+            // (cleared by a small matrix instruction: the compiler makes five moves of a vector of zeros)
+            acc = __builtin_amdgcn_mfma_f32_4x4x1f32(zero, zero, floatx4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+            for (int st = 0; st < NST; ++st) {
+                const uint4_t pa = v[(p * NST + st) % NBUF][0], pb2 = v[(p * NST + st) % NBUF][1];
+                const uint8v_t both = {pa[0], pa[1], pa[2], pa[3], pb2[0], pb2[1], pb2[2], pb2[3]};
+                acc = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(selv, __builtin_bit_cast(bf16x16_t, both), acc, (int)sidx, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (M == 32 && p == 0 && st + NBUF == 4) {
+                    // block 1 of this slice: what was fetched during the last pass of the slice before can be put in place now
+                    // that everyone has left that slice; or what was sent for has arrived
+                    if (STAGE && sl > s_begin) {
+                        store_block(1);
+                        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                    } else {
+                        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                    }
+                    bare_barrier();
+                }
+                if (st + NBUF < NST) issue(p, st + NBUF);
+                else if (p + 1 < NP) issue(p + 1 < NP ? p + 1 : p, st + NBUF - NST);  // (after the last pass: of codes 0, not used)
+                __builtin_amdgcn_sched_barrier(0);
+                if (M == 32 && p == NP - 1 && st == 3 && more) {
+                    // everyone has read the last pieces of block 0: the next slice's may come
+                    bare_barrier();
+                    if (STAGE) {
+                        store_block(0);
+                        fetch_block(sl + 1, 1);
+                    } else {
+                        send_block(sl + 1, 0, 0);
+                    }
+                }
+                if (M == 32 && !STAGE && p == NP - 1 && st == 7 && more) {
+                    bare_barrier();
+                    send_block(sl + 1, 1, 1);
+                }
+                part(st);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        auto pair = [&](auto kc) __attribute__((always_inline)) {
+            constexpr int k = decltype(kc)::value;
+            pass(std::integral_constant<int, 2 * k>{}, acc_e, eh_e, [&](int st) { if (DELAY && k > 0) finish(k > 0 ? k - 1 : 0, st); });
+            if (k == 0 || (chg >> (2 * k - 1) & 7u)) fold(k);
+            if constexpr (2 * k + 1 < NP) {
+                pass(std::integral_constant<int, 2 * k + 1>{}, acc_o, eh_o, [&](int st) { if (st < 2) rotate(st, acc_e, eh_e, xy); });
+            } else {
+                rotate(0, acc_e, eh_e, xy);
+                rotate(1, acc_e, eh_e, xy);
+                acc_o = floatx4_t{0.f, 0.f, 0.f, 0.f};
+                eh_o = uint4_t{0u, 0u, 0u, 0u};
+            }
+            if (!DELAY || k == NPAIR - 1) {
+#pragma unroll
+                for (int st = 0; st < NST; ++st) finish(k, st);
+            }
+        };
+#pragma unroll
+        for (int st = 0; st < NBUF; ++st) issue(0, st);
+        pair(std::integral_constant<int, 0>());
+        if constexpr (NPAIR > 1) pair(std::integral_constant<int, (NPAIR > 1 ? 1 : 0)>());
+        if constexpr (NPAIR > 2) pair(std::integral_constant<int, (NPAIR > 2 ? 2 : 0)>());
+        if constexpr (NPAIR > 3) pair(std::integral_constant<int, (NPAIR > 3 ? 3 : 0)>());
+    }
+
+    // Write-out.  A wavefront's tokens are scattered over the pass (4 fine positions x 8 coarse rows), so the logits of
+    // four heads at a time are transposed through the now idle codebook blocks, [head][pass][coarse row][68] floats (rows
+    // padded from 64: the 64 lanes of a write fall on 64 different banks), and leave as runs of 256 consecutive tokens
+    // per wavefront, whose (max, sum of exp) are taken on the way.  A slice group leaves partial logits in its own array;
+    // the statistics then come from k_score_combine.
+    float *stg = reinterpret_cast<float *>(tab);
+    float2 *wst = reinterpret_cast<float2 *>(reinterpret_cast<char *>(tab) + kWstOff);
+    const int4 *segs = reinterpret_cast<const int4 *>(reinterpret_cast<const char *>(tab) + kSegOff);
+    float *dst0 = scores + (size_t)eg * a.part_stride;
+    const int ln = fresh_lane(), wpar = ln >> 4 & 1, wf = 4 * wave + (ln >> 2 & 3), wrow = (ln & 3) + 4 * (ln >> 5);
+    const int wp = wave >> 1, rel = ((wave & 1) * 64 + ln) * 4;  // the pass and the 4 tokens this thread writes
+#pragma unroll
+    for (int x = 0; x < NGRP; ++x) {
+        __syncthreads();  // the last slice (x = 0) or the previous group's logits have been read by everyone
+#pragma unroll
+        for (int k = 0; k < NPAIR; ++k)
+            if (2 * k < np) {
+#pragma unroll
+                for (int h = 0; h < 4; ++h)
+                    if (2 * k + wpar < NP) stg[((h * NP + 2 * k + wpar) * 8 + wrow) * 68 + wf] = sc[k][x][h] * a.scale;
+            }
+        __syncthreads();
+        if (wp < np) {
+            const int4 sg = segs[wp];
+            const int L = __builtin_amdgcn_readfirstlane(sg.z), t0 = __builtin_amdgcn_readfirstlane(sg.y);
+            const int c0 = __builtin_amdgcn_readfirstlane(sg.w);
+            const int tok = t0 + rel;
+#pragma unroll
+            for (int h = 0; h < 4; ++h) {
+                if (4 * x + h >= G) break;
+                const float4 w = *reinterpret_cast<const float4 *>(stg + ((h * NP + wp) * 8 + (rel >> kLoBits)) * 68 + (rel & (kLo - 1)));
+                float *dst = dst0 + (size_t)c0 * a.Hq + (size_t)(g * G + 4 * x + h) * L + tok;
+                if (tok + 3 < L) {
+                    typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));  // L need not be a multiple of 4
+                    const f4u ww = {w.x, w.y, w.z, w.w};
+                    *reinterpret_cast<f4u *>(dst) = ww;
+                } else {
+                    if (tok < L) dst[0] = w.x;
+                    if (tok + 1 < L) dst[1] = w.y;
+                    if (tok + 2 < L) dst[2] = w.z;
+                }
+                if (a.groups == 1) {
+                    const float w0 = tok < L ? w.x : -INFINITY, w1 = tok + 1 < L ? w.y : -INFINITY;
+                    const float w2 = tok + 2 < L ? w.z : -INFINITY, w3 = tok + 3 < L ? w.w : -INFINITY;
+                    const float m = wave_max(fmaxf(fmaxf(w0, w1), fmaxf(w2, w3)));
+                    float l = 0.f;
+                    if (m != -INFINITY)
+                        l = __builtin_amdgcn_exp2f((w0 - m) * kLog2e) + __builtin_amdgcn_exp2f((w1 - m) * kLog2e) +
+                            __builtin_amdgcn_exp2f((w2 - m) * kLog2e) + __builtin_amdgcn_exp2f((w3 - m) * kLog2e);
+                    l = wave_sum(l);
+                    if (ln == 0) wst[wave * 8 + 4 * x + h] = make_float2(m, l);
+                }
+            }
+        }
+    }
+    if (a.groups == 1) {
+        __syncthreads();
+        const int x = wave * 64 + ln;
+        if (x < np * G) {
+            const int p = x / G, h = x % G;
+            const int4 sg = segs[p];
+            const float2 s0 = wst[2 * p * 8 + h], s1 = wst[(2 * p + 1) * 8 + h];  // (the first half is never empty)
+            float l = s0.y;
+            const float m = fmaxf(s0.x, s1.x);
+            l *= __builtin_amdgcn_exp2f((s0.x - m) * kLog2e);
+            if (s1.x != -INFINITY) l += s1.y * __builtin_amdgcn_exp2f((s1.x - m) * kLog2e);
+            sstat[((size_t)sg.x * a.Hq + (size_t)g * G + h) * a.nstat + sg.y / kPassTokens] = make_float2(m, l);
+        }
+    }
+}
+
 // x + y after exchanging the odd 16-lane rows of x with the even rows of y (row r of the result:
 // r even: x[r] + x[r+1], r odd: y[r-1] + y[r]), and the same with 32-lane halves.
 __device__ __forceinline__ float swap16_add(float x, float y)
@@ -531,53 +1143,46 @@ __device__ __forceinline__ float swap32_add(float x, float y)
     return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
 }
 
-// The tile's (max, sum of exp) per head, and the logits to memory, for the slice-streaming score kernels.
-// sc[p][x][o] of lane (n, gk) is the logit of head 4 x + gk (M = 16) or 4 x + 2 o + par (M = 32) for the lane's token
-// of pass p, tb + p * 4 * 64 * (sets of the pass).  The tokens of a wavefront are scattered over the tile (4 fine
-// positions x 4 coarse rows per pass), so the logits of four heads at a time are transposed through the now idle
-// slice area of LDS (stg), [head][coarse row][68] floats (rows padded from 64, heads offset by 16 banks: the writes
-// of a wavefront fall on 32 different banks), and leave as runs of 256 consecutive tokens per wavefront.
+// The tile's (max, sum of exp) per head, and the logits to memory, for the pair-code score kernel.
+// sc[p][x] of lane (n, gk) is the logit of head 4 x + gk for the lane's token of pass p, tb + p * 4 * 64.  The tokens
+// of a wavefront are scattered over the tile (4 fine positions x 4 coarse rows per pass), so the logits of four heads
+// at a time are transposed through the now idle slice area of LDS (stg), [head][coarse row][68] floats (rows padded
+// from 64, heads offset by 16 banks: the writes of a wavefront fall on 32 different banks), and leave as runs of 256
+// consecutive tokens per wavefront.
 // stat_dst: where the tile's statistics of head 0 go (stride nsplit per head), or null.
-template <int M, int G, int TPT, int NPASS, int NGRP, int NOUT>
-__device__ __forceinline__ void write_tile_logits(const float (&sc)[NPASS][NGRP][NOUT], float *stg, float2 (*wstat)[G],
+template <int G, int TPT, int NPASS, int NGRP>
+__device__ __forceinline__ void write_tile_logits(const float (&sc)[NPASS][NGRP], float *stg, float2 (*wstat)[G],
                                                   float *srow, float2 *stat_dst, int nsplit, int tb, int t0, int L)
 {
     constexpr int TILE = TPT * kSliceThreads, NW = kSliceThreads / 64;
-    constexpr int PSTRIDE = 4 * kLo * (M == 16 ? 1 : 2);
+    constexpr int PSTRIDE = 4 * kLo;
     constexpr int SROW = 68, SHEAD = (TILE / kLo) * SROW + 16;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int n = lane & 15, gk = lane >> 4, par = gk & 1, set = gk >> 1;
+    const int n = lane & 15, gk = lane >> 4;
     const int rel0 = tb - t0;
 #pragma unroll
     for (int x = 0; x < NGRP; ++x) {
+        const int head = 4 * x + gk;
+        float mx = -INFINITY;
 #pragma unroll
-        for (int o = 0; o < NOUT; ++o) {
-            const int head = 4 * x + (M == 16 ? gk : 2 * o + par);
-            float mx = -INFINITY;
-#pragma unroll
-            for (int p = 0; p < NPASS; ++p) {
-                const int tok = tb + p * PSTRIDE;
-                if (head < G && tok < L) mx = fmaxf(mx, sc[p][x][o]);
-            }
-            const float wm = head_lanes_max<M>(mx);
-            float l = 0.f;
-#pragma unroll
-            for (int p = 0; p < NPASS; ++p) {
-                const int tok = tb + p * PSTRIDE;
-                if (head < G && tok < L) l += __builtin_amdgcn_exp2f((sc[p][x][o] - wm) * kLog2e);
-            }
-            l = head_lanes_sum<M>(l);
-            if (n == 0 && head < G && (M == 16 || set == 0)) wstat[wave][head] = make_float2(wm, l);
+        for (int p = 0; p < NPASS; ++p) {
+            const int tok = tb + p * PSTRIDE;
+            if (head < G && tok < L) mx = fmaxf(mx, sc[p][x]);
         }
+        const float wm = row_max16(mx);
+        float l = 0.f;
+#pragma unroll
+        for (int p = 0; p < NPASS; ++p) {
+            const int tok = tb + p * PSTRIDE;
+            if (head < G && tok < L) l += __builtin_amdgcn_exp2f((sc[p][x] - wm) * kLog2e);
+        }
+        l = row_sum16(l);
+        if (n == 0 && head < G) wstat[wave][head] = make_float2(wm, l);
         __syncthreads();  // the last slice (x = 0) or the previous group's logits have been read by everyone
 #pragma unroll
-        for (int o = 0; o < NOUT; ++o) {
-            const int hl = M == 16 ? gk : 2 * o + par;
-#pragma unroll
-            for (int p = 0; p < NPASS; ++p) {
-                const int rel = rel0 + p * PSTRIDE;
-                stg[hl * SHEAD + (rel >> kLoBits) * SROW + (rel & (kLo - 1))] = sc[p][x][o];
-            }
+        for (int p = 0; p < NPASS; ++p) {
+            const int rel = rel0 + p * PSTRIDE;
+            stg[gk * SHEAD + (rel >> kLoBits) * SROW + (rel & (kLo - 1))] = sc[p][x];
         }
         __syncthreads();
 #pragma unroll
@@ -611,479 +1216,6 @@ __device__ __forceinline__ void write_tile_logits(const float (&sc)[NPASS][NGRP]
         }
         stat_dst[(size_t)tid * nsplit] = make_float2(m, l);
     }
-}
-
-// Slice-streaming score kernel with both contractions on the matrix cores (Eq. new_attention,
-// re-bracketed: gather-sum the codeword blocks first, rotate once, contract with the G queries).
-// Works on the key codebook repacked by k_prep: slice sl (DS = 256 / M consecutive elements of
-// every codeword) sits in LDS as tab[P][M][K] 16-byte pieces while all tokens of the tile pass by.
-//
-// Tokens.  A tile of TILE = 1024 TPT tokens is 64 fine positions (token mod 64) x TILE / 64 coarse rows.  A
-// wavefront owns 4 fine positions; in a pass, lane n of its 16 token lanes takes fine position n / 4 and
-// coarse row n % 4 of the pass's block of rows (M = 32: a second set of 16 tokens, 4 rows further on).
-// So the 4 lanes of a 4-lane block, and all passes of a lane, are whole coarse rows apart: they share the
-// fine phase factor E_lo of the relative position 64 H + lo, which is therefore folded into the block's
-// query operand once per slice, and a pass only rotates by the coarse factor E_hi.
-//
-// Codes.  The tile's codes are read once and stay in registers for all slices, already in the byte order
-// of the lane's gather steps (M = 16: streamed in during the first slice; see STREAM0).
-//
-// Per slice and pass:
-//  1. Gather-sum: v_smfmac_f32_16x16x64_bf16 (structured-sparse first operand) with a constant 0/1
-//     selection matrix as first operand and 128 gathered pieces as second: lane n + 16 g supplies two
-//     pieces, A and B, for column n.  Products with 1.0 are exact, so this is the plain fp32 sum of the
-//     M codeword slices.  Rows 0..7 of the result are the elements of the four lanes' A pieces added up,
-//     rows 8..15 those of their B pieces:
-//       M = 16 (two planes): a pass covers 16 tokens; A / B = plane 0 / plane 1 of one codebook;
-//               lane (n, g) receives elements 4g .. 4g+3 of the slice for its token;
-//       M = 32 (one plane):  a pass covers 32 tokens in two sets; A / B = the same codebook for the
-//               lane's token of set 0 and of set 1; lane (n, g) receives elements 4 (g & 1) .. +3 for
-//               its token of set g >> 1.
-//     The LDS reads of a group of steps are issued right after the matrix instructions that consumed the
-//     group's registers, so the first reads of the next pass travel while this pass is finished.
-//  2. Each lane rotates its two (x, y) sub-spaces by the coarse phase factor of its token.
-//  3. Contraction with the queries: four v_mfma_f32_4x4x1_16b_f32 per group of 4 heads.  In each
-//     block of 4 lanes, lane i supplies q'[head i][the block's r-th element] (q' = q conj(E_lo)) and every
-//     lane its own rotated r-th element, so register i of a lane receives the partial logit of head i for
-//     the lane's own token over the lane's 4 elements.  The 4 (M = 16) or 2 (M = 32) lanes of a token
-//     are then combined with row / half swaps so that each keeps the total of one (two) heads:
-//     lane (n, g) holds head g of its token (M = 16), heads g & 1 and 2 + (g & 1) (M = 32).
-// On gfx950 the vector and matrix instructions of a SIMD do not overlap (measured again on this kernel:
-// interleaving the next pass's gather-sum with this pass's vector work changes nothing), so a pass costs the
-// sum of its instruction issue: 4 (8) sparse MFMA of 16 clk, 4 small ones of 8 per head group, ~28 vector
-// instructions.
-//
-// Short contexts: a launch may cut every tile along the slices as well (SliceDims::groups workgroups per
-// tile); each then writes partial logits, which k_score_combine adds.
-template <int M, int G, int TPT>
-__global__ __launch_bounds__(kSliceThreads) void k_score_mfma(
-    const void *__restrict__ q, const uint8_t *__restrict__ key_codes, const uint4 *__restrict__ packed,
-    const int32_t *__restrict__ cu, const int32_t *__restrict__ q_pos, const float2 *__restrict__ tbl_hi,
-    const float2 *__restrict__ tbl_lo, float *__restrict__ scores, float2 *__restrict__ sstat, const SliceDims a)
-{
-    constexpr int DS = 256 / M;          // elements per slice (16 or 8)
-    constexpr int NJ = DS / 2;           // sub-spaces per slice
-    constexpr int P = DS / 8;            // 16-byte planes per slice
-    constexpr int S = kD / DS;           // slices
-    constexpr int TILE = TPT * kSliceThreads;
-    constexpr int NW = kSliceThreads / 64;
-    constexpr int SETS = M == 16 ? 1 : 2;                     // 16-token sets per wavefront pass
-    constexpr int NPASS = TILE / (16 * SETS * NW);
-    constexpr int PARTS = NJ / 2;                             // 16-byte (two sub-space) parts of a slice's phase rows
-    constexpr int NHR = TILE / kLo + 1;                       // coarse phase rows a tile can touch
-    constexpr int NGRP = (G + 3) / 4;                         // groups of 4 heads (padded with zero queries)
-    constexpr int NOUT = M == 16 ? 1 : 2;                     // heads per group whose totals a lane keeps
-    constexpr int CW = M / 8;                                 // code dwords a lane needs per token
-    static_assert(NPASS % 2 == 0, "code double-buffer parity assumes an even number of passes");
-    extern __shared__ __attribute__((aligned(16))) uint4 tab[];  // [2][K][16] 16-byte pieces, then the phase factors
-    float4 *elo = reinterpret_cast<float4 *>(tab + kSliceBytes / 16);  // [PARTS][64]  exp(i theta_j lo), this slice's j
-    float4 *ehi = elo + PARTS * kLo;                                   // [NHR][PARTS] exp(i theta_j 64 H), H = Hmin + row
-    // the slice sits at LDS address 0 (no static LDS in this kernel), so gather addresses need no base added
-    float2(*wstat)[G] = reinterpret_cast<float2(*)[G]>(reinterpret_cast<char *>(tab) + kSliceBytes + 2 * kPhaseBytes);  // [NW][G]
-
-    int id = blockIdx.x;
-    const int g = id % a.Hkv;
-    id /= a.Hkv;
-    const int tile = id % a.nsplit;
-    id /= a.nsplit;
-    const int eg = id % a.groups;                             // which group of slices (0 when tiles are not cut along them)
-    const int b = id / a.groups;
-    const int s_begin = eg * (S / a.groups), s_end = s_begin + S / a.groups;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // The first slice of the head's codebook depends on nothing but the workgroup index: it is requested before the
-    // sequence's bounds are even known, so that its (cold) fetch, that of the bounds and that of the tile's codes
-    // overlap.  Later slices are fetched into the same registers while the last pass of the current one finishes (its
-    // gather registers are dead by then).
-    constexpr int PIECES = P * M * kK;
-    constexpr int PPT = PIECES / kSliceThreads;
-    const uint4 *src = packed + (size_t)g * S * P * M * kK;
-    const __amdgpu_buffer_rsrc_t src_rs = make_rsrc(src, (unsigned)S * PIECES * 16u);
-    uint4_t stage[PPT];
-    auto fetch_slice = [&](int sl) {
-        // the slice index is the same in every lane; said so explicitly, or the loads may be wrapped in a loop over
-        // the distinct values of what the compiler holds in a vector register
-        const unsigned soff = __builtin_amdgcn_readfirstlane((unsigned)sl * (PIECES * 16u));
-#pragma unroll
-        for (int x = 0; x < PPT; ++x)
-            stage[x] = __builtin_amdgcn_raw_buffer_load_b128(src_rs, (unsigned)(x * kSliceThreads + tid) * 16u, soff, 0);
-    };
-    constexpr bool PREFETCH = !(M == 32 && G == 8 && TPT == 4);  // that instantiation has no registers to spare
-    if (PREFETCH) fetch_slice(s_begin);
-    const int cu0 = cu[b];
-    const int L = cu[b + 1] - cu0;
-    const int t0 = tile * TILE;
-    if (t0 >= L) return;
-    const int n = lane & 15, gk = lane >> 4;
-    const int par = gk & 1;                                   // odd / even codebook of a gather step
-    const int set = gk >> 1;                                  // M = 32: which 16-token set the lane gathers for
-    const int el = M == 16 ? 4 * gk : 4 * par;                // first of the lane's 4 slice elements
-    const int qpos = q_pos[b];
-    const uint8_t *codes = key_codes + ((size_t)cu0 * a.Hkv + (size_t)g * L) * M;
-    const __amdgpu_buffer_rsrc_t cd_rs = make_rsrc(codes, (unsigned)L * M);
-    const unsigned qesz = a.q_bf16 ? 2u : 4u;
-    const __amdgpu_buffer_rsrc_t q_rs =
-        make_rsrc(static_cast<const char *>(q) + ((size_t)b * a.Hq + (size_t)g * G) * kD * qesz, (unsigned)G * kD * qesz);
-
-    // Selection operand of v_smfmac_f32_16x16x64_bf16 (first operand structured-sparse: two of every four
-    // consecutive k kept, 2-bit positions in an index register).  Its second operand takes two 16-byte pieces per
-    // lane, A (elements 0..7) and B (8..15); measured layout (micro-benchmark smfmac_layouts): logical k =
-    // 32 * (A | B) + 8 * (lane / 16) + element, and first-operand lane (row i, block q) covers k = 16 q .. 16 q + 15
-    // with stored slots 2 t, 2 t + 1 for its t-th group of four.  Rows 0..7 must add element i of the four lanes'
-    // A pieces, rows 8..15 element i - 8 of their B pieces: lane (i, q) is active when (i < 8) == (q < 2) and then
-    // keeps 1.0 at position e % 4 of groups e / 4 and 2 + e / 4 (e = i % 8); every other stored value is 0.0.
-    uint4_t sel = {0u, 0u, 0u, 0u};
-    unsigned sidx = 0x44444444u;  // default positions (0, 1) of every stored pair
-    {
-        const int e = n & 7;
-        if ((n < 8) == (gk < 2)) {
-            const int t = e >> 2, pos = e & 3, other = pos == 0 ? 1 : 0;
-            sel[t] = 0x00003f80u;        // slot 2 t      = 1.0, slot 2 t + 1 = 0.0
-            sel[2 + t] = 0x00003f80u;    // slot 4 + 2 t  = 1.0
-            const unsigned pair = (unsigned)pos | (unsigned)other << 2;
-            sidx = (sidx & ~(0xfu << (4 * t)) & ~(0xfu << (4 * (2 + t)))) | pair << (4 * t) | pair << (4 * (2 + t));
-            sidx = (sidx & 0xffffu) | sidx << 16;
-        }
-    }
-    const bf16x8_t selv = __builtin_bit_cast(bf16x8_t, sel);
-    // as first operand of the query contraction the lane supplies head 4 grp + n % 4; rows past the last
-    // head read beyond the end of the buffer, i.e. zero
-    const unsigned q_off = (unsigned)(n & 3) * kD + (unsigned)el;  // in elements
-
-    float sc[NPASS][NGRP][NOUT];
-#pragma unroll
-    for (int p = 0; p < NPASS; ++p)
-#pragma unroll
-        for (int x = 0; x < NGRP; ++x)
-#pragma unroll
-            for (int o = 0; o < NOUT; ++o) sc[p][x][o] = 0.f;
-
-    // What a lane gathers (gk = (hi, par)):
-    //   M = 16: for its own token the 4 codebooks 8 par + (n + 4 hi + st) mod 8, st = 0..3, piece A from plane 0 and
-    //           piece B from plane 1 of each: the four lanes of a token cover its 16 codebooks in 4 instructions;
-    //   M = 32: for tokens n (piece A) and n + 16 (piece B) of the pass the 8 codebooks 16 hi + 8 par + (n + st) mod 8.
-    // In every group of lanes that the LDS checks against each other for bank conflicts the 16 pieces of one read
-    // then come from 16 different bank columns, whatever the codes.  xreg[st]: byte 0 = 16 * column read at step
-    // st, byte 2 = 64 KiB block (M = 16: 0, and byte 3 = 1 for plane 1; M = 32: hi); a byte permute splices the code
-    // in as byte 1, which yields the LDS byte address 65536 blk + 256 c + 16 col in one instruction.
-    const int hi = gk >> 1;
-    constexpr int NST = M == 16 ? 4 : 8;  // gather steps = sparse matrix instructions per pass
-    unsigned xreg[NST];
-#pragma unroll
-    for (int st = 0; st < NST; ++st)
-        xreg[st] = (unsigned)(8 * par + ((n + st + (M == 16 ? 4 * hi : 0)) & 7)) * 16u | (M == 16 ? 1u << 24 : (unsigned)hi << 16);
-    // byte selectors that rotate 8 code bytes so that step st finds its code at byte st
-    unsigned rsel_lo = 0u, rsel_hi = 0u;
-#pragma unroll
-    for (int x = 0; x < 4; ++x) {
-        rsel_lo |= (unsigned)((x + n + (M == 16 ? 4 * hi : 0)) & 7) << (8 * x);
-        rsel_hi |= (unsigned)((x + 4 + n) & 7) << (8 * x);
-    }
-
-    // tb is the lane's token of pass 0 (the one whose logits it ends up with; pass p: tb + p PSTRIDE); it is re-read
-    // through an opaque copy in every slice so that nothing that depends on a token index (table offsets) is hoisted
-    // out of the slice loop.  M = 32: the lane gathers for the set-0 token tb - 256 set and the set-1 token 256 further.
-    int tb = t0 + 4 * wave + (n >> 2) + kLo * ((n & 3) + (M == 16 ? 0 : 4 * set));
-    constexpr int PSTRIDE = 4 * kLo * SETS;  // tokens between two passes of a lane: a whole number of coarse rows
-    // byte offset of the codes the lane gathers in pass 0 (M = 32: of the first of its two tokens, the second is
-    // 4 coarse rows further on); refreshed with tb in every slice
-    unsigned code_off = (unsigned)(tb - (M == 16 ? 0 : 4 * kLo * set)) * M + (M == 16 ? 8u * par : 16u * hi + 8u * par);
-    auto fetch_codes = [&](int p, unsigned(&dst)[CW]) {
-        // tokens past the end of the sequence read zeros (the descriptor ends with the sequence): code 0, a valid row
-        if (M == 16) {  // bytes 8 par .. + 7 of the token's codes
-            const uint2_t c2 = __builtin_amdgcn_raw_buffer_load_b64(cd_rs, code_off + (unsigned)(p * PSTRIDE * M), 0, 0);
-            dst[0] = c2[0]; dst[1] = c2[1];
-        } else {        // bytes 16 hi + 8 par .. + 7 of both tokens
-#pragma unroll
-            for (int v = 0; v < 2; ++v) {
-                const uint2_t c2 = __builtin_amdgcn_raw_buffer_load_b64(cd_rs, code_off + (unsigned)((p * PSTRIDE + 4 * kLo * v) * M), 0, 0);
-                dst[2 * v + 0] = c2[0]; dst[2 * v + 1] = c2[1];
-            }
-        }
-    };
-    // cc[v][h]: rotated code bytes 4 h .. 4 h + 3 of token v (M = 16: one token, steps 0..3 only): what the gather
-    // addresses of a pass are made from.
-    constexpr int CV = M == 16 ? 1 : 2;
-    auto make_cc = [&](const unsigned(&c)[CW], unsigned(&cc)[CV][CV]) {
-        if (M == 16) {
-            cc[0][0] = __builtin_amdgcn_perm(c[1], c[0], rsel_lo);
-        } else {
-#pragma unroll
-            for (int v = 0; v < 2; ++v) {
-                cc[v][0] = __builtin_amdgcn_perm(c[2 * v + 1], c[2 * v], rsel_lo);
-                cc[v][CV - 1] = __builtin_amdgcn_perm(c[2 * v + 1], c[2 * v], rsel_hi);
-            }
-        }
-    };
-    // The codes of the whole tile are read ONCE and stay in registers, in gather order (ccall[p] = cc of pass p), for
-    // all slices: a per-pass fetch has to cover the latency of a load that misses L1 in every slice (the tile's codes
-    // are 64 KiB or more), which a look-ahead of two passes does not, and it re-reads the tile's codes once per slice.
-    // Only the first slice streams them (STREAM0): its pass p turns the codes of pass p + 1 into ccall[p + 1] and
-    // requests those of pass p + 3, so that the cold fetch of the codes hides behind the first slice's arithmetic.
-    // Raw codes in flight: those of passes 0 and 1 (requested here) wait in the ccall slots of the LAST passes, which
-    // are not written until the raw values have long been used; later ones in the first registers of the slice
-    // staging buffer, idle between the slice's LDS write and the last pass.
-    constexpr bool STREAM0 = M == 16 && NPASS >= 4;  // (with 32 codebooks the stream's two loads per pass do not hide)
-    constexpr int RAWS = NPASS * CV * CV / CW;                // ccall slots that one pass's raw codes take (2 or 1)
-    unsigned ccall[NPASS][CV][CV];
-    auto raw_slot = [&](int k, unsigned(&dst)[CW]) {          // raw codes of pass k (0 or 1): copy out of their parking slots
-#pragma unroll
-        for (int i = 0; i < CW; ++i) {
-            const int flat = (NPASS * CV * CV - 2 * CW) + k * CW + i;
-            dst[i] = ccall[flat / (CV * CV)][(flat / CV) % CV][flat % CV];
-        }
-    };
-    if (STREAM0) {
-        unsigned r0[CW], r1[CW];
-        fetch_codes(0, r0);
-        fetch_codes(1, r1);
-#pragma unroll
-        for (int i = 0; i < CW; ++i) {
-            const int f0 = (NPASS * CV * CV - 2 * CW) + i, f1 = f0 + CW;
-            ccall[f0 / (CV * CV)][(f0 / CV) % CV][f0 % CV] = r0[i];
-            ccall[f1 / (CV * CV)][(f1 / CV) % CV][f1 % CV] = r1[i];
-        }
-    } else {
-        unsigned craw[NPASS][CW];
-#pragma unroll
-        for (int p = 0; p < NPASS; ++p) fetch_codes(p, craw[p]);
-#pragma unroll
-        for (int p = 0; p < NPASS; ++p) make_cc(craw[p], ccall[p]);
-    }
-    (void)RAWS;
-    const int hmin = (qpos - (t0 + TILE - 1)) >> kLoBits;     // coarse row of the tile's last token (arithmetic shift)
-    const unsigned elo_base = (unsigned)kSliceBytes + (unsigned)(M == 16 ? gk : par) * (kLo * 16u);
-    const unsigned ehi_base = (unsigned)kSliceBytes + (unsigned)(PARTS * kLo) * 16u + (unsigned)(M == 16 ? gk : par) * 16u;
-
-    // Phase factors of a slice's sub-spaces, two buffers of [PARTS * 64 fine entries][NHR * PARTS coarse entries]:
-    // the fine table as it is, and the rows of the coarse table that the tile's distances q_pos - token can reach,
-    // row-major, so that the four coarse rows and the parts that the lanes of a read touch are 16 consecutive 16-byte
-    // pieces (no bank conflicts).  Thread t < PARTS * 64 moves fine entry t, the next PARTS * NHR threads one coarse
-    // entry each.  Where no distance of the tile is negative the entries go from memory straight into LDS, a whole
-    // slice ahead; a negative distance takes the conjugate of the row of its absolute value, which needs a register.
-    const bool DMA_OK = hmin >= 0;
-    auto phase_src = [&](int sl, bool &neg) -> const float2 * {
-        neg = false;
-        if (tid < PARTS * kLo) {
-            const int part = tid / kLo, lo = tid % kLo;
-            return tbl_lo + (size_t)lo * kJ + sl * NJ + 2 * part;
-        }
-        const int x = tid - PARTS * kLo;
-        const int part = x % PARTS, H = hmin + x / PARTS;
-        neg = H < 0;
-        return tbl_hi + (size_t)min(H < 0 ? -H : H, a.n_hi - 1) * kJ + sl * NJ + 2 * part;
-    };
-    static_assert(PARTS * kLo + PARTS * NHR <= kSliceThreads && (PARTS * kLo) % 64 == 0, "one phase entry per thread");
-    auto dma_phase = [&](int sl, int buf) {
-        if (tid < PARTS * kLo + PARTS * NHR) {
-            bool neg;
-            const float2 *srcp = phase_src(sl, neg);
-            lds_dma16(srcp, __builtin_amdgcn_readfirstlane((unsigned)kSliceBytes + (unsigned)buf * kPhaseBytes + (unsigned)wave * 1024u));
-        }
-    };
-    auto stage_phase = [&](int sl, int buf) {
-        if (tid < PARTS * kLo + PARTS * NHR) {
-            bool neg;
-            float4 e = *reinterpret_cast<const float4 *>(phase_src(sl, neg));
-            if (neg) { e.y = -e.y; e.w = -e.w; }
-            elo[(size_t)buf * (kPhaseBytes / 16) + tid] = e;
-        }
-    };
-    if (DMA_OK) dma_phase(s_begin, s_begin & 1);
-
-    for (int si = 0; si < s_end - s_begin; ++si) {  // (counted from 0, so that the first slice's extra work can be peeled off)
-        const int sl = s_begin + si;
-        if (!PREFETCH) fetch_slice(sl);
-        // queries of this slice (head 4 grp + n % 4, the lane's 4 elements): requested before the barriers, so
-        // that they have arrived when the first pass needs them
-        uint4_t qraw[NGRP];
-#pragma unroll
-        for (int x = 0; x < NGRP; ++x) {
-            const unsigned off = q_off + (unsigned)x * (4u * kD);
-            if (a.q_bf16) {
-                const uint2_t q2 = __builtin_amdgcn_raw_buffer_load_b64(q_rs, off * 2u, (unsigned)sl * DS * 2u, 0);
-                qraw[x][0] = q2[0]; qraw[x][1] = q2[1]; qraw[x][2] = 0u; qraw[x][3] = 0u;
-            } else {
-                qraw[x] = __builtin_amdgcn_raw_buffer_load_b128(q_rs, off * 4u, (unsigned)sl * DS * 4u, 0);
-            }
-        }
-        __syncthreads();  // everyone is done reading the previous slice
-#pragma unroll
-        for (int x = 0; x < PPT; ++x) reinterpret_cast<uint4_t *>(tab)[x * kSliceThreads + tid] = stage[x];
-        if (!DMA_OK) stage_phase(sl, sl & 1);
-        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this slice's phase factors (sent a slice ago) are in LDS
-        __syncthreads();
-        // the phase factors of the next slice travel into the other phase buffer while this slice is worked on
-        if (DMA_OK) dma_phase(min(sl + 1, S - 1), (sl + 1) & 1);
-        const unsigned ph_off = (unsigned)(sl & 1) * kPhaseBytes;
-        asm volatile("" : "+v"(tb));
-        code_off = (unsigned)(tb - (M == 16 ? 0 : 4 * kLo * set)) * M + (M == 16 ? 8u * par : 16u * hi + 8u * par);
-        // byte offsets (in the LDS phase tables) of the lane's part, and its distance to the query, times 16
-        const int dist16 = (qpos - tb) * 16;
-        // scaled queries of this slice
-        float qrow[NGRP][4];
-#pragma unroll
-        for (int x = 0; x < NGRP; ++x) {
-            if (a.q_bf16) {
-                qrow[x][0] = bf16_lo(qraw[x][0]) * a.scale; qrow[x][1] = bf16_hi(qraw[x][0]) * a.scale;
-                qrow[x][2] = bf16_lo(qraw[x][1]) * a.scale; qrow[x][3] = bf16_hi(qraw[x][1]) * a.scale;
-            } else {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const unsigned u = qraw[x][r];
-                    qrow[x][r] = __builtin_bit_cast(float, u) * a.scale;
-                }
-            }
-        }
-        // The tokens of a lane (one per pass) and of the four lanes of a 4-lane block are whole coarse rows (64
-        // tokens) apart: they share the fine phase factor E_lo, so it is folded into the block's query operand
-        // once per slice, q' = q conj(E_lo) (Re(conj(q) a E_hi E_lo) = Re(conj(q') a E_hi)), and a pass only rotates
-        // by the coarse factor, whose row steps down by a constant from pass to pass.
-        static_assert(PSTRIDE % kLo == 0, "pass stride in whole coarse rows");
-        {
-            const uint4_t elr = lds_read_b128(elo_base + ph_off + (unsigned)(dist16 & ((kLo - 1) * 16)));
-#pragma unroll
-            for (int x = 0; x < NGRP; ++x)
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const unsigned lxr = elr[2 * u], lyr = elr[2 * u + 1];
-                    const float lx = __builtin_bit_cast(float, lxr), ly = __builtin_bit_cast(float, lyr);
-                    const float qx = qrow[x][2 * u], qy = qrow[x][2 * u + 1];
-                    qrow[x][2 * u] = qx * lx + qy * ly;
-                    qrow[x][2 * u + 1] = qy * lx - qx * ly;
-                }
-        }
-        const unsigned ehi_last = ehi_base + ph_off + (unsigned)(((dist16 >> (kLoBits + 4)) - hmin - (NPASS - 1) * (PSTRIDE / kLo)) * (16 * PARTS));
-        // per step two LDS reads (pieces A and B) and one sparse MFMA; reads in groups of RG steps, two groups in flight
-        constexpr int RG = (G == 8 && TPT == 4) ? 1 : 2, NG = NST / RG;  // fewer reads in flight where registers are short
-        uint4_t v[2][RG][2];
-        auto issue = [&](int grp, const unsigned(&cc)[CV][CV], uint4_t(&dst)[RG][2]) {
-#pragma unroll
-            for (int r = 0; r < RG; ++r) {
-                const int st = grp * RG + r;
-#pragma unroll
-                for (int ab = 0; ab < 2; ++ab) {
-                    // address bytes: [0] column, [1] code byte st % 4 of its dword, [2] block, [3] zero.  M = 16: block =
-                    // plane = ab (xreg bytes 2, 3 hold 0, 1); M = 32: block = hi (xreg byte 2), the code is token ab's
-                    const unsigned sel = 0x0c000000u | (unsigned)(M == 16 ? 2 + ab : 2) << 16 | (unsigned)(4 + st % 4) << 8;
-                    const unsigned addr = __builtin_amdgcn_perm(cc[M == 16 ? 0 : ab][M == 16 ? 0 : st / 4], xreg[st], sel);
-                    dst[r][ab] = lds_read_b128(addr);
-                }
-            }
-        };
-        // The passes are software-pipelined: the LDS reads of a group of steps are issued as soon as the matrix
-        // instructions that consumed the group's registers have been issued -- for the last groups of a pass these are
-        // the first reads of the NEXT pass, which then travel while this pass is rotated and contracted with the queries.
-        unsigned cc[CV][CV];
-        if (STREAM0 && si == 0) {
-            unsigned r[CW];
-            raw_slot(0, r);
-            make_cc(r, ccall[0]);
-            if (2 < NPASS) {
-                unsigned f[CW];
-                fetch_codes(2, f);
-#pragma unroll
-                for (int i = 0; i < CW; ++i) stage[0][i] = f[i];
-            }
-        }
-        // an opaque copy per slice: the gather addresses made from these must not be hoisted out of the slice loop
-        // (they would need eight registers per pass instead of one)
-#pragma unroll
-        for (int pp = 0; pp < NPASS; ++pp)
-#pragma unroll
-            for (int i = 0; i < CV; ++i)
-#pragma unroll
-                for (int j = 0; j < CV; ++j) asm volatile("" : "+v"(ccall[pp][i][j]));
-#pragma unroll
-        for (int i = 0; i < CV; ++i)
-#pragma unroll
-            for (int j = 0; j < CV; ++j) cc[i][j] = ccall[0][i][j];
-        issue(0, cc, v[0]);
-        if (NG > 1) issue(1, cc, v[1]);
-#pragma unroll
-        for (int p = 0; p < NPASS; ++p) {
-            __builtin_amdgcn_sched_barrier(0);  // one pass at a time: keeps register pressure flat
-            // coarse phase factor of the lane's token and part, from LDS: a pass is a whole number of coarse rows
-            // further on
-            const uint4_t ehr = lds_read_b128(ehi_last + (unsigned)((NPASS - 1 - p) * (PSTRIDE / kLo) * (16 * PARTS)));
-            unsigned ccn[CV][CV];
-            if (p + 1 < NPASS) {
-                if (STREAM0 && si == 0) {
-                    // first slice: the codes of pass p + 1 have arrived (raw, requested two passes ago); keep them in
-                    // gather order and request those of pass p + 3 into the buffer they leave
-                    unsigned r[CW];
-                    if (p == 0) {
-                        raw_slot(1, r);
-                    } else {
-#pragma unroll
-                        for (int i = 0; i < CW; ++i) r[i] = stage[(p + 1) & 1][i];
-                    }
-                    make_cc(r, ccall[p + 1]);
-                    if (p + 3 < NPASS) {
-                        unsigned f[CW];
-                        fetch_codes(p + 3, f);
-#pragma unroll
-                        for (int i = 0; i < CW; ++i) stage[(p + 1) & 1][i] = f[i];
-                    }
-                }
-#pragma unroll
-                for (int i = 0; i < CV; ++i)
-#pragma unroll
-                    for (int j = 0; j < CV; ++j) ccn[i][j] = ccall[p + 1][i][j];
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            // 1. gather-sum on the matrix cores
-            floatx4_t acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int grp = 0; grp < NG; ++grp) {
-#pragma unroll
-                for (int r = 0; r < RG; ++r) {
-                    const uint4_t pa = v[grp & 1][r][0], pb = v[grp & 1][r][1];
-                    const uint8v_t both = {pa[0], pa[1], pa[2], pa[3], pb[0], pb[1], pb[2], pb[3]};
-                    acc = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(selv, __builtin_bit_cast(bf16x16_t, both), acc, (int)sidx, 0, 0);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                if (grp + 2 < NG) issue(grp + 2, cc, v[grp & 1]);
-                else if (p + 1 < NPASS) issue(grp + 2 - NG, ccn, v[grp & 1]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            if (PREFETCH && p == NPASS - 1) fetch_slice(min(sl + 1, S - 1));  // after the last slice: a harmless re-read
-            if (p + 1 < NPASS) {
-#pragma unroll
-                for (int i = 0; i < CV; ++i)
-#pragma unroll
-                    for (int j = 0; j < CV; ++j) cc[i][j] = ccn[i][j];
-            }
-            // 2. the lane's two sub-spaces rotated by the coarse phase factor: A E_hi
-            float val[4];
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const unsigned hxr = ehr[2 * u], hyr = ehr[2 * u + 1];
-                const float ex = __builtin_bit_cast(float, hxr);
-                const float ey = __builtin_bit_cast(float, hyr);
-                const float ax = acc[2 * u], ay = acc[2 * u + 1];
-                val[2 * u] = ax * ex - ay * ey;
-                val[2 * u + 1] = ax * ey + ay * ex;
-            }
-            // 3. per-lane partial logits of 4 heads at a time, then totals over the lanes of the token
-#pragma unroll
-            for (int x = 0; x < NGRP; ++x) {
-                floatx4_t t = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int r = 0; r < 4; ++r) t = __builtin_amdgcn_mfma_f32_4x4x1f32(qrow[x][r], val[r], t, 0, 0, 0);
-                if (M == 16) {
-                    sc[p][x][0] += swap16_add(swap32_add(t[0], t[2]), swap32_add(t[1], t[3]));
-                } else {
-                    sc[p][x][0] += swap16_add(t[0], t[1]);
-                    sc[p][x][NOUT - 1] += swap16_add(t[2], t[3]);
-                }
-            }
-        }
-    }
-
-    // a slice group leaves partial logits in its own array; the tile statistics then come from k_score_combine
-    float *srow = scores + (size_t)eg * a.part_stride + (size_t)cu0 * a.Hq + (size_t)g * G * L;
-    float2 *stat_dst = a.groups == 1 ? sstat + ((size_t)b * a.Hq + (size_t)g * G) * a.nsplit + tile : nullptr;
-    write_tile_logits<M, G, TPT, NPASS, NGRP, NOUT>(sc, reinterpret_cast<float *>(tab), wstat, srow, stat_dst, a.nsplit, tb, t0, L);
 }
 
 // ------------------------------------------------------------------ k_score_combine
@@ -1482,7 +1614,7 @@ __global__ __launch_bounds__(256) void k_prep_pairs(const uint4 *__restrict__ ta
     packed[t] = v;
 }
 
-// Score kernel for paired-code keys: same scheme as k_score_mfma (codebook streamed through LDS in
+// Score kernel for paired-code keys: same scheme as k_score_stream (codebook streamed through LDS in
 // slices, gather-sum and query product on the matrix cores), with
 //   * a slice = 4 planes of 8 elements of every centre of every level (NB blocks of 16 levels, one
 //     bank column per level, 64 rows = centre index): 64 KiB (R <= 16) or 128 KiB (R <= 32);
@@ -1539,7 +1671,7 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_pair(
         make_rsrc(static_cast<const char *>(q) + ((size_t)b * a.Hq + (size_t)g * G) * kD * qesz, (unsigned)G * kD * qesz);
     constexpr int PPT = SLICE / 16 / kSliceThreads;
 
-    // Selection operand of the structured-sparse v_smfmac_f32_16x16x64_bf16 (layout: see k_score_mfma).  Second
+    // Selection operand of the structured-sparse v_smfmac_f32_16x16x64_bf16 (layout: see k_score_stream).  Second
     // operand: two pieces per lane, both from levels of the lane's own type.  Row i = n adds element
     // e = 2 (i >> 2) + (i & 1) of both pieces of the two lanes of its type (i >> 1) & 1: first-operand lane (i, q)
     // covers the pieces of second-operand lanes 2 (q & 1), 2 (q & 1) + 1, i.e. of type q & 1 (its first piece for
@@ -1557,11 +1689,11 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_pair(
     }
     const bf16x8_t selv = __builtin_bit_cast(bf16x8_t, sel);
 
-    float sc[NPASS][NGRP][1];
+    float sc[NPASS][NGRP];
 #pragma unroll
     for (int p = 0; p < NPASS; ++p)
 #pragma unroll
-        for (int x = 0; x < NGRP; ++x) sc[p][x][0] = 0.f;
+        for (int x = 0; x < NGRP; ++x) sc[p][x] = 0.f;
 
     // xreg[st]: byte 0 = 16 * bank column (= level within the block) read at step st, byte 2 = 0, byte 3 = 1;
     // a byte permute splices the centre index in as byte 1: address = 256 c + 16 col (+ 65536 via byte 3)
@@ -1575,7 +1707,7 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_pair(
         rsel_hi |= (unsigned)((x + 4 + n) & 7) << (8 * x);
     }
 
-    // Token mapping as in k_score_mfma (M = 16): lane n of a wavefront's 16 token lanes takes fine position
+    // Token mapping as in k_score_stream (M = 16): lane n of a wavefront's 16 token lanes takes fine position
     // 4 wave + n / 4 and coarse row n % 4 of the pass's block of four rows, so the lanes of a 4-lane block and all
     // passes of a lane are whole coarse rows apart and share the fine phase factor, which is folded into the query.
     int tb = t0 + 4 * wave + (n >> 2) + kLo * (n & 3);
@@ -1743,7 +1875,7 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_pair(
             }
             // totals over the 4 lanes of the token: lane (n, gk) keeps head 4 grp + gk
 #pragma unroll
-            for (int x = 0; x < NGRP; ++x) sc[p][x][0] += swap16_add(swap32_add(t[x][0], t[x][2]), swap32_add(t[x][1], t[x][3]));
+            for (int x = 0; x < NGRP; ++x) sc[p][x] += swap16_add(swap32_add(t[x][0], t[x][2]), swap32_add(t[x][1], t[x][3]));
             if (p + 1 < NPASS) {
 #pragma unroll
                 for (int i = 0; i < 2 * NB; ++i) cc[i] = ccn[i];
@@ -1753,7 +1885,7 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_pair(
 
     float *srow = scores + (size_t)cu0 * a.Hq + (size_t)g * G * L;
     float2 *stat_dst = sstat + ((size_t)b * a.Hq + (size_t)g * G) * a.nsplit + tile;
-    write_tile_logits<16, G, TPT, NPASS, NGRP, 1>(sc, reinterpret_cast<float *>(tab), wstat, srow, stat_dst, a.nsplit, tb, t0, L);
+    write_tile_logits<G, TPT, NPASS, NGRP>(sc, reinterpret_cast<float *>(tab), wstat, srow, stat_dst, a.nsplit, tb, t0, L);
 }
 
 // ------------------------------------------------------------------ k_bins
@@ -2262,7 +2394,7 @@ commvq_status prep(const commvq_handle *h, const commvq_positions *pos, void *wo
     commvq_status st = check_positions(h, pos);
     if (st != COMMVQ_OK) return st;
     if (pair_keys(h->cfg) && pos->key_pos) return COMMVQ_ERR_CONFIG;  // paired-code keys: contiguous positions only
-    make_plan(h, pos->batch, pos->max_seqlen, use_sliced(h, pos->key_pos != nullptr), plan);
+    make_plan(h, pos->batch, pos->total_tokens, pos->max_seqlen, use_sliced(h, pos->key_pos != nullptr), plan);
     carve(h, pos->batch, pos->total_tokens, pos->max_seqlen, workspace, w);
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) || workspace_bytes < w->bytes)
         return COMMVQ_ERR_WORKSPACE;
@@ -2347,33 +2479,43 @@ struct SliceArgs {
     SliceDims d;
 };
 
-template <int M, int G, int TPT>
-hipError_t launch_sliced_mgt(const SliceArgs &a, int grid, hipStream_t s)
+struct StreamArgs {
+    const void *q;
+    const uint8_t *key_codes;
+    const uint4 *packed;
+    const int32_t *cu, *q_pos;
+    const float2 *tbl_hi, *tbl_lo;
+    float *scores;
+    float2 *sstat;
+    StreamDims d;
+};
+
+template <int M, int NGRP, int NP>
+hipError_t launch_stream_n(const StreamArgs &a, int grid, hipStream_t s)
 {
     static std::atomic<uint64_t> lds_ok{0};  // per instantiation and device
-    if (hipError_t e = allow_dynamic_lds(&k_score_mfma<M, G, TPT>, kScoreLds, lds_ok); e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_score_mfma<M, G, TPT>), dim3(grid), dim3(kSliceThreads), kScoreLds, s, a.q, a.key_codes,
+    if (hipError_t e = allow_dynamic_lds(&k_score_stream<M, NGRP, NP>, kStreamLds, lds_ok); e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_score_stream<M, NGRP, NP>), dim3(grid), dim3(kSliceThreads), kStreamLds, s, a.q, a.key_codes,
                        a.packed, a.cu, a.q_pos, a.tbl_hi, a.tbl_lo, a.scores, a.sstat, a.d);
     return hipGetLastError();
 }
-template <int M, int G>
-hipError_t launch_sliced_mg(const SliceArgs &a, int tpt, int grid, hipStream_t s)
+template <int M, int NGRP>
+hipError_t launch_stream_g(const StreamArgs &a, int passes, int grid, hipStream_t s)
 {
-    switch (tpt) {
-    case 1: return launch_sliced_mgt<M, G, 1>(a, grid, s);
-    case 2: return launch_sliced_mgt<M, G, 2>(a, grid, s);
-    default: return launch_sliced_mgt<M, G, 4>(a, grid, s);
+    switch (passes) {
+    case 2: return launch_stream_n<M, NGRP, 2>(a, grid, s);
+    case 3: return launch_stream_n<M, NGRP, 3>(a, grid, s);
+    case 4: return launch_stream_n<M, NGRP, 4>(a, grid, s);
+    case 5: return launch_stream_n<M, NGRP, 5>(a, grid, s);
+    case 6: return launch_stream_n<M, NGRP, 6>(a, grid, s);
+    case 7: return launch_stream_n<M, NGRP, 7>(a, grid, s);
+    default: return launch_stream_n<M, NGRP, 8>(a, grid, s);
     }
 }
-template <int M>
-hipError_t launch_sliced_m(const SliceArgs &a, int G, int tpt, int grid, hipStream_t s)
+hipError_t launch_stream(const StreamArgs &a, int M, int passes, int grid, hipStream_t s)
 {
-    switch (G) {
-    case 1: return launch_sliced_mg<M, 1>(a, tpt, grid, s);
-    case 2: return launch_sliced_mg<M, 2>(a, tpt, grid, s);
-    case 4: return launch_sliced_mg<M, 4>(a, tpt, grid, s);
-    default: return launch_sliced_mg<M, 8>(a, tpt, grid, s);
-    }
+    if (M == 16) return a.d.G == 8 ? launch_stream_g<16, 2>(a, passes, grid, s) : launch_stream_g<16, 1>(a, passes, grid, s);
+    return a.d.G == 8 ? launch_stream_g<32, 2>(a, passes, grid, s) : launch_stream_g<32, 1>(a, passes, grid, s);
 }
 
 template <int NB, int G, int TPT>
@@ -2479,7 +2621,7 @@ commvq_status run_scores(commvq_handle *h, const void *q, const uint8_t *key_cod
     if (c.position_free) {  // scalar look-up table: build T = scale q C^T, then M look-ups per token
         SliceDims d;
         d.Hq = c.n_q_heads; d.Hkv = c.n_kv_heads; d.nsplit = plan.score_splits; d.n_hi = h->n_hi;
-        d.q_bf16 = c.q_dtype == COMMVQ_BF16; d.scale = h->scale; d.groups = 1; d.part_stride = 0;
+        d.q_bf16 = c.q_dtype == COMMVQ_BF16; d.scale = h->scale;
         const int grid = pos->batch * c.n_kv_heads * plan.score_splits;
         const int tpt = plan.score_split_len / kSliceThreads;
         const bool bf16 = c.codebook_dtype == COMMVQ_BF16;
@@ -2495,18 +2637,15 @@ commvq_status run_scores(commvq_handle *h, const void *q, const uint8_t *key_cod
             if (launch_prep(c, key_cb, w.packed, s) != hipSuccess) return COMMVQ_ERR_LAUNCH;
             packed = w.packed;
         }
-        SliceArgs sa;
-        sa.q = q; sa.key_codes = key_codes; sa.packed = packed; sa.cu = pos->cu_seqlens; sa.q_pos = pos->q_pos;
-        sa.tbl_hi = h->tbl_hi; sa.tbl_lo = h->tbl_lo; sa.scores = w.scores; sa.sstat = w.sstat;
-        sa.d.Hq = c.n_q_heads; sa.d.Hkv = c.n_kv_heads; sa.d.nsplit = plan.score_splits; sa.d.n_hi = h->n_hi;
-        sa.d.q_bf16 = c.q_dtype == COMMVQ_BF16; sa.d.scale = h->scale;
-        const int groups = pair_keys(c) ? 1 : plan.score_slice_groups;
-        sa.d.groups = groups; sa.d.part_stride = (long long)pos->total_tokens * c.n_q_heads;
-        if (groups > 1) sa.scores = w.scores_part;
-        const int grid = pos->batch * c.n_kv_heads * plan.score_splits * groups;
-        const int tpt = plan.score_split_len / kSliceThreads;
         hipError_t e;
         if (pair_keys(c)) {
+            SliceArgs sa;
+            sa.q = q; sa.packed = packed; sa.cu = pos->cu_seqlens; sa.q_pos = pos->q_pos;
+            sa.tbl_hi = h->tbl_hi; sa.tbl_lo = h->tbl_lo; sa.scores = w.scores; sa.sstat = w.sstat;
+            sa.d.Hq = c.n_q_heads; sa.d.Hkv = c.n_kv_heads; sa.d.nsplit = plan.score_splits; sa.d.n_hi = h->n_hi;
+            sa.d.q_bf16 = c.q_dtype == COMMVQ_BF16; sa.d.scale = h->scale;
+            const int grid = pos->batch * c.n_kv_heads * plan.score_splits;
+            const int tpt = plan.score_split_len / kSliceThreads;
             // 12-bit pairs -> one byte per index, then the paired-code score kernel
             hipLaunchKernelGGL(k_unpack_pairs, dim3((unsigned)((pos->max_seqlen + 255) / 256), (unsigned)(pos->batch * c.n_kv_heads)),
                                dim3(256), 0, s, key_codes, w.pair_bytes, pos->cu_seqlens, c.n_kv_heads, c.key_levels,
@@ -2515,11 +2654,21 @@ commvq_status run_scores(commvq_handle *h, const void *q, const uint8_t *key_cod
             sa.key_codes = w.pair_bytes;
             e = pair_blocks(c) == 1 ? launch_pair_b<1>(sa, h->G, tpt, grid, s) : launch_pair_b<2>(sa, h->G, tpt, grid, s);
         } else {
-            e = c.m_key == 16 ? launch_sliced_m<16>(sa, h->G, tpt, grid, s) : launch_sliced_m<32>(sa, h->G, tpt, grid, s);
-            if (e == hipSuccess && groups > 1) {
-                const int ns = stat_splits(plan, pos->max_seqlen);
+            const StreamShape ss = stream_shape(h, pos->batch, pos->total_tokens, pos->max_seqlen);
+            StreamArgs sa;
+            sa.q = q; sa.key_codes = key_codes; sa.packed = packed; sa.cu = pos->cu_seqlens; sa.q_pos = pos->q_pos;
+            sa.tbl_hi = h->tbl_hi; sa.tbl_lo = h->tbl_lo; sa.scores = ss.groups > 1 ? w.scores_part : w.scores; sa.sstat = w.sstat;
+            sa.d.Hq = c.n_q_heads; sa.d.Hkv = c.n_kv_heads; sa.d.G = h->G; sa.d.batch = pos->batch; sa.d.n_hi = h->n_hi;
+            sa.d.q_bf16 = c.q_dtype == COMMVQ_BF16; sa.d.scale = h->scale;
+            sa.d.tiles = ss.tiles; sa.d.groups = ss.groups;
+            sa.d.nstat = stat_splits(h, plan, pos->max_seqlen);
+            sa.d.part_stride = (long long)pos->total_tokens * c.n_q_heads;
+            const int grid = c.n_kv_heads * ss.tiles * ss.groups;
+            e = launch_stream(sa, c.m_key, ss.passes, grid, s);
+            if (e == hipSuccess && ss.groups > 1) {
+                const int ns = sa.d.nstat;
                 hipLaunchKernelGGL(k_score_combine, dim3((unsigned)(pos->batch * c.n_q_heads * ns)), dim3(kCombineThreads), 0, s,
-                                   w.scores_part, w.scores, w.sstat, pos->cu_seqlens, c.n_q_heads, ns, stat_len(plan), groups,
+                                   w.scores_part, w.scores, w.sstat, pos->cu_seqlens, c.n_q_heads, ns, stat_len(h, plan), ss.groups,
                                    sa.d.part_stride);
                 e = hipGetLastError();
             }
@@ -2548,7 +2697,7 @@ commvq_status run_bins(commvq_handle *h, const uint8_t *val_codes, const commvq_
         v.val_bits = val_codes; v.cu = pos->cu_seqlens; v.scores = w.scores; v.sstat = w.sstat;
         v.bins = w.bins; v.vscale = w.vscale; v.lsum = w.lsum;
         v.Hq = c.n_q_heads; v.Hkv = c.n_kv_heads; v.G = h->G;
-        v.nsplit = stat_splits(plan, pos->max_seqlen); v.split_len = stat_len(plan);
+        v.nsplit = stat_splits(h, plan, pos->max_seqlen); v.split_len = stat_len(h, plan);
         v.nvsplit = plan.value_splits; v.vsplit_len = plan.value_split_len;
         v.Nc = c.value_bits; v.batch = pos->batch;
         return commvq_launch_vbits(v, s) == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;
@@ -2556,7 +2705,7 @@ commvq_status run_bins(commvq_handle *h, const uint8_t *val_codes, const commvq_
     BinsArgs a;
     a.val_codes = val_codes; a.cu = pos->cu_seqlens; a.scores = w.scores; a.sstat = w.sstat;
     a.bins = w.bins; a.vscale = w.vscale; a.lsum = w.lsum;
-    a.Hq = c.n_q_heads; a.Hkv = c.n_kv_heads; a.nsplit = stat_splits(plan, pos->max_seqlen); a.split_len = stat_len(plan);
+    a.Hq = c.n_q_heads; a.Hkv = c.n_kv_heads; a.nsplit = stat_splits(h, plan, pos->max_seqlen); a.split_len = stat_len(h, plan);
     a.nvsplit = plan.value_splits; a.vsplit_len = plan.value_split_len;
     const int grid = pos->batch * c.n_kv_heads * plan.value_splits;
     hipError_t e = c.m_val == 16 ? launch_bins_m<16>(a, h->G, grid, s) : launch_bins_m<32>(a, h->G, grid, s);
@@ -2748,7 +2897,7 @@ commvq_status commvq_plan_query(const commvq_handle *h, int32_t batch, int64_t t
     // explicit key positions are not known here: the distance check belongs to the calls that see them
     const commvq_status st = check_shape(h, batch, total_tokens, max_seqlen, true);
     if (st != COMMVQ_OK) return st;
-    make_plan(h, batch, max_seqlen, use_sliced(h, false), plan);
+    make_plan(h, batch, total_tokens, max_seqlen, use_sliced(h, false), plan);
     return COMMVQ_OK;
 }
 

@@ -19,7 +19,10 @@ constexpr int kJ = 64;          // 2-D sub-spaces = lanes of a wavefront
 constexpr int kK = 256;         // codewords per codebook
 constexpr int kLoBits = 6;      // relative position = hi * 64 + lo
 constexpr int kLo = 1 << kLoBits;
-constexpr int kScoreMaxTpt = 4;      // slice-streaming score tile: at most 4 x 1024 tokens
+constexpr int kScoreMaxTpt = 4;      // tiles of k_score_pair and k_score_lut: at most 4 x 1024 tokens
+constexpr int kStreamPasses = 8;     // k_score_stream: passes of a workgroup at most
+constexpr int kPassTokens = 512;     // tokens of a pass: 16 wavefronts x 32
+constexpr int kStreamSlices = kD / 8;  // codebook slices: 8 elements of every codeword each
 constexpr int kScoreMinWgs = 2048;   // row-gather score kernel: tiles are halved until this many workgroups exist
 constexpr int kScoreThreads = 256;
 constexpr int kBinsThreads = 1024;
@@ -115,6 +118,12 @@ __device__ __forceinline__ float cb_elem(const void *cb, size_t i)
 __device__ __forceinline__ void lds_dma16(const void *gptr, unsigned lds_byte_addr_uniform)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_byte_addr_uniform), "v"(gptr) : "memory");
+}
+
+// the same from a wavefront-uniform address plus a byte offset per lane
+__device__ __forceinline__ void lds_dma16(const void *base_uniform, unsigned offset, unsigned lds_byte_addr_uniform)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_byte_addr_uniform), "v"(offset), "s"(base_uniform) : "memory");
 }
 
 __device__ __forceinline__ float bf16_lo(unsigned v) { return __builtin_bit_cast(float, v << 16); }

@@ -1,0 +1,59 @@
+"""The slice-streaming score kernel where a workgroup's passes (512-token segments) belong to several sequences, and every
+number of passes a workgroup can have: parity with the oracle as in test_gpu_parity.py."""
+import numpy as np
+import pytest
+
+from paper_2506_18879_amd import synth
+
+from test_gpu_parity import TOL_SCORE, assert_rows, gpu, oracle_out  # noqa: F401  (gpu: fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(gpu, oracle, w, **kw):
+    import torch
+    print(f"case {w.name} lens={np.diff(w.cu_seqlens)[:12]}", flush=True)
+    dw, op = gpu.DeviceWorkload(w), gpu.DecodeAttention(w, **kw)
+    s, out = op.scores(dw), op(dw)
+    torch.cuda.synchronize()
+    ref, ref_scores, _ = oracle_out(oracle, w, return_intermediates=True)
+    assert np.abs(s.cpu().numpy().astype(np.float64) - ref_scores).max() <= TOL_SCORE
+    assert_rows(out.cpu().numpy(), ref, w.name)
+    op.close()
+
+
+@pytest.mark.parametrize("Mk,G", [(16, 4), (16, 8), (32, 2), (32, 8)])
+@pytest.mark.parametrize("lens", [[512, 1, 513, 511, 1024, 700, 3, 512, 1537], [40, 2000, 512, 0, 1023, 9]])
+def test_sequences_that_share_a_workgroup(gpu, oracle, Mk, G, lens):  # noqa: F811
+    # boundaries between sequences at even and odd passes, queries at, before (negative distances) and past the end
+    w = synth.make_workload(f"share_m{Mk}_g{G}_{len(lens)}", B=len(lens), Hq=8 * G, Hkv=8, seqlens=[max(1, x) for x in lens], Mk=Mk,
+                            Mv=16, dtype="bf16", seed=Mk + G + len(lens))
+    w.q_pos = np.array([(max(1, x) - 1, x // 3, x + 777)[i % 3] for i, x in enumerate(lens)], np.int32)
+    _check(gpu, oracle, w, max_position=4096)
+
+
+@pytest.mark.parametrize("Mk", [16, 32])
+def test_more_sequences_than_one_round_of_the_segment_lookup(gpu, oracle, Mk):  # noqa: F811
+    lens = [(37 * i) % 601 + 1 for i in range(150)]
+    _check(gpu, oracle, synth.make_workload(f"many_m{Mk}", B=150, Hq=4, Hkv=1, seqlens=lens, Mk=Mk, Mv=16, dtype="bf16", seed=Mk))
+
+
+@pytest.mark.parametrize("Mk", [16, 32])
+@pytest.mark.parametrize("heads,L", [(4, 20000), (4, 13000), (8, 20000), (8, 9000), (1, 33000)])
+def test_numbers_of_passes(gpu, oracle, Mk, heads, L):  # noqa: F811
+    # one KV head at lengths whose plans use different numbers of passes and slice groups
+    _check(gpu, oracle, synth.make_workload(f"passes_m{Mk}_g{heads}_{L}", B=1, Hq=heads, Hkv=1, seqlens=[L], Mk=Mk, Mv=16,
+                                            dtype="bf16", seed=L + Mk))
+
+
+def test_query_that_is_not_16_byte_aligned(gpu, oracle):  # noqa: F811
+    import torch
+    w = synth.make_workload("odd_q", B=2, Hq=8, Hkv=2, seqlens=[900, 1300], Mk=16, Mv=16, dtype="bf16", seed=3)
+    dw, op = gpu.DeviceWorkload(w), gpu.DecodeAttention(w)
+    room = torch.empty(dw.q.numel() + 1, dtype=dw.q.dtype, device="cuda")
+    room[1:] = dw.q.view(-1)
+    dw.q = room[1:]
+    out = op(dw)
+    torch.cuda.synchronize()
+    assert_rows(out.cpu().numpy(), oracle_out(oracle, w), w.name)
+    op.close()
