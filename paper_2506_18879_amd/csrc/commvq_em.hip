@@ -297,255 +297,569 @@ __global__ __launch_bounds__(256) void k_em_solve(const float *__restrict__ nab,
 // one matrix T^T S T (it only holds N_ab = sum_i W_i,ab) and one right-hand side per sub-space, which needs
 // only the marginals of W:  rhs_j[x_a] = sum_i k_i^jx Wa_i[a] + k_i^jy Wb_i[a],  rhs_j[y_a] = sum_i k_i^jy Wa_i[a] -
 // k_i^jx Wb_i[a],  Wa_i[a] = sum_b W_i,ab,  Wb_i[a] = sum_b W_i,ba.
-constexpr int kEmsPts = 32;     // points per workgroup of k_ems_assign
-constexpr int kEmsSplits = 16;  // point ranges whose right-hand-side partials are summed in a fixed order
+//
+// Three kernels: k_ems_accumulate (per workgroup a range of points: N_ab and rhs partials), k_ems_reduce (their sums
+// in a fixed order), k_ems_solve.  Index range padded to NP = 8 NB (16, 32 or 64) centres: X_ab = INFINITY there, so the
+// weights are exact zeros.
+constexpr int kEmsPts = 32;       // points per pass of a workgroup of k_ems_accumulate
+constexpr int kEmsThreads = 512;  // 2 wavefronts per SIMD: the 2 NB^2 registers of weights and sums leave no room for more
+constexpr int kEmsMaxWg = 256;    // one workgroup per compute unit
 
-// X_ab and N_a of the current codebook (one thread per (a, b)).
-__global__ __launch_bounds__(256) void k_ems_tables(const float2 *__restrict__ phi, float *__restrict__ xab, float *__restrict__ nn,
-                                                    int J, int Nc)
+typedef float em_f4 __attribute__((ext_vector_type(4)));
+
+template <int CTRL>
+__device__ __forceinline__ float em_dpp(float v)
 {
-    const int ab = blockIdx.x * 256 + threadIdx.x;
-    if (ab >= Nc * Nc) return;
-    const int a = ab / Nc, b = ab % Nc;
-    float x = 0.f, n = 0.f;
-    for (int j = 0; j < J; ++j) {
-        const float2 pa = phi[(size_t)j * Nc + a], pb = phi[(size_t)j * Nc + b];
-        x += pa.y * pb.x - pa.x * pb.y;
-        n += pa.x * pa.x + pa.y * pa.y;
-    }
-    xab[ab] = 2.f * x;
-    if (b == 0) nn[a] = n;
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+constexpr int kDppXor1 = 0xb1, kDppXor2 = 0x4e, kDppHalfMirror = 0x141, kDppRor8 = 0x128, kDppBcast = 0x150;
+// x + y where x's odd 16-lane rows and y's even rows change places (and the same with 32-lane halves): with x == y a
+// step of an all-lanes sum, otherwise two sums at once, x's in the even rows and y's in the odd ones
+__device__ __forceinline__ float em_swap16_add(float x, float y)
+{
+    auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, y), false, false);
+    return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+}
+__device__ __forceinline__ float em_swap32_add(float x, float y)
+{
+    auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, y), false, false);
+    return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+}
+__device__ __forceinline__ float em_swap_min(float v)
+{
+    const unsigned u = __builtin_bit_cast(unsigned, v);
+    auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    const unsigned w = __builtin_bit_cast(unsigned, fminf(__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1])));
+    auto t = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+    return fminf(__builtin_bit_cast(float, (unsigned)t[0]), __builtin_bit_cast(float, (unsigned)t[1]));
+}
+__device__ __forceinline__ float em_sum8(float v)  // over 8 consecutive lanes
+{
+    v += em_dpp<kDppXor1>(v);
+    v += em_dpp<kDppXor2>(v);
+    return v + em_dpp<kDppHalfMirror>(v);
+}
+__device__ __forceinline__ float em_min8(float v)
+{
+    v = fminf(v, em_dpp<kDppXor1>(v));
+    v = fminf(v, em_dpp<kDppXor2>(v));
+    return fminf(v, em_dpp<kDppHalfMirror>(v));
 }
 
-// Workgroup = 32 points.  LDS: the codebook (later overwritten by X), the points, u = N_a - 2 P[a] and
-// v = N_b - 2 Q[b] per point.
-// 1. P, Q by plain FMAs (thread = point x eighth of the rows);  2. per point, eight lanes sweep the Nc^2 centres
-// twice: nearest distance, then the softmax denominator;  3. per centre pair, four lanes sweep the 32 points:
-// N_ab partial of the workgroup and the marginal Wa (first index fixed), then again transposed for Wb.
-__global__ __launch_bounds__(256) void k_ems_assign(const float2 *__restrict__ data, const float2 *__restrict__ phi,
-                                                    const float *__restrict__ xab_g, const float *__restrict__ nn_g,
-                                                    float *__restrict__ nab_part, float *__restrict__ wa_g, float *__restrict__ wb_g,
-                                                    int N, int J, int Nc, float c)
+// Sizes shared by host and device.
+struct EmsDims {
+    int np, j2, j16, ps;   // padded centres; sub-spaces padded to 2 and to 16; floats per point row in LDS
+    __host__ __device__ EmsDims(int J, int NP) : np(NP), j2((J + 1) & ~1), j16((J + 15) & ~15), ps(2 * ((J + 15) & ~15) + 4) {}
+    __host__ __device__ int part() const { return np * np + 2 * j16 * np; }  // floats of a workgroup's partial sums
+    __host__ __device__ int lds() const
+    {
+        const int all = np * np + 2 * kEmsPts * (np + 4) + 9 * np + kEmsPts + kEmsPts * ps + 2 * j2 * np;
+        return (all > 4 * np * np ? all : 4 * np * np) * 4;  // the end of the kernel needs 4 planes of N_ab
+    }
+};
+
+// Workgroup = a range of P points, 32 at a time.  The contractions (X, then P and Q, then the right-hand sides) are fp32
+// matrix instructions out of LDS.  The sweep over the centre pairs in between gives a wavefront one point: lane (al, bl)
+// holds the pairs a = NB al + .., b = NB bl + .., so that the distances, the weights, both marginals and the
+// denominator come from ONE evaluation of each pair, kept in registers until the denominator is known.
+//   bound: the quarter-rate v_sqrt_f32 and v_exp_f32, one each per (point, pair), and 7 more operations of the
+// vector unit per pair.
+// 8192 points, 64 x 64 pairs, 64 sub-spaces: 28 us, of which the sweep 13 and the contractions 9; as separate passes over
+// the points (tables, four evaluations of each pair, right-hand sides from the stored marginals) it was 196 us.
+template <int NB>
+__global__ __launch_bounds__(kEmsThreads) void k_ems_accumulate(const float2 *__restrict__ data, const float2 *__restrict__ phi,
+                                                                float *__restrict__ part, int N, int J, int Nc, int P, float c)
 {
+    constexpr int NP = 8 * NB, NT = NP / 16, US = NP + 4;
     extern __shared__ __attribute__((aligned(16))) float ems_lds[];
-    const int JS = J + 1, NS = Nc + 1;                      // padded strides
-    const int r0 = (max(J * Nc * 2, Nc * Nc) + 1) & ~1;     // floats (even) of the region that holds phi, then X
-    float2 *ph = reinterpret_cast<float2 *>(ems_lds);       // [J][Nc]      (step 1)
-    float *xs = ems_lds;                                    // [Nc][Nc]     (steps 2 and 3)
-    float2 *pts = reinterpret_cast<float2 *>(ems_lds + r0); // [32][J + 1]
-    float *u = reinterpret_cast<float *>(pts + kEmsPts * JS);  // [32][Nc + 1]
-    float *v = u + kEmsPts * NS;                            // [32][Nc + 1]
-    float *kk = v + kEmsPts * NS;                           // [32] ||k||^2
-    float *dmin = kk + kEmsPts;                             // [32]
-    float *rz = dmin + kEmsPts;                             // [32] 1 / softmax denominator
-    const int tid = threadIdx.x;
-    const int i0 = blockIdx.x * kEmsPts;
-    const int cnt = min(kEmsPts, N - i0);
-    for (int x = tid; x < J * Nc; x += 256) ph[x] = phi[x];
-    for (int x = tid; x < kEmsPts * J; x += 256) {
-        const int i = x / J, j = x % J;
-        pts[i * JS + j] = i < cnt ? data[(size_t)(i0 + i) * J + j] : make_float2(0.f, 0.f);
-    }
-    __syncthreads();
-    {   // 1. thread = (point i, rows a = ag, ag + 8, ...)
-        const int i = tid & (kEmsPts - 1), ag = tid / kEmsPts;
-        for (int a = ag; a < Nc; a += 256 / kEmsPts) {
-            float P = 0.f, Q = 0.f;
-            for (int j = 0; j < J; ++j) {
-                const float2 k = pts[i * JS + j], r = ph[j * Nc + a];
-                P += k.x * r.x + k.y * r.y;
-                Q += k.y * r.x - k.x * r.y;
-            }
-            const float na = nn_g[a];
-            u[i * NS + a] = na - 2.f * P;
-            v[i * NS + a] = na - 2.f * Q;
-        }
-        if (ag == 0) {
-            float s = 0.f;
-            for (int j = 0; j < J; ++j) { const float2 k = pts[i * JS + j]; s += k.x * k.x + k.y * k.y; }
-            kk[i] = s;
-        }
-    }
-    __syncthreads();  // phi is no longer read: X takes its place
-    for (int x = tid; x < Nc * Nc; x += 256) xs[x] = xab_g[x];
-    __syncthreads();
-    {   // 2. lane (n, q) of wavefront w: point 8 w + n, first indices a = q, q + 8, ...
-        const int n = tid & 7, q = (tid >> 3) & 7, i = (tid >> 6) * 8 + n;
-        const float ki = kk[i];
-        float d2m = INFINITY;
-        for (int a = q; a < Nc; a += 8) {
-            const float ua = ki + u[i * NS + a];
-            for (int b = 0; b < Nc; ++b) d2m = fminf(d2m, ua + (v[i * NS + b] + xs[a * Nc + b]));
-        }
-        d2m = fminf(d2m, __shfl_xor(d2m, 8));
-        d2m = fminf(d2m, __shfl_xor(d2m, 16));
-        d2m = fminf(d2m, __shfl_xor(d2m, 32));
-        const float dm = em_sqrt(fmaxf(d2m, 0.f));
-        float z = 0.f;
-        for (int a = q; a < Nc; a += 8) {
-            const float ua = ki + u[i * NS + a];
-#pragma unroll 4
-            for (int b = 0; b < Nc; ++b) {
-                const float d = em_sqrt(fmaxf(ua + (v[i * NS + b] + xs[a * Nc + b]), 0.f));
-                z += __builtin_amdgcn_exp2f(-(d - dm) * c);
-            }
-        }
-        z += __shfl_xor(z, 8);
-        z += __shfl_xor(z, 16);
-        z += __shfl_xor(z, 32);
-        if (q == 0) { dmin[i] = dm; rz[i] = 1.f / z; }
-    }
-    __syncthreads();
-    // 3. thread = (first index f = tid / 4, second indices s = tid % 4, + 4, ...); tr = 1: the same with the
-    // roles of the two indices exchanged (marginal over the first index)
-    const int f = tid >> 2, sq = tid & 3;
-    for (int tr = 0; tr < 2; ++tr) {
-        float nacc[kEmMaxNc / 4], xr[kEmMaxNc / 4];
+    const EmsDims dm(J, NP);
+    float *xl = ems_lds;                       // X in the sweep's order: [NB^2 / 4][64 lanes][4]
+    float *us = xl + NP * NP;                  // [32][US] N_a - 2 P[a], then Wa
+    float *vs = us + kEmsPts * US;             // [32][US] N_b - 2 Q[b], then Wb
+    float *na = vs + kEmsPts * US;             // [NP]
+    float *nap = na + NP;                      // [8][NP]
+    float *kk = nap + 8 * NP;                  // [32] ||k||^2
+    float *pts = kk + kEmsPts;                 // [32][ps] (x, y) of the sub-spaces; zeros past J
+    float *ph = pts + kEmsPts * dm.ps;         // [j2][NP] (x, y); zeros past J and Nc
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n = lane & 15, g = lane >> 4, gh = g >> 1, gl = g & 1;
+    const int first = blockIdx.x * P, last = min(N, first + P);
+    {   // every load of the codebook (at most NB a thread) and of the first points under way before the first is used
+        float2 pv[NB];
 #pragma unroll
-        for (int e = 0; e < kEmMaxNc / 4; ++e) {
-            nacc[e] = 0.f;
-            const int s2 = sq + 4 * e;
-            xr[e] = (f < Nc && s2 < Nc) ? (tr == 0 ? xs[f * Nc + s2] : xs[s2 * Nc + f]) : 0.f;
+        for (int e = 0; e < NB; ++e) {
+            const int x = tid + e * kEmsThreads, j = x / NP, a = x % NP;
+            pv[e] = phi[(size_t)min(j, J - 1) * Nc + min(a, Nc - 1)];
+            if (j >= J || a >= Nc) pv[e] = make_float2(0.f, 0.f);
         }
-        const float *mine = tr == 0 ? u : v, *other = tr == 0 ? v : u;
-        float *marg = tr == 0 ? wa_g : wb_g;
-        for (int i = 0; i < cnt; ++i) {
-            float w = 0.f;
-            if (f < Nc) {
-                const float base = kk[i] + mine[i * NS + f];
-                const float dm = dmin[i], r = rz[i];
 #pragma unroll
-                for (int e = 0; e < kEmMaxNc / 4; ++e) {
-                    const int s2 = sq + 4 * e;
-                    if (s2 < Nc) {
-                        const float d = em_sqrt(fmaxf(base + (other[i * NS + s2] + xr[e]), 0.f));
-                        const float wi = __builtin_amdgcn_exp2f(-(d - dm) * c) * r;
-                        nacc[e] += wi;
-                        w += wi;
+        for (int e = 0; e < NB; ++e) {
+            const int x = tid + e * kEmsThreads;
+            if (x < dm.j2 * NP) *reinterpret_cast<float2 *>(ph + 2 * x) = pv[e];
+        }
+    }
+    float nacc[NB * NB];
+#pragma unroll
+    for (int e = 0; e < NB * NB; ++e) nacc[e] = 0.f;
+    em_f4 racc[2][2] = {};
+    for (int i0 = first; i0 < last; i0 += kEmsPts) {
+        const int cnt = min(kEmsPts, last - i0), cnt8 = (cnt + 7) & ~7;
+        float2 kv[kEmsPts / 8];
+#pragma unroll
+        for (int e = 0; e < kEmsPts / 8; ++e) {
+            const int i = wave + 8 * e;
+            kv[e] = data[(size_t)(i0 + min(i, cnt - 1)) * J + min(lane, J - 1)];
+            if (i >= cnt || lane >= J) kv[e] = make_float2(0.f, 0.f);
+        }
+#pragma unroll
+        for (int e = 0; e < kEmsPts / 8; ++e) {
+            const int i = wave + 8 * e;
+            if (lane < dm.j16) *reinterpret_cast<float2 *>(pts + i * dm.ps + 2 * lane) = kv[e];
+            float s = kv[e].x * kv[e].x + kv[e].y * kv[e].y;
+            s = em_sum8(s);
+            s += em_dpp<kDppRor8>(s);
+            s = em_swap16_add(s, s);
+            s = em_swap32_add(s, s);
+            if (lane == 0) kk[i] = s;
+        }
+        __syncthreads();
+        if (i0 == first) {
+            // X_ab = 2 sum_j (y_a x_b - x_a y_b): rows a, columns b, contraction over (j, component); lane (n, g) supplies
+            // component g & 1 of sub-space j + (g >> 1)
+            constexpr int TW = NT * NT > 8 ? NT * NT / 8 : 1;  // tiles of a wavefront, all of one row of tiles
+            if (wave * TW < NT * NT) {
+                const int ta = wave * TW / NT, tb = wave * TW % NT;
+                const float *pa = ph + 2 * (gh * NP + 16 * ta + n) + 1 - gl, *pb = ph + 2 * (gh * NP + 16 * tb + n) + gl;
+                const float sign = gl ? -2.f : 2.f;
+                em_f4 acc[TW] = {};
+#pragma unroll 8
+                for (int j = 0; j < dm.j2; j += 2) {
+                    const float av = sign * pa[2 * j * NP];
+#pragma unroll
+                    for (int e = 0; e < TW; ++e) acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, pb[2 * j * NP + 32 * e], acc[e], 0, 0, 0);
+                }
+#pragma unroll
+                for (int e = 0; e < TW; ++e) {
+                    const int b = 16 * (tb + e) + n, bl = b / NB, bi = b % NB;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int a = 16 * ta + 4 * g + r, al = a / NB, f = (a % NB) * NB + bi;
+                        xl[((f >> 2) * 64 + al * 8 + bl) * 4 + (f & 3)] = a < Nc && b < Nc ? acc[e][r] : INFINITY;
                     }
                 }
             }
-            w += __shfl_xor(w, 1);
-            w += __shfl_xor(w, 2);
-            if (f < Nc && sq == 0) marg[(size_t)(i0 + i) * Nc + f] = w;
-        }
-        if (tr == 0 && f < Nc) {
+            for (int x = tid; x < 8 * NP; x += kEmsThreads) {
+                const int a = x % NP;
+                float s = 0.f;
+#pragma unroll 8
+                for (int j = x / NP; j < J; j += 8) {
+                    const float2 v = *reinterpret_cast<const float2 *>(ph + 2 * (j * NP + a));
+                    s += v.x * v.x + v.y * v.y;
+                }
+                nap[x] = s;
+            }
+            __syncthreads();
+            if (tid < NP) {
+                float s = 0.f;
 #pragma unroll
-            for (int e = 0; e < kEmMaxNc / 4; ++e) {
-                const int s2 = sq + 4 * e;
-                if (s2 < Nc) nab_part[(size_t)blockIdx.x * Nc * Nc + f * Nc + s2] = nacc[e];
+                for (int e = 0; e < 8; ++e) s += nap[e * NP + tid];
+                na[tid] = s;
+            }
+            __syncthreads();
+        }
+        // P[i][a] = sum_j k.x x_a + k.y y_a and Q[i][b] = sum_j k.y x_b - k.x y_b: the same right operand
+        for (int t = wave; t < (cnt + 15) / 16 * NT; t += 8) {
+            const int ti = t / NT, ta = t % NT;
+            const float *row = pts + (16 * ti + n) * dm.ps + 2 * gh, *pb = ph + 2 * (gh * NP + 16 * ta + n) + gl;
+            em_f4 accp = {}, accq = {};
+#pragma unroll 8
+            for (int j = 0; j < dm.j2; j += 2) {
+                const float kx = row[2 * j], ky = row[2 * j + 1], b = pb[2 * j * NP];
+                accp = __builtin_amdgcn_mfma_f32_16x16x4f32(gl ? ky : kx, b, accp, 0, 0, 0);
+                accq = __builtin_amdgcn_mfma_f32_16x16x4f32(gl ? -kx : ky, b, accq, 0, 0, 0);
+            }
+            const float nv = na[16 * ta + n];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int i = 16 * ti + 4 * g + r;
+                us[i * US + 16 * ta + n] = nv - 2.f * accp[r];
+                vs[i * US + 16 * ta + n] = nv - 2.f * accq[r];
+            }
+        }
+        __syncthreads();
+        for (int i = wave; i < cnt8; i += 8) {
+            const int al = lane >> 3, bl = lane & 7;
+            float *urow = us + i * US + NB * al, *vrow = vs + i * US + NB * bl;
+            if (i >= cnt) {  // no point here: zero weights for the contraction below
+                if (bl == 0)
+                    for (int e = 0; e < NB; ++e) urow[e] = 0.f;
+                if (al == 0)
+                    for (int e = 0; e < NB; ++e) vrow[e] = 0.f;
+                continue;
+            }
+            float u[NB], v[NB], e[NB * NB];
+            const float ki = kk[i];
+#pragma unroll
+            for (int x = 0; x < NB; ++x) {
+                u[x] = ki + urow[x];
+                v[x] = vrow[x];
+            }
+#pragma unroll
+            for (int q = 0; q < NB * NB / 4; ++q) {
+                const em_f4 x4 = *reinterpret_cast<const em_f4 *>(xl + (q * 64 + lane) * 4);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) e[4 * q + r] = x4[r];
+            }
+            float d2m = INFINITY;
+#pragma unroll
+            for (int f = 0; f < NB * NB; ++f) {
+                e[f] = u[f / NB] + (v[f % NB] + e[f]);
+                d2m = fminf(d2m, e[f]);
+            }
+            d2m = em_min8(d2m);
+            d2m = fminf(d2m, em_dpp<kDppRor8>(d2m));
+            d2m = em_swap_min(d2m);
+            if (d2m < 0.f) {  // a point on a centre, by rounding
+#pragma unroll
+                for (int f = 0; f < NB * NB; ++f) e[f] = fmaxf(e[f], 0.f);
+                d2m = 0.f;
+            }
+            // every weight of the point carries the same rounding of dmc, which the division by the sum takes out
+            const float dmc = em_sqrt(d2m) * c;
+            float row[NB], col[NB];
+#pragma unroll
+            for (int f = 0; f < NB * NB; ++f) {
+                const float w = __builtin_amdgcn_exp2f(__builtin_fmaf(em_sqrt(e[f]), -c, dmc));
+                e[f] = w;
+                row[f / NB] = f % NB == 0 ? w : row[f / NB] + w;
+                col[f % NB] = f < NB ? w : col[f % NB] + w;
+            }
+            float z = 0.f;
+#pragma unroll
+            for (int x = 0; x < NB; ++x) {
+                row[x] = em_sum8(row[x]);
+                z += row[x];
+            }
+            z += em_dpp<kDppRor8>(z);
+            z = em_swap16_add(z, z);
+            z = em_swap32_add(z, z);
+            const float rz = em_rcp(z);
+#pragma unroll
+            for (int f = 0; f < NB * NB; ++f) nacc[f] = __builtin_fmaf(e[f], rz, nacc[f]);
+#pragma unroll
+            for (int x = 0; x < NB; ++x) {
+                col[x] += em_dpp<kDppRor8>(col[x]);
+                col[x] = em_swap16_add(col[x], col[x]);
+                col[x] = em_swap32_add(col[x], col[x]);
+            }
+            if (bl == 0) {
+#pragma unroll
+                for (int x = 0; x < NB; ++x) urow[x] = row[x] * rz;
+            }
+            if (al == 0) {
+#pragma unroll
+                for (int x = 0; x < NB; ++x) vrow[x] = col[x] * rz;
+            }
+        }
+        __syncthreads();
+        // rhs_j[x_a] += k.x Wa + k.y Wb, rhs_j[y_a] += k.y Wa - k.x Wb: rows j, columns a, contraction over (point, Wa or Wb)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int unit = wave + 8 * t, tj = unit / NT, ta = unit % NT;
+            if (tj < dm.j16 / 16) {
+                const float *kp = pts + gh * dm.ps + 2 * (16 * tj + n), *wp = (gl ? vs : us) + gh * US + 16 * ta + n;
+#pragma unroll 4
+                for (int i = 0; i < cnt8; i += 2) {
+                    const float2 k = *reinterpret_cast<const float2 *>(kp + i * dm.ps);
+                    const float w = wp[i * US];
+                    racc[t][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(gl ? k.y : k.x, w, racc[t][0], 0, 0, 0);
+                    racc[t][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(gl ? -k.x : k.y, w, racc[t][1], 0, 0, 0);
+                }
+            }
+        }
+        __syncthreads();
+    }
+    // N_ab of the 8 wavefronts, in the sweep's order
+    float *slot = ems_lds + (wave & 3) * NP * NP;
+    if (wave >= 4) {
+#pragma unroll
+        for (int q = 0; q < NB * NB / 4; ++q)
+            *reinterpret_cast<em_f4 *>(slot + (q * 64 + lane) * 4) = em_f4{nacc[4 * q], nacc[4 * q + 1], nacc[4 * q + 2], nacc[4 * q + 3]};
+    }
+    __syncthreads();
+    if (wave < 4) {
+#pragma unroll
+        for (int q = 0; q < NB * NB / 4; ++q)
+            *reinterpret_cast<em_f4 *>(slot + (q * 64 + lane) * 4) += em_f4{nacc[4 * q], nacc[4 * q + 1], nacc[4 * q + 2], nacc[4 * q + 3]};
+    }
+    __syncthreads();
+    float *mine = part + (size_t)blockIdx.x * dm.part();
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const int unit = wave + 8 * t, tj = unit / NT, ta = unit % NT;
+        if (tj < dm.j16 / 16) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int x = 0; x < 2; ++x)
+                    mine[NP * NP + (x * dm.j16 + 16 * tj + 4 * g + r) * NP + 16 * ta + n] = racc[t][x][r];
+        }
+    }
+    for (int x = tid; x < NP * NP; x += kEmsThreads)
+        mine[x] = (ems_lds[x] + ems_lds[NP * NP + x]) + (ems_lds[2 * NP * NP + x] + ems_lds[3 * NP * NP + x]);
+}
+
+// Sums of the workgroups' partials in a fixed order: 16 threads per 4 neighbouring sums take every 16th workgroup.
+// Bound by the read of 12.6 MB that the launch before has just written (256 workgroups, largest shape): 4.5 us.
+__global__ __launch_bounds__(256) void k_ems_reduce(const float *__restrict__ part, float *__restrict__ sums, int n_wg, int len)
+{
+    __shared__ em_f4 red[16][16];
+    const int l = threadIdx.x & 15, q = threadIdx.x >> 4;
+    const int at = blockIdx.x * 64 + 4 * l;
+    em_f4 s = {};
+#pragma unroll 8
+    for (int w = q; w < n_wg; w += 16) s += *reinterpret_cast<const em_f4 *>(part + (size_t)w * len + at);
+    red[q][l] = s;
+    __syncthreads();
+    if (q == 0) {
+#pragma unroll
+        for (int e = 1; e < 16; ++e) s += red[e][l];
+        *reinterpret_cast<em_f4 *>(sums + at) = s;
+    }
+}
+
+// In-place inverse of a symmetric positive definite 16 x 16 block by Gauss-Jordan elimination in one wavefront: lane
+// (r, g) holds a[e] = A[r][4 g + e].  Rows and columns travel by DPP and lane swaps: about 120 cycles a pivot.
+template <int K>
+__device__ __forceinline__ void em_pivot(float (&a)[4], int r, int g)
+{
+    const float p = em_lane(a[K % 4], K + K / 4 * 16);
+    const unsigned own = __builtin_bit_cast(unsigned, a[K % 4]);
+    auto s = __builtin_amdgcn_permlane16_swap(own, own, false, false);
+    const unsigned w = (unsigned)s[(K / 4) & 1];
+    auto t = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+    const bool is = r == K;
+    const float f = is ? -1.f : __builtin_bit_cast(float, (unsigned)t[(K / 4) >> 1]);  // A[r][K] in all four lanes of row r
+    const float x = __builtin_amdgcn_rcpf(p), c = 2.f - p * x;  // 1 / p = x c
+    const float m = (f * x) * c;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) a[e] = __builtin_fmaf(-m, em_dpp<kDppBcast + K>(a[e]), is ? 0.f : a[e]);
+    if (g == K / 4) a[K % 4] = -m;  // row K: 1 / p
+}
+__device__ __forceinline__ void em_invert16(float (&a)[4], int r, int g)
+{
+    em_pivot<0>(a, r, g), em_pivot<1>(a, r, g), em_pivot<2>(a, r, g), em_pivot<3>(a, r, g);
+    em_pivot<4>(a, r, g), em_pivot<5>(a, r, g), em_pivot<6>(a, r, g), em_pivot<7>(a, r, g);
+    em_pivot<8>(a, r, g), em_pivot<9>(a, r, g), em_pivot<10>(a, r, g), em_pivot<11>(a, r, g);
+    em_pivot<12>(a, r, g), em_pivot<13>(a, r, g), em_pivot<14>(a, r, g), em_pivot<15>(a, r, g);
+}
+
+// Solutions for 16 sub-spaces per workgroup.  With the unknowns ordered (x_0 .. x_n, y_0 .. y_n) the system is
+//   [D V; V^T D] [x; y] = [rx; ry],   D = diag(sum_b N_ab + N_ba),  V_ab = N_ba - N_ab = -V_ba,
+// so the first half of a Cholesky factorisation is a division by D, and what remains is half the order:
+//   (D + V D^-1 V) y = ry + V D^-1 rx,   x = D^-1 (rx - V y).
+// It is eliminated in blocks of 16 (block Gauss-Jordan: the diagonal blocks' inverses by one wavefront, the rest matrix
+// instructions).  Every workgroup repeats the factorisation, a chain that one workgroup runs as fast as many.
+// All matrices lie in LDS row by row, right-hand sides one row per sub-space, and the matrix instructions take the
+// contraction index in the order 16 s + 4 (lane / 16) + step: operands are float4 reads along a row, a result's lanes
+// hold what the next product needs as an operand, and symmetric tiles are stored transposed, again as float4.
+//   bound: the chain of NP pivots.  64 x 64 pairs, 64 sub-spaces: 10 us (a Cholesky
+// factorisation of the whole system with substitution on the vector unit: 71 us).
+constexpr int kEmsSolveThreads = 1024;  // 16 wavefronts: the 14 tiles of the largest reduced system at once
+template <int NB>
+__global__ __launch_bounds__(kEmsSolveThreads) void k_ems_solve(const float *__restrict__ sums, float2 *__restrict__ phi, int J, int Nc)
+{
+    constexpr int NP = 8 * NB, NT = NP / 16, LD = NP + 4;
+    __shared__ __attribute__((aligned(16))) float nm[NP * LD], vm[NP * LD], rx[16 * LD], ry[16 * LD], pinv[NT * 16 * 20],
+        dsum[NP], dinv[NP], dp[8 * NP];
+    float *sm = nm;  // the matrix of the reduced system, once N_ab has been read
+    const EmsDims dm(J, NP);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n = lane & 15, g = lane >> 4;
+    const int j0 = blockIdx.x * 16;
+    {
+        constexpr int NE = (NP * NP + kEmsSolveThreads - 1) / kEmsSolveThreads;
+        const bool in = tid < 16 * NP;
+        const int j = tid / NP, ja = tid % NP;
+        const float *rp = sums + NP * NP + (in ? (j0 + j) * NP + ja : 0);
+        const float vx = rp[0], vy = rp[dm.j16 * NP];
+        float v[NE];
+#pragma unroll
+        for (int e = 0; e < NE; ++e) v[e] = sums[min(tid + e * kEmsSolveThreads, NP * NP - 1)];
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            const int x = tid + e * kEmsSolveThreads, l = (x >> 2) & 63, f = (x >> 8) * 4 + (x & 3);
+            if (x < NP * NP) nm[(NB * (l >> 3) + f / NB) * LD + NB * (l & 7) + f % NB] = v[e];
+        }
+        if (in) {
+            rx[j * LD + ja] = vx;
+            ry[j * LD + ja] = vy;
+        }
+    }
+    __syncthreads();
+    for (int x = tid; x < NP * NP; x += kEmsSolveThreads) {
+        const int a = x / NP, b = x % NP;
+        vm[a * LD + b] = nm[b * LD + a] - nm[a * LD + b];
+    }
+    if (tid < 8 * NP) {
+        const int a = tid % NP, b0 = tid / NP;
+        float s = 0.f;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) s += nm[a * LD + b0 + 8 * b] + nm[(b0 + 8 * b) * LD + a];
+        dp[tid] = s;
+    }
+    __syncthreads();
+    if (tid < NP) {
+        float s = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s += dp[e * NP + tid];
+        s = tid < Nc ? s : 1.f;
+        dsum[tid] = s;
+        dinv[tid] = 1.f / s;
+    }
+    __syncthreads();
+    // C + A B over all NP, A's rows at ap, B's columns at bp; two chains, since each step waits for the one before
+    auto product = [&](em_f4 acc, const float *ap, const float *bp, auto scale) {
+        em_f4 acc2 = {};
+#pragma unroll
+        for (int s = 0; s < NT; ++s) {
+            const em_f4 av = *reinterpret_cast<const em_f4 *>(ap + 16 * s + 4 * g);
+            const em_f4 bv = *reinterpret_cast<const em_f4 *>(bp + 16 * s + 4 * g);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                em_f4 &to = r & 1 ? acc2 : acc;
+                to = __builtin_amdgcn_mfma_f32_16x16x4f32(av[r], scale(16 * s + 4 * g + r) * bv[r], to, 0, 0, 0);
+            }
+        }
+        return acc + acc2;
+    };
+    // tiles (ti, tj), ti <= tj < NT: D + V D^-1 V (V[k][b] = -V[b][k]), as tile [tj][ti]; tj = NT: ry + V D^-1 rx
+    int unit = 0;
+#pragma unroll
+    for (int ti = 0; ti < NT; ++ti)
+#pragma unroll
+        for (int tj = ti; tj <= NT; ++tj) {
+            if (unit++ != wave) continue;
+            float *row = tj < NT ? sm + (16 * tj + n) * LD : ry + n * LD;
+            em_f4 acc;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int a = 16 * ti + 4 * g + r;
+                acc[r] = tj == NT ? row[a] : a == 16 * tj + n ? dsum[a] : 0.f;
+            }
+            acc = product(acc, vm + (16 * ti + n) * LD, tj < NT ? vm + (16 * tj + n) * LD : rx + n * LD,
+                          [&](int k) { return tj < NT ? -dinv[k] : dinv[k]; });
+            *reinterpret_cast<em_f4 *>(row + 16 * ti + 4 * g) = acc;
+        }
+    __syncthreads();
+    // Stage k: S_ij -= S_ik P_k S_kj, P_k = S_kk^-1, for every i other than k and j > k (j = NT: the right-hand sides).  i < k
+    // takes the place of a back substitution; tile (i, j) is kept as [j][i].  Wavefront 0 takes (k + 1, k + 1), which
+    // leaves the matrix unit in the order that the inversion starts from, and inverts it while the others update.
+    auto update = [&](int k, int i, int j) {
+        const em_f4 pv = *reinterpret_cast<const em_f4 *>(pinv + (k * 16 + n) * 20 + 4 * g);
+        em_f4 iv;
+        if (i > k) {
+            iv = *reinterpret_cast<const em_f4 *>(sm + (16 * i + n) * LD + 16 * k + 4 * g);
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) iv[r] = sm[(16 * k + 4 * g + r) * LD + 16 * i + n];
+        }
+        float *row = j < NT ? sm + (16 * j + n) * LD : ry + n * LD;
+        const em_f4 jv = *reinterpret_cast<const em_f4 *>(row + 16 * k + 4 * g);
+        em_f4 acc = *reinterpret_cast<const em_f4 *>(row + 16 * i + 4 * g), acc2 = {}, m = {}, m2 = {};
+#pragma unroll
+        for (int r = 0; r < 4; r += 2) {
+            m = __builtin_amdgcn_mfma_f32_16x16x4f32(pv[r], iv[r], m, 0, 0, 0);
+            m2 = __builtin_amdgcn_mfma_f32_16x16x4f32(pv[r + 1], iv[r + 1], m2, 0, 0, 0);
+        }
+        m += m2;
+#pragma unroll
+        for (int r = 0; r < 4; r += 2) {
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(-m[r], jv[r], acc, 0, 0, 0);
+            acc2 = __builtin_amdgcn_mfma_f32_16x16x4f32(-m[r + 1], jv[r + 1], acc2, 0, 0, 0);
+        }
+        return acc + acc2;
+    };
+    auto invert = [&](int k, em_f4 blk) {
+        float a[4] = {blk[0], blk[1], blk[2], blk[3]};
+        em_invert16(a, n, g);
+        *reinterpret_cast<em_f4 *>(pinv + (k * 16 + n) * 20 + 4 * g) = em_f4{a[0], a[1], a[2], a[3]};
+    };
+    if (wave == 0) invert(0, *reinterpret_cast<const em_f4 *>(sm + n * LD + 4 * g));
+    __syncthreads();
+    for (int k = 0; k < NT; ++k) {
+        if (wave == 0) {
+            if (k + 1 < NT) invert(k + 1, update(k, k + 1, k + 1));
+        } else {
+            int left = wave - 1;  // the unit of this wavefront among the stage's (i, j)
+            for (int i = 0; i < NT; ++i) {
+                if (i == k) continue;
+                const int from = i < k ? k + 1 : i == k + 1 ? i + 1 : i;
+                if (left <= NT - from) {
+                    const int j = from + left;
+                    const em_f4 acc = update(k, i, j);
+                    *reinterpret_cast<em_f4 *>((j < NT ? sm + (16 * j + n) * LD : ry + n * LD) + 16 * i + 4 * g) = acc;
+                    break;
+                }
+                left -= NT - from + 1;
+            }
+        }
+        __syncthreads();
+    }
+    if (wave < NT) {  // y_k = P_k ry_k
+        float *yp = ry + n * LD + 16 * wave + 4 * g;
+        const em_f4 pv = *reinterpret_cast<const em_f4 *>(pinv + (wave * 16 + n) * 20 + 4 * g), yv = *reinterpret_cast<const em_f4 *>(yp);
+        em_f4 acc = {};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(pv[r], yv[r], acc, 0, 0, 0);
+        *reinterpret_cast<em_f4 *>(yp) = acc;
+    }
+    __syncthreads();
+    if (wave < NT) {  // x = D^-1 (rx - V y)
+        const em_f4 acc = product(*reinterpret_cast<const em_f4 *>(rx + n * LD + 16 * wave + 4 * g), vm + (16 * wave + n) * LD,
+                                  ry + n * LD, [](int) { return -1.f; });
+        if (j0 + n < J) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int a = 16 * wave + 4 * g + r;
+                if (a < Nc) phi[(size_t)(j0 + n) * Nc + a] = make_float2(acc[r] * dinv[a], ry[n * LD + a]);
             }
         }
     }
 }
 
-// N_ab = sum of the workgroups' partials in a fixed order: 16 lanes per centre pair take every 16th workgroup,
-// then a butterfly over the 16 lanes.
-__global__ __launch_bounds__(256) void k_ems_reduce(const float *__restrict__ nab_part, float *__restrict__ nab, int n_wg, int Nc)
-{
-    const int ab = blockIdx.x * 16 + (threadIdx.x >> 4), l = threadIdx.x & 15;
-    float s = 0.f;
-    if (ab < Nc * Nc)
-        for (int w = l; w < n_wg; w += 16) s += nab_part[(size_t)w * Nc * Nc + ab];
-    s += __shfl_xor(s, 1);
-    s += __shfl_xor(s, 2);
-    s += __shfl_xor(s, 4);
-    s += __shfl_xor(s, 8);
-    if (ab < Nc * Nc && l == 0) nab[ab] = s;
-}
-
-// Right-hand sides: workgroup = (sub-space j, range of points), thread = a.
-__global__ __launch_bounds__(kEmMaxNc) void k_ems_rhs(const float2 *__restrict__ data, const float *__restrict__ wa_g,
-                                                     const float *__restrict__ wb_g, float2 *__restrict__ rhs_part, int N, int J, int Nc)
-{
-    const int j = blockIdx.x, sp = blockIdx.y, a = threadIdx.x;
-    const int per = (N + kEmsSplits - 1) / kEmsSplits;
-    const int i0 = sp * per, i1 = min(N, i0 + per);
-    float rx = 0.f, ry = 0.f;
-    if (a < Nc) {
-#pragma unroll 4
-        for (int i = i0; i < i1; ++i) {
-            const float2 k = data[(size_t)i * J + j];
-            const float wa = wa_g[(size_t)i * Nc + a], wb = wb_g[(size_t)i * Nc + a];
-            rx += k.x * wa + k.y * wb;
-            ry += k.y * wa - k.x * wb;
-        }
-        rhs_part[((size_t)sp * J + j) * Nc + a] = make_float2(rx, ry);
-    }
-}
-
-// The common 2Nc x 2Nc matrix, its Cholesky factor, and the right-hand sides of the J sub-spaces side by side.
-// The factorisation is a chain of dependent steps that one workgroup runs as fast as sixteen, while the
-// right-hand sides are independent: workgroup w repeats the (cheap) factorisation and substitutes for the
-// kEmsSolveCols sub-spaces w * kEmsSolveCols ... only.
-constexpr int kEmsSolveThreads = 1024;
-constexpr int kEmsSolveCols = 4;
-__global__ __launch_bounds__(kEmsSolveThreads) void k_ems_solve(const float *__restrict__ nab, const float2 *__restrict__ rhs_part,
-                                                   float2 *__restrict__ phi, int J, int Nc)
-{
-    extern __shared__ float em_lds[];
-    const int n2 = 2 * Nc, np = em_pad(n2), ld = np + 1;
-    const int tid = threadIdx.x;
-    const int j0 = blockIdx.x * kEmsSolveCols, jn = min(kEmsSolveCols, J - j0);
-    float *A = em_lds;                 // [np][np + 1]; identity past n2
-    float *R = A + np * ld;            // [np][jn]
-    float *Dinv = R + np * kEmsSolveCols;  // [np / 16][16][16]
-    for (int x = tid; x < np * ld; x += kEmsSolveThreads) A[x] = 0.f;
-    for (int x = tid; x < np * jn; x += kEmsSolveThreads) R[x] = 0.f;
-    __syncthreads();
-    if (tid >= n2 && tid < np) A[tid * ld + tid] = 1.f;
-    for (int x = tid; x < Nc * Nc; x += kEmsSolveThreads) {
-        const int a = x / Nc, b = x % Nc;
-        const float v = nab[b * Nc + a] - nab[a * Nc + b];
-        A[(2 * a) * ld + 2 * b + 1] = v;
-        A[(2 * b + 1) * ld + 2 * a] = v;
-    }
-    for (int x = tid; x < Nc * jn; x += kEmsSolveThreads) {
-        const int a = x / jn, j = x % jn;
-        float rx = 0.f, ry = 0.f;
-        for (int sp = 0; sp < kEmsSplits; ++sp) {
-            const float2 p = rhs_part[((size_t)sp * J + j0 + j) * Nc + a];
-            rx += p.x;
-            ry += p.y;
-        }
-        R[(2 * a) * jn + j] = rx;
-        R[(2 * a + 1) * jn + j] = ry;
-    }
-    __syncthreads();
-    if (tid < Nc) {
-        float d = 0.f;
-        for (int b = 0; b < Nc; ++b) d += nab[tid * Nc + b] + nab[b * Nc + tid];
-        A[(2 * tid) * ld + 2 * tid] = d;
-        A[(2 * tid + 1) * ld + 2 * tid + 1] = d;
-    }
-    __syncthreads();
-    em_cholesky<kEmsSolveThreads>(A, ld, np, Dinv, tid);
-    em_substitute<kEmsSolveThreads>(A, ld, np, Dinv, R, jn, tid);
-    for (int x = tid; x < jn * Nc; x += kEmsSolveThreads) {
-        const int j = x / Nc, a = x % Nc;
-        phi[(size_t)j0 * Nc + x] = make_float2(R[(2 * a) * jn + j], R[(2 * a + 1) * jn + j]);
-    }
-}
-
+// Points per workgroup: a wavefront has one at a time, and up to 256 workgroups (one per compute unit) share the points
+// before any of them gets a second round of 8.
 struct EmsLayout {
-    size_t xab, nn, wa, wb, nab_part, nab, rhs_part, bytes;
-    int n_wg;
+    int n_wg, per, np, len;
+    size_t part, sums, bytes;
 };
 inline EmsLayout ems_layout(int J, int N, int Nc)
 {
     EmsLayout l;
-    l.n_wg = (N + kEmsPts - 1) / kEmsPts;
-    size_t off = 0;
-    auto take = [&](size_t bytes) { const size_t at = off; off += em_align(bytes); return at; };
-    l.xab = take((size_t)Nc * Nc * 4);
-    l.nn = take((size_t)Nc * 4);
-    l.wa = take((size_t)N * Nc * 4);
-    l.wb = take((size_t)N * Nc * 4);
-    l.nab_part = take((size_t)l.n_wg * Nc * Nc * 4);
-    l.nab = take((size_t)Nc * Nc * 4);
-    l.rhs_part = take((size_t)kEmsSplits * J * Nc * 8);
-    l.bytes = off;
+    l.np = Nc <= 16 ? 16 : Nc <= 32 ? 32 : 64;
+    l.per = ((N + kEmsMaxWg - 1) / kEmsMaxWg + 7) / 8 * 8;
+    l.n_wg = (N + l.per - 1) / l.per;
+    l.len = EmsDims(J, l.np).part();
+    l.part = 0;
+    l.sums = em_align((size_t)l.n_wg * l.len * 4);
+    l.bytes = l.sums + em_align((size_t)l.len * 4);
     return l;
+}
+
+template <int NB>
+inline commvq_status ems_launch(const EmsLayout &l, const float2 *data, float2 *phi, float *part, float *sums, int N, int J, int Nc,
+                                float c, hipStream_t s)
+{
+    static std::atomic<uint64_t> lds_ok{0};
+    if (allow_dynamic_lds(&k_ems_accumulate<NB>, EmsDims(64, 8 * NB).lds(), lds_ok) != hipSuccess) return COMMVQ_ERR_LAUNCH;
+    hipLaunchKernelGGL(k_ems_accumulate<NB>, dim3((unsigned)l.n_wg), dim3(kEmsThreads), EmsDims(J, 8 * NB).lds(), s, data, phi, part,
+                       N, J, Nc, l.per, c);
+    if (hipGetLastError() != hipSuccess) return COMMVQ_ERR_LAUNCH;
+    hipLaunchKernelGGL(k_ems_reduce, dim3((unsigned)(l.len / 64)), dim3(256), 0, s, part, sums, l.n_wg, l.len);
+    if (hipGetLastError() != hipSuccess) return COMMVQ_ERR_LAUNCH;
+    hipLaunchKernelGGL(k_ems_solve<NB>, dim3((unsigned)((J + 15) / 16)), dim3(kEmsSolveThreads), 0, s, sums, phi, J, Nc);
+    return hipGetLastError() == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;
 }
 
 }  // namespace
@@ -617,34 +931,16 @@ commvq_status commvq_em_step_shared(const float *data, int32_t group, int32_t n_
     const int J = group, N = n_points, Nc = n_centres;
     const EmsLayout l = ems_layout(J, N, Nc);
     char *w = static_cast<char *>(workspace);
-    float *xab = reinterpret_cast<float *>(w + l.xab), *nn = reinterpret_cast<float *>(w + l.nn);
-    float *wa = reinterpret_cast<float *>(w + l.wa), *wb = reinterpret_cast<float *>(w + l.wb);
-    float *nab_part = reinterpret_cast<float *>(w + l.nab_part), *nab = reinterpret_cast<float *>(w + l.nab);
-    float2 *rhs_part = reinterpret_cast<float2 *>(w + l.rhs_part);
+    float *part = reinterpret_cast<float *>(w + l.part), *sums = reinterpret_cast<float *>(w + l.sums);
     hipStream_t s = static_cast<hipStream_t>(stream);
     const float2 *d2 = reinterpret_cast<const float2 *>(data);
     float2 *p2 = reinterpret_cast<float2 *>(phi);
-    const unsigned cgrid = (unsigned)((Nc * Nc + 255) / 256);
-    hipLaunchKernelGGL(k_ems_tables, dim3(cgrid), dim3(256), 0, s, p2, xab, nn, J, Nc);
-    if (hipGetLastError() != hipSuccess) return COMMVQ_ERR_LAUNCH;
-    const int lds_a = ((((J * Nc * 2 > Nc * Nc ? J * Nc * 2 : Nc * Nc) + 1) & ~1) + kEmsPts * (J + 1) * 2 + 2 * kEmsPts * (Nc + 1) + 3 * kEmsPts) * 4;
-    const int np_s = (2 * Nc + 15) / 16 * 16;
-    const int lds_s = (np_s * (np_s + 1) + np_s * kEmsSolveCols + np_s * 16) * 4;
-    static std::atomic<uint64_t> lds_ok_a{0}, lds_ok_s{0};
-    const int max_a = (64 * 64 * 2 + kEmsPts * 65 * 2 + 2 * kEmsPts * 65 + 3 * kEmsPts) * 4;
-    const int max_s = (128 * 129 + 128 * kEmsSolveCols + 128 * 16) * 4;
-    if (allow_dynamic_lds(&k_ems_assign, max_a, lds_ok_a) != hipSuccess || allow_dynamic_lds(&k_ems_solve, max_s, lds_ok_s) != hipSuccess)
-        return COMMVQ_ERR_LAUNCH;
-    hipLaunchKernelGGL(k_ems_assign, dim3((unsigned)l.n_wg), dim3(256), lds_a, s, d2, p2, xab, nn, nab_part, wa, wb, N, J, Nc,
-                       kLog2eEm / temperature);
-    if (hipGetLastError() != hipSuccess) return COMMVQ_ERR_LAUNCH;
-    hipLaunchKernelGGL(k_ems_reduce, dim3((unsigned)((Nc * Nc + 15) / 16)), dim3(256), 0, s, nab_part, nab, l.n_wg, Nc);
-    if (hipGetLastError() != hipSuccess) return COMMVQ_ERR_LAUNCH;
-    hipLaunchKernelGGL(k_ems_rhs, dim3((unsigned)J, (unsigned)kEmsSplits), dim3(kEmMaxNc), 0, s, d2, wa, wb, rhs_part, N, J, Nc);
-    if (hipGetLastError() != hipSuccess) return COMMVQ_ERR_LAUNCH;
-    hipLaunchKernelGGL(k_ems_solve, dim3((unsigned)((J + kEmsSolveCols - 1) / kEmsSolveCols)), dim3(kEmsSolveThreads), lds_s, s, nab,
-                       rhs_part, p2, J, Nc);
-    return hipGetLastError() == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;
+    const float c = kLog2eEm / temperature;
+    switch (l.np) {
+        case 16: return ems_launch<2>(l, d2, p2, part, sums, N, J, Nc, c, s);
+        case 32: return ems_launch<4>(l, d2, p2, part, sums, N, J, Nc, c, s);
+        default: return ems_launch<8>(l, d2, p2, part, sums, N, J, Nc, c, s);
+    }
 }
 
 }  // extern "C"

@@ -1,0 +1,34 @@
+"""The shared-code EM step at the edges of its kernels' tiles: 16, 32 and 64 padded centres, sub-spaces around a multiple
+of 16 (and odd), points around the 8 of a workgroup's round, around 8 x 256 workgroups, and more than 32 a workgroup.
+Oracle: oracle.em_step_shared (fp64)."""
+import numpy as np
+import pytest
+
+from test_gpu_em import em_shared, shared_calibration  # noqa: F401  (fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("J,Nc,N", [(1, 1, 40), (2, 16, 1031), (15, 17, 2048), (17, 32, 2049), (33, 33, 777), (64, 48, 2305), (5, 64, 4099),
+                                    (3, 12, 8193), (16, 8, 8449), (64, 5, 9)])
+def test_tile_edges_match_oracle(em_shared, oracle, J, Nc, N):  # noqa: F811
+    data, start = shared_calibration(J, N, Nc, seed=J * 1000 + Nc)
+    T = 0.3 * np.sqrt(J)
+    print(f"case group={J} Nc={Nc} N={N} T={T:.2f}", flush=True)
+    got = em_shared(data, start, T)
+    ref, _ = oracle.em_step_shared(data, start, temperature=T)
+    worst = np.abs(got - ref).max() / np.abs(ref).max()
+    print(f"  max relative deviation of phi: {worst:.3e}", flush=True)
+    assert worst <= 2e-3
+
+
+def test_a_point_on_a_centre(em_shared, oracle):  # noqa: F811
+    """Squared distances that come out negative by rounding count as zero."""
+    data, start = shared_calibration(8, 600, 9, seed=5, noise=0.0)
+    hidden = (start[..., 0] + 1j * start[..., 1]).astype(np.complex64)
+    for i in range(100):
+        c = hidden[:, i % 9] + 1j * hidden[:, (i * 5) % 9]
+        data[i, :, 0], data[i, :, 1] = c.real, c.imag
+    got = em_shared(data, start, 0.5)
+    ref, _ = oracle.em_step_shared(data, start, temperature=0.5)
+    assert np.isfinite(got).all() and np.abs(got - ref).max() <= 2e-3 * np.abs(ref).max()
