@@ -217,13 +217,13 @@ def bench_encode(args):
     # algorithmic work per (token, head, level): the dot products with the level's rows, the candidate scan
     flop = n * w.Hkv * levels * (2 * w.d * (2 * K if paired else K) + (5 * K * K if paired else 2 * K) + 2 * w.d)
     tf = flop / (kernel_ms * 1e-3) / 1e12
-    roof = {"kernel": "k_encode_lds" if paired else "k_encode_dma", "bound": "alu", "achieved": round(tf, 3),
+    roof = {"kernel": "k_encode_lds" if paired else "k_encode", "bound": "alu", "achieved": round(tf, 3),
             "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": round(tf / FP32_PEAK_TFLOPS, 4), "traffic": None,
             "kernel_ms": round(kernel_ms, 5)}
-    if not paired and n >= 64:
-        # 64 tokens per workgroup: the dot products run as bf16 MFMA on an exact three-way split of the fp32 residual
+    if not paired and w.dtype == "bf16":
+        # the dot products run as bf16 MFMA on an exact three-way split of the fp32 residual
         mf = 3 * n * w.Hkv * levels * 2 * w.d * K / (kernel_ms * 1e-3) / 1e12
-        roof = {"kernel": "k_encode_batch", "bound": "mfma", "achieved": round(mf, 2), "peak": MFMA_BF16_PEAK_TFLOPS,
+        roof = {"kernel": "k_encode_rows", "bound": "mfma", "achieved": round(mf, 2), "peak": MFMA_BF16_PEAK_TFLOPS,
                 "unit": "TFLOP/s", "frac": round(mf / MFMA_BF16_PEAK_TFLOPS, 4), "traffic": None,
                 "kernel_ms": round(kernel_ms, 5)}
     if paired and n >= 64:

@@ -1,6 +1,8 @@
 // libcommvq: key encoding for cache append (residual nearest-centre search), hand-written for gfx950.
 #include "commvq_internal.hpp"
 
+#include <algorithm>
+
 namespace {
 
 // ------------------------------------------------------------------ key encoding (cache append)
@@ -37,13 +39,34 @@ __global__ __launch_bounds__(256) void k_encode_tables(const void *__restrict__ 
     }
 }
 
+// The lower of the minima that lanes l, l ^ 16, l ^ 32 and l ^ 48 hold, and its index (the lower one on ties): every one
+// of the four lanes receives both.
+__device__ __forceinline__ void min4(float &best, int &index)
+{
+    auto lower = [&](unsigned b0, unsigned b1, unsigned i0, unsigned i1) {
+        const float f0 = __builtin_bit_cast(float, b0), f1 = __builtin_bit_cast(float, b1);
+        const bool second = f1 < f0 || (f1 == f0 && (int)i1 < (int)i0);
+        best = second ? f1 : f0;
+        index = second ? (int)i1 : (int)i0;
+    };
+    unsigned b = __builtin_bit_cast(unsigned, best), i = (unsigned)index;
+    auto b16 = __builtin_amdgcn_permlane16_swap(b, b, false, false);
+    auto i16 = __builtin_amdgcn_permlane16_swap(i, i, false, false);
+    lower(b16[0], b16[1], i16[0], i16[1]);
+    b = __builtin_bit_cast(unsigned, best);
+    i = (unsigned)index;
+    auto b32 = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+    auto i32 = __builtin_amdgcn_permlane32_swap(i, i, false, false);
+    lower(b32[0], b32[1], i32[0], i32[1]);
+}
+
 struct EncodeDims {
     int Hkv, levels, K, key_bf16, record_bytes;
     long long token_stride, head_stride;
 };
 
 // Index-form keys, fp32 codebooks: one workgroup per (token, KV head), one thread per centre of the level, rows
-// straight from L2.  Ties go to the lowest index.  (bf16 codebooks: k_encode_dma and k_encode_batch below.)
+// straight from L2.  Ties go to the lowest index.  (bf16 codebooks: k_encode_rows below.)
 template <bool BF16>
 __global__ __launch_bounds__(256) void k_encode(const void *__restrict__ keys, const void *__restrict__ cb,
                                                 const float *__restrict__ norms, uint8_t *__restrict__ out, const EncodeDims a)
@@ -86,165 +109,126 @@ __global__ __launch_bounds__(256) void k_encode(const void *__restrict__ keys, c
     if (tid < a.levels) out[tok * a.token_stride + (long long)g * a.head_stride + tid] = (uint8_t)chosen[tid];
 }
 
-// Index-form keys, few tokens (a decode step appends one token per sequence): the levels are a dependent chain,
-// so what counts is the latency of one level.  The rows of level l + 1 do not depend on the residual: they travel
-// from memory straight into LDS (global_load_lds_dwordx4: 16 bytes per lane, no register destination) while
-// level l is searched, into the other half of a double buffer; a level then reads its rows -- and the winning
-// row for the residual update -- from LDS instead of waiting for memory twice.  Image of a level: row-major,
-// [256 rows][16 slots] x 16 bytes, with piece x of row t in slot (x + t) mod 16 of its row: a thread then reads its
-// own row without bank conflicts, and one load instruction (64 lanes -> 64 consecutive slots from the slot in
-// M0) still covers four whole rows = 1 KiB of contiguous memory, only permuted within each row: lane (r, col) of
-// the instruction fetches piece (col - t) mod 16 of row t = first row + r.  (One row per lane, the obvious
-// mapping, touches 64 different cache lines per instruction: 2 us per level instead of 0.5.)
-// The loads are issued from inline asm: the compiler
-// then knows nothing of them and makes no LDS access wait for them; the kernel waits itself (s_waitcnt vmcnt(0))
-// at the top of the next level.  No static LDS: the images sit at LDS address 0.
-constexpr int kEdImg = 16 * 256;  // 16-byte pieces of one level's rows
-constexpr int kEdLds = 2 * kEdImg * 16 + kD * 4 + 8 * 4 + 8 * 4 + 32 * 4;
-__global__ __launch_bounds__(256) void k_encode_dma(const void *__restrict__ keys, const uint4 *__restrict__ cb,
-                                                    const float *__restrict__ norms, uint8_t *__restrict__ out, const EncodeDims a)
-{
-    extern __shared__ __attribute__((aligned(16))) uint4 ed_lds[];
-    uint4 *img = ed_lds;                                              // [2][16][256]
-    float *res = reinterpret_cast<float *>(ed_lds + 2 * kEdImg);      // [d]
-    float *wbest = res + kD;                                          // [2][4]
-    int *wcand = reinterpret_cast<int *>(wbest + 8);                  // [2][4]
-    int *chosen = wcand + 8;                                          // [32]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int g = blockIdx.x % a.Hkv;
-    const size_t tok = blockIdx.x / a.Hkv;
-    const uint4 *rows = cb + (size_t)g * a.levels * kK * 16;  // level 0 of this head; a level is kK * 16 pieces on
-    auto dma_level = [&](int l, int buf) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {  // instruction i of the wavefront: rows 64 wave + 4 i .. + 3
-            const int t = wave * 64 + 4 * i + (lane >> 4);
-            const unsigned slot = __builtin_amdgcn_readfirstlane((unsigned)(buf * kEdImg + (wave * 64 + 4 * i) * 16));
-            lds_dma16(rows + ((size_t)l * kK + t) * 16 + ((lane - t) & 15), slot * 16u);
-        }
-    };
-    dma_level(0, 0);
-    if (tid < kD) {
-        const size_t i = (tok * a.Hkv + g) * kD + tid;
-        res[tid] = a.key_bf16 ? __builtin_bit_cast(float, (unsigned)static_cast<const uint16_t *>(keys)[i] << 16)
-                              : static_cast<const float *>(keys)[i];
-    }
-    float nrm = norms[(size_t)g * a.levels * kK + tid];
-    for (int l = 0; l < a.levels; ++l) {
-        const int buf = l & 1;
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's rows of level l have landed
-        __syncthreads();                                   // ... and everybody's; the residual is up to date
-        uint4 pc[16];
-#pragma unroll
-        for (int x = 0; x < 16; ++x) pc[x] = img[buf * kEdImg + tid * 16 + ((x + tid) & 15)];
-        float nrm_next = 0.f;
-        if (l + 1 < a.levels) {
-            // the other image was last read during level l - 1, before the barrier above
-            dma_level(l + 1, buf ^ 1);
-            nrm_next = norms[((size_t)g * a.levels + l + 1) * kK + tid];
-        }
-        float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
-#pragma unroll
-        for (int x = 0; x < 16; ++x) {
-            const unsigned v[4] = {pc[x].x, pc[x].y, pc[x].z, pc[x].w};
-            const float4 r0 = *reinterpret_cast<const float4 *>(res + 8 * x), r1 = *reinterpret_cast<const float4 *>(res + 8 * x + 4);
-            a0 = __builtin_fmaf(r0.x, bf16_lo(v[0]), a0); a1 = __builtin_fmaf(r0.y, bf16_hi(v[0]), a1);
-            a2 = __builtin_fmaf(r0.z, bf16_lo(v[1]), a2); a3 = __builtin_fmaf(r0.w, bf16_hi(v[1]), a3);
-            a0 = __builtin_fmaf(r1.x, bf16_lo(v[2]), a0); a1 = __builtin_fmaf(r1.y, bf16_hi(v[2]), a1);
-            a2 = __builtin_fmaf(r1.z, bf16_lo(v[3]), a2); a3 = __builtin_fmaf(r1.w, bf16_hi(v[3]), a3);
-        }
-        const float best = nrm - 2.f * ((a0 + a1) + (a2 + a3));
-        // argmin over the workgroup, lowest index on ties
-        const float wm = -wave_max(-best);
-        const unsigned long long hit = __ballot(best == wm);
-        if (lane == 0) { wbest[buf * 4 + wave] = wm; wcand[buf * 4 + wave] = wave * 64 + (int)__builtin_ctzll(hit); }
-        __syncthreads();
-        float m = wbest[buf * 4];
-        int c = wcand[buf * 4];
-        for (int w = 1; w < 4; ++w)
-            if (wbest[buf * 4 + w] < m || (wbest[buf * 4 + w] == m && wcand[buf * 4 + w] < c)) { m = wbest[buf * 4 + w]; c = wcand[buf * 4 + w]; }
-        if (tid == 0) chosen[l] = c;
-        if (tid < kD / 2) {  // dword tid of row c: piece tid / 4
-            const unsigned v = reinterpret_cast<const unsigned *>(img)[(buf * kEdImg + c * 16 + (((tid >> 2) + c) & 15)) * 4 + (tid & 3)];
-            res[2 * tid] -= bf16_lo(v);
-            res[2 * tid + 1] -= bf16_hi(v);
-        }
-        nrm = nrm_next;
-    }
-    __syncthreads();
-    if (tid < a.levels) out[tok * a.token_stride + (long long)g * a.head_stride + tid] = (uint8_t)chosen[tid];
-}
-
-// Index-form keys, many tokens at once (prefill-sized chunks): the dot products of a level are a
-// (256 rows x 128) x (128 x tokens) matrix product, so they run on the matrix cores.  A workgroup takes 64
-// tokens of one KV head (16 per wavefront) and stages the level's 256 bf16 rows in LDS once for all of them.
-// The fp32 residual of a token is split EXACTLY into three bf16 parts (its 24 mantissa bits are 8 + 8 + 8:
-// truncate, subtract, truncate, subtract), each multiplied with the exact bf16 rows and accumulated in fp32:
-// the same dot product as the fp32 FMA chain of k_encode up to summation order.
-//   first operand : 16 rows x 32 elements from LDS (row stride 288 bytes: the 16 lanes of a k-group and the two
-//                   k-groups that are checked together hit different banks)
+// Index-form vectors, bf16 codebooks.  The dot products of a level are a (256 rows x 128) x (128 x tokens) matrix
+// product, so they run on the matrix cores, for one token as for thousands.  The fp32 residual of a token is split
+// EXACTLY into three bf16 parts (its 24 mantissa bits are 8 + 8 + 8: truncate, subtract, truncate, subtract), each
+// multiplied with the exact bf16 rows and accumulated in fp32: the same dot product as an fp32 FMA chain up to
+// summation order.
+//   first operand : 16 rows x 32 elements from LDS
 //   second operand: lane (n, g) supplies elements 32 kc + 8 g .. + 7 of token n, the part of the residual it keeps
 //   result        : lane (n, g) receives rows 4 g .. 4 g + 3 of the row tile for token n
-constexpr int kEbTokens = 64;
-constexpr int kEbRowBytes = 288;
-constexpr int kEbLds = 256 * kEbRowBytes + 256 * 4 + (kEbTokens * 32);
-__global__ __launch_bounds__(256) void k_encode_batch(const void *__restrict__ keys, const uint4 *__restrict__ cb,
-                                                      const float *__restrict__ norms, uint8_t *__restrict__ out,
-                                                      const EncodeDims a, int n_tokens)
+// The levels are a dependent chain, but the rows of level l + 1 do not depend on the residual: they travel from memory
+// straight into LDS (16 bytes per lane, no register destination) while level l is searched, into the other half of a
+// double buffer.  Piece x of row t sits in slot x xor (t mod 16) of its row: the operand reads are free of bank
+// conflicts, and a load instruction (64 lanes -> 64 consecutive slots) still covers 1 KiB of contiguous memory.
+// Eight wavefronts: 8 / RS sets of 16 tokens, the 256 rows of a level shared by the RS wavefronts of a set, which
+// exchange their minima through LDS.  RS = 1 (128 tokens) has the least work per token; its level takes 5.3 us, of which
+// 3.7 the 16 row tiles (192 matrix instructions of 16 clk and 16 x 16 vector ones per wavefront, two wavefronts a SIMD:
+// the two kinds do not overlap), 0.6 the update, 0.5 the split and 0.4 waiting for rows.  RS = 8 (16 tokens) has the
+// shortest level, 1.5 us; with a split and an update per wavefront instead of shared ones it was 2.1.
+// 32000 vectors, 32 levels: 179 us, with 64 tokens per workgroup, rows staged through registers and one image 289 us;
+// 64 vectors, 16 levels: 25 us, with a workgroup per vector and fp32 FMAs 32 us.
+// The images sit at LDS address 0: no static LDS here.
+constexpr int kErThreads = 512;
+constexpr int kErImg = 16 * kK;  // 16-byte pieces of one level's rows
+constexpr int kErNorms = 2 * kErImg * 16;              // [2][256] floats
+constexpr int kErPart = kErNorms + 2 * kK * 4;         // [8 wavefronts][16 tokens] minimum and its row
+constexpr int kErSplit = kErPart + 8 * 16 * 8;         // RS >= 4: [sets][3 parts][4 kc][64 lanes] operands of the token sets
+constexpr int er_chosen(int rs) { return kErSplit + (rs >= 4 ? 8 / rs * 12 * 64 * 16 : 0); }  // [tokens][32 levels] bytes
+constexpr int er_lds(int rs) { return er_chosen(rs) + 128 / rs * 32; }
+static_assert(er_lds(1) <= 163840 && er_lds(2) <= 163840 && er_lds(4) <= 163840 && er_lds(8) <= 163840, "LDS of a compute unit");
+template <int RS>
+__global__ __launch_bounds__(kErThreads) void k_encode_rows(const void *__restrict__ keys, const uint4 *__restrict__ cb,
+                                                            const float *__restrict__ norms, uint8_t *__restrict__ out,
+                                                            const EncodeDims a, int n_tokens)
 {
-    extern __shared__ __attribute__((aligned(16))) uint4 eb_lds[];
-    char *rows = reinterpret_cast<char *>(eb_lds);
-    float *nrm = reinterpret_cast<float *>(rows + 256 * kEbRowBytes);
-    uint8_t *chosen = reinterpret_cast<uint8_t *>(nrm + 256);  // [64 tokens][32 levels]
+    extern __shared__ __attribute__((aligned(16))) uint4 er_mem[];
+    char *lds = reinterpret_cast<char *>(er_mem);
+    uint8_t *chosen = reinterpret_cast<uint8_t *>(lds + er_chosen(RS));
+    constexpr int kSets = 8 / RS, kTiles = 16 / RS;
+    constexpr bool kShare = RS >= 4;           // the wavefronts of a set share the update and the split of its residuals
+    constexpr int kOwn = kShare ? 32 / RS : 32;  // elements of its token that a lane keeps: from `own` of its 4 kc x 8
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = lane & 15, gk = lane >> 4;
+    const int set = wave % kSets, rs = wave / kSets;
+    const int own = kShare ? rs * kOwn : 0;
+    uint4_t *split = reinterpret_cast<uint4_t *>(lds + kErSplit) + (kShare ? set * 12 * 64 : 0);
     const int g = blockIdx.x % a.Hkv;
-    const int tl = wave * 16 + n;                                // token within the workgroup
-    const long long tok = (long long)(blockIdx.x / a.Hkv) * kEbTokens + tl;
+    const int tl = set * 16 + n;  // token within the workgroup
+    const long long tok = (long long)(blockIdx.x / a.Hkv) * (16 * kSets) + tl;
     const size_t tokc = (size_t)(tok < n_tokens ? tok : n_tokens - 1);
-    float res[4][8];
+    const uint4 *rows = cb + (size_t)g * a.levels * kErImg;
+    const float *nrows = norms + (size_t)g * a.levels * kK;
+    auto fetch_level = [&](int l, int buf) {
+        const uint4 *src = rows + (size_t)l * kErImg;
 #pragma unroll
-    for (int kc = 0; kc < 4; ++kc) {
-        const size_t i = (tokc * a.Hkv + g) * kD + kc * 32 + 8 * gk;
+        for (int i = 0; i < 8; ++i) {  // instruction i of the wavefront: rows 32 wave + 4 i .. + 3
+            const int r0 = wave * 32 + 4 * i, t = r0 + (lane >> 4);
+            const unsigned slot = __builtin_amdgcn_readfirstlane((unsigned)(buf * kErImg + r0 * 16));
+            lds_dma16(src, (unsigned)(t * 16 + ((lane ^ t) & 15)) * 16u, slot * 16u);
+        }
+        if (wave == 0) lds_dma16(nrows + (size_t)l * kK, (unsigned)lane * 16u, (unsigned)(kErNorms + buf * kK * 4));
+    };
+    fetch_level(0, 0);
+    float res[kOwn];
+#pragma unroll
+    for (int i = 0; i < kOwn; i += 4) {  // elements 32 kc + 8 gk .. + 7 of the token, four at a time
+        const int f = own + i;
+        const size_t at = (tokc * a.Hkv + g) * kD + (f >> 3) * 32 + 8 * gk + (f & 7);
         if (a.key_bf16) {
-            const uint4 v = *reinterpret_cast<const uint4 *>(static_cast<const uint16_t *>(keys) + i);
-            const unsigned w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) { res[kc][2 * e] = bf16_lo(w[e]); res[kc][2 * e + 1] = bf16_hi(w[e]); }
+            const uint2 v = *reinterpret_cast<const uint2 *>(static_cast<const uint16_t *>(keys) + at);
+            res[i] = bf16_lo(v.x); res[i + 1] = bf16_hi(v.x);
+            res[i + 2] = bf16_lo(v.y); res[i + 3] = bf16_hi(v.y);
         } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) res[kc][e] = static_cast<const float *>(keys)[i + e];
+            const float4 v = *reinterpret_cast<const float4 *>(static_cast<const float *>(keys) + at);
+            res[i] = v.x; res[i + 1] = v.y; res[i + 2] = v.z; res[i + 3] = v.w;
         }
     }
     for (int l = 0; l < a.levels; ++l) {
-        const size_t level = (size_t)g * a.levels + l;
-        __syncthreads();  // the previous level's rows are no longer read
-        for (int x = tid; x < 256 * 16; x += 256)
-            *reinterpret_cast<uint4 *>(rows + (x >> 4) * kEbRowBytes + (x & 15) * 16) = cb[level * 256 * 16 + x];
-        nrm[tid] = norms[level * 256 + tid];
-        __syncthreads();
-        // exact three-way bf16 split of the lane's part of the residual, packed as MFMA operands
+        const int buf = l & 1;
+        const char *img = lds + buf * kErImg * 16;
+        const float *nrm = reinterpret_cast<const float *>(lds + kErNorms) + buf * kK;
+        // exact three-way bf16 split of the residuals, packed as MFMA operands
+        unsigned mine[3][kOwn / 2];
+#pragma unroll
+        for (int i = 0; i < kOwn / 2; ++i) {
+            float v0 = res[2 * i], v1 = res[2 * i + 1];
+#pragma unroll
+            for (int s3 = 0; s3 < 3; ++s3) {
+                const unsigned u0 = __builtin_bit_cast(unsigned, v0), u1 = __builtin_bit_cast(unsigned, v1);
+                mine[s3][i] = __builtin_amdgcn_perm(u1, u0, 0x07060302u);  // the upper halves
+                v0 -= __builtin_bit_cast(float, u0 & 0xffff0000u);
+                v1 -= __builtin_bit_cast(float, u1 & 0xffff0000u);
+            }
+        }
+        if (kShare) {
+#pragma unroll
+            for (int s3 = 0; s3 < 3; ++s3) {
+                uint4_t *dst = split + (s3 * 4 + (own >> 3)) * 64 + lane;
+                if constexpr (RS == 4) *dst = uint4_t{mine[s3][0], mine[s3][1], mine[s3][2], mine[s3][3]};
+                if constexpr (RS == 8) reinterpret_cast<uint2_t *>(dst)[rs & 1] = uint2_t{mine[s3][0], mine[s3][1]};
+            }
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's rows of level l have landed
+        __syncthreads();                                   // ... and everybody's; the other image is no longer read
+        if (l + 1 < a.levels) fetch_level(l + 1, buf ^ 1);
         uint4_t part[3][4];
 #pragma unroll
-        for (int kc = 0; kc < 4; ++kc)
+        for (int s3 = 0; s3 < 3; ++s3)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                float v0 = res[kc][2 * e], v1 = res[kc][2 * e + 1];
-#pragma unroll
-                for (int s3 = 0; s3 < 3; ++s3) {
-                    const unsigned t0 = __builtin_bit_cast(unsigned, v0) & 0xffff0000u, t1 = __builtin_bit_cast(unsigned, v1) & 0xffff0000u;
-                    part[s3][kc][e] = (t0 >> 16) | t1;
-                    v0 -= __builtin_bit_cast(float, t0);
-                    v1 -= __builtin_bit_cast(float, t1);
-                }
+            for (int kc = 0; kc < 4; ++kc) {
+                if constexpr (kShare) part[s3][kc] = split[(s3 * 4 + kc) * 64 + lane];
+                else part[s3][kc] = uint4_t{mine[s3][4 * kc], mine[s3][4 * kc + 1], mine[s3][4 * kc + 2], mine[s3][4 * kc + 3]};
             }
         float best = INFINITY;
         int brow = 0;
 #pragma unroll 2
-        for (int rt = 0; rt < 16; ++rt) {
+        for (int t = 0; t < kTiles; ++t) {
+            const int rt = rs * kTiles + t;
             floatx4_t D = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int kc = 0; kc < 4; ++kc) {
-                const uint4 pc = *reinterpret_cast<const uint4 *>(rows + (rt * 16 + n) * kEbRowBytes + kc * 64 + gk * 16);
+                const uint4 pc = *reinterpret_cast<const uint4 *>(img + (rt * 16 + n) * 256 + ((4 * kc + gk) ^ n) * 16);
                 const uint4_t pv = {pc.x, pc.y, pc.z, pc.w};
                 const bf16x8_t A = __builtin_bit_cast(bf16x8_t, pv);
 #pragma unroll
@@ -258,34 +242,41 @@ __global__ __launch_bounds__(256) void k_encode_batch(const void *__restrict__ k
                 if (sc < best) { best = sc; brow = rt * 16 + 4 * gk + r; }  // rows come in increasing order: ties keep the lowest
             }
         }
-        // the four lanes of a token hold the minima of disjoint row sets
+        min4(best, brow);  // the four lanes of a token hold the minima of disjoint row sets
+        if (RS > 1) {  // ... and so do the RS wavefronts of a token set
+            float2 *pm = reinterpret_cast<float2 *>(lds + kErPart);
+            if (gk == 0) pm[wave * 16 + n] = make_float2(best, __builtin_bit_cast(float, brow));
+            __syncthreads();
+            float2 m = pm[set * 16 + n];
 #pragma unroll
-        for (int off = 16; off <= 32; off <<= 1) {
-            const float ov = __shfl_xor(best, off);
-            const int orow = __shfl_xor(brow, off);
-            if (ov < best || (ov == best && orow < brow)) { best = ov; brow = orow; }
+            for (int w = 1; w < RS; ++w) {
+                const float2 o = pm[(w * kSets + set) * 16 + n];
+                if (o.x < m.x) m = o;  // rows come in increasing order
+            }
+            brow = __builtin_bit_cast(int, m.y);
         }
-        if (gk == 0) chosen[tl * 32 + l] = (uint8_t)brow;
-        // residual -= chosen row (the lane's 32 elements of it)
+        if (gk == 0 && rs == 0) chosen[tl * 32 + l] = (uint8_t)brow;
+        // residual -= chosen row (the lane's elements of it)
 #pragma unroll
-        for (int kc = 0; kc < 4; ++kc) {
-            const uint4 pc = *reinterpret_cast<const uint4 *>(rows + brow * kEbRowBytes + kc * 64 + gk * 16);
-            const unsigned w[4] = {pc.x, pc.y, pc.z, pc.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) { res[kc][2 * e] -= bf16_lo(w[e]); res[kc][2 * e + 1] -= bf16_hi(w[e]); }
+        for (int i = 0; i < kOwn; i += 4) {
+            const int f = own + i;
+            const uint2 w = *reinterpret_cast<const uint2 *>(img + brow * 256 + ((4 * (f >> 3) + gk) ^ (brow & 15)) * 16 + (f & 4) * 2);
+            res[i] -= bf16_lo(w.x); res[i + 1] -= bf16_hi(w.x);
+            res[i + 2] -= bf16_lo(w.y); res[i + 3] -= bf16_hi(w.y);
         }
     }
     __syncthreads();
-    if (tok < n_tokens) {
+    if (tok < n_tokens && rs == 0) {
         uint8_t *dst = out + tok * a.token_stride + (long long)g * a.head_stride;
         for (int l = gk; l < a.levels; l += 4) dst[l] = chosen[tl * 32 + l];
     }
 }
 
-// Paired-format keys, many tokens at once.  Same scheme as k_encode_batch for the two sets of 64 dot products of a
+// Paired-format keys, many tokens at once.  Same scheme as k_encode_rows for the two sets of 64 dot products of a
 // level -- P[a] = res . C[a] and Q[b] = res . (i C[b]) = res' . C[b] with res' = (res_y, -res_x) per sub-space, whose
 // bf16 parts are the parts of res with halves swapped and one sign flipped -- then every lane scans 16 x 64 of the
 // token's 4096 centres:  ||c_ab||^2 - 2 res . c_ab = (N[a] - 2 P[a]) + (N[b] - 2 Q[b]) + X[a][b].
+constexpr int kEbTokens = 64;  // tokens of a workgroup
 constexpr int kEpRowBytes = 288;
 constexpr int kEpVecBytes = 272;  // padded stride of a token's 64 floats: 16 tokens hit 64 different banks
 constexpr int kEpLds = 64 * kEpRowBytes + 64 * 64 * 4 + 64 * 4 + 2 * kEbTokens * kEpVecBytes + kEbTokens * 64;
@@ -664,6 +655,40 @@ commvq_status encoder_prepare(commvq_handle *h, bool values, const void *cb, voi
     return hipGetLastError() == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;
 }
 
+template <int RS>
+commvq_status launch_encode_rows(const void *keys, const void *cb, const float *norms, uint8_t *out, const EncodeDims &d, int n_tokens,
+                                 hipStream_t s)
+{
+    static std::atomic<uint64_t> lds_ok{0};
+    if (allow_dynamic_lds(&k_encode_rows<RS>, er_lds(RS), lds_ok) != hipSuccess) return COMMVQ_ERR_LAUNCH;
+    constexpr int per_wg = 16 * (8 / RS);
+    hipLaunchKernelGGL(k_encode_rows<RS>, dim3((unsigned)((n_tokens + per_wg - 1) / per_wg * d.Hkv)), dim3(kErThreads), er_lds(RS), s, keys,
+                       static_cast<const uint4 *>(cb), norms, out, d, n_tokens);
+    return hipGetLastError() == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;
+}
+
+commvq_status encode_rows(const void *keys, const void *cb, const float *norms, uint8_t *out, const EncodeDims &d, int n_tokens,
+                          hipStream_t s)
+{
+    // A compute unit holds one workgroup, so a launch of up to 256 is one round, and a round is the cheaper the more
+    // wavefronts share a token set: 32 levels of 8 heads take 47 us with RS = 8 (up to 512 tokens), 76 (4; 1024), 112
+    // (2; 2048), 172 (1; 4096).  So full rounds go to RS = 1, and the rest to the largest RS that needs one round:
+    // 4097 tokens in one launch of RS = 1 would take 323 us.
+    const int64_t round = 128 * (int64_t)std::max(1, 256 / d.Hkv);
+    const int full = (int)(n_tokens / round * round), rest = n_tokens - full;
+    if (full) {
+        const commvq_status st = launch_encode_rows<1>(keys, cb, norms, out, d, full, s);
+        if (st != COMMVQ_OK || !rest) return st;
+        keys = static_cast<const char *>(keys) + (size_t)full * d.Hkv * kD * (d.key_bf16 ? 2 : 4);
+        out += full * d.token_stride;
+    }
+    auto one_round = [&](int per_wg) { return (int64_t)(rest + per_wg - 1) / per_wg * d.Hkv <= 256; };
+    if (one_round(16)) return launch_encode_rows<8>(keys, cb, norms, out, d, rest, s);
+    if (one_round(32)) return launch_encode_rows<4>(keys, cb, norms, out, d, rest, s);
+    if (one_round(64)) return launch_encode_rows<2>(keys, cb, norms, out, d, rest, s);
+    return launch_encode_rows<1>(keys, cb, norms, out, d, rest, s);
+}
+
 commvq_status encode_vectors(commvq_handle *h, bool values, const void *keys, int32_t n_tokens, const void *key_cb, const void *tables,
                              uint8_t *codes_out, int64_t token_stride, int64_t head_stride, void *stream)
 {
@@ -697,16 +722,8 @@ commvq_status encode_vectors(commvq_handle *h, bool values, const void *keys, in
         static std::atomic<uint64_t> lds_ok{0};
         if (allow_dynamic_lds(&k_encode_lds<true>, lds, lds_ok) != hipSuccess) return COMMVQ_ERR_LAUNCH;
         hipLaunchKernelGGL(k_encode_lds<true>, grid, dim3(256), lds, s, keys, static_cast<const unsigned *>(key_cb), norms, cross, codes_out, d);
-    } else if (bf16 && n_tokens >= kEbTokens) {  // many tokens: rows staged once per 64 tokens, dot products on the matrix cores
-        static std::atomic<uint64_t> lds_ok{0};
-        if (allow_dynamic_lds(&k_encode_batch, kEbLds, lds_ok) != hipSuccess) return COMMVQ_ERR_LAUNCH;
-        const dim3 bgrid((unsigned)((n_tokens + kEbTokens - 1) / kEbTokens * c.n_kv_heads));
-        hipLaunchKernelGGL(k_encode_batch, bgrid, dim3(256), kEbLds, s, keys, static_cast<const uint4 *>(key_cb), norms, codes_out, d,
-                           n_tokens);
-    } else if (bf16) {  // few tokens: next level's rows on their way into LDS while this level is searched
-        static std::atomic<uint64_t> lds_ok{0};
-        if (allow_dynamic_lds(&k_encode_dma, kEdLds, lds_ok) != hipSuccess) return COMMVQ_ERR_LAUNCH;
-        hipLaunchKernelGGL(k_encode_dma, grid, dim3(256), kEdLds, s, keys, static_cast<const uint4 *>(key_cb), norms, codes_out, d);
+    } else if (bf16) {
+        return encode_rows(keys, key_cb, norms, codes_out, d, n_tokens, s);
     } else {
         hipLaunchKernelGGL(k_encode<false>, grid, dim3(256), 0, s, keys, key_cb, norms, codes_out, d);
     }
