@@ -60,6 +60,18 @@ __device__ __forceinline__ void min4(float &best, int &index)
     lower(b32[0], b32[1], i32[0], i32[1]);
 }
 
+// The same over the two halves of a wavefront: lanes l and l ^ 32.
+__device__ __forceinline__ void min2_halves(float &best, int &index)
+{
+    const unsigned b = __builtin_bit_cast(unsigned, best), i = (unsigned)index;
+    auto b32 = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+    auto i32 = __builtin_amdgcn_permlane32_swap(i, i, false, false);
+    const float f0 = __builtin_bit_cast(float, (unsigned)b32[0]), f1 = __builtin_bit_cast(float, (unsigned)b32[1]);
+    const bool second = f1 < f0 || (f1 == f0 && (int)i32[1] < (int)i32[0]);
+    best = second ? f1 : f0;
+    index = second ? (int)i32[1] : (int)i32[0];
+}
+
 struct EncodeDims {
     int Hkv, levels, K, key_bf16, record_bytes;
     long long token_stride, head_stride;
@@ -272,35 +284,56 @@ __global__ __launch_bounds__(kErThreads) void k_encode_rows(const void *__restri
     }
 }
 
-// Paired-format keys, many tokens at once.  Same scheme as k_encode_rows for the two sets of 64 dot products of a
-// level -- P[a] = res . C[a] and Q[b] = res . (i C[b]) = res' . C[b] with res' = (res_y, -res_x) per sub-space, whose
-// bf16 parts are the parts of res with halves swapped and one sign flipped -- then every lane scans 16 x 64 of the
-// token's 4096 centres:  ||c_ab||^2 - 2 res . c_ab = (N[a] - 2 P[a]) + (N[b] - 2 Q[b]) + X[a][b].
-constexpr int kEbTokens = 64;  // tokens of a workgroup
-constexpr int kEpRowBytes = 288;
-constexpr int kEpVecBytes = 272;  // padded stride of a token's 64 floats: 16 tokens hit 64 different banks
-constexpr int kEpLds = 64 * kEpRowBytes + 64 * 64 * 4 + 64 * 4 + 2 * kEbTokens * kEpVecBytes + kEbTokens * 64;
-__global__ __launch_bounds__(256) void k_encode_pair_batch(const void *__restrict__ keys, const uint4 *__restrict__ cb,
-                                                           const float *__restrict__ norms, const float *__restrict__ cross,
-                                                           uint8_t *__restrict__ out, const EncodeDims a, int n_tokens)
+// Paired-format keys, many tokens at once.  A level is two sets of 64 dot products, P[a] = res . C[a] and
+// Q[b] = res . (i C[b]), on the matrix cores with the exact split of k_encode_rows, and a scan of the 64 x 64 centres:
+//   ||c_ab||^2 - 2 res . c_ab = U[a] + (V[b] + X[a][b]),  U = N[a] - 2 P[a],  V = N[b] - 2 Q[b]
+// The scan is a minimum over b of V[b] + X[a][b] for every a and token.  The sums are matrix instructions too: for one a
+// and 32 tokens, result[b][token] = V[b][token] + x0 * 1 + x1 * 1 + x2 * 1 with V in the accumulator operand and the exact
+// bf16 parts of X[a][b] along k.  That is 1024 sums in 32 clk where vector adds take 64, and a cross term is read from LDS
+// once for 32 tokens; what is left to the vector unit is half a three-way minimum per centre.
+// Four wavefronts, one per SIMD: 4 / RS sets of 32 tokens.  The RS wavefronts of a set share the rows a of the scan (and
+// compute only their part of P); residual, split and Q are each wavefront's own: handing them round through LDS, with
+// eight wavefronts and the residuals split between two, cost more than it saved (8.9 us a level at RS = 1's sizes).
+// A level takes 8.1 us with RS = 1 (128 tokens), 6.0 (2) and 5.2 (4), of which a row of the scan is 50 ns: two matrix
+// instructions (64 clk) and 21 vector ones (90 clk) that hide in each other only where they alternate in the program, so
+// the order is fixed below (left to the compiler: 90 ns).  32000 vectors, 21 levels: 172 us, 8192 vectors 113; with the
+// scan's sums on the vector unit and cross terms read per 16 tokens 258 and 165.
+//   32 x 32 operands: lane (n, h) supplies row / token n and elements 8 h .. + 7 of a chunk of 16 (scan: 4 h .. + 3 of 8)
+//   32 x 32 result  : lane (n, h) receives, in register i, row 8 (i / 4) + 4 h + i % 4 for token n
+// A level's tables do not depend on the residual: they are fetched into registers one level ahead.
+constexpr int kEpThreads = 256;
+constexpr int kEpRows = 0;                          // [C | i C][64] rows of 256 bytes, piece x of row t in slot x xor (t mod 16)
+constexpr int kEpParts = 2 * 64 * 256;              // [64 a][64 b] x0, x1, x2, 0 of the cross terms, 8 bytes each
+constexpr int kEpCross = kEpParts + 4096 * 8;       // [64 a][64 b] cross terms, float4 x of row a in slot x xor (a mod 16)
+constexpr int kEpNorms = kEpCross + 4096 * 4;       // [64]
+constexpr int kEpMin = kEpNorms + 64 * 4;           // [4 wavefronts][32 tokens] minimum and its row
+constexpr int kEpChosen = kEpMin + 4 * 32 * 8;      // [tokens][32 levels][2]
+constexpr int ep_lds(int rs) { return kEpChosen + 128 / rs * 64; }
+static_assert(ep_lds(1) <= 163840, "LDS of a compute unit");
+typedef float floatx16_t __attribute__((ext_vector_type(16)));
+typedef short shortx4_t __attribute__((ext_vector_type(4)));
+template <int RS>
+__global__ __launch_bounds__(kEpThreads, 2) void k_encode_pairs(const void *__restrict__ keys, const uint4 *__restrict__ cb,
+                                                             const float *__restrict__ norms, const float *__restrict__ cross,
+                                                             uint8_t *__restrict__ out, const EncodeDims a, int n_tokens)
 {
-    extern __shared__ __attribute__((aligned(16))) uint4 ep_lds[];
-    char *rows = reinterpret_cast<char *>(ep_lds);                        // [64][288 B]
-    float *xs = reinterpret_cast<float *>(rows + 64 * kEpRowBytes);       // [64][64]
-    float *nrm = xs + 64 * 64;                                            // [64]
-    char *uvec = reinterpret_cast<char *>(nrm + 64);                      // [64 tokens][272 B]: N[a] - 2 P[a]
-    char *vvec = uvec + kEbTokens * kEpVecBytes;                          // [64 tokens][272 B]: N[b] - 2 Q[b]
-    uint8_t *chosen = reinterpret_cast<uint8_t *>(vvec + kEbTokens * kEpVecBytes);  // [64 tokens][32 levels][2]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int n = lane & 15, gk = lane >> 4;
+    extern __shared__ __attribute__((aligned(16))) uint4 ep_mem[];
+    char *lds = reinterpret_cast<char *>(ep_mem);
+    float *nrm = reinterpret_cast<float *>(lds + kEpNorms);
+    uint8_t *chosen = reinterpret_cast<uint8_t *>(lds + kEpChosen);
+    constexpr int kSets = 4 / RS, kTiles = RS == 1 ? 2 : 1, kPairs = 32 / RS;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 31, h = lane >> 5;
+    const int set = wave % kSets, rs = wave / kSets;
+    const int a0 = 64 / RS * rs;  // the wavefront's first row a; its tile of P begins at a0 & 32
     const int g = blockIdx.x % a.Hkv;
-    const int tl = wave * 16 + n;
-    const long long tok = (long long)(blockIdx.x / a.Hkv) * kEbTokens + tl;
+    const int tl = set * 32 + n;
+    const long long tok = (long long)(blockIdx.x / a.Hkv) * (32 * kSets) + tl;
     const size_t tokc = (size_t)(tok < n_tokens ? tok : n_tokens - 1);
-    float res[4][8];
+    float res[8][8];  // dimensions 16 kc + 8 h .. + 7
 #pragma unroll
-    for (int kc = 0; kc < 4; ++kc) {
-        const size_t i = (tokc * a.Hkv + g) * kD + kc * 32 + 8 * gk;
+    for (int kc = 0; kc < 8; ++kc) {
+        const size_t i = (tokc * a.Hkv + g) * kD + 16 * kc + 8 * h;
         if (a.key_bf16) {
             const uint4 v = *reinterpret_cast<const uint4 *>(static_cast<const uint16_t *>(keys) + i);
             const unsigned w[4] = {v.x, v.y, v.z, v.w};
@@ -311,153 +344,205 @@ __global__ __launch_bounds__(256) void k_encode_pair_batch(const void *__restric
             for (int e = 0; e < 8; ++e) res[kc][e] = static_cast<const float *>(keys)[i + e];
         }
     }
-    // a level's tables do not depend on the residual: they are fetched into registers one level ahead
-    uint4 prow0, prow1, prow2, prow3;
-    float4 pcr0, pcr1, pcr2, pcr3;
+    uint4 prow[4];
+    float4 pcross[4];
     float pnorm = 0.f;
-#define COMMVQ_EP_FETCH(l_)                                                                        \
-    {                                                                                              \
-        const size_t level_ = (size_t)g * a.levels + (l_);                                         \
-        const uint4 *r_ = cb + level_ * 64 * 16 + tid;                                             \
-        const float4 *c_ = reinterpret_cast<const float4 *>(cross + level_ * 64 * 64) + tid;       \
-        prow0 = r_[0]; prow1 = r_[256]; prow2 = r_[512]; prow3 = r_[768];                          \
-        pcr0 = c_[0]; pcr1 = c_[256]; pcr2 = c_[512]; pcr3 = c_[768];                              \
-        if (tid < 64) pnorm = norms[level_ * 64 + tid];                                            \
-    }
-    COMMVQ_EP_FETCH(0)
-    for (int l = 0; l < a.levels; ++l) {
-        __syncthreads();  // the previous level's tables are no longer read
-        {
-            char *rp = rows + (tid >> 4) * kEpRowBytes + (tid & 15) * 16;  // element tid + 256 x: 16 rows further on
-            *reinterpret_cast<uint4 *>(rp) = prow0;
-            *reinterpret_cast<uint4 *>(rp + 16 * kEpRowBytes) = prow1;
-            *reinterpret_cast<uint4 *>(rp + 32 * kEpRowBytes) = prow2;
-            *reinterpret_cast<uint4 *>(rp + 48 * kEpRowBytes) = prow3;
-            float4 *xp = reinterpret_cast<float4 *>(xs) + tid;
-            xp[0] = pcr0; xp[256] = pcr1; xp[512] = pcr2; xp[768] = pcr3;
+    auto fetch_level = [&](int l) {
+        const size_t level = (size_t)g * a.levels + l;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            prow[x] = cb[level * 64 * 16 + x * 256 + tid];
+            pcross[x] = reinterpret_cast<const float4 *>(cross + level * 4096)[x * 256 + tid];
+        }
+        if (tid < 64) pnorm = norms[level * 64 + tid];
+    };
+    auto park_level = [&]() {
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            const int p = x * 256 + tid, t = p >> 4, slot = (p ^ t) & 15;  // row t, piece / float4 p mod 16
+            uint4 *dst = reinterpret_cast<uint4 *>(lds + kEpRows + t * 256 + slot * 16);
+            dst[0] = prow[x];
+            const unsigned w[4] = {prow[x].x, prow[x].y, prow[x].z, prow[x].w};
+            unsigned r[4];  // (x, y) -> (-y, x)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) r[e] = __builtin_amdgcn_alignbit(w[e], w[e], 16) ^ 0x8000u;
+            dst[64 * 16] = make_uint4(r[0], r[1], r[2], r[3]);
+            *reinterpret_cast<float4 *>(lds + kEpCross + t * 256 + slot * 16) = pcross[x];
+            const float xv[4] = {pcross[x].x, pcross[x].y, pcross[x].z, pcross[x].w};
+            unsigned pr[8];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const unsigned u0 = __builtin_bit_cast(unsigned, xv[e]);
+                const float v1 = xv[e] - __builtin_bit_cast(float, u0 & 0xffff0000u);
+                const unsigned u1 = __builtin_bit_cast(unsigned, v1);
+                const float v2 = v1 - __builtin_bit_cast(float, u1 & 0xffff0000u);
+                pr[2 * e] = __builtin_amdgcn_perm(u1, u0, 0x07060302u);
+                pr[2 * e + 1] = __builtin_bit_cast(unsigned, v2) >> 16;
+            }
+            uint4 *pd = reinterpret_cast<uint4 *>(lds + kEpParts + p * 32);
+            pd[0] = make_uint4(pr[0], pr[1], pr[2], pr[3]);
+            pd[1] = make_uint4(pr[4], pr[5], pr[6], pr[7]);
         }
         if (tid < 64) nrm[tid] = pnorm;
-        if (l + 1 < a.levels) COMMVQ_EP_FETCH(l + 1)
+    };
+    // three ones along k in the lanes of the lower half, nothing in the upper: every cross term enters once
+    const uint2_t ones_bits = h ? uint2_t{0u, 0u} : uint2_t{0x3f803f80u, 0x3f80u};
+    const shortx4_t ones = __builtin_bit_cast(shortx4_t, ones_bits);
+    fetch_level(0);
+    for (int l = 0; l < a.levels; ++l) {
+        __syncthreads();  // the previous level's tables are no longer read
+        park_level();
         __syncthreads();
-        uint4_t part[3][4];
+        floatx16_t P[kTiles], V[2];
 #pragma unroll
-        for (int kc = 0; kc < 4; ++kc)
+        for (int t = 0; t < kTiles; ++t) P[t] = floatx16_t{0.f};
+        V[0] = V[1] = floatx16_t{0.f};
+#pragma unroll
+        for (int kc = 0; kc < 8; ++kc) {
+            uint4_t part[3];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 float v0 = res[kc][2 * e], v1 = res[kc][2 * e + 1];
 #pragma unroll
                 for (int s3 = 0; s3 < 3; ++s3) {
-                    const unsigned t0 = __builtin_bit_cast(unsigned, v0) & 0xffff0000u, t1 = __builtin_bit_cast(unsigned, v1) & 0xffff0000u;
-                    part[s3][kc][e] = (t0 >> 16) | t1;
-                    v0 -= __builtin_bit_cast(float, t0);
-                    v1 -= __builtin_bit_cast(float, t1);
+                    const unsigned u0 = __builtin_bit_cast(unsigned, v0), u1 = __builtin_bit_cast(unsigned, v1);
+                    part[s3][e] = __builtin_amdgcn_perm(u1, u0, 0x07060302u);  // the upper halves
+                    v0 -= __builtin_bit_cast(float, u0 & 0xffff0000u);
+                    v1 -= __builtin_bit_cast(float, u1 & 0xffff0000u);
                 }
             }
-        // P and Q for the 64 rows, 16 at a time; lane (n, gk) receives rows 16 rt + 4 gk .. + 3 of token n
+            bf16x8_t A[kTiles + 2];
 #pragma unroll
-        for (int rt = 0; rt < 4; ++rt) {
-            floatx4_t DP = {0.f, 0.f, 0.f, 0.f}, DQ = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int kc = 0; kc < 4; ++kc) {
-                const uint4 pc = *reinterpret_cast<const uint4 *>(rows + (rt * 16 + n) * kEpRowBytes + kc * 64 + gk * 16);
+            for (int t = 0; t < kTiles + 2; ++t) {
+                const int row = (t < kTiles ? (RS == 1 ? 32 * t : (a0 & 32)) : 64 + 32 * (t - kTiles)) + n;
+                const uint4 pc = *reinterpret_cast<const uint4 *>(lds + kEpRows + row * 256 + ((2 * kc + h) ^ (n & 15)) * 16);
                 const uint4_t pv = {pc.x, pc.y, pc.z, pc.w};
-                const bf16x8_t A = __builtin_bit_cast(bf16x8_t, pv);
-#pragma unroll
-                for (int s3 = 0; s3 < 3; ++s3) {
-                    DP = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, __builtin_bit_cast(bf16x8_t, part[s3][kc]), DP, 0, 0, 0);
-                    uint4_t rot;  // (x, y) -> (y, -x): swap the halves, flip the sign of the new upper half
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) rot[e] = __builtin_amdgcn_alignbit(part[s3][kc][e], part[s3][kc][e], 16) ^ 0x80000000u;
-                    DQ = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, __builtin_bit_cast(bf16x8_t, rot), DQ, 0, 0, 0);
-                }
+                A[t] = __builtin_bit_cast(bf16x8_t, pv);
             }
-            const float4 nr = *reinterpret_cast<const float4 *>(nrm + rt * 16 + 4 * gk);
-            *reinterpret_cast<float4 *>(uvec + tl * kEpVecBytes + (rt * 16 + 4 * gk) * 4) =
-                make_float4(nr.x - 2.f * DP[0], nr.y - 2.f * DP[1], nr.z - 2.f * DP[2], nr.w - 2.f * DP[3]);
-            *reinterpret_cast<float4 *>(vvec + tl * kEpVecBytes + (rt * 16 + 4 * gk) * 4) =
-                make_float4(nr.x - 2.f * DQ[0], nr.y - 2.f * DQ[1], nr.z - 2.f * DQ[2], nr.w - 2.f * DQ[3]);
-        }
-        __syncthreads();
-        // scan in two stages, with the result of a sequential scan in increasing a * 64 + b under a strict "<":
-        // rounding is monotone, so min over b of fl(u + t[b]) is fl(u + min t[b]), and stage one needs only an add
-        // and half a three-way minimum per centre.  Lane (n, gk) takes a = 16 gk .. 16 gk + 15 and all b of token n.
-        float vb[64];
 #pragma unroll
-        for (int b4 = 0; b4 < 16; ++b4) {
-            const float4 v4 = *reinterpret_cast<const float4 *>(vvec + tl * kEpVecBytes + b4 * 16);
-            vb[4 * b4] = v4.x; vb[4 * b4 + 1] = v4.y; vb[4 * b4 + 2] = v4.z; vb[4 * b4 + 3] = v4.w;
+            for (int s3 = 0; s3 < 3; ++s3)
+#pragma unroll
+                for (int t = 0; t < kTiles + 2; ++t) {
+                    floatx16_t &d = t < kTiles ? P[t] : V[t - kTiles];
+                    d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[t], __builtin_bit_cast(bf16x8_t, part[s3]), d, 0, 0, 0);
+                }
         }
+        if (l + 1 < a.levels) fetch_level(l + 1);
+        float U[kPairs];  // of row a0 + 8 (i / 4) + 4 h + i % 4
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const float4 nr = *reinterpret_cast<const float4 *>(nrm + 8 * q + 4 * h);
+            const float nv[4] = {nr.x, nr.y, nr.z, nr.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) V[q >> 2][4 * (q & 3) + e] = nv[e] - 2.f * V[q >> 2][4 * (q & 3) + e];
+        }
+#pragma unroll
+        for (int q = 0; q < kPairs / 4; ++q) {
+            const float4 nr = *reinterpret_cast<const float4 *>(nrm + a0 + 8 * q + 4 * h);
+            const float nv[4] = {nr.x, nr.y, nr.z, nr.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float p;
+                if constexpr (RS == 1) p = P[q >> 2][4 * (q & 3) + e];
+                else if constexpr (RS == 2) p = P[0][4 * q + e];
+                else p = rs & 1 ? P[0][8 + 4 * q + e] : P[0][4 * q + e];
+                U[4 * q + e] = nv[e] - 2.f * p;
+            }
+        }
+        // stage one: the row a of the nearest centre.  The sums of a row are issued before the minimum of the row
+        // before it is taken; a pair of rows (r, r + 4) gives each half of the wavefront one of them to finish.
         float best = INFINITY;
-        int ca = 0;
+        int bi = 0;
         {
-            // the cross terms are read a quarter row (four float4) ahead of their use; the read ahead of the last
-            // quarter of row 63 lands on the norms that follow the cross table in LDS and is not used
-            const float4 *xrow = reinterpret_cast<const float4 *>(xs) + 16 * gk * 16;
-            float4 cur[4], nxt[4];
+            const uint2_t *xs = reinterpret_cast<const uint2_t *>(lds + kEpParts) + a0 * 64 + n;
+            auto row_of = [](int k) { return 8 * (k >> 3) + ((k >> 1) & 3) + 4 * (k & 1); };  // k-th row in the order of the pairs
+            // the minimum as the median with -inf: fminf of values that might be NaN is preceded by a quieting of each
+            const float low = __builtin_bit_cast(float, opaque_sgpr(0xff800000u));
+            auto least = [&](float x, float y) { return __builtin_amdgcn_fmed3f(x, y, low); };
+            floatx16_t D[2][2];
+            uint2_t x0 = xs[0], x1 = xs[32];
+            float half[2] = {0.f, 0.f}, m0 = 0.f, m1 = 0.f;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) cur[q] = xrow[q];
-            for (int ai = 0; ai < 16; ++ai) {
-                float m = INFINITY;
+            for (int k = 0; k <= 2 * kPairs; ++k) {
+                const int cur = k & 1, old = cur ^ 1;
+                if (k < 2 * kPairs) D[cur][0] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(__builtin_bit_cast(shortx4_t, x0), ones, V[0], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (k > 0) {
+                    m0 = least(D[old][0][0], D[old][0][1]);
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) nxt[q] = xrow[ai * 16 + (c + 1) * 4 + q];
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int b = 16 * c + 4 * q;
-                        m = fminf(fminf(m, vb[b] + cur[q].x), vb[b + 1] + cur[q].y);
-                        m = fminf(fminf(m, vb[b + 2] + cur[q].z), vb[b + 3] + cur[q].w);
-                    }
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) cur[q] = nxt[q];
+                    for (int i = 2; i < 16; i += 2) m0 = fminf(fminf(m0, D[old][0][i]), D[old][0][i + 1]);
                 }
-                const int a2 = 16 * gk + ai;
-                const float sc = *reinterpret_cast<const float *>(uvec + tl * kEpVecBytes + a2 * 4) + m;
-                if (sc < best) { best = sc; ca = a2; }
+                __builtin_amdgcn_sched_barrier(0);
+                if (k < 2 * kPairs) {
+                    D[cur][1] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(__builtin_bit_cast(shortx4_t, x1), ones, V[1], 0, 0, 0);
+                    if (k + 1 < 2 * kPairs) { x0 = xs[row_of(k + 1) * 64]; x1 = xs[row_of(k + 1) * 64 + 32]; }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                if (k > 0) {
+                    m1 = least(D[old][1][0], D[old][1][1]);
+#pragma unroll
+                    for (int i = 2; i < 16; i += 2) m1 = fminf(fminf(m1, D[old][1][i]), D[old][1][i + 1]);
+                    half[old] = least(m0, m1);
+                    if (!cur) {
+                        const auto sw = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, half[0]), __builtin_bit_cast(unsigned, half[1]), false, false);
+                        const int i = (k >> 1) - 1;
+                        const float sc = U[i] + least(__builtin_bit_cast(float, (unsigned)sw[0]), __builtin_bit_cast(float, (unsigned)sw[1]));
+                        if (sc < best) { best = sc; bi = i; }  // a lane's rows come in increasing order
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
+        int ca = a0 + 8 * (bi >> 2) + 4 * h + (bi & 3);
+        min2_halves(best, ca);
+        if (RS > 1) {
+            float2 *pm = reinterpret_cast<float2 *>(lds + kEpMin);
+            if (h == 0) pm[wave * 32 + n] = make_float2(best, __builtin_bit_cast(float, ca));
+            __syncthreads();
+            float2 m = pm[set * 32 + n];
 #pragma unroll
-        for (int off = 16; off <= 32; off <<= 1) {
-            const float ov = __shfl_xor(best, off);
-            const int oc = __shfl_xor(ca, off);
-            if (ov < best || (ov == best && oc < ca)) { best = ov; ca = oc; }
-        }
-        // stage two: the lowest b of row ca whose sum rounds to the minimum; the four lanes of a token take 16 b each
-        int cb2 = 64;
-        {
-            const float ua = *reinterpret_cast<const float *>(uvec + tl * kEpVecBytes + ca * 4);
-#pragma unroll
-            for (int b4 = 3; b4 >= 0; --b4) {
-                const float4 v4 = *reinterpret_cast<const float4 *>(vvec + tl * kEpVecBytes + (4 * gk + b4) * 16);
-                const float4 xb = *reinterpret_cast<const float4 *>(xs + ca * 64 + (4 * gk + b4) * 4);
-                const int b0 = 16 * gk + 4 * b4;
-                if (ua + (v4.w + xb.w) == best) cb2 = b0 + 3;
-                if (ua + (v4.z + xb.z) == best) cb2 = b0 + 2;
-                if (ua + (v4.y + xb.y) == best) cb2 = b0 + 1;
-                if (ua + (v4.x + xb.x) == best) cb2 = b0;
+            for (int w = 1; w < RS; ++w) {
+                const float2 o = pm[(w * kSets + set) * 32 + n];
+                if (o.x < m.x) m = o;  // rows come in increasing order
             }
-#pragma unroll
-            for (int off = 16; off <= 32; off <<= 1) cb2 = min(cb2, __shfl_xor(cb2, off));
-            cb2 &= 63;  // always below 64 for finite input; keeps the row read in range otherwise
+            ca = __builtin_bit_cast(int, m.y);
         }
-        if (gk == 0) { chosen[(tl * 32 + l) * 2] = (uint8_t)ca; chosen[(tl * 32 + l) * 2 + 1] = (uint8_t)cb2; }
-        // residual -= C[a] + i C[b]: per sub-space (x_a - y_b, y_a + x_b)
+        // stage two: the partner b of row ca, the lowest of equals
+        float bestb = INFINITY;
+        int cb2 = 0;
 #pragma unroll
-        for (int kc = 0; kc < 4; ++kc) {
-            const uint4 pa = *reinterpret_cast<const uint4 *>(rows + ca * kEpRowBytes + kc * 64 + gk * 16);
-            const uint4 pb = *reinterpret_cast<const uint4 *>(rows + cb2 * kEpRowBytes + kc * 64 + gk * 16);
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int b0 = 32 * t + 8 * q + 4 * h;
+                const float4 x4 = *reinterpret_cast<const float4 *>(lds + kEpCross + ca * 256 + (((b0 >> 2) ^ ca) & 15) * 16);
+                const float xv[4] = {x4.x, x4.y, x4.z, x4.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float sc = V[t][4 * q + e] + xv[e];
+                    if (sc < bestb) { bestb = sc; cb2 = b0 + e; }
+                }
+            }
+        min2_halves(bestb, cb2);
+        if (h == 0 && rs == 0) { chosen[(tl * 32 + l) * 2] = (uint8_t)ca; chosen[(tl * 32 + l) * 2 + 1] = (uint8_t)cb2; }
+        // residual -= C[a] + i C[b]
+#pragma unroll
+        for (int kc = 0; kc < 8; ++kc) {
+            const int piece = 2 * kc + h;
+            const uint4 pa = *reinterpret_cast<const uint4 *>(lds + kEpRows + ca * 256 + (piece ^ (ca & 15)) * 16);
+            const uint4 pb = *reinterpret_cast<const uint4 *>(lds + kEpRows + (64 + cb2) * 256 + (piece ^ (cb2 & 15)) * 16);
             const unsigned wa[4] = {pa.x, pa.y, pa.z, pa.w}, wb[4] = {pb.x, pb.y, pb.z, pb.w};
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                res[kc][2 * e] -= bf16_lo(wa[e]) - bf16_hi(wb[e]);
-                res[kc][2 * e + 1] -= bf16_hi(wa[e]) + bf16_lo(wb[e]);
+                res[kc][2 * e] -= bf16_lo(wa[e]) + bf16_lo(wb[e]);
+                res[kc][2 * e + 1] -= bf16_hi(wa[e]) + bf16_hi(wb[e]);
             }
         }
     }
     __syncthreads();
     if (tok < n_tokens) {
         uint8_t *dst = out + tok * a.token_stride + (long long)g * a.head_stride;
-        for (int byte = gk; byte < a.record_bytes; byte += 4) {
+        for (int byte = 2 * rs + h; byte < a.record_bytes; byte += 2 * RS) {
             unsigned v = 0;
             for (int r = (8 * byte) / 12; r < a.levels && 12 * r < 8 * byte + 8; ++r) {
                 const unsigned pr = (unsigned)chosen[(tl * 32 + r) * 2] | (unsigned)chosen[(tl * 32 + r) * 2 + 1] << 6;
@@ -469,28 +554,24 @@ __global__ __launch_bounds__(256) void k_encode_pair_batch(const void *__restric
     }
 }
 
-#undef COMMVQ_EP_FETCH
-
-// Paired-format keys (and the template's index-form variant, not dispatched: staging 64 KiB of rows that are
-// used once does not pay), shaped for latency (a decode step appends one token per sequence, and the R
-// levels are a dependent chain): the rows, norms and cross terms of level l + 1 do not depend on the
+// Paired-format keys, few tokens: one workgroup per (token, KV head), shaped for latency (a decode step appends one token
+// per sequence, and the R levels are a dependent chain): the rows, norms and cross terms of level l + 1 do not depend on the
 // residual, so they are fetched into registers while level l is searched and parked in the other half
 // of a double-buffered LDS image; every level then runs out of LDS.  Rows are padded to 65 dwords so
 // that 64 lanes reading 64 different rows hit 64 different banks.
 constexpr int kEncRowDw = kD / 2 + 1;  // dwords per padded bf16 row
-template <bool PAIRED>
 __global__ __launch_bounds__(256) void k_encode_lds(const void *__restrict__ keys, const unsigned *__restrict__ cb,
                                                     const float *__restrict__ norms, const float *__restrict__ cross,
                                                     uint8_t *__restrict__ out, const EncodeDims a)
 {
-    constexpr int K = PAIRED ? 64 : 256;
+    constexpr int K = 64;
     constexpr int ROWS_DW = K * kEncRowDw;             // one level's rows
-    constexpr int CROSS = PAIRED ? K * K : 0;
-    constexpr int RPT = K * (kD / 2) / 256;            // row dwords per thread: 16 (paired) or 64
+    constexpr int CROSS = K * K;
+    constexpr int RPT = K * (kD / 2) / 256;            // row dwords per thread
     constexpr int XPT = CROSS / 256;
     extern __shared__ __attribute__((aligned(16))) unsigned enc_lds[];
     unsigned *rows = enc_lds;                                          // [2][K][65]
-    float *xs = reinterpret_cast<float *>(enc_lds + 2 * ROWS_DW);      // [2][K * K]  (paired)
+    float *xs = reinterpret_cast<float *>(enc_lds + 2 * ROWS_DW);      // [2][K * K]
     float *ns = xs + 2 * CROSS;                                        // [2][K]
     float *res = ns + 2 * K;                                           // [d]
     float *dots = res + kD;                                            // [256]
@@ -502,7 +583,7 @@ __global__ __launch_bounds__(256) void k_encode_lds(const void *__restrict__ key
     const size_t tok = blockIdx.x / a.Hkv;
 
     unsigned prow[RPT];
-    float pcross[XPT > 0 ? XPT : 1], pnorm = 0.f;
+    float pcross[XPT], pnorm = 0.f;
     auto fetch_level = [&](int l) {
         const size_t level = (size_t)g * a.levels + l;
 #pragma unroll
@@ -535,40 +616,28 @@ __global__ __launch_bounds__(256) void k_encode_lds(const void *__restrict__ key
         const unsigned *R = rows + buf * ROWS_DW;
         float best = INFINITY;
         int cand = 0x7fffffff;
-        if (!PAIRED) {
-            float acc = 0.f;
+        // thread = (row c, a-dot or b-dot, which half of the sub-spaces); the two halves are added in a fixed order
+        const int c = tid & 63, second = (tid >> 6) & 1, hj = tid >> 7;
+        float acc0 = 0.f, acc1 = 0.f;  // two chains (even / odd sub-spaces), added in a fixed order
 #pragma unroll 16
-            for (int j = 0; j < kJ; ++j) {
-                const unsigned v = R[tid * kEncRowDw + j];
-                acc = __builtin_fmaf(res[2 * j], bf16_lo(v), acc);
-                acc = __builtin_fmaf(res[2 * j + 1], bf16_hi(v), acc);
-            }
-            best = ns[buf * K + tid] - 2.f * acc;
-            cand = tid;
-        } else {
-            // thread = (row c, a-dot or b-dot, which half of the sub-spaces); the two halves are added in a fixed order
-            const int c = tid & 63, second = (tid >> 6) & 1, hj = tid >> 7;
-            float acc0 = 0.f, acc1 = 0.f;  // two chains (even / odd sub-spaces), added in a fixed order
-#pragma unroll 16
-            for (int j = 32 * hj; j < 32 * hj + 32; j += 2) {
-                const unsigned v = R[c * kEncRowDw + j], w = R[c * kEncRowDw + j + 1];
-                const float4 r = *reinterpret_cast<const float4 *>(res + 2 * j);
-                const float x = bf16_lo(v), y = bf16_hi(v), x1 = bf16_lo(w), y1 = bf16_hi(w);
-                acc0 = second ? __builtin_fmaf(r.y, x, __builtin_fmaf(-r.x, y, acc0)) : __builtin_fmaf(r.y, y, __builtin_fmaf(r.x, x, acc0));
-                acc1 = second ? __builtin_fmaf(r.w, x1, __builtin_fmaf(-r.z, y1, acc1)) : __builtin_fmaf(r.w, y1, __builtin_fmaf(r.z, x1, acc1));
-            }
-            dots[tid] = acc0 + acc1;
-            __syncthreads();
-            // candidate k * 256 + tid is the pair (a = 4 k + tid / 64, b = tid % 64): b is the thread's own
-            const int cb2 = tid & (K - 1);
-            const float vb = ns[buf * K + cb2] - 2.f * (dots[64 + cb2] + dots[192 + cb2]);
+        for (int j = 32 * hj; j < 32 * hj + 32; j += 2) {
+            const unsigned v = R[c * kEncRowDw + j], w = R[c * kEncRowDw + j + 1];
+            const float4 r = *reinterpret_cast<const float4 *>(res + 2 * j);
+            const float x = bf16_lo(v), y = bf16_hi(v), x1 = bf16_lo(w), y1 = bf16_hi(w);
+            acc0 = second ? __builtin_fmaf(r.y, x, __builtin_fmaf(-r.x, y, acc0)) : __builtin_fmaf(r.y, y, __builtin_fmaf(r.x, x, acc0));
+            acc1 = second ? __builtin_fmaf(r.w, x1, __builtin_fmaf(-r.z, y1, acc1)) : __builtin_fmaf(r.w, y1, __builtin_fmaf(r.z, x1, acc1));
+        }
+        dots[tid] = acc0 + acc1;
+        __syncthreads();
+        // candidate k * 256 + tid is the pair (a = 4 k + tid / 64, b = tid % 64): b is the thread's own
+        const int cb2 = tid & (K - 1);
+        const float vb = ns[buf * K + cb2] - 2.f * (dots[64 + cb2] + dots[192 + cb2]);
 #pragma unroll
-            for (int k = 0; k < K * K / 256; ++k) {
-                const int cc = k * 256 + tid, ca = cc / K;
-                const float ua = ns[buf * K + ca] - 2.f * (dots[ca] + dots[128 + ca]);
-                const float sc = ua + (vb + xs[buf * CROSS + cc]);
-                if (sc < best) { best = sc; cand = cc; }
-            }
+        for (int k = 0; k < K * K / 256; ++k) {
+            const int cc = k * 256 + tid, ca = cc / K;
+            const float ua = ns[buf * K + ca] - 2.f * (dots[ca] + dots[128 + ca]);
+            const float sc = ua + (vb + xs[buf * CROSS + cc]);
+            if (sc < best) { best = sc; cand = cc; }
         }
         const float wm = -wave_max(-best);
         int wc = best == wm ? cand : 0x7fffffff;
@@ -583,23 +652,16 @@ __global__ __launch_bounds__(256) void k_encode_lds(const void *__restrict__ key
             if (tid == 0) chosen[l] = c;
             if (tid < kD) {
                 const int e2 = tid >> 1;
-                if (!PAIRED) {
-                    const unsigned v = R[c * kEncRowDw + e2];
-                    res[tid] -= (tid & 1) ? bf16_hi(v) : bf16_lo(v);
-                } else {
-                    const unsigned va = R[(c / K) * kEncRowDw + e2], vb = R[(c % K) * kEncRowDw + e2];
-                    // element of i C[b]: (-y_b, x_b) of its sub-space
-                    res[tid] -= (tid & 1) ? bf16_hi(va) + bf16_lo(vb) : bf16_lo(va) - bf16_hi(vb);
-                }
+                const unsigned va = R[(c / K) * kEncRowDw + e2], vb = R[(c % K) * kEncRowDw + e2];
+                // element of i C[b]: (-y_b, x_b) of its sub-space
+                res[tid] -= (tid & 1) ? bf16_hi(va) + bf16_lo(vb) : bf16_lo(va) - bf16_hi(vb);
             }
         }
         if (l + 1 < a.levels) park_level(buf ^ 1);
         __syncthreads();
     }
     uint8_t *dst = out + tok * a.token_stride + (long long)g * a.head_stride;
-    if (!PAIRED) {
-        if (tid < a.levels) dst[tid] = (uint8_t)chosen[tid];
-    } else if (tid < a.record_bytes) {
+    if (tid < a.record_bytes) {
         unsigned v = 0;
         for (int r = (8 * tid) / 12; r < a.levels && 12 * r < 8 * tid + 8; ++r) {
             const unsigned pr = (unsigned)(chosen[r] / K) | (unsigned)(chosen[r] % K) << 6;
@@ -689,6 +751,50 @@ commvq_status encode_rows(const void *keys, const void *cb, const float *norms, 
     return launch_encode_rows<1>(keys, cb, norms, out, d, rest, s);
 }
 
+template <int RS>
+commvq_status launch_encode_pairs(const void *keys, const void *cb, const float *norms, const float *cross, uint8_t *out,
+                                  const EncodeDims &d, int n_tokens, hipStream_t s)
+{
+    static std::atomic<uint64_t> lds_ok{0};
+    if (allow_dynamic_lds(&k_encode_pairs<RS>, ep_lds(RS), lds_ok) != hipSuccess) return COMMVQ_ERR_LAUNCH;
+    constexpr int per_wg = 128 / RS;
+    hipLaunchKernelGGL(k_encode_pairs<RS>, dim3((unsigned)((n_tokens + per_wg - 1) / per_wg * d.Hkv)), dim3(kEpThreads), ep_lds(RS), s, keys,
+                       static_cast<const uint4 *>(cb), norms, cross, out, d, n_tokens);
+    return hipGetLastError() == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;
+}
+
+commvq_status launch_encode_lds(const void *keys, const void *cb, const float *norms, const float *cross, uint8_t *out,
+                                const EncodeDims &d, int n_tokens, hipStream_t s)
+{
+    const int lds = (2 * d.K * kEncRowDw + 2 * d.K * d.K + 2 * d.K + kD + 256 + 8 + 32) * 4;
+    static std::atomic<uint64_t> lds_ok{0};
+    if (allow_dynamic_lds(&k_encode_lds, lds, lds_ok) != hipSuccess) return COMMVQ_ERR_LAUNCH;
+    hipLaunchKernelGGL(k_encode_lds, dim3((unsigned)(n_tokens * d.Hkv)), dim3(256), lds, s, keys, static_cast<const unsigned *>(cb), norms,
+                       cross, out, d);
+    return hipGetLastError() == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;
+}
+
+commvq_status encode_pairs(const void *keys, const void *cb, const float *norms, const float *cross, uint8_t *out, const EncodeDims &d,
+                           int n_tokens, hipStream_t s)
+{
+    // As in encode_rows: full rounds of one workgroup per compute unit go to RS = 1, and the rest to what needs one round.
+    // 21 levels of 8 heads take 108 us with RS = 4 (up to 1024 tokens), 127 (2; 2048), 170 (1; 4096).  A workgroup per
+    // vector takes 56 us while the vectors fit the chip, two workgroups per compute unit: 65 tokens would take 124.
+    const int64_t round = 128 * (int64_t)std::max(1, 256 / d.Hkv);
+    const int full = (int)(n_tokens / round * round), rest = n_tokens - full;
+    if (full) {
+        const commvq_status st = launch_encode_pairs<1>(keys, cb, norms, cross, out, d, full, s);
+        if (st != COMMVQ_OK || !rest) return st;
+        keys = static_cast<const char *>(keys) + (size_t)full * d.Hkv * kD * (d.key_bf16 ? 2 : 4);
+        out += full * d.token_stride;
+    }
+    auto one_round = [&](int per_wg) { return (int64_t)(rest + per_wg - 1) / per_wg * d.Hkv <= 256; };
+    if ((int64_t)rest * d.Hkv <= 512) return launch_encode_lds(keys, cb, norms, cross, out, d, rest, s);
+    if (one_round(32)) return launch_encode_pairs<4>(keys, cb, norms, cross, out, d, rest, s);
+    if (one_round(64)) return launch_encode_pairs<2>(keys, cb, norms, cross, out, d, rest, s);
+    return launch_encode_pairs<1>(keys, cb, norms, cross, out, d, rest, s);
+}
+
 commvq_status encode_vectors(commvq_handle *h, bool values, const void *keys, int32_t n_tokens, const void *key_cb, const void *tables,
                              uint8_t *codes_out, int64_t token_stride, int64_t head_stride, void *stream)
 {
@@ -706,26 +812,16 @@ commvq_status encode_vectors(commvq_handle *h, bool values, const void *keys, in
     d.token_stride = token_stride; d.head_stride = head_stride;
     const int rows = c.n_kv_heads * levels * K;
     const float *norms = static_cast<const float *>(tables), *cross = norms + rows;
-    const dim3 grid((unsigned)(n_tokens * c.n_kv_heads));
     hipStream_t s = static_cast<hipStream_t>(stream);
     const bool bf16 = c.codebook_dtype == COMMVQ_BF16;
     if (paired && !bf16) return COMMVQ_ERR_CONFIG;
     if (h->device < 0) return COMMVQ_ERR_NO_DEVICE;
-    if (paired && n_tokens >= kEbTokens) {  // many tokens: 64 per workgroup, dot products on the matrix cores
-        static std::atomic<uint64_t> lds_ok{0};
-        if (allow_dynamic_lds(&k_encode_pair_batch, kEpLds, lds_ok) != hipSuccess) return COMMVQ_ERR_LAUNCH;
-        const dim3 bgrid((unsigned)((n_tokens + kEbTokens - 1) / kEbTokens * c.n_kv_heads));
-        hipLaunchKernelGGL(k_encode_pair_batch, bgrid, dim3(256), kEpLds, s, keys, static_cast<const uint4 *>(key_cb), norms, cross,
-                           codes_out, d, n_tokens);
-    } else if (paired) {  // rows, norms and cross terms staged in LDS, next level prefetched
-        const int lds = (2 * K * kEncRowDw + 2 * K * K + 2 * K + kD + 256 + 8 + 32) * 4;
-        static std::atomic<uint64_t> lds_ok{0};
-        if (allow_dynamic_lds(&k_encode_lds<true>, lds, lds_ok) != hipSuccess) return COMMVQ_ERR_LAUNCH;
-        hipLaunchKernelGGL(k_encode_lds<true>, grid, dim3(256), lds, s, keys, static_cast<const unsigned *>(key_cb), norms, cross, codes_out, d);
+    if (paired) {
+        return encode_pairs(keys, key_cb, norms, cross, codes_out, d, n_tokens, s);
     } else if (bf16) {
         return encode_rows(keys, key_cb, norms, codes_out, d, n_tokens, s);
     } else {
-        hipLaunchKernelGGL(k_encode<false>, grid, dim3(256), 0, s, keys, key_cb, norms, codes_out, d);
+        hipLaunchKernelGGL(k_encode<false>, dim3((unsigned)(n_tokens * c.n_kv_heads)), dim3(256), 0, s, keys, key_cb, norms, codes_out, d);
     }
     return hipGetLastError() == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;
 }
