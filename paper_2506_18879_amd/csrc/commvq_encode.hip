@@ -72,6 +72,20 @@ __device__ __forceinline__ void min2_halves(float &best, int &index)
     index = second ? (int)i32[1] : (int)i32[0];
 }
 
+// The least of the 64 lanes' non-negative indices, in every lane.
+__device__ __forceinline__ int wave_min_index(int v)
+{
+    auto other = [&](float f) { v = min(v, __builtin_bit_cast(int, f)); };
+    other(dpp_mov<0xB1>(__builtin_bit_cast(float, v)));
+    other(dpp_mov<0x4E>(__builtin_bit_cast(float, v)));
+    other(dpp_mov<0x141>(__builtin_bit_cast(float, v)));
+    other(dpp_mov<0x140>(__builtin_bit_cast(float, v)));
+    auto r16 = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
+    v = min((int)r16[0], (int)r16[1]);
+    auto r32 = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
+    return min((int)r32[0], (int)r32[1]);
+}
+
 struct EncodeDims {
     int Hkv, levels, K, key_bf16, record_bytes;
     long long token_stride, head_stride;
@@ -554,117 +568,124 @@ __global__ __launch_bounds__(kEpThreads, 2) void k_encode_pairs(const void *__re
     }
 }
 
-// Paired-format keys, few tokens: one workgroup per (token, KV head), shaped for latency (a decode step appends one token
-// per sequence, and the R levels are a dependent chain): the rows, norms and cross terms of level l + 1 do not depend on the
-// residual, so they are fetched into registers while level l is searched and parked in the other half
-// of a double-buffered LDS image; every level then runs out of LDS.  Rows are padded to 65 dwords so
-// that 64 lanes reading 64 different rows hit 64 different banks.
-constexpr int kEncRowDw = kD / 2 + 1;  // dwords per padded bf16 row
-__global__ __launch_bounds__(256) void k_encode_lds(const void *__restrict__ keys, const unsigned *__restrict__ cb,
-                                                    const float *__restrict__ norms, const float *__restrict__ cross,
-                                                    uint8_t *__restrict__ out, const EncodeDims a)
+// Paired-format keys, few vectors (a decode step appends one token per sequence): one workgroup per (token, KV head),
+// shaped for the latency of a level, since the levels are a dependent chain.  The rows and cross terms of level l + 1
+// travel from memory into the other half of a double buffer while level l is searched, the rows in the layout of
+// k_encode_rows.  Four lanes share a dot product (32 of its 128 elements each, summed by quad permutes): 512 threads for 64
+// rows and two products of each.  Their sums come back through LDS, and wavefront w scans the rows a = 8 w .. + 7, lane b.
+// Ties go to the lowest index.  11 levels, 64 vectors: 18.5 us (31 us with 256 threads, the next level fetched through
+// registers and the products re-added from LDS by every candidate), 512 vectors 26 us (37).  The same shape for the 256
+// rows of an index-form level takes 1.95 us a level, k_encode_rows 1.5.
+// No static LDS: the images sit at LDS address 0.
+constexpr int kOneThreads = 512;
+constexpr int kOneResFloats = kD + 4 * 8;  // 8 unused after every 32: the four lanes of a dot product hit different banks
+constexpr int kOneImage = 64 * 256, kOneCross = 2 * kOneImage, kOneTail = kOneCross + 2 * 4096 * 4;
+constexpr int kOneLds = kOneTail + kOneResFloats * 4 + 128 * 4 + 8 * 8 + 32 * 4;
+__global__ __launch_bounds__(kOneThreads) void k_encode_one(const void *__restrict__ keys, const uint4 *__restrict__ cb,
+                                                            const float *__restrict__ norms, const float *__restrict__ cross,
+                                                            uint8_t *__restrict__ out, const EncodeDims a)
 {
-    constexpr int K = 64;
-    constexpr int ROWS_DW = K * kEncRowDw;             // one level's rows
-    constexpr int CROSS = K * K;
-    constexpr int RPT = K * (kD / 2) / 256;            // row dwords per thread
-    constexpr int XPT = CROSS / 256;
-    extern __shared__ __attribute__((aligned(16))) unsigned enc_lds[];
-    unsigned *rows = enc_lds;                                          // [2][K][65]
-    float *xs = reinterpret_cast<float *>(enc_lds + 2 * ROWS_DW);      // [2][K * K]
-    float *ns = xs + 2 * CROSS;                                        // [2][K]
-    float *res = ns + 2 * K;                                           // [d]
-    float *dots = res + kD;                                            // [256]
-    float *wbest = dots + 256;                                         // [4]
-    int *wcand = reinterpret_cast<int *>(wbest + 4);                   // [4]
-    int *chosen = wcand + 4;                                           // [32]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int K = 64, kWaves = kOneThreads / 64;
+    extern __shared__ __attribute__((aligned(16))) uint4 one_mem[];
+    char *lds = reinterpret_cast<char *>(one_mem);
+    float *res = reinterpret_cast<float *>(lds + kOneTail);              // element e at e + 8 (e / 32)
+    float *uv = res + kOneResFloats;                                  // [U 64][V 64]
+    float2 *part = reinterpret_cast<float2 *>(uv + 128);              // [wavefronts] minimum and its index
+    int *chosen = reinterpret_cast<int *>(part + kWaves);             // [32]
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = blockIdx.x % a.Hkv;
     const size_t tok = blockIdx.x / a.Hkv;
-
-    unsigned prow[RPT];
-    float pcross[XPT], pnorm = 0.f;
-    auto fetch_level = [&](int l) {
-        const size_t level = (size_t)g * a.levels + l;
+    const int q = tid & 3, row = (tid >> 2) & (K - 1);
+    const bool second = wave >= kWaves / 2;  // the products with i C
+    const uint4 *rows = cb + (size_t)g * a.levels * K * 16;
+    const float *nrows = norms + (size_t)g * a.levels * K;
+    const float *xrows = cross + (size_t)g * a.levels * 4096;
+    auto fetch_level = [&](int l, int buf) {
 #pragma unroll
-        for (int x = 0; x < RPT; ++x) prow[x] = cb[level * K * (kD / 2) + x * 256 + tid];
-#pragma unroll
-        for (int x = 0; x < XPT; ++x) pcross[x] = cross[level * CROSS + x * 256 + tid];
-        if (tid < K) pnorm = norms[level * K + tid];
-    };
-    auto park_level = [&](int buf) {
-#pragma unroll
-        for (int x = 0; x < RPT; ++x) {
-            const int i = x * 256 + tid;  // dword i of the level: row i / 64, column i % 64
-            rows[buf * ROWS_DW + (i >> 6) * kEncRowDw + (i & 63)] = prow[x];
+        for (int i = 0; i < 2; ++i) {
+            const int p0 = (wave * 2 + i) * 64, p = p0 + lane, t = p >> 4;
+            lds_dma16(rows + (size_t)l * K * 16, (unsigned)(t * 16 + ((p ^ t) & 15)) * 16u, (unsigned)(buf * kOneImage + p0 * 16));
+            lds_dma16(xrows + (size_t)l * 4096, (unsigned)p * 16u, (unsigned)(kOneCross + buf * 4096 * 4 + p0 * 16));
         }
-#pragma unroll
-        for (int x = 0; x < XPT; ++x) xs[buf * CROSS + x * 256 + tid] = pcross[x];
-        if (tid < K) ns[buf * K + tid] = pnorm;
     };
-    fetch_level(0);
+    fetch_level(0, 0);
+    float mine = 0.f;  // threads below 128: an element of the residual each
     if (tid < kD) {
         const size_t i = (tok * a.Hkv + g) * kD + tid;
-        res[tid] = a.key_bf16 ? __builtin_bit_cast(float, (unsigned)static_cast<const uint16_t *>(keys)[i] << 16)
-                              : static_cast<const float *>(keys)[i];
+        mine = a.key_bf16 ? __builtin_bit_cast(float, (unsigned)static_cast<const uint16_t *>(keys)[i] << 16)
+                          : static_cast<const float *>(keys)[i];
+        res[tid + (tid >> 5) * 8] = mine;
     }
-    park_level(0);
-    __syncthreads();
+    float nrm = nrows[row];
     for (int l = 0; l < a.levels; ++l) {
         const int buf = l & 1;
-        if (l + 1 < a.levels) fetch_level(l + 1);
-        const unsigned *R = rows + buf * ROWS_DW;
-        float best = INFINITY;
-        int cand = 0x7fffffff;
-        // thread = (row c, a-dot or b-dot, which half of the sub-spaces); the two halves are added in a fixed order
-        const int c = tid & 63, second = (tid >> 6) & 1, hj = tid >> 7;
-        float acc0 = 0.f, acc1 = 0.f;  // two chains (even / odd sub-spaces), added in a fixed order
-#pragma unroll 16
-        for (int j = 32 * hj; j < 32 * hj + 32; j += 2) {
-            const unsigned v = R[c * kEncRowDw + j], w = R[c * kEncRowDw + j + 1];
-            const float4 r = *reinterpret_cast<const float4 *>(res + 2 * j);
-            const float x = bf16_lo(v), y = bf16_hi(v), x1 = bf16_lo(w), y1 = bf16_hi(w);
-            acc0 = second ? __builtin_fmaf(r.y, x, __builtin_fmaf(-r.x, y, acc0)) : __builtin_fmaf(r.y, y, __builtin_fmaf(r.x, x, acc0));
-            acc1 = second ? __builtin_fmaf(r.w, x1, __builtin_fmaf(-r.z, y1, acc1)) : __builtin_fmaf(r.w, y1, __builtin_fmaf(r.z, x1, acc1));
+        const char *img = lds + buf * kOneImage;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's part of level l has landed
+        __syncthreads();                                   // ... and everybody's; the residual is up to date
+        float nrm_next = 0.f;
+        if (l + 1 < a.levels) {
+            nrm_next = nrows[(size_t)(l + 1) * K + row];
+            fetch_level(l + 1, buf ^ 1);
         }
-        dots[tid] = acc0 + acc1;
-        __syncthreads();
-        // candidate k * 256 + tid is the pair (a = 4 k + tid / 64, b = tid % 64): b is the thread's own
-        const int cb2 = tid & (K - 1);
-        const float vb = ns[buf * K + cb2] - 2.f * (dots[64 + cb2] + dots[192 + cb2]);
+        float s0 = 0.f, s1 = 0.f;
 #pragma unroll
-        for (int k = 0; k < K * K / 256; ++k) {
-            const int cc = k * 256 + tid, ca = cc / K;
-            const float ua = ns[buf * K + ca] - 2.f * (dots[ca] + dots[128 + ca]);
-            const float sc = ua + (vb + xs[buf * CROSS + cc]);
-            if (sc < best) { best = sc; cand = cc; }
-        }
-        const float wm = -wave_max(-best);
-        int wc = best == wm ? cand : 0x7fffffff;
-        for (int off = 32; off > 0; off >>= 1) wc = min(wc, __shfl_xor(wc, off));
-        if (lane == 0) { wbest[wave] = wm; wcand[wave] = wc; }
-        __syncthreads();
-        {
-            float m = wbest[0];
-            int c = wcand[0];
-            for (int w = 1; w < 4; ++w)
-                if (wbest[w] < m || (wbest[w] == m && wcand[w] < c)) { m = wbest[w]; c = wcand[w]; }
-            if (tid == 0) chosen[l] = c;
-            if (tid < kD) {
-                const int e2 = tid >> 1;
-                const unsigned va = R[(c / K) * kEncRowDw + e2], vb = R[(c % K) * kEncRowDw + e2];
-                // element of i C[b]: (-y_b, x_b) of its sub-space
-                res[tid] -= (tid & 1) ? bf16_hi(va) + bf16_lo(vb) : bf16_lo(va) - bf16_hi(vb);
+        for (int i = 0; i < 4; ++i) {
+            const uint4 pc = *reinterpret_cast<const uint4 *>(img + row * 256 + ((4 * q + i) ^ (row & 15)) * 16);
+            const unsigned w[4] = {pc.x, pc.y, pc.z, pc.w};
+            const float4 r0 = *reinterpret_cast<const float4 *>(res + 40 * q + 8 * i), r1 = *reinterpret_cast<const float4 *>(res + 40 * q + 8 * i + 4);
+            const float rx[4] = {r0.x, r0.z, r1.x, r1.z}, ry[4] = {r0.y, r0.w, r1.y, r1.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float x = bf16_lo(w[e]), y = bf16_hi(w[e]);
+                if (second) { s0 = __builtin_fmaf(ry[e], x, s0); s1 = __builtin_fmaf(-rx[e], y, s1); }
+                else { s0 = __builtin_fmaf(rx[e], x, s0); s1 = __builtin_fmaf(ry[e], y, s1); }
             }
         }
-        if (l + 1 < a.levels) park_level(buf ^ 1);
+        float dot = s0 + s1;
+        dot += dpp_mov<0xB1>(dot);
+        dot += dpp_mov<0x4E>(dot);
+        if (q == 0) uv[tid >> 2] = nrm - 2.f * dot;
         __syncthreads();
+        const float4 u0 = *reinterpret_cast<const float4 *>(uv + 8 * wave), u1 = *reinterpret_cast<const float4 *>(uv + 8 * wave + 4);
+        const float u[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
+        const float v = uv[64 + lane];
+        const float *xs = reinterpret_cast<const float *>(lds + kOneCross) + buf * 4096 + 8 * wave * 64 + lane;
+        float best = INFINITY;
+        int cand = 0;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const float sc = u[k] + (v + xs[k * 64]);
+            if (sc < best) { best = sc; cand = (8 * wave + k) * 64 + lane; }
+        }
+        const float wm = -wave_max(-best);
+        const int wc = wave_min_index(best == wm ? cand : 0x7fffffff);
+        if (lane == 0) part[wave] = make_float2(wm, __builtin_bit_cast(float, wc));
+        __syncthreads();
+        if (tid < kD) {
+            float m = INFINITY;
+            int c = 0x7fffffff;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {  // the wavefronts hold increasing indices
+                const float2 o = part[w];
+                if (o.x < m) { m = o.x; c = __builtin_bit_cast(int, o.y); }
+            }
+            c &= 4095;  // always in range for finite input
+            auto element = [&](int r, int e) {
+                return __builtin_bit_cast(float, (unsigned)*reinterpret_cast<const uint16_t *>(img + r * 256 + (((e >> 3) ^ r) & 15) * 16 + (e & 7) * 2) << 16);
+            };
+            const float va = element(c >> 6, tid), vb = element(c & 63, tid ^ 1);  // C[a] + i C[b], i (x, y) = (-y, x)
+            mine -= tid & 1 ? va + vb : va - vb;
+            res[tid + (tid >> 5) * 8] = mine;
+            if (tid == 0) chosen[l] = c;
+        }
+        nrm = nrm_next;
     }
+    __syncthreads();
     uint8_t *dst = out + tok * a.token_stride + (long long)g * a.head_stride;
     if (tid < a.record_bytes) {
         unsigned v = 0;
         for (int r = (8 * tid) / 12; r < a.levels && 12 * r < 8 * tid + 8; ++r) {
-            const unsigned pr = (unsigned)(chosen[r] / K) | (unsigned)(chosen[r] % K) << 6;
+            const unsigned pr = (unsigned)(chosen[r] >> 6) | (unsigned)(chosen[r] & 63) << 6;
             const int sh = 12 * r - 8 * tid;
             v |= sh >= 0 ? pr << sh : pr >> -sh;
         }
@@ -717,6 +738,16 @@ commvq_status encoder_prepare(commvq_handle *h, bool values, const void *cb, voi
     return hipGetLastError() == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;
 }
 
+commvq_status launch_encode_one(const void *keys, const void *cb, const float *norms, const float *cross, uint8_t *out,
+                                const EncodeDims &d, int n_tokens, hipStream_t s)
+{
+    static std::atomic<uint64_t> lds_ok{0};
+    if (allow_dynamic_lds(&k_encode_one, kOneLds, lds_ok) != hipSuccess) return COMMVQ_ERR_LAUNCH;
+    hipLaunchKernelGGL(k_encode_one, dim3((unsigned)(n_tokens * d.Hkv)), dim3(kOneThreads), kOneLds, s, keys,
+                       static_cast<const uint4 *>(cb), norms, cross, out, d);
+    return hipGetLastError() == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;
+}
+
 template <int RS>
 commvq_status launch_encode_rows(const void *keys, const void *cb, const float *norms, uint8_t *out, const EncodeDims &d, int n_tokens,
                                  hipStream_t s)
@@ -763,23 +794,12 @@ commvq_status launch_encode_pairs(const void *keys, const void *cb, const float 
     return hipGetLastError() == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;
 }
 
-commvq_status launch_encode_lds(const void *keys, const void *cb, const float *norms, const float *cross, uint8_t *out,
-                                const EncodeDims &d, int n_tokens, hipStream_t s)
-{
-    const int lds = (2 * d.K * kEncRowDw + 2 * d.K * d.K + 2 * d.K + kD + 256 + 8 + 32) * 4;
-    static std::atomic<uint64_t> lds_ok{0};
-    if (allow_dynamic_lds(&k_encode_lds, lds, lds_ok) != hipSuccess) return COMMVQ_ERR_LAUNCH;
-    hipLaunchKernelGGL(k_encode_lds, dim3((unsigned)(n_tokens * d.Hkv)), dim3(256), lds, s, keys, static_cast<const unsigned *>(cb), norms,
-                       cross, out, d);
-    return hipGetLastError() == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;
-}
-
 commvq_status encode_pairs(const void *keys, const void *cb, const float *norms, const float *cross, uint8_t *out, const EncodeDims &d,
                            int n_tokens, hipStream_t s)
 {
     // As in encode_rows: full rounds of one workgroup per compute unit go to RS = 1, and the rest to what needs one round.
     // 21 levels of 8 heads take 108 us with RS = 4 (up to 1024 tokens), 127 (2; 2048), 170 (1; 4096).  A workgroup per
-    // vector takes 56 us while the vectors fit the chip, two workgroups per compute unit: 65 tokens would take 124.
+    // vector takes 33 to 46 us while the vectors fit the chip, two workgroups per compute unit.
     const int64_t round = 128 * (int64_t)std::max(1, 256 / d.Hkv);
     const int full = (int)(n_tokens / round * round), rest = n_tokens - full;
     if (full) {
@@ -789,7 +809,7 @@ commvq_status encode_pairs(const void *keys, const void *cb, const float *norms,
         out += full * d.token_stride;
     }
     auto one_round = [&](int per_wg) { return (int64_t)(rest + per_wg - 1) / per_wg * d.Hkv <= 256; };
-    if ((int64_t)rest * d.Hkv <= 512) return launch_encode_lds(keys, cb, norms, cross, out, d, rest, s);
+    if ((int64_t)rest * d.Hkv <= 512) return launch_encode_one(keys, cb, norms, cross, out, d, rest, s);
     if (one_round(32)) return launch_encode_pairs<4>(keys, cb, norms, cross, out, d, rest, s);
     if (one_round(64)) return launch_encode_pairs<2>(keys, cb, norms, cross, out, d, rest, s);
     return launch_encode_pairs<1>(keys, cb, norms, cross, out, d, rest, s);
