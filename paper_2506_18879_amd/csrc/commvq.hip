@@ -2080,6 +2080,7 @@ struct OutArgs {
     float *partial, *out;
     int Hq, Hkv, nvsplit, vsplit_len, nchunk, Mv;
     int batch;
+    int per_wg;  // k_out_mfma: chunks of kOutMfmaRows rows that a workgroup takes one after the other
     // Index form: bins row r of a KV head = codeword r / M_v of codebook r % M_v, whose value-codebook row (of d
     // elements) is g * M_v K + (r % M_v) * K + r / M_v.  Binary code (cb_linear): bins row r = code bit c =
     // vbits_code_bit(r), codebook [N_c][Hkv * d], row of d elements c * Hkv + g.
@@ -2236,7 +2237,7 @@ __global__ __launch_bounds__(256) void k_prep_values(const uint16_t *__restrict_
 
 // The output stage for batches (Eq. optimized_v's bins x C_V as what it is for several sequences, a matrix product):
 // per KV head, [sequences x query heads] x [M_v K rows] times [rows] x [d].  A workgroup takes 16 output rows
-// (16 / G sequences), kOutMfmaRows codebook rows and all d columns: it sums the fixed-point bins of its rows over the
+// (16 / G sequences), per_wg chunks of kOutMfmaRows codebook rows and all d columns: it sums the fixed-point bins of its rows over the
 // value splits (fp32, each split's unit applied), splits every fp32 weight EXACTLY into three bf16 parts (24 mantissa
 // bits = 8 + 8 + 8) and multiplies them with the bf16 codebook by v_mfma_f32_16x16x32_bf16, accumulating in fp32: the
 // fp32 product up to summation order, at a tenth of the vector instructions.  Each wavefront takes 32 of the 128 columns;
@@ -2248,45 +2249,19 @@ __global__ __launch_bounds__(kOutThreads) void k_out_mfma(OutArgs a, const uint4
     constexpr int KC = kOutMfmaRows, SPT = 16 / G, WS = KC + 8;  // (row stride padded: the 16 rows fall on different banks)
     __shared__ __attribute__((aligned(16))) uint16_t Wl[3][16][WS];
     int id = blockIdx.x;
-    const int chunk = id % a.nchunk;
+    const int part = id % a.nchunk;  // chunks part * per_wg .. + per_wg - 1 of kOutMfmaRows rows
     id /= a.nchunk;
     const int g = id % a.Hkv;
     const int b0 = (id / a.Hkv) * SPT;
     const int MK = a.Mv * kK;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (int it = tid; it < SPT * KC; it += kOutThreads) {
-        const int sq = it / KC, k = it % KC, b = b0 + sq;
-        float w[G];
-#pragma unroll
-        for (int hh = 0; hh < G; ++hh) w[hh] = 0.f;
-        if (b < a.batch) {
-            const int L = a.cu[b + 1] - a.cu[b];
-            const int nvs = min((L + a.vsplit_len - 1) / a.vsplit_len, a.nvsplit);
-            const unsigned *src = a.bins + (size_t)(b * a.Hkv + g) * a.nvsplit * G * MK + (size_t)(chunk * KC + k) * G;
-            const float *scl = a.vscale + ((size_t)b * a.Hq + (size_t)g * G) * a.nvsplit;
-#pragma unroll 4
-            for (int v = 0; v < nvs; ++v) {
-                const unsigned *pv = src + (size_t)v * G * MK;
-                unsigned bv[G];
-                if (G >= 4) {
-#pragma unroll
-                    for (int q4 = 0; q4 < G / 4; ++q4) {
-                        const uint4 t4 = reinterpret_cast<const uint4 *>(pv)[q4];
-                        bv[4 * q4 + 0] = t4.x; bv[4 * q4 + 1 < G ? 4 * q4 + 1 : 0] = t4.y; bv[4 * q4 + 2 < G ? 4 * q4 + 2 : 0] = t4.z; bv[4 * q4 + 3 < G ? 4 * q4 + 3 : 0] = t4.w;
-                    }
-                } else if (G == 2) {
-                    const uint2 t2 = *reinterpret_cast<const uint2 *>(pv);
-                    bv[0] = t2.x; bv[G - 1] = t2.y;
-                } else {
-                    bv[0] = pv[0];
-                }
-#pragma unroll
-                for (int hh = 0; hh < G; ++hh) w[hh] += (float)bv[hh] * scl[(size_t)hh * a.nvsplit + v];
-            }
-        }
+    // first operand: lane (i = lane % 16, kg = lane / 16) supplies weights of output row i for rows 8 kg .. 8 kg + 7 of the
+    // k-step; second: lane (n, kg) the same rows of column n; result: lane (n, rg) holds rows 4 rg .. 4 rg + 3 of column n
+    const int n = lane & 15, kg = lane >> 4;
+    // hi = the top 16 bits, mid = the top 16 bits of what is left, lo = the rest (exact: 8 + 8 + 8 mantissa bits)
+    auto put = [&](int sq, int k, const float (&w)[G]) {
 #pragma unroll
         for (int hh = 0; hh < G; ++hh) {
-            // hi = the top 16 bits, mid = the top 16 bits of what is left, lo = the rest (exact: 8 + 8 + 8 mantissa bits)
             const unsigned u0 = __builtin_bit_cast(unsigned, w[hh]) & 0xffff0000u;
             const float r1 = w[hh] - __builtin_bit_cast(float, u0);
             const unsigned u1 = __builtin_bit_cast(unsigned, r1) & 0xffff0000u;
@@ -2296,30 +2271,94 @@ __global__ __launch_bounds__(kOutThreads) void k_out_mfma(OutArgs a, const uint4
             Wl[1][sq * G + hh][k] = (uint16_t)(u1 >> 16);
             Wl[2][sq * G + hh][k] = (uint16_t)(u2 >> 16);
         }
-    }
-    __syncthreads();
-    // first operand: lane (i = lane % 16, kg = lane / 16) supplies weights of output row i for rows 8 kg .. 8 kg + 7 of the
-    // k-step; second: lane (n, kg) the same rows of column n; result: lane (n, rg) holds rows 4 rg .. 4 rg + 3 of column n
-    const int n = lane & 15, kg = lane >> 4;
-    floatx4_t acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-    const uint4 *bsrc = vp + (((size_t)g * (MK / 32) + (size_t)chunk * (KC / 32)) * kD + 32 * wave + n) * 4 + kg;
+    };
+    auto load_bins = [](const unsigned *pv, unsigned (&bv)[G]) {
+        if constexpr (G >= 4) {
 #pragma unroll
-    for (int kt = 0; kt < KC / 32; ++kt) {
-        const uint4 B0 = bsrc[(size_t)(kt * kD) * 4], B1 = bsrc[(size_t)(kt * kD + 16) * 4];
-#pragma unroll
-        for (int p = 0; p < 3; ++p) {
-            const uint4 A = *reinterpret_cast<const uint4 *>(&Wl[p][n][32 * kt + 8 * kg]);
-            acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, A), __builtin_bit_cast(bf16x8_t, B0), acc[0], 0, 0, 0);
-            acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, A), __builtin_bit_cast(bf16x8_t, B1), acc[1], 0, 0, 0);
+            for (int q4 = 0; q4 < G / 4; ++q4) {
+                const uint4 t4 = reinterpret_cast<const uint4 *>(pv)[q4];
+                bv[4 * q4] = t4.x; bv[4 * q4 + 1] = t4.y; bv[4 * q4 + 2] = t4.z; bv[4 * q4 + 3] = t4.w;
+            }
+        } else if constexpr (G == 2) {
+            const uint2 t2 = *reinterpret_cast<const uint2 *>(pv);
+            bv[0] = t2.x; bv[1] = t2.y;
+        } else {
+            bv[0] = pv[0];
         }
+    };
+    floatx4_t total[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    for (int c = 0; c < a.per_wg; ++c) {
+        const int chunk = part * a.per_wg + c;
+        if (c > 0) __syncthreads();  // the previous chunk's weights are no longer read
+        if (a.nvsplit == 1) {
+            // one value split (batch x KV heads above 128): a thread's bins of all SPT sequences travel together (64 sequences
+            // 129 -> 125 us, 40 of 8 heads 147 -> 144.6); with 16 splits and few workgroups this form takes 25 us, the other 13
+            static_assert(KC == kOutThreads, "a thread takes one codebook row of every sequence");
+            unsigned bv[SPT][G];
+            float unit[SPT][G];
+#pragma unroll
+            for (int i = 0; i < SPT; ++i) {
+#pragma unroll
+                for (int hh = 0; hh < G; ++hh) { bv[i][hh] = 0u; unit[i][hh] = 0.f; }
+                const int b = b0 + i;
+                if (b < a.batch && a.cu[b + 1] > a.cu[b]) {
+                    load_bins(a.bins + (size_t)(b * a.Hkv + g) * G * MK + (size_t)(chunk * KC + tid) * G, bv[i]);
+#pragma unroll
+                    for (int hh = 0; hh < G; ++hh) unit[i][hh] = a.vscale[(size_t)b * a.Hq + (size_t)g * G + hh];
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < SPT; ++i) {
+                float w[G];
+#pragma unroll
+                for (int hh = 0; hh < G; ++hh) w[hh] = (float)bv[i][hh] * unit[i][hh];
+                put(i, tid, w);
+            }
+        } else {
+            for (int it = tid; it < SPT * KC; it += kOutThreads) {
+                const int sq = it / KC, k = it % KC, b = b0 + sq;
+                float w[G];
+#pragma unroll
+                for (int hh = 0; hh < G; ++hh) w[hh] = 0.f;
+                if (b < a.batch) {
+                    const int L = a.cu[b + 1] - a.cu[b];
+                    const int nvs = min((L + a.vsplit_len - 1) / a.vsplit_len, a.nvsplit);
+                    const unsigned *src = a.bins + (size_t)(b * a.Hkv + g) * a.nvsplit * G * MK + (size_t)(chunk * KC + k) * G;
+                    const float *scl = a.vscale + ((size_t)b * a.Hq + (size_t)g * G) * a.nvsplit;
+#pragma unroll 4
+                    for (int v = 0; v < nvs; ++v) {
+                        unsigned bv[G];
+                        load_bins(src + (size_t)v * G * MK, bv);
+#pragma unroll
+                        for (int hh = 0; hh < G; ++hh) w[hh] += (float)bv[hh] * scl[(size_t)hh * a.nvsplit + v];
+                    }
+                }
+                put(sq, k, w);
+            }
+        }
+        __syncthreads();
+        floatx4_t acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+        const uint4 *bsrc = vp + (((size_t)g * (MK / 32) + (size_t)chunk * (KC / 32)) * kD + 32 * wave + n) * 4 + kg;
+#pragma unroll
+        for (int kt = 0; kt < KC / 32; ++kt) {
+            const uint4 B0 = bsrc[(size_t)(kt * kD) * 4], B1 = bsrc[(size_t)(kt * kD + 16) * 4];
+#pragma unroll
+            for (int p = 0; p < 3; ++p) {
+                const uint4 A = *reinterpret_cast<const uint4 *>(&Wl[p][n][32 * kt + 8 * kg]);
+                acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, A), __builtin_bit_cast(bf16x8_t, B0), acc[0], 0, 0, 0);
+                acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, A), __builtin_bit_cast(bf16x8_t, B1), acc[1], 0, 0, 0);
+            }
+        }
+        total[0] += acc[0];
+        total[1] += acc[1];
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int i = 4 * kg + r, b = b0 + i / G, hh = i % G;
         if (b < a.batch) {
-            float *dst = a.partial + (((size_t)b * a.Hq + (size_t)g * G + hh) * a.nchunk + chunk) * kD + 32 * wave + n;
-            dst[0] = acc[0][r];
-            dst[16] = acc[1][r];
+            float *dst = a.partial + (((size_t)b * a.Hq + (size_t)g * G + hh) * a.nchunk + part) * kD + 32 * wave + n;
+            dst[0] = total[0][r];
+            dst[16] = total[1][r];
         }
     }
 }
@@ -2721,7 +2760,7 @@ commvq_status run_output(commvq_handle *h, const void *val_cb, const commvq_posi
     a.partial = w.partial; a.out = out;
     a.Hq = c.n_q_heads; a.Hkv = c.n_kv_heads;
     a.nvsplit = plan.value_splits; a.vsplit_len = plan.value_split_len;
-    a.nchunk = plan.out_chunks; a.Mv = val_books(c); a.batch = pos->batch;
+    a.nchunk = plan.out_chunks; a.Mv = val_books(c); a.batch = pos->batch; a.per_wg = 1;
     a.cb_linear = bin_values(c) ? 1 : 0;
     const int grid = pos->batch * c.n_kv_heads * plan.out_chunks;
     const bool bf16 = c.codebook_dtype == COMMVQ_BF16;
@@ -2736,7 +2775,14 @@ commvq_status run_output(commvq_handle *h, const void *val_cb, const commvq_posi
         }
         a.nchunk = val_books(c) * kK / kOutMfmaRows;
         const int spt = 16 / h->G;
-        const int mgrid = ((pos->batch + spt - 1) / spt) * c.n_kv_heads * a.nchunk;
+        const int rows = (pos->batch + spt - 1) / spt * c.n_kv_heads;
+        // A workgroup takes several chunks one after the other as long as 1024 workgroups, four per compute unit, are left:
+        // its partial results are then one row instead of one per chunk, written here and read by k_out_final.  Whole
+        // call, 64 sequences of 512..1024 tokens, 32 codebooks: 136 us with 4096 workgroups, 129 with 1024, 140 with
+        // 512; 32 sequences 79 with 2048, 75 with 1024, 82 with 512.
+        a.per_wg = 1;
+        while (a.nchunk % 2 == 0 && (int64_t)rows * (a.nchunk / 2) >= 1024) { a.nchunk /= 2; a.per_wg *= 2; }
+        const int mgrid = rows * a.nchunk;
         switch (h->G) {
         case 1: hipLaunchKernelGGL(k_out_mfma<1>, dim3(mgrid), dim3(kOutThreads), 0, s, a, vp); break;
         case 2: hipLaunchKernelGGL(k_out_mfma<2>, dim3(mgrid), dim3(kOutThreads), 0, s, a, vp); break;
