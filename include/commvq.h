@@ -305,7 +305,8 @@ commvq_status commvq_em_step(const float *data, int32_t n_subspaces, int32_t n_p
  *   data         device [n_points][group][2] fp32: the calibration vectors (d = 2 * group values each)
  *   phi          device [group][n_centres][2] fp32, in/out
  *   group        1..64;  n_centres 1..64;  n_points 1..2^24
- * Results do not depend on the launch shape (all sums run in a fixed order).  A first or second index whose
+ * Results do not depend on the launch shape (all sums run in a fixed order).  T may be as small (hard assignment) or as
+ * large (infinity: equal weights) as a positive fp32 number is.  A first or second index whose
  * total weight underflows to zero makes the system singular (as in the paper's closed form): keep T large
  * enough for every index to keep weight.  Status codes as commvq_em_step.
  */

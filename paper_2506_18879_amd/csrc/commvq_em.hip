@@ -18,6 +18,8 @@
 // sub-space, the 2 N_c' x 2 N_c' system in LDS).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cfloat>
 #include <cstdint>
 
 #include "commvq.h"
@@ -362,9 +364,9 @@ struct EmsDims {
 // matrix instructions out of LDS.  The sweep over the centre pairs in between gives a wavefront one point: lane (al, bl)
 // holds the pairs a = NB al + .., b = NB bl + .., so that the distances, the weights, both marginals and the
 // denominator come from ONE evaluation of each pair, kept in registers until the denominator is known.
-//   bound: the quarter-rate v_sqrt_f32 and v_exp_f32, one each per (point, pair), and 7 more operations of the
+//   bound: the quarter-rate v_sqrt_f32 and v_exp_f32, one each per (point, pair), and 8 more operations of the
 // vector unit per pair.
-// 8192 points, 64 x 64 pairs, 64 sub-spaces: 28 us, of which the sweep 13 and the contractions 9; as separate passes over
+// 8192 points, 64 x 64 pairs, 64 sub-spaces: 29 us, of which the sweep 14 and the contractions 9; as separate passes over
 // the points (tables, four evaluations of each pair, right-hand sides from the stored marginals) it was 196 us.
 template <int NB>
 __global__ __launch_bounds__(kEmsThreads) void k_ems_accumulate(const float2 *__restrict__ data, const float2 *__restrict__ phi,
@@ -524,12 +526,15 @@ __global__ __launch_bounds__(kEmsThreads) void k_ems_accumulate(const float2 *__
                 for (int f = 0; f < NB * NB; ++f) e[f] = fmaxf(e[f], 0.f);
                 d2m = 0.f;
             }
-            // every weight of the point carries the same rounding of dmc, which the division by the sum takes out
-            const float dmc = em_sqrt(d2m) * c;
+            // The difference first: the nearest centre's weight is exactly 1 at every temperature.  One fused multiply-add with
+            // dmin c would carry the rounding of dmin c, up to 2^-24 dmin c, into every exponent: once T is below some 1e-9 dmin
+            // all weights of a point are then 0 or infinity.  (8192 points, 64 x 64 pairs: 44.2 us an iteration against 43.2 with the
+            // fused form, 45.2 with a branch between the two.)
+            const float dmin = em_sqrt(d2m);
             float row[NB], col[NB];
 #pragma unroll
             for (int f = 0; f < NB * NB; ++f) {
-                const float w = __builtin_amdgcn_exp2f(__builtin_fmaf(em_sqrt(e[f]), -c, dmc));
+                const float w = __builtin_amdgcn_exp2f((dmin - em_sqrt(e[f])) * c);
                 e[f] = w;
                 row[f / NB] = f % NB == 0 ? w : row[f / NB] + w;
                 col[f % NB] = f < NB ? w : col[f % NB] + w;
@@ -935,7 +940,9 @@ commvq_status commvq_em_step_shared(const float *data, int32_t group, int32_t n_
     hipStream_t s = static_cast<hipStream_t>(stream);
     const float2 *d2 = reinterpret_cast<const float2 *>(data);
     float2 *p2 = reinterpret_cast<float2 *>(phi);
-    const float c = kLog2eEm / temperature;
+    // A normal, finite number for every T > 0: 0 (T = infinity) would make NaN of the padding's infinite distances, infinity
+    // of the nearest centre's zero.  At either end the weights are what they would be beyond it: all alike, or one centre's.
+    const float c = std::min(std::max(kLog2eEm / temperature, FLT_MIN), FLT_MAX);
     switch (l.np) {
         case 16: return ems_launch<2>(l, d2, p2, part, sums, N, J, Nc, c, s);
         case 32: return ems_launch<4>(l, d2, p2, part, sums, N, J, Nc, c, s);

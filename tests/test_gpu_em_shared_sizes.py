@@ -32,3 +32,28 @@ def test_a_point_on_a_centre(em_shared, oracle):  # noqa: F811
     got = em_shared(data, start, 0.5)
     ref, _ = oracle.em_step_shared(data, start, temperature=0.5)
     assert np.isfinite(got).all() and np.abs(got - ref).max() <= 2e-3 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("T", [1e-40, 1e-37, 1e-20, 1e-10, 1e-9, 1e6, 1e30, float("inf")])
+@pytest.mark.parametrize("J,Nc,N", [(8, 12, 3000), (5, 16, 1500), (8, 33, 9000)])
+def test_temperatures_from_hard_to_uniform_assignment(em_shared, oracle, J, Nc, N, T):  # noqa: F811
+    """Every temperature above zero: as T -> 0 a point belongs to its nearest centre, as T -> infinity to all alike.
+
+    Points whose two nearest centres differ by less than 1e-3 are left out (fp32 distances would decide them), so that for
+    the small temperatures both sides assign every point to the same centre and N_ab is a sum of whole numbers.
+    Tolerance: the right-hand sides are fp32 sums of up to 36 points per wavefront, 8 wavefronts and 256 partial sums: 300
+    roundings of 2^-24, 1.8e-5, if all went one way."""
+    data, start = shared_calibration(J, N, Nc, seed=J * 77 + Nc)
+    z = start[..., 0].astype(np.complex128) + 1j * start[..., 1]
+    cen = (z[:, :, None] + 1j * z[:, None, :]).reshape(J, -1)                      # [J][Nc^2]
+    k = data[..., 0].astype(np.complex128) + 1j * data[..., 1]                     # [N][J]
+    d2 = (np.abs(k) ** 2).sum(1)[:, None] + (np.abs(cen) ** 2).sum(0) - 2 * (k @ cen.conj()).real
+    near = np.sqrt(np.sort(d2, axis=1)[:, :2])
+    data = data[near[:, 1] - near[:, 0] > 1e-3]
+    print(f"case group={J} Nc={Nc} N={len(data)} T={T:g}", flush=True)
+    got = em_shared(data, start, T)
+    ref, _ = oracle.em_step_shared(data, start, temperature=None if T < 1e-8 else T)
+    assert np.isfinite(got).all()
+    worst = np.abs(got - ref).max() / np.abs(ref).max()
+    print(f"  max relative deviation of phi: {worst:.3e}", flush=True)
+    assert worst <= 2e-5
