@@ -144,7 +144,8 @@ commvq_status commvq_create_planner(const commvq_config *config, commvq_handle *
 
 /* Host-only: work decomposition and workspace size for a batch shape.  COMMVQ_ERR_SHAPE if batch < 1,
  * max_seqlen < 1, total_tokens outside [max_seqlen, batch * max_seqlen] or above 2^30, or if one (sequence,
- * KV head) stream (max_seqlen * bytes per token of codes, unpacked pair indices or logits) passes 2^32 - 1 bytes. */
+ * KV head) stream (max_seqlen * bytes per token of codes, unpacked pair indices or logits) passes 2^32 - 1 bytes.
+ * A shorter context can need more than a longer one (it is cut into more pieces): size for every shape that occurs. */
 commvq_status commvq_plan_query(const commvq_handle *handle, int32_t batch, int64_t total_tokens,
                                 int32_t max_seqlen, commvq_plan *plan);
 commvq_status commvq_workspace_bytes(const commvq_handle *handle, int32_t batch, int64_t total_tokens,

@@ -41,17 +41,19 @@ static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 namespace {
 
 struct Workspace {
-    float *scores;    // [T * Hq] scaled logits
     float2 *sstat;    // [B * Hq * score_splits] (max, sum of exp(logit - max)) of each score split
+    float *scores;    // [T * Hq] scaled logits
+    // written and read by the value and output stages only
     float *vscale;    // [B * Hq * value_splits] 2^-S: value of one fixed-point unit of that split's bins
     float *lsum;      // [B * Hq * value_splits] sum of exp(logit - sequence max) over the score tiles that begin in that value split
     unsigned *bins;   // [B * Hkv * value_splits][K][Mv][G] fixed-point bins (codeword-major: see k_bins)
     float *partial;   // [B * Hq * out_chunks][d]
+    uint4 *packed_val;    // value codebook re-laid for k_out_mfma (batches; only if the caller has not packed it)
+    // written and read by the score stage only, in the same memory as the above; in front of them, right behind `scores`, the
+    // partial logits of slice groups 1, 2, .. when the score tiles are also cut along the slices (group 0's are in `scores`)
     uint4 *packed;    // key codebook re-laid slice-major for k_score_stream / k_score_pair
     uint8_t *pair_bytes;  // paired-code keys: one byte per index, [T * Hkv][32 * blocks]
     float *lut;           // position-free keys: scale * q . C, [B * Hkv][M_k * K][G]
-    float *scores_part;   // [slice groups][T * Hq] partial logits when the score tiles are also cut along the slices
-    uint4 *packed_val;    // value codebook re-laid for k_out_mfma (batches; only if the caller has not packed it)
     size_t bytes;
 };
 
@@ -85,6 +87,52 @@ inline size_t packed_key_bytes(const commvq_config &c)
     return (size_t)c.n_kv_heads * c.m_key * kK * kD * 2;
 }
 
+// Value split for statistics tiles of slen tokens.
+int value_split_len(const commvq_handle *h, int B, int max_seqlen, int slen)
+{
+    const int units = B * h->cfg.n_kv_heads;
+    int nv = 256 / units;  // about one value workgroup per compute unit
+    if (bin_values(h->cfg))  // a workgroup of the binary-code value kernel: 16 query heads x 1024 code bits of one token range
+        nv = 256 / (B * ((h->cfg.n_q_heads + kVbitsHeads - 1) / kVbitsHeads) * (h->cfg.value_bits / kVbitsCols));
+    if (nv < 1) nv = 1;
+    int vlen = (max_seqlen + nv - 1) / nv;
+    // a value split is a whole number of statistics tiles (score tiles; 1024 tokens when k_score_combine writes the
+    // statistics), or a power-of-two fraction of one (never less than 1024 tokens): k_bins takes its exp-sums from them
+    if (vlen >= slen || slen <= 1024) {
+        const int round_to = slen > 1024 ? slen : 1024;
+        vlen = (vlen + round_to - 1) / round_to * round_to;
+    } else {
+        int part = 1024;
+        while (part < vlen) part *= 2;
+        vlen = part;  // 1024 or 2048 inside a 2048- or 4096-token tile
+    }
+    // the binary-code value kernel sums signed digit x bit products in 32-bit accumulators: |digit| <= 2^7, |bit byte| <= 2^7,
+    // so a range of at most 2^16 tokens stays within 2^30
+    if (bin_values(h->cfg) && vlen > (1 << 16)) vlen = 1 << 16;
+    return vlen;
+}
+
+// Bytes of the logits, and from one slice group's partial logits to the next's.
+inline size_t logit_bytes(const commvq_handle *h, int64_t T) { return align_up((size_t)T * h->cfg.n_q_heads * 4, 256); }
+
+// Bytes of the workspace that only the value and output stages use (Workspace: vscale to packed_val).
+size_t value_stage_bytes(const commvq_handle *h, int B, size_t vsplits)
+{
+    const commvq_config &c = h->cfg;
+    const size_t rows = (size_t)val_books(c) * kK, heads = (size_t)B * c.n_q_heads;
+    return 2 * align_up(heads * vsplits * 4, 256) + align_up(heads * vsplits * rows * 4, 256) + align_up(heads * (rows / kOutRows) * kD * 4, 256) +
+           (use_out_mfma(h, B) ? align_up((size_t)c.n_kv_heads * rows * kD * 2, 256) : 0);
+}
+
+// Launches of so few tokens that 1024-token tiles leave compute units without one: a tile's partial logits for each unit.
+size_t few_tile_bytes(const commvq_handle *h, int B, int64_t T, int max_seqlen)
+{
+    const int64_t tiles = (int64_t)B * h->cfg.n_kv_heads * ((max_seqlen + 1023) / 1024);
+    int64_t cut = 1;
+    while (2 * cut <= h->cfg.m_key / 2 && 2 * cut * tiles <= 256) cut *= 2;
+    return cut > 1 ? (size_t)cut * logit_bytes(h, T) : 0;
+}
+
 // How k_score_stream cuts a launch: `passes` segments of 512 tokens per workgroup, `tiles` workgroups per KV head, each of
 // them once per slice group.
 struct StreamShape {
@@ -103,10 +151,15 @@ StreamShape stream_shape(const commvq_handle *h, int B, int64_t T, int max_seqle
     const bool two = h->cfg.m_key == 32;
     const double fixed = 9.0, sw = two ? 1.25 : h->G == 8 ? 0.6 : 0.5, c = two ? (h->G == 8 ? 0.70 : 0.66) : (h->G == 8 ? 0.47 : 0.41);
     const double part = (double)T * h->cfg.n_q_heads / 1e6 + (two ? 0.08 : 0.15);
+    // The partial logits may not need more memory than the bins that follow them, apart from few_tile_bytes: a shape that fits a
+    // workspace of some size (the static one in particular) must not outgrow it for the sake of a faster cut.
+    const int vlen = value_split_len(h, B, max_seqlen, 1024);
+    const size_t one = logit_bytes(h, T);
+    const size_t room = value_stage_bytes(h, B, (size_t)(max_seqlen + vlen - 1) / vlen) + few_tile_bytes(h, B, T, max_seqlen);
     StreamShape best = {2, 1, 1};
     double t_best = 1e30;
     for (int passes = 2; passes <= kStreamPasses; ++passes)
-        for (int e = 1; e <= kStreamSlices; e *= 2) {
+        for (int e = 1; e <= kStreamSlices && (e - 1) * one <= room; e *= 2) {
             const int64_t wgs = (likely + passes - 1) / passes * h->cfg.n_kv_heads * e;
             const double t = (double)((wgs + 255) / 256) * (fixed + (double)(kStreamSlices / e) * (sw + passes * c)) + (e > 1 ? 5.0 + e * part : 0.0);
             if (t < t_best * 0.9999) { t_best = t; best = StreamShape{passes, 0, e}; }
@@ -147,25 +200,7 @@ void make_plan(const commvq_handle *h, int B, int64_t T, int max_seqlen, bool sl
     }
     p->score_split_len = len;
     p->score_splits = (max_seqlen + len - 1) / len;
-    int nv = 256 / units;  // about one value workgroup per compute unit
-    if (bin_values(h->cfg))  // a workgroup of the binary-code value kernel: 16 query heads x 1024 code bits of one token range
-        nv = 256 / (B * ((h->cfg.n_q_heads + kVbitsHeads - 1) / kVbitsHeads) * (h->cfg.value_bits / kVbitsCols));
-    if (nv < 1) nv = 1;
-    int vlen = (max_seqlen + nv - 1) / nv;
-    // a value split is a whole number of statistics tiles (score tiles; 1024 tokens when k_score_combine writes the
-    // statistics), or a power-of-two fraction of one (never less than 1024 tokens): k_bins takes its exp-sums from them
-    const int slen = groups > 1 ? 1024 : len;
-    if (vlen >= slen || slen <= 1024) {
-        const int round_to = slen > 1024 ? slen : 1024;
-        vlen = (vlen + round_to - 1) / round_to * round_to;
-    } else {
-        int part = 1024;
-        while (part < vlen) part *= 2;
-        vlen = part;  // 1024 or 2048 inside a 2048- or 4096-token tile
-    }
-    // the binary-code value kernel sums signed digit x bit products in 32-bit accumulators: |digit| <= 2^7, |bit byte| <= 2^7,
-    // so a range of at most 2^16 tokens stays within 2^30
-    if (bin_values(h->cfg) && vlen > (1 << 16)) vlen = 1 << 16;
+    const int vlen = value_split_len(h, B, max_seqlen, groups > 1 ? 1024 : len);
     p->value_split_len = vlen;
     p->value_splits = (max_seqlen + vlen - 1) / vlen;
     p->out_chunks = val_books(h->cfg) * kK / kOutRows;
@@ -182,8 +217,12 @@ inline int stat_len(const commvq_handle *h, const commvq_plan &p)
 }
 inline int stat_splits(const commvq_handle *h, const commvq_plan &p, int max_seqlen) { return (max_seqlen + stat_len(h, p) - 1) / stat_len(h, p); }
 
-// Carves the workspace.  Array sizes are the larger of what the two score kernels need, so one
-// workspace size serves a batch shape whether or not explicit positions are passed.
+// Carves the workspace.  Array sizes are the larger of what the two score kernels need, so one workspace size serves a batch
+// shape whether or not explicit positions are passed.  Behind the statistics, the logits and the partial logits, the score
+// stage's arrays and those of the value and output stages share memory: the stages of a call run one after the other, and
+// no kernel of one touches what only the other uses.  The latter arrays lie over the partial logits too, except in launches of
+// few tokens as far as there is room: lines that other XCDs have just had in their L2 cost the bins' writes 0.8 us (1237
+// tokens, 32 + 32 codebooks: 31.7 us a call, 30.9 apart).
 void carve(const commvq_handle *h, int B, int64_t T, int max_seqlen, void *base, Workspace *w)
 {
     const commvq_config &c = h->cfg;
@@ -192,24 +231,30 @@ void carve(const commvq_handle *h, int B, int64_t T, int max_seqlen, void *base,
     make_plan(h, B, T, max_seqlen, false, &pb);
     const size_t ssplits = std::max<size_t>(std::max(pa.score_splits, pb.score_splits), (size_t)stat_splits(h, pa, max_seqlen));
     const size_t vsplits = pa.value_splits > pb.value_splits ? pa.value_splits : pb.value_splits;
+    const size_t heads = (size_t)B * c.n_q_heads, rows = (size_t)val_books(c) * kK;
+    const bool bf16 = c.codebook_dtype == COMMVQ_BF16;
     size_t off = 0;
     auto take = [&](size_t n_floats) {
         float *ptr = base ? reinterpret_cast<float *>(static_cast<char *>(base) + off) : nullptr;
         off += align_up(n_floats * sizeof(float), 256);
         return ptr;
     };
+    w->sstat = reinterpret_cast<float2 *>(take(heads * ssplits * 2));
     w->scores = take((size_t)T * c.n_q_heads);
-    w->sstat = reinterpret_cast<float2 *>(take((size_t)B * c.n_q_heads * ssplits * 2));
-    w->vscale = take((size_t)B * c.n_q_heads * vsplits);
-    w->lsum = take((size_t)B * c.n_q_heads * vsplits);
-    w->bins = reinterpret_cast<unsigned *>(take((size_t)B * c.n_kv_heads * vsplits * h->G * val_books(c) * kK));
-    w->partial = take((size_t)B * c.n_q_heads * pa.out_chunks * kD);
-    w->packed = reinterpret_cast<uint4 *>(take(packed_key_bytes(c) / 4));
+    const size_t parts = bf16 && stream_keys(c) ? (pa.score_slice_groups - 1) * logit_bytes(h, T) : 0;
+    const size_t shared = off += parts;
+    w->packed = bf16 && !c.position_free ? reinterpret_cast<uint4 *>(take(packed_key_bytes(c) / 4)) : nullptr;
     w->pair_bytes = pair_keys(c) ? reinterpret_cast<uint8_t *>(take((size_t)T * c.n_kv_heads * 8 * pair_blocks(c))) : nullptr;
-    w->lut = c.position_free ? take((size_t)B * c.n_q_heads * c.m_key * kK) : nullptr;
-    w->scores_part = pa.score_slice_groups > 1 ? take((size_t)pa.score_slice_groups * T * c.n_q_heads) : nullptr;
-    w->packed_val = use_out_mfma(h, B) ? reinterpret_cast<uint4 *>(take((size_t)c.n_kv_heads * val_books(c) * kK * kD * 2 / 4)) : nullptr;
-    w->bytes = off;
+    w->lut = c.position_free ? take(heads * c.m_key * kK) : nullptr;
+    const size_t score_end = off, value_bytes = value_stage_bytes(h, B, vsplits);
+    const size_t few = few_tile_bytes(h, B, T, max_seqlen), apart = few ? few + std::min(score_end - shared, value_bytes) : 0;
+    off = shared - (parts > apart ? parts - apart : 0);
+    w->vscale = take(heads * vsplits);
+    w->lsum = take(heads * vsplits);
+    w->bins = reinterpret_cast<unsigned *>(take(heads * vsplits * rows));
+    w->partial = take(heads * pa.out_chunks * kD);
+    w->packed_val = use_out_mfma(h, B) ? reinterpret_cast<uint4 *>(take((size_t)c.n_kv_heads * rows * kD * 2 / 4)) : nullptr;
+    w->bytes = std::max(off, score_end);
 }
 
 // ------------------------------------------------------------------ k_score
@@ -1221,11 +1266,10 @@ __device__ __forceinline__ void write_tile_logits(const float (&sc)[NPASS][NGRP]
 // ------------------------------------------------------------------ k_score_combine
 // Score tiles that were also cut along the codebook slices (short contexts): the logit of a token is the sum of the
 // partial logits of the slice groups (Eq. new_attention's sum over the sub-spaces, split in `groups` parts).  One
-// workgroup per (sequence, query head, 1024 tokens): adds the parts in a fixed order, writes the logits and the
-// (max, sum of exp) of its 1024 tokens.
+// workgroup per (sequence, query head, 1024 tokens): adds the parts in a fixed order, writes the logits (over the
+// first group's part) and the (max, sum of exp) of its 1024 tokens.
 constexpr int kCombineThreads = 256;
-__global__ __launch_bounds__(kCombineThreads) void k_score_combine(const float *__restrict__ part, float *__restrict__ scores,
-                                                                  float2 *__restrict__ sstat, const int32_t *__restrict__ cu,
+__global__ __launch_bounds__(kCombineThreads) void k_score_combine(float *scores, float2 *__restrict__ sstat, const int32_t *__restrict__ cu,
                                                                   int Hq, int nsplit, int tile_len, int groups, long long part_stride)
 {
     __shared__ float red[kCombineThreads / 64];
@@ -1249,14 +1293,18 @@ __global__ __launch_bounds__(kCombineThreads) void k_score_combine(const float *
             // all parts requested at once (at most 16 slice groups), added in a fixed order
             float pv[16];
 #pragma unroll
-            for (int e = 0; e < 16; ++e) pv[e] = e < groups ? part[(size_t)e * part_stride + row + tok] : 0.f;
+            for (int e = 0; e < 16; ++e) pv[e] = e < groups ? scores[(size_t)e * part_stride + row + tok] : 0.f;
             float acc = pv[0];
 #pragma unroll
             for (int e = 1; e < 16; ++e) acc += pv[e];
-            scores[row + tok] = acc;
             v[k] = acc;
             mx = fmaxf(mx, acc);
         }
+    }
+#pragma unroll
+    for (int k = 0; k < MAXV; ++k) {  // over the first group's part, once nothing of it is wanted any more
+        const int tok = t0 + k * kCombineThreads + (int)threadIdx.x;
+        if (k * kCombineThreads < tile_len && tok < t1) scores[row + tok] = v[k];
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     mx = wave_max(mx);
@@ -2696,19 +2744,18 @@ commvq_status run_scores(commvq_handle *h, const void *q, const uint8_t *key_cod
             const StreamShape ss = stream_shape(h, pos->batch, pos->total_tokens, pos->max_seqlen);
             StreamArgs sa;
             sa.q = q; sa.key_codes = key_codes; sa.packed = packed; sa.cu = pos->cu_seqlens; sa.q_pos = pos->q_pos;
-            sa.tbl_hi = h->tbl_hi; sa.tbl_lo = h->tbl_lo; sa.scores = ss.groups > 1 ? w.scores_part : w.scores; sa.sstat = w.sstat;
+            sa.tbl_hi = h->tbl_hi; sa.tbl_lo = h->tbl_lo; sa.scores = w.scores; sa.sstat = w.sstat;
             sa.d.Hq = c.n_q_heads; sa.d.Hkv = c.n_kv_heads; sa.d.G = h->G; sa.d.batch = pos->batch; sa.d.n_hi = h->n_hi;
             sa.d.q_bf16 = c.q_dtype == COMMVQ_BF16; sa.d.scale = h->scale;
             sa.d.tiles = ss.tiles; sa.d.groups = ss.groups;
             sa.d.nstat = stat_splits(h, plan, pos->max_seqlen);
-            sa.d.part_stride = (long long)pos->total_tokens * c.n_q_heads;
+            sa.d.part_stride = (long long)(logit_bytes(h, pos->total_tokens) / 4);
             const int grid = c.n_kv_heads * ss.tiles * ss.groups;
             e = launch_stream(sa, c.m_key, ss.passes, grid, s);
             if (e == hipSuccess && ss.groups > 1) {
                 const int ns = sa.d.nstat;
                 hipLaunchKernelGGL(k_score_combine, dim3((unsigned)(pos->batch * c.n_q_heads * ns)), dim3(kCombineThreads), 0, s,
-                                   w.scores_part, w.scores, w.sstat, pos->cu_seqlens, c.n_q_heads, ns, stat_len(h, plan), ss.groups,
-                                   sa.d.part_stride);
+                                   w.scores, w.sstat, pos->cu_seqlens, c.n_q_heads, ns, stat_len(h, plan), ss.groups, sa.d.part_stride);
                 e = hipGetLastError();
             }
         }

@@ -267,6 +267,56 @@ def test_static_scratch_entry_point_checks_its_arguments(planner):
     assert call(cv.binding.make_positions(1, _Buf(4096), _Buf(8192), None, 0, 0)) == 3
 
 
+@pytest.mark.parametrize("kw,B,T,L", [
+    (dict(m_key=16, m_val=16), 8, 24000, 3000),                   # the 8B-shaped layer at 1 bit, eight chats
+    (dict(n_q_heads=64, m_key=16, m_val=16), 1, 24000, 24000),    # the 70B-shaped layer at 1 bit
+    (dict(m_key=32, m_val=32), 2, 28800, 24000)])                 # the 8B-shaped layer at 2 bits, two sequences
+def test_static_scratch_holds_contexts_cut_along_the_slices(planner, kw, B, T, L):
+    h = planner(**kw)
+    a = _call_args(h)
+    pos = cv.binding.make_positions(B, _Buf(4096), _Buf(8192), None, T, L)
+    assert cv.commvq_workspace_bytes(h, B, T, L) <= cv.commvq_static_scratch_bytes()
+    assert status_of(cv.commvq_decode_attn_static, h, a["q"], a["key_codes"], a["val_codes"], a["key_codebooks"],
+                     a["val_codebooks"], pos, a["out"]) == 6              # acceptable: a full handle would launch
+
+
+@pytest.mark.parametrize("kw", [
+    dict(m_key=16, m_val=16), dict(m_key=32, m_val=32), dict(m_key=32, m_val=16), dict(n_q_heads=64, m_key=32, m_val=16),
+    dict(n_q_heads=1, n_kv_heads=1, m_key=16, m_val=16), dict(n_q_heads=16, n_kv_heads=2, m_key=32, m_val=16),
+    dict(n_q_heads=32, n_kv_heads=32, m_key=16, m_val=16), dict(m_key=16, value_format=cv.COMMVQ_VALUES_BINARY, value_bits=1024)])
+def test_partial_logits_do_not_enlarge_the_workspace(planner, kw):
+    """Tiles that are also cut along the slices: the partial logits lie where the bins are written later.  Only launches of at
+    most 128 tiles of 1024 tokens, which would leave compute units without a tile, may need more than that, one
+    tile's logits per compute unit."""
+    cfg = good_cfg(**kw)
+    h, gather = planner(**kw), planner(**dict(kw, codebook_dtype=0))      # (the latter plans as with explicit positions)
+    Hq, Hkv, G = cfg.n_q_heads, cfg.n_kv_heads, cfg.n_q_heads // cfg.n_kv_heads
+    up = lambda n: -(-n // 256) * 256
+    rows = cfg.value_bits if cfg.value_format else cfg.m_val * 256
+    cut = 0
+    for B in (1, 2, 3, 8, 16, 24):
+        for L in (1, 300, 800, 1237, 1536, 1792, 3000, 4096, 5001, 10500, 16384, 24000, 32951, 65536, 74436, 131072):
+            for T in sorted({max(L, B * L // 2), B * L}):
+                p, pg = cv.commvq_plan_query(h, B, T, L), cv.commvq_plan_query(gather, B, T, L)
+                nv = max(p.value_splits, pg.value_splits)
+                cut += p.score_slice_groups > 1
+                logits = up(4 * T * Hq)
+                stats = up(8 * B * Hq * max(-(-L // 512), pg.score_splits))
+                value = (2 * up(4 * B * Hq * nv) + up(4 * B * Hq * nv * rows) + up(4 * B * Hq * p.out_chunks * 128)
+                         + (up(2 * Hkv * rows * 128) if B * G >= 16 else 0))
+                packed = Hkv * cfg.m_key * 256 * 128 * 2
+                few = 4 * 1024 * 256 * G + 256 * 16 if B * Hkv * -(-L // 1024) <= 128 else 0
+                assert cv.commvq_workspace_bytes(h, B, T, L) <= logits + stats + packed + value + few, (B, T, L)
+    assert cut > 20
+
+
+@pytest.mark.parametrize("kw", [dict(m_key=16, m_val=16), dict(m_key=32, m_val=32), dict(n_q_heads=64, m_key=16, m_val=16)])
+def test_sixteen_chats_never_need_less_workspace_for_longer_contexts(planner, kw):
+    h = planner(**kw)
+    need = [cv.commvq_workspace_bytes(h, 16, 16 * L, L) for L in (512, 1024, 1280, 1536, 1600, 1792, 2048, 2560, 3072, 4096)]
+    assert need == sorted(need)
+
+
 def test_bench_refuses_more_than_one_gpu():
     # one GPU per box in this build: --gpus N > 1 exits with a message and prints no result line
     import subprocess

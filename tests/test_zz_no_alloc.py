@@ -60,3 +60,33 @@ def test_static_scratch_entry_point_matches_workspace_entry_point(oracle):
     assert e.value.status == 4
     op_big.close()
     op2.close()
+
+
+@pytest.mark.parametrize("B,L,Hq,Mk,Mv", [(8, 3000, 32, 16, 16), (1, 24000, 64, 16, 16), (2, 24000, 32, 32, 32)])
+def test_tiles_cut_along_the_slices_fit_the_static_scratch(oracle, B, L, Hq, Mk, Mv):
+    """Partial logits, packed codebook and bins share memory: the static array holds these shapes, and the outputs do not depend on
+    what the workspace held or on where the packed codebook lies."""
+    import torch
+    import paper_2506_18879_amd as cv
+    from paper_2506_18879_amd import device
+    lens = [L if i == 0 else max(1, L // 5 - 61 * i) if B == 2 else L - 7 * i for i in range(B)]
+    w = synth.make_workload(f"cut_b{B}", B=B, Hq=Hq, Hkv=8, seqlens=lens, Mk=Mk, Mv=Mv, dtype="bf16", seed=B + L)
+    op, dw, ref, out = _both(cv, device, w, torch)
+    print(f"case B={B} L={L} groups={op.plan.score_slice_groups} workspace={op.workspace_bytes}", flush=True)
+    assert op.plan.score_slice_groups > 1 and op.workspace_bytes <= cv.commvq_static_scratch_bytes()
+    assert torch.equal(out, ref)
+    op.workspace.fill_(0xFF)                                       # NaN wherever it is read as a float
+    assert torch.equal(op(dw), ref)
+    op.workspace.fill_(0xFF)
+    assert torch.equal(op.staged(dw), ref)
+    op.pack_key_codebooks(dw)
+    op.pack_value_codebooks(dw)
+    op.workspace.fill_(0xFF)
+    assert torch.equal(op(dw), ref)
+    want = oracle.decode_attn(w.as_f64("q"), w.key_codes, w.val_codes, w.as_f64("key_codebooks"), w.as_f64("val_codebooks"),
+                              w.cu_seqlens, w.q_pos, rope_base=w.rope_base, unit_mask=np.eye(1, 8 * B, 3, dtype=bool).reshape(B, 8),
+                              n_threads=16)
+    G = Hq // 8
+    got, want = ref.cpu().numpy().astype(np.float64)[0, 3 * G:4 * G], want[0, 3 * G:4 * G]
+    assert (np.abs(got - want).max(axis=-1) / np.abs(want).max(axis=-1)).max() <= 2e-5
+    op.close()
