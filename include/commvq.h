@@ -245,7 +245,10 @@ commvq_status commvq_forget_packed_value_codebooks(commvq_handle *handle, const 
  * Each new (pre-RoPE) key vector is assigned to its nearest clustering centre (the E step of Sec. 4.2),
  * level by level on the error left by the previous levels (residual refinement, Sec. 4.2); a centre of
  * the paired format is C[r][a] + i C[r][b] (Eq. def_center, App. A.1), searched over all 64 x 64 pairs.
- * Distances are compared in fp32 as ||c||^2 - 2 res.c; ties go to the lowest index (a * 64 + b).
+ * Distances are compared in fp32 as ||c||^2 - 2 res.c, for the paired format summed as (||C[a]||^2 - 2 res.C[a]) +
+ * ((||C[b]||^2 - 2 res.(i C[b])) + 2 C[a].(i C[b])); ties go to the lowest index (a * 64 + b).  The dot products are
+ * summed in an order that depends on how many tokens a call encodes: a vector that is as near to two centres up to
+ * fp32 rounding can get the one in a small call and the other in a large one.
  *   commvq_encoder_table_bytes / commvq_encoder_prepare
  *       one-time tables for a set of key codebooks (squared norms of all rows; paired: plus the
  *       cross terms 2 C[a].(i C[b])): `tables` is a device buffer of that many bytes, 16-byte aligned

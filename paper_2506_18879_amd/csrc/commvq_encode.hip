@@ -60,8 +60,8 @@ __device__ __forceinline__ void min4(float &best, int &index)
     lower(b32[0], b32[1], i32[0], i32[1]);
 }
 
-// The same over the two halves of a wavefront: lanes l and l ^ 32.
-__device__ __forceinline__ void min2_halves(float &best, int &index)
+// The same over the two halves of a wavefront, lanes l and l ^ 32; returns which of them held it.
+__device__ __forceinline__ bool min2_halves(float &best, int &index)
 {
     const unsigned b = __builtin_bit_cast(unsigned, best), i = (unsigned)index;
     auto b32 = __builtin_amdgcn_permlane32_swap(b, b, false, false);
@@ -70,6 +70,7 @@ __device__ __forceinline__ void min2_halves(float &best, int &index)
     const bool second = f1 < f0 || (f1 == f0 && (int)i32[1] < (int)i32[0]);
     best = second ? f1 : f0;
     index = second ? (int)i32[1] : (int)i32[0];
+    return second;
 }
 
 // The least of the 64 lanes' non-negative indices, in every lane.
@@ -303,14 +304,15 @@ __global__ __launch_bounds__(kErThreads) void k_encode_rows(const void *__restri
 //   ||c_ab||^2 - 2 res . c_ab = U[a] + (V[b] + X[a][b]),  U = N[a] - 2 P[a],  V = N[b] - 2 Q[b]
 // The scan is a minimum over b of V[b] + X[a][b] for every a and token.  The sums are matrix instructions too: for one a
 // and 32 tokens, result[b][token] = V[b][token] + x0 * 1 + x1 * 1 + x2 * 1 with V in the accumulator operand and the exact
-// bf16 parts of X[a][b] along k.  That is 1024 sums in 32 clk where vector adds take 64, and a cross term is read from LDS
+// bf16 parts of X[a][b] along k.  (Measured: one rounded addition of V and X while their exponents are within 2 of each
+// other, otherwise up to a unit in the last place beside it.)  That is 1024 sums in 32 clk where vector adds take 64, and a cross term is read from LDS
 // once for 32 tokens; what is left to the vector unit is half a three-way minimum per centre.
 // Four wavefronts, one per SIMD: 4 / RS sets of 32 tokens.  The RS wavefronts of a set share the rows a of the scan (and
 // compute only their part of P); residual, split and Q are each wavefront's own: handing them round through LDS, with
 // eight wavefronts and the residuals split between two, cost more than it saved (8.9 us a level at RS = 1's sizes).
-// A level takes 8.1 us with RS = 1 (128 tokens), 6.0 (2) and 5.2 (4), of which a row of the scan is 50 ns: two matrix
+// A level takes 8.2 us with RS = 1 (128 tokens), 6.1 (2) and 5.1 (4), of which a row of the scan is 50 ns: two matrix
 // instructions (64 clk) and 21 vector ones (90 clk) that hide in each other only where they alternate in the program, so
-// the order is fixed below (left to the compiler: 90 ns).  32000 vectors, 21 levels: 172 us, 8192 vectors 113; with the
+// the order is fixed below (left to the compiler: 90 ns).  32768 vectors, 21 levels: 179 us, 8192 vectors 113; with the
 // scan's sums on the vector unit and cross terms read per 16 tokens 258 and 165.
 //   32 x 32 operands: lane (n, h) supplies row / token n and elements 8 h .. + 7 of a chunk of 16 (scan: 4 h .. + 3 of 8)
 //   32 x 32 result  : lane (n, h) receives, in register i, row 8 (i / 4) + 4 h + i % 4 for token n
@@ -320,8 +322,8 @@ constexpr int kEpRows = 0;                          // [C | i C][64] rows of 256
 constexpr int kEpParts = 2 * 64 * 256;              // [64 a][64 b] x0, x1, x2, 0 of the cross terms, 8 bytes each
 constexpr int kEpCross = kEpParts + 4096 * 8;       // [64 a][64 b] cross terms, float4 x of row a in slot x xor (a mod 16)
 constexpr int kEpNorms = kEpCross + 4096 * 4;       // [64]
-constexpr int kEpMin = kEpNorms + 64 * 4;           // [4 wavefronts][32 tokens] minimum and its row
-constexpr int kEpChosen = kEpMin + 4 * 32 * 8;      // [tokens][32 levels][2]
+constexpr int kEpMin = kEpNorms + 64 * 4;           // [4 wavefronts][32 tokens] minimum, its row and that row's U
+constexpr int kEpChosen = kEpMin + 4 * 32 * 16;     // [tokens][32 levels][2]
 constexpr int ep_lds(int rs) { return kEpChosen + 128 / rs * 64; }
 static_assert(ep_lds(1) <= 163840, "LDS of a compute unit");
 typedef float floatx16_t __attribute__((ext_vector_type(16)));
@@ -465,7 +467,7 @@ __global__ __launch_bounds__(kEpThreads, 2) void k_encode_pairs(const void *__re
         }
         // stage one: the row a of the nearest centre.  The sums of a row are issued before the minimum of the row
         // before it is taken; a pair of rows (r, r + 4) gives each half of the wavefront one of them to finish.
-        float best = INFINITY;
+        float best = INFINITY, ubest = U[0];  // (and the row's U)
         int bi = 0;
         {
             const uint2_t *xs = reinterpret_cast<const uint2_t *>(lds + kEpParts) + a0 * 64 + n;
@@ -501,27 +503,33 @@ __global__ __launch_bounds__(kEpThreads, 2) void k_encode_pairs(const void *__re
                         const auto sw = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, half[0]), __builtin_bit_cast(unsigned, half[1]), false, false);
                         const int i = (k >> 1) - 1;
                         const float sc = U[i] + least(__builtin_bit_cast(float, (unsigned)sw[0]), __builtin_bit_cast(float, (unsigned)sw[1]));
-                        if (sc < best) { best = sc; bi = i; }  // a lane's rows come in increasing order
+                        if (sc < best) { best = sc; bi = i; ubest = U[i]; }  // a lane's rows come in increasing order
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
         int ca = a0 + 8 * (bi >> 2) + 4 * h + (bi & 3);
-        min2_halves(best, ca);
+        {
+            const bool second = min2_halves(best, ca);
+            const auto u32 = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, ubest), __builtin_bit_cast(unsigned, ubest), false, false);
+            ubest = __builtin_bit_cast(float, second ? (unsigned)u32[1] : (unsigned)u32[0]);
+        }
         if (RS > 1) {
-            float2 *pm = reinterpret_cast<float2 *>(lds + kEpMin);
-            if (h == 0) pm[wave * 32 + n] = make_float2(best, __builtin_bit_cast(float, ca));
+            float4 *pm = reinterpret_cast<float4 *>(lds + kEpMin);
+            if (h == 0) pm[wave * 32 + n] = make_float4(best, __builtin_bit_cast(float, ca), ubest, 0.f);
             __syncthreads();
-            float2 m = pm[set * 32 + n];
+            float4 m = pm[set * 32 + n];
 #pragma unroll
             for (int w = 1; w < RS; ++w) {
-                const float2 o = pm[(w * kSets + set) * 32 + n];
+                const float4 o = pm[(w * kSets + set) * 32 + n];
                 if (o.x < m.x) m = o;  // rows come in increasing order
             }
             ca = __builtin_bit_cast(int, m.y);
+            ubest = m.z;
         }
-        // stage two: the partner b of row ca, the lowest of equals
+        // stage two: the partner b of row ca, the lowest of those whose whole cost is the least.  (V + X alone would tell apart
+        // costs that are equal in fp32, and give a vector another code than k_encode_one does; it would save 3 of 179 us.)
         float bestb = INFINITY;
         int cb2 = 0;
 #pragma unroll
@@ -533,7 +541,7 @@ __global__ __launch_bounds__(kEpThreads, 2) void k_encode_pairs(const void *__re
                 const float xv[4] = {x4.x, x4.y, x4.z, x4.w};
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const float sc = V[t][4 * q + e] + xv[e];
+                    const float sc = ubest + (V[t][4 * q + e] + xv[e]);
                     if (sc < bestb) { bestb = sc; cb2 = b0 + e; }
                 }
             }
@@ -798,7 +806,7 @@ commvq_status encode_pairs(const void *keys, const void *cb, const float *norms,
                            int n_tokens, hipStream_t s)
 {
     // As in encode_rows: full rounds of one workgroup per compute unit go to RS = 1, and the rest to what needs one round.
-    // 21 levels of 8 heads take 108 us with RS = 4 (up to 1024 tokens), 127 (2; 2048), 170 (1; 4096).  A workgroup per
+    // 21 levels of 8 heads take 113 us with RS = 4 (up to 1024 tokens), 132 (2; 2048), 179 (1; 4096).  A workgroup per
     // vector takes 33 to 46 us while the vectors fit the chip, two workgroups per compute unit.
     const int64_t round = 128 * (int64_t)std::max(1, 256 / d.Hkv);
     const int full = (int)(n_tokens / round * round), rest = n_tokens - full;

@@ -32,3 +32,39 @@ def test_encode_pairs_sizes(gpu, oracle, n, heads, R):  # noqa: F811
         codes = np.stack(oracle.unpack_key_pairs(np.ascontiguousarray(got[g, pick]), R), axis=-1)
         same.append(judge(oracle, kf[pick, g], w.as_f64("key_codebooks")[g], codes, True))
     assert np.concatenate(same).mean() >= 0.98
+
+
+def _tied_vectors(seed, n):
+    """One level of one head whose costs tie in fp32 although they differ: sub-space 1 adds the same 1 - 2 * 4096 to every
+    a, so that the sum of the two halves of a cost is rounded to 2^-10, while sub-space 0 holds small multiples of 2^-6.  All
+    products and sums of them are exact in fp32, in any order; U rounds once, V + cross not at all."""
+    rng = np.random.default_rng(seed)
+    cb = np.zeros((1, 1, 64, 128), np.float32)
+    cb[0, 0, :, 0:2] = rng.integers(-3, 4, (64, 2)) / 64.0
+    cb[0, 0, :, 2] = 1.0
+    keys = np.zeros((n, 1, 128), np.float32)
+    keys[:, 0, 0:2] = rng.integers(-16, 17, (n, 2)) / 16.0
+    keys[:, 0, 2] = 4096.0
+    return cb, keys
+
+
+# one workgroup per token, and 32, 64 and 128 tokens per workgroup
+@pytest.mark.parametrize("n", [1, 200, 512, 5000, 16000, 33000])
+def test_paired_ties_go_to_the_lowest_index_at_every_size(gpu, oracle, n):  # noqa: F811
+    """Costs (||C[a]||^2 - 2 res.C[a]) + ((||C[b]||^2 - 2 res.(i C[b])) + cross), summed in fp32; the lowest a * 64 + b of equals."""
+    cb, few = _tied_vectors(3, 500)
+    keys = few[np.arange(n) % 500]
+    w = synth.make_pair_workload("ties", B=1, Hq=1, Hkv=1, seqlens=[8], R=1, Mv=16, seed=1)
+    w.key_codebooks = synth.f32_to_bf16_bits(cb).reshape(w.key_codebooks.shape)
+    got = encode_on_gpu(gpu, w, synth.f32_to_bf16_bits(keys), L_cap=n)
+    codes = np.stack(oracle.unpack_key_pairs(np.ascontiguousarray(got[0]), 1), axis=-1).reshape(n, 2).astype(np.int64)
+    c = (cb[0, 0, :, 0::2] + 1j * cb[0, 0, :, 1::2]).astype(np.complex128)
+    k = (few[:, 0, 0::2] + 1j * few[:, 0, 1::2]).astype(np.complex128)
+    norm = (np.abs(c) ** 2).sum(1)
+    U = (norm - 2 * (k @ c.conj().T).real).astype(np.float32)
+    V = (norm - 2 * (k @ (1j * c).conj().T).real).astype(np.float32)
+    X = (2 * (c @ (1j * c).conj().T).real).astype(np.float32)
+    cost = U[:, :, None] + (V[:, None, :] + X)
+    want = cost.reshape(len(k), -1).argmin(1)                  # the first of equals
+    assert ((cost.reshape(len(k), -1) == cost.reshape(len(k), -1).min(1, keepdims=True)).sum(1) > 1).mean() > 0.5
+    assert np.array_equal(codes[:, 0] * 64 + codes[:, 1], want[np.arange(n) % 500])
