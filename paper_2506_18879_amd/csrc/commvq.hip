@@ -2908,7 +2908,8 @@ static commvq_handle *new_handle(const commvq_config *config, int device)
     h->cfg = *config;
     h->G = config->n_q_heads / config->n_kv_heads;
     h->scale = (float)(config->softmax_scale > 0.0 ? config->softmax_scale : 1.0 / std::sqrt((double)kD));
-    h->n_hi = (config->max_position >> kLoBits) + 1;
+    // a distance ad behind the query is 64 (ad / 64) + lo, one before it -64 ceil(ad / 64) + lo, with lo on 0..63
+    h->n_hi = ((config->max_position + kLo - 1) >> kLoBits) + 1;
     h->device = device;
     h->tbl_hi = h->tbl_lo = nullptr;
     h->static_scratch = nullptr;

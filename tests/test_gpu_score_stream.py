@@ -5,7 +5,7 @@ import pytest
 
 from paper_2506_18879_amd import synth
 
-from test_gpu_parity import TOL_SCORE, assert_rows, gpu, oracle_out  # noqa: F401  (gpu: fixture)
+from test_gpu_parity import TOL_SCORE, assert_rows, gpu, oracle_out, oracle_out_paired  # noqa: F401  (gpu: fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -16,7 +16,7 @@ def _check(gpu, oracle, w, **kw):
     dw, op = gpu.DeviceWorkload(w), gpu.DecodeAttention(w, **kw)
     s, out = op.scores(dw), op(dw)
     torch.cuda.synchronize()
-    ref, ref_scores, _ = oracle_out(oracle, w, return_intermediates=True)
+    ref, ref_scores, _ = (oracle_out_paired if w.key_format == "paired" else oracle_out)(oracle, w, return_intermediates=True)
     assert np.abs(s.cpu().numpy().astype(np.float64) - ref_scores).max() <= TOL_SCORE
     assert_rows(out.cpu().numpy(), ref, w.name)
     op.close()
@@ -57,3 +57,17 @@ def test_query_that_is_not_16_byte_aligned(gpu, oracle):  # noqa: F811
     torch.cuda.synchronize()
     assert_rows(out.cpu().numpy(), oracle_out(oracle, w), w.name)
     op.close()
+
+
+@pytest.mark.parametrize("max_position", [64, 100, 127, 128, 129])
+@pytest.mark.parametrize("form", ["m16", "m32", "paired", "gathered"])
+def test_keys_after_the_query_up_to_the_largest_distance(gpu, oracle, form, max_position):  # noqa: F811
+    """A negative distance is 64 H + lo with lo >= 0, so |H| reaches max_position / 64 rounded up."""
+    L = max_position + 1
+    if form == "paired":
+        w = synth.make_pair_workload(f"far_{form}", B=2, Hq=8, Hkv=2, seqlens=[L, L], R=11, Mv=16, seed=L)
+    else:
+        w = synth.make_workload(f"far_{form}", B=2, Hq=8, Hkv=2, seqlens=[L, L], Mk=32 if form == "m32" else 16, Mv=16,
+                                dtype="f32" if form == "gathered" else "bf16", seed=L)
+    w.q_pos = np.array([0, L - 1], np.int32)
+    _check(gpu, oracle, w, max_position=max_position)
