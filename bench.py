@@ -442,7 +442,7 @@ def main():
                    "context_tokens": T, "m_key": w.Mk, "m_val": w.Mv, "codewords": w.K, "storage": w.dtype,
                    "key_format": w.key_format, "key_levels": w.key_levels, "value_format": w.val_format,
                    "value_bits": w.val_bits, "position_free": bool(args.position_free),
-                   "codes": w.code_dist, "score_tile_tokens": op.plan.score_split_len,
+                   "codes": w.code_dist, "score_tile_tokens_at_most": op.plan.score_split_len,
                    "score_slice_groups": op.plan.score_slice_groups, "value_split_tokens": op.plan.value_split_len,
                    "buffer_copies_rotated": n_copies,
                    "key_codebooks_packed_before_timed_region": prepacked, "value_codebooks_packed_before_timed_region": prepacked, "hip_graph_replay": bool(args.graph),

@@ -111,14 +111,16 @@ typedef struct {
 
 /* How one call is cut into workgroups (host struct, filled by commvq_plan_query). */
 typedef struct {
-    int32_t score_split_len;  /* context tokens per score tile (at most; a power of two) */
-    int32_t score_splits;     /* score workgroups per (sequence, KV head) for max_seqlen */
+    int32_t score_split_len;  /* context tokens of a score tile, rounded up to a power of two.  (Indexed bf16 keys with RoPE:
+                                 a tile is 2 to 8 segments of 512 tokens, of one sequence or of several short ones) */
+    int32_t score_splits;     /* max_seqlen / score_split_len, rounded up: tiles of the longest sequence, if none is shared
+                                 with another sequence or shorter than the rounded length */
     int32_t value_split_len;  /* context tokens per value workgroup */
     int32_t value_splits;     /* value workgroups per (sequence, KV head) for max_seqlen */
     int32_t out_chunks;       /* codebook-row chunks per (sequence, KV head) in the bins x codebook product */
     int32_t score_kernel;     /* 0: rows gathered through L1 (fp32 codebooks or explicit key positions);
                                  1: codebook slices streamed through LDS (or the look-up table of position_free) */
-    int32_t score_slice_groups; /* score workgroups per tile: contexts too short to fill the chip are also cut along the
+    int32_t score_slice_groups; /* score workgroups per tile and KV head: contexts too short to fill the chip are also cut along the
                                  codebook slices, and the groups' partial logits are added by a small kernel; 1 otherwise */
 } commvq_plan;
 

@@ -87,7 +87,7 @@ inline size_t packed_key_bytes(const commvq_config &c)
     return (size_t)c.n_kv_heads * c.m_key * kK * kD * 2;
 }
 
-// Value split for statistics tiles of slen tokens.
+// Value split for score tiles of slen tokens (1024 where k_score_combine writes the statistics).
 int value_split_len(const commvq_handle *h, int B, int max_seqlen, int slen)
 {
     const int units = B * h->cfg.n_kv_heads;
@@ -96,8 +96,8 @@ int value_split_len(const commvq_handle *h, int B, int max_seqlen, int slen)
         nv = 256 / (B * ((h->cfg.n_q_heads + kVbitsHeads - 1) / kVbitsHeads) * (h->cfg.value_bits / kVbitsCols));
     if (nv < 1) nv = 1;
     int vlen = (max_seqlen + nv - 1) / nv;
-    // a value split is a whole number of statistics tiles (score tiles; 1024 tokens when k_score_combine writes the
-    // statistics), or a power-of-two fraction of one (never less than 1024 tokens): k_bins takes its exp-sums from them
+    // a whole number of tiles, or a power-of-two fraction of one (never less than 1024 tokens): k_bins takes its exp-sums from
+    // the tiles' statistics.  (k_score_stream's are per 512 tokens, so there the tile is more than would be necessary.)
     if (vlen >= slen || slen <= 1024) {
         const int round_to = slen > 1024 ? slen : 1024;
         vlen = (vlen + round_to - 1) / round_to * round_to;
@@ -171,15 +171,20 @@ StreamShape stream_shape(const commvq_handle *h, int B, int64_t T, int max_seqle
 // Whether the sliced score path is k_score_stream (index-form keys with RoPE).
 inline bool stream_keys(const commvq_config &c) { return !pair_keys(c) && !c.position_free; }
 
-void make_plan(const commvq_handle *h, int B, int64_t T, int max_seqlen, bool sliced, commvq_plan *p)
+// A plan and what of k_score_stream's shape the public part does not say.
+struct Plan : commvq_plan {
+    StreamShape stream;
+};
+
+void make_plan(const commvq_handle *h, int B, int64_t T, int max_seqlen, bool sliced, Plan *p)
 {
     const int units = B * h->cfg.n_kv_heads;
-    int len, groups = 1;
+    int len;
+    p->stream = StreamShape{0, 0, 1};
     if (sliced && stream_keys(h->cfg)) {
-        const StreamShape ss = stream_shape(h, B, T, max_seqlen);
-        groups = ss.groups;
-        len = 1024;
-        while (len < ss.passes * kPassTokens) len *= 2;
+        p->stream = stream_shape(h, B, T, max_seqlen);
+        len = 1024;  // what is reported, and value splits are cut by: the workgroup's tokens rounded up to a power of two
+        while (len < p->stream.passes * kPassTokens) len *= 2;
     } else if (sliced) {
         // Tile = 1024, 2048 or 4096 tokens of one (sequence, KV head).  Cost model of a workgroup, in microseconds: a fixed
         // start (first fetches, write-out), per slice a switch (LDS refill, barriers) and the passes themselves.
@@ -198,6 +203,7 @@ void make_plan(const commvq_handle *h, int B, int64_t T, int max_seqlen, bool sl
         // down to 4 tokens per wavefront (one iteration of four tokens): a short context still spreads over the chip
         while (len > 16 && (long)units * ((max_seqlen + len - 1) / len) < kScoreMinWgs) len /= 2;
     }
+    const int groups = p->stream.groups;
     p->score_split_len = len;
     p->score_splits = (max_seqlen + len - 1) / len;
     const int vlen = value_split_len(h, B, max_seqlen, groups > 1 ? 1024 : len);
@@ -210,12 +216,12 @@ void make_plan(const commvq_handle *h, int B, int64_t T, int max_seqlen, bool sl
 
 // Granularity of the (max, sum of exp) statistics that the score stage leaves for k_bins: the score tile, except that
 // k_score_stream writes them per 512-token segment and k_score_combine (tiles cut along the slices) per 1024 tokens.
-inline int stat_len(const commvq_handle *h, const commvq_plan &p)
+inline int stat_len(const commvq_handle *h, const Plan &p)
 {
     if (p.score_kernel && stream_keys(h->cfg)) return p.score_slice_groups > 1 ? 1024 : kPassTokens;
     return p.score_split_len;
 }
-inline int stat_splits(const commvq_handle *h, const commvq_plan &p, int max_seqlen) { return (max_seqlen + stat_len(h, p) - 1) / stat_len(h, p); }
+inline int stat_splits(const commvq_handle *h, const Plan &p, int max_seqlen) { return (max_seqlen + stat_len(h, p) - 1) / stat_len(h, p); }
 
 // Carves the workspace.  Array sizes are the larger of what the two score kernels need, so one workspace size serves a batch
 // shape whether or not explicit positions are passed.  Behind the statistics, the logits and the partial logits, the score
@@ -226,7 +232,7 @@ inline int stat_splits(const commvq_handle *h, const commvq_plan &p, int max_seq
 void carve(const commvq_handle *h, int B, int64_t T, int max_seqlen, void *base, Workspace *w)
 {
     const commvq_config &c = h->cfg;
-    commvq_plan pa, pb;
+    Plan pa, pb;
     make_plan(h, B, T, max_seqlen, true, &pa);
     make_plan(h, B, T, max_seqlen, false, &pb);
     const size_t ssplits = std::max<size_t>(std::max(pa.score_splits, pb.score_splits), (size_t)stat_splits(h, pa, max_seqlen));
@@ -2475,7 +2481,7 @@ commvq_status check_positions(const commvq_handle *h, const commvq_positions *p)
 }
 
 commvq_status prep(const commvq_handle *h, const commvq_positions *pos, void *workspace, size_t workspace_bytes,
-                   commvq_plan *plan, Workspace *w)
+                   Plan *plan, Workspace *w)
 {
     if (!h) return COMMVQ_ERR_NULL;
     commvq_status st = check_positions(h, pos);
@@ -2702,7 +2708,7 @@ hipError_t launch_lut_m(int G, const void *q, const void *key_cb, bool bf16, flo
 }
 
 commvq_status run_scores(commvq_handle *h, const void *q, const uint8_t *key_codes, const void *key_cb,
-                         const commvq_positions *pos, const commvq_plan &plan, const Workspace &w, hipStream_t s)
+                         const commvq_positions *pos, const Plan &plan, const Workspace &w, hipStream_t s)
 {
     const commvq_config &c = h->cfg;
     if (c.position_free) {  // scalar look-up table: build T = scale q C^T, then M look-ups per token
@@ -2741,7 +2747,7 @@ commvq_status run_scores(commvq_handle *h, const void *q, const uint8_t *key_cod
             sa.key_codes = w.pair_bytes;
             e = pair_blocks(c) == 1 ? launch_pair_b<1>(sa, h->G, tpt, grid, s) : launch_pair_b<2>(sa, h->G, tpt, grid, s);
         } else {
-            const StreamShape ss = stream_shape(h, pos->batch, pos->total_tokens, pos->max_seqlen);
+            const StreamShape &ss = plan.stream;
             StreamArgs sa;
             sa.q = q; sa.key_codes = key_codes; sa.packed = packed; sa.cu = pos->cu_seqlens; sa.q_pos = pos->q_pos;
             sa.tbl_hi = h->tbl_hi; sa.tbl_lo = h->tbl_lo; sa.scores = w.scores; sa.sstat = w.sstat;
@@ -2775,7 +2781,7 @@ commvq_status run_scores(commvq_handle *h, const void *q, const uint8_t *key_cod
 }
 
 commvq_status run_bins(commvq_handle *h, const uint8_t *val_codes, const commvq_positions *pos,
-                       const commvq_plan &plan, const Workspace &w, hipStream_t s)
+                       const Plan &plan, const Workspace &w, hipStream_t s)
 {
     const commvq_config &c = h->cfg;
     if (bin_values(c)) {  // free binary code: Softmax(A) S_V as an integer matrix product (commvq_vbits.hip)
@@ -2798,7 +2804,7 @@ commvq_status run_bins(commvq_handle *h, const uint8_t *val_codes, const commvq_
     return e == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;
 }
 
-commvq_status run_output(commvq_handle *h, const void *val_cb, const commvq_positions *pos, const commvq_plan &plan,
+commvq_status run_output(commvq_handle *h, const void *val_cb, const commvq_positions *pos, const Plan &plan,
                          const Workspace &w, float *out, hipStream_t s)
 {
     const commvq_config &c = h->cfg;
@@ -2991,7 +2997,9 @@ commvq_status commvq_plan_query(const commvq_handle *h, int32_t batch, int64_t t
     // explicit key positions are not known here: the distance check belongs to the calls that see them
     const commvq_status st = check_shape(h, batch, total_tokens, max_seqlen, true);
     if (st != COMMVQ_OK) return st;
-    make_plan(h, batch, total_tokens, max_seqlen, use_sliced(h, false), plan);
+    Plan p;
+    make_plan(h, batch, total_tokens, max_seqlen, use_sliced(h, false), &p);
+    *plan = p;
     return COMMVQ_OK;
 }
 
@@ -3094,7 +3102,7 @@ commvq_status commvq_stage_scores(commvq_handle *h, const void *q, const uint8_t
 {
     if (!h || !q || !key_codes || !key_cb) return COMMVQ_ERR_NULL;
     if (reinterpret_cast<uintptr_t>(key_codes) & 15u) return COMMVQ_ERR_SHAPE;
-    commvq_plan plan;
+    Plan plan;
     Workspace w;
     commvq_status st = prep(h, pos, workspace, workspace_bytes, &plan, &w);
     if (st != COMMVQ_OK) return st;
@@ -3113,7 +3121,7 @@ commvq_status commvq_stage_bins(commvq_handle *h, const uint8_t *val_codes, cons
 {
     if (!h || !val_codes) return COMMVQ_ERR_NULL;
     if (reinterpret_cast<uintptr_t>(val_codes) & 15u) return COMMVQ_ERR_SHAPE;
-    commvq_plan plan;
+    Plan plan;
     Workspace w;
     commvq_status st = prep(h, pos, workspace, workspace_bytes, &plan, &w);
     if (st != COMMVQ_OK) return st;
@@ -3124,7 +3132,7 @@ commvq_status commvq_stage_output(commvq_handle *h, const void *val_cb, const co
                                   void *workspace, size_t workspace_bytes, void *stream)
 {
     if (!h || !val_cb || !out) return COMMVQ_ERR_NULL;
-    commvq_plan plan;
+    Plan plan;
     Workspace w;
     commvq_status st = prep(h, pos, workspace, workspace_bytes, &plan, &w);
     if (st != COMMVQ_OK) return st;
@@ -3137,7 +3145,7 @@ commvq_status commvq_decode_attn(commvq_handle *h, const void *q, const uint8_t 
 {
     if (!h || !q || !key_codes || !val_codes || !key_cb || !val_cb || !out) return COMMVQ_ERR_NULL;
     if ((reinterpret_cast<uintptr_t>(key_codes) | reinterpret_cast<uintptr_t>(val_codes)) & 15u) return COMMVQ_ERR_SHAPE;
-    commvq_plan plan;
+    Plan plan;
     Workspace w;
     commvq_status st = prep(h, pos, workspace, workspace_bytes, &plan, &w);
     if (st != COMMVQ_OK) return st;
@@ -3175,7 +3183,7 @@ commvq_status commvq_decode_attn_static(commvq_handle *h, const void *q, const u
 {
     if (!h || !q || !key_codes || !val_codes || !key_cb || !val_cb || !out) return COMMVQ_ERR_NULL;
     if ((reinterpret_cast<uintptr_t>(key_codes) | reinterpret_cast<uintptr_t>(val_codes)) & 15u) return COMMVQ_ERR_SHAPE;
-    commvq_plan plan;
+    Plan plan;
     Workspace w;
     // the handle's copy of the scratch array is the workspace; a batch shape that needs more than the array holds
     // comes back as COMMVQ_ERR_WORKSPACE from the same check that vets a caller's workspace
