@@ -129,6 +129,7 @@ __global__ __launch_bounds__(256) void k_encode(const void *__restrict__ keys, c
         int c = wcand[0];
         for (int w = 1; w < 4; ++w)
             if (wbest[w] < m || (wbest[w] == m && wcand[w] < c)) { m = wbest[w]; c = wcand[w]; }
+        c &= K - 1;  // no candidate if every distance is NaN: any row, but one of the codebook's
         if (tid == 0) chosen[l] = c;
         if (tid < kD) res[tid] -= cb_elem<BF16>(cb, base + (size_t)c * kD + tid);
         __syncthreads();

@@ -68,3 +68,19 @@ def test_paired_ties_go_to_the_lowest_index_at_every_size(gpu, oracle, n):  # no
     want = cost.reshape(len(k), -1).argmin(1)                  # the first of equals
     assert ((cost.reshape(len(k), -1) == cost.reshape(len(k), -1).min(1, keepdims=True)).sum(1) > 1).mean() > 0.5
     assert np.array_equal(codes[:, 0] * 64 + codes[:, 1], want[np.arange(n) % 500])
+
+
+@pytest.mark.parametrize("form,n", [("f32", 3), ("bf16", 3), ("bf16", 700), ("paired", 3), ("paired", 1100), ("paired", 4200)])
+def test_vectors_that_are_not_finite_leave_their_neighbours_alone(gpu, form, n):  # noqa: F811
+    """NaN and infinite vectors get some record (every kernel keeps its row index in range); the others' do not change."""
+    if form == "paired":
+        w = synth.make_pair_workload("enc_nan", B=1, Hq=2, Hkv=2, seqlens=[8], R=3, Mv=16, seed=5)
+    else:
+        w = synth.make_workload("enc_nan", B=1, Hq=2, Hkv=2, seqlens=[8], Mk=16, Mv=16, dtype=form, seed=5)
+    keys, _ = _keys(np.random.default_rng(n), n, w)
+    bad = keys.copy()
+    bad[1, 0], bad[n - 1, 1] = (np.nan, np.inf) if form == "f32" else (0x7fc0, 0x7f80)
+    a, b = encode_on_gpu(gpu, w, keys, L_cap=n), encode_on_gpu(gpu, w, bad, L_cap=n)
+    same = np.ones((2, n), bool)
+    same[0, 1] = same[1, n - 1] = False
+    assert np.array_equal(a[same], b[same])
