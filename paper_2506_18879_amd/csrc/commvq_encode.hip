@@ -94,8 +94,7 @@ struct EncodeDims {
 
 // Index-form keys, fp32 codebooks: one workgroup per (token, KV head), one thread per centre of the level, rows
 // straight from L2.  Ties go to the lowest index.  (bf16 codebooks: k_encode_rows below.)
-template <bool BF16>
-__global__ __launch_bounds__(256) void k_encode(const void *__restrict__ keys, const void *__restrict__ cb,
+__global__ __launch_bounds__(256) void k_encode(const void *__restrict__ keys, const float *__restrict__ cb,
                                                 const float *__restrict__ norms, uint8_t *__restrict__ out, const EncodeDims a)
 {
     __shared__ float res[kD];
@@ -117,7 +116,7 @@ __global__ __launch_bounds__(256) void k_encode(const void *__restrict__ keys, c
         const size_t base = level * K * kD;
         float acc = 0.f;
 #pragma unroll 16
-        for (int e = 0; e < kD; ++e) acc = __builtin_fmaf(res[e], cb_elem<BF16>(cb, base + (size_t)tid * kD + e), acc);
+        for (int e = 0; e < kD; ++e) acc = __builtin_fmaf(res[e], cb[base + (size_t)tid * kD + e], acc);
         const float best = norms[level * K + tid] - 2.f * acc;
         // argmin over the workgroup, lowest index on ties
         const float wm = -wave_max(-best);
@@ -131,7 +130,7 @@ __global__ __launch_bounds__(256) void k_encode(const void *__restrict__ keys, c
             if (wbest[w] < m || (wbest[w] == m && wcand[w] < c)) { m = wbest[w]; c = wcand[w]; }
         c &= K - 1;  // no candidate if every distance is NaN: any row, but one of the codebook's
         if (tid == 0) chosen[l] = c;
-        if (tid < kD) res[tid] -= cb_elem<BF16>(cb, base + (size_t)c * kD + tid);
+        if (tid < kD) res[tid] -= cb[base + (size_t)c * kD + tid];
         __syncthreads();
     }
     if (tid < a.levels) out[tok * a.token_stride + (long long)g * a.head_stride + tid] = (uint8_t)chosen[tid];
@@ -850,7 +849,8 @@ commvq_status encode_vectors(commvq_handle *h, bool values, const void *keys, in
     } else if (bf16) {
         return encode_rows(keys, key_cb, norms, codes_out, d, n_tokens, s);
     } else {
-        hipLaunchKernelGGL(k_encode<false>, dim3((unsigned)(n_tokens * c.n_kv_heads)), dim3(256), 0, s, keys, key_cb, norms, codes_out, d);
+        hipLaunchKernelGGL(k_encode, dim3((unsigned)(n_tokens * c.n_kv_heads)), dim3(256), 0, s, keys, static_cast<const float *>(key_cb), norms,
+                           codes_out, d);
     }
     return hipGetLastError() == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;
 }
