@@ -2345,8 +2345,9 @@ __global__ __launch_bounds__(kOutThreads) void k_out_mfma(OutArgs a, const uint4
         const int chunk = part * a.per_wg + c;
         if (c > 0) __syncthreads();  // the previous chunk's weights are no longer read
         if (a.nvsplit == 1) {
-            // one value split (batch x KV heads above 128): a thread's bins of all SPT sequences travel together (64 sequences
-            // 129 -> 125 us, 40 of 8 heads 147 -> 144.6); with 16 splits and few workgroups this form takes 25 us, the other 13
+            // one value split (up to 1024 tokens, or batch x KV heads above 128): a thread's bins of all SPT sequences travel
+            // together.  Whole call, inputs changing from pass to pass, 32 codebooks, 512..1000 tokens: 4 sequences 40.1 -> 38.8 us, 64
+            // 140.8 -> 136.0, 40 of 8 heads 153.2 -> 148.6; with 16 splits and few workgroups this form takes 25 us, the other 13
             static_assert(KC == kOutThreads, "a thread takes one codebook row of every sequence");
             unsigned bv[SPT][G];
             float unit[SPT][G];
@@ -2831,8 +2832,9 @@ commvq_status run_output(commvq_handle *h, const void *val_cb, const commvq_posi
         const int rows = (pos->batch + spt - 1) / spt * c.n_kv_heads;
         // A workgroup takes several chunks one after the other as long as 1024 workgroups, four per compute unit, are left:
         // its partial results are then one row instead of one per chunk, written here and read by k_out_final.  Whole
-        // call, 64 sequences of 512..1024 tokens, 32 codebooks: 136 us with 4096 workgroups, 129 with 1024, 140 with
-        // 512; 32 sequences 79 with 2048, 75 with 1024, 82 with 512.
+        // call, inputs changing from pass to pass, 64 sequences of 512..1024 tokens: 32 codebooks 139.6 us with 4096 workgroups,
+        // 134.8 with 2048, 135.6 with 1024, 156 with 512; 16 codebooks 109.4 with 2048, 107.2 with 1024, 116 with 512; 32
+        // sequences, 32 codebooks 82.5 with 2048, 81.1 with 1024, 91.6 with 512.
         a.per_wg = 1;
         while (a.nchunk % 2 == 0 && (int64_t)rows * (a.nchunk / 2) >= 1024) { a.nchunk /= 2; a.per_wg *= 2; }
         const int mgrid = rows * a.nchunk;

@@ -150,8 +150,9 @@ __global__ __launch_bounds__(256) void k_encode(const void *__restrict__ keys, c
 // conflicts, and a load instruction (64 lanes -> 64 consecutive slots) still covers 1 KiB of contiguous memory.
 // Eight wavefronts: 8 / RS sets of 16 tokens, the 256 rows of a level shared by the RS wavefronts of a set, which
 // exchange their minima through LDS.  RS = 1 (128 tokens) has the least work per token; its level takes 5.3 us, of which
-// 3.7 the 16 row tiles (192 matrix instructions of 16 clk and 16 x 16 vector ones per wavefront, two wavefronts a SIMD:
-// the two kinds do not overlap), 0.6 the update, 0.5 the split and 0.4 waiting for rows.  RS = 8 (16 tokens) has the
+// 3.7 the 16 row tiles (192 matrix instructions of 16 clk and 16 x 16 vector ones per wavefront, two wavefronts a SIMD;
+// in this order the two kinds hardly overlap: a vector instruction runs in 28 % of the matrix unit's busy cycles, in
+// k_encode_pairs, whose order is fixed, in 55 %), 0.6 the update, 0.5 the split and 0.4 waiting for rows.  RS = 8 (16 tokens) has the
 // shortest level, 1.5 us; with a split and an update per wavefront instead of shared ones it was 2.1.
 // 32000 vectors, 32 levels: 179 us, with 64 tokens per workgroup, rows staged through registers and one image 289 us;
 // 64 vectors, 16 levels: 25 us, with a workgroup per vector and fp32 FMAs 32 us.
