@@ -322,7 +322,8 @@ commvq_status commvq_em_step_shared(const float *data, int32_t group, int32_t n_
 
 /*
  * The three stages of commvq_decode_attn, callable on their own (tests and profiling).
- * They read/write the same workspace; run them in this order on one stream.
+ * They read/write the same workspace; run them in this order on one stream.  The score stage's own arrays share memory
+ * with the bins and partial results: after commvq_stage_scores has run again, commvq_stage_bins must too.
  *   commvq_stage_scores  Eq. new_attention: scaled logits for every (b, h, token) and the
  *                        per-split maxima.  If scores_out is not NULL it receives a copy of the
  *                        logits, fp32 [T*Hq], (b, h, i) at cu_seqlens[b]*Hq + h*L_b + i.
