@@ -898,7 +898,7 @@ commvq_status commvq_em_step(const float *data, int32_t n_subspaces, int32_t n_p
     float *nab = reinterpret_cast<float *>(w + 2 * em_align(pts * 4));
     float2 *sab = reinterpret_cast<float2 *>(w + 2 * em_align(pts * 4) + em_align(cen * 4));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const float inv_t = 1.f / temperature;
+    const float inv_t = std::min(1.f / temperature, FLT_MAX / 2.f);  // finite, and times log2 e too: the nearest centre's exponent is 0 times it
     const float2 *d2 = reinterpret_cast<const float2 *>(data);
     float2 *p2 = reinterpret_cast<float2 *>(phi);
     hipLaunchKernelGGL(k_em_norm, dim3((unsigned)((n_points + 255) / 256), (unsigned)n_subspaces), dim3(256), 0, s, d2, p2,

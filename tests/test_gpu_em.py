@@ -62,6 +62,20 @@ def test_one_em_step_matches_oracle(em, oracle, Nc, N, T):
     assert worst <= 2e-3
 
 
+@pytest.mark.parametrize("T", [1e-40, 1e-20, 1e-10, 1e30, float("inf")])
+def test_temperatures_from_hard_to_uniform_assignment(em, oracle, T):
+    # points whose two nearest centres differ by less than 1e-4 are left out: fp32 distances would decide them
+    data, start = calibration(1, 3000, 6, seed=77)
+    z = start[0, :, 0].astype(np.complex128) + 1j * start[0, :, 1]
+    near = np.sort(np.abs((data[0, :, 0].astype(np.complex128) + 1j * data[0, :, 1])[:, None] - (z[:, None] + 1j * z).reshape(-1)), axis=1)
+    data = np.ascontiguousarray(data[:, near[:, 1] - near[:, 0] > 1e-4])
+    got = em(data, start, T)
+    ref, _ = oracle.em_step(data[0], start[0], temperature=None if T < 1e-8 else T)
+    worst = np.abs(got[0] - ref).max() / np.abs(ref).max()
+    print(f"case T={T:g} N={data.shape[1]}: max relative deviation of phi {worst:.3e}", flush=True)
+    assert worst <= 2e-3
+
+
 def test_annealed_iterations_lower_the_objective(em, oracle):
     J, N, Nc = 2, 2000, 8
     data, start = calibration(J, N, Nc, seed=5)
