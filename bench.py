@@ -408,24 +408,28 @@ def main():
         roofline = {"kernel": kname, "bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": round(gbs / HBM_PEAK_GBS, 4), "traffic": None, "kernel_ms": round(stage_ms[0], 5),
                     "launches_averaged": n_prof, "timed_region_includes": "k_lut_build + k_score_lut"}
-    # the two stages that can be judged against HBM: the value stage streams the value codes (and re-reads the
-    # logits), the output stage reads the bins of every value split and the value codebook once per sequence
+    # the value stage streams the value codes and re-reads the logits; for binary values its bins then go through memory to the
+    # output stage, which reads them and the codebook, for indexed values the stage ends with the product and the output
+    # stage only adds partial results
     bins_s, out_s = stage_ms[1] * 1e-3, stage_ms[2] * 1e-3
     val_gbs = w.val_codes.nbytes / bins_s / 1e9 if bins_s > 0 else 0.0
     bins_alg = w.val_codes.nbytes + T * w.Hq * 4
     vbin = w.val_format == "binary"
-    val_rows = w.val_bits if vbin else w.Mv * w.K            # bins per query head
-    out_alg = op.plan.value_splits * w.B * w.Hq * val_rows * 4 + w.B * w.val_codebooks.nbytes
+    vname = "k_vbits" if vbin else "k_values"
     stage_views = {
-        "value_stream_view": {"stage": "k_vbits" if vbin else "k_bins", "value_code_GBs": round(val_gbs, 1),
+        "value_stream_view": {"stage": vname, "value_code_GBs": round(val_gbs, 1),
                               "frac_of_hbm_peak": round(val_gbs / HBM_PEAK_GBS, 4),
                               "with_logits_read_GBs": round(bins_alg / bins_s / 1e9, 1) if bins_s > 0 else 0.0,
-                              "with_logits_read_and_bins_written_GBs": round((bins_alg + op.plan.value_splits * w.B * w.Hq * val_rows * 4) / bins_s / 1e9, 1) if bins_s > 0 else 0.0,
-                              "counter_bytes": stored.get("k_vbits" if vbin else "k_bins"), "stage_ms": round(stage_ms[1], 5)},
-        "output_view": {"stage": "k_out (k_out_mfma for batches) + k_out_final", "bins_and_codebook_GBs": round(out_alg / out_s / 1e9, 1) if out_s > 0 else 0.0,
-                        "frac_of_hbm_peak": round(out_alg / out_s / 1e9 / HBM_PEAK_GBS, 4) if out_s > 0 else 0.0,
+                              "counter_bytes": stored.get(vname), "stage_ms": round(stage_ms[1], 5)},
+        "output_view": {"stage": "k_out (k_out_mfma for batches) + k_out_final" if vbin else "k_out_final",
                         "counter_bytes": sum(v for k, v in stored.items() if k.startswith("k_out") and isinstance(v, (int, float))) or None,
                         "stage_ms": round(stage_ms[2], 5)}}
+    if vbin:
+        bins_bytes = op.plan.value_splits * w.B * w.Hq * w.val_bits * 4
+        out_alg = bins_bytes + w.B * w.val_codebooks.nbytes
+        stage_views["value_stream_view"]["with_logits_read_and_bins_written_GBs"] = round((bins_alg + bins_bytes) / bins_s / 1e9, 1) if bins_s > 0 else 0.0
+        stage_views["output_view"]["bins_and_codebook_GBs"] = round(out_alg / out_s / 1e9, 1) if out_s > 0 else 0.0
+        stage_views["output_view"]["frac_of_hbm_peak"] = round(out_alg / out_s / 1e9 / HBM_PEAK_GBS, 4) if out_s > 0 else 0.0
     if vbin and bins_s > 0:
         # Softmax(A) S_V as a dense product: heads (padded to 32 per workgroup) x N_c x tokens, four 8-bit digits
         heads = -(-w.Hq // 32) * 32

@@ -115,9 +115,10 @@ typedef struct {
                                  a tile is 2 to 8 segments of 512 tokens, of one sequence or of several short ones) */
     int32_t score_splits;     /* max_seqlen / score_split_len, rounded up: tiles of the longest sequence, if none is shared
                                  with another sequence or shorter than the rounded length */
-    int32_t value_split_len;  /* context tokens per value workgroup */
-    int32_t value_splits;     /* value workgroups per (sequence, KV head) for max_seqlen */
-    int32_t out_chunks;       /* codebook-row chunks per (sequence, KV head) in the bins x codebook product */
+    int32_t value_split_len;  /* context tokens of a value split.  Binary values: of a value workgroup.  Indexed values: the workspace
+                                 is sized for splits of this length, a workgroup takes that many tokens or more */
+    int32_t value_splits;     /* max_seqlen / value_split_len, rounded up */
+    int32_t out_chunks;       /* chunks of 64 codebook rows per (sequence, KV head): the partial results that the workspace holds */
     int32_t score_kernel;     /* 0: rows gathered through L1 (fp32 codebooks or explicit key positions);
                                  1: codebook slices streamed through LDS (or the look-up table of position_free) */
     int32_t score_slice_groups; /* score workgroups per tile and KV head: contexts too short to fill the chip are also cut along the
@@ -227,16 +228,17 @@ commvq_status commvq_pack_key_codebooks(commvq_handle *handle, const void *key_c
 commvq_status commvq_forget_packed_key_codebooks(commvq_handle *handle, const void *key_codebooks);
 
 /*
- * The same for the value codebooks (Eq. optimized_v: bins x C_V).  For batches of several sequences (16 or more
- * output rows = sequences x query heads per KV head, bf16 codebooks) the product with the value codebook runs on the
- * matrix cores and reads the codebook in k-step order ([KV head][32 rows][dimension][32] with rows ordered
- * codeword * M_v + codebook).  Without preparation every such call re-lays the value codebook into its workspace first;
- * commvq_pack_value_codebooks does it once and remembers (val_codebooks -> packed) in the handle, exactly as above:
- *   val_codebooks  [Hkv][M_v][K][d] bf16, as for commvq_decode_attn
+ * The same for the value codebooks (Eq. optimized_v: bins x C_V) of COMMVQ_VALUES_BINARY.  For batches of several sequences (16
+ * or more output rows = sequences x query heads per KV head, bf16 codebooks) the product with the value codebook reads the
+ * codebook in k-step order ([KV head][32 rows][dimension][32]).  Without preparation every such call re-lays the value
+ * codebook into its workspace first; commvq_pack_value_codebooks does it once and remembers (val_codebooks -> packed) in the
+ * handle, exactly as above:
+ *   val_codebooks  as for commvq_decode_attn
  *   packed         device buffer of commvq_packed_value_codebook_bytes() bytes, 16-byte aligned, caller-owned
- * Results are bit-identical either way; smaller batches do not use it.  COMMVQ_ERR_CONFIG for fp32 codebooks.
- * COMMVQ_VALUES_BINARY: val_codebooks is [N_c][Hkv * d]; row r of head g is then the code bit that the value stage
- * keeps in row r of its bins (the six low bits of r permuted), restricted to the head's columns.
+ * Results are bit-identical either way; smaller batches do not use it.  COMMVQ_ERR_CONFIG for fp32 codebooks.  Indexed
+ * values need no other layout: the call then checks its arguments and leaves `packed` as it is.
+ * Row r of head g is the code bit that the value stage keeps in row r of its bins (the seven low bits of r permuted),
+ * restricted to the head's columns.
  */
 commvq_status commvq_packed_value_codebook_bytes(const commvq_handle *handle, size_t *bytes);
 commvq_status commvq_pack_value_codebooks(commvq_handle *handle, const void *val_codebooks, void *packed, void *stream);
@@ -321,7 +323,9 @@ commvq_status commvq_em_step_shared(const float *data, int32_t group, int32_t n_
                                     float temperature, float *phi, void *workspace, size_t workspace_bytes, void *stream);
 
 /*
- * The three stages of commvq_decode_attn, callable on their own (tests and profiling).
+ * The three stages of commvq_decode_attn, callable on their own (tests and profiling), with the same bits.  (The whole call
+ * runs stage two and the product of stage three as one kernel for indexed values; called on their own they pass the bins on
+ * through the workspace.)
  * They read/write the same workspace; run them in this order on one stream.  The score stage's own arrays share memory
  * with the bins and partial results: after commvq_stage_scores has run again, commvq_stage_bins must too.
  *   commvq_stage_scores  Eq. new_attention: scaled logits for every (b, h, token) and the

@@ -9,14 +9,11 @@
 //               resident in registers, gather-sum and query contraction on the matrix cores), for
 //               short contexts with the tiles also cut along the slices + k_score_combine;
 //               fp32 codebooks or explicit key positions: k_score (rows gathered through L1).
-//   k_bins      Softmax(A) S_V of Eq. optimized_v (unnormalised): exp(logit - max) is
-//               scatter-added into LDS bins (one per head, value codebook and codeword; written out
-//               as [K][M_v][G]), one bin set per context split.  The
-//               bins are 32-bit fixed point (integer LDS atomics run ~20x faster than fp32 ones
-//               on gfx950); the scale of each split is chosen from its known exp-sum so that
-//               no bin can overflow and the worst-case error is (tokens per split) * 2^-31.
-//   k_out       (bins C_V): split reduction + bins x value-codebook product, per chunk of rows.
-//   k_out_final sum of the per-chunk products, division by the softmax denominator.
+//   k_values    Softmax(A) S_V of Eq. optimized_v and its product with the value codebook (commvq_values.hpp): exp(logit - max) is
+//               scatter-added into LDS bins, one per head, value codebook and codeword, in 32-bit fixed point (integer LDS
+//               atomics run ~20x faster than fp32 ones on gfx950), and the bins are multiplied by the codebook rows on the matrix
+//               cores.  Binary value code: k_vbits, then k_out or k_out_mfma with the bins in memory in between.
+//   k_out_final sum of the partial products, division by the softmax denominator.
 // Key encoding for cache append lives in commvq_encode.hip, the EM codebook learner in commvq_em.hip.
 //
 // RoPE algebra used by k_score (Sec. 3.2, Eq. rope_ri).  Writing a 2-D sub-vector (x, y) as
@@ -29,6 +26,7 @@
 #include <cstring>
 
 #include "commvq_internal.hpp"
+#include "commvq_values.hpp"
 #include "commvq_vbits.hpp"
 
 // Scratch memory of commvq_decode_attn_static: the workspace of a call, held by the library itself so that the
@@ -96,7 +94,7 @@ int value_split_len(const commvq_handle *h, int B, int max_seqlen, int slen)
         nv = 256 / (B * ((h->cfg.n_q_heads + kVbitsHeads - 1) / kVbitsHeads) * (h->cfg.value_bits / kVbitsCols));
     if (nv < 1) nv = 1;
     int vlen = (max_seqlen + nv - 1) / nv;
-    // a whole number of tiles, or a power-of-two fraction of one (never less than 1024 tokens): k_bins takes its exp-sums from
+    // a whole number of tiles, or a power-of-two fraction of one (never less than 1024 tokens): k_vbits takes its exp-sums from
     // the tiles' statistics.  (k_score_stream's are per 512 tokens, so there the tile is more than would be necessary.)
     if (vlen >= slen || slen <= 1024) {
         const int round_to = slen > 1024 ? slen : 1024;
@@ -121,6 +119,7 @@ size_t value_stage_bytes(const commvq_handle *h, int B, size_t vsplits)
     const commvq_config &c = h->cfg;
     const size_t rows = (size_t)val_books(c) * kK, heads = (size_t)B * c.n_q_heads;
     return 2 * align_up(heads * vsplits * 4, 256) + align_up(heads * vsplits * rows * 4, 256) + align_up(heads * (rows / kOutRows) * kD * 4, 256) +
+           // (indexed values have no use for the packed codebook any more; a batch's workspace keeps its size)
            (use_out_mfma(h, B) ? align_up((size_t)c.n_kv_heads * rows * kD * 2, 256) : 0);
 }
 
@@ -171,10 +170,57 @@ StreamShape stream_shape(const commvq_handle *h, int B, int64_t T, int max_seqle
 // Whether the sliced score path is k_score_stream (index-form keys with RoPE).
 inline bool stream_keys(const commvq_config &c) { return !pair_keys(c) && !c.position_free; }
 
-// A plan and what of k_score_stream's shape the public part does not say.
+// Indexed values go through k_values, the binary code through k_vbits and the output kernels.
+inline bool fused_values(const commvq_config &c) { return !bin_values(c); }
+
+// How k_values cuts a launch: codebooks per workgroup, whole sequences per workgroup (1: a token range of one), column
+// parts, threads, token ranges per sequence and their length.
+struct ValueShape {
+    int books, slots, parts, threads, ranges, range_len;
+};
+
+// A plan and what of the kernels' shapes the public part does not say.
 struct Plan : commvq_plan {
     StreamShape stream;
+    ValueShape values;
 };
+
+// room: value splits per sequence that the workspace holds.  Whole calls in microseconds, one choice against the other:
+//  * 4 codebooks a workgroup, so that a token range is long where a sequence has few heads: 9001 tokens 36.3 against 38.4
+//    with 8, 1237 tokens 24.7 against 26.4; from 128 groups of four on (64 of 8 heads) 8, which compute half as many
+//    exponentials: 8 x 8K..64K 456 against 499, 4 x 2.5K..20K (at the line) 56.6 against 55.0;
+//  * 1024 threads, one workgroup per compute unit, which then reads its codebook rows once: 9001 tokens 36.3 against 39.1
+//    with 512, 60001 tokens 53.4 against 57.5; where there are more workgroups than compute units anyway two of 512 run
+//    side by side: 40 x 1500..3000 105.9 against 110.2, 12 x 1K..9K of 8 heads 114.3 against 116.3;
+//  * whole sequences side by side, four of 4 heads or two of 8 (128 KiB of bins), which share the codebook rows, once that leaves
+//    256 workgroups and the sequences are short: 64 x 512..1024 119.7 against 132.2 one by one, 30 x 300..600 of 8 heads
+//    83.1 against 89.9; with ranges of 2250 tokens on average no gain (107.4 against 105.9);
+//  * a quarter of the columns each where not even 64 workgroups would be there: 300 tokens 17.6 against 19.5, 2000 tokens
+//    20.7 against 22.2 (with 64: 24.7 either way; with 256: 61 against 79).
+ValueShape value_shape(const commvq_handle *h, int B, int64_t T, int max_seqlen, int room)
+{
+    const int G = h->G, M = h->cfg.m_val, units = B * h->cfg.n_kv_heads;
+    const bool wide = h->cfg.codebook_dtype == COMMVQ_BF16 && G >= 4;
+    ValueShape v = {4, 1, 1, wide ? 1024 : 512, 1, 0};
+    if (wide && (int64_t)G * units * M > 2048) {
+        v.books = 8;
+        const int groups = units * (M / 8);
+        if (T <= (int64_t)B * 1536) {
+            if (G == 4 && groups >= 1024) v.slots = 4;
+            else if (groups >= 512) v.slots = 2;
+        }
+        if (groups > 256) v.threads = 512;
+    }
+    const int groups = units * (M / v.books);
+    // as many ranges as there is place for bins (stage by stage) and output rows (the rows / 64 of the other output kernels)
+    int n = std::max(1, (v.threads == 512 ? 512 : 256) / groups);
+    n = v.slots > 1 ? 1 : std::max(1, std::min(n, std::min(room, 4 * v.books)));
+    v.range_len = std::max(1024, ((max_seqlen + n - 1) / n + 511) / 512 * 512);
+    v.ranges = v.slots > 1 ? 1 : (max_seqlen + v.range_len - 1) / v.range_len;
+    if (v.slots > 1) v.range_len = max_seqlen;
+    if (v.books == 4 && (int64_t)groups * v.ranges * 4 <= 256) v.parts = 4;
+    return v;
+}
 
 void make_plan(const commvq_handle *h, int B, int64_t T, int max_seqlen, bool sliced, Plan *p)
 {
@@ -209,12 +255,13 @@ void make_plan(const commvq_handle *h, int B, int64_t T, int max_seqlen, bool sl
     const int vlen = value_split_len(h, B, max_seqlen, groups > 1 ? 1024 : len);
     p->value_split_len = vlen;
     p->value_splits = (max_seqlen + vlen - 1) / vlen;
+    if (fused_values(h->cfg)) p->values = value_shape(h, B, T, max_seqlen, p->value_splits);
     p->out_chunks = val_books(h->cfg) * kK / kOutRows;
     p->score_kernel = sliced ? 1 : 0;
     p->score_slice_groups = groups;
 }
 
-// Granularity of the (max, sum of exp) statistics that the score stage leaves for k_bins: the score tile, except that
+// Granularity of the (max, sum of exp) statistics that the score stage leaves for the value stage: the score tile, except that
 // k_score_stream writes them per 512-token segment and k_score_combine (tiles cut along the slices) per 1024 tokens.
 inline int stat_len(const commvq_handle *h, const Plan &p)
 {
@@ -236,7 +283,7 @@ void carve(const commvq_handle *h, int B, int64_t T, int max_seqlen, void *base,
     make_plan(h, B, T, max_seqlen, true, &pa);
     make_plan(h, B, T, max_seqlen, false, &pb);
     const size_t ssplits = std::max<size_t>(std::max(pa.score_splits, pb.score_splits), (size_t)stat_splits(h, pa, max_seqlen));
-    const size_t vsplits = pa.value_splits > pb.value_splits ? pa.value_splits : pb.value_splits;
+    const size_t vsplits = std::max(pa.value_splits, pb.value_splits);
     const size_t heads = (size_t)B * c.n_q_heads, rows = (size_t)val_books(c) * kK;
     const bool bf16 = c.codebook_dtype == COMMVQ_BF16;
     size_t off = 0;
@@ -269,13 +316,6 @@ struct ScoreDims {
     float scale;
 };
 
-
-// Raw buffer descriptor over [base, base + bytes): loads take a per-lane byte offset plus a
-// wave-uniform (scalar) byte offset, and reads past the end return zero instead of faulting.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *base, unsigned bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
-}
 
 __device__ __forceinline__ float row_max16(float v)
 {
@@ -577,15 +617,6 @@ __device__ __forceinline__ void bare_barrier()
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-}
-
-// The lane's index, made anew wherever it is asked for: what depends on it is then neither hoisted out of a loop nor kept in
-// registers (or spilled) across it.
-__device__ __forceinline__ int fresh_lane()
-{
-    int l;
-    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
-    return l;
 }
 
 constexpr int kBlockBytes = 64 * 1024;    // 16 codebooks x 256 codewords x 16 bytes
@@ -1179,19 +1210,6 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_stream(
             sstat[((size_t)sg.x * a.Hq + (size_t)g * G + h) * a.nstat + sg.y / kPassTokens] = make_float2(m, l);
         }
     }
-}
-
-// x + y after exchanging the odd 16-lane rows of x with the even rows of y (row r of the result:
-// r even: x[r] + x[r+1], r odd: y[r-1] + y[r]), and the same with 32-lane halves.
-__device__ __forceinline__ float swap16_add(float x, float y)
-{
-    auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, y), false, false);
-    return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
-}
-__device__ __forceinline__ float swap32_add(float x, float y)
-{
-    auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, y), false, false);
-    return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
 }
 
 // The tile's (max, sum of exp) per head, and the logits to memory, for the pair-code score kernel.
@@ -1942,189 +1960,6 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_pair(
     write_tile_logits<G, TPT, NPASS, NGRP>(sc, reinterpret_cast<float *>(tab), wstat, srow, stat_dst, a.nsplit, tb, t0, L);
 }
 
-// ------------------------------------------------------------------ k_bins
-struct BinsArgs {
-    const uint8_t *val_codes;
-    const int32_t *cu;
-    const float *scores;
-    const float2 *sstat;
-    unsigned *bins;
-    float *vscale, *lsum;
-    int Hq, Hkv, nsplit, split_len;  // score-stage split geometry (for the statistics)
-    int nvsplit, vsplit_len;
-    int Gtot;  // query heads per KV head; a workgroup handles G of them (all, unless their bins exceed the LDS)
-};
-
-// One thread per token: w = exp(logit - max) for the G heads of the group, then M_v * G
-// integer atomic adds into LDS bins indexed by the token's value codes (index form of
-// Softmax(A) S_V).  w is added as round(w * 2^S): the score stage already produced the
-// exp-sum l of this split (relative to the sequence maximum), every bin is bounded by it, so
-// S = 30 - floor(log2 l) keeps every bin below 2^31 while the rounding error of the whole
-// split stays below (tokens in split) * 2^-31 of its weight (half a unit per token, a unit being at most 2^-30 of the exp-sum).  Integer adds commute, so the
-// result does not depend on the order in which wavefronts arrive.
-template <int M, int G>
-__global__ __launch_bounds__(kBinsThreads) void k_bins(BinsArgs a)
-{
-    extern __shared__ __attribute__((aligned(16))) unsigned bins[];  // G * M * K; for G >= 2 used as 64-bit pairs
-    __shared__ float eoff_s[G];
-    int id = blockIdx.x;
-    const int g = id % a.Hkv;
-    id /= a.Hkv;
-    const int ngrp = a.Gtot / G;
-    const int h0 = g * a.Gtot + (id % ngrp) * G;  // first of the G query heads of this workgroup
-    id /= ngrp;
-    const int vs = id % a.nvsplit;
-    const int b = id / a.nvsplit;
-    const int cu0 = a.cu[b];
-    const int L = a.cu[b + 1] - cu0;
-    const int v0 = vs * a.vsplit_len;
-    if (v0 >= L) return;
-    const int v1 = min(v0 + a.vsplit_len, L);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    constexpr int NB = G * M * kK;
-
-    // For G >= 2 the bins of heads 2p and 2p + 1 share one 64-bit word (low / high half): one 64-bit LDS
-    // atomic then serves two heads.  Each half stays below 2^31 (see above), so no carry crosses.
-    // LDS layout [K codewords][G/2 pairs][M codebooks]: a 64-bit LDS operation is served 16 lanes at a time, and
-    // 16 lanes that update the same pair of 16 consecutive codebooks (cyclically) touch 16 consecutive 8-byte
-    // words -- 16 different bank pairs whatever their codes, where a [codebook][codeword] layout lets random
-    // codes collide.  The pair is an immediate offset, so an atomic costs no address arithmetic of its own.
-    constexpr int NP = G >= 2 ? G / 2 : 1;
-    // The token's codes and logits are fetched one iteration ahead (the first before the statistics below), so
-    // that their latency runs under the previous token's atomics.
-    const uint8_t *codes = a.val_codes + ((size_t)cu0 * a.Hkv + (size_t)g * L) * M;
-    const float *srow = a.scores + (size_t)cu0 * a.Hq + (size_t)h0 * L;
-    uint4 cnext[M / 16];
-    float snext[G];
-#define COMMVQ_BINS_FETCH(i_)                                                                            \
-    do {                                                                                                 \
-        const uint4 *cp_ = reinterpret_cast<const uint4 *>(codes + (size_t)(i_) * M);                    \
-        _Pragma("unroll") for (int v = 0; v < M / 16; ++v) cnext[v] = cp_[v];                            \
-        _Pragma("unroll") for (int hh = 0; hh < G; ++hh) snext[hh] = srow[(size_t)hh * L + (i_)];        \
-    } while (0)
-    if (v0 + tid < v1) COMMVQ_BINS_FETCH(v0 + tid);
-    for (int x = tid; x < NB / 4; x += kBinsThreads) reinterpret_cast<uint4 *>(bins)[x] = make_uint4(0u, 0u, 0u, 0u);
-    if (wave < G) {
-        const int ns = min((L + a.split_len - 1) / a.split_len, a.nsplit);
-        const float2 *st = a.sstat + ((size_t)b * a.Hq + h0 + wave) * a.nsplit;
-        // the first 64 splits' statistics stay in registers: one round of loads serves both passes
-        const float2 first = lane < ns ? st[lane] : make_float2(-INFINITY, 0.f);
-        float mx = first.x;  // maximum logit of head h0 + wave over the whole sequence
-        for (int s = lane + 64; s < ns; s += 64) mx = fmaxf(mx, st[s].x);
-        mx = wave_max(mx);
-        // Sum of exp(logit - mx) over the score tiles that this value split touches: it bounds every bin of the split
-        // (it IS the split's own sum when the split is a whole number of tiles) and fixes the fixed-point unit.  What
-        // the split reports towards the softmax denominator (lown) are the tiles that BEGIN inside it, so that a tile
-        // shared by several value splits is counted once.
-        const int sa = v0 / a.split_len, sb = min((v1 + a.split_len - 1) / a.split_len, ns);
-        float l = 0.f, lown = 0.f;
-        if (lane >= sa && lane < sb) {
-            l = first.y * __builtin_amdgcn_exp2f((first.x - mx) * kLog2e);
-            if (lane * a.split_len >= v0) lown = l;
-        }
-        for (int s = lane + 64; s < sb; s += 64)
-            if (s >= sa) {
-                const float t = st[s].y * __builtin_amdgcn_exp2f((st[s].x - mx) * kLog2e);
-                l += t;
-                if (s * a.split_len >= v0) lown += t;
-            }
-        l = wave_sum(l);
-        lown = wave_sum(lown);
-        int S = 0;
-        if (l >= 1e-30f) S = min(30 - ilogbf(l), 120);
-        if (lane == 0) {
-            eoff_s[wave] = (float)S - mx * kLog2e;
-            a.vscale[((size_t)b * a.Hq + h0 + wave) * a.nvsplit + vs] = ldexpf(1.f, -S);
-            a.lsum[((size_t)b * a.Hq + h0 + wave) * a.nvsplit + vs] = lown;
-        }
-    }
-    __syncthreads();
-    float eoff[G];
-#pragma unroll
-    for (int hh = 0; hh < G; ++hh) eoff[hh] = eoff_s[hh];
-
-    constexpr int CW = M / 4;
-    const unsigned rot = (unsigned)lane & (unsigned)(M - 1);
-    typedef __attribute__((address_space(3))) unsigned long long *lds_u64_ptr;
-    const unsigned bins_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned *)bins;
-    for (int i = v0 + tid; i < v1; i += kBinsThreads) {
-        unsigned cw[M / 4];
-#pragma unroll
-        for (int v = 0; v < M / 16; ++v) {
-            const uint4 c4 = cnext[v];
-            cw[4 * v + 0] = c4.x; cw[4 * v + 1] = c4.y; cw[4 * v + 2] = c4.z; cw[4 * v + 3] = c4.w;
-        }
-        unsigned p[G];
-#pragma unroll
-        for (int hh = 0; hh < G; ++hh)
-            p[hh] = (unsigned)(__builtin_amdgcn_exp2f(snext[hh] * kLog2e + eoff[hh]) + 0.5f);
-        if (i + kBinsThreads < v1) COMMVQ_BINS_FETCH(i + kBinsThreads);
-        asm volatile("" ::: "memory");  // keeps the compiler from sinking the fetch below the atomics
-        // Lane l walks the codebooks in the order (l + k) % M, so that at every step the 64 lanes spread over
-        // all M codebooks (bank columns, see above; skewed code usage would otherwise also put a dozen lanes on
-        // the same LDS address in one instruction).  The code vector is rotated by `rot` bytes once per token
-        // (dword selects + alignbyte).
-#pragma unroll
-        for (int st = 1; st < CW; st <<= 1) {
-            unsigned t[CW];
-#pragma unroll
-            for (int j = 0; j < CW; ++j) t[j] = ((rot >> 2) & st) ? cw[(j + st) % CW] : cw[j];
-#pragma unroll
-            for (int j = 0; j < CW; ++j) cw[j] = t[j];
-        }
-        unsigned rv[CW];
-#pragma unroll
-        for (int j = 0; j < CW; ++j) rv[j] = __builtin_amdgcn_alignbyte(cw[(j + 1) % CW], cw[j], rot & 3u);
-        unsigned long long pp[NP];
-        if (G >= 2) {
-#pragma unroll
-            for (int hp = 0; hp < NP; ++hp) pp[hp] = (unsigned long long)p[(2 * hp) % G] | (unsigned long long)p[(2 * hp + 1) % G] << 32;
-        }
-#pragma unroll
-        for (int k = 0; k < M; ++k) {
-            const unsigned c = (rv[k / 4] >> (8 * (k % 4))) & 0xffu;
-            const unsigned m = ((unsigned)k + rot) & (unsigned)(M - 1);
-            if (G == 1) {
-                atomicAdd(&bins[c * M + m], p[0]);
-            } else {
-                const unsigned ad = bins_base + c * (unsigned)(NP * M * 8) + m * 8u;
-#pragma unroll
-                for (int hp = 0; hp < NP; ++hp)
-                    __hip_atomic_fetch_add(reinterpret_cast<lds_u64_ptr>(ad + (unsigned)(hp * M * 8)), pp[hp], __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_WORKGROUP);
-            }
-        }
-    }
-#undef COMMVQ_BINS_FETCH
-    __syncthreads();
-    // memory layout [K][M][Gtot] 32-bit bins (heads innermost: a pair's two halves are heads 2p, 2p + 1)
-    unsigned *dst = a.bins + ((size_t)(b * a.Hkv + g) * a.nvsplit + vs) * (size_t)(a.Gtot * M * kK) + (h0 - g * a.Gtot);
-    if (G == 1) {
-        if (a.Gtot == 1) {
-            for (int x = tid; x < NB / 4; x += kBinsThreads)
-                reinterpret_cast<uint4 *>(dst)[x] = reinterpret_cast<const uint4 *>(bins)[x];
-        } else {
-            for (int x = tid; x < NB; x += kBinsThreads) dst[(size_t)x * a.Gtot] = bins[x];
-        }
-    } else {
-        const uint2 *src = reinterpret_cast<const uint2 *>(bins);  // [K][NP][M] pairs
-        for (int x = tid; x < kK * M; x += kBinsThreads) {
-            const int c = x / M, m = x % M;
-            uint2 v[NP];
-#pragma unroll
-            for (int hp = 0; hp < NP; ++hp) v[hp] = src[(c * NP + hp) * M + m];
-            unsigned *row = dst + (size_t)x * a.Gtot;  // 8-byte aligned for G = 2, 16-byte aligned for G >= 4
-            if (NP == 1) {
-                *reinterpret_cast<uint2 *>(row) = v[0];
-            } else {
-#pragma unroll
-                for (int hp = 0; hp < NP; hp += 2)
-                    *reinterpret_cast<uint4 *>(row + 2 * hp) = make_uint4(v[hp].x, v[hp].y, v[(hp + 1) % NP].x, v[(hp + 1) % NP].y);
-            }
-        }
-    }
-}
-
 // ------------------------------------------------------------------ k_out
 struct OutArgs {
     const void *val_cb;
@@ -2134,13 +1969,12 @@ struct OutArgs {
     float *partial, *out;
     int Hq, Hkv, nvsplit, vsplit_len, nchunk, Mv;
     int batch;
+    int per_split;  // partial results per value split (k_values); 0: nchunk in all
     int per_wg;  // k_out_mfma: chunks of kOutMfmaRows rows that a workgroup takes one after the other
-    // Index form: bins row r of a KV head = codeword r / M_v of codebook r % M_v, whose value-codebook row (of d
-    // elements) is g * M_v K + (r % M_v) * K + r / M_v.  Binary code (cb_linear): bins row r = code bit c =
-    // vbits_code_bit(r), codebook [N_c][Hkv * d], row of d elements c * Hkv + g.
-    int cb_linear;
 };
 
+// Second half of the binary value code (indexed values: k_values).  Bins row r of a KV head is code bit c = vbits_code_bit(r),
+// whose codebook row of d elements, in [N_c][Hkv * d], is c * Hkv + g.
 // Workgroup = (sequence, KV head, chunk of codebook rows): sums the chunk's bins over the
 // context splits (fixed point -> fp32 with each split's unit), then multiplies them with the
 // chunk's value-codebook rows (Eq. optimized_v).
@@ -2187,8 +2021,7 @@ __global__ __launch_bounds__(kOutThreads) void k_out(OutArgs a)
     const int cpc = kOutRows / a.Mv, mpw = a.Mv / (kOutThreads / 64);  // codewords per chunk, codebooks per wavefront
     auto load_row = [&](int i) -> float2 {
         const int m = wave * mpw + i / cpc, cl = i % cpc;
-        const size_t row = a.cb_linear ? (size_t)vbits_code_bit(chunk * kOutRows + cl * a.Mv + m) * a.Hkv + g
-                                       : (size_t)g * MK + (size_t)m * kK + (size_t)chunk * cpc + cl;
+        const size_t row = (size_t)vbits_code_bit(chunk * kOutRows + cl * a.Mv + m) * a.Hkv + g;
         if (BF16) {
             const unsigned v = static_cast<const unsigned *>(a.val_cb)[row * kJ + lane];
             return make_float2(bf16_lo(v), bf16_hi(v));
@@ -2265,11 +2098,10 @@ __global__ __launch_bounds__(kOutThreads) void k_out(OutArgs a)
     }
 }
 
-// Value codebook re-laid for k_out_mfma: vp[g][kt][dim][32] bf16, where row 32 kt + j of head g is codeword
-// (32 kt + j) / M_v of codebook (32 kt + j) % M_v (the row order of the bins) -- the 32 rows of a k-step of the matrix
+// Value codebook of the binary code re-laid for k_out_mfma: vp[g][kt][dim][32] bf16, where row 32 kt + j of head g is code bit
+// vbits_code_bit(32 kt + j) (the row order of the bins) -- the 32 rows of a k-step of the matrix
 // instruction contiguous per output dimension.  One thread per 16-byte piece of the output (static data, done once).
-__global__ __launch_bounds__(256) void k_prep_values(const uint16_t *__restrict__ val_cb, uint4 *__restrict__ vp, int Hkv, int Mv,
-                                                     int linear)
+__global__ __launch_bounds__(256) void k_prep_values(const uint16_t *__restrict__ val_cb, uint4 *__restrict__ vp, int Hkv, int Mv)
 {
     const int MK = Mv * kK;
     const size_t n = (size_t)Hkv * (MK / 32) * kD * 4;
@@ -2282,8 +2114,7 @@ __global__ __launch_bounds__(256) void k_prep_values(const uint16_t *__restrict_
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
         const int r = 32 * kt + 8 * kg + e;
-        const unsigned v = linear ? val_cb[((size_t)vbits_code_bit(r) * Hkv + g) * kD + dim]  // binary code: [N_c][Hkv * d]
-                                  : val_cb[(((size_t)g * Mv + r % Mv) * kK + r / Mv) * kD + dim];
+        const unsigned v = val_cb[((size_t)vbits_code_bit(r) * Hkv + g) * kD + dim];
         if (e & 1) w[e / 2] |= v << 16; else w[e / 2] = v;
     }
     vp[t] = make_uint4(w[0], w[1], w[2], w[3]);
@@ -2431,14 +2262,15 @@ __global__ __launch_bounds__(kD * kFinalParts) void k_out_final(OutArgs a)
     const int bh = blockIdx.x;
     const int b = bh / a.Hq;
     const int e = threadIdx.x % kD, q = threadIdx.x / kD;
-    const float *pp = a.partial + (size_t)bh * a.nchunk * kD + e;
+    const int L = a.cu[b + 1] - a.cu[b];
+    const int nvs = min((L + a.vsplit_len - 1) / a.vsplit_len, a.nvsplit);
+    const int rows = a.per_split ? a.nvsplit * a.per_split : a.nchunk, n = a.per_split ? nvs * a.per_split : a.nchunk;
+    const float *pp = a.partial + (size_t)bh * rows * kD + e;
     float s = 0.f;
 #pragma unroll 16
-    for (int c = q; c < a.nchunk; c += kFinalParts) s += pp[(size_t)c * kD];
+    for (int c = q; c < n; c += kFinalParts) s += pp[(size_t)c * kD];
     part[q][e] = s;
     if (threadIdx.x < 64) {
-        const int L = a.cu[b + 1] - a.cu[b];
-        const int nvs = min((L + a.vsplit_len - 1) / a.vsplit_len, a.nvsplit);
         float l = 0.f;
         for (int v = threadIdx.x; v < nvs; v += 64) l += a.lsum[(size_t)bh * a.nvsplit + v];
         l = wave_sum(l);
@@ -2526,31 +2358,6 @@ hipError_t launch_score_m(const ScoreArgs &a, int G, bool bf16, int grid, hipStr
     case 2: return launch_score_mg<M, 2>(a, bf16, grid, s);
     case 4: return launch_score_mg<M, 4>(a, bf16, grid, s);
     default: return launch_score_mg<M, 8>(a, bf16, grid, s);
-    }
-}
-
-template <int M, int G>
-hipError_t launch_bins_mg(BinsArgs a, int Gtot, int grid, hipStream_t s)
-{
-    a.Gtot = Gtot;
-    grid *= Gtot / G;
-    const size_t lds = (size_t)G * M * kK * sizeof(unsigned);
-    static std::atomic<uint64_t> lds_ok{0};  // per instantiation and device
-    if (hipError_t e = allow_dynamic_lds(&k_bins<M, G>, (int)lds, lds_ok); e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_bins<M, G>), dim3(grid), dim3(kBinsThreads), lds, s, a);
-    return hipGetLastError();
-}
-template <int M>
-hipError_t launch_bins_m(const BinsArgs &a, int G, int grid, hipStream_t s)
-{
-    switch (G) {
-    case 1: return launch_bins_mg<M, 1>(a, 1, grid, s);
-    case 2: return launch_bins_mg<M, 2>(a, 2, grid, s);
-    case 4: return launch_bins_mg<M, 4>(a, 4, grid, s);
-    default:
-        // 8 heads x 32 codebooks of bins are 256 KiB, more than a compute unit's LDS: two workgroups of 4 heads
-        if (M == 32) return launch_bins_mg<M, 4>(a, 8, grid, s);
-        return launch_bins_mg<M, 8>(a, 8, grid, s);
     }
 }
 
@@ -2664,7 +2471,7 @@ hipError_t launch_prep_values(const commvq_config &c, const void *val_cb, uint4 
 {
     const size_t n = (size_t)c.n_kv_heads * val_books(c) * kK * kD * 2 / 16;
     hipLaunchKernelGGL(k_prep_values, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, static_cast<const uint16_t *>(val_cb), vp,
-                       c.n_kv_heads, val_books(c), bin_values(c) ? 1 : 0);
+                       c.n_kv_heads, val_books(c));
     return hipGetLastError();
 }
 
@@ -2781,28 +2588,80 @@ commvq_status run_scores(commvq_handle *h, const void *q, const uint8_t *key_cod
     return e == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;
 }
 
+template <int G, int CB, int S, int NCS, int NT, bool BF16>
+hipError_t launch_values_n(const ValuesArgs &a, hipStream_t s)
+{
+    constexpr int lds = values_lds<G, CB, S, NCS, NT>();
+    if (a.ncg * CB != a.M) return hipErrorInvalidValue;  // (a shape that this instantiation is not for)
+    static std::atomic<uint64_t> lds_ok{0};  // per instantiation and device
+    if (hipError_t e = allow_dynamic_lds(&k_values<G, CB, S, NCS, NT, BF16>, lds, lds_ok); e != hipSuccess) return e;
+    const unsigned grid = (unsigned)(S == 1 ? a.batch * a.ranges : (a.batch + S - 1) / S) * (unsigned)(NCS * a.ncg * a.Hkv);
+    hipLaunchKernelGGL((k_values<G, CB, S, NCS, NT, BF16>), dim3(grid), dim3(NT), lds, s, a);
+    return hipGetLastError();
+}
+template <int G>
+hipError_t launch_values_g(const ValuesArgs &a, const ValueShape &v, bool bf16, hipStream_t s)
+{
+    if (!bf16) return v.parts == 4 ? launch_values_n<G, 4, 1, 4, 512, false>(a, s) : launch_values_n<G, 4, 1, 1, 512, false>(a, s);
+    if (v.parts == 4) return launch_values_n<G, 4, 1, 4, 512, true>(a, s);
+    if constexpr (G >= 4) {
+        if (v.slots == 2) return launch_values_n<G, 8, 2, 1, 512, true>(a, s);
+        if constexpr (G == 4)
+            if (v.slots == 4) return launch_values_n<4, 8, 4, 1, 512, true>(a, s);
+        if (v.books == 8) return v.threads == 1024 ? launch_values_n<G, 8, 1, 1, 1024, true>(a, s) : launch_values_n<G, 8, 1, 1, 512, true>(a, s);
+        return launch_values_n<G, 4, 1, 1, 1024, true>(a, s);
+    } else {
+        return launch_values_n<G, 4, 1, 1, 512, true>(a, s);
+    }
+}
+
+// Value stage and product with the value codebook: mode 0 in one, 1 up to the bins, 2 from the bins on (k_values).
+commvq_status run_values(commvq_handle *h, const uint8_t *val_codes, const void *val_cb, const commvq_positions *pos,
+                         const Plan &plan, const Workspace &w, int mode, hipStream_t s)
+{
+    const commvq_config &c = h->cfg;
+    ValuesArgs a;
+    a.val_codes = val_codes; a.val_cb = val_cb; a.cu = pos->cu_seqlens; a.scores = w.scores; a.sstat = w.sstat;
+    a.bins = w.bins; a.vscale = w.vscale; a.lsum = w.lsum; a.partial = w.partial;
+    a.Hq = c.n_q_heads; a.Hkv = c.n_kv_heads; a.M = c.m_val;
+    a.nsplit = stat_splits(h, plan, pos->max_seqlen); a.split_len = stat_len(h, plan);
+    a.ranges = plan.values.ranges; a.range_len = plan.values.range_len;
+    a.batch = pos->batch; a.ncg = c.m_val / plan.values.books; a.mode = mode;
+    hipError_t e;
+    const bool bf16 = c.codebook_dtype == COMMVQ_BF16;
+    switch (h->G) {
+    case 1: e = launch_values_g<1>(a, plan.values, bf16, s); break;
+    case 2: e = launch_values_g<2>(a, plan.values, bf16, s); break;
+    case 4: e = launch_values_g<4>(a, plan.values, bf16, s); break;
+    default: e = launch_values_g<8>(a, plan.values, bf16, s); break;
+    }
+    return e == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;
+}
+
+// Sum of the partial results of k_values.
+commvq_status run_values_final(commvq_handle *h, const commvq_positions *pos, const Plan &plan, const Workspace &w, float *out, hipStream_t s)
+{
+    OutArgs a = {};
+    a.cu = pos->cu_seqlens; a.lsum = w.lsum; a.partial = w.partial; a.out = out;
+    a.Hq = h->cfg.n_q_heads; a.Hkv = h->cfg.n_kv_heads; a.nvsplit = plan.values.ranges; a.vsplit_len = plan.values.range_len;
+    a.per_split = h->cfg.m_val / plan.values.books; a.batch = pos->batch;
+    hipLaunchKernelGGL(k_out_final, dim3(pos->batch * h->cfg.n_q_heads), dim3(kD * kFinalParts), 0, s, a);
+    return hipGetLastError() == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;
+}
+
+// Binary code: Softmax(A) S_V as an integer matrix product (commvq_vbits.hip), then its product with the codebook.
 commvq_status run_bins(commvq_handle *h, const uint8_t *val_codes, const commvq_positions *pos,
                        const Plan &plan, const Workspace &w, hipStream_t s)
 {
     const commvq_config &c = h->cfg;
-    if (bin_values(c)) {  // free binary code: Softmax(A) S_V as an integer matrix product (commvq_vbits.hip)
-        VbitsArgs v;
-        v.val_bits = val_codes; v.cu = pos->cu_seqlens; v.scores = w.scores; v.sstat = w.sstat;
-        v.bins = w.bins; v.vscale = w.vscale; v.lsum = w.lsum;
-        v.Hq = c.n_q_heads; v.Hkv = c.n_kv_heads; v.G = h->G;
-        v.nsplit = stat_splits(h, plan, pos->max_seqlen); v.split_len = stat_len(h, plan);
-        v.nvsplit = plan.value_splits; v.vsplit_len = plan.value_split_len;
-        v.Nc = c.value_bits; v.batch = pos->batch;
-        return commvq_launch_vbits(v, s) == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;
-    }
-    BinsArgs a;
-    a.val_codes = val_codes; a.cu = pos->cu_seqlens; a.scores = w.scores; a.sstat = w.sstat;
-    a.bins = w.bins; a.vscale = w.vscale; a.lsum = w.lsum;
-    a.Hq = c.n_q_heads; a.Hkv = c.n_kv_heads; a.nsplit = stat_splits(h, plan, pos->max_seqlen); a.split_len = stat_len(h, plan);
-    a.nvsplit = plan.value_splits; a.vsplit_len = plan.value_split_len;
-    const int grid = pos->batch * c.n_kv_heads * plan.value_splits;
-    hipError_t e = c.m_val == 16 ? launch_bins_m<16>(a, h->G, grid, s) : launch_bins_m<32>(a, h->G, grid, s);
-    return e == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;
+    VbitsArgs v;
+    v.val_bits = val_codes; v.cu = pos->cu_seqlens; v.scores = w.scores; v.sstat = w.sstat;
+    v.bins = w.bins; v.vscale = w.vscale; v.lsum = w.lsum;
+    v.Hq = c.n_q_heads; v.Hkv = c.n_kv_heads; v.G = h->G;
+    v.nsplit = stat_splits(h, plan, pos->max_seqlen); v.split_len = stat_len(h, plan);
+    v.nvsplit = plan.value_splits; v.vsplit_len = plan.value_split_len;
+    v.Nc = c.value_bits; v.batch = pos->batch;
+    return commvq_launch_vbits(v, s) == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;
 }
 
 commvq_status run_output(commvq_handle *h, const void *val_cb, const commvq_positions *pos, const Plan &plan,
@@ -2814,8 +2673,7 @@ commvq_status run_output(commvq_handle *h, const void *val_cb, const commvq_posi
     a.partial = w.partial; a.out = out;
     a.Hq = c.n_q_heads; a.Hkv = c.n_kv_heads;
     a.nvsplit = plan.value_splits; a.vsplit_len = plan.value_split_len;
-    a.nchunk = plan.out_chunks; a.Mv = val_books(c); a.batch = pos->batch; a.per_wg = 1;
-    a.cb_linear = bin_values(c) ? 1 : 0;
+    a.nchunk = plan.out_chunks; a.Mv = val_books(c); a.batch = pos->batch; a.per_wg = 1; a.per_split = 0;
     const int grid = pos->batch * c.n_kv_heads * plan.out_chunks;
     const bool bf16 = c.codebook_dtype == COMMVQ_BF16;
     hipError_t e;
@@ -3061,6 +2919,7 @@ commvq_status commvq_pack_value_codebooks(commvq_handle *h, const void *val_cb, 
     if (h->cfg.codebook_dtype != COMMVQ_BF16) return COMMVQ_ERR_CONFIG;
     if ((reinterpret_cast<uintptr_t>(val_cb) | reinterpret_cast<uintptr_t>(packed)) & 15u) return COMMVQ_ERR_SHAPE;
     if (h->device < 0) return COMMVQ_ERR_NO_DEVICE;
+    if (!bin_values(h->cfg)) return COMMVQ_OK;  // k_values reads the codebook as it is
     if (launch_prep_values(h->cfg, val_cb, static_cast<uint4 *>(packed), static_cast<hipStream_t>(stream)) != hipSuccess)
         return COMMVQ_ERR_LAUNCH;
     for (auto &e : h->packed_vals)
@@ -3127,6 +2986,7 @@ commvq_status commvq_stage_bins(commvq_handle *h, const uint8_t *val_codes, cons
     Workspace w;
     commvq_status st = prep(h, pos, workspace, workspace_bytes, &plan, &w);
     if (st != COMMVQ_OK) return st;
+    if (fused_values(h->cfg)) return run_values(h, val_codes, nullptr, pos, plan, w, 1, static_cast<hipStream_t>(stream));
     return run_bins(h, val_codes, pos, plan, w, static_cast<hipStream_t>(stream));
 }
 
@@ -3138,6 +2998,10 @@ commvq_status commvq_stage_output(commvq_handle *h, const void *val_cb, const co
     Workspace w;
     commvq_status st = prep(h, pos, workspace, workspace_bytes, &plan, &w);
     if (st != COMMVQ_OK) return st;
+    if (fused_values(h->cfg)) {
+        st = run_values(h, nullptr, val_cb, pos, plan, w, 2, static_cast<hipStream_t>(stream));
+        return st == COMMVQ_OK ? run_values_final(h, pos, plan, w, out, static_cast<hipStream_t>(stream)) : st;
+    }
     return run_output(h, val_cb, pos, plan, w, out, static_cast<hipStream_t>(stream));
 }
 
@@ -3166,10 +3030,11 @@ commvq_status commvq_decode_attn(commvq_handle *h, const void *q, const uint8_t 
     st = run_scores(h, q, key_codes, key_cb, pos, plan, w, s);
     if (st != COMMVQ_OK) return st;
     if (ev && hipEventRecord(ev[1], s) != hipSuccess) return COMMVQ_ERR_LAUNCH;
-    st = run_bins(h, val_codes, pos, plan, w, s);
+    const bool fused = fused_values(h->cfg);
+    st = fused ? run_values(h, val_codes, val_cb, pos, plan, w, 0, s) : run_bins(h, val_codes, pos, plan, w, s);
     if (st != COMMVQ_OK) return st;
     if (ev && hipEventRecord(ev[2], s) != hipSuccess) return COMMVQ_ERR_LAUNCH;
-    st = run_output(h, val_cb, pos, plan, w, out, s);
+    st = fused ? run_values_final(h, pos, plan, w, out, s) : run_output(h, val_cb, pos, plan, w, out, s);
     if (st != COMMVQ_OK) return st;
     if (ev) {
         if (hipEventRecord(ev[3], s) != hipSuccess) return COMMVQ_ERR_LAUNCH;
@@ -3196,9 +3061,10 @@ commvq_status commvq_decode_attn_static(commvq_handle *h, const void *q, const u
     hipStream_t s = static_cast<hipStream_t>(stream);
     st = run_scores(h, q, key_codes, key_cb, pos, plan, w, s);
     if (st != COMMVQ_OK) return st;
-    st = run_bins(h, val_codes, pos, plan, w, s);
+    const bool fused = fused_values(h->cfg);
+    st = fused ? run_values(h, val_codes, val_cb, pos, plan, w, 0, s) : run_bins(h, val_codes, pos, plan, w, s);
     if (st != COMMVQ_OK) return st;
-    return run_output(h, val_cb, pos, plan, w, out, s);
+    return fused ? run_values_final(h, pos, plan, w, out, s) : run_output(h, val_cb, pos, plan, w, out, s);
 }
 
 commvq_status commvq_static_scratch_bytes(size_t *bytes)

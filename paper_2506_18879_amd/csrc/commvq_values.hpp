@@ -1,0 +1,498 @@
+// Value and output stage of indexed values in one kernel (included by commvq.hip).
+#pragma once
+#include "commvq_internal.hpp"
+
+namespace {
+
+// 64-bit words of a codeword's row of bins (a word per pair of heads and codebook, repeated to fill the row), and bytes of
+// the bins of one slot.
+template <int G, int CB, int S>
+constexpr int values_words()
+{
+    constexpr int own = (G >= 2 ? G / 2 : 1) * CB, row = S == 1 && G >= 4 ? 32 : 16;
+    return own > row ? own : row;
+}
+template <int G, int CB, int S>
+constexpr int values_slot() { return kK * values_words<G, CB, S>() * 8; }
+// LDS of a workgroup: the slots' bins or, later, the wavefronts' sums; behind them two numbers per slot and head.
+template <int G, int CB, int S, int NCS, int NT>
+constexpr int values_lds()
+{
+    constexpr int red = NT / 64 * S * G * (kD / NCS) * 4, bins = S * values_slot<G, CB, S>();
+    return (bins > red ? bins : red) + 2 * S * G * 4;
+}
+
+struct ValuesArgs {
+    const uint8_t *val_codes;
+    const void *val_cb;       // [Hkv][M][K][d] bf16 or fp32
+    const int32_t *cu;
+    const float *scores;
+    const float2 *sstat;      // [B * Hq][nsplit] (max, sum of exp(logit - max)) of the score stage
+    unsigned *bins;           // mode 1 writes, mode 2 reads: [B * Hkv][ranges][ncg][K][pairs][CB][2 heads]
+    float *vscale, *lsum;     // [B * Hq][ranges]
+    float *partial;           // [B * Hq][ranges][ncg][d]
+    int Hq, Hkv, M;
+    int nsplit, split_len;    // statistics tiles of the score stage
+    int batch, ncg;
+    int ranges, range_len;    // token ranges of a sequence (S > 1: one)
+    int mode;                 // 0: everything; 1: up to the bins, which go to memory; 2: from there on
+};
+
+// The lane's index, made anew wherever it is asked for: what depends on it is then neither hoisted out of a loop nor kept in
+// registers (or spilled) across it.
+__device__ __forceinline__ int fresh_lane()
+{
+    int l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+    return l;
+}
+
+// Raw buffer descriptor over [base, base + bytes): loads take a per-lane byte offset plus a
+// wave-uniform (scalar) byte offset, and reads past the end return zero instead of faulting.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *base, unsigned bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
+}
+
+// floor(x + 0.5) of numbers on [0, 2^31).  (The s_nop is the wait state between an exponential and the use of its result,
+// which the compiler does not insert in front of inline asm.)
+template <int G>
+__device__ __forceinline__ void round_up_half(const float (&x)[G], unsigned (&r)[G])
+{
+    if constexpr (G % 4 == 0) {
+#pragma unroll
+        for (int k = 0; k < G; k += 4) {
+            float e0 = x[k], e1 = x[k + 1], e2 = x[k + 2], e3 = x[k + 3];
+            asm("s_nop 1\n\tv_cvt_rpi_i32_f32 %0, %0\n\tv_cvt_rpi_i32_f32 %1, %1\n\tv_cvt_rpi_i32_f32 %2, %2\n\tv_cvt_rpi_i32_f32 %3, %3"
+                : "+v"(e0), "+v"(e1), "+v"(e2), "+v"(e3));
+            r[k] = __builtin_bit_cast(unsigned, e0); r[k + 1] = __builtin_bit_cast(unsigned, e1);
+            r[k + 2] = __builtin_bit_cast(unsigned, e2); r[k + 3] = __builtin_bit_cast(unsigned, e3);
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < G; ++k) {
+            float e = x[k];
+            asm("s_nop 1\n\tv_cvt_rpi_i32_f32 %0, %0" : "+v"(e));
+            r[k] = __builtin_bit_cast(unsigned, e);
+        }
+    }
+}
+
+// x + y after exchanging the odd 16-lane rows of x with the even rows of y (row r of the result:
+// r even: x[r] + x[r+1], r odd: y[r-1] + y[r]), and the same with 32-lane halves.
+__device__ __forceinline__ float swap16_add(float x, float y)
+{
+    auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, y), false, false);
+    return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+}
+__device__ __forceinline__ float swap32_add(float x, float y)
+{
+    auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, y), false, false);
+    return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+}
+
+// Softmax(A) S_V of Eq. optimized_v and its product with the value codebook, without the bins' trip through memory.  A
+// workgroup takes CB of the M value codebooks of a KV head, for a range of a sequence's tokens or (S > 1) for S whole
+// sequences side by side, and leaves one unnormalised output row per head and range, which k_out_final adds.
+//
+// Bins.  w = exp(logit - max of the sequence) is added as round(w 2^sh) with integer LDS atomics.  The score stage has
+// left the exp-sum l of every statistics tile; sh = 30 - floor(log2 l) of the tiles that the range touches keeps every bin below 2^31
+// and the rounding below (tokens) 2^-31 of l.  Heads 2 p and 2 p + 1 share a 64-bit word (no carry crosses).  A 64-bit LDS
+// atomic is served 16 lanes at a time, so a codeword's row is [copy][pair][codebook] with at least 16 words and
+// lane l starts at (copy, pair, codebook) l mod 16 and walks pairs and codebooks by exclusive or: 16 lanes are on 16 bank pairs
+// at every step, whatever their codes, and lanes with the same code do not meet either.
+//
+// Product.  The bins of CB codebooks are a (heads x CB K) x (CB K x d) matrix product.  A bin is an integer of four 8-bit
+// digits, each exact in bf16, so that digit x head fill the 16 rows of v_mfma_f32_16x16x32_bf16 (4 heads; two tiles for 8) and
+// the exact bins are multiplied, not their 24 leading bits; the digits' sums are scaled by 256^digit at the end.  The
+// wavefronts share the k-steps; a lane loads 16 bytes of 8 rows (256 bytes of a row per 16 lanes) and interleaves them in
+// registers, column 8 n + t of lane n for tile t, so the codebook needs no other layout.  fp32 rows are multiplied by vector
+// instructions, four columns per lane.
+//
+// What bounds it, by variants with a part left out, 128K tokens of the 8B layer at 16 codebooks (21 us): 5.6 until the first token is
+// worked on (4.7 of them the launch after a kernel that leaves 17 MB of dirty lines), 8 for the tokens (the atomics alone are
+// 6.7 at 8.2 lanes a clock), 7.6 for the product (512 KiB of rows through the L1 of every compute unit, at 27 to 64
+// bytes a clock; 4 codebooks a workgroup halve that and double the exponentials).  The bins' way through memory
+// that it replaces (16 MB out of one kernel and into the next at that size, 67 MB for 64 chats) and one launch less, whole call:
+// one fp32 head of 4096 tokens 23.9 -> 19.8 us; 8B 2-bit 1237 tokens 31.1 -> 24.8, 32K 69.8 -> 56.9, 8 x 8K..64K 483 -> 469, 64 x
+// 512..1024 136 -> 118; 8B 1-bit 128K 92.8 -> 88.6, position-free 39.5 -> 36.0; 70B 4 x 128K 559 -> 553.  Not kept: equal chunks of the whole batch
+// instead of ranges per sequence (more products: 8 x 8K..64K 456 -> 480), rows touched early to have them in L2 (no change).
+template <int G, int CB, int S, int NCS, int NT, bool BF16>
+__global__ __launch_bounds__(NT, S > 1 ? 2 : 4) void k_values(const ValuesArgs a)
+{
+    constexpr int NP = G >= 2 ? G / 2 : 1;                 // head pairs, a 64-bit word each
+    constexpr int WORDS = values_words<G, CB, S>(), ROWB = WORDS * 8, SLOT = values_slot<G, CB, S>(), COPIES = WORDS / (NP * CB);
+    constexpr int PX = CB * COPIES < 16 ? 16 / (CB * COPIES) : 1;  // pairs that the lanes walk by exclusive or; the others are offsets
+    static_assert((ROWB == 128 || ROWB == 256) && (CB == 4 || CB == 8), "rows of bins of one or half an LDS bank row");
+    static_assert(BF16 || S == 1, "fp32 rows: one slot");
+    constexpr int CD = CB / 4;                             // code dwords of a token
+    constexpr int NW = NT / 64;
+    constexpr int KS = CB * kK / 32 / NW;                  // k-steps of a wavefront
+    constexpr int NX = (G + 3) / 4;                        // first-operand tiles: 4 heads x 4 digits
+    constexpr int COLS = kD / NCS, NCT = COLS / 16;        // columns of the workgroup, tiles of 16
+    constexpr int ND = NCT / 2;                            // dwords of a codebook row that a lane loads
+    constexpr int DEPTH = S == 1 ? (CB * NP <= 8 ? 4 : 2) : S == 2 ? 2 : 1;  // tokens whose codes and logits are in flight, per slot
+    extern __shared__ __attribute__((aligned(128))) unsigned char lds[];
+    float *eoff_s = reinterpret_cast<float *>(lds + values_lds<G, CB, S, NCS, NT>()) - 2 * S * G, *unit_s = eoff_s + S * G;
+    float *red = reinterpret_cast<float *>(lds);           // [NW][S][G][COLS]
+
+    int id = blockIdx.x;
+    const int g = id % a.Hkv;                              // (head = index mod Hkv: with 8 KV heads an XCD serves one head)
+    id /= a.Hkv;
+    const int cg = id % a.ncg;
+    id /= a.ncg;
+    const int cs = id % NCS, grp = id / NCS;
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    const int mshift = a.M == 32 ? 5 : 4;                  // (16 or 32 codebooks)
+    int sb[S], sv0[S], sv1[S], sL[S], scu[S];              // sequence, first and last token + 1, length, offset of the slots
+    bool any = false;
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        const int b = S == 1 ? grp % a.batch : grp * S + s;
+        sb[s] = b < a.batch ? b : 0;
+        scu[s] = a.cu[sb[s]];
+        sL[s] = a.cu[sb[s] + 1] - scu[s];
+        sv0[s] = S == 1 ? grp / a.batch * a.range_len : 0;
+        sv1[s] = S == 1 ? min(sv0[s] + a.range_len, sL[s]) : b < a.batch ? sL[s] : 0;
+        any |= sv0[s] < sv1[s];
+    }
+    if (!any) return;
+    const int rng = S == 1 ? grp / a.batch : 0;
+
+    // the first tokens' codes and logits
+    // (buffer loads: one offset per lane, reads past the sequence return zeros)
+    unsigned cnext[S][DEPTH][CD];
+    float snext[S][DEPTH][G];
+    auto fetch = [&](int s, int d, int t) __attribute__((always_inline)) {
+        const __amdgpu_buffer_rsrc_t codes = make_rsrc(a.val_codes + ((size_t)scu[s] * a.Hkv + (size_t)g * sL[s]) * a.M, (unsigned)sL[s] * (unsigned)a.M);
+        const __amdgpu_buffer_rsrc_t rows = make_rsrc(a.scores + (size_t)scu[s] * a.Hq + (size_t)g * G * sL[s], (unsigned)sL[s] * (unsigned)(G * 4));
+        const unsigned i = (unsigned)(t + tid), at = i << mshift;
+        if constexpr (CD == 1) {
+            cnext[s][d][0] = __builtin_amdgcn_raw_buffer_load_b32(codes, at, (unsigned)(cg * CB), 0);
+        } else {
+            const uint2_t c = __builtin_amdgcn_raw_buffer_load_b64(codes, at, (unsigned)(cg * CB), 0);
+            cnext[s][d][0] = c[0];
+            cnext[s][d][1] = c[1];
+        }
+#pragma unroll
+        for (int hh = 0; hh < G; ++hh)
+            snext[s][d][hh] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rows, i * 4u, (unsigned)(hh * 4) * (unsigned)sL[s], 0));
+    };
+    if (a.mode != 2) {
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+#pragma unroll
+            for (int d = 0; d < DEPTH; ++d)
+                if (sv0[s] + d * NT < sv1[s]) fetch(s, d, sv0[s] + d * NT);
+    }
+    for (int x = tid; x < S * SLOT / 16; x += NT) reinterpret_cast<uint4 *>(lds)[x] = make_uint4(0u, 0u, 0u, 0u);
+
+    // (maximum of the sequence, exp-sum of the range) of every slot and head
+    for (int job = wave; job < S * G; job += NW) {
+        const int s = job / G, hh = job % G;
+        int b = 0, v0 = 0, v1 = 0, L = 0;
+#pragma unroll
+        for (int k = 0; k < S; ++k)
+            if (s == k) { b = sb[k]; v0 = sv0[k]; v1 = sv1[k]; L = sL[k]; }
+        if (v0 >= v1) continue;
+        const size_t at = ((size_t)b * a.Hq + (size_t)g * G + hh) * a.ranges + rng;
+        if (a.mode == 2) {
+            if (lane == 0) unit_s[job] = a.vscale[at];
+            continue;
+        }
+        const int ns = min((L + a.split_len - 1) / a.split_len, a.nsplit);
+        const float2 *st = a.sstat + ((size_t)b * a.Hq + (size_t)g * G + hh) * a.nsplit;
+        // the first 64 tiles' statistics stay in registers: one round of loads serves both passes
+        const float2 first = lane < ns ? st[lane] : make_float2(-INFINITY, 0.f);
+        float mx = first.x;
+        for (int k = lane + 64; k < ns; k += 64) mx = fmaxf(mx, st[k].x);
+        mx = wave_max(mx);
+        // l bounds every bin of the range: all tiles that it touches; what it reports towards the softmax denominator (lown)
+        // are the tiles that BEGIN inside it, so that a tile shared by two ranges is counted once
+        const int ta = v0 / a.split_len, tb = min((v1 + a.split_len - 1) / a.split_len, ns);
+        float l = 0.f, lown = 0.f;
+        if (lane >= ta && lane < tb) {
+            l = first.y * __builtin_amdgcn_exp2f((first.x - mx) * kLog2e);
+            if (lane * a.split_len >= v0) lown = l;
+        }
+        for (int k = lane + 64; k < tb; k += 64)
+            if (k >= ta) {
+                const float t = st[k].y * __builtin_amdgcn_exp2f((st[k].x - mx) * kLog2e);
+                l += t;
+                if (k * a.split_len >= v0) lown += t;
+            }
+        l = wave_sum(l);
+        lown = wave_sum(lown);
+        int sh = 0;
+        if (l >= 1e-30f) sh = min(30 - ilogbf(l), 120);
+        if (lane == 0) {
+            const float unit = ldexpf(1.f, -sh);
+            eoff_s[job] = (float)sh - mx * kLog2e;
+            unit_s[job] = unit;
+            if (cg == 0 && cs == 0) {
+                a.lsum[at] = lown;
+                if (a.mode == 1) a.vscale[at] = unit;
+            }
+        }
+    }
+    __syncthreads();
+
+    // the wavefront's codebook rows, k-step by k-step: the first ones travel while the tokens are worked on
+    // (addresses: a uniform base per codebook and k-step, one offset per lane)
+    const char *cb0 = static_cast<const char *>(a.val_cb) + (((size_t)g * a.M + (size_t)cg * CB) * (size_t)(kK * kD) + cs * COLS) * 2;
+    constexpr int RB = S * NX == 1 ? 2 : 1;            // k-steps whose rows are in flight
+    constexpr int CL = 8 / CB;                         // codewords of a lane's eight rows
+    unsigned R[RB][8][ND];
+    auto load_rows = [&](int j, unsigned(&r)[8][ND]) __attribute__((always_inline)) {
+        const int ln = fresh_lane();
+        const unsigned off = (unsigned)((ln >> 4) * CL * kD + (ln & 15) * NCT) * 2u;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int code = (wave * KS + j) * (32 / CB) + e / CB, cb = e % CB;
+            const unsigned *p = reinterpret_cast<const unsigned *>(cb0 + (size_t)(cb * kK + code) * (size_t)(kD * 2) + off);
+            if constexpr (ND == 4) {
+                typedef unsigned u4u __attribute__((ext_vector_type(4), aligned(4)));  // (the caller's codebook: any alignment that its elements have)
+                const u4u v = *reinterpret_cast<const u4u *>(p);
+                r[e][0] = v[0]; r[e][1] = v[1]; r[e][2] = v[2]; r[e][3] = v[3];
+            } else {
+                static_assert(ND == 4 || ND == 1, "16 or 4 bytes of a row");
+                r[e][0] = p[0];
+            }
+        }
+    };
+    __builtin_amdgcn_sched_barrier(0);
+    if (BF16 && a.mode != 1) load_rows(0, R[0]);
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+
+    typedef __attribute__((address_space(3))) unsigned long long *lds_u64_ptr;  // (dynamic LDS begins at LDS address 0: there is no other)
+    if (a.mode != 2) {
+        const int cbl = lane & (CB - 1);                   // codebook of step k: cbl ^ k
+        const int copy = lane / CB % COPIES;
+        const int pr = lane / (CB * COPIES) % PX;          // pair of step kp: kp ^ pr
+        unsigned sel[CD];                              // byte selectors: the codes in the order of the steps
+#pragma unroll
+        for (int v = 0; v < CD; ++v) {
+            sel[v] = 0u;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) sel[v] |= (unsigned)(cbl ^ (4 * v + j)) << (8 * j);
+        }
+        const unsigned lanepart = (unsigned)(copy * NP * CB + pr * CB + cbl) * 8u;
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            float eoff[G];
+#pragma unroll
+            for (int hh = 0; hh < G; ++hh) {
+                eoff[hh] = eoff_s[s * G + hh];
+                asm volatile("" : "+v"(eoff[hh]));     // (waited for here, not in the loop, where the wait would include the atomics)
+            }
+            unsigned lane_k[CB];
+#pragma unroll
+            for (int k = 0; k < CB; ++k) lane_k[k] = (unsigned)(s * SLOT) + (lanepart ^ (unsigned)(k * 8));
+            for (int t0 = sv0[s]; t0 < sv1[s]; t0 += DEPTH * NT) {
+#pragma unroll
+                for (int d = 0; d < DEPTH; ++d) {
+                    const int t = t0 + d * NT;
+                    if (t < sv1[s]) {
+                        float w[G];
+                        unsigned p[G], cw[CD];
+#pragma unroll
+                        for (int v = 0; v < CD; ++v) cw[v] = __builtin_amdgcn_perm(cnext[s][d][CD - 1], cnext[s][d][0], sel[v]);
+#pragma unroll
+                        for (int hh = 0; hh < G; ++hh) w[hh] = __builtin_amdgcn_exp2f(snext[s][d][hh] * kLog2e + eoff[hh]);
+                        round_up_half(w, p);
+                        if (S == 1 || t + DEPTH * NT < sv1[s]) fetch(s, d, t + DEPTH * NT);
+                        asm volatile("" ::: "memory");     // keeps the compiler from sinking the fetch below the atomics
+                        unsigned long long pp[NP];
+                        if (G == 1) {
+                            pp[0] = p[0];
+                        } else {
+#pragma unroll
+                            for (int hp = 0; hp < NP; ++hp) pp[hp] = (unsigned long long)p[(2 * hp) % G] | (unsigned long long)p[(2 * hp + 1) % G] << 32;
+                        }
+#pragma unroll
+                        for (int st = 1; st < PX; st *= 2) {  // pp[kp] <- pp[kp ^ pr]
+                            unsigned long long q[NP];
+#pragma unroll
+                            for (int hp = 0; hp < NP; ++hp) q[hp] = (pr & st) ? pp[hp ^ st] : pp[hp];
+#pragma unroll
+                            for (int hp = 0; hp < NP; ++hp) pp[hp] = q[hp];
+                        }
+                        if (t + tid < sv1[s]) {
+#pragma unroll
+                            for (int k = 0; k < CB; ++k) {
+                                const unsigned c = (cw[k / 4] >> (8 * (k % 4))) & 0xffu;
+                                const unsigned ad = ROWB == 256 ? __builtin_amdgcn_perm(cw[k / 4], lane_k[k], 0x03020000u | (unsigned)(4 + k % 4) << 8)
+                                                                : (c << 7) | lane_k[k];
+#pragma unroll
+                                for (int hp = 0; hp < NP; ++hp)
+                                    __hip_atomic_fetch_add(reinterpret_cast<lds_u64_ptr>((ad ^ (unsigned)(hp % PX * CB * 8)) + (unsigned)(hp / PX * PX * CB * 8)), pp[hp],
+                                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                            }
+                        }
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        if constexpr (COPIES > 1) {                        // the copies' sums, in copy 0 (no carry between the halves: their sums stay below 2^31)
+            constexpr int ROW = NP * CB;
+            for (int x = tid; x < S * kK * ROW; x += NT) {
+                unsigned long long *row = reinterpret_cast<unsigned long long *>(lds) + x / ROW * WORDS + x % ROW;
+                unsigned long long v = 0;
+#pragma unroll
+                for (int k = 0; k < COPIES; ++k) v += row[((k + x / ROW) & (COPIES - 1)) * ROW];  // (neighbouring rows on different banks)
+                row[0] = v;
+            }
+            __syncthreads();
+        }
+    }
+    if (a.mode != 0) {
+        constexpr int ROW = NP * CB;                   // words of a row without copies
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            if (sv0[s] >= sv1[s]) continue;
+            // (one head: its half of the words only)
+            const size_t first = ((((size_t)sb[s] * a.Hkv + g) * a.ranges + rng) * a.ncg + cg) * (size_t)(kK * ROW);
+            unsigned long long *mem = reinterpret_cast<unsigned long long *>(a.bins) + first, *own = reinterpret_cast<unsigned long long *>(lds + s * SLOT);
+            for (int x = tid; x < kK * ROW; x += NT) {
+                unsigned long long *row = own + x / ROW * WORDS + x % ROW;
+                if (a.mode == 1) {
+                    if (cs == 0 && G == 1) a.bins[first + x] = (unsigned)row[0];
+                    if (cs == 0 && G > 1) mem[x] = row[0];
+                } else {
+                    row[0] = G == 1 ? a.bins[first + x] : mem[x];
+                }
+            }
+        }
+        __syncthreads();
+    }
+
+    if (a.mode != 1) {
+        if constexpr (BF16) {
+            auto convert = [&](int s, int x, int ks) __attribute__((always_inline)) {
+                const int ln = fresh_lane(), hh = 4 * x + (ln & 3);
+                const unsigned dsh = (unsigned)(ln & 12) * 2u;  // the lane's digit of the weight
+                const unsigned char *at = lds + s * SLOT + (ks * (32 / CB) + (ln >> 4) * CL) * ROWB + (hh >> 1) * (CB * 8) + (hh & 1) * 4;
+                unsigned f[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const unsigned v = *reinterpret_cast<const unsigned *>(at + e / CB * ROWB + e % CB * 8);
+                    const float d = (float)((v >> dsh) & 0xffu);
+                    f[e] = __builtin_bit_cast(unsigned, G % 4 != 0 && hh >= G ? 0.f : d);
+                }
+                uint4_t w;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[e] = __builtin_amdgcn_perm(f[2 * e + 1], f[2 * e], 0x07060302u);
+                return __builtin_bit_cast(bf16x8_t, w);
+            };
+            __builtin_amdgcn_sched_barrier(0);
+            floatx4_t acc[S][NX][NCT];
+#pragma unroll
+            for (int s = 0; s < S; ++s)
+#pragma unroll
+                for (int x = 0; x < NX; ++x)
+#pragma unroll
+                    for (int t = 0; t < NCT; ++t) acc[s][x][t] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int j = 0; j < KS; ++j) {
+                if (RB == 2 && j + 1 < KS) load_rows(j + 1, R[(j + 1) % RB]);
+                bf16x8_t A[S][NX];
+#pragma unroll
+                for (int s = 0; s < S; ++s)
+#pragma unroll
+                    for (int x = 0; x < NX; ++x) {
+                        A[s][x] = convert(s, x, wave * KS + j);
+                        if (S * NX > 1) __builtin_amdgcn_sched_barrier(0);
+                    }
+#pragma unroll
+                for (int t = 0; t < NCT; ++t) {
+                    uint4_t w;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        w[e] = __builtin_amdgcn_perm(R[j % RB][2 * e + 1][t / 2], R[j % RB][2 * e][t / 2], t & 1 ? 0x07060302u : 0x05040100u);
+#pragma unroll
+                    for (int s = 0; s < S; ++s)
+#pragma unroll
+                        for (int x = 0; x < NX; ++x)
+                            acc[s][x][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[s][x], __builtin_bit_cast(bf16x8_t, w), acc[s][x][t], 0, 0, 0);
+                    if (S * NX > 1) __builtin_amdgcn_sched_barrier(0);
+                }
+                if (RB == 1 && j + 1 < KS) load_rows(j + 1, R[0]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            const int ln = fresh_lane(), n = ln & 15, kg = ln >> 4;
+            // digits combined: lane (n, kg) keeps head 4 x + kg of column NCT n + t
+            const float dscale = kg == 0 ? 1.f : kg == 1 ? 256.f : kg == 2 ? 65536.f : 16777216.f;
+            float sums[S][NX][NCT];
+#pragma unroll
+            for (int s = 0; s < S; ++s)
+#pragma unroll
+                for (int x = 0; x < NX; ++x)
+#pragma unroll
+                    for (int t = 0; t < NCT; ++t) {
+                        const floatx4_t v = acc[s][x][t] * dscale;
+                        sums[s][x][t] = swap16_add(swap32_add(v[0], v[2]), swap32_add(v[1], v[3]));
+                    }
+            __syncthreads();                           // the bins have been read
+#pragma unroll
+            for (int s = 0; s < S; ++s)
+#pragma unroll
+                for (int x = 0; x < NX; ++x)
+#pragma unroll
+                    for (int t = 0; t < NCT; ++t)
+                        if (4 * x + kg < G) red[((wave * S + s) * G + 4 * x + kg) * COLS + n * NCT + t] = sums[s][x][t];
+        } else {
+            // a lane takes four columns of every RPL-th row of the wavefront's share
+            constexpr int LPR = COLS / 4, RPL = 64 / LPR, NR = CB * kK / NW;
+            const int cl = lane % LPR, rl = lane / LPR;
+            const float *rows = static_cast<const float *>(a.val_cb) + ((size_t)g * a.M + (size_t)cg * CB) * (size_t)(kK * kD) + cs * COLS + 4 * cl;
+            float sum[G][4];
+#pragma unroll
+            for (int hh = 0; hh < G; ++hh)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sum[hh][e] = 0.f;
+#pragma unroll 8
+            for (int r = 0; r < NR / RPL; ++r) {
+                const int row = wave * NR + r * RPL + rl, cb = row / kK, code = row % kK;
+                typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+                const f4u c = *reinterpret_cast<const f4u *>(rows + (size_t)row * kD);
+                const unsigned char *at = lds + code * ROWB + cb * 8;
+#pragma unroll
+                for (int hh = 0; hh < G; ++hh) {
+                    const float w = (float)*reinterpret_cast<const unsigned *>(at + hh / 2 * (CB * 8) + (hh & 1) * 4);
+                    sum[hh][0] += w * c.x; sum[hh][1] += w * c.y; sum[hh][2] += w * c.z; sum[hh][3] += w * c.w;
+                }
+            }
+#pragma unroll
+            for (int m = LPR; m < 64; m *= 2)
+#pragma unroll
+                for (int hh = 0; hh < G; ++hh)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sum[hh][e] += __shfl_xor(sum[hh][e], m);
+            __syncthreads();                           // the bins have been read
+            if (rl == 0)
+#pragma unroll
+                for (int hh = 0; hh < G; ++hh)
+                    *reinterpret_cast<float4 *>(red + (wave * G + hh) * COLS + 4 * cl) = make_float4(sum[hh][0], sum[hh][1], sum[hh][2], sum[hh][3]);
+        }
+        __syncthreads();
+        // the wavefronts' sums
+        for (int o = tid; o < S * G * COLS; o += NT) {
+            const int s = o / (G * COLS), hh = o / COLS % G, col = o % COLS;
+            int b = 0, v0 = 0, v1 = 0;
+#pragma unroll
+            for (int k = 0; k < S; ++k)
+                if (s == k) { b = sb[k]; v0 = sv0[k]; v1 = sv1[k]; }
+            if (v0 >= v1) continue;
+            float sum = 0.f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) sum += red[w * (S * G * COLS) + o];
+            a.partial[((((size_t)b * a.Hq + (size_t)g * G + hh) * a.ranges + rng) * a.ncg + cg) * kD + cs * COLS + col] = sum * unit_s[s * G + hh];
+        }
+    }
+}
+
+}  // namespace
