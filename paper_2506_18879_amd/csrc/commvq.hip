@@ -1604,16 +1604,23 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_lut(const float *__rest
 // (Eq. def_center: per 2-D sub-space (x_a - y_b, y_a + x_b)), i.e. index form with 2R tied codebooks.
 constexpr int kPairK = 64;       // centres per level
 constexpr int kPairPlanes = 4;   // 8-element planes per LDS slice (4 slices cover the 16 planes of d = 128)
-constexpr int kPairBlock = kPairK * 256;  // bytes of one (plane, block of 16 levels): 64 rows x 16 pieces
+constexpr int kPairSet = kPairK * 256;    // bytes of a set of four levels: 64 rows x 16 pieces
+
+// Sets of four levels that the kernels work on: levels beyond key_levels are zeros (R = 11: 3 sets, R = 21: 6).
+inline int pair_sets(const commvq_config &c) { return c.key_levels <= 12 ? 3 : c.key_levels <= 16 ? 4 : 6; }
+// Bytes of a token's unpacked indices for each (type, half) below.
+constexpr int pair_lane_bytes(int sets) { return sets <= 4 ? 8 : 12; }
 
 // Packed 12-bit pairs -> one byte per index, in the order the score kernel wants.
 //   pairs : per (sequence, KV head) L records of PB = ceil(12 R / 8) bytes; pair r of a token is bits
 //           12 r .. 12 r + 11 of its record (little endian), a_r = low 6 bits, b_r = high 6 bits
-//   bytes : [token-unit][blk][t][16]: level 16 blk + col of type t (0 = a, 1 = b); 0 for levels >= R
+//   bytes : [token-unit][type: a | b][half][2 SETS bytes, padded to 8 or 12]: byte 2 s + st of token i is the index of level
+//           4 s + ((i / 64 + 2 half + st) mod 4); 0 for levels >= R
 // One workgroup = 256 consecutive tokens of one (sequence, KV head); their records are contiguous and
 // are staged through LDS with aligned dword loads.
+template <int SETS>
 __global__ __launch_bounds__(256) void k_unpack_pairs(const uint8_t *__restrict__ pairs, uint8_t *__restrict__ bytes,
-                                                      const int32_t *__restrict__ cu, int Hkv, int R, int PB, int NB)
+                                                      const int32_t *__restrict__ cu, int Hkv, int R, int PB)
 {
     __shared__ unsigned stage[256 * 32 / 4 + 12];  // a few dwords of slack: threads read 9 whole dwords each
     const int b = blockIdx.y / Hkv, g = blockIdx.y % Hkv;
@@ -1643,61 +1650,78 @@ __global__ __launch_bounds__(256) void k_unpack_pairs(const uint8_t *__restrict_
     for (int k = 0; k < 9; ++k) raw[k] = 4 * k < PB + 3 ? stage[(at >> 2) + k] : 0u;  // PB <= 32: 9 dwords cover any skew
 #pragma unroll
     for (int k = 0; k < 8; ++k) rec[k] = __builtin_amdgcn_alignbyte(raw[k + 1], raw[k], sh);
-    uint4 *dst = reinterpret_cast<uint4 *>(bytes + ((size_t)cu0 * Hkv + (size_t)g * L + i0 + threadIdx.x) * (32 * NB));
+    const unsigned rot = (unsigned)((i0 + (int)threadIdx.x) >> kLoBits) & 3u;
+    unsigned w[2][SETS];  // a set's four indices, rotated
 #pragma unroll
-    for (int blk = 0; blk < 2; ++blk) {
-        if (blk >= NB) break;
-        unsigned wa[4] = {0, 0, 0, 0}, wb[4] = {0, 0, 0, 0};
+    for (int s = 0; s < SETS; ++s) {
+        unsigned wa = 0u, wb = 0u;
 #pragma unroll
-        for (int col = 0; col < 16; ++col) {
-            const int r = 16 * blk + col;
+        for (int k = 0; k < 4; ++k) {
+            const int r = 4 * s + k;
             if (r < R && r < 21) {
                 const int bit = 12 * r;  // a pair never needs more than two dwords
-                const unsigned lo = rec[bit >> 5], hi = (bit >> 5) + 1 < 8 ? rec[(bit >> 5) + 1] : 0u;
-                const unsigned pr = __builtin_amdgcn_alignbit(hi, lo, (unsigned)(bit & 31)) & 0xfffu;
-                wa[col >> 2] |= (pr & 63u) << (8 * (col & 3));
-                wb[col >> 2] |= (pr >> 6) << (8 * (col & 3));
+                const unsigned lo32 = rec[bit >> 5], hi32 = (bit >> 5) + 1 < 8 ? rec[(bit >> 5) + 1] : 0u;
+                const unsigned pr = __builtin_amdgcn_alignbit(hi32, lo32, (unsigned)(bit & 31)) & 0xfffu;
+                wa |= (pr & 63u) << (8 * k);
+                wb |= (pr >> 6) << (8 * k);
             }
         }
-        dst[2 * blk] = make_uint4(wa[0], wa[1], wa[2], wa[3]);
-        dst[2 * blk + 1] = make_uint4(wb[0], wb[1], wb[2], wb[3]);
+        w[0][s] = __builtin_amdgcn_alignbyte(wa, wa, rot);
+        w[1][s] = __builtin_amdgcn_alignbyte(wb, wb, rot);
     }
+    constexpr int LD = pair_lane_bytes(SETS) / 4;
+    unsigned out[4 * LD];
+#pragma unroll
+    for (int type = 0; type < 2; ++type)
+#pragma unroll
+        for (int half = 0; half < 2; ++half)
+#pragma unroll
+            for (int k = 0; k < LD; ++k)
+                out[(2 * type + half) * LD + k] = 2 * k >= SETS ? 0u
+                    : __builtin_amdgcn_perm(2 * k + 1 < SETS ? w[type][(2 * k + 1) % SETS] : 0u, w[type][2 * k % SETS], half ? 0x07060302u : 0x05040100u);
+    uint4 *dst = reinterpret_cast<uint4 *>(bytes + ((size_t)cu0 * Hkv + (size_t)g * L + i0 + threadIdx.x) * (16 * LD));
+#pragma unroll
+    for (int k = 0; k < LD; ++k) dst[k] = make_uint4(out[4 * k], out[4 * k + 1], out[4 * k + 2], out[4 * k + 3]);
 }
 
 // Tied table [Hkv][R][64][d] bf16 -> LDS images for k_score_pair:
-//   packed[g][slice][plane][blk][c][col] 16-byte pieces = elements 8 (4 slice + plane) .. +7 of centre c of
-//   level 16 blk + col (zeros for levels >= R).  One thread per piece of the output.
+//   packed[g][slice][set][c][4 plane + k] 16-byte pieces = elements 8 (4 slice + plane) .. +7 of centre c of
+//   level 4 set + k (zeros for levels >= R).  One thread per piece of the output.
 __global__ __launch_bounds__(256) void k_prep_pairs(const uint4 *__restrict__ table, uint4 *__restrict__ packed, int Hkv,
-                                                    int R, int NB)
+                                                    int R, int sets)
 {
-    const size_t n = (size_t)Hkv * 16 * NB * kPairK * 16;
+    const size_t n = (size_t)Hkv * 4 * sets * kPairK * 16;
     const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (t >= n) return;
     const int col = (int)(t & 15);
     const int c = (int)((t >> 4) % kPairK);
     size_t rest = (t >> 4) / kPairK;
-    const int blk = (int)(rest % NB);
-    rest /= NB;
-    const int plane16 = (int)(rest % 16);  // 4 slice + plane
-    const int g = (int)(rest / 16);
-    const int r = 16 * blk + col;
+    const int set = (int)(rest % sets);
+    rest /= sets;
+    const int slice = (int)(rest % 4), g = (int)(rest / 4);
+    const int r = 4 * set + (col & 3);
     uint4 v = make_uint4(0, 0, 0, 0);
-    if (r < R) v = table[(((size_t)g * R + r) * kPairK + c) * 16 + plane16];
+    if (r < R) v = table[(((size_t)g * R + r) * kPairK + c) * 16 + 4 * slice + (col >> 2)];
     packed[t] = v;
 }
 
 // Score kernel for paired-code keys: same scheme as k_score_stream (codebook streamed through LDS in
 // slices, gather-sum and query product on the matrix cores), with
-//   * a slice = 4 planes of 8 elements of every centre of every level (NB blocks of 16 levels, one
-//     bank column per level, 64 rows = centre index): 64 KiB (R <= 16) or 128 KiB (R <= 32);
-//   * k-groups = (a | b) x (levels 8h .. 8h + 7): lane (n, g) gathers the centres that the a (g < 2) or
-//     b (g >= 2) indices of token n select in levels 8 (g & 1) + (n + step) mod 8 of every block;
+//   * a slice = 4 planes of 8 elements of every centre of every level, SETS sets of four levels: a set is 64 rows (centre
+//     index) of 16 bank columns, 4 of them per plane;
+//   * the four lanes of a token are (a | b) x half: in step (s, st) of a plane lane (n, g) gathers the centre that
+//     the a (g < 2) or b (g >= 2) index of token n selects in level 4 s + (n + 2 (g & 1) + st) mod 4;
+//   * lanes n with the same n / 4 = j work on plane i ^ j in round i.  The 16 lanes that a 16-byte read checks against each other
+//     are four such quads with four different j (0..3, 12..15, 20..23, 24..27 of every 32 lanes, and the other 16): four planes
+//     x four levels, 16 bank columns whatever the indices.  So only the sets that hold levels are read, 2 SETS pieces per
+//     lane and plane, where a column per level for one plane at a time needs all 16: 128K tokens, R = 11, 98.5 -> 91.9 us
+//     (whole call with binary values 144.4 -> 138.1);
 //   * a selection matrix that routes the a-sum and the b-sum of sub-space g of the plane to rows
 //     4g .. 4g + 3, so that lane (n, g) receives (SA_x, SA_y, SB_x, SB_y) and forms the decoded block
 //     (SA_x - SB_y, SA_y + SB_x) of Eq. def_center locally;
 //   * one cross-lane head total per slice: the 4x4x1 query MFMAs of the slice's 4 planes chain into
-//     one accumulator before the row / half swaps.
-template <int NB, int G, int TPT>
+//     one accumulator before the row / half swaps (the 4 lanes of a block share the plane).
+template <int SETS, int G, int TPT>
 __global__ __launch_bounds__(kSliceThreads) void k_score_pair(
     const void *__restrict__ q, const uint8_t *__restrict__ codes_all, const uint4 *__restrict__ packed,
     const int32_t *__restrict__ cu, const int32_t *__restrict__ q_pos, const float2 *__restrict__ tbl_hi,
@@ -1705,17 +1729,17 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_pair(
 {
     constexpr int PL = kPairPlanes;
     constexpr int S = 16 / PL;
-    constexpr int CB = 32 * NB;                      // code bytes per token
-    constexpr int SLICE = PL * NB * kPairBlock;      // LDS bytes of one slice
+    constexpr int LB = pair_lane_bytes(SETS), CB = 4 * LB;  // index bytes per lane and per token
+    constexpr int SLICE = SETS * kPairSet;           // LDS bytes of one slice
     constexpr int TILE = TPT * kSliceThreads;
     constexpr int NW = kSliceThreads / 64;
     constexpr int NPASS = TILE / (16 * NW);
     constexpr int NHR = TILE / kLo + 1;
     constexpr int NGRP = (G + 3) / 4;
     constexpr int PARTS = 8;                          // (sub-space of a plane) x (planes 0,1 | 2,3)
-    constexpr int HROW = 12;                          // 16-byte entries per coarse phase row (8 used: conflict-free reads)
+    constexpr int HROW = 20;                          // 16-byte entries per coarse phase row (16 used: conflict-free reads)
     static_assert(NPASS % 2 == 0, "code double-buffer parity assumes an even number of passes");
-    extern __shared__ __attribute__((aligned(16))) uint4 tab[];  // [PL][NB][64][16] pieces, then the phase factors
+    extern __shared__ __attribute__((aligned(16))) uint4 tab[];  // [SETS][64][16] pieces, then the phase factors
     float4 *elo = reinterpret_cast<float4 *>(reinterpret_cast<char *>(tab) + SLICE);  // [PARTS][64]
     float4 *ehi = elo + PARTS * kLo;                                                   // [NHR][HROW]
     float2(*wstat)[G] = reinterpret_cast<float2(*)[G]>(ehi + HROW * NHR);             // [NW][G]
@@ -1733,7 +1757,8 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_pair(
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = lane & 15, gk = lane >> 4;
     const int type = gk >> 1;                         // 0: the a indices, 1: the b indices
-    const int half = gk & 1;                          // levels 8 half .. 8 half + 7 of every block
+    const int half = gk & 1;                          // two of the four levels of every set
+    const int j = n >> 2;                             // the lane works on plane i ^ j in round i
     const int qpos = q_pos[b];
     const uint8_t *codes = codes_all + ((size_t)cu0 * a.Hkv + (size_t)g * L) * CB;
     const uint4 *src = packed + (size_t)g * S * (SLICE / 16);
@@ -1767,54 +1792,42 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_pair(
 #pragma unroll
         for (int x = 0; x < NGRP; ++x) sc[p][x] = 0.f;
 
-    // xreg[st]: byte 0 = 16 * bank column (= level within the block) read at step st, byte 2 = 0, byte 3 = 1;
+    // xreg[i][st]: byte 0 = 16 * bank column read in round i, step st, byte 2 = 0, byte 3 = 1;
     // a byte permute splices the centre index in as byte 1: address = 256 c + 16 col (+ 65536 via byte 3)
-    unsigned xreg[8];
+    unsigned xreg[PL][2];
 #pragma unroll
-    for (int st = 0; st < 8; ++st) xreg[st] = (unsigned)(8 * half + ((n + st) & 7)) * 16u | 1u << 24;
-    unsigned rsel_lo = 0u, rsel_hi = 0u;
+    for (int i = 0; i < PL; ++i)
 #pragma unroll
-    for (int x = 0; x < 4; ++x) {
-        rsel_lo |= (unsigned)((x + n) & 7) << (8 * x);
-        rsel_hi |= (unsigned)((x + 4 + n) & 7) << (8 * x);
-    }
+        for (int st = 0; st < 2; ++st) xreg[i][st] = (unsigned)(4 * (i ^ j) + ((n + 2 * half + st) & 3)) * 16u | 1u << 24;
 
     // Token mapping as in k_score_stream (M = 16): lane n of a wavefront's 16 token lanes takes fine position
     // 4 wave + n / 4 and coarse row n % 4 of the pass's block of four rows, so the lanes of a 4-lane block and all
     // passes of a lane are whole coarse rows apart and share the fine phase factor, which is folded into the query.
     int tb = t0 + 4 * wave + (n >> 2) + kLo * (n & 3);
     constexpr int PSTRIDE = 4 * kLo;
-    unsigned cw[2][2 * NB];
-    auto fetch_codes = [&](int p, unsigned(&dst)[2 * NB]) {
+    constexpr int CD = LB / 4;
+    unsigned cw[2][CD];
+    auto fetch_codes = [&](int p, unsigned(&dst)[CD]) {
         const int tok = min(tb + p * PSTRIDE, L - 1);
-#pragma unroll
-        for (int v = 0; v < NB; ++v) {  // bytes 32 v + 16 type + 8 half .. + 7 of the token's indices
-            const uint2_t c2 = __builtin_amdgcn_raw_buffer_load_b64(cd_rs, (unsigned)tok * CB + 32u * v + 16u * type + 8u * half, 0, 0);
-            dst[2 * v + 0] = c2[0]; dst[2 * v + 1] = c2[1];
-        }
-    };
-    // rotated index bytes of a pass: what its gather addresses are made from
-    auto make_cc = [&](const unsigned(&c)[2 * NB], unsigned(&cc)[2 * NB]) {
-#pragma unroll
-        for (int v = 0; v < NB; ++v) {
-            cc[2 * v + 0] = __builtin_amdgcn_perm(c[2 * v + 1], c[2 * v], rsel_lo);
-            cc[2 * v + 1] = __builtin_amdgcn_perm(c[2 * v + 1], c[2 * v], rsel_hi);
-        }
+        const unsigned at = (unsigned)tok * CB + (unsigned)(gk * LB);
+        const uint2_t c2 = __builtin_amdgcn_raw_buffer_load_b64(cd_rs, at, 0, 0);
+        dst[0] = c2[0]; dst[1] = c2[1];
+        if constexpr (CD == 3) dst[2] = __builtin_amdgcn_raw_buffer_load_b32(cd_rs, at + 8u, 0, 0);
     };
     fetch_codes(0, cw[0]);
     const int hmin = (qpos - (t0 + TILE - 1)) >> kLoBits;
     const unsigned elo_base = (unsigned)SLICE + (unsigned)(2 * gk) * (kLo * 16u);
-    const unsigned ehi_base = (unsigned)SLICE + (unsigned)(PARTS * kLo) * 16u + (unsigned)gk * 16u;
+    const unsigned ehi_base = (unsigned)SLICE + (unsigned)(PARTS * kLo) * 16u + (unsigned)(4 * gk + j) * 16u;
 
     for (int sl = 0; sl < S; ++sl) {
-        // queries of this slice (head 4 grp + n % 4, sub-space gk of each of the 4 planes): requested ahead of the
+        // queries of this slice (head 4 grp + n % 4, sub-space gk of the plane of each round): requested ahead of the
         // slice itself, so that they have arrived when the first pass needs them
         uint2_t qraw[NGRP][PL];
 #pragma unroll
         for (int x = 0; x < NGRP; ++x)
 #pragma unroll
             for (int pl = 0; pl < PL; ++pl) {
-                const unsigned off = (unsigned)(4 * x + (n & 3)) * kD + 2u * (unsigned)(16 * sl + 4 * pl + gk);  // elements
+                const unsigned off = (unsigned)(4 * x + (n & 3)) * kD + 2u * (unsigned)(16 * sl + 4 * (pl ^ j) + gk);  // elements
                 if (a.q_bf16) {
                     qraw[x][pl][0] = __builtin_amdgcn_raw_buffer_load_b32(q_rs, off * 2u, 0, 0);
                     qraw[x][pl][1] = 0u;
@@ -1830,9 +1843,10 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_pair(
 #pragma unroll
             for (int x = 0; x < PPT; ++x) tab[x * kSliceThreads + tid] = stage[x];
         }
-        // phase factors of this slice's 16 sub-spaces: an entry (s, h) holds sub-space s of planes 2h and 2h + 1;
-        // fine table [2 s + h][64 positions], coarse table [row][4 h + s] (rows padded to 12 entries, so that the four
-        // rows x four sub-spaces that the lanes of a read touch are 16 different 16-byte bank groups)
+        // phase factors of this slice's 16 sub-spaces: a fine entry (s, h) holds sub-space s of planes 2h and 2h + 1, table
+        // [2 s + h][64 positions]; a coarse entry (s, h, v) the same, in the other order for v = 1, table [row][4 s + 2 h + v]: the
+        // lane's planes in the order of its rounds.  In the 16 lanes of a read the four quads have four different 2 h + v, and
+        // the four rows of a quad are 4 entries apart (mod 16): 16 different 16-byte bank groups
         if (tid < PARTS * kLo) {
             const int part = tid / kLo, lo = tid % kLo;
             const int j0 = 16 * sl + 8 * (part & 1) + (part >> 1);
@@ -1840,12 +1854,14 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_pair(
             elo[tid] = make_float4(e0.x, e0.y, e1.x, e1.y);
         }
         for (int x = tid; x < PARTS * NHR; x += kSliceThreads) {
-            const int c = x % PARTS, H = hmin + x / PARTS;
+            const int c = x % PARTS, H = hmin + x / PARTS;  // c = 2 s + h
             const int hi = min(H < 0 ? -H : H, a.n_hi - 1);
-            const int j0 = 16 * sl + 8 * (c >> 2) + (c & 3);
+            const int j0 = 16 * sl + 8 * (c & 1) + (c >> 1);
             const float2 e0 = tbl_hi[(size_t)hi * kJ + j0], e1 = tbl_hi[(size_t)hi * kJ + j0 + 4];
             const float sg = H < 0 ? -1.f : 1.f;
-            ehi[(x / PARTS) * HROW + c] = make_float4(e0.x, sg * e0.y, e1.x, sg * e1.y);
+            float4 *dst = ehi + (x / PARTS) * HROW + 2 * c;
+            dst[0] = make_float4(e0.x, sg * e0.y, e1.x, sg * e1.y);
+            dst[1] = make_float4(e1.x, sg * e1.y, e0.x, sg * e0.y);
         }
         __syncthreads();
         asm volatile("" : "+v"(tb));
@@ -1856,7 +1872,11 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_pair(
         {
             uint4_t elr[2];
 #pragma unroll
-            for (int h = 0; h < 2; ++h) elr[h] = lds_read_b128(elo_base + (unsigned)(dist16 & ((kLo - 1) * 16)) + (unsigned)(h * (kLo * 16)));
+            for (int h = 0; h < 2; ++h) {
+                const uint4_t e = lds_read_b128(elo_base + (unsigned)(dist16 & ((kLo - 1) * 16)) + (unsigned)((h ^ (j >> 1)) * (kLo * 16)));
+#pragma unroll
+                for (int k = 0; k < 4; ++k) elr[h][k] = j & 1 ? e[k ^ 2] : e[k];
+            }
 #pragma unroll
             for (int x = 0; x < NGRP; ++x)
 #pragma unroll
@@ -1876,27 +1896,25 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_pair(
         }
         // coarse phase row of the lane's token of the LAST pass; a pass is a whole number of rows further on
         const unsigned ehi_last = ehi_base + (unsigned)(((dist16 >> (kLoBits + 4)) - hmin - (NPASS - 1) * (PSTRIDE / kLo)) * (16 * HROW));
-        // Gather: 8 NB pieces per lane and plane, in groups of RG reads; the groups of all planes of a pass form one
-        // sequence, and a group's reads are issued before the matrix instructions of the group before it -- across
-        // planes and passes, so that the first reads of the next plane (pass) travel while this one is rotated and
-        // contracted with the queries.
-        constexpr int NS = 8 * NB, RG = (NB == 2 || G == 8) ? 2 : 4, NG = NS / RG, NFLAT = PL * NG;  // fewer reads in flight where registers are short
-        static_assert(NFLAT % 2 == 0, "read buffers alternate across passes");
-        uint4_t v[2][RG];
-        auto issue = [&](int flat, const unsigned(&cc)[2 * NB], uint4_t(&dst)[RG]) {
-            const int pl = flat / NG, grp = flat % NG;
+        // Gather: 2 SETS pieces per lane and plane, two reads (one matrix instruction) at a time; the reads of all planes of a pass form
+        // one sequence of which NBUF - 1 to NBUF steps are in flight -- across planes and passes, so that the first reads of
+        // the next plane (pass) travel while this one is rotated and contracted with the queries.
+        constexpr int NFLAT = PL * SETS, NBUF = SETS == 4 ? (G == 8 ? 2 : 4) : G == 8 ? 2 : 3;  // fewer where registers are short
+        static_assert(NFLAT % NBUF == 0, "read buffers alternate across passes");
+        uint4_t v[NBUF][2];
+        auto issue = [&](int flat, const unsigned(&cc)[CD], uint4_t(&dst)[2]) {
+            const int i = flat / SETS, set = flat % SETS;
 #pragma unroll
-            for (int r = 0; r < RG; ++r) {
-                const int st = grp * RG + r;       // level 16 (st / 8) + 8 half + (n + st) mod 8
-                const int idx = pl * NB + st / 8;  // (plane, block) image of 16 KiB
-                const unsigned selb = 0x0c000000u | (unsigned)(2 + idx / 4) << 16 | (unsigned)(4 + st % 4) << 8;
-                const unsigned addr = __builtin_amdgcn_perm(cc[st / 4], xreg[st % 8], selb);
-                dst[r] = lds_read_b128((unsigned)((idx % 4) * kPairBlock) + addr);
+            for (int st = 0; st < 2; ++st) {
+                const int byte = 2 * set + st;
+                const unsigned selb = 0x0c000000u | (unsigned)(2 + set / 4) << 16 | (unsigned)(4 + byte % 4) << 8;
+                const unsigned addr = __builtin_amdgcn_perm(cc[byte / 4], xreg[i][st], selb);
+                dst[st] = lds_read_b128((unsigned)((set % 4) * kPairSet) + addr);
             }
         };
-        unsigned cc[2 * NB];
-        make_cc(cw[0], cc);  // (the last pass of the previous slice requested the codes of pass 0 again)
-        issue(0, cc, v[0]);
+        // (the last pass of the previous slice requested the codes of pass 0 again)
+#pragma unroll
+        for (int f = 0; f < NBUF - 1; ++f) issue(f, cw[0], v[f]);
 #pragma unroll
         for (int p = 0; p < NPASS; ++p) {
             __builtin_amdgcn_sched_barrier(0);  // one pass at a time: keeps register pressure flat
@@ -1904,9 +1922,8 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_pair(
             uint4_t ehr[2];
 #pragma unroll
             for (int h = 0; h < 2; ++h)
-                ehr[h] = lds_read_b128(ehi_last + (unsigned)((NPASS - 1 - p) * (PSTRIDE / kLo) * (16 * HROW) + h * 64));
+                ehr[h] = lds_read_b128((ehi_last ^ (unsigned)(h * 32)) + (unsigned)((NPASS - 1 - p) * (PSTRIDE / kLo) * (16 * HROW)));
             __builtin_amdgcn_sched_barrier(0);
-            unsigned ccn[2 * NB];
             floatx4_t t[NGRP];
 #pragma unroll
             for (int x = 0; x < NGRP; ++x) t[x] = floatx4_t{0.f, 0.f, 0.f, 0.f};
@@ -1915,21 +1932,14 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_pair(
                 // 1. gather-sum of the plane
                 floatx4_t acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int grp = 0; grp < NG; ++grp) {
-                    const int flat = pl * NG + grp;
-                    if (flat + 1 < NFLAT) {
-                        issue(flat + 1, cc, v[(flat + 1) & 1]);
-                    } else if (p + 1 < NPASS) {
-                        make_cc(cw[(p + 1) & 1], ccn);
-                        issue(0, ccn, v[(flat + 1) & 1]);
-                    }
+                for (int set = 0; set < SETS; ++set) {
+                    const int flat = pl * SETS + set, next = flat + NBUF - 1;
+                    if (next < NFLAT) issue(next, cw[p & 1], v[next % NBUF]);
+                    else issue(next - NFLAT, cw[(p + 1) & 1], v[next % NBUF]);  // (after the last pass: of pass 0 in this slice, not used)
                     __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int r = 0; r < RG; r += 2) {
-                        const uint4_t pa = v[flat & 1][r], pb = v[flat & 1][r + 1];
-                        const uint8v_t both = {pa[0], pa[1], pa[2], pa[3], pb[0], pb[1], pb[2], pb[3]};
-                        acc = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(selv, __builtin_bit_cast(bf16x16_t, both), acc, (int)sidx, 0, 0);
-                    }
+                    const uint4_t pa = v[flat % NBUF][0], pb = v[flat % NBUF][1];
+                    const uint8v_t both = {pa[0], pa[1], pa[2], pa[3], pb[0], pb[1], pb[2], pb[3]};
+                    acc = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(selv, __builtin_bit_cast(bf16x16_t, both), acc, (int)sidx, 0, 0);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 // 2. decoded block of sub-space gk (Eq. def_center), rotated by the coarse phase factor
@@ -1948,10 +1958,6 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_pair(
             // totals over the 4 lanes of the token: lane (n, gk) keeps head 4 grp + gk
 #pragma unroll
             for (int x = 0; x < NGRP; ++x) sc[p][x] += swap16_add(swap32_add(t[x][0], t[x][2]), swap32_add(t[x][1], t[x][3]));
-            if (p + 1 < NPASS) {
-#pragma unroll
-                for (int i = 0; i < 2 * NB; ++i) cc[i] = ccn[i];
-            }
         }
     }
 
@@ -2419,38 +2425,38 @@ hipError_t launch_stream(const StreamArgs &a, int M, int passes, int grid, hipSt
     return a.d.G == 8 ? launch_stream_g<32, 2>(a, passes, grid, s) : launch_stream_g<32, 1>(a, passes, grid, s);
 }
 
-template <int NB, int G, int TPT>
+template <int SETS, int G, int TPT>
 hipError_t launch_pair_bgt(const SliceArgs &a, int grid, hipStream_t s)
 {
     constexpr int tile = TPT * kSliceThreads;
-    // slice + fine phase factors + coarse rows (12 entries each) + per-wavefront statistics; the write-out stages four
+    // slice + fine phase factors + coarse rows (20 entries each) + per-wavefront statistics; the write-out stages four
     // heads of the tile's logits, [64 positions padded to 68] per coarse row, over the slice and the phase factors
-    constexpr int work = kPairPlanes * NB * kPairBlock + 8 * kLo * 16 + 12 * (tile / kLo + 1) * 16;
+    constexpr int work = SETS * kPairSet + 8 * kLo * 16 + 20 * (tile / kLo + 1) * 16;
     constexpr int stg = 4 * ((tile / kLo) * 68 + 16) * 4;
     constexpr int lds = (work > stg ? work : stg) + kStatBytes;
     static std::atomic<uint64_t> lds_ok{0};  // per instantiation and device
-    if (hipError_t e = allow_dynamic_lds(&k_score_pair<NB, G, TPT>, lds, lds_ok); e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_score_pair<NB, G, TPT>), dim3(grid), dim3(kSliceThreads), lds, s, a.q, a.key_codes, a.packed,
+    if (hipError_t e = allow_dynamic_lds(&k_score_pair<SETS, G, TPT>, lds, lds_ok); e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_score_pair<SETS, G, TPT>), dim3(grid), dim3(kSliceThreads), lds, s, a.q, a.key_codes, a.packed,
                        a.cu, a.q_pos, a.tbl_hi, a.tbl_lo, a.scores, a.sstat, a.d);
     return hipGetLastError();
 }
-template <int NB, int G>
+template <int SETS, int G>
 hipError_t launch_pair_bg(const SliceArgs &a, int tpt, int grid, hipStream_t s)
 {
     switch (tpt) {
-    case 1: return launch_pair_bgt<NB, G, 1>(a, grid, s);
-    case 2: return launch_pair_bgt<NB, G, 2>(a, grid, s);
-    default: return launch_pair_bgt<NB, G, 4>(a, grid, s);
+    case 1: return launch_pair_bgt<SETS, G, 1>(a, grid, s);
+    case 2: return launch_pair_bgt<SETS, G, 2>(a, grid, s);
+    default: return launch_pair_bgt<SETS, G, 4>(a, grid, s);
     }
 }
-template <int NB>
+template <int SETS>
 hipError_t launch_pair_b(const SliceArgs &a, int G, int tpt, int grid, hipStream_t s)
 {
     switch (G) {
-    case 1: return launch_pair_bg<NB, 1>(a, tpt, grid, s);
-    case 2: return launch_pair_bg<NB, 2>(a, tpt, grid, s);
-    case 4: return launch_pair_bg<NB, 4>(a, tpt, grid, s);
-    default: return launch_pair_bg<NB, 8>(a, tpt, grid, s);
+    case 1: return launch_pair_bg<SETS, 1>(a, tpt, grid, s);
+    case 2: return launch_pair_bg<SETS, 2>(a, tpt, grid, s);
+    case 4: return launch_pair_bg<SETS, 4>(a, tpt, grid, s);
+    default: return launch_pair_bg<SETS, 8>(a, tpt, grid, s);
     }
 }
 
@@ -2460,7 +2466,7 @@ hipError_t launch_prep(const commvq_config &c, const void *key_cb, uint4 *packed
     const size_t n_pieces = packed_key_bytes(c) / 16;
     if (pair_keys(c))
         hipLaunchKernelGGL(k_prep_pairs, dim3((unsigned)((n_pieces + 255) / 256)), dim3(256), 0, s,
-                           static_cast<const uint4 *>(key_cb), packed, c.n_kv_heads, c.key_levels, pair_blocks(c));
+                           static_cast<const uint4 *>(key_cb), packed, c.n_kv_heads, c.key_levels, pair_sets(c));
     else
         hipLaunchKernelGGL(k_prep, dim3((unsigned)((n_pieces + 255) / 256)), dim3(256), 0, s,
                            static_cast<const uint4 *>(key_cb), packed, c.n_kv_heads, c.m_key);
@@ -2548,12 +2554,14 @@ commvq_status run_scores(commvq_handle *h, const void *q, const uint8_t *key_cod
             const int grid = pos->batch * c.n_kv_heads * plan.score_splits;
             const int tpt = plan.score_split_len / kSliceThreads;
             // 12-bit pairs -> one byte per index, then the paired-code score kernel
-            hipLaunchKernelGGL(k_unpack_pairs, dim3((unsigned)((pos->max_seqlen + 255) / 256), (unsigned)(pos->batch * c.n_kv_heads)),
-                               dim3(256), 0, s, key_codes, w.pair_bytes, pos->cu_seqlens, c.n_kv_heads, c.key_levels,
-                               pair_record_bytes(c), pair_blocks(c));
+            const dim3 blocks((unsigned)((pos->max_seqlen + 255) / 256), (unsigned)(pos->batch * c.n_kv_heads));
+            const int sets = pair_sets(c), rec = pair_record_bytes(c);
+            if (sets == 3) hipLaunchKernelGGL(k_unpack_pairs<3>, blocks, dim3(256), 0, s, key_codes, w.pair_bytes, pos->cu_seqlens, c.n_kv_heads, c.key_levels, rec);
+            else if (sets == 4) hipLaunchKernelGGL(k_unpack_pairs<4>, blocks, dim3(256), 0, s, key_codes, w.pair_bytes, pos->cu_seqlens, c.n_kv_heads, c.key_levels, rec);
+            else hipLaunchKernelGGL(k_unpack_pairs<6>, blocks, dim3(256), 0, s, key_codes, w.pair_bytes, pos->cu_seqlens, c.n_kv_heads, c.key_levels, rec);
             if (hipGetLastError() != hipSuccess) return COMMVQ_ERR_LAUNCH;
             sa.key_codes = w.pair_bytes;
-            e = pair_blocks(c) == 1 ? launch_pair_b<1>(sa, h->G, tpt, grid, s) : launch_pair_b<2>(sa, h->G, tpt, grid, s);
+            e = sets == 3 ? launch_pair_b<3>(sa, h->G, tpt, grid, s) : sets == 4 ? launch_pair_b<4>(sa, h->G, tpt, grid, s) : launch_pair_b<6>(sa, h->G, tpt, grid, s);
         } else {
             const StreamShape &ss = plan.stream;
             StreamArgs sa;

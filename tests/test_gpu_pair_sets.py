@@ -1,0 +1,33 @@
+"""Paired keys at the numbers of levels where the score kernel's sets of four levels begin and end, with contexts around its passes and
+tiles and of several sequences: logits and outputs against the oracle as in test_gpu_parity.py."""
+import numpy as np
+import pytest
+
+from paper_2506_18879_amd import synth
+
+from test_gpu_parity import TOL_SCORE, assert_rows, gpu  # noqa: F401  (gpu: fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("R,G,lens", [(1, 4, [700]), (4, 8, [513, 1]), (5, 4, [511, 0, 64, 63]), (12, 4, [1024, 2049]), (12, 8, [4095]), (13, 4, [300, 65]),
+                                      (15, 2, [600]), (16, 4, [4100, 7]), (17, 8, [900, 130]), (20, 4, [1537]), (21, 8, [2500, 511, 0, 1024]),
+                                      (21, 4, [97] * 9), (11, 4, [700, 40, 2100, 0, 333, 512, 1])])
+def test_levels_around_sets(gpu, oracle, R, G, lens):  # noqa: F811
+    import torch
+    w = synth.make_pair_workload(f"sets_R{R}_{len(lens)}", B=len(lens), Hq=2 * G, Hkv=2, seqlens=lens, R=R, Mv=16, seed=40 + R + len(lens))
+    dw, op = gpu.DeviceWorkload(w), gpu.DecodeAttention(w)
+    op.workspace.fill_(0xFF)
+    s = op.scores(dw)
+    out = op(dw)
+    torch.cuda.synchronize()
+    keep = [i for i, n in enumerate(lens) if n > 0]        # (the oracle rejects empty sequences; their rows are zeros)
+    kc = oracle.paired_as_indexed(w.key_codes, w.key_levels, w.cu_seqlens, w.Hkv)
+    cu = np.concatenate([[0], np.cumsum([lens[i] for i in keep])]).astype(np.int32)
+    ref, ref_scores, _ = oracle.decode_attn(w.as_f64("q")[keep], kc, w.val_codes, oracle.tied_table_as_codebooks(w.as_f64("key_codebooks"), K=w.K),
+                                            w.as_f64("val_codebooks"), cu, w.q_pos[keep], rope_base=w.rope_base, n_threads=16, return_intermediates=True)
+    assert np.abs(s.cpu().numpy().astype(np.float64) - ref_scores).max() <= TOL_SCORE
+    got = out.cpu().numpy()
+    assert_rows(got[keep], ref, w.name)
+    assert not np.delete(got, keep, axis=0).any()
+    op.close()
