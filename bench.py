@@ -378,25 +378,26 @@ def main():
                       if traffic is not None else None)
     key_stream_gbs = w.key_codes.nbytes / score_s / 1e9 if score_s > 0 else 0.0
     # the pipes the kernel actually loads: codeword pieces gathered from LDS, and the matrix instructions that
-    # sum them: 256 issued flop per 16-byte piece (mostly multiplications by zero), as one dense 16x16x32 bf16 MFMA
-    # per 64 pieces (paired keys) or one structured-sparse 16x16x64 per 128 (index form; twice the dense rate)
-    gather_bytes = units * w.Mk * w.d * esz
+    # sum them: 256 issued flop per 16-byte piece (mostly multiplications by zero), one structured-sparse 16x16x64 per 128 pieces (twice
+    # the dense rate).  Paired keys: a and b of the levels rounded up to whole sets of four (12, 16 or 24)
+    pieces = 2 * (12 if w.key_levels <= 12 else 16 if w.key_levels <= 16 else 24) if paired else w.Mk
+    gather_bytes = units * pieces * w.d * esz
     gather_tbs = gather_bytes / score_s / 1e12 if score_s > 0 else 0.0
     mfma_tflops = (gather_bytes / 16 / 64 * 16384) / score_s / 1e12 if (score_s > 0 and w.dtype == "bf16") else 0.0
-    mfma_peak = MFMA_BF16_PEAK_TFLOPS if paired else 2.0 * MFMA_BF16_PEAK_TFLOPS
+    mfma_peak = 2.0 * MFMA_BF16_PEAK_TFLOPS
     roofline = {"kernel": kname, "bound": "alu", "achieved": round(achieved_tflops, 3), "peak": FP32_PEAK_TFLOPS,
                 "unit": "TFLOP/s", "frac": round(achieved_tflops / FP32_PEAK_TFLOPS, 4), "traffic": traffic,
                 "traffic_source": traffic_source,
                 "kernel_ms": round(stage_ms[0], 5), "launches_averaged": n_prof,
                 "launches_sampled": ("every call of a separate eager run" if args.graph else
                                      f"every {args.stage_event_interval}th call of the timed region"),
-                "timed_region_includes": ("index unpacking (k_unpack_pairs) + k_score_pair" if paired else
+                "timed_region_includes": ("k_score_pair + k_score_combine" if paired and op.plan.score_slice_groups > 1 else "k_score_pair" if paired else
                                           "k_score_stream + k_score_combine" if prepacked and op.plan.score_slice_groups > 1 else
                                           "k_score_stream only" if prepacked else "codebook re-layout (k_prep) + score kernel"),
                 "lds_gather_view": {"codeword_bytes_TBs": round(gather_tbs, 2), "peak_TBs": LDS_PEAK_TBS,
                                     "frac": round(gather_tbs / LDS_PEAK_TBS, 4)},
                 "mfma_view": {"issued_bf16_TFLOPs": round(mfma_tflops, 1), "peak_TFLOPs": mfma_peak,
-                              "instruction": "v_mfma_f32_16x16x32_bf16" if paired else "v_smfmac_f32_16x16x64_bf16 (sparse first operand)",
+                              "instruction": "v_smfmac_f32_16x16x64_bf16 (sparse first operand)",
                               "frac": round(mfma_tflops / mfma_peak, 4)},
                 "hbm_view": {"key_code_stream_GBs": round(key_stream_gbs, 1),
                              "frac_of_hbm_peak": round(key_stream_gbs / HBM_PEAK_GBS, 4)}}

@@ -111,7 +111,7 @@ typedef struct {
 
 /* How one call is cut into workgroups (host struct, filled by commvq_plan_query). */
 typedef struct {
-    int32_t score_split_len;  /* context tokens of a score tile, rounded up to a power of two.  (Indexed bf16 keys with RoPE:
+    int32_t score_split_len;  /* context tokens of a score tile, rounded up to a power of two.  (Paired or indexed bf16 keys with RoPE:
                                  a tile is 2 to 8 segments of 512 tokens, of one sequence or of several short ones) */
     int32_t score_splits;     /* max_seqlen / score_split_len, rounded up: tiles of the longest sequence, if none is shared
                                  with another sequence or shorter than the rounded length */
@@ -147,7 +147,7 @@ commvq_status commvq_create_planner(const commvq_config *config, commvq_handle *
 
 /* Host-only: work decomposition and workspace size for a batch shape.  COMMVQ_ERR_SHAPE if batch < 1,
  * max_seqlen < 1, total_tokens outside [max_seqlen, batch * max_seqlen] or above 2^30, or if one (sequence,
- * KV head) stream (max_seqlen * bytes per token of codes, unpacked pair indices or logits) passes 2^32 - 1 bytes.
+ * KV head) stream (max_seqlen * bytes per token of codes, of two index bytes per level of whole blocks of 16, or of logits) passes 2^32 - 1 bytes.
  * A shorter context can need more than a longer one (it is cut into more pieces): size for every shape that occurs. */
 commvq_status commvq_plan_query(const commvq_handle *handle, int32_t batch, int64_t total_tokens,
                                 int32_t max_seqlen, commvq_plan *plan);
@@ -220,8 +220,8 @@ commvq_status commvq_static_scratch_bytes(size_t *bytes /* host */);
  * use `packed` instead of re-laying (the caller vouches that the contents did not change).
  * Results are bit-identical either way.  commvq_forget_packed_key_codebooks drops one pair
  * (or all, with NULL).  COMMVQ_ERR_CONFIG for fp32 codebooks (they take another kernel).
- * COMMVQ_KEYS_PAIRED: key_codebooks is the tied table; `packed` then holds it padded to blocks of
- * 16 levels, in LDS-image order.
+ * COMMVQ_KEYS_PAIRED: key_codebooks is the tied table; `packed` then holds it padded to 12, 16 or 24 levels, in
+ * LDS-image order (its size is that of whole blocks of 16 levels).
  */
 commvq_status commvq_packed_key_codebook_bytes(const commvq_handle *handle, size_t *bytes);
 commvq_status commvq_pack_key_codebooks(commvq_handle *handle, const void *key_codebooks, void *packed, void *stream);

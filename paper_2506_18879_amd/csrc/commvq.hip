@@ -50,7 +50,6 @@ struct Workspace {
     // written and read by the score stage only, in the same memory as the above; in front of them, right behind `scores`, the
     // partial logits of slice groups 1, 2, .. when the score tiles are also cut along the slices (group 0's are in `scores`)
     uint4 *packed;    // key codebook re-laid slice-major for k_score_stream / k_score_pair
-    uint8_t *pair_bytes;  // paired-code keys: one byte per index, [T * Hkv][32 * blocks]
     float *lut;           // position-free keys: scale * q . C, [B * Hkv][M_k * K][G]
     size_t bytes;
 };
@@ -75,10 +74,17 @@ inline bool use_out_mfma(const commvq_handle *h, int batch)
 inline bool bin_values(const commvq_config &c) { return c.value_format == COMMVQ_VALUES_BINARY; }
 inline int val_books(const commvq_config &c) { return bin_values(c) ? c.value_bits / kK : c.m_val; }
 
-// Paired-code key format: blocks of 16 levels, bytes of one packed record, bytes of the unpacked indices of a token.
+// Paired-code key format: blocks of 16 levels (sizes), bytes of one packed record.
 inline bool pair_keys(const commvq_config &c) { return c.key_format == COMMVQ_KEYS_PAIRED; }
 inline int pair_blocks(const commvq_config &c) { return (c.key_levels + 15) / 16; }
 inline int pair_record_bytes(const commvq_config &c) { return (12 * c.key_levels + 7) / 8; }
+// Sets of four levels that the kernels work on: levels beyond key_levels are zeros (R = 11: 3 sets, R = 21: 6).
+inline int pair_sets(const commvq_config &c) { return c.key_levels <= 12 ? 3 : c.key_levels <= 16 ? 4 : 6; }
+constexpr int kPairSlices = 4;  // LDS slices of four planes
+// Passes of k_score_pair at most (2, 4 or these).
+constexpr int pair_passes(int sets) { return sets == 3 ? 8 : 6; }
+// Memory that paired keys have had in a workspace beside the packed table (an index byte per level, unpacked): partial logits may use it.
+inline size_t pair_room(const commvq_config &c, int64_t T) { return pair_keys(c) ? (size_t)T * c.n_kv_heads * 32 * pair_blocks(c) : 0; }
 inline size_t packed_key_bytes(const commvq_config &c)
 {
     if (pair_keys(c)) return (size_t)c.n_kv_heads * 16 * pair_blocks(c) * 64 * 256;  // 16 planes x blocks x 16 KiB
@@ -113,19 +119,29 @@ int value_split_len(const commvq_handle *h, int B, int max_seqlen, int slen)
 // Bytes of the logits, and from one slice group's partial logits to the next's.
 inline size_t logit_bytes(const commvq_handle *h, int64_t T) { return align_up((size_t)T * h->cfg.n_q_heads * 4, 256); }
 
+// Partial output rows per head in the workspace, and whether it has a place for the packed value codebook.  Indexed values need neither
+// so many rows nor the codebook: their batches' workspaces keep the sizes they have had.  With paired keys the statistics, one per
+// 512 tokens, take some of it instead (batches: 256 codebook rows per partial row).
+inline size_t partial_rows(const commvq_handle *h, int B)
+{
+    const size_t rows = (size_t)val_books(h->cfg) * kK;
+    return pair_keys(h->cfg) && use_out_mfma(h, B) ? rows / kOutMfmaRows : rows / kOutRows;
+}
+inline bool packed_value_room(const commvq_handle *h, int B) { return use_out_mfma(h, B) && (bin_values(h->cfg) || !pair_keys(h->cfg)); }
+
 // Bytes of the workspace that only the value and output stages use (Workspace: vscale to packed_val).
 size_t value_stage_bytes(const commvq_handle *h, int B, size_t vsplits)
 {
     const commvq_config &c = h->cfg;
     const size_t rows = (size_t)val_books(c) * kK, heads = (size_t)B * c.n_q_heads;
-    return 2 * align_up(heads * vsplits * 4, 256) + align_up(heads * vsplits * rows * 4, 256) + align_up(heads * (rows / kOutRows) * kD * 4, 256) +
-           // (indexed values have no use for the packed codebook any more; a batch's workspace keeps its size)
-           (use_out_mfma(h, B) ? align_up((size_t)c.n_kv_heads * rows * kD * 2, 256) : 0);
+    return 2 * align_up(heads * vsplits * 4, 256) + align_up(heads * vsplits * rows * 4, 256) + align_up(heads * partial_rows(h, B) * kD * 4, 256) +
+           (packed_value_room(h, B) ? align_up((size_t)c.n_kv_heads * rows * kD * 2, 256) : 0);
 }
 
 // Launches of so few tokens that 1024-token tiles leave compute units without one: a tile's partial logits for each unit.
 size_t few_tile_bytes(const commvq_handle *h, int B, int64_t T, int max_seqlen)
 {
+    if (pair_keys(h->cfg)) return 0;
     const int64_t tiles = (int64_t)B * h->cfg.n_kv_heads * ((max_seqlen + 1023) / 1024);
     int64_t cut = 1;
     while (2 * cut <= h->cfg.m_key / 2 && 2 * cut * tiles <= 256) cut *= 2;
@@ -150,25 +166,39 @@ StreamShape stream_shape(const commvq_handle *h, int B, int64_t T, int max_seqle
     const bool two = h->cfg.m_key == 32;
     const double fixed = 9.0, sw = two ? 1.25 : h->G == 8 ? 0.6 : 0.5, c = two ? (h->G == 8 ? 0.70 : 0.66) : (h->G == 8 ? 0.47 : 0.41);
     const double part = (double)T * h->cfg.n_q_heads / 1e6 + (two ? 0.08 : 0.15);
+    // k_score_pair: 16 rounds, four to a slice; 2, 4 or pair_passes passes.  Fitted to 29 shapes of 2000 to 131072 tokens, 1 to 8
+    // sequences, R = 11 and 21: 15 cuts each, the one chosen is 0.7 % slower than the best on average (8 sequences of 1100 to 2200 tokens, R = 11:
+    // 55.9 us with groups of 8 rounds, 63.0 uncut; one of 2000: 39.9 with groups of two rounds, 56.8 uncut).
+    const bool pair = pair_keys(h->cfg);
+    const int sets = pair_sets(h->cfg);
+    const double pc = (h->G == 8 ? 0.10 : 0.0) + (sets == 3 ? 0.443 : sets == 4 ? 0.535 : 0.728);
     // The partial logits may not need more memory than the bins that follow them, apart from few_tile_bytes: a shape that fits a
     // workspace of some size (the static one in particular) must not outgrow it for the sake of a faster cut.
     const int vlen = value_split_len(h, B, max_seqlen, 1024);
     const size_t one = logit_bytes(h, T);
-    const size_t room = value_stage_bytes(h, B, (size_t)(max_seqlen + vlen - 1) / vlen) + few_tile_bytes(h, B, T, max_seqlen);
+    const size_t value = value_stage_bytes(h, B, (size_t)(max_seqlen + vlen - 1) / vlen);
+    size_t room = value + few_tile_bytes(h, B, T, max_seqlen);
+    if (pair) {  // no more than the shape has needed with unpacked indices, or 32 MB in all
+        const size_t rest = one + packed_key_bytes(h->cfg) + align_up((size_t)B * h->cfg.n_q_heads * per_seq * 8, 256), small = (size_t)32 << 20;
+        room = std::max({pair_room(h->cfg, T), value - std::min(value, packed_key_bytes(h->cfg)), small - std::min(small, rest)});
+    }
     StreamShape best = {2, 1, 1};
     double t_best = 1e30;
-    for (int passes = 2; passes <= kStreamPasses; ++passes)
+    for (int passes = 2; passes <= (pair ? pair_passes(sets) : kStreamPasses); passes += pair ? 2 + (passes == 4 ? pair_passes(sets) - 6 : 0) : 1)
         for (int e = 1; e <= kStreamSlices && (e - 1) * one <= room; e *= 2) {
             const int64_t wgs = (likely + passes - 1) / passes * h->cfg.n_kv_heads * e;
-            const double t = (double)((wgs + 255) / 256) * (fixed + (double)(kStreamSlices / e) * (sw + passes * c)) + (e > 1 ? 5.0 + e * part : 0.0);
+            const double rounds = (double)kStreamSlices / e;
+            const double t = pair ? (double)((wgs + 255) / 256) * (9.4 + std::max(1.0, rounds / 4) * 0.32 + rounds * (0.27 + passes * pc)) +
+                                        (e > 1 ? 4.8 + e * 3.35 * (double)T * h->cfg.n_q_heads / 1e6 : 0.0)
+                                  : (double)((wgs + 255) / 256) * (fixed + rounds * (sw + passes * c)) + (e > 1 ? 5.0 + e * part : 0.0);
             if (t < t_best * 0.9999) { t_best = t; best = StreamShape{passes, 0, e}; }
         }
     best.tiles = (int)((most + best.passes - 1) / best.passes);
     return best;
 }
 
-// Whether the sliced score path is k_score_stream (index-form keys with RoPE).
-inline bool stream_keys(const commvq_config &c) { return !pair_keys(c) && !c.position_free; }
+// Whether the sliced score path is k_score_stream or k_score_pair (keys with RoPE), not the look-up table.
+inline bool stream_keys(const commvq_config &c) { return !c.position_free; }
 
 // Indexed values go through k_values, the binary code through k_vbits and the output kernels.
 inline bool fused_values(const commvq_config &c) { return !bin_values(c); }
@@ -212,9 +242,9 @@ ValueShape value_shape(const commvq_handle *h, int B, int64_t T, int max_seqlen,
         if (groups > 256) v.threads = 512;
     }
     const int groups = units * (M / v.books);
-    // as many ranges as there is place for bins (stage by stage) and output rows (the rows / 64 of the other output kernels)
+    // as many ranges as there is place for bins (stage by stage) and output rows
     int n = std::max(1, (v.threads == 512 ? 512 : 256) / groups);
-    n = v.slots > 1 ? 1 : std::max(1, std::min(n, std::min(room, 4 * v.books)));
+    n = v.slots > 1 ? 1 : std::max(1, std::min(n, std::min(room, (int)partial_rows(h, B) * v.books / M)));
     v.range_len = std::max(1024, ((max_seqlen + n - 1) / n + 511) / 512 * 512);
     v.ranges = v.slots > 1 ? 1 : (max_seqlen + v.range_len - 1) / v.range_len;
     if (v.slots > 1) v.range_len = max_seqlen;
@@ -234,12 +264,12 @@ void make_plan(const commvq_handle *h, int B, int64_t T, int max_seqlen, bool sl
     } else if (sliced) {
         // Tile = 1024, 2048 or 4096 tokens of one (sequence, KV head).  Cost model of a workgroup, in microseconds: a fixed
         // start (first fetches, write-out), per slice a switch (LDS refill, barriers) and the passes themselves.
-        const int S = pair_keys(h->cfg) ? 4 : h->cfg.m_key / 2;                       // slices per tile
-        const double c1024 = h->cfg.m_key == 16 && !pair_keys(h->cfg) ? 2.1 : 1.85;  // passes of 1024 tokens over one slice
+        const int S = h->cfg.m_key / 2;                       // slices per tile
+        const double c1024 = h->cfg.m_key == 16 ? 2.1 : 1.85;  // passes of 1024 tokens over one slice
         double best = 1e30;
         len = 1024;
         for (int tpt = 1; tpt <= kScoreMaxTpt; tpt *= 2) {
-            if (tpt == 4 && h->G == 8 && (h->cfg.m_key == 16 || pair_keys(h->cfg))) break;  // those instantiations run out of registers
+            if (tpt == 4 && h->G == 8 && h->cfg.m_key == 16) break;  // those instantiations run out of registers
             const long wgs = (long)units * ((max_seqlen + 1024 * tpt - 1) / (1024 * tpt));
             const double t = (double)((wgs + 255) / 256) * (9.0 + (double)S * (1.3 + tpt * c1024));
             if (t < best * 0.9999) { best = t; len = 1024 * tpt; }
@@ -282,6 +312,7 @@ void carve(const commvq_handle *h, int B, int64_t T, int max_seqlen, void *base,
     Plan pa, pb;
     make_plan(h, B, T, max_seqlen, true, &pa);
     make_plan(h, B, T, max_seqlen, false, &pb);
+    if (pair_keys(c)) pb = pa;  // (no explicit positions)
     const size_t ssplits = std::max<size_t>(std::max(pa.score_splits, pb.score_splits), (size_t)stat_splits(h, pa, max_seqlen));
     const size_t vsplits = std::max(pa.value_splits, pb.value_splits);
     const size_t heads = (size_t)B * c.n_q_heads, rows = (size_t)val_books(c) * kK;
@@ -297,7 +328,6 @@ void carve(const commvq_handle *h, int B, int64_t T, int max_seqlen, void *base,
     const size_t parts = bf16 && stream_keys(c) ? (pa.score_slice_groups - 1) * logit_bytes(h, T) : 0;
     const size_t shared = off += parts;
     w->packed = bf16 && !c.position_free ? reinterpret_cast<uint4 *>(take(packed_key_bytes(c) / 4)) : nullptr;
-    w->pair_bytes = pair_keys(c) ? reinterpret_cast<uint8_t *>(take((size_t)T * c.n_kv_heads * 8 * pair_blocks(c))) : nullptr;
     w->lut = c.position_free ? take(heads * c.m_key * kK) : nullptr;
     const size_t score_end = off, value_bytes = value_stage_bytes(h, B, vsplits);
     const size_t few = few_tile_bytes(h, B, T, max_seqlen), apart = few ? few + std::min(score_end - shared, value_bytes) : 0;
@@ -305,8 +335,8 @@ void carve(const commvq_handle *h, int B, int64_t T, int max_seqlen, void *base,
     w->vscale = take(heads * vsplits);
     w->lsum = take(heads * vsplits);
     w->bins = reinterpret_cast<unsigned *>(take(heads * vsplits * rows));
-    w->partial = take(heads * pa.out_chunks * kD);
-    w->packed_val = use_out_mfma(h, B) ? reinterpret_cast<uint4 *>(take((size_t)c.n_kv_heads * rows * kD * 2 / 4)) : nullptr;
+    w->partial = take(heads * partial_rows(h, B) * kD);
+    w->packed_val = packed_value_room(h, B) ? reinterpret_cast<uint4 *>(take((size_t)c.n_kv_heads * rows * kD * 2 / 4)) : nullptr;
     w->bytes = std::max(off, score_end);
 }
 
@@ -316,14 +346,6 @@ struct ScoreDims {
     float scale;
 };
 
-
-__device__ __forceinline__ float row_max16(float v)
-{
-    v = fmaxf(v, dpp_mov<0xB1>(v));
-    v = fmaxf(v, dpp_mov<0x4E>(v));
-    v = fmaxf(v, dpp_mov<0x141>(v));
-    return fmaxf(v, dpp_mov<0x140>(v));
-}
 
 // Sum over each 16-lane row; every lane of the row receives the row total.
 __device__ __forceinline__ float row_sum16(float v)
@@ -576,7 +598,6 @@ __global__ __launch_bounds__(kScoreThreads) void k_score(
 
 // ------------------------------------------------------------------ k_prep
 constexpr int kSliceThreads = 1024;              // one workgroup per compute unit
-constexpr int kStatBytes = (kSliceThreads / 64) * 8 * 8;  // per-wavefront (max, sum) of up to 8 heads
 
 // Key codebook re-laid for k_score_stream.
 //   packed[g][s][blk][c][col] : 16-byte pieces (8 bf16).  Slice s holds elements 8 s .. 8 s + 7 of every codeword as
@@ -630,6 +651,7 @@ constexpr int kSegOff = 2 * kBlockBytes + 2 * kAuxBytes;          // int4 per pa
 constexpr int kWstOff = kSegOff + kStreamPasses * 16;             // float2 [8 passes][2 halves][8 heads]
 constexpr int kAuxTabOff = kWstOff + kStreamPasses * 2 * 8 * 8;   // where thread x's piece comes from (for slice 0)
 constexpr int kStreamLds = kAuxTabOff + kAuxPieces * 8;
+constexpr int kPairLds = 129696;                                  // k_score_pair's
 
 struct StreamDims {
     int Hq, Hkv, G, batch, n_hi, q_bf16;
@@ -1212,80 +1234,7 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_stream(
     }
 }
 
-// The tile's (max, sum of exp) per head, and the logits to memory, for the pair-code score kernel.
-// sc[p][x] of lane (n, gk) is the logit of head 4 x + gk for the lane's token of pass p, tb + p * 4 * 64.  The tokens
-// of a wavefront are scattered over the tile (4 fine positions x 4 coarse rows per pass), so the logits of four heads
-// at a time are transposed through the now idle slice area of LDS (stg), [head][coarse row][68] floats (rows padded
-// from 64, heads offset by 16 banks: the writes of a wavefront fall on 32 different banks), and leave as runs of 256
-// consecutive tokens per wavefront.
-// stat_dst: where the tile's statistics of head 0 go (stride nsplit per head), or null.
-template <int G, int TPT, int NPASS, int NGRP>
-__device__ __forceinline__ void write_tile_logits(const float (&sc)[NPASS][NGRP], float *stg, float2 (*wstat)[G],
-                                                  float *srow, float2 *stat_dst, int nsplit, int tb, int t0, int L)
-{
-    constexpr int TILE = TPT * kSliceThreads, NW = kSliceThreads / 64;
-    constexpr int PSTRIDE = 4 * kLo;
-    constexpr int SROW = 68, SHEAD = (TILE / kLo) * SROW + 16;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int n = lane & 15, gk = lane >> 4;
-    const int rel0 = tb - t0;
-#pragma unroll
-    for (int x = 0; x < NGRP; ++x) {
-        const int head = 4 * x + gk;
-        float mx = -INFINITY;
-#pragma unroll
-        for (int p = 0; p < NPASS; ++p) {
-            const int tok = tb + p * PSTRIDE;
-            if (head < G && tok < L) mx = fmaxf(mx, sc[p][x]);
-        }
-        const float wm = row_max16(mx);
-        float l = 0.f;
-#pragma unroll
-        for (int p = 0; p < NPASS; ++p) {
-            const int tok = tb + p * PSTRIDE;
-            if (head < G && tok < L) l += __builtin_amdgcn_exp2f((sc[p][x] - wm) * kLog2e);
-        }
-        l = row_sum16(l);
-        if (n == 0 && head < G) wstat[wave][head] = make_float2(wm, l);
-        __syncthreads();  // the last slice (x = 0) or the previous group's logits have been read by everyone
-#pragma unroll
-        for (int p = 0; p < NPASS; ++p) {
-            const int rel = rel0 + p * PSTRIDE;
-            stg[gk * SHEAD + (rel >> kLoBits) * SROW + (rel & (kLo - 1))] = sc[p][x];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int it = 0; it < TPT; ++it) {
-            const int idx = it * kSliceThreads + tid;
-            const int hl = idx / (TILE / 4), rel = 4 * (idx % (TILE / 4));
-            const int head = 4 * x + hl, tok = t0 + rel;
-            if (head < G && tok < L) {
-                const float4 v = *reinterpret_cast<const float4 *>(stg + hl * SHEAD + (rel >> kLoBits) * SROW + (rel & (kLo - 1)));
-                float *dst = srow + (size_t)head * L + tok;
-                if (tok + 3 < L) {
-                    typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));  // L need not be a multiple of 4
-                    const f4u vv = {v.x, v.y, v.z, v.w};
-                    *reinterpret_cast<f4u *>(dst) = vv;
-                } else {
-                    dst[0] = v.x;
-                    if (tok + 1 < L) dst[1] = v.y;
-                    if (tok + 2 < L) dst[2] = v.z;
-                }
-            }
-        }
-    }
-    __syncthreads();
-    if (tid < G && stat_dst) {
-        float m = -INFINITY;
-        for (int w = 0; w < NW; ++w) m = fmaxf(m, wstat[w][tid].x);
-        float l = 0.f;
-        for (int w = 0; w < NW; ++w) {
-            const float2 st = wstat[w][tid];
-            if (st.x != -INFINITY) l += st.y * __builtin_amdgcn_exp2f((st.x - m) * kLog2e);
-        }
-        stat_dst[(size_t)tid * nsplit] = make_float2(m, l);
-    }
-}
+#include "commvq_pairs.hpp"
 
 // ------------------------------------------------------------------ k_score_combine
 // Score tiles that were also cut along the codebook slices (short contexts): the logit of a token is the sum of the
@@ -1596,374 +1545,6 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_lut(const float *__rest
         }
         sstat[((size_t)b * a.Hq + (size_t)g * G + grp * HG + tid) * a.nsplit + tile] = make_float2(m, l);
     }
-}
-
-// ------------------------------------------------------------------ paired-code keys (App. A.1)
-// The paper's own key format: per token and KV head R residual levels, each a pair (a, b) of 6-bit
-// indices into ONE table of N_c' = 64 centres per level; level r contributes C[r][a] + i C[r][b]
-// (Eq. def_center: per 2-D sub-space (x_a - y_b, y_a + x_b)), i.e. index form with 2R tied codebooks.
-constexpr int kPairK = 64;       // centres per level
-constexpr int kPairPlanes = 4;   // 8-element planes per LDS slice (4 slices cover the 16 planes of d = 128)
-constexpr int kPairSet = kPairK * 256;    // bytes of a set of four levels: 64 rows x 16 pieces
-
-// Sets of four levels that the kernels work on: levels beyond key_levels are zeros (R = 11: 3 sets, R = 21: 6).
-inline int pair_sets(const commvq_config &c) { return c.key_levels <= 12 ? 3 : c.key_levels <= 16 ? 4 : 6; }
-// Bytes of a token's unpacked indices for each (type, half) below.
-constexpr int pair_lane_bytes(int sets) { return sets <= 4 ? 8 : 12; }
-
-// Packed 12-bit pairs -> one byte per index, in the order the score kernel wants.
-//   pairs : per (sequence, KV head) L records of PB = ceil(12 R / 8) bytes; pair r of a token is bits
-//           12 r .. 12 r + 11 of its record (little endian), a_r = low 6 bits, b_r = high 6 bits
-//   bytes : [token-unit][type: a | b][half][2 SETS bytes, padded to 8 or 12]: byte 2 s + st of token i is the index of level
-//           4 s + ((i / 64 + 2 half + st) mod 4); 0 for levels >= R
-// One workgroup = 256 consecutive tokens of one (sequence, KV head); their records are contiguous and
-// are staged through LDS with aligned dword loads.
-template <int SETS>
-__global__ __launch_bounds__(256) void k_unpack_pairs(const uint8_t *__restrict__ pairs, uint8_t *__restrict__ bytes,
-                                                      const int32_t *__restrict__ cu, int Hkv, int R, int PB)
-{
-    __shared__ unsigned stage[256 * 32 / 4 + 12];  // a few dwords of slack: threads read 9 whole dwords each
-    const int b = blockIdx.y / Hkv, g = blockIdx.y % Hkv;
-    const int cu0 = cu[b], L = cu[b + 1] - cu0;
-    const int i0 = blockIdx.x * 256;
-    if (i0 >= L) return;
-    const int cnt = min(256, L - i0);
-    const size_t first = ((size_t)cu0 * Hkv + (size_t)g * L + i0) * PB;  // byte offset of the first record
-    const size_t lo = first & ~(size_t)3, hi = first + (size_t)cnt * PB;  // hi never passes the end of the (b, g) stream
-    const unsigned skew = (unsigned)(first - lo);
-    const unsigned ndw = (unsigned)((hi - lo + 3) / 4);
-    for (unsigned x = threadIdx.x; x < ndw; x += 256) {
-        // the last dword may reach past the stream: read it byte by byte
-        const size_t at = lo + (size_t)x * 4;
-        unsigned v = 0;
-        if (at + 4 <= hi) v = *reinterpret_cast<const unsigned *>(pairs + at);
-        else for (unsigned k = 0; at + k < hi; ++k) v |= (unsigned)pairs[at + k] << (8 * k);
-        stage[x] = v;
-    }
-    __syncthreads();
-    if ((int)threadIdx.x >= cnt) return;
-    // the thread's record as aligned dwords: whole dwords out of LDS, then one byte-granular funnel shift each
-    const unsigned at = skew + threadIdx.x * PB;
-    const unsigned sh = at & 3u;
-    unsigned raw[9], rec[8];
-#pragma unroll
-    for (int k = 0; k < 9; ++k) raw[k] = 4 * k < PB + 3 ? stage[(at >> 2) + k] : 0u;  // PB <= 32: 9 dwords cover any skew
-#pragma unroll
-    for (int k = 0; k < 8; ++k) rec[k] = __builtin_amdgcn_alignbyte(raw[k + 1], raw[k], sh);
-    const unsigned rot = (unsigned)((i0 + (int)threadIdx.x) >> kLoBits) & 3u;
-    unsigned w[2][SETS];  // a set's four indices, rotated
-#pragma unroll
-    for (int s = 0; s < SETS; ++s) {
-        unsigned wa = 0u, wb = 0u;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int r = 4 * s + k;
-            if (r < R && r < 21) {
-                const int bit = 12 * r;  // a pair never needs more than two dwords
-                const unsigned lo32 = rec[bit >> 5], hi32 = (bit >> 5) + 1 < 8 ? rec[(bit >> 5) + 1] : 0u;
-                const unsigned pr = __builtin_amdgcn_alignbit(hi32, lo32, (unsigned)(bit & 31)) & 0xfffu;
-                wa |= (pr & 63u) << (8 * k);
-                wb |= (pr >> 6) << (8 * k);
-            }
-        }
-        w[0][s] = __builtin_amdgcn_alignbyte(wa, wa, rot);
-        w[1][s] = __builtin_amdgcn_alignbyte(wb, wb, rot);
-    }
-    constexpr int LD = pair_lane_bytes(SETS) / 4;
-    unsigned out[4 * LD];
-#pragma unroll
-    for (int type = 0; type < 2; ++type)
-#pragma unroll
-        for (int half = 0; half < 2; ++half)
-#pragma unroll
-            for (int k = 0; k < LD; ++k)
-                out[(2 * type + half) * LD + k] = 2 * k >= SETS ? 0u
-                    : __builtin_amdgcn_perm(2 * k + 1 < SETS ? w[type][(2 * k + 1) % SETS] : 0u, w[type][2 * k % SETS], half ? 0x07060302u : 0x05040100u);
-    uint4 *dst = reinterpret_cast<uint4 *>(bytes + ((size_t)cu0 * Hkv + (size_t)g * L + i0 + threadIdx.x) * (16 * LD));
-#pragma unroll
-    for (int k = 0; k < LD; ++k) dst[k] = make_uint4(out[4 * k], out[4 * k + 1], out[4 * k + 2], out[4 * k + 3]);
-}
-
-// Tied table [Hkv][R][64][d] bf16 -> LDS images for k_score_pair:
-//   packed[g][slice][set][c][4 plane + k] 16-byte pieces = elements 8 (4 slice + plane) .. +7 of centre c of
-//   level 4 set + k (zeros for levels >= R).  One thread per piece of the output.
-__global__ __launch_bounds__(256) void k_prep_pairs(const uint4 *__restrict__ table, uint4 *__restrict__ packed, int Hkv,
-                                                    int R, int sets)
-{
-    const size_t n = (size_t)Hkv * 4 * sets * kPairK * 16;
-    const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= n) return;
-    const int col = (int)(t & 15);
-    const int c = (int)((t >> 4) % kPairK);
-    size_t rest = (t >> 4) / kPairK;
-    const int set = (int)(rest % sets);
-    rest /= sets;
-    const int slice = (int)(rest % 4), g = (int)(rest / 4);
-    const int r = 4 * set + (col & 3);
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (r < R) v = table[(((size_t)g * R + r) * kPairK + c) * 16 + 4 * slice + (col >> 2)];
-    packed[t] = v;
-}
-
-// Score kernel for paired-code keys: same scheme as k_score_stream (codebook streamed through LDS in
-// slices, gather-sum and query product on the matrix cores), with
-//   * a slice = 4 planes of 8 elements of every centre of every level, SETS sets of four levels: a set is 64 rows (centre
-//     index) of 16 bank columns, 4 of them per plane;
-//   * the four lanes of a token are (a | b) x half: in step (s, st) of a plane lane (n, g) gathers the centre that
-//     the a (g < 2) or b (g >= 2) index of token n selects in level 4 s + (n + 2 (g & 1) + st) mod 4;
-//   * lanes n with the same n / 4 = j work on plane i ^ j in round i.  The 16 lanes that a 16-byte read checks against each other
-//     are four such quads with four different j (0..3, 12..15, 20..23, 24..27 of every 32 lanes, and the other 16): four planes
-//     x four levels, 16 bank columns whatever the indices.  So only the sets that hold levels are read, 2 SETS pieces per
-//     lane and plane, where a column per level for one plane at a time needs all 16: 128K tokens, R = 11, 98.5 -> 91.9 us
-//     (whole call with binary values 144.4 -> 138.1);
-//   * a selection matrix that routes the a-sum and the b-sum of sub-space g of the plane to rows
-//     4g .. 4g + 3, so that lane (n, g) receives (SA_x, SA_y, SB_x, SB_y) and forms the decoded block
-//     (SA_x - SB_y, SA_y + SB_x) of Eq. def_center locally;
-//   * one cross-lane head total per slice: the 4x4x1 query MFMAs of the slice's 4 planes chain into
-//     one accumulator before the row / half swaps (the 4 lanes of a block share the plane).
-template <int SETS, int G, int TPT>
-__global__ __launch_bounds__(kSliceThreads) void k_score_pair(
-    const void *__restrict__ q, const uint8_t *__restrict__ codes_all, const uint4 *__restrict__ packed,
-    const int32_t *__restrict__ cu, const int32_t *__restrict__ q_pos, const float2 *__restrict__ tbl_hi,
-    const float2 *__restrict__ tbl_lo, float *__restrict__ scores, float2 *__restrict__ sstat, const SliceDims a)
-{
-    constexpr int PL = kPairPlanes;
-    constexpr int S = 16 / PL;
-    constexpr int LB = pair_lane_bytes(SETS), CB = 4 * LB;  // index bytes per lane and per token
-    constexpr int SLICE = SETS * kPairSet;           // LDS bytes of one slice
-    constexpr int TILE = TPT * kSliceThreads;
-    constexpr int NW = kSliceThreads / 64;
-    constexpr int NPASS = TILE / (16 * NW);
-    constexpr int NHR = TILE / kLo + 1;
-    constexpr int NGRP = (G + 3) / 4;
-    constexpr int PARTS = 8;                          // (sub-space of a plane) x (planes 0,1 | 2,3)
-    constexpr int HROW = 20;                          // 16-byte entries per coarse phase row (16 used: conflict-free reads)
-    static_assert(NPASS % 2 == 0, "code double-buffer parity assumes an even number of passes");
-    extern __shared__ __attribute__((aligned(16))) uint4 tab[];  // [SETS][64][16] pieces, then the phase factors
-    float4 *elo = reinterpret_cast<float4 *>(reinterpret_cast<char *>(tab) + SLICE);  // [PARTS][64]
-    float4 *ehi = elo + PARTS * kLo;                                                   // [NHR][HROW]
-    float2(*wstat)[G] = reinterpret_cast<float2(*)[G]>(ehi + HROW * NHR);             // [NW][G]
-    static_assert(4 * ((TILE / kLo) * 68 + 16) * 4 <= SLICE + (PARTS * kLo + HROW * NHR) * 16, "the write-out stages its logits below the statistics");
-
-    int id = blockIdx.x;
-    const int g = id % a.Hkv;
-    id /= a.Hkv;
-    const int tile = id % a.nsplit;
-    const int b = id / a.nsplit;
-    const int cu0 = cu[b];
-    const int L = cu[b + 1] - cu0;
-    const int t0 = tile * TILE;
-    if (t0 >= L) return;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int n = lane & 15, gk = lane >> 4;
-    const int type = gk >> 1;                         // 0: the a indices, 1: the b indices
-    const int half = gk & 1;                          // two of the four levels of every set
-    const int j = n >> 2;                             // the lane works on plane i ^ j in round i
-    const int qpos = q_pos[b];
-    const uint8_t *codes = codes_all + ((size_t)cu0 * a.Hkv + (size_t)g * L) * CB;
-    const uint4 *src = packed + (size_t)g * S * (SLICE / 16);
-    const __amdgpu_buffer_rsrc_t cd_rs = make_rsrc(codes, (unsigned)L * CB);
-    const unsigned qesz = a.q_bf16 ? 2u : 4u;
-    const __amdgpu_buffer_rsrc_t q_rs =
-        make_rsrc(static_cast<const char *>(q) + ((size_t)b * a.Hq + (size_t)g * G) * kD * qesz, (unsigned)G * kD * qesz);
-    constexpr int PPT = SLICE / 16 / kSliceThreads;
-
-    // Selection operand of the structured-sparse v_smfmac_f32_16x16x64_bf16 (layout: see k_score_stream).  Second
-    // operand: two pieces per lane, both from levels of the lane's own type.  Row i = n adds element
-    // e = 2 (i >> 2) + (i & 1) of both pieces of the two lanes of its type (i >> 1) & 1: first-operand lane (i, q)
-    // covers the pieces of second-operand lanes 2 (q & 1), 2 (q & 1) + 1, i.e. of type q & 1 (its first piece for
-    // q < 2, its second for q >= 2), and keeps 1.0 at position e % 4 of groups e / 4 and 2 + e / 4.
-    uint4_t sel = {0u, 0u, 0u, 0u};
-    unsigned sidx = 0x44444444u;  // default positions (0, 1) of every stored pair
-    if ((gk & 1) == ((n >> 1) & 1)) {
-        const int e = 2 * (n >> 2) + (n & 1);
-        const int t = e >> 2, pos = e & 3, other = pos == 0 ? 1 : 0;
-        sel[t] = 0x00003f80u;
-        sel[2 + t] = 0x00003f80u;
-        const unsigned pair = (unsigned)pos | (unsigned)other << 2;
-        sidx = (sidx & ~(0xfu << (4 * t)) & ~(0xfu << (4 * (2 + t)))) | pair << (4 * t) | pair << (4 * (2 + t));
-        sidx = (sidx & 0xffffu) | sidx << 16;
-    }
-    const bf16x8_t selv = __builtin_bit_cast(bf16x8_t, sel);
-
-    float sc[NPASS][NGRP];
-#pragma unroll
-    for (int p = 0; p < NPASS; ++p)
-#pragma unroll
-        for (int x = 0; x < NGRP; ++x) sc[p][x] = 0.f;
-
-    // xreg[i][st]: byte 0 = 16 * bank column read in round i, step st, byte 2 = 0, byte 3 = 1;
-    // a byte permute splices the centre index in as byte 1: address = 256 c + 16 col (+ 65536 via byte 3)
-    unsigned xreg[PL][2];
-#pragma unroll
-    for (int i = 0; i < PL; ++i)
-#pragma unroll
-        for (int st = 0; st < 2; ++st) xreg[i][st] = (unsigned)(4 * (i ^ j) + ((n + 2 * half + st) & 3)) * 16u | 1u << 24;
-
-    // Token mapping as in k_score_stream (M = 16): lane n of a wavefront's 16 token lanes takes fine position
-    // 4 wave + n / 4 and coarse row n % 4 of the pass's block of four rows, so the lanes of a 4-lane block and all
-    // passes of a lane are whole coarse rows apart and share the fine phase factor, which is folded into the query.
-    int tb = t0 + 4 * wave + (n >> 2) + kLo * (n & 3);
-    constexpr int PSTRIDE = 4 * kLo;
-    constexpr int CD = LB / 4;
-    unsigned cw[2][CD];
-    auto fetch_codes = [&](int p, unsigned(&dst)[CD]) {
-        const int tok = min(tb + p * PSTRIDE, L - 1);
-        const unsigned at = (unsigned)tok * CB + (unsigned)(gk * LB);
-        const uint2_t c2 = __builtin_amdgcn_raw_buffer_load_b64(cd_rs, at, 0, 0);
-        dst[0] = c2[0]; dst[1] = c2[1];
-        if constexpr (CD == 3) dst[2] = __builtin_amdgcn_raw_buffer_load_b32(cd_rs, at + 8u, 0, 0);
-    };
-    fetch_codes(0, cw[0]);
-    const int hmin = (qpos - (t0 + TILE - 1)) >> kLoBits;
-    const unsigned elo_base = (unsigned)SLICE + (unsigned)(2 * gk) * (kLo * 16u);
-    const unsigned ehi_base = (unsigned)SLICE + (unsigned)(PARTS * kLo) * 16u + (unsigned)(4 * gk + j) * 16u;
-
-    for (int sl = 0; sl < S; ++sl) {
-        // queries of this slice (head 4 grp + n % 4, sub-space gk of the plane of each round): requested ahead of the
-        // slice itself, so that they have arrived when the first pass needs them
-        uint2_t qraw[NGRP][PL];
-#pragma unroll
-        for (int x = 0; x < NGRP; ++x)
-#pragma unroll
-            for (int pl = 0; pl < PL; ++pl) {
-                const unsigned off = (unsigned)(4 * x + (n & 3)) * kD + 2u * (unsigned)(16 * sl + 4 * (pl ^ j) + gk);  // elements
-                if (a.q_bf16) {
-                    qraw[x][pl][0] = __builtin_amdgcn_raw_buffer_load_b32(q_rs, off * 2u, 0, 0);
-                    qraw[x][pl][1] = 0u;
-                } else {
-                    qraw[x][pl] = __builtin_amdgcn_raw_buffer_load_b64(q_rs, off * 4u, 0, 0);
-                }
-            }
-        __syncthreads();  // everyone is done reading the previous slice
-        {
-            uint4 stage[PPT];
-#pragma unroll
-            for (int x = 0; x < PPT; ++x) stage[x] = src[(size_t)sl * (SLICE / 16) + x * kSliceThreads + tid];
-#pragma unroll
-            for (int x = 0; x < PPT; ++x) tab[x * kSliceThreads + tid] = stage[x];
-        }
-        // phase factors of this slice's 16 sub-spaces: a fine entry (s, h) holds sub-space s of planes 2h and 2h + 1, table
-        // [2 s + h][64 positions]; a coarse entry (s, h, v) the same, in the other order for v = 1, table [row][4 s + 2 h + v]: the
-        // lane's planes in the order of its rounds.  In the 16 lanes of a read the four quads have four different 2 h + v, and
-        // the four rows of a quad are 4 entries apart (mod 16): 16 different 16-byte bank groups
-        if (tid < PARTS * kLo) {
-            const int part = tid / kLo, lo = tid % kLo;
-            const int j0 = 16 * sl + 8 * (part & 1) + (part >> 1);
-            const float2 e0 = tbl_lo[(size_t)lo * kJ + j0], e1 = tbl_lo[(size_t)lo * kJ + j0 + 4];
-            elo[tid] = make_float4(e0.x, e0.y, e1.x, e1.y);
-        }
-        for (int x = tid; x < PARTS * NHR; x += kSliceThreads) {
-            const int c = x % PARTS, H = hmin + x / PARTS;  // c = 2 s + h
-            const int hi = min(H < 0 ? -H : H, a.n_hi - 1);
-            const int j0 = 16 * sl + 8 * (c & 1) + (c >> 1);
-            const float2 e0 = tbl_hi[(size_t)hi * kJ + j0], e1 = tbl_hi[(size_t)hi * kJ + j0 + 4];
-            const float sg = H < 0 ? -1.f : 1.f;
-            float4 *dst = ehi + (x / PARTS) * HROW + 2 * c;
-            dst[0] = make_float4(e0.x, sg * e0.y, e1.x, sg * e1.y);
-            dst[1] = make_float4(e1.x, sg * e1.y, e0.x, sg * e0.y);
-        }
-        __syncthreads();
-        asm volatile("" : "+v"(tb));
-        const int dist16 = (qpos - tb) * 16;
-        // scaled queries of this slice, times the conjugate of the fine phase factor (shared by the lane's tokens of all
-        // passes and by the four lanes of its block): q' = q conj(E_lo), Re(conj(q) k E_hi E_lo) = Re(conj(q') k E_hi)
-        float qrow[NGRP][PL][2];
-        {
-            uint4_t elr[2];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const uint4_t e = lds_read_b128(elo_base + (unsigned)(dist16 & ((kLo - 1) * 16)) + (unsigned)((h ^ (j >> 1)) * (kLo * 16)));
-#pragma unroll
-                for (int k = 0; k < 4; ++k) elr[h][k] = j & 1 ? e[k ^ 2] : e[k];
-            }
-#pragma unroll
-            for (int x = 0; x < NGRP; ++x)
-#pragma unroll
-                for (int pl = 0; pl < PL; ++pl) {
-                    const unsigned u0 = qraw[x][pl][0], u1 = qraw[x][pl][1];
-                    float qx, qy;
-                    if (a.q_bf16) {
-                        qx = bf16_lo(u0) * a.scale; qy = bf16_hi(u0) * a.scale;
-                    } else {
-                        qx = __builtin_bit_cast(float, u0) * a.scale; qy = __builtin_bit_cast(float, u1) * a.scale;
-                    }
-                    const unsigned lxr = elr[pl / 2][2 * (pl & 1)], lyr = elr[pl / 2][2 * (pl & 1) + 1];
-                    const float lx = __builtin_bit_cast(float, lxr), ly = __builtin_bit_cast(float, lyr);
-                    qrow[x][pl][0] = qx * lx + qy * ly;
-                    qrow[x][pl][1] = qy * lx - qx * ly;
-                }
-        }
-        // coarse phase row of the lane's token of the LAST pass; a pass is a whole number of rows further on
-        const unsigned ehi_last = ehi_base + (unsigned)(((dist16 >> (kLoBits + 4)) - hmin - (NPASS - 1) * (PSTRIDE / kLo)) * (16 * HROW));
-        // Gather: 2 SETS pieces per lane and plane, two reads (one matrix instruction) at a time; the reads of all planes of a pass form
-        // one sequence of which NBUF - 1 to NBUF steps are in flight -- across planes and passes, so that the first reads of
-        // the next plane (pass) travel while this one is rotated and contracted with the queries.
-        constexpr int NFLAT = PL * SETS, NBUF = SETS == 4 ? (G == 8 ? 2 : 4) : G == 8 ? 2 : 3;  // fewer where registers are short
-        static_assert(NFLAT % NBUF == 0, "read buffers alternate across passes");
-        uint4_t v[NBUF][2];
-        auto issue = [&](int flat, const unsigned(&cc)[CD], uint4_t(&dst)[2]) {
-            const int i = flat / SETS, set = flat % SETS;
-#pragma unroll
-            for (int st = 0; st < 2; ++st) {
-                const int byte = 2 * set + st;
-                const unsigned selb = 0x0c000000u | (unsigned)(2 + set / 4) << 16 | (unsigned)(4 + byte % 4) << 8;
-                const unsigned addr = __builtin_amdgcn_perm(cc[byte / 4], xreg[i][st], selb);
-                dst[st] = lds_read_b128((unsigned)((set % 4) * kPairSet) + addr);
-            }
-        };
-        // (the last pass of the previous slice requested the codes of pass 0 again)
-#pragma unroll
-        for (int f = 0; f < NBUF - 1; ++f) issue(f, cw[0], v[f]);
-#pragma unroll
-        for (int p = 0; p < NPASS; ++p) {
-            __builtin_amdgcn_sched_barrier(0);  // one pass at a time: keeps register pressure flat
-            fetch_codes((p + 1) % NPASS, cw[(p + 1) & 1]);
-            uint4_t ehr[2];
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-                ehr[h] = lds_read_b128((ehi_last ^ (unsigned)(h * 32)) + (unsigned)((NPASS - 1 - p) * (PSTRIDE / kLo) * (16 * HROW)));
-            __builtin_amdgcn_sched_barrier(0);
-            floatx4_t t[NGRP];
-#pragma unroll
-            for (int x = 0; x < NGRP; ++x) t[x] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int pl = 0; pl < PL; ++pl) {
-                // 1. gather-sum of the plane
-                floatx4_t acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int set = 0; set < SETS; ++set) {
-                    const int flat = pl * SETS + set, next = flat + NBUF - 1;
-                    if (next < NFLAT) issue(next, cw[p & 1], v[next % NBUF]);
-                    else issue(next - NFLAT, cw[(p + 1) & 1], v[next % NBUF]);  // (after the last pass: of pass 0 in this slice, not used)
-                    __builtin_amdgcn_sched_barrier(0);
-                    const uint4_t pa = v[flat % NBUF][0], pb = v[flat % NBUF][1];
-                    const uint8v_t both = {pa[0], pa[1], pa[2], pa[3], pb[0], pb[1], pb[2], pb[3]};
-                    acc = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(selv, __builtin_bit_cast(bf16x16_t, both), acc, (int)sidx, 0, 0);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                // 2. decoded block of sub-space gk (Eq. def_center), rotated by the coarse phase factor
-                const unsigned hxr = ehr[pl / 2][2 * (pl & 1)], hyr = ehr[pl / 2][2 * (pl & 1) + 1];
-                const float ex = __builtin_bit_cast(float, hxr), ey = __builtin_bit_cast(float, hyr);
-                const float kx = acc[0] - acc[3], ky = acc[1] + acc[2];
-                const float bx = kx * ex - ky * ey;
-                const float by = kx * ey + ky * ex;
-                // 3. partial logits of 4 heads at a time; chained over the planes of the slice
-#pragma unroll
-                for (int x = 0; x < NGRP; ++x) {
-                    t[x] = __builtin_amdgcn_mfma_f32_4x4x1f32(qrow[x][pl][0], bx, t[x], 0, 0, 0);
-                    t[x] = __builtin_amdgcn_mfma_f32_4x4x1f32(qrow[x][pl][1], by, t[x], 0, 0, 0);
-                }
-            }
-            // totals over the 4 lanes of the token: lane (n, gk) keeps head 4 grp + gk
-#pragma unroll
-            for (int x = 0; x < NGRP; ++x) sc[p][x] += swap16_add(swap32_add(t[x][0], t[x][2]), swap32_add(t[x][1], t[x][3]));
-        }
-    }
-
-    float *srow = scores + (size_t)cu0 * a.Hq + (size_t)g * G * L;
-    float2 *stat_dst = sstat + ((size_t)b * a.Hq + (size_t)g * G) * a.nsplit + tile;
-    write_tile_logits<G, TPT, NPASS, NGRP>(sc, reinterpret_cast<float *>(tab), wstat, srow, stat_dst, a.nsplit, tb, t0, L);
 }
 
 // ------------------------------------------------------------------ k_out
@@ -2299,7 +1880,8 @@ commvq_status check_shape(const commvq_handle *h, int32_t batch, int64_t total_t
     if (total_tokens < max_seqlen) return COMMVQ_ERR_SHAPE;
     if (total_tokens > (int64_t)batch * max_seqlen) return COMMVQ_ERR_SHAPE;
     if (total_tokens > (int64_t)1 << 30) return COMMVQ_ERR_SHAPE;
-    // the kernels address one (sequence, KV head)'s codes, unpacked pair indices and logits with 32-bit byte offsets
+    // the kernels address one (sequence, KV head)'s codes and logits with 32-bit byte offsets (paired keys: the bound is that of
+    // two index bytes per level of whole blocks of 16)
     const commvq_config &c = h->cfg;
     int64_t rec = bin_values(c) ? c.value_bits / 8 : c.m_val;
     if (pair_keys(c)) rec = std::max<int64_t>(rec, 32 * pair_blocks(c));
@@ -2375,17 +1957,6 @@ hipError_t launch_out_g(const OutArgs &a, bool bf16, int grid, hipStream_t s)
     return hipGetLastError();
 }
 
-struct SliceArgs {
-    const void *q;
-    const uint8_t *key_codes;
-    const uint4 *packed;
-    const int32_t *cu, *q_pos;
-    const float2 *tbl_hi, *tbl_lo;
-    float *scores;
-    float2 *sstat;
-    SliceDims d;
-};
-
 struct StreamArgs {
     const void *q;
     const uint8_t *key_codes;
@@ -2425,38 +1996,35 @@ hipError_t launch_stream(const StreamArgs &a, int M, int passes, int grid, hipSt
     return a.d.G == 8 ? launch_stream_g<32, 2>(a, passes, grid, s) : launch_stream_g<32, 1>(a, passes, grid, s);
 }
 
-template <int SETS, int G, int TPT>
-hipError_t launch_pair_bgt(const SliceArgs &a, int grid, hipStream_t s)
+template <int SETS, int NGRP, int NP>
+hipError_t launch_pair_n(const StreamArgs &a, int R, int PB, int grid, hipStream_t s)
 {
-    constexpr int tile = TPT * kSliceThreads;
-    // slice + fine phase factors + coarse rows (20 entries each) + per-wavefront statistics; the write-out stages four
-    // heads of the tile's logits, [64 positions padded to 68] per coarse row, over the slice and the phase factors
-    constexpr int work = SETS * kPairSet + 8 * kLo * 16 + 20 * (tile / kLo + 1) * 16;
-    constexpr int stg = 4 * ((tile / kLo) * 68 + 16) * 4;
-    constexpr int lds = (work > stg ? work : stg) + kStatBytes;
     static std::atomic<uint64_t> lds_ok{0};  // per instantiation and device
-    if (hipError_t e = allow_dynamic_lds(&k_score_pair<SETS, G, TPT>, lds, lds_ok); e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_score_pair<SETS, G, TPT>), dim3(grid), dim3(kSliceThreads), lds, s, a.q, a.key_codes, a.packed,
-                       a.cu, a.q_pos, a.tbl_hi, a.tbl_lo, a.scores, a.sstat, a.d);
+    if (hipError_t e = allow_dynamic_lds(&k_score_pair<SETS, NGRP, NP>, kPairLds, lds_ok); e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_score_pair<SETS, NGRP, NP>), dim3(grid), dim3(kSliceThreads), kPairLds, s, a.q, a.key_codes,
+                       a.packed, a.cu, a.q_pos, a.tbl_hi, a.tbl_lo, a.scores, a.sstat, a.d, R, PB);
     return hipGetLastError();
 }
-template <int SETS, int G>
-hipError_t launch_pair_bg(const SliceArgs &a, int tpt, int grid, hipStream_t s)
-{
-    switch (tpt) {
-    case 1: return launch_pair_bgt<SETS, G, 1>(a, grid, s);
-    case 2: return launch_pair_bgt<SETS, G, 2>(a, grid, s);
-    default: return launch_pair_bgt<SETS, G, 4>(a, grid, s);
-    }
-}
 template <int SETS>
-hipError_t launch_pair_b(const SliceArgs &a, int G, int tpt, int grid, hipStream_t s)
+hipError_t launch_pair_s(const StreamArgs &a, int passes, int R, int PB, int grid, hipStream_t s)
 {
-    switch (G) {
-    case 1: return launch_pair_bg<SETS, 1>(a, tpt, grid, s);
-    case 2: return launch_pair_bg<SETS, 2>(a, tpt, grid, s);
-    case 4: return launch_pair_bg<SETS, 4>(a, tpt, grid, s);
-    default: return launch_pair_bg<SETS, 8>(a, tpt, grid, s);
+    constexpr int most = pair_passes(SETS);
+    if (a.d.G == 8) {
+        if (passes == 2) return launch_pair_n<SETS, 2, 2>(a, R, PB, grid, s);
+        if (passes == 4) return launch_pair_n<SETS, 2, 4>(a, R, PB, grid, s);
+        return launch_pair_n<SETS, 2, most>(a, R, PB, grid, s);
+    }
+    if (passes == 2) return launch_pair_n<SETS, 1, 2>(a, R, PB, grid, s);
+    if (passes == 4) return launch_pair_n<SETS, 1, 4>(a, R, PB, grid, s);
+    return launch_pair_n<SETS, 1, most>(a, R, PB, grid, s);
+}
+hipError_t launch_pair(const StreamArgs &a, const commvq_config &c, int passes, int grid, hipStream_t s)
+{
+    const int R = c.key_levels, PB = pair_record_bytes(c);
+    switch (pair_sets(c)) {
+    case 3: return launch_pair_s<3>(a, passes, R, PB, grid, s);
+    case 4: return launch_pair_s<4>(a, passes, R, PB, grid, s);
+    default: return launch_pair_s<6>(a, passes, R, PB, grid, s);
     }
 }
 
@@ -2545,41 +2113,22 @@ commvq_status run_scores(commvq_handle *h, const void *q, const uint8_t *key_cod
             packed = w.packed;
         }
         hipError_t e;
-        if (pair_keys(c)) {
-            SliceArgs sa;
-            sa.q = q; sa.packed = packed; sa.cu = pos->cu_seqlens; sa.q_pos = pos->q_pos;
-            sa.tbl_hi = h->tbl_hi; sa.tbl_lo = h->tbl_lo; sa.scores = w.scores; sa.sstat = w.sstat;
-            sa.d.Hq = c.n_q_heads; sa.d.Hkv = c.n_kv_heads; sa.d.nsplit = plan.score_splits; sa.d.n_hi = h->n_hi;
-            sa.d.q_bf16 = c.q_dtype == COMMVQ_BF16; sa.d.scale = h->scale;
-            const int grid = pos->batch * c.n_kv_heads * plan.score_splits;
-            const int tpt = plan.score_split_len / kSliceThreads;
-            // 12-bit pairs -> one byte per index, then the paired-code score kernel
-            const dim3 blocks((unsigned)((pos->max_seqlen + 255) / 256), (unsigned)(pos->batch * c.n_kv_heads));
-            const int sets = pair_sets(c), rec = pair_record_bytes(c);
-            if (sets == 3) hipLaunchKernelGGL(k_unpack_pairs<3>, blocks, dim3(256), 0, s, key_codes, w.pair_bytes, pos->cu_seqlens, c.n_kv_heads, c.key_levels, rec);
-            else if (sets == 4) hipLaunchKernelGGL(k_unpack_pairs<4>, blocks, dim3(256), 0, s, key_codes, w.pair_bytes, pos->cu_seqlens, c.n_kv_heads, c.key_levels, rec);
-            else hipLaunchKernelGGL(k_unpack_pairs<6>, blocks, dim3(256), 0, s, key_codes, w.pair_bytes, pos->cu_seqlens, c.n_kv_heads, c.key_levels, rec);
-            if (hipGetLastError() != hipSuccess) return COMMVQ_ERR_LAUNCH;
-            sa.key_codes = w.pair_bytes;
-            e = sets == 3 ? launch_pair_b<3>(sa, h->G, tpt, grid, s) : sets == 4 ? launch_pair_b<4>(sa, h->G, tpt, grid, s) : launch_pair_b<6>(sa, h->G, tpt, grid, s);
-        } else {
-            const StreamShape &ss = plan.stream;
-            StreamArgs sa;
-            sa.q = q; sa.key_codes = key_codes; sa.packed = packed; sa.cu = pos->cu_seqlens; sa.q_pos = pos->q_pos;
-            sa.tbl_hi = h->tbl_hi; sa.tbl_lo = h->tbl_lo; sa.scores = w.scores; sa.sstat = w.sstat;
-            sa.d.Hq = c.n_q_heads; sa.d.Hkv = c.n_kv_heads; sa.d.G = h->G; sa.d.batch = pos->batch; sa.d.n_hi = h->n_hi;
-            sa.d.q_bf16 = c.q_dtype == COMMVQ_BF16; sa.d.scale = h->scale;
-            sa.d.tiles = ss.tiles; sa.d.groups = ss.groups;
-            sa.d.nstat = stat_splits(h, plan, pos->max_seqlen);
-            sa.d.part_stride = (long long)(logit_bytes(h, pos->total_tokens) / 4);
-            const int grid = c.n_kv_heads * ss.tiles * ss.groups;
-            e = launch_stream(sa, c.m_key, ss.passes, grid, s);
-            if (e == hipSuccess && ss.groups > 1) {
-                const int ns = sa.d.nstat;
-                hipLaunchKernelGGL(k_score_combine, dim3((unsigned)(pos->batch * c.n_q_heads * ns)), dim3(kCombineThreads), 0, s,
-                                   w.scores, w.sstat, pos->cu_seqlens, c.n_q_heads, ns, stat_len(h, plan), ss.groups, sa.d.part_stride);
-                e = hipGetLastError();
-            }
+        const StreamShape &ss = plan.stream;
+        StreamArgs sa;
+        sa.q = q; sa.key_codes = key_codes; sa.packed = packed; sa.cu = pos->cu_seqlens; sa.q_pos = pos->q_pos;
+        sa.tbl_hi = h->tbl_hi; sa.tbl_lo = h->tbl_lo; sa.scores = w.scores; sa.sstat = w.sstat;
+        sa.d.Hq = c.n_q_heads; sa.d.Hkv = c.n_kv_heads; sa.d.G = h->G; sa.d.batch = pos->batch; sa.d.n_hi = h->n_hi;
+        sa.d.q_bf16 = c.q_dtype == COMMVQ_BF16; sa.d.scale = h->scale;
+        sa.d.tiles = ss.tiles; sa.d.groups = ss.groups;
+        sa.d.nstat = stat_splits(h, plan, pos->max_seqlen);
+        sa.d.part_stride = (long long)(logit_bytes(h, pos->total_tokens) / 4);
+        const int grid = c.n_kv_heads * ss.tiles * ss.groups;
+        e = pair_keys(c) ? launch_pair(sa, c, ss.passes, grid, s) : launch_stream(sa, c.m_key, ss.passes, grid, s);
+        if (e == hipSuccess && ss.groups > 1) {
+            const int ns = sa.d.nstat;
+            hipLaunchKernelGGL(k_score_combine, dim3((unsigned)(pos->batch * c.n_q_heads * ns)), dim3(kCombineThreads), 0, s,
+                               w.scores, w.sstat, pos->cu_seqlens, c.n_q_heads, ns, stat_len(h, plan), ss.groups, sa.d.part_stride);
+            e = hipGetLastError();
         }
         return e == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;
     }
@@ -2762,7 +2311,7 @@ commvq_status commvq_validate_config(const commvq_config *c)
     if (c->key_format == COMMVQ_KEYS_INDEXED) {
         if (c->m_key != 16 && c->m_key != 32) return COMMVQ_ERR_CONFIG;
     } else if (c->key_format == COMMVQ_KEYS_PAIRED) {
-        // 12 R bits per record must fit the unpack kernel's staging (R <= 21: 32 bytes); one table for a and b, bf16 only
+        // a record is at most 32 bytes (R <= 21); one table for a and b, bf16 only
         if (c->key_levels < 1 || c->key_levels > 21 || c->codebook_dtype != COMMVQ_BF16) return COMMVQ_ERR_CONFIG;
     } else {
         return COMMVQ_ERR_CONFIG;

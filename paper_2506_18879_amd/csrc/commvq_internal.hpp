@@ -19,7 +19,7 @@ constexpr int kJ = 64;          // 2-D sub-spaces = lanes of a wavefront
 constexpr int kK = 256;         // codewords per codebook
 constexpr int kLoBits = 6;      // relative position = hi * 64 + lo
 constexpr int kLo = 1 << kLoBits;
-constexpr int kScoreMaxTpt = 4;      // tiles of k_score_pair and k_score_lut: at most 4 x 1024 tokens
+constexpr int kScoreMaxTpt = 4;      // tiles of k_score_lut: at most 4 x 1024 tokens
 constexpr int kStreamPasses = 8;     // k_score_stream: passes of a workgroup at most
 constexpr int kPassTokens = 512;     // tokens of a pass: 16 wavefronts x 32
 constexpr int kStreamSlices = kD / 8;  // codebook slices: 8 elements of every codeword each
