@@ -73,6 +73,36 @@ __device__ __forceinline__ bool min2_halves(float &best, int &index)
     return second;
 }
 
+// a token's largest and second largest value, from those of its lanes 16 (32) apart
+__device__ __forceinline__ void two_largest(unsigned b0, unsigned b1, unsigned s0, unsigned s1, float &best, float &second)
+{
+    const float f0 = __builtin_bit_cast(float, b0), f1 = __builtin_bit_cast(float, b1);
+    second = fmaxf(fminf(f0, f1), fmaxf(__builtin_bit_cast(float, s0), __builtin_bit_cast(float, s1)));
+    best = fmaxf(f0, f1);
+}
+__device__ __forceinline__ void two_largest16(float &best, float &second)
+{
+    const unsigned b = __builtin_bit_cast(unsigned, best), s = __builtin_bit_cast(unsigned, second);
+    const auto b16 = __builtin_amdgcn_permlane16_swap(b, b, false, false);
+    const auto s16 = __builtin_amdgcn_permlane16_swap(s, s, false, false);
+    two_largest(b16[0], b16[1], s16[0], s16[1], best, second);
+}
+__device__ __forceinline__ void two_largest32(float &best, float &second)
+{
+    const unsigned b = __builtin_bit_cast(unsigned, best), s = __builtin_bit_cast(unsigned, second);
+    const auto b32 = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+    const auto s32 = __builtin_amdgcn_permlane32_swap(s, s, false, false);
+    two_largest(b32[0], b32[1], s32[0], s32[1], best, second);
+}
+__device__ __forceinline__ float sum4(float v)  // over the four lanes of a token
+{
+    const unsigned u = __builtin_bit_cast(unsigned, v);
+    const auto r16 = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    const unsigned w = __builtin_bit_cast(unsigned, __builtin_bit_cast(float, (unsigned)r16[0]) + __builtin_bit_cast(float, (unsigned)r16[1]));
+    const auto r32 = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+    return __builtin_bit_cast(float, (unsigned)r32[0]) + __builtin_bit_cast(float, (unsigned)r32[1]);
+}
+typedef float floatx2_t __attribute__((ext_vector_type(2)));
 // The least of the 64 lanes' non-negative indices, in every lane.
 __device__ __forceinline__ int wave_min_index(int v)
 {
@@ -149,12 +179,8 @@ __global__ __launch_bounds__(256) void k_encode(const void *__restrict__ keys, c
 // double buffer.  Piece x of row t sits in slot x xor (t mod 16) of its row: the operand reads are free of bank
 // conflicts, and a load instruction (64 lanes -> 64 consecutive slots) still covers 1 KiB of contiguous memory.
 // Eight wavefronts: 8 / RS sets of 16 tokens, the 256 rows of a level shared by the RS wavefronts of a set, which
-// exchange their minima through LDS.  RS = 1 (128 tokens) has the least work per token; its level takes 5.3 us, of which
-// 3.7 the 16 row tiles (192 matrix instructions of 16 clk and 16 x 16 vector ones per wavefront, two wavefronts a SIMD;
-// in this order the two kinds hardly overlap: a vector instruction runs in 28 % of the matrix unit's busy cycles, in
-// k_encode_pairs, whose order is fixed, in 55 %), 0.6 the update, 0.5 the split and 0.4 waiting for rows.  RS = 8 (16 tokens) has the
-// shortest level, 1.5 us; with a split and an update per wavefront instead of shared ones it was 2.1.
-// 32000 vectors, 32 levels: 179 us, with 64 tokens per workgroup, rows staged through registers and one image 289 us;
+// exchange their minima through LDS.  RS = 8 (16 tokens) has the shortest level, 1.5 us; with a split and an update per
+// wavefront instead of shared ones it was 2.1.
 // 64 vectors, 16 levels: 25 us, with a workgroup per vector and fp32 FMAs 32 us.
 // The images sit at LDS address 0: no static LDS here.
 constexpr int kErThreads = 512;
@@ -164,7 +190,7 @@ constexpr int kErPart = kErNorms + 2 * kK * 4;         // [8 wavefronts][16 toke
 constexpr int kErSplit = kErPart + 8 * 16 * 8;         // RS >= 4: [sets][3 parts][4 kc][64 lanes] operands of the token sets
 constexpr int er_chosen(int rs) { return kErSplit + (rs >= 4 ? 8 / rs * 12 * 64 * 16 : 0); }  // [tokens][32 levels] bytes
 constexpr int er_lds(int rs) { return er_chosen(rs) + 128 / rs * 32; }
-static_assert(er_lds(1) <= 163840 && er_lds(2) <= 163840 && er_lds(4) <= 163840 && er_lds(8) <= 163840, "LDS of a compute unit");
+static_assert(er_lds(2) <= 163840 && er_lds(4) <= 163840 && er_lds(8) <= 163840, "LDS of a compute unit");
 template <int RS>
 __global__ __launch_bounds__(kErThreads) void k_encode_rows(const void *__restrict__ keys, const uint4 *__restrict__ cb,
                                                             const float *__restrict__ norms, uint8_t *__restrict__ out,
@@ -271,7 +297,7 @@ __global__ __launch_bounds__(kErThreads) void k_encode_rows(const void *__restri
             }
         }
         min4(best, brow);  // the four lanes of a token hold the minima of disjoint row sets
-        if (RS > 1) {  // ... and so do the RS wavefronts of a token set
+        {  // ... and so do the RS wavefronts of a token set
             float2 *pm = reinterpret_cast<float2 *>(lds + kErPart);
             if (gk == 0) pm[wave * 16 + n] = make_float2(best, __builtin_bit_cast(float, brow));
             __syncthreads();
@@ -295,6 +321,248 @@ __global__ __launch_bounds__(kErThreads) void k_encode_rows(const void *__restri
     }
     __syncthreads();
     if (tok < n_tokens && rs == 0) {
+        uint8_t *dst = out + tok * a.token_stride + (long long)g * a.head_stride;
+        for (int l = gk; l < a.levels; l += 4) dst[l] = chosen[tl * 32 + l];
+    }
+}
+
+// Index-form vectors, many at a time: the choices of k_encode_rows, 128 tokens per workgroup, from two thirds of its products.
+// The third part of a residual decides next to nothing.  So the costs are screened with the first two (the second rounded
+// instead of truncated), from -|c|^2 / 2 as the accumulator's start, and a row costs three vector instructions: its number
+// goes into the last six bits of r c - |c|^2 / 2, and two medians keep the largest and the second largest.  What all that can
+// be off by is bounded; where a token's second best is within the bound of its best (0.2 to 0.3 % of a Gaussian token's levels),
+// the row tiles that hold its candidates are taken again exactly as k_encode_rows does.  The codes are the same, bit for bit.
+// A level takes 7900 clk: the matrix unit needs 4200 of them (two wavefronts a SIMD, 128 products of 16 clk each; between
+// two products of a wavefront there is room for two vector instructions, and they are placed so), the choice 700, the
+// update 600, the split 650, the second look 700 on average.  4000 tokens, 8 heads, 32 levels: 136 us, with all three parts and
+// the compiler's order 177 us.  The two wavefronts of a SIMD half a level apart (a barrier for each half) took 155: a
+// wavefront by itself issues an instruction every 5 clk, and that bounds its products at 26 clk each.  Two workgroups of four
+// wavefronts with an image each, 147.  (A codebook whose every row has a twin is searched twice throughout: 335 us.)
+constexpr int kManyThreads = 512, kManyTokens = 128;
+constexpr int kManyNorms = 2 * kErImg * 16;              // [2][256] -|c|^2 / 2
+constexpr int kManyWhole = kManyNorms + 2 * kK * 4;        // [2][256] |c|^2
+constexpr int kManyTops = kManyWhole + 2 * kK * 4;         // [2][4] the largest |c|^2 / 2 of 64 rows
+constexpr int kManyChosen = kManyTops + 2 * 4 * 4;         // [128 tokens][32 levels] bytes
+constexpr int kManyLds = kManyChosen + kManyTokens * 32;
+static_assert(kManyLds <= 163840, "LDS of a compute unit");
+__global__ __launch_bounds__(kManyThreads, 2) void k_encode_many(const void *__restrict__ keys, const uint4 *__restrict__ cb,
+                                                               const float *__restrict__ norms, uint8_t *__restrict__ out,
+                                                               const EncodeDims a, int n_tokens)
+{
+    extern __shared__ __attribute__((aligned(16))) uint4 many_mem[];
+    char *lds = reinterpret_cast<char *>(many_mem);
+    uint8_t *chosen = reinterpret_cast<uint8_t *>(lds + kManyChosen);
+    float *tops = reinterpret_cast<float *>(lds + kManyTops);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 15, gk = lane >> 4;
+    const bool norms_too = wave < 4;                       // (these are through with a level's products first)
+    const int g = blockIdx.x % a.Hkv;
+    const int tl = wave * 16 + n;  // token within the workgroup
+    const long long tok = (long long)(blockIdx.x / a.Hkv) * kManyTokens + tl;
+    const size_t tokc = (size_t)(tok < n_tokens ? tok : n_tokens - 1);
+    const uint4 *rows = cb + (size_t)g * a.levels * kErImg;
+    const float *nrows = norms + (size_t)g * a.levels * kK;
+    auto fetch_rows = [&](int l, int buf, int i) __attribute__((always_inline)) {  // rows 32 wave + 4 i .. + 3, slots as in k_encode_rows
+        const int r0 = 32 * wave + 4 * i, t = r0 + gk;
+        lds_dma16(rows + (size_t)l * kErImg, (unsigned)(t * 16 + ((lane ^ t) & 15)) * 16u, (unsigned)(buf * kErImg + r0 * 16) * 16u);
+    };
+    float norm = 0.f;
+    auto put_norms = [&](int buf) __attribute__((always_inline)) {  // wavefronts 0 to 3
+        const float half = 0.5f * norm, top = wave_max(half);
+        reinterpret_cast<float *>(lds + kManyNorms)[buf * kK + tid] = -half;
+        reinterpret_cast<float *>(lds + kManyWhole)[buf * kK + tid] = norm;
+        if (lane == 0) tops[buf * 4 + wave] = top;
+    };
+#pragma unroll
+    for (int i = 0; i < 8; ++i) fetch_rows(0, 0, i);
+    if (norms_too) {
+        norm = nrows[tid];
+        put_norms(0);
+    }
+    float res[32];
+#pragma unroll
+    for (int kc = 0; kc < 4; ++kc) {  // elements 32 kc + 8 gk .. + 7 of the token
+        const size_t at = (tokc * a.Hkv + g) * kD + 32 * kc + 8 * gk;
+        if (a.key_bf16) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const uint2 v = *reinterpret_cast<const uint2 *>(static_cast<const uint16_t *>(keys) + at + 4 * i);
+                res[8 * kc + 4 * i] = bf16_lo(v.x); res[8 * kc + 4 * i + 1] = bf16_hi(v.x);
+                res[8 * kc + 4 * i + 2] = bf16_lo(v.y); res[8 * kc + 4 * i + 3] = bf16_hi(v.y);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const float4 v = *reinterpret_cast<const float4 *>(static_cast<const float *>(keys) + at + 4 * i);
+                res[8 * kc + 4 * i] = v.x; res[8 * kc + 4 * i + 1] = v.y; res[8 * kc + 4 * i + 2] = v.z; res[8 * kc + 4 * i + 3] = v.w;
+            }
+        }
+    }
+    uint4_t part[2][4];
+    float third, whole2 = 0.f;  // the third part's norm and the squared norm of the residual are at most this
+#pragma unroll
+    for (int i = 0; i < 32; ++i) whole2 = __builtin_fmaf(res[i], res[i], whole2);
+    whole2 = sum4(whole2) * 1.0001f + 1e-34f;
+    auto split = [&]() __attribute__((always_inline)) {
+        float rest2[2] = {0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            float v0 = res[2 * i], v1 = res[2 * i + 1];
+            const unsigned u0 = __builtin_bit_cast(unsigned, v0), u1 = __builtin_bit_cast(unsigned, v1);
+            const unsigned hi = __builtin_amdgcn_perm(u1, u0, 0x07060302u);  // the upper halves
+            v0 -= __builtin_bit_cast(float, u0 & 0xffff0000u);
+            v1 -= __builtin_bit_cast(float, u1 & 0xffff0000u);
+            const floatx2_t rest = {v0, v1};
+            const unsigned mid = __builtin_bit_cast(unsigned, __builtin_convertvector(rest, bf16x2_t));
+            rest2[0] = __builtin_fmaf(v0, v0, rest2[0]);
+            rest2[1] = __builtin_fmaf(v1, v1, rest2[1]);
+            part[0][i >> 2][i & 3] = hi;
+            part[1][i >> 2][i & 3] = mid;
+        }
+        // what rounding to the second part leaves is at most 2^-8 of it; 1 % covers this sum's own rounding
+        third = 0.00395f * __builtin_amdgcn_sqrtf(sum4(rest2[0] + rest2[1]) + 1e-34f);
+    };
+    split();
+    const unsigned keep = opaque_sgpr(0xffffffc0u);
+    const float inf = __builtin_bit_cast(float, opaque_sgpr(0x7f800000u));
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // level 0 has landed
+    __syncthreads();
+    for (int l = 0; l < a.levels; ++l) {
+        const char *img = lds + (l & 1) * kErImg * 16;
+        const float *nrm = reinterpret_cast<const float *>(lds + kManyNorms) + (l & 1) * kK;
+        auto rows_of = [&](int t, int kc) __attribute__((always_inline)) {
+            return *reinterpret_cast<const uint4_t *>(img + (t * 16 + n) * 256 + ((4 * kc + gk) ^ n) * 16);
+        };
+        auto mul = [&](const uint4_t &r, const uint4_t &x, const floatx4_t &d) __attribute__((always_inline)) {
+            return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, r), __builtin_bit_cast(bf16x8_t, x), d, 0, 0, 0);
+        };
+        // multiply: two row tiles at a time, with the medians of the two before them between the matrix instructions
+        const int next = l + 1 < a.levels ? l + 1 : l;     // (the last level is sent once more, to nobody)
+        norm = nrows[(unsigned)(next * kK + (tid & (kK - 1)))];
+        uint4_t A[2][4][2];
+        floatx4_t D[2][2], start[2];
+        auto norms_of = [&](int t) __attribute__((always_inline)) { return *reinterpret_cast<const floatx4_t *>(nrm + t * 16 + 4 * gk); };
+#pragma unroll
+        for (int e = 0; e < 2; ++e) start[e] = norms_of(e);
+#pragma unroll
+        for (int kc = 0; kc < 4; ++kc)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) A[0][kc][e] = rows_of(e, kc);
+        float best = -INFINITY, second = -INFINITY, sc = 0.f;
+#pragma unroll
+        for (int t = 0; t <= 16; t += 2) {
+            const int cur = (t >> 1) & 1, old = cur ^ 1;
+#pragma unroll
+            for (int m = 0; m < 16; ++m) {                 // a matrix instruction (16 clk), one or two vector ones, a read or none
+                const int st = m >> 1, kc = st >> 1, e = m & 1;
+                if (t < 16) D[cur][e] = mul(A[cur][kc][e], part[st & 1][kc], st == 0 ? start[e] : D[cur][e]);
+                if (t > 0)
+#pragma unroll
+                    for (int u = (24 * m) / 16; u < (24 * m + 24) / 16; ++u) {
+                        const int i = u / 3;
+                        const float d = D[old][i >> 2][i & 3];  // (a bit cast of the element itself would read element 0)
+                        if (u % 3 == 0) sc = __builtin_bit_cast(float, (__builtin_bit_cast(unsigned, d) & keep) | (unsigned)(4 * (t - 2) + i));
+                        if (u % 3 == 1) second = __builtin_amdgcn_fmed3f(best, second, sc);
+                        if (u % 3 == 2) best = __builtin_amdgcn_fmed3f(best, sc, inf);  // the larger one
+                    }
+                if (t < 14) {
+                    if (!(m & 1)) A[old][m >> 2][(m >> 1) & 1] = rows_of(t + 2 + ((m >> 1) & 1), m >> 2);
+                    if (m == 3 || m == 5) start[(m >> 1) - 1] = norms_of(t + 2 + (m >> 1) - 1);
+                }
+                if (t < 16 && m == 7) fetch_rows(next, (l + 1) & 1, t >> 1);
+                if (t > 0) asm volatile("" : "+v"(best), "+v"(second), "+v"(sc));  // here, not where they are used
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (norms_too) put_norms((l + 1) & 1);
+        const float4 t4 = *reinterpret_cast<const float4 *>(tops + (l & 1) * 4);
+        // choose
+        float lo = best, up = second;
+        two_largest16(lo, up);
+        two_largest32(lo, up);
+        const unsigned long long who = __ballot(best == lo);  // one lane of the token's four
+        const unsigned w0 = (unsigned)who >> n, w1 = (unsigned)(who >> 32) >> n;
+        const int at = (int)(__builtin_bit_cast(unsigned, lo) & 63u);
+        int brow = (at >> 2) * 16 + 4 * (int)(((w0 >> 16) & 1u) + 2u * (w1 & 1u) + 3u * ((w1 >> 16) & 1u)) + (at & 3);
+        // A cost is off by the third part, |r''| |c|; by the last six bits, 2^-17 of it; and by the roundings of the sums, 8 here
+        // and 13 in k_encode_rows, of at most |c|^2 / 2 + |r| |c|.  Overflow and NaN fail a comparison.
+        const float top = fmaxf(fmaxf(t4.x, t4.y), fmaxf(t4.z, t4.w)), cmax = __builtin_amdgcn_sqrtf(2.f * top + 1e-34f), rc = 1.01f * __builtin_amdgcn_sqrtf(whole2) * cmax;
+        const float bound = 2.f * third * cmax + 1.6e-5f * fabsf(lo) + 7.7e-6f * (top + rc);
+        const float left = __builtin_fmaf(whole2, 1.000001f, 4.f * bound - 2.f * lo);  // |r - c|^2 = |r|^2 - 2 (r c - |c|^2 / 2)
+        whole2 = left < 1e-34f ? 1e-34f : left;            // (not fmaxf: NaN has to stay, and to fail the comparison below)
+        const bool near = !(lo - up > bound && rc < 1e37f);
+        if (__any(near)) {
+            // the row tiles that hold a near token's candidates: the lanes' best, or all tiles if a lane's second best is one too
+            unsigned long long hold = __ballot(near && best >= lo - bound);
+            unsigned tiles = 0u;
+            if (__any(near && !(second < lo - bound && rc < 1e37f))) {
+                tiles = 0xffffu;
+            } else {
+                for (; hold; hold &= hold - 1)
+                    tiles |= 1u << (__builtin_amdgcn_readlane(__builtin_bit_cast(int, best), __builtin_ctzll(hold)) >> 2 & 15);
+            }
+            uint4_t exact[3][4];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                float v0 = res[2 * i], v1 = res[2 * i + 1];
+#pragma unroll
+                for (int s3 = 0; s3 < 3; ++s3) {
+                    const unsigned u0 = __builtin_bit_cast(unsigned, v0), u1 = __builtin_bit_cast(unsigned, v1);
+                    exact[s3][i >> 2][i & 3] = __builtin_amdgcn_perm(u1, u0, 0x07060302u);
+                    v0 -= __builtin_bit_cast(float, u0 & 0xffff0000u);
+                    v1 -= __builtin_bit_cast(float, u1 & 0xffff0000u);
+                }
+            }
+            float least = INFINITY;
+            int row = 0;
+            while (tiles) {                                // two at a time; rows come in increasing order: ties keep the lowest
+                int t[2];
+                t[0] = __builtin_ctz(tiles);
+                tiles &= tiles - 1;
+                t[1] = tiles ? __builtin_ctz(tiles) : t[0];
+                tiles &= tiles - 1;
+                floatx4_t nr[2], E[2];
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    nr[e] = *reinterpret_cast<const floatx4_t *>(lds + kManyWhole + ((l & 1) * kK + t[e] * 16 + 4 * gk) * 4);
+                    E[e] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+                }
+#pragma unroll
+                for (int kc = 0; kc < 4; ++kc) {
+                    const uint4_t r[2] = {rows_of(t[0], kc), rows_of(t[1], kc)};
+#pragma unroll
+                    for (int s3 = 0; s3 < 3; ++s3)
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) E[e] = mul(r[e], exact[s3][kc], E[e]);
+                }
+#pragma unroll
+                for (int e = 0; e < 2; ++e)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const float sc = nr[e][r] - 2.f * E[e][r];
+                        if (sc < least) { least = sc; row = t[e] * 16 + 4 * gk + r; }
+                    }
+            }
+            min4(least, row);
+            brow = near ? row : brow;
+        }
+        if (gk == 0) chosen[tl * 32 + l] = (uint8_t)brow;
+        // residual -= chosen row (the lane's elements of it)
+#pragma unroll
+        for (int kc = 0; kc < 4; ++kc) {
+            const uint4 w = *reinterpret_cast<const uint4 *>(img + brow * 256 + ((4 * kc + gk) ^ (brow & 15)) * 16);
+            const unsigned ws[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                res[8 * kc + 2 * i] -= bf16_lo(ws[i]);
+                res[8 * kc + 2 * i + 1] -= bf16_hi(ws[i]);
+            }
+        }
+        split();
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's rows of level l + 1 have landed
+        __syncthreads();                                   // ... and everybody's, and level l is no longer read
+    }
+    if (tok < n_tokens) {
         uint8_t *dst = out + tok * a.token_stride + (long long)g * a.head_stride;
         for (int l = gk; l < a.levels; l += 4) dst[l] = chosen[tl * 32 + l];
     }
@@ -769,17 +1037,26 @@ commvq_status launch_encode_rows(const void *keys, const void *cb, const float *
     return hipGetLastError() == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;
 }
 
+commvq_status launch_encode_many(const void *keys, const void *cb, const float *norms, uint8_t *out, const EncodeDims &d, int n_tokens, hipStream_t s)
+{
+    static std::atomic<uint64_t> lds_ok{0};
+    if (allow_dynamic_lds(&k_encode_many, kManyLds, lds_ok) != hipSuccess) return COMMVQ_ERR_LAUNCH;
+    hipLaunchKernelGGL(k_encode_many, dim3((unsigned)((n_tokens + kManyTokens - 1) / kManyTokens * d.Hkv)), dim3(kManyThreads), kManyLds, s, keys,
+                       static_cast<const uint4 *>(cb), norms, out, d, n_tokens);
+    return hipGetLastError() == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;
+}
+
 commvq_status encode_rows(const void *keys, const void *cb, const float *norms, uint8_t *out, const EncodeDims &d, int n_tokens,
                           hipStream_t s)
 {
     // A compute unit holds one workgroup, so a launch of up to 256 is one round, and a round is the cheaper the more
     // wavefronts share a token set: 32 levels of 8 heads take 47 us with RS = 8 (up to 512 tokens), 76 (4; 1024), 112
-    // (2; 2048), 172 (1; 4096).  So full rounds go to RS = 1, and the rest to the largest RS that needs one round:
-    // 4097 tokens in one launch of RS = 1 would take 323 us.
+    // (2; 2048), 136 with k_encode_many (4096).  So full rounds go to the latter, and the rest to the largest RS that needs
+    // one round.
     const int64_t round = 128 * (int64_t)std::max(1, 256 / d.Hkv);
     const int full = (int)(n_tokens / round * round), rest = n_tokens - full;
     if (full) {
-        const commvq_status st = launch_encode_rows<1>(keys, cb, norms, out, d, full, s);
+        const commvq_status st = launch_encode_many(keys, cb, norms, out, d, full, s);
         if (st != COMMVQ_OK || !rest) return st;
         keys = static_cast<const char *>(keys) + (size_t)full * d.Hkv * kD * (d.key_bf16 ? 2 : 4);
         out += full * d.token_stride;
@@ -788,7 +1065,7 @@ commvq_status encode_rows(const void *keys, const void *cb, const float *norms, 
     if (one_round(16)) return launch_encode_rows<8>(keys, cb, norms, out, d, rest, s);
     if (one_round(32)) return launch_encode_rows<4>(keys, cb, norms, out, d, rest, s);
     if (one_round(64)) return launch_encode_rows<2>(keys, cb, norms, out, d, rest, s);
-    return launch_encode_rows<1>(keys, cb, norms, out, d, rest, s);
+    return launch_encode_many(keys, cb, norms, out, d, rest, s);
 }
 
 template <int RS>
