@@ -125,6 +125,39 @@ __device__ __forceinline__ void lds_dma16(const void *base_uniform, unsigned off
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_byte_addr_uniform), "v"(offset), "s"(base_uniform) : "memory");
 }
 
+// Softmax statistics of one head over tokens v0 .. of a sequence, by a wavefront, from the (max, sum of exp(logit - max)) of the ns
+// score tiles of split_len tokens: the maximum of the sequence, the exp-sum of the tiles ta .. tb - 1 that the range touches, and
+// of those that BEGIN inside it (a tile shared by two ranges is counted once).  Every load is requested before
+// the first is waited for.  128K tokens have 256 tiles: four rounds of 64 for the maximum and as many again for the sums, each
+// after the one before, took k_values 20.8 us instead of 19.7, k_vbits 24.0 instead of 22.7; one fp32 head of 4096 tokens, in tiles
+// of 16, 7.0 instead of 5.9.
+struct RangeStats {
+    float2 first[4], own;
+    __device__ __forceinline__ void request(const float2 *st, int ns, int ta, int tb, int lane)
+    {
+        const int k = ta + ((lane - ta) & 63);
+        own = k < tb ? st[k] : make_float2(-INFINITY, 0.f);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) first[i] = lane + 64 * i < ns ? st[lane + 64 * i] : make_float2(-INFINITY, 0.f);
+    }
+    __device__ __forceinline__ void finish(const float2 *st, int ns, int ta, int tb, int split_len, int v0, int lane, float &mx, float &l, float &lown) const
+    {
+        mx = fmaxf(fmaxf(first[0].x, first[1].x), fmaxf(first[2].x, first[3].x));
+        for (int k = lane + 256; k < ns; k += 64) mx = fmaxf(mx, st[k].x);
+        mx = wave_max(mx);
+        l = lown = 0.f;
+        float2 s = own;
+        for (int k = ta + ((lane - ta) & 63); k < tb; k += 64) {
+            if (k >= ta + 64) s = st[k];
+            const float t = s.y * __builtin_amdgcn_exp2f((s.x - mx) * kLog2e);
+            l += t;
+            if (k * split_len >= v0) lown += t;
+        }
+        l = wave_sum(l);
+        lown = wave_sum(lown);
+    }
+};
+
 __device__ __forceinline__ float bf16_lo(unsigned v) { return __builtin_bit_cast(float, v << 16); }
 __device__ __forceinline__ float bf16_hi(unsigned v) { return __builtin_bit_cast(float, v & 0xffff0000u); }
 

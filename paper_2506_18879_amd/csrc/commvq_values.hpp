@@ -204,27 +204,12 @@ __global__ __launch_bounds__(NT, S > 1 ? 2 : 4) void k_values(const ValuesArgs a
         }
         const int ns = min((L + a.split_len - 1) / a.split_len, a.nsplit);
         const float2 *st = a.sstat + ((size_t)b * a.Hq + (size_t)g * G + hh) * a.nsplit;
-        // the first 64 tiles' statistics stay in registers: one round of loads serves both passes
-        const float2 first = lane < ns ? st[lane] : make_float2(-INFINITY, 0.f);
-        float mx = first.x;
-        for (int k = lane + 64; k < ns; k += 64) mx = fmaxf(mx, st[k].x);
-        mx = wave_max(mx);
-        // l bounds every bin of the range: all tiles that it touches; what it reports towards the softmax denominator (lown)
-        // are the tiles that BEGIN inside it, so that a tile shared by two ranges is counted once
+        // the exp-sum l of all tiles that the range touches bounds every bin; what it reports towards the softmax denominator is lown
         const int ta = v0 / a.split_len, tb = min((v1 + a.split_len - 1) / a.split_len, ns);
-        float l = 0.f, lown = 0.f;
-        if (lane >= ta && lane < tb) {
-            l = first.y * __builtin_amdgcn_exp2f((first.x - mx) * kLog2e);
-            if (lane * a.split_len >= v0) lown = l;
-        }
-        for (int k = lane + 64; k < tb; k += 64)
-            if (k >= ta) {
-                const float t = st[k].y * __builtin_amdgcn_exp2f((st[k].x - mx) * kLog2e);
-                l += t;
-                if (k * a.split_len >= v0) lown += t;
-            }
-        l = wave_sum(l);
-        lown = wave_sum(lown);
+        RangeStats stats;
+        stats.request(st, ns, ta, tb, lane);
+        float mx, l, lown;
+        stats.finish(st, ns, ta, tb, a.split_len, v0, lane, mx, l, lown);
         int sh = 0;
         if (l >= 1e-30f) sh = min(30 - ilogbf(l), 120);
         if (lane == 0) {

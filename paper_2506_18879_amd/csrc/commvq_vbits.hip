@@ -103,11 +103,12 @@ __global__ __launch_bounds__(kVbThreads) void k_vbits(VbitsArgs a)
     // (what it reports towards the softmax denominator).
     constexpr int HPW = kVbitsHeads / (kVbThreads / 64);  // heads per wavefront
     const int ns = min((L + a.split_len - 1) / a.split_len, a.nsplit);
-    float2 first[HPW];  // the first 64 tiles' statistics of every head, requested together
+    const int sa = v0 / a.split_len, sb = min((v1 + a.split_len - 1) / a.split_len, ns);
+    RangeStats stats[HPW];  // of every head, requested together
 #pragma unroll
     for (int u = 0; u < HPW; ++u) {
         const int h = h0 + wave + (kVbThreads / 64) * u;
-        first[u] = (h < a.Hq && lane < ns) ? a.sstat[((size_t)b * a.Hq + h) * a.nsplit + lane] : make_float2(-INFINITY, 0.f);
+        stats[u].request(a.sstat + ((size_t)b * a.Hq + min(h, a.Hq - 1)) * a.nsplit, ns, sa, sb, lane);
     }
 #pragma unroll
     for (int u = 0; u < HPW; ++u) {
@@ -116,24 +117,8 @@ __global__ __launch_bounds__(kVbThreads) void k_vbits(VbitsArgs a)
             if (lane == 0) eoff_s[hl] = 0.f;
             continue;
         }
-        const float2 *st = a.sstat + ((size_t)b * a.Hq + h) * a.nsplit;
-        float mx = first[u].x;
-        for (int s = lane + 64; s < ns; s += 64) mx = fmaxf(mx, st[s].x);
-        mx = wave_max(mx);
-        const int sa = v0 / a.split_len, sb = min((v1 + a.split_len - 1) / a.split_len, ns);
-        float l = 0.f, lown = 0.f;
-        if (lane >= sa && lane < sb) {
-            l = first[u].y * __builtin_amdgcn_exp2f((first[u].x - mx) * kLog2e);
-            if (lane * a.split_len >= v0) lown = l;
-        }
-        for (int s = lane + 64; s < sb; s += 64)
-            if (s >= sa) {
-                const float t = st[s].y * __builtin_amdgcn_exp2f((st[s].x - mx) * kLog2e);
-                l += t;
-                if (s * a.split_len >= v0) lown += t;
-            }
-        l = wave_sum(l);
-        lown = wave_sum(lown);
+        float mx, l, lown;
+        stats[u].finish(a.sstat + ((size_t)b * a.Hq + h) * a.nsplit, ns, sa, sb, a.split_len, v0, lane, mx, l, lown);
         int S = 0;
         if (l >= 1e-30f) S = min(29 - ilogbf(l), 120);
         if (lane == 0) {
