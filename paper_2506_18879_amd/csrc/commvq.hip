@@ -44,7 +44,7 @@ struct Workspace {
     // written and read by the value and output stages only
     float *vscale;    // [B * Hq * value_splits] 2^-S: value of one fixed-point unit of that split's bins
     float *lsum;      // [B * Hq * value_splits] sum of exp(logit - sequence max) over the score tiles that begin in that value split
-    unsigned *bins;   // [B * Hkv * value_splits][K][Mv][G] fixed-point bins (codeword-major: see k_bins)
+    unsigned *bins;   // [B * Hkv * value_splits][K][Mv][G] fixed-point bins (binary values; stage calls of indexed ones)
     float *partial;   // [B * Hq * out_chunks][d]
     uint4 *packed_val;    // value codebook re-laid for k_out_mfma (batches; only if the caller has not packed it)
     // written and read by the score stage only, in the same memory as the above; in front of them, right behind `scores`, the
