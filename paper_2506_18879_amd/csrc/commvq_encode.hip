@@ -326,6 +326,207 @@ __global__ __launch_bounds__(kErThreads) void k_encode_rows(const void *__restri
     }
 }
 
+// Index-form vectors, few at a time (a decode step appends one token per sequence): the matrix product of k_encode_rows, shaped
+// for the latency of a level, since the levels are a dependent chain.  The exact three-way split of up to five residuals is
+// 15 columns of ONE second operand, so a level costs a wavefront (32 of the 256 rows) 8 matrix instructions and 12 operand
+// reads of LDS, where k_encode_rows<8> takes a part after the other: 24 and 20; the sums of a token's three parts are added by
+// two row shifts.  Two more wavefronts do nothing but send the next level's rows (64 KiB, memory -> LDS): 8 sends of every
+// wavefront in a row hold it up for as long as its products take.
+// Per level: products, minimum over a lane's 8 rows, the 32 minima of a token through LDS; then wavefront w < 5 (two elements of
+// token w's residual a lane) finds the least, subtracts the row and leaves the parts of the next level's operand.
+// Second operand: lane (n, g) supplies elements 32 kc + 8 g .. + 7 of column n; piece s = 4 kc + g of column n sits in slot n xor s
+// of 16, so that neither the reads nor the writes of a token's 64 lanes collide.  The images sit at LDS address 0.
+// What bounds it: the rows' way into one compute unit's LDS, 64 KiB in 0.95 us.  64 vectors, 16 levels, codebook in the L2: 18.2 us
+// (k_encode_rows<8> 24.8; rows sent by the eight wavefronts themselves 22.5; loaded into registers straight from memory in operand order,
+// 64 cache lines an instruction, 38), 32 levels 33.8 (47.2); codebook from the last-level cache 22 (25).  Words of the levels after the
+// next asked for early, into the L2: 26.  Up to 160 tokens of 8 heads (one round of workgroups): 37.1 (48.4).
+constexpr int kFewTok = 5, kFewThreads = 640;
+constexpr int kFewParts = 2 * kErImg * 16;             // [16 pieces][16 slots] 16 bytes
+constexpr int kFewMin = kFewParts + 16 * 16 * 16;      // [5 tokens][8 wavefronts][4] least cost of 8 rows, its row, the second least
+constexpr int kFewTop = kFewMin + kFewTok * 32 * 16;   // [2] the largest |c|^2 of a level
+constexpr int kFewLds = kFewTop + 2 * 4;
+static_assert(kFewLds <= 163840, "LDS of a compute unit");
+__global__ __launch_bounds__(kFewThreads) void k_encode_few(const void *__restrict__ keys, const uint4 *__restrict__ cb,
+                                                            const float *__restrict__ norms, uint8_t *__restrict__ out,
+                                                            const EncodeDims a, int n_tokens)
+{
+    extern __shared__ __attribute__((aligned(16))) uint4 few_mem[];
+    char *lds = reinterpret_cast<char *>(few_mem);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 15, gk = lane >> 4;
+    const int g = blockIdx.x % a.Hkv;
+    const uint4 *rows = cb + (size_t)g * a.levels * kErImg;
+    const float4 *all_norms = reinterpret_cast<const float4 *>(norms + (size_t)g * a.levels * kK);  // 64 a level
+    float *tops = reinterpret_cast<float *>(lds + kFewTop);
+    if (wave >= 8) {                                       // the senders: slots as in k_encode_rows
+        auto send = [&](int l, int half) __attribute__((always_inline)) {
+            const uint4 *src = rows + (size_t)l * kErImg;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int r0 = half * 128 + (wave - 8) * 64 + 4 * i, t = r0 + gk;
+                lds_dma16(src, (unsigned)(t * 16 + ((lane ^ t) & 15)) * 16u, (unsigned)((l & 1) * kErImg + r0 * 16) * 16u);
+            }
+        };
+        float4 nq = all_norms[lane];
+        send(0, 0);
+        send(0, 1);
+        for (int l = 0; l < a.levels; ++l) {
+            const float top = wave_max(fmaxf(fmaxf(nq.x, nq.y), fmaxf(nq.z, nq.w)));  // of level l
+            if (wave == 8 && lane == 0) tops[l & 1] = top;  // (of level l - 2 nothing is read any more)
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // level l has landed
+            __syncthreads();
+            nq = all_norms[(l + 1 < a.levels ? l + 1 : l) * 64 + lane];
+            if (l + 1 < a.levels) send(l + 1, 0);
+            __syncthreads();
+            if (l + 1 < a.levels) send(l + 1, 1);
+        }
+        return;
+    }
+    const long long tok = (long long)(blockIdx.x / a.Hkv) * kFewTok + wave;  // the token whose residual the wavefront keeps
+    const bool owner = wave < kFewTok;
+    const float4 *nrows = all_norms + 8 * wave + gk;
+    float4 next_norm[2] = {nrows[0], nrows[4]};
+    float r0 = 0.f, r1 = 0.f;                              // elements 2 lane, 2 lane + 1
+    if (owner && tok < n_tokens) {
+        const size_t at = ((size_t)tok * a.Hkv + g) * kD + 2 * lane;
+        if (a.key_bf16) {
+            const uint16_t *k = static_cast<const uint16_t *>(keys) + at;
+            r0 = __builtin_bit_cast(float, (unsigned)k[0] << 16);
+            r1 = __builtin_bit_cast(float, (unsigned)k[1] << 16);
+        } else {
+            const float *k = static_cast<const float *>(keys) + at;
+            r0 = k[0];
+            r1 = k[1];
+        }
+    }
+    auto put_parts = [&]() __attribute__((always_inline)) {
+        const int piece = lane >> 2;
+        float v0 = r0, v1 = r1;
+#pragma unroll
+        for (int s3 = 0; s3 < 3; ++s3) {
+            const unsigned u0 = __builtin_bit_cast(unsigned, v0), u1 = __builtin_bit_cast(unsigned, v1);
+            reinterpret_cast<unsigned *>(lds + kFewParts)[(piece * 16 + ((3 * wave + s3) ^ piece)) * 4 + (lane & 3)] = __builtin_amdgcn_perm(u1, u0, 0x07060302u);
+            v0 -= __builtin_bit_cast(float, u0 & 0xffff0000u);
+            v1 -= __builtin_bit_cast(float, u1 & 0xffff0000u);
+        }
+    };
+    float whole2 = wave_sum(r0 * r0 + r1 * r1) * 1.0001f + 1e-34f;  // at least the squared norm of the residual
+    if (owner) put_parts();
+    else if (wave == kFewTok && lane < 16) reinterpret_cast<uint4 *>(lds + kFewParts)[lane * 16 + (15 ^ lane)] = make_uint4(0u, 0u, 0u, 0u);
+    unsigned keep = 0u;                                    // lane l: the row chosen in level l
+    float4 *pm = reinterpret_cast<float4 *>(lds + kFewMin);
+    for (int l = 0; l < a.levels; ++l) {
+        const char *img = lds + (l & 1) * kErImg * 16;
+        __syncthreads();                                   // the rows and the operand are there
+        uint4_t A[2][4], B[4];
+#pragma unroll
+        for (int kc = 0; kc < 4; ++kc) {
+            B[kc] = *reinterpret_cast<const uint4_t *>(lds + kFewParts + ((4 * kc + gk) * 16 + (n ^ (4 * kc + gk))) * 16);
+#pragma unroll
+            for (int t = 0; t < 2; ++t) A[t][kc] = *reinterpret_cast<const uint4_t *>(img + (32 * wave + 16 * t + n) * 256 + ((4 * kc + gk) ^ n) * 16);
+        }
+        const float nv[2][4] = {{next_norm[0].x, next_norm[0].y, next_norm[0].z, next_norm[0].w}, {next_norm[1].x, next_norm[1].y, next_norm[1].z, next_norm[1].w}};
+        floatx4_t D[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int kc = 0; kc < 4; ++kc)
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+                D[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, A[t][kc]), __builtin_bit_cast(bf16x8_t, B[kc]), D[t], 0, 0, 0);
+        float best = INFINITY, second = INFINITY;
+        int brow = 0;
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float d = D[t][r], dot = d + (dpp_mov<0x101>(d) + dpp_mov<0x102>(d));  // columns n + 1, n + 2: the smaller parts
+                const float sc = nv[t][r] - 2.f * dot;
+                second = __builtin_amdgcn_fmed3f(best, second, sc);
+                if (sc < best) { best = sc; brow = 32 * wave + 16 * t + 4 * gk + r; }  // rows come in increasing order: ties keep the lowest
+            }
+        const int tk = n / 3;
+        if (n < 15 && n == 3 * tk) pm[(tk * 8 + wave) * 4 + gk] = make_float4(best, __builtin_bit_cast(float, brow), second, 0.f);
+        {
+            const int next = l + 1 < a.levels ? l + 1 : l;
+            next_norm[0] = nrows[next * (kK / 4)];
+            next_norm[1] = nrows[next * (kK / 4) + 4];
+        }
+        __syncthreads();
+        if (owner) {
+            const float4 o = pm[wave * 32 + (lane & 31)];  // lanes 32 .. 63 as 0 .. 31
+            const float cc = tops[l & 1], m = -wave_max(-o.x);
+            const int win = __builtin_ctz((unsigned)__ballot(o.x == m) | 0x80000000u);
+            const float up = -wave_max(-((lane & 31) == win ? o.z : o.x));  // (of two equal ones: the same again)
+            int row = __builtin_amdgcn_readlane(__builtin_bit_cast(int, o.y), win);
+            // The sums here and in k_encode_rows are of the same products: 5 and 12 roundings of at most |r| |c| each, twice in a
+            // cost, and one of the cost itself.  If the second least cost is within what that can amount to for two rows, or
+            // something overflows or is not a number, the row tiles of the candidates are taken again in the order of
+            // k_encode_rows: its codes, bit for bit.
+            const float rc = 1.01f * __builtin_amdgcn_sqrtf(whole2 * (cc + 1e-34f)), bound = 9e-6f * rc + 5e-7f * cc;
+            const float left = __builtin_fmaf(whole2, 1.000001f, m + 2.f * bound);  // |r - c|^2 = |r|^2 + (|c|^2 - 2 r c)
+            whole2 = left < 1e-34f ? 1e-34f : left;        // (not fmaxf: NaN has to stay)
+            if (__any(!(up - m > bound && rc < 1e37f))) {
+                uint4_t part[3][4];
+#pragma unroll
+                for (int s3 = 0; s3 < 3; ++s3)
+#pragma unroll
+                    for (int kc = 0; kc < 4; ++kc)
+                        part[s3][kc] = *reinterpret_cast<const uint4_t *>(lds + kFewParts + ((4 * kc + gk) * 16 + ((3 * wave + s3) ^ (4 * kc + gk))) * 16);
+                unsigned tiles = 0u;
+                if (__any(!(o.z > m + bound && rc < 1e37f))) {  // two of a lane's 8 rows
+                    tiles = 0xffffu;
+                } else {
+                    for (unsigned hold = (unsigned)__ballot(o.x <= m + bound); hold; hold &= hold - 1)
+                        tiles |= 1u << (__builtin_amdgcn_readlane(__builtin_bit_cast(int, o.y), __builtin_ctz(hold)) >> 4 & 15);
+                }
+                float least = INFINITY;
+                row = 0;
+                while (tiles) {                            // two at a time; rows come in increasing order: ties keep the lowest
+                    int t[2];
+                    t[0] = __builtin_ctz(tiles);
+                    tiles &= tiles - 1;
+                    t[1] = tiles ? __builtin_ctz(tiles) : t[0];
+                    tiles &= tiles - 1;
+                    float4 nr[2];
+                    floatx4_t E[2];
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        nr[e] = all_norms[(unsigned)(l * 64 + 4 * t[e] + gk)];
+                        E[e] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+                    }
+#pragma unroll
+                    for (int kc = 0; kc < 4; ++kc) {
+                        uint4_t x[2];
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) x[e] = *reinterpret_cast<const uint4_t *>(img + (16 * t[e] + n) * 256 + ((4 * kc + gk) ^ n) * 16);
+#pragma unroll
+                        for (int s3 = 0; s3 < 3; ++s3)
+#pragma unroll
+                            for (int e = 0; e < 2; ++e)
+                                E[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, x[e]), __builtin_bit_cast(bf16x8_t, part[s3][kc]), E[e], 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        const float ev[4] = {nr[e].x, nr[e].y, nr[e].z, nr[e].w};
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const float sc = ev[r] - 2.f * E[e][r];
+                            if (sc < least) { least = sc; row = 16 * t[e] + 4 * gk + r; }
+                        }
+                    }
+                }
+                min4(least, row);
+                row = __builtin_amdgcn_readfirstlane(row);
+            }
+            keep = lane == l ? (unsigned)row : keep;
+            const unsigned v = *reinterpret_cast<const unsigned *>(img + row * 256 + (((lane >> 2) ^ row) & 15) * 16 + (lane & 3) * 4);
+            r0 -= bf16_lo(v);
+            r1 -= bf16_hi(v);
+            put_parts();
+        }
+    }
+    if (owner && tok < n_tokens && lane < a.levels) out[tok * a.token_stride + (long long)g * a.head_stride + lane] = (uint8_t)keep;
+}
+
 // Index-form vectors, many at a time: the choices of k_encode_rows, 128 tokens per workgroup, from two thirds of its products.
 // The third part of a residual decides next to nothing.  So the costs are screened with the first two (the second rounded
 // instead of truncated), from -|c|^2 / 2 as the accumulator's start, and a row costs three vector instructions: its number
@@ -1037,6 +1238,15 @@ commvq_status launch_encode_rows(const void *keys, const void *cb, const float *
     return hipGetLastError() == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;
 }
 
+commvq_status launch_encode_few(const void *keys, const void *cb, const float *norms, uint8_t *out, const EncodeDims &d, int n_tokens, hipStream_t s)
+{
+    static std::atomic<uint64_t> lds_ok{0};
+    if (allow_dynamic_lds(&k_encode_few, kFewLds, lds_ok) != hipSuccess) return COMMVQ_ERR_LAUNCH;
+    hipLaunchKernelGGL(k_encode_few, dim3((unsigned)((n_tokens + kFewTok - 1) / kFewTok * d.Hkv)), dim3(kFewThreads), kFewLds, s, keys,
+                       static_cast<const uint4 *>(cb), norms, out, d, n_tokens);
+    return hipGetLastError() == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;
+}
+
 commvq_status launch_encode_many(const void *keys, const void *cb, const float *norms, uint8_t *out, const EncodeDims &d, int n_tokens, hipStream_t s)
 {
     static std::atomic<uint64_t> lds_ok{0};
@@ -1050,9 +1260,9 @@ commvq_status encode_rows(const void *keys, const void *cb, const float *norms, 
                           hipStream_t s)
 {
     // A compute unit holds one workgroup, so a launch of up to 256 is one round, and a round is the cheaper the more
-    // wavefronts share a token set: 32 levels of 8 heads take 47 us with RS = 8 (up to 512 tokens), 76 (4; 1024), 112
-    // (2; 2048), 136 with k_encode_many (4096).  So full rounds go to the latter, and the rest to the largest RS that needs
-    // one round.
+    // wavefronts share a token set: 32 levels of 8 heads take 34 to 37 us with k_encode_few (up to 160 tokens), 48 with
+    // RS = 8 (512), 76 (4; 1024), 112 (2; 2048), 136 with k_encode_many (4096).  So full rounds go to the latter, and the rest to the first of them that
+    // needs one round.
     const int64_t round = 128 * (int64_t)std::max(1, 256 / d.Hkv);
     const int full = (int)(n_tokens / round * round), rest = n_tokens - full;
     if (full) {
@@ -1062,6 +1272,7 @@ commvq_status encode_rows(const void *keys, const void *cb, const float *norms, 
         out += full * d.token_stride;
     }
     auto one_round = [&](int per_wg) { return (int64_t)(rest + per_wg - 1) / per_wg * d.Hkv <= 256; };
+    if (one_round(kFewTok)) return launch_encode_few(keys, cb, norms, out, d, rest, s);
     if (one_round(16)) return launch_encode_rows<8>(keys, cb, norms, out, d, rest, s);
     if (one_round(32)) return launch_encode_rows<4>(keys, cb, norms, out, d, rest, s);
     if (one_round(64)) return launch_encode_rows<2>(keys, cb, norms, out, d, rest, s);
