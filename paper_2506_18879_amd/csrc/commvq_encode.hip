@@ -179,11 +179,12 @@ __global__ __launch_bounds__(256) void k_encode(const void *__restrict__ keys, c
 // double buffer.  Piece x of row t sits in slot x xor (t mod 16) of its row: the operand reads are free of bank
 // conflicts, and a load instruction (64 lanes -> 64 consecutive slots) still covers 1 KiB of contiguous memory.
 // Eight wavefronts: 8 / RS sets of 16 tokens, the 256 rows of a level shared by the RS wavefronts of a set, which
-// exchange their minima through LDS.  RS = 8 (16 tokens) has the shortest level, 1.5 us; with a split and an update per
-// wavefront instead of shared ones it was 2.1.
-// 64 vectors, 16 levels: 25 us, with a workgroup per vector and fp32 FMAs 32 us.
+// exchange their minima through LDS.  With a split and an update per wavefront instead of shared ones a level of RS = 8 (16 tokens) took
+// 2.1 us instead of 1.5.  RS = 4 and 8 leave the sending to two wavefronts more: eight sends of every wavefront before it can
+// go on held it up for as long as its products take (1000 tokens, 32 levels 75.6 -> 64 us, 500 tokens 52 -> 47.6, 16 levels 40.3 -> 34.2
+// and 27.7 -> 25.1; RS = 2, whose level is longer: no change, so its wavefronts send for themselves).
 // The images sit at LDS address 0: no static LDS here.
-constexpr int kErThreads = 512;
+constexpr int er_threads(int rs) { return rs >= 4 ? 640 : 512; }
 constexpr int kErImg = 16 * kK;  // 16-byte pieces of one level's rows
 constexpr int kErNorms = 2 * kErImg * 16;              // [2][256] floats
 constexpr int kErPart = kErNorms + 2 * kK * 4;         // [8 wavefronts][16 tokens] minimum and its row
@@ -192,7 +193,7 @@ constexpr int er_chosen(int rs) { return kErSplit + (rs >= 4 ? 8 / rs * 12 * 64 
 constexpr int er_lds(int rs) { return er_chosen(rs) + 128 / rs * 32; }
 static_assert(er_lds(2) <= 163840 && er_lds(4) <= 163840 && er_lds(8) <= 163840, "LDS of a compute unit");
 template <int RS>
-__global__ __launch_bounds__(kErThreads) void k_encode_rows(const void *__restrict__ keys, const uint4 *__restrict__ cb,
+__global__ __launch_bounds__(er_threads(RS)) void k_encode_rows(const void *__restrict__ keys, const uint4 *__restrict__ cb,
                                                             const float *__restrict__ norms, uint8_t *__restrict__ out,
                                                             const EncodeDims a, int n_tokens)
 {
@@ -200,9 +201,10 @@ __global__ __launch_bounds__(kErThreads) void k_encode_rows(const void *__restri
     char *lds = reinterpret_cast<char *>(er_mem);
     uint8_t *chosen = reinterpret_cast<uint8_t *>(lds + er_chosen(RS));
     constexpr int kSets = 8 / RS, kTiles = 16 / RS;
+    constexpr bool kSenders = RS >= 4;         // two wavefronts more, for the rows of the next level
     constexpr bool kShare = RS >= 4;           // the wavefronts of a set share the update and the split of its residuals
     constexpr int kOwn = kShare ? 32 / RS : 32;  // elements of its token that a lane keeps: from `own` of its 4 kc x 8
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, gk = lane >> 4;
     const int set = wave % kSets, rs = wave / kSets;
     const int own = kShare ? rs * kOwn : 0;
@@ -213,17 +215,37 @@ __global__ __launch_bounds__(kErThreads) void k_encode_rows(const void *__restri
     const size_t tokc = (size_t)(tok < n_tokens ? tok : n_tokens - 1);
     const uint4 *rows = cb + (size_t)g * a.levels * kErImg;
     const float *nrows = norms + (size_t)g * a.levels * kK;
-    auto fetch_level = [&](int l, int buf) {
+    auto send = [&](int l, int first, auto count) __attribute__((always_inline)) {  // an instruction: four rows
         const uint4 *src = rows + (size_t)l * kErImg;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {  // instruction i of the wavefront: rows 32 wave + 4 i .. + 3
-            const int r0 = wave * 32 + 4 * i, t = r0 + (lane >> 4);
-            const unsigned slot = __builtin_amdgcn_readfirstlane((unsigned)(buf * kErImg + r0 * 16));
-            lds_dma16(src, (unsigned)(t * 16 + ((lane ^ t) & 15)) * 16u, slot * 16u);
+        for (int i = 0; i < decltype(count)::value; ++i) {
+            const int r0 = first + 4 * i, t = r0 + gk;
+            lds_dma16(src, (unsigned)(t * 16 + ((lane ^ t) & 15)) * 16u, (unsigned)((l & 1) * kErImg + r0 * 16) * 16u);
         }
-        if (wave == 0) lds_dma16(nrows + (size_t)l * kK, (unsigned)lane * 16u, (unsigned)(kErNorms + buf * kK * 4));
     };
-    fetch_level(0, 0);
+    auto send_norms = [&](int l) { lds_dma16(nrows + (size_t)l * kK, (unsigned)lane * 16u, (unsigned)(kErNorms + (l & 1) * kK * 4)); };
+    auto send_share = [&](int l) __attribute__((always_inline)) {  // RS = 2: a wavefront's share
+        send(l, 32 * wave, std::integral_constant<int, 8>());
+        if (wave == 0) send_norms(l);
+    };
+    if (kSenders && wave >= 8) {
+        auto send_half = [&](int l, int half) __attribute__((always_inline)) {
+            send(l, half * 128 + (wave - 8) * 64, std::integral_constant<int, 16>());
+            if (half && wave == 8) send_norms(l);
+        };
+        send_half(0, 0);
+        send_half(0, 1);
+        for (int l = 0; l < a.levels; ++l) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // level l has landed
+            __syncthreads();
+            if (l + 1 < a.levels) send_half(l + 1, 0);
+            __syncthreads();
+            if (l + 1 < a.levels) send_half(l + 1, 1);
+        }
+        __syncthreads();
+        return;
+    }
+    if (!kSenders) send_share(0);
     float res[kOwn];
 #pragma unroll
     for (int i = 0; i < kOwn; i += 4) {  // elements 32 kc + 8 gk .. + 7 of the token, four at a time
@@ -263,9 +285,9 @@ __global__ __launch_bounds__(kErThreads) void k_encode_rows(const void *__restri
                 if constexpr (RS == 8) reinterpret_cast<uint2_t *>(dst)[rs & 1] = uint2_t{mine[s3][0], mine[s3][1]};
             }
         }
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's rows of level l have landed
+        if (!kSenders) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's rows of level l have landed
         __syncthreads();                                   // ... and everybody's; the other image is no longer read
-        if (l + 1 < a.levels) fetch_level(l + 1, buf ^ 1);
+        if (!kSenders && l + 1 < a.levels) send_share(l + 1);
         uint4_t part[3][4];
 #pragma unroll
         for (int s3 = 0; s3 < 3; ++s3)
@@ -1233,7 +1255,7 @@ commvq_status launch_encode_rows(const void *keys, const void *cb, const float *
     static std::atomic<uint64_t> lds_ok{0};
     if (allow_dynamic_lds(&k_encode_rows<RS>, er_lds(RS), lds_ok) != hipSuccess) return COMMVQ_ERR_LAUNCH;
     constexpr int per_wg = 16 * (8 / RS);
-    hipLaunchKernelGGL(k_encode_rows<RS>, dim3((unsigned)((n_tokens + per_wg - 1) / per_wg * d.Hkv)), dim3(kErThreads), er_lds(RS), s, keys,
+    hipLaunchKernelGGL(k_encode_rows<RS>, dim3((unsigned)((n_tokens + per_wg - 1) / per_wg * d.Hkv)), dim3(er_threads(RS)), er_lds(RS), s, keys,
                        static_cast<const uint4 *>(cb), norms, out, d, n_tokens);
     return hipGetLastError() == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;
 }
@@ -1260,8 +1282,8 @@ commvq_status encode_rows(const void *keys, const void *cb, const float *norms, 
                           hipStream_t s)
 {
     // A compute unit holds one workgroup, so a launch of up to 256 is one round, and a round is the cheaper the more
-    // wavefronts share a token set: 32 levels of 8 heads take 34 to 37 us with k_encode_few (up to 160 tokens), 48 with
-    // RS = 8 (512), 76 (4; 1024), 112 (2; 2048), 136 with k_encode_many (4096).  So full rounds go to the latter, and the rest to the first of them that
+    // wavefronts share a token set: 32 levels of 8 heads take 34 to 37 us with k_encode_few (up to 160 tokens), 47 with
+    // RS = 8 (512), 64 (4; 1024), 112 (2; 2048), 136 with k_encode_many (4096).  So full rounds go to the latter, and the rest to the first of them that
     // needs one round.
     const int64_t round = 128 * (int64_t)std::max(1, 256 / d.Hkv);
     const int full = (int)(n_tokens / round * round), rest = n_tokens - full;
