@@ -81,7 +81,7 @@ inline int pair_record_bytes(const commvq_config &c) { return (12 * c.key_levels
 // Sets of four levels that the kernels work on: levels beyond key_levels are zeros (R = 11: 3 sets, R = 21: 6).
 inline int pair_sets(const commvq_config &c) { return c.key_levels <= 12 ? 3 : c.key_levels <= 16 ? 4 : 6; }
 constexpr int kPairSlices = 4;  // LDS slices of four planes
-// Passes of k_score_pair at most (2, 4 or these).
+// Passes of k_score_pair at most (2, 3, 4 or these).
 constexpr int pair_passes(int sets) { return sets == 3 ? 8 : 6; }
 // Memory that paired keys have had in a workspace beside the packed table (an index byte per level, unpacked): partial logits may use it.
 inline size_t pair_room(const commvq_config &c, int64_t T) { return pair_keys(c) ? (size_t)T * c.n_kv_heads * 32 * pair_blocks(c) : 0; }
@@ -158,7 +158,13 @@ StreamShape stream_shape(const commvq_handle *h, int B, int64_t T, int max_seqle
     const int per_seq = (max_seqlen + kPassTokens - 1) / kPassTokens;
     // segments per KV head: at most one partly filled one per sequence more than the tokens need; about half of them for the estimate
     const int64_t most = std::min<int64_t>((int64_t)B * per_seq, T / kPassTokens + B);
-    const int64_t likely = B == 1 ? most : std::min<int64_t>((int64_t)B * per_seq, T / kPassTokens + (B + 1) / 2);
+    // (k_score_pair: and the standard deviation, sqrt(B / 12), of the partly filled ones more.  Its cuts fill the 256 compute units once, and one
+    // segment too many for that is a second round: 8 sequences of 1250 to 2500 tokens 71.3 us without, 63.2 with.)
+    const bool pair = pair_keys(h->cfg);
+    const int sets = pair_sets(h->cfg);
+    int spread = 0;
+    while (pair && B > 1 && 12 * spread * spread < B) ++spread;
+    const int64_t likely = B == 1 ? most : std::min<int64_t>((int64_t)B * per_seq, T / kPassTokens + (B + 1) / 2 + spread);
     // Cost of a workgroup in microseconds, fitted to sweeps over lengths from 350 tokens up: a fixed start and end (launch, first
     // fetches, write-out), and per slice a switch and the passes.  A launch too short to fill the 256 compute units is also
     // cut along the slices; every group then fetches the tile's codes again, the partial logits take a trip through
@@ -166,11 +172,14 @@ StreamShape stream_shape(const commvq_handle *h, int B, int64_t T, int max_seqle
     const bool two = h->cfg.m_key == 32;
     const double fixed = 9.0, sw = two ? 1.25 : h->G == 8 ? 0.6 : 0.5, c = two ? (h->G == 8 ? 0.70 : 0.66) : (h->G == 8 ? 0.47 : 0.41);
     const double part = (double)T * h->cfg.n_q_heads / 1e6 + (two ? 0.08 : 0.15);
-    // k_score_pair: 16 rounds, four to a slice; 2, 4 or pair_passes passes.  Fitted to 29 shapes of 2000 to 131072 tokens, 1 to 8
+    // k_score_pair: 16 rounds, four to a slice; 2, 3, 4 or pair_passes passes.  Fitted to 29 shapes of 2000 to 131072 tokens, 1 to 8
     // sequences, R = 11 and 21: 15 cuts each, the one chosen is 0.7 % slower than the best on average (8 sequences of 1100 to 2200 tokens, R = 11:
     // 55.9 us with groups of 8 rounds, 63.0 uncut; one of 2000: 39.9 with groups of two rounds, 56.8 uncut).
-    const bool pair = pair_keys(h->cfg);
-    const int sets = pair_sets(h->cfg);
+    // Three passes where two do not fit one workgroup per compute unit and four leave too many of them idle, best of the others -> three:
+    // R = 21, one sequence of 17000 tokens 70.7 -> 65.2 us, of 9000 56.3 -> 53.1; R = 11, 40000 tokens 75.1 -> 70.8, 16 sequences of 1500 to
+    // 3000 85.3 -> 80.7.  Uncut with six sets of levels it loses to six passes in two groups (two sequences of 10000 to 20000: 90.2 against 94.3).
+    // Two passes of three sets uncut take 2.5 us (8 heads per KV head: 5) more than the line through the others (their rounds are too short
+    // for the codes on their way): 8 sequences of 1374 to 2748 tokens 64.7 us, 63.2 with three passes in two groups; 8 heads, one of 17000 63.5 and 61.3.
     const double pc = (h->G == 8 ? 0.10 : 0.0) + (sets == 3 ? 0.443 : sets == 4 ? 0.535 : 0.728);
     // The partial logits may not need more memory than the bins that follow them, apart from few_tile_bytes: a shape that fits a
     // workspace of some size (the static one in particular) must not outgrow it for the sake of a faster cut.
@@ -184,12 +193,14 @@ StreamShape stream_shape(const commvq_handle *h, int B, int64_t T, int max_seqle
     }
     StreamShape best = {2, 1, 1};
     double t_best = 1e30;
-    for (int passes = 2; passes <= (pair ? pair_passes(sets) : kStreamPasses); passes += pair ? 2 + (passes == 4 ? pair_passes(sets) - 6 : 0) : 1)
+    const int most_passes = pair ? pair_passes(sets) : kStreamPasses;
+    for (int passes = 2; passes <= most_passes; passes = !pair || passes != 4 ? passes + 1 : most_passes)
         for (int e = 1; e <= kStreamSlices && (e - 1) * one <= room; e *= 2) {
+            if (pair && passes == 3 && e == 1 && sets > 3) continue;
             const int64_t wgs = (likely + passes - 1) / passes * h->cfg.n_kv_heads * e;
             const double rounds = (double)kStreamSlices / e;
             const double t = pair ? (double)((wgs + 255) / 256) * (9.4 + std::max(1.0, rounds / 4) * 0.32 + rounds * (0.27 + passes * pc)) +
-                                        (e > 1 ? 4.8 + e * 3.35 * (double)T * h->cfg.n_q_heads / 1e6 : 0.0)
+                                        (e > 1 ? 4.8 + e * 3.35 * (double)T * h->cfg.n_q_heads / 1e6 : passes == 2 && sets == 3 ? (h->G == 8 ? 5.0 : 2.5) : 0.0)
                                   : (double)((wgs + 255) / 256) * (fixed + rounds * (sw + passes * c)) + (e > 1 ? 5.0 + e * part : 0.0);
             if (t < t_best * 0.9999) { t_best = t; best = StreamShape{passes, 0, e}; }
         }
@@ -2013,10 +2024,12 @@ hipError_t launch_pair_s(const StreamArgs &a, int passes, int R, int PB, int gri
     constexpr int most = pair_passes(SETS);
     if (a.d.G == 8) {
         if (passes == 2) return launch_pair_n<SETS, 2, 2>(a, R, PB, grid, s);
+        if (passes == 3) return launch_pair_n<SETS, 2, 3>(a, R, PB, grid, s);
         if (passes == 4) return launch_pair_n<SETS, 2, 4>(a, R, PB, grid, s);
         return launch_pair_n<SETS, 2, most>(a, R, PB, grid, s);
     }
     if (passes == 2) return launch_pair_n<SETS, 1, 2>(a, R, PB, grid, s);
+    if (passes == 3) return launch_pair_n<SETS, 1, 3>(a, R, PB, grid, s);
     if (passes == 4) return launch_pair_n<SETS, 1, 4>(a, R, PB, grid, s);
     return launch_pair_n<SETS, 1, most>(a, R, PB, grid, s);
 }

@@ -10,12 +10,9 @@ from test_gpu_parity import TOL_SCORE, assert_rows, gpu  # noqa: F401  (gpu: fix
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("R,G,lens", [(1, 4, [700]), (4, 8, [513, 1]), (5, 4, [511, 0, 64, 63]), (12, 4, [1024, 2049]), (12, 8, [4095]), (13, 4, [300, 65]),
-                                      (15, 2, [600]), (16, 4, [4100, 7]), (17, 8, [900, 130]), (20, 4, [1537]), (21, 8, [2500, 511, 0, 1024]),
-                                      (21, 4, [97] * 9), (11, 4, [700, 40, 2100, 0, 333, 512, 1])])
-def test_levels_around_sets(gpu, oracle, R, G, lens):  # noqa: F811
+def check(gpu, oracle, R, G, Hkv, lens):  # noqa: F811
     import torch
-    w = synth.make_pair_workload(f"sets_R{R}_{len(lens)}", B=len(lens), Hq=2 * G, Hkv=2, seqlens=lens, R=R, Mv=16, seed=40 + R + len(lens))
+    w = synth.make_pair_workload(f"sets_R{R}_{len(lens)}", B=len(lens), Hq=Hkv * G, Hkv=Hkv, seqlens=lens, R=R, Mv=16, seed=40 + R + len(lens))
     dw, op = gpu.DeviceWorkload(w), gpu.DecodeAttention(w)
     op.workspace.fill_(0xFF)
     s = op.scores(dw)
@@ -31,3 +28,17 @@ def test_levels_around_sets(gpu, oracle, R, G, lens):  # noqa: F811
     assert_rows(got[keep], ref, w.name)
     assert not np.delete(got, keep, axis=0).any()
     op.close()
+
+
+@pytest.mark.parametrize("R,G,lens", [(1, 4, [700]), (4, 8, [513, 1]), (5, 4, [511, 0, 64, 63]), (12, 4, [1024, 2049]), (12, 8, [4095]), (13, 4, [300, 65]),
+                                      (15, 2, [600]), (16, 4, [4100, 7]), (17, 8, [900, 130]), (20, 4, [1537]), (21, 8, [2500, 511, 0, 1024]),
+                                      (21, 4, [97] * 9), (11, 4, [700, 40, 2100, 0, 333, 512, 1])])
+def test_levels_around_sets(gpu, oracle, R, G, lens):  # noqa: F811
+    check(gpu, oracle, R, G, 2, lens)
+
+
+# Launches that are cut into three passes of 512 tokens per workgroup (in 8, 4, 2 and 1 groups of slices): whole and partly filled last ones.
+@pytest.mark.parametrize("R,G,Hkv,lens", [(12, 4, 8, [513, 512, 511, 514, 513]), (21, 4, 8, [4500]), (14, 4, 8, [1537] * 5), (21, 8, 8, [1536, 1537, 1535, 1600, 1537]),
+                                          (21, 4, 16, [8400]), (11, 2, 16, [17500])])
+def test_three_passes(gpu, oracle, R, G, Hkv, lens):  # noqa: F811
+    check(gpu, oracle, R, G, Hkv, lens)
