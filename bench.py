@@ -224,9 +224,10 @@ def bench_encode(args):
     if not paired and w.dtype == "bf16":
         # the dot products run as bf16 MFMA on an exact three-way split of the fp32 residual; where the launch fills the chip two of
         # the parts decide nearly everything
-        many = (n + 63) // 64 * w.Hkv > 256
+        many, few = (n + 63) // 64 * w.Hkv > 256, (n + 4) // 5 * w.Hkv <= 256
         mf = (2 if many else 3) * n * w.Hkv * levels * 2 * w.d * K / (kernel_ms * 1e-3) / 1e12
-        roof = {"kernel": "k_encode_many" if many else "k_encode_rows", "bound": "mfma", "achieved": round(mf, 2), "peak": MFMA_BF16_PEAK_TFLOPS,
+        roof = {"kernel": "k_encode_many" if many else "k_encode_few" if few else "k_encode_rows", "bound": "mfma", "achieved": round(mf, 2),
+                "peak": MFMA_BF16_PEAK_TFLOPS,
                 "unit": "TFLOP/s", "frac": round(mf / MFMA_BF16_PEAK_TFLOPS, 4), "traffic": None,
                 "kernel_ms": round(kernel_ms, 5)}
     if paired and n * w.Hkv > 512:
