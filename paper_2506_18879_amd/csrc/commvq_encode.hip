@@ -360,8 +360,11 @@ __global__ __launch_bounds__(er_threads(RS)) void k_encode_rows(const void *__re
 // of 16, so that neither the reads nor the writes of a token's 64 lanes collide.  The images sit at LDS address 0.
 // What bounds it: the rows' way into one compute unit's LDS, 64 KiB in 0.95 us.  64 vectors, 16 levels, codebook in the L2: 18.2 us
 // (k_encode_rows<8> 24.8; rows sent by the eight wavefronts themselves 22.5; loaded into registers straight from memory in operand order,
-// 64 cache lines an instruction, 38), 32 levels 33.8 (47.2); codebook from the last-level cache 22 (25).  Words of the levels after the
-// next asked for early, into the L2: 26.  Up to 160 tokens of 8 heads (one round of workgroups): 37.1 (48.4).
+// 64 cache lines an instruction, 38), 32 levels 33.8 (47.2).  Up to 160 tokens of 8 heads (one round of workgroups): 37.1 (48.4).
+// The codebook of a layer is seldom in the L2 when its turn comes, and a level from the last-level cache takes 0.25 us more.  So where the
+// launch leaves compute units idle, they get workgroups that read a word of every cache line of the levels to come: 22.3 -> 18.9 (in the
+// L2 already: 18.4 -> 18.9).  A head's have the head's place in the numbering, with 8 or 16 heads that is the same L2.  Asked for by the
+// workgroups that need them, the same words stand in the way of the rows: 26.
 constexpr int kFewTok = 5, kFewThreads = 640;
 constexpr int kFewParts = 2 * kErImg * 16;             // [16 pieces][16 slots] 16 bytes
 constexpr int kFewMin = kFewParts + 16 * 16 * 16;      // [5 tokens][8 wavefronts][4] least cost of 8 rows, its row, the second least
@@ -370,7 +373,7 @@ constexpr int kFewLds = kFewTop + 2 * 4;
 static_assert(kFewLds <= 163840, "LDS of a compute unit");
 __global__ __launch_bounds__(kFewThreads) void k_encode_few(const void *__restrict__ keys, const uint4 *__restrict__ cb,
                                                             const float *__restrict__ norms, uint8_t *__restrict__ out,
-                                                            const EncodeDims a, int n_tokens)
+                                                            const EncodeDims a, int n_tokens, int workers)
 {
     extern __shared__ __attribute__((aligned(16))) uint4 few_mem[];
     char *lds = reinterpret_cast<char *>(few_mem);
@@ -379,6 +382,15 @@ __global__ __launch_bounds__(kFewThreads) void k_encode_few(const void *__restri
     const int g = blockIdx.x % a.Hkv;
     const uint4 *rows = cb + (size_t)g * a.levels * kErImg;
     const float4 *all_norms = reinterpret_cast<const float4 *>(norms + (size_t)g * a.levels * kK);  // 64 a level
+    if ((int)blockIdx.x >= workers) {                      // reads ahead: a word of each of a level's 512 + 8 cache lines
+        for (int l = 1 + ((int)blockIdx.x - workers) / a.Hkv; l < a.levels; l += ((int)gridDim.x - workers) / a.Hkv) {
+            const unsigned *line = tid < 512 ? reinterpret_cast<const unsigned *>(rows + (size_t)l * kErImg + 8 * tid)
+                                             : reinterpret_cast<const unsigned *>(all_norms + l * 64 + 8 * ((tid - 512) & 7));
+            const unsigned word = *line;
+            asm volatile("" : : "v"(word));
+        }
+        return;
+    }
     float *tops = reinterpret_cast<float *>(lds + kFewTop);
     if (wave >= 8) {                                       // the senders: slots as in k_encode_rows
         auto send = [&](int l, int half) __attribute__((always_inline)) {
@@ -1264,8 +1276,9 @@ commvq_status launch_encode_few(const void *keys, const void *cb, const float *n
 {
     static std::atomic<uint64_t> lds_ok{0};
     if (allow_dynamic_lds(&k_encode_few, kFewLds, lds_ok) != hipSuccess) return COMMVQ_ERR_LAUNCH;
-    hipLaunchKernelGGL(k_encode_few, dim3((unsigned)((n_tokens + kFewTok - 1) / kFewTok * d.Hkv)), dim3(kFewThreads), kFewLds, s, keys,
-                       static_cast<const uint4 *>(cb), norms, out, d, n_tokens);
+    const int workers = (n_tokens + kFewTok - 1) / kFewTok * d.Hkv, ahead = std::min(d.levels - 1, std::max(0, 256 - workers) / d.Hkv) * d.Hkv;
+    hipLaunchKernelGGL(k_encode_few, dim3((unsigned)(workers + ahead)), dim3(kFewThreads), kFewLds, s, keys,
+                       static_cast<const uint4 *>(cb), norms, out, d, n_tokens, workers);
     return hipGetLastError() == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;
 }
 
