@@ -368,8 +368,8 @@ __global__ __launch_bounds__(er_threads(RS)) void k_encode_rows(const void *__re
 constexpr int kFewTok = 5, kFewThreads = 640;
 constexpr int kFewParts = 2 * kErImg * 16;             // [16 pieces][16 slots] 16 bytes
 constexpr int kFewMin = kFewParts + 16 * 16 * 16;      // [5 tokens][8 wavefronts][4] least cost of 8 rows, its row, the second least
-constexpr int kFewTop = kFewMin + kFewTok * 32 * 16;   // [2] the largest |c|^2 of a level
-constexpr int kFewLds = kFewTop + 2 * 4;
+constexpr int kFewTop = kFewMin + kFewTok * 32 * 16;   // [2] the largest |c|^2 of a level and its root
+constexpr int kFewLds = kFewTop + 2 * 8;
 static_assert(kFewLds <= 163840, "LDS of a compute unit");
 __global__ __launch_bounds__(kFewThreads) void k_encode_few(const void *__restrict__ keys, const uint4 *__restrict__ cb,
                                                             const float *__restrict__ norms, uint8_t *__restrict__ out,
@@ -391,7 +391,7 @@ __global__ __launch_bounds__(kFewThreads) void k_encode_few(const void *__restri
         }
         return;
     }
-    float *tops = reinterpret_cast<float *>(lds + kFewTop);
+    float2 *tops = reinterpret_cast<float2 *>(lds + kFewTop);
     if (wave >= 8) {                                       // the senders: slots as in k_encode_rows
         auto send = [&](int l, int half) __attribute__((always_inline)) {
             const uint4 *src = rows + (size_t)l * kErImg;
@@ -406,7 +406,7 @@ __global__ __launch_bounds__(kFewThreads) void k_encode_few(const void *__restri
         send(0, 1);
         for (int l = 0; l < a.levels; ++l) {
             const float top = wave_max(fmaxf(fmaxf(nq.x, nq.y), fmaxf(nq.z, nq.w)));  // of level l
-            if (wave == 8 && lane == 0) tops[l & 1] = top;  // (of level l - 2 nothing is read any more)
+            if (wave == 8 && lane == 0) tops[l & 1] = make_float2(top, __builtin_amdgcn_sqrtf(top + 1e-34f));  // (of level l - 2 nothing is read any more)
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // level l has landed
             __syncthreads();
             nq = all_norms[(l + 1 < a.levels ? l + 1 : l) * 64 + lane];
@@ -487,7 +487,8 @@ __global__ __launch_bounds__(kFewThreads) void k_encode_few(const void *__restri
         __syncthreads();
         if (owner) {
             const float4 o = pm[wave * 32 + (lane & 31)];  // lanes 32 .. 63 as 0 .. 31
-            const float cc = tops[l & 1], m = -wave_max(-o.x);
+            const float2 longest = tops[l & 1];
+            const float cc = longest.x, m = -wave_max(-o.x);
             const int win = __builtin_ctz((unsigned)__ballot(o.x == m) | 0x80000000u);
             const float up = -wave_max(-((lane & 31) == win ? o.z : o.x));  // (of two equal ones: the same again)
             int row = __builtin_amdgcn_readlane(__builtin_bit_cast(int, o.y), win);
@@ -495,7 +496,8 @@ __global__ __launch_bounds__(kFewThreads) void k_encode_few(const void *__restri
             // cost, and one of the cost itself.  If the second least cost is within what that can amount to for two rows, or
             // something overflows or is not a number, the row tiles of the candidates are taken again in the order of
             // k_encode_rows: its codes, bit for bit.
-            const float rc = 1.01f * __builtin_amdgcn_sqrtf(whole2 * (cc + 1e-34f)), bound = 9e-6f * rc + 5e-7f * cc;
+            // (The norms' product, not the root of their squares' product: that leaves the range of fp32 for rows and vectors of 2^-32 or 2^31.)
+            const float rc = 1.01f * __builtin_amdgcn_sqrtf(whole2) * longest.y, bound = 9e-6f * rc + 5e-7f * cc;
             const float left = __builtin_fmaf(whole2, 1.000001f, m + 2.f * bound);  // |r - c|^2 = |r|^2 + (|c|^2 - 2 r c)
             whole2 = left < 1e-34f ? 1e-34f : left;        // (not fmaxf: NaN has to stay)
             if (__any(!(up - m > bound && rc < 1e37f))) {
