@@ -215,9 +215,9 @@ inline bool stream_keys(const commvq_config &c) { return !c.position_free; }
 inline bool fused_values(const commvq_config &c) { return !bin_values(c); }
 
 // How k_values cuts a launch: codebooks per workgroup, whole sequences per workgroup (1: a token range of one), column
-// parts, threads, token ranges per sequence and their length.
+// parts, threads, token ranges per sequence and their length, tokens of a range that share a fixed-point unit.
 struct ValueShape {
-    int books, slots, parts, threads, ranges, range_len;
+    int books, slots, parts, threads, ranges, range_len, span;
 };
 
 // A plan and what of the kernels' shapes the public part does not say.
@@ -226,7 +226,18 @@ struct Plan : commvq_plan {
     ValueShape values;
 };
 
-// room: value splits per sequence that the workspace holds.  Whole calls in microseconds, one choice against the other:
+// Granularity of the (max, sum of exp) statistics that the score stage leaves for the value stage: the score tile, except that
+// k_score_stream writes them per 512-token segment and k_score_combine (tiles cut along the slices) per 1024 tokens.
+inline int stat_len(const commvq_handle *h, const Plan &p)
+{
+    if (p.score_kernel && stream_keys(h->cfg)) return p.score_slice_groups > 1 ? 1024 : kPassTokens;
+    return p.score_split_len;
+}
+inline int stat_splits(const commvq_handle *h, const Plan &p, int max_seqlen) { return (max_seqlen + stat_len(h, p) - 1) / stat_len(h, p); }
+
+// splits, split_len: value splits per sequence that the workspace holds, and their length; tile: tokens of a statistics tile.
+// Spans are two value splits long (k_values), ranges whole tiles: a tile that two spans share counts towards both their units, and
+// those may be no coarser than what a value split or a tile gives.  Whole calls in microseconds, one choice against the other:
 //  * 4 codebooks a workgroup, so that a token range is long where a sequence has few heads: 9001 tokens 36.3 against 38.4
 //    with 8, 1237 tokens 24.7 against 26.4; from 128 groups of four on (64 of 8 heads) 8, which compute half as many
 //    exponentials: 8 x 8K..64K 456 against 499, 4 x 2.5K..20K (at the line) 56.6 against 55.0;
@@ -238,11 +249,11 @@ struct Plan : commvq_plan {
 //    83.1 against 89.9; with ranges of 2250 tokens on average no gain (107.4 against 105.9);
 //  * a quarter of the columns each where not even 64 workgroups would be there: 300 tokens 17.6 against 19.5, 2000 tokens
 //    20.7 against 22.2 (with 64: 24.7 either way; with 256: 61 against 79).
-ValueShape value_shape(const commvq_handle *h, int B, int64_t T, int max_seqlen, int room)
+ValueShape value_shape(const commvq_handle *h, int B, int64_t T, int max_seqlen, int splits, int split_len, int tile)
 {
     const int G = h->G, M = h->cfg.m_val, units = B * h->cfg.n_kv_heads;
     const bool wide = h->cfg.codebook_dtype == COMMVQ_BF16 && G >= 4;
-    ValueShape v = {4, 1, 1, wide ? 1024 : 512, 1, 0};
+    ValueShape v = {4, 1, 1, wide ? 1024 : 512, 1, 0, 2 * std::max(split_len, tile)};
     if (wide && (int64_t)G * units * M > 2048) {
         v.books = 8;
         const int groups = units * (M / 8);
@@ -255,10 +266,14 @@ ValueShape value_shape(const commvq_handle *h, int B, int64_t T, int max_seqlen,
     const int groups = units * (M / v.books);
     // as many ranges as there is place for bins (stage by stage) and output rows
     int n = std::max(1, (v.threads == 512 ? 512 : 256) / groups);
-    n = v.slots > 1 ? 1 : std::max(1, std::min(n, std::min(room, (int)partial_rows(h, B) * v.books / M)));
-    v.range_len = std::max(1024, ((max_seqlen + n - 1) / n + 511) / 512 * 512);
+    // (two workgroups on a compute unit have no LDS for the sums of several spans: at most two ranges, since a sequence then has three splits at most)
+    if (wide && v.threads == 512) n = std::max(n, (max_seqlen + v.span - 1) / v.span);
+    n = v.slots > 1 ? 1 : std::max(1, std::min(n, std::min(splits, (int)partial_rows(h, B) * v.books / M)));
+    const int step = std::max(512, tile);
+    v.range_len = std::max(1024, ((max_seqlen + n - 1) / n + step - 1) / step * step);
     v.ranges = v.slots > 1 ? 1 : (max_seqlen + v.range_len - 1) / v.range_len;
-    if (v.slots > 1) v.range_len = max_seqlen;
+    if (v.slots > 1) v.range_len = v.span = max_seqlen;  // (128 of these at least: two value splits at most)
+    v.span = std::min(v.span, v.range_len);
     if (v.books == 4 && (int64_t)groups * v.ranges * 4 <= 256) v.parts = 4;
     return v;
 }
@@ -296,20 +311,11 @@ void make_plan(const commvq_handle *h, int B, int64_t T, int max_seqlen, bool sl
     const int vlen = value_split_len(h, B, max_seqlen, groups > 1 ? 1024 : len);
     p->value_split_len = vlen;
     p->value_splits = (max_seqlen + vlen - 1) / vlen;
-    if (fused_values(h->cfg)) p->values = value_shape(h, B, T, max_seqlen, p->value_splits);
     p->out_chunks = val_books(h->cfg) * kK / kOutRows;
     p->score_kernel = sliced ? 1 : 0;
     p->score_slice_groups = groups;
+    if (fused_values(h->cfg)) p->values = value_shape(h, B, T, max_seqlen, p->value_splits, vlen, stat_len(h, *p));
 }
-
-// Granularity of the (max, sum of exp) statistics that the score stage leaves for the value stage: the score tile, except that
-// k_score_stream writes them per 512-token segment and k_score_combine (tiles cut along the slices) per 1024 tokens.
-inline int stat_len(const commvq_handle *h, const Plan &p)
-{
-    if (p.score_kernel && stream_keys(h->cfg)) return p.score_slice_groups > 1 ? 1024 : kPassTokens;
-    return p.score_split_len;
-}
-inline int stat_splits(const commvq_handle *h, const Plan &p, int max_seqlen) { return (max_seqlen + stat_len(h, p) - 1) / stat_len(h, p); }
 
 // Carves the workspace.  Array sizes are the larger of what the two score kernels need, so one workspace size serves a batch
 // shape whether or not explicit positions are passed.  Behind the statistics, the logits and the partial logits, the score
@@ -2163,10 +2169,10 @@ commvq_status run_scores(commvq_handle *h, const void *q, const uint8_t *key_cod
 template <int G, int CB, int S, int NCS, int NT, bool BF16>
 hipError_t launch_values_n(const ValuesArgs &a, hipStream_t s)
 {
-    constexpr int lds = values_lds<G, CB, S, NCS, NT>();
-    if (a.ncg * CB != a.M) return hipErrorInvalidValue;  // (a shape that this instantiation is not for)
+    const int lds = values_lds<G, CB, S, NCS, NT>(a.spans);
+    if (a.ncg * CB != a.M || lds > kLdsBytes || (a.spans > 1 && (S > 1 || (CB == 8 && NT == 512)))) return hipErrorInvalidValue;  // (a shape that this instantiation is not for)
     static std::atomic<uint64_t> lds_ok{0};  // per instantiation and device
-    if (hipError_t e = allow_dynamic_lds(&k_values<G, CB, S, NCS, NT, BF16>, lds, lds_ok); e != hipSuccess) return e;
+    if (hipError_t e = allow_dynamic_lds(&k_values<G, CB, S, NCS, NT, BF16>, kLdsBytes, lds_ok); e != hipSuccess) return e;
     const unsigned grid = (unsigned)(S == 1 ? a.batch * a.ranges : (a.batch + S - 1) / S) * (unsigned)(NCS * a.ncg * a.Hkv);
     hipLaunchKernelGGL((k_values<G, CB, S, NCS, NT, BF16>), dim3(grid), dim3(NT), lds, s, a);
     return hipGetLastError();
@@ -2197,7 +2203,8 @@ commvq_status run_values(commvq_handle *h, const uint8_t *val_codes, const void 
     a.bins = w.bins; a.vscale = w.vscale; a.lsum = w.lsum; a.partial = w.partial;
     a.Hq = c.n_q_heads; a.Hkv = c.n_kv_heads; a.M = c.m_val;
     a.nsplit = stat_splits(h, plan, pos->max_seqlen); a.split_len = stat_len(h, plan);
-    a.ranges = plan.values.ranges; a.range_len = plan.values.range_len;
+    a.ranges = plan.values.ranges; a.range_len = plan.values.range_len; a.span = plan.values.span;
+    a.spans = (a.range_len + a.span - 1) / a.span;
     a.batch = pos->batch; a.ncg = c.m_val / plan.values.books; a.mode = mode;
     hipError_t e;
     const bool bf16 = c.codebook_dtype == COMMVQ_BF16;

@@ -30,6 +30,7 @@ constexpr int kMaxValueSplits = 256;  // value_splits never exceeds 256 / (batch
 constexpr int kOutRows = 64;    // codebook rows per k_out workgroup
 constexpr int kOutMfmaRows = 256;   // codebook rows per k_out_mfma workgroup (batched output stage)
 constexpr int kOutMfmaMinRows = 16;  // batch * (query heads per KV head) from which the batched output kernel is used
+constexpr int kLdsBytes = 160 * 1024;  // LDS of a compute unit
 constexpr int kProfRing = 64;
 constexpr float kLog2e = 1.4426950408889634f;
 

@@ -14,12 +14,30 @@ constexpr int values_words()
 }
 template <int G, int CB, int S>
 constexpr int values_slot() { return kK * values_words<G, CB, S>() * 8; }
-// LDS of a workgroup: the slots' bins or, later, the wavefronts' sums; behind them two numbers per slot and head.
+// LDS of a workgroup: the slots' bins or, later, the wavefronts' sums; behind them, for more than one span, the sums of the spans before
+// (two floats per word of a row without copies), and three numbers per slot and head and two more per span.
 template <int G, int CB, int S, int NCS, int NT>
-constexpr int values_lds()
+constexpr int values_bins()
 {
     constexpr int red = NT / 64 * S * G * (kD / NCS) * 4, bins = S * values_slot<G, CB, S>();
-    return (bins > red ? bins : red) + 2 * S * G * 4;
+    return bins > red ? bins : red;
+}
+template <int G, int CB, int S, int NCS, int NT>
+constexpr int values_lds(int spans)
+{
+    return values_bins<G, CB, S, NCS, NT>() + (spans > 1 ? kK * (G >= 2 ? G / 2 : 1) * CB * 8 : 0) + (3 + 2 * spans) * S * G * 4;
+}
+
+// Units of a fixed-point sum per 1: with n numbers of sum l, each rounded to a whole number of them, the sum stays below 2^32 (2^-14 covers
+// what l and the numbers, computed apart, differ by, and a second rounding of such sums another 2^-14).
+__device__ __forceinline__ float units_per_one(float l, int n, float margin)
+{
+    return l >= 1e-30f ? fminf((4294967296.f * (1.f - margin) - (float)n) * __builtin_amdgcn_rcpf(l), 0x1p120f) : 1.f;
+}
+__device__ __forceinline__ float unit_of(float per)        // its reciprocal, to a rounding
+{
+    const float r = __builtin_amdgcn_rcpf(per);
+    return __builtin_fmaf(r, __builtin_fmaf(-per, r, 1.f), r);
 }
 
 struct ValuesArgs {
@@ -35,6 +53,7 @@ struct ValuesArgs {
     int nsplit, split_len;    // statistics tiles of the score stage
     int batch, ncg;
     int ranges, range_len;    // token ranges of a sequence (S > 1: one)
+    int span, spans;          // tokens of a range that share a fixed-point unit (S > 1: all); spans of a range
     int mode;                 // 0: everything; 1: up to the bins, which go to memory; 2: from there on
 };
 
@@ -54,28 +73,13 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *base, un
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
 }
 
-// floor(x + 0.5) of numbers on [0, 2^31).  (The s_nop is the wait state between an exponential and the use of its result,
-// which the compiler does not insert in front of inline asm.)
-template <int G>
-__device__ __forceinline__ void round_up_half(const float (&x)[G], unsigned (&r)[G])
+// x in whole units (numbers on [0, 2^32)): rounded to nearest, NaN to 0.
+__device__ __forceinline__ unsigned whole_units(float x, float per)
 {
-    if constexpr (G % 4 == 0) {
-#pragma unroll
-        for (int k = 0; k < G; k += 4) {
-            float e0 = x[k], e1 = x[k + 1], e2 = x[k + 2], e3 = x[k + 3];
-            asm("s_nop 1\n\tv_cvt_rpi_i32_f32 %0, %0\n\tv_cvt_rpi_i32_f32 %1, %1\n\tv_cvt_rpi_i32_f32 %2, %2\n\tv_cvt_rpi_i32_f32 %3, %3"
-                : "+v"(e0), "+v"(e1), "+v"(e2), "+v"(e3));
-            r[k] = __builtin_bit_cast(unsigned, e0); r[k + 1] = __builtin_bit_cast(unsigned, e1);
-            r[k + 2] = __builtin_bit_cast(unsigned, e2); r[k + 3] = __builtin_bit_cast(unsigned, e3);
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < G; ++k) {
-            float e = x[k];
-            asm("s_nop 1\n\tv_cvt_rpi_i32_f32 %0, %0" : "+v"(e));
-            r[k] = __builtin_bit_cast(unsigned, e);
-        }
-    }
+    unsigned r;
+    const float y = __builtin_fmaf(x, per, 0.5f);
+    asm("v_cvt_u32_f32 %0, %1" : "=v"(r) : "v"(y));        // (truncates; saturates, which C++ leaves open)
+    return r;
 }
 
 // x + y after exchanging the odd 16-lane rows of x with the even rows of y (row r of the result:
@@ -95,9 +99,15 @@ __device__ __forceinline__ float swap32_add(float x, float y)
 // workgroup takes CB of the M value codebooks of a KV head, for a range of a sequence's tokens or (S > 1) for S whole
 // sequences side by side, and leaves one unnormalised output row per head and range, which k_out_final adds.
 //
-// Bins.  w = exp(logit - max of the sequence) is added as round(w 2^sh) with integer LDS atomics.  The score stage has
-// left the exp-sum l of every statistics tile; sh = 30 - floor(log2 l) of the tiles that the range touches keeps every bin below 2^31
-// and the rounding below (tokens) 2^-31 of l.  Heads 2 p and 2 p + 1 share a 64-bit word (no carry crosses).  A 64-bit LDS
+// Bins.  w = exp(logit - max of the sequence) is added in whole units with integer LDS atomics.  The score stage has
+// left the exp-sum l of every statistics tile; a unit of l / 2^32 (a little more: units_per_one), l of the tiles that a span of tokens touches,
+// keeps every bin below 2^32 and the rounding below (tokens) 2^-33 of l.  A span is two value splits of the plan at most, so that
+// weights are as fine as with a unit of l / 2^31 per split.  A range of several spans is added up in fp32 between them, each with its unit, and at
+// its end made whole numbers once more: 0.8 us a span (three of them in a range at 32K, 32 codebooks: 55.7 -> 58.7 us a call, with one unit for the
+// range), where ranges of one span would each read the codebook rows again.  (logit - max) is taken before the product with log2 e and the
+// unit after the exponential: both in one sum of up to 32 took 4e-7 of a weight.  Error against 64 bits, codebooks of mean zero, one unit per range
+// of 2^30 to 2^31 and one sum -> now: 32K of 8 x 4 heads 1.2e-6 -> 3.2e-7, 64K of 64 x 4 heads 7.7e-6 -> 1.5e-6 (a unit per split and
+// one sum: 1.1e-6 and 2.4e-6).  Heads 2 p and 2 p + 1 share a 64-bit word (no carry crosses).  A 64-bit LDS
 // atomic is served 16 lanes at a time, so a codeword's row is [copy][pair][codebook] with at least 16 words and
 // lane l starts at (copy, pair, codebook) l mod 16 and walks pairs and codebooks by exclusive or: 16 lanes are on 16 bank pairs
 // at every step, whatever their codes, and lanes with the same code do not meet either.
@@ -133,7 +143,13 @@ __global__ __launch_bounds__(NT, S > 1 ? 2 : 4) void k_values(const ValuesArgs a
     constexpr int ND = NCT / 2;                            // dwords of a codebook row that a lane loads
     constexpr int DEPTH = S == 1 ? (CB * NP <= 8 ? 4 : 2) : S == 2 ? 2 : 1;  // tokens whose codes and logits are in flight, per slot
     extern __shared__ __attribute__((aligned(128))) unsigned char lds[];
-    float *eoff_s = reinterpret_cast<float *>(lds + values_lds<G, CB, S, NCS, NT>()) - 2 * S * G, *unit_s = eoff_s + S * G;
+    constexpr int ROW = NP * CB;                           // words of a row of bins without copies
+    constexpr bool SPANS = S == 1 && !(CB == 8 && NT == 512);  // (value_shape: these have one)
+    const int spans = SPANS ? a.spans : 1;
+    float2 *const sums = reinterpret_cast<float2 *>(lds + values_bins<G, CB, S, NCS, NT>());
+    float *const max_s = reinterpret_cast<float *>(sums) + (spans > 1 ? 2 * kK * ROW : 0);  // maximum of the sequence
+    float *const unit_s = max_s + S * G, *const per_s = unit_s + S * G;  // the last bins' unit, units per 1
+    float *const span_s = per_s + S * G, *const own_s = span_s + spans * S * G;  // [span] units per 1; exp-sum
     float *red = reinterpret_cast<float *>(lds);           // [NW][S][G][COLS]
 
     int id = blockIdx.x;
@@ -189,40 +205,63 @@ __global__ __launch_bounds__(NT, S > 1 ? 2 : 4) void k_values(const ValuesArgs a
     }
     for (int x = tid; x < S * SLOT / 16; x += NT) reinterpret_cast<uint4 *>(lds)[x] = make_uint4(0u, 0u, 0u, 0u);
 
-    // (maximum of the sequence, exp-sum of the range) of every slot and head
-    for (int job = wave; job < S * G; job += NW) {
-        const int s = job / G, hh = job % G;
+    // (maximum of the sequence, exp-sum) of every span, slot and head
+    const int live = spans > 1 ? (sv1[0] - sv0[0] + a.span - 1) / a.span : 1;  // spans that have tokens
+    for (int job = wave; job < live * (S * G); job += NW) {
+        const int s = job / G % S, hh = job % G, span = job / (S * G);
         int b = 0, v0 = 0, v1 = 0, L = 0;
 #pragma unroll
         for (int k = 0; k < S; ++k)
             if (s == k) { b = sb[k]; v0 = sv0[k]; v1 = sv1[k]; L = sL[k]; }
         if (v0 >= v1) continue;
+        if constexpr (SPANS) {
+            v0 += span * a.span;
+            v1 = min(v1, v0 + a.span);
+        }
         const size_t at = ((size_t)b * a.Hq + (size_t)g * G + hh) * a.ranges + rng;
         if (a.mode == 2) {
-            if (lane == 0) unit_s[job] = a.vscale[at];
+            if (lane == 0 && span == 0) unit_s[job] = a.vscale[at];
             continue;
         }
         const int ns = min((L + a.split_len - 1) / a.split_len, a.nsplit);
         const float2 *st = a.sstat + ((size_t)b * a.Hq + (size_t)g * G + hh) * a.nsplit;
-        // the exp-sum l of all tiles that the range touches bounds every bin; what it reports towards the softmax denominator is lown
+        // the exp-sum l of all tiles that the span touches bounds every bin; what it reports towards the softmax denominator is lown
         const int ta = v0 / a.split_len, tb = min((v1 + a.split_len - 1) / a.split_len, ns);
         RangeStats stats;
         stats.request(st, ns, ta, tb, lane);
         float mx, l, lown;
         stats.finish(st, ns, ta, tb, a.split_len, v0, lane, mx, l, lown);
-        int sh = 0;
-        if (l >= 1e-30f) sh = min(30 - ilogbf(l), 120);
         if (lane == 0) {
-            const float unit = ldexpf(1.f, -sh);
-            eoff_s[job] = (float)sh - mx * kLog2e;
-            unit_s[job] = unit;
-            if (cg == 0 && cs == 0) {
-                a.lsum[at] = lown;
-                if (a.mode == 1) a.vscale[at] = unit;
+            const float per = units_per_one(l, v1 - v0, 0x1p-14f);
+            span_s[job] = per;
+            own_s[job] = lown;
+            if (span == 0) max_s[job] = mx;
+            if (live == 1) {
+                unit_s[job] = unit_of(per);
+                if (cg == 0 && cs == 0) {
+                    a.lsum[at] = lown;
+                    if (a.mode == 1) a.vscale[at] = unit_of(per);
+                }
             }
         }
     }
     __syncthreads();
+    if (SPANS && live > 1 && a.mode != 2 && tid < G) {    // of the whole range
+        float own = 0.f, all = 0.f;
+        for (int k = 0; k < live; ++k) {
+            const float per = span_s[k * G + tid];
+            own += own_s[k * G + tid];
+            all += per == 1.f ? 0.f : (4294967296.f * (1.f - 0x1p-14f)) * unit_of(per);  // (no less than the span's exp-sum; 1: nothing in it rounds to a unit)
+        }
+        const float per = units_per_one(all, sv1[0] - sv0[0], 0x1p-13f);
+        per_s[tid] = per;
+        unit_s[tid] = unit_of(per);
+        if (cg == 0 && cs == 0) {
+            const size_t at = ((size_t)sb[0] * a.Hq + (size_t)g * G + tid) * a.ranges + rng;
+            a.lsum[at] = own;
+            if (a.mode == 1) a.vscale[at] = unit_of(per);
+        }
+    }
 
     // the wavefront's codebook rows, k-step by k-step: the first ones travel while the tokens are worked on
     // (addresses: a uniform base per codebook and k-step, one offset per lane)
@@ -265,29 +304,78 @@ __global__ __launch_bounds__(NT, S > 1 ? 2 : 4) void k_values(const ValuesArgs a
             for (int j = 0; j < 4; ++j) sel[v] |= (unsigned)(cbl ^ (4 * v + j)) << (8 * j);
         }
         const unsigned lanepart = (unsigned)(copy * NP * CB + pr * CB + cbl) * 8u;
+        auto copies_sum = [&](int x) __attribute__((always_inline)) {  // (no carry between the halves: their sums stay below 2^32)
+            const unsigned long long *row = reinterpret_cast<const unsigned long long *>(lds) + x / ROW * WORDS + x % ROW;
+            unsigned long long v = 0;
+#pragma unroll
+            for (int k = 0; k < COPIES; ++k) v += row[((k + x / ROW) & (COPIES - 1)) * ROW];  // (neighbouring rows on different banks)
+            return v;
+        };
+        // what to do with the sums of the spans up to this one, word by word of the first slot, a few of the thread's at a time (NT is a
+        // multiple of ROW: they are of two heads)
+        constexpr int OWN = kK * ROW / NT, AT_ONCE = OWN < 4 ? OWN : G == 8 ? 2 : 4;
+        const int head0 = tid % ROW / CB * 2, head1 = min(head0 + 1, G - 1);
+        auto add_span = [&](int span, auto put) __attribute__((always_inline)) {
+            const float unit0 = unit_of(span_s[span * G + head0]), unit1 = unit_of(span_s[span * G + head1]);
+#pragma unroll 1
+            for (int x0 = tid; x0 < kK * ROW; x0 += AT_ONCE * NT) {
+                uint2_t v[AT_ONCE];
+                float2 t[AT_ONCE];
+#pragma unroll
+                for (int i = 0; i < AT_ONCE; ++i) {
+                    v[i] = __builtin_bit_cast(uint2_t, copies_sum(x0 + i * NT));
+                    t[i] = span > 0 ? sums[x0 + i * NT] : make_float2(0.f, 0.f);
+                }
+#pragma unroll
+                for (int i = 0; i < AT_ONCE; ++i)
+                    put(x0 + i * NT, make_float2(__builtin_fmaf((float)v[i][0], unit0, t[i].x), __builtin_fmaf((float)v[i][1], unit1, t[i].y)));
+            }
+        };
+        auto next_span = [&](int span) __attribute__((always_inline)) {  // the bins to the sums, and empty for the next span
+            // (This barrier stands at the head of the loop; the compiler has left out its own wait there, with atomics of the
+            // iteration before under way.)
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __syncthreads();
+            add_span(span, [&](int x, float2 t) __attribute__((always_inline)) {
+                sums[x] = t;
+#pragma unroll
+                for (int k = 0; k < COPIES; ++k)           // (in copies_sum's order)
+                    reinterpret_cast<unsigned long long *>(lds)[x / ROW * WORDS + x % ROW + ((k + x / ROW) & (COPIES - 1)) * ROW] = 0;
+            });
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __syncthreads();
+        };
+        auto uniform = [](float x) { return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x))); };
 #pragma unroll
         for (int s = 0; s < S; ++s) {
-            float eoff[G];
-#pragma unroll
-            for (int hh = 0; hh < G; ++hh) {
-                eoff[hh] = eoff_s[s * G + hh];
-                asm volatile("" : "+v"(eoff[hh]));     // (waited for here, not in the loop, where the wait would include the atomics)
-            }
             unsigned lane_k[CB];
 #pragma unroll
             for (int k = 0; k < CB; ++k) lane_k[k] = (unsigned)(s * SLOT) + (lanepart ^ (unsigned)(k * 8));
+            float mx[G], per[G];                           // (uniform)
+#pragma unroll
+            for (int hh = 0; hh < G; ++hh) {
+                mx[hh] = uniform(max_s[s * G + hh]);
+                per[hh] = uniform(span_s[s * G + hh]);
+            }
+            int span = 0, next = live > 1 ? sv0[s] + a.span : -1;  // (a span is a whole number of rounds of NT tokens)
             for (int t0 = sv0[s]; t0 < sv1[s]; t0 += DEPTH * NT) {
 #pragma unroll
                 for (int d = 0; d < DEPTH; ++d) {
                     const int t = t0 + d * NT;
                     if (t < sv1[s]) {
-                        float w[G];
+                        if (SPANS && t == next) {
+                            next_span(span);
+                            ++span;
+                            next += a.span;
+#pragma unroll
+                            for (int hh = 0; hh < G; ++hh) per[hh] = uniform(span_s[span * G + hh]);
+                        }
                         unsigned p[G], cw[CD];
 #pragma unroll
                         for (int v = 0; v < CD; ++v) cw[v] = __builtin_amdgcn_perm(cnext[s][d][CD - 1], cnext[s][d][0], sel[v]);
 #pragma unroll
-                        for (int hh = 0; hh < G; ++hh) w[hh] = __builtin_amdgcn_exp2f(snext[s][d][hh] * kLog2e + eoff[hh]);
-                        round_up_half(w, p);
+                        for (int hh = 0; hh < G; ++hh)
+                            p[hh] = whole_units(__builtin_amdgcn_exp2f((snext[s][d][hh] - mx[hh]) * kLog2e), per[hh]);
                         if (S == 1 || t + DEPTH * NT < sv1[s]) fetch(s, d, t + DEPTH * NT);
                         asm volatile("" ::: "memory");     // keeps the compiler from sinking the fetch below the atomics
                         unsigned long long pp[NP];
@@ -322,20 +410,19 @@ __global__ __launch_bounds__(NT, S > 1 ? 2 : 4) void k_values(const ValuesArgs a
             }
         }
         __syncthreads();
-        if constexpr (COPIES > 1) {                        // the copies' sums, in copy 0 (no carry between the halves: their sums stay below 2^31)
-            constexpr int ROW = NP * CB;
-            for (int x = tid; x < S * kK * ROW; x += NT) {
-                unsigned long long *row = reinterpret_cast<unsigned long long *>(lds) + x / ROW * WORDS + x % ROW;
-                unsigned long long v = 0;
-#pragma unroll
-                for (int k = 0; k < COPIES; ++k) v += row[((k + x / ROW) & (COPIES - 1)) * ROW];  // (neighbouring rows on different banks)
-                row[0] = v;
-            }
+        if (SPANS && live > 1) {                          // the spans' sums in whole units of the range
+            const float per0 = per_s[head0], per1 = per_s[head1];
+            add_span(live - 1, [&](int x, float2 t) __attribute__((always_inline)) {
+                reinterpret_cast<unsigned long long *>(lds)[x / ROW * WORDS + x % ROW] =
+                    (unsigned long long)whole_units(t.x, per0) | (unsigned long long)whole_units(t.y, per1) << 32;
+            });
+            __syncthreads();
+        } else if constexpr (COPIES > 1) {                 // the copies' sums, in copy 0
+            for (int x = tid; x < S * kK * ROW; x += NT) reinterpret_cast<unsigned long long *>(lds)[x / ROW * WORDS + x % ROW] = copies_sum(x);
             __syncthreads();
         }
     }
     if (a.mode != 0) {
-        constexpr int ROW = NP * CB;                   // words of a row without copies
 #pragma unroll
         for (int s = 0; s < S; ++s) {
             if (sv0[s] >= sv1[s]) continue;
