@@ -114,7 +114,7 @@ __device__ __forceinline__ float swap32_add(float x, float y)
 //
 // Product.  The bins of CB codebooks are a (heads x CB K) x (CB K x d) matrix product.  A bin is an integer of four 8-bit
 // digits, each exact in bf16, so that digit x head fill the 16 rows of v_mfma_f32_16x16x32_bf16 (4 heads; two tiles for 8) and
-// the exact bins are multiplied, not their 24 leading bits; the digits' sums are scaled by 256^digit at the end.  The
+// the exact bins are multiplied, not their 24 leading bits; the digits' sums are scaled by 256^(digit - 4) at the end.  The
 // wavefronts share the k-steps; a lane loads 16 bytes of 8 rows (256 bytes of a row per 16 lanes) and interleaves them in
 // registers, column 8 n + t of lane n for tile t, so the codebook needs no other layout.  fp32 rows are multiplied by vector
 // instructions, four columns per lane.
@@ -496,8 +496,9 @@ __global__ __launch_bounds__(NT, S > 1 ? 2 : 4) void k_values(const ValuesArgs a
                 __builtin_amdgcn_sched_barrier(0);
             }
             const int ln = fresh_lane(), n = ln & 15, kg = ln >> 4;
-            // digits combined: lane (n, kg) keeps head 4 x + kg of column NCT n + t
-            const float dscale = kg == 0 ? 1.f : kg == 1 ? 256.f : kg == 2 ? 65536.f : 16777216.f;
+            // digits combined: lane (n, kg) keeps head 4 x + kg of column NCT n + t.  (Bins as fractions of 2^32, so that no sum is larger than the
+            // codebook's rows; a wavefront's own, of digits, overflow for codebooks beyond 5e33.)
+            const float dscale = kg == 0 ? 0x1p-32f : kg == 1 ? 0x1p-24f : kg == 2 ? 0x1p-16f : 0x1p-8f;
             float sums[S][NX][NCT];
 #pragma unroll
             for (int s = 0; s < S; ++s)
@@ -534,7 +535,7 @@ __global__ __launch_bounds__(NT, S > 1 ? 2 : 4) void k_values(const ValuesArgs a
                 const unsigned char *at = lds + code * ROWB + cb * 8;
 #pragma unroll
                 for (int hh = 0; hh < G; ++hh) {
-                    const float w = (float)*reinterpret_cast<const unsigned *>(at + hh / 2 * (CB * 8) + (hh & 1) * 4);
+                    const float w = (float)*reinterpret_cast<const unsigned *>(at + hh / 2 * (CB * 8) + (hh & 1) * 4) * 0x1p-32f;
                     sum[hh][0] += w * c.x; sum[hh][1] += w * c.y; sum[hh][2] += w * c.z; sum[hh][3] += w * c.w;
                 }
             }
@@ -562,7 +563,7 @@ __global__ __launch_bounds__(NT, S > 1 ? 2 : 4) void k_values(const ValuesArgs a
             float sum = 0.f;
 #pragma unroll
             for (int w = 0; w < NW; ++w) sum += red[w * (S * G * COLS) + o];
-            a.partial[((((size_t)b * a.Hq + (size_t)g * G + hh) * a.ranges + rng) * a.ncg + cg) * kD + cs * COLS + col] = sum * unit_s[s * G + hh];
+            a.partial[((((size_t)b * a.Hq + (size_t)g * G + hh) * a.ranges + rng) * a.ncg + cg) * kD + cs * COLS + col] = sum * (unit_s[s * G + hh] * 4294967296.f);
         }
     }
 }

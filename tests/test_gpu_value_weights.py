@@ -69,3 +69,18 @@ def test_weights_are_as_fine_as_value_splits_make_them(gpu, keys, G, Hkv, Mv, dt
     print(f"  error {err:.2e}, bound {bound:.2e} (splits of {op.plan.value_split_len}: {coarse:.2e})", flush=True)
     assert err <= bound
     op.close()
+
+
+# Codebooks of any magnitude: a power of two comes through unchanged.  (Bins are whole numbers of up to 2^32, of which a product with them as they
+# are would overflow from 2^96 on.)
+@pytest.mark.parametrize("exponent", [-100, 100])
+@pytest.mark.parametrize("G,Hkv,Mv,dtype,lens", [(4, 8, 16, "bf16", [3000]), (4, 8, 32, "bf16", [9000]), (8, 8, 32, "bf16", [3000, 5]),
+                                                 (4, 8, 32, "bf16", [300] * 40), (1, 1, 16, "f32", [4000]), (8, 2, 16, "f32", [2000])])
+def test_codebooks_of_any_magnitude(gpu, G, Hkv, Mv, dtype, lens, exponent):  # noqa: F811
+    import torch
+    w = make("indexed", G, Hkv, Mv, dtype, lens)
+    dw, op = gpu.DeviceWorkload(w), gpu.DecodeAttention(w)
+    plain = op(dw).clone()
+    dw.val_codebooks = (dw.val_codebooks.float() * 2.0 ** exponent).to(dw.val_codebooks.dtype)
+    assert torch.equal(op(dw), plain * 2.0 ** exponent)
+    op.close()
