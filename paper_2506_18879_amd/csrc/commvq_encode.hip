@@ -508,11 +508,16 @@ __global__ __launch_bounds__(kFewThreads) void k_encode_few(const void *__restri
                     for (int kc = 0; kc < 4; ++kc)
                         part[s3][kc] = *reinterpret_cast<const uint4_t *>(lds + kFewParts + ((4 * kc + gk) * 16 + ((3 * wave + s3) ^ (4 * kc + gk))) * 16);
                 unsigned tiles = 0u;
-                if (__any(!(o.z > m + bound && rc < 1e37f))) {  // two of a lane's 8 rows
+                const unsigned some = (unsigned)__ballot(!(o.x > m + bound));
+                if (__any(!(rc < 1e37f)) || __builtin_popcount(some) > 12) {
                     tiles = 0xffffu;
-                } else {
-                    for (unsigned hold = (unsigned)__ballot(o.x <= m + bound); hold; hold &= hold - 1)
-                        tiles |= 1u << (__builtin_amdgcn_readlane(__builtin_bit_cast(int, o.y), __builtin_ctz(hold)) >> 4 & 15);
+                } else {                                   // a lane's 8 rows are of two tiles: both, if two of the rows are candidates.  (32 levels of 8 tokens,
+                                                           // every row with a twin next to it: 54 us, with all tiles then 156; k_encode_rows<8> 47)
+                    const unsigned both = (unsigned)__ballot(!(o.z > m + bound));
+                    for (unsigned hold = some; hold; hold &= hold - 1) {
+                        const int at = __builtin_ctz(hold), t = __builtin_amdgcn_readlane(__builtin_bit_cast(int, o.y), at) >> 4 & 15;
+                        tiles |= both >> at & 1 ? 3u << (t & 14) : 1u << t;
+                    }
                 }
                 float least = INFINITY;
                 row = 0;
@@ -574,7 +579,10 @@ __global__ __launch_bounds__(kFewThreads) void k_encode_few(const void *__restri
 // update 600, the split 650, the second look 700 on average.  4000 tokens, 8 heads, 32 levels: 136 us, with all three parts and
 // the compiler's order 177 us.  The two wavefronts of a SIMD half a level apart (a barrier for each half) took 155: a
 // wavefront by itself issues an instruction every 5 clk, and that bounds its products at 26 clk each.  Two workgroups of four
-// wavefronts with an image each, 147.  (A codebook whose every row has a twin is searched twice throughout: 335 us.)
+// wavefronts with an image each, 147.
+// Where rows have twins (a trained codebook with merged codewords) the screen decides nothing.  A wavefront that has had to repeat every tile for five
+// tokens, of one level or of several, takes the next 15 levels without a screen, and 31 after each further try.  Every row with a twin, 32 levels:
+// 265 -> 168 us (all three parts throughout: 168); a tenth of the rows: 234 -> 204 (178).
 constexpr int kManyThreads = 512, kManyTokens = 128;
 constexpr int kManyNorms = 2 * kErImg * 16;              // [2][256] -|c|^2 / 2
 constexpr int kManyWhole = kManyNorms + 2 * kK * 4;        // [2][256] |c|^2
@@ -662,6 +670,9 @@ __global__ __launch_bounds__(kManyThreads, 2) void k_encode_many(const void *__r
     split();
     const unsigned keep = opaque_sgpr(0xffffffc0u);
     const float inf = __builtin_bit_cast(float, opaque_sgpr(0x7f800000u));
+    // Levels to come without a screen, how many when next it does not pay, and what tells: 4 for each near token of a screen that repeated
+    // every tile, 1 less for each that did not.
+    int plain = 0, stretch = 15, in_vain = 0;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // level 0 has landed
     __syncthreads();
     for (int l = 0; l < a.levels; ++l) {
@@ -673,71 +684,87 @@ __global__ __launch_bounds__(kManyThreads, 2) void k_encode_many(const void *__r
         auto mul = [&](const uint4_t &r, const uint4_t &x, const floatx4_t &d) __attribute__((always_inline)) {
             return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, r), __builtin_bit_cast(bf16x8_t, x), d, 0, 0, 0);
         };
-        // multiply: two row tiles at a time, with the medians of the two before them between the matrix instructions
         const int next = l + 1 < a.levels ? l + 1 : l;     // (the last level is sent once more, to nobody)
         norm = nrows[(unsigned)(next * kK + (tid & (kK - 1)))];
-        uint4_t A[2][4][2];
-        floatx4_t D[2][2], start[2];
-        auto norms_of = [&](int t) __attribute__((always_inline)) { return *reinterpret_cast<const floatx4_t *>(nrm + t * 16 + 4 * gk); };
+        int brow = 0;
+        bool near = true;
+        unsigned tiles = 0xffffu;
+        const bool searched = plain > 0;
+        if (searched) {
+            --plain;
 #pragma unroll
-        for (int e = 0; e < 2; ++e) start[e] = norms_of(e);
+            for (int i = 0; i < 8; ++i) fetch_rows(next, (l + 1) & 1, i);
+        } else {
+            // multiply: two row tiles at a time, with the medians of the two before them between the matrix instructions
+            uint4_t A[2][4][2];
+            floatx4_t D[2][2], start[2];
+            auto norms_of = [&](int t) __attribute__((always_inline)) { return *reinterpret_cast<const floatx4_t *>(nrm + t * 16 + 4 * gk); };
 #pragma unroll
-        for (int kc = 0; kc < 4; ++kc)
+            for (int e = 0; e < 2; ++e) start[e] = norms_of(e);
 #pragma unroll
-            for (int e = 0; e < 2; ++e) A[0][kc][e] = rows_of(e, kc);
-        float best = -INFINITY, second = -INFINITY, sc = 0.f;
+            for (int kc = 0; kc < 4; ++kc)
 #pragma unroll
-        for (int t = 0; t <= 16; t += 2) {
-            const int cur = (t >> 1) & 1, old = cur ^ 1;
+                for (int e = 0; e < 2; ++e) A[0][kc][e] = rows_of(e, kc);
+            float best = -INFINITY, second = -INFINITY, sc = 0.f;
 #pragma unroll
-            for (int m = 0; m < 16; ++m) {                 // a matrix instruction (16 clk), one or two vector ones, a read or none
-                const int st = m >> 1, kc = st >> 1, e = m & 1;
-                if (t < 16) D[cur][e] = mul(A[cur][kc][e], part[st & 1][kc], st == 0 ? start[e] : D[cur][e]);
-                if (t > 0)
+            for (int t = 0; t <= 16; t += 2) {
+                const int cur = (t >> 1) & 1, old = cur ^ 1;
 #pragma unroll
-                    for (int u = (24 * m) / 16; u < (24 * m + 24) / 16; ++u) {
-                        const int i = u / 3;
-                        const float d = D[old][i >> 2][i & 3];  // (a bit cast of the element itself would read element 0)
-                        if (u % 3 == 0) sc = __builtin_bit_cast(float, (__builtin_bit_cast(unsigned, d) & keep) | (unsigned)(4 * (t - 2) + i));
-                        if (u % 3 == 1) second = __builtin_amdgcn_fmed3f(best, second, sc);
-                        if (u % 3 == 2) best = __builtin_amdgcn_fmed3f(best, sc, inf);  // the larger one
+                for (int m = 0; m < 16; ++m) {                 // a matrix instruction (16 clk), one or two vector ones, a read or none
+                    const int st = m >> 1, kc = st >> 1, e = m & 1;
+                    if (t < 16) D[cur][e] = mul(A[cur][kc][e], part[st & 1][kc], st == 0 ? start[e] : D[cur][e]);
+                    if (t > 0)
+#pragma unroll
+                        for (int u = (24 * m) / 16; u < (24 * m + 24) / 16; ++u) {
+                            const int i = u / 3;
+                            const float d = D[old][i >> 2][i & 3];  // (a bit cast of the element itself would read element 0)
+                            if (u % 3 == 0) sc = __builtin_bit_cast(float, (__builtin_bit_cast(unsigned, d) & keep) | (unsigned)(4 * (t - 2) + i));
+                            if (u % 3 == 1) second = __builtin_amdgcn_fmed3f(best, second, sc);
+                            if (u % 3 == 2) best = __builtin_amdgcn_fmed3f(best, sc, inf);  // the larger one
+                        }
+                    if (t < 14) {
+                        if (!(m & 1)) A[old][m >> 2][(m >> 1) & 1] = rows_of(t + 2 + ((m >> 1) & 1), m >> 2);
+                        if (m == 3 || m == 5) start[(m >> 1) - 1] = norms_of(t + 2 + (m >> 1) - 1);
                     }
-                if (t < 14) {
-                    if (!(m & 1)) A[old][m >> 2][(m >> 1) & 1] = rows_of(t + 2 + ((m >> 1) & 1), m >> 2);
-                    if (m == 3 || m == 5) start[(m >> 1) - 1] = norms_of(t + 2 + (m >> 1) - 1);
+                    if (t < 16 && m == 7) fetch_rows(next, (l + 1) & 1, t >> 1);
+                    if (t > 0) asm volatile("" : "+v"(best), "+v"(second), "+v"(sc));  // here, not where they are used
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-                if (t < 16 && m == 7) fetch_rows(next, (l + 1) & 1, t >> 1);
-                if (t > 0) asm volatile("" : "+v"(best), "+v"(second), "+v"(sc));  // here, not where they are used
-                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (norms_too) put_norms((l + 1) & 1);
+            const float4 t4 = *reinterpret_cast<const float4 *>(tops + (l & 1) * 4);
+            // choose
+            float lo = best, up = second;
+            two_largest16(lo, up);
+            two_largest32(lo, up);
+            const unsigned long long who = __ballot(best == lo);  // one lane of the token's four
+            const unsigned w0 = (unsigned)who >> n, w1 = (unsigned)(who >> 32) >> n;
+            const int at = (int)(__builtin_bit_cast(unsigned, lo) & 63u);
+            brow = (at >> 2) * 16 + 4 * (int)(((w0 >> 16) & 1u) + 2u * (w1 & 1u) + 3u * ((w1 >> 16) & 1u)) + (at & 3);
+            // A cost is off by the third part, |r''| |c|; by the last six bits, 2^-17 of it; and by the roundings of the sums, 8 here
+            // and 13 in k_encode_rows, of at most |c|^2 / 2 + |r| |c|.  Overflow and NaN fail a comparison.
+            const float top = fmaxf(fmaxf(t4.x, t4.y), fmaxf(t4.z, t4.w)), cmax = __builtin_amdgcn_sqrtf(2.f * top + 1e-34f), rc = 1.01f * __builtin_amdgcn_sqrtf(whole2) * cmax;
+            const float bound = 2.f * third * cmax + 1.6e-5f * fabsf(lo) + 7.7e-6f * (top + rc);
+            const float left = __builtin_fmaf(whole2, 1.000001f, 4.f * bound - 2.f * lo);  // |r - c|^2 = |r|^2 - 2 (r c - |c|^2 / 2)
+            whole2 = left < 1e-34f ? 1e-34f : left;            // (not fmaxf: NaN has to stay, and to fail the comparison below)
+            near = !(lo - up > bound && rc < 1e37f);
+            tiles = 0u;
+            if (__any(near)) {
+                // the row tiles that hold a near token's candidates: the lanes' best, or all tiles if a lane's second best is one too
+                if (__any(near && !(second < lo - bound && rc < 1e37f))) {
+                    tiles = 0xffffu;
+                } else {
+                    for (unsigned long long hold = __ballot(near && best >= lo - bound); hold; hold &= hold - 1)
+                        tiles |= 1u << (__builtin_amdgcn_readlane(__builtin_bit_cast(int, best), __builtin_ctzll(hold)) >> 2 & 15);
+                }
+            }
+            in_vain = tiles == 0xffffu ? in_vain + __builtin_popcountll(__ballot(near)) : max(in_vain - 1, 0);
+            if (in_vain >= 20) {
+                plain = stretch;
+                stretch = 31;
             }
         }
-        if (norms_too) put_norms((l + 1) & 1);
-        const float4 t4 = *reinterpret_cast<const float4 *>(tops + (l & 1) * 4);
-        // choose
-        float lo = best, up = second;
-        two_largest16(lo, up);
-        two_largest32(lo, up);
-        const unsigned long long who = __ballot(best == lo);  // one lane of the token's four
-        const unsigned w0 = (unsigned)who >> n, w1 = (unsigned)(who >> 32) >> n;
-        const int at = (int)(__builtin_bit_cast(unsigned, lo) & 63u);
-        int brow = (at >> 2) * 16 + 4 * (int)(((w0 >> 16) & 1u) + 2u * (w1 & 1u) + 3u * ((w1 >> 16) & 1u)) + (at & 3);
-        // A cost is off by the third part, |r''| |c|; by the last six bits, 2^-17 of it; and by the roundings of the sums, 8 here
-        // and 13 in k_encode_rows, of at most |c|^2 / 2 + |r| |c|.  Overflow and NaN fail a comparison.
-        const float top = fmaxf(fmaxf(t4.x, t4.y), fmaxf(t4.z, t4.w)), cmax = __builtin_amdgcn_sqrtf(2.f * top + 1e-34f), rc = 1.01f * __builtin_amdgcn_sqrtf(whole2) * cmax;
-        const float bound = 2.f * third * cmax + 1.6e-5f * fabsf(lo) + 7.7e-6f * (top + rc);
-        const float left = __builtin_fmaf(whole2, 1.000001f, 4.f * bound - 2.f * lo);  // |r - c|^2 = |r|^2 - 2 (r c - |c|^2 / 2)
-        whole2 = left < 1e-34f ? 1e-34f : left;            // (not fmaxf: NaN has to stay, and to fail the comparison below)
-        const bool near = !(lo - up > bound && rc < 1e37f);
-        if (__any(near)) {
-            // the row tiles that hold a near token's candidates: the lanes' best, or all tiles if a lane's second best is one too
-            unsigned long long hold = __ballot(near && best >= lo - bound);
-            unsigned tiles = 0u;
-            if (__any(near && !(second < lo - bound && rc < 1e37f))) {
-                tiles = 0xffffu;
-            } else {
-                for (; hold; hold &= hold - 1)
-                    tiles |= 1u << (__builtin_amdgcn_readlane(__builtin_bit_cast(int, best), __builtin_ctzll(hold)) >> 2 & 15);
-            }
+        if (tiles) {
             uint4_t exact[3][4];
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
@@ -752,12 +779,7 @@ __global__ __launch_bounds__(kManyThreads, 2) void k_encode_many(const void *__r
             }
             float least = INFINITY;
             int row = 0;
-            while (tiles) {                                // two at a time; rows come in increasing order: ties keep the lowest
-                int t[2];
-                t[0] = __builtin_ctz(tiles);
-                tiles &= tiles - 1;
-                t[1] = tiles ? __builtin_ctz(tiles) : t[0];
-                tiles &= tiles - 1;
+            auto take = [&](const int (&t)[2]) __attribute__((always_inline)) {  // two tiles; rows come in increasing order: ties keep the lowest
                 floatx4_t nr[2], E[2];
 #pragma unroll
                 for (int e = 0; e < 2; ++e) {
@@ -779,9 +801,23 @@ __global__ __launch_bounds__(kManyThreads, 2) void k_encode_many(const void *__r
                         const float sc = nr[e][r] - 2.f * E[e][r];
                         if (sc < least) { least = sc; row = t[e] * 16 + 4 * gk + r; }
                     }
+            };
+            if (tiles == 0xffffu) {
+#pragma unroll
+                for (int e = 0; e < 16; e += 2) take({e, e + 1});
+            } else {
+                while (tiles) {
+                    int t[2];
+                    t[0] = __builtin_ctz(tiles);
+                    tiles &= tiles - 1;
+                    t[1] = tiles ? __builtin_ctz(tiles) : t[0];
+                    tiles &= tiles - 1;
+                    take(t);
+                }
             }
             min4(least, row);
             brow = near ? row : brow;
+            if (searched && norms_too) put_norms((l + 1) & 1);
         }
         if (gk == 0) chosen[tl * 32 + l] = (uint8_t)brow;
         // residual -= chosen row (the lane's elements of it)
@@ -795,7 +831,15 @@ __global__ __launch_bounds__(kManyThreads, 2) void k_encode_many(const void *__r
                 res[8 * kc + 2 * i + 1] -= bf16_hi(ws[i]);
             }
         }
-        split();
+        if (!plain) {
+            if (searched) {
+                whole2 = 0.f;
+#pragma unroll
+                for (int i = 0; i < 32; ++i) whole2 = __builtin_fmaf(res[i], res[i], whole2);
+                whole2 = sum4(whole2) * 1.0001f + 1e-34f;
+            }
+            split();
+        }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's rows of level l + 1 have landed
         __syncthreads();                                   // ... and everybody's, and level l is no longer read
     }

@@ -50,3 +50,33 @@ def test_codes_do_not_depend_on_the_size_of_the_call(gpu, n, heads, kind):  # no
     few = 512 if heads == 8 else 500
     want = np.concatenate([encode_on_gpu(gpu, w, np.ascontiguousarray(keys[some[i:i + few]]), L_cap=few + 1) for i in range(0, len(some), few)], axis=1)
     assert np.array_equal(got[:, some], want)
+
+
+# Rows that have twins (merged codewords) tie at every level.  Repeating what the screen left open took 1.95 times (thousands of vectors)
+# and 4.6 times (a few) as long as a codebook without; searching without a screen and only the tiles that hold candidates, 1.25 and 1.7.
+@pytest.mark.parametrize("n,most", [(4000, 1.6), (8, 2.6)])
+def test_codebooks_with_twins_are_not_searched_twice(gpu, n, most):  # noqa: F811
+    import torch
+    import paper_2506_18879_amd as cv
+    w = synth.make_workload("enc_twins", B=1, Hq=8, Hkv=8, seqlens=[8], Mk=32, Mv=16, dtype="bf16", seed=9)
+    op = gpu.DecodeAttention(w)
+    books = [gpu.to_device(w.key_codebooks, True)]
+    books.append(books[0].view(8, 32, 128, 2, 128)[:, :, :, :1].expand(8, 32, 128, 2, 128).contiguous())
+    keys = torch.randn((n, 8, 128), device="cuda").to(torch.bfloat16)
+    codes = torch.empty((8, n, 32), dtype=torch.uint8, device="cuda")
+    times = []
+    for book in books:
+        tables = torch.empty(cv.commvq_encoder_table_bytes(op.handle), dtype=torch.uint8, device="cuda")
+        cv.commvq_encoder_prepare(op.handle, book, tables)
+        best = float("inf")
+        for _ in range(8):
+            start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            start.record()
+            for _ in range(10):
+                cv.commvq_encode_keys(op.handle, keys, n, book, tables, codes, 32, n * 32)
+            end.record()
+            torch.cuda.synchronize()
+            best = min(best, start.elapsed_time(end))
+        times.append(best)
+    op.close()
+    assert times[1] <= most * times[0], times
