@@ -1576,7 +1576,6 @@ struct OutArgs {
     int Hq, Hkv, nvsplit, vsplit_len, nchunk, Mv;
     int batch;
     int per_split;  // partial results per value split (k_values); 0: nchunk in all
-    int per_wg;  // k_out_mfma: chunks of kOutMfmaRows rows that a workgroup takes one after the other
 };
 
 // Second half of the binary value code (indexed values: k_values).  Bins row r of a KV head is code bit c = vbits_code_bit(r),
@@ -1728,7 +1727,7 @@ __global__ __launch_bounds__(256) void k_prep_values(const uint16_t *__restrict_
 
 // The output stage for batches (Eq. optimized_v's bins x C_V as what it is for several sequences, a matrix product):
 // per KV head, [sequences x query heads] x [M_v K rows] times [rows] x [d].  A workgroup takes 16 output rows
-// (16 / G sequences), per_wg chunks of kOutMfmaRows codebook rows and all d columns: it sums the fixed-point bins of its rows over the
+// (16 / G sequences), kOutMfmaRows codebook rows and all d columns: it sums the fixed-point bins of its rows over the
 // value splits (fp32, each split's unit applied), splits every fp32 weight EXACTLY into three bf16 parts (24 mantissa
 // bits = 8 + 8 + 8) and multiplies them with the bf16 codebook by v_mfma_f32_16x16x32_bf16, accumulating in fp32: the
 // fp32 product up to summation order, at a tenth of the vector instructions.  Each wavefront takes 32 of the 128 columns;
@@ -1740,7 +1739,7 @@ __global__ __launch_bounds__(kOutThreads) void k_out_mfma(OutArgs a, const uint4
     constexpr int KC = kOutMfmaRows, SPT = 16 / G, WS = KC + 8;  // (row stride padded: the 16 rows fall on different banks)
     __shared__ __attribute__((aligned(16))) uint16_t Wl[3][16][WS];
     int id = blockIdx.x;
-    const int part = id % a.nchunk;  // chunks part * per_wg .. + per_wg - 1 of kOutMfmaRows rows
+    const int chunk = id % a.nchunk;  // of kOutMfmaRows rows
     id /= a.nchunk;
     const int g = id % a.Hkv;
     const int b0 = (id / a.Hkv) * SPT;
@@ -1777,80 +1776,73 @@ __global__ __launch_bounds__(kOutThreads) void k_out_mfma(OutArgs a, const uint4
             bv[0] = pv[0];
         }
     };
-    floatx4_t total[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-    for (int c = 0; c < a.per_wg; ++c) {
-        const int chunk = part * a.per_wg + c;
-        if (c > 0) __syncthreads();  // the previous chunk's weights are no longer read
-        if (a.nvsplit == 1) {
-            // one value split (up to 1024 tokens, or batch x KV heads above 128): a thread's bins of all SPT sequences travel
-            // together.  Whole call, inputs changing from pass to pass, 32 codebooks, 512..1000 tokens: 4 sequences 40.1 -> 38.8 us, 64
-            // 140.8 -> 136.0, 40 of 8 heads 153.2 -> 148.6; with 16 splits and few workgroups this form takes 25 us, the other 13
-            static_assert(KC == kOutThreads, "a thread takes one codebook row of every sequence");
-            unsigned bv[SPT][G];
-            float unit[SPT][G];
+    if (a.nvsplit == 1) {
+        // one value split: a thread's bins of all SPT sequences travel together.  Whole call with the form below and with this one, inputs
+        // changing from pass to pass: 64 sequences of 512..1024 tokens, 4096 bits 109.3 -> 107.8 us, 130 of them 241.2 -> 238.2, 260 of
+        // 64..128, 1024 bits 183.2 -> 180.7
+        static_assert(KC == kOutThreads, "a thread takes one codebook row of every sequence");
+        unsigned bv[SPT][G];
+        float unit[SPT][G];
 #pragma unroll
-            for (int i = 0; i < SPT; ++i) {
+        for (int i = 0; i < SPT; ++i) {
 #pragma unroll
-                for (int hh = 0; hh < G; ++hh) { bv[i][hh] = 0u; unit[i][hh] = 0.f; }
-                const int b = b0 + i;
-                if (b < a.batch && a.cu[b + 1] > a.cu[b]) {
-                    load_bins(a.bins + (size_t)(b * a.Hkv + g) * G * MK + (size_t)(chunk * KC + tid) * G, bv[i]);
+            for (int hh = 0; hh < G; ++hh) { bv[i][hh] = 0u; unit[i][hh] = 0.f; }
+            const int b = b0 + i;
+            if (b < a.batch && a.cu[b + 1] > a.cu[b]) {
+                load_bins(a.bins + (size_t)(b * a.Hkv + g) * G * MK + (size_t)(chunk * KC + tid) * G, bv[i]);
 #pragma unroll
-                    for (int hh = 0; hh < G; ++hh) unit[i][hh] = a.vscale[(size_t)b * a.Hq + (size_t)g * G + hh];
-                }
+                for (int hh = 0; hh < G; ++hh) unit[i][hh] = a.vscale[(size_t)b * a.Hq + (size_t)g * G + hh];
             }
+        }
 #pragma unroll
-            for (int i = 0; i < SPT; ++i) {
-                float w[G];
+        for (int i = 0; i < SPT; ++i) {
+            float w[G];
 #pragma unroll
-                for (int hh = 0; hh < G; ++hh) w[hh] = (float)bv[i][hh] * unit[i][hh];
-                put(i, tid, w);
-            }
-        } else {
-            for (int it = tid; it < SPT * KC; it += kOutThreads) {
-                const int sq = it / KC, k = it % KC, b = b0 + sq;
-                float w[G];
+            for (int hh = 0; hh < G; ++hh) w[hh] = (float)bv[i][hh] * unit[i][hh];
+            put(i, tid, w);
+        }
+    } else {
+        for (int it = tid; it < SPT * KC; it += kOutThreads) {
+            const int sq = it / KC, k = it % KC, b = b0 + sq;
+            float w[G];
 #pragma unroll
-                for (int hh = 0; hh < G; ++hh) w[hh] = 0.f;
-                if (b < a.batch) {
-                    const int L = a.cu[b + 1] - a.cu[b];
-                    const int nvs = min((L + a.vsplit_len - 1) / a.vsplit_len, a.nvsplit);
-                    const unsigned *src = a.bins + (size_t)(b * a.Hkv + g) * a.nvsplit * G * MK + (size_t)(chunk * KC + k) * G;
-                    const float *scl = a.vscale + ((size_t)b * a.Hq + (size_t)g * G) * a.nvsplit;
+            for (int hh = 0; hh < G; ++hh) w[hh] = 0.f;
+            if (b < a.batch) {
+                const int L = a.cu[b + 1] - a.cu[b];
+                const int nvs = min((L + a.vsplit_len - 1) / a.vsplit_len, a.nvsplit);
+                const unsigned *src = a.bins + (size_t)(b * a.Hkv + g) * a.nvsplit * G * MK + (size_t)(chunk * KC + k) * G;
+                const float *scl = a.vscale + ((size_t)b * a.Hq + (size_t)g * G) * a.nvsplit;
 #pragma unroll 4
-                    for (int v = 0; v < nvs; ++v) {
-                        unsigned bv[G];
-                        load_bins(src + (size_t)v * G * MK, bv);
+                for (int v = 0; v < nvs; ++v) {
+                    unsigned bv[G];
+                    load_bins(src + (size_t)v * G * MK, bv);
 #pragma unroll
-                        for (int hh = 0; hh < G; ++hh) w[hh] += (float)bv[hh] * scl[(size_t)hh * a.nvsplit + v];
-                    }
+                    for (int hh = 0; hh < G; ++hh) w[hh] += (float)bv[hh] * scl[(size_t)hh * a.nvsplit + v];
                 }
-                put(sq, k, w);
             }
+            put(sq, k, w);
         }
-        __syncthreads();
-        floatx4_t acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-        const uint4 *bsrc = vp + (((size_t)g * (MK / 32) + (size_t)chunk * (KC / 32)) * kD + 32 * wave + n) * 4 + kg;
+    }
+    __syncthreads();
+    floatx4_t acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    const uint4 *bsrc = vp + (((size_t)g * (MK / 32) + (size_t)chunk * (KC / 32)) * kD + 32 * wave + n) * 4 + kg;
 #pragma unroll
-        for (int kt = 0; kt < KC / 32; ++kt) {
-            const uint4 B0 = bsrc[(size_t)(kt * kD) * 4], B1 = bsrc[(size_t)(kt * kD + 16) * 4];
+    for (int kt = 0; kt < KC / 32; ++kt) {
+        const uint4 B0 = bsrc[(size_t)(kt * kD) * 4], B1 = bsrc[(size_t)(kt * kD + 16) * 4];
 #pragma unroll
-            for (int p = 0; p < 3; ++p) {
-                const uint4 A = *reinterpret_cast<const uint4 *>(&Wl[p][n][32 * kt + 8 * kg]);
-                acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, A), __builtin_bit_cast(bf16x8_t, B0), acc[0], 0, 0, 0);
-                acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, A), __builtin_bit_cast(bf16x8_t, B1), acc[1], 0, 0, 0);
-            }
+        for (int p = 0; p < 3; ++p) {
+            const uint4 A = *reinterpret_cast<const uint4 *>(&Wl[p][n][32 * kt + 8 * kg]);
+            acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, A), __builtin_bit_cast(bf16x8_t, B0), acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, A), __builtin_bit_cast(bf16x8_t, B1), acc[1], 0, 0, 0);
         }
-        total[0] += acc[0];
-        total[1] += acc[1];
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int i = 4 * kg + r, b = b0 + i / G, hh = i % G;
         if (b < a.batch) {
-            float *dst = a.partial + (((size_t)b * a.Hq + (size_t)g * G + hh) * a.nchunk + part) * kD + 32 * wave + n;
-            dst[0] = total[0][r];
-            dst[16] = total[1][r];
+            float *dst = a.partial + (((size_t)b * a.Hq + (size_t)g * G + hh) * a.nchunk + chunk) * kD + 32 * wave + n;
+            dst[0] = acc[0][r];
+            dst[16] = acc[1][r];
         }
     }
 }
@@ -2252,7 +2244,7 @@ commvq_status run_output(commvq_handle *h, const void *val_cb, const commvq_posi
     a.partial = w.partial; a.out = out;
     a.Hq = c.n_q_heads; a.Hkv = c.n_kv_heads;
     a.nvsplit = plan.value_splits; a.vsplit_len = plan.value_split_len;
-    a.nchunk = plan.out_chunks; a.Mv = val_books(c); a.batch = pos->batch; a.per_wg = 1; a.per_split = 0;
+    a.nchunk = plan.out_chunks; a.Mv = val_books(c); a.batch = pos->batch; a.per_split = 0;
     const int grid = pos->batch * c.n_kv_heads * plan.out_chunks;
     const bool bf16 = c.codebook_dtype == COMMVQ_BF16;
     hipError_t e;
@@ -2267,13 +2259,8 @@ commvq_status run_output(commvq_handle *h, const void *val_cb, const commvq_posi
         a.nchunk = val_books(c) * kK / kOutMfmaRows;
         const int spt = 16 / h->G;
         const int rows = (pos->batch + spt - 1) / spt * c.n_kv_heads;
-        // A workgroup takes several chunks one after the other as long as 1024 workgroups, four per compute unit, are left:
-        // its partial results are then one row instead of one per chunk, written here and read by k_out_final.  Whole
-        // call, inputs changing from pass to pass, 64 sequences of 512..1024 tokens: 32 codebooks 139.6 us with 4096 workgroups,
-        // 134.8 with 2048, 135.6 with 1024, 156 with 512; 16 codebooks 109.4 with 2048, 107.2 with 1024, 116 with 512; 32
-        // sequences, 32 codebooks 82.5 with 2048, 81.1 with 1024, 91.6 with 512.
-        a.per_wg = 1;
-        while (a.nchunk % 2 == 0 && (int64_t)rows * (a.nchunk / 2) >= 1024) { a.nchunk /= 2; a.per_wg *= 2; }
+        // A chunk per workgroup.  Two or four one after the other, for fewer partial results, made no difference of half a microsecond
+        // (130 sequences of 64..128 tokens, 2048 bits 128.0 -> 127.8 us, 4096 bits 161.2 -> 160.8; of 512..1024 tokens 186.6 and 232.7 either way).
         const int mgrid = rows * a.nchunk;
         switch (h->G) {
         case 1: hipLaunchKernelGGL(k_out_mfma<1>, dim3(mgrid), dim3(kOutThreads), 0, s, a, vp); break;

@@ -654,8 +654,8 @@ def test_two_handles_on_two_streams_do_not_disturb_each_other(gpu):
 @pytest.mark.parametrize("G,Hkv,Mv,lens", [(4, 2, 16, [900, 40, 2100, 0, 333]), (8, 1, 32, [1500, 700]), (1, 2, 32, [300] * 17),
                                            (2, 2, 16, [64, 1, 5000, 129, 77, 2048, 3, 999, 12])])
 def test_batched_output_stage_on_the_matrix_cores(gpu, oracle, G, Hkv, Mv, lens):
-    # 16 or more output rows (sequences x query heads of a KV head): bins x value codebook as a matrix product
-    # (k_out_mfma), with the value codebook re-laid per call or once (commvq_pack_value_codebooks): identical bits
+    # batches of indexed values: bins x value codebook on the matrix cores inside k_values.  It reads the codebook as it is: packing and
+    # forgetting are accepted and change nothing.  (What they do for binary values: test_gpu_output_batches.py)
     import torch
     import paper_2506_18879_amd as cv
     assert len(lens) * G >= 16
