@@ -1,5 +1,7 @@
 """Paired keys at the numbers of levels where the score kernel's sets of four levels begin and end, with contexts around its passes and
 tiles and of several sequences: logits and outputs against the oracle as in test_gpu_parity.py."""
+import re
+
 import numpy as np
 import pytest
 
@@ -10,7 +12,7 @@ from test_gpu_parity import TOL_SCORE, assert_rows, gpu  # noqa: F401  (gpu: fix
 pytestmark = pytest.mark.gpu
 
 
-def check(gpu, oracle, R, G, Hkv, lens):  # noqa: F811
+def check(gpu, oracle, R, G, Hkv, lens, cut=None):  # noqa: F811
     import torch
     w = synth.make_pair_workload(f"sets_R{R}_{len(lens)}", B=len(lens), Hq=Hkv * G, Hkv=Hkv, seqlens=lens, R=R, Mv=16, seed=40 + R + len(lens))
     dw, op = gpu.DeviceWorkload(w), gpu.DecodeAttention(w)
@@ -18,6 +20,8 @@ def check(gpu, oracle, R, G, Hkv, lens):  # noqa: F811
     s = op.scores(dw)
     out = op(dw)
     torch.cuda.synchronize()
+    if cut:                                                # (passes of 512 tokens, groups of slices)
+        assert (passes_of_score_kernel(op, dw), op.plan.score_slice_groups) == cut
     keep = [i for i, n in enumerate(lens) if n > 0]        # (the oracle rejects empty sequences; their rows are zeros)
     kc = oracle.paired_as_indexed(w.key_codes, w.key_levels, w.cu_seqlens, w.Hkv)
     cu = np.concatenate([[0], np.cumsum([lens[i] for i in keep])]).astype(np.int32)
@@ -30,6 +34,18 @@ def check(gpu, oracle, R, G, Hkv, lens):  # noqa: F811
     op.close()
 
 
+def passes_of_score_kernel(op, dw):
+    """The last template argument of the k_score_pair that a call launches."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CUDA]) as trace:
+        op(dw)
+        torch.cuda.synchronize()
+    names = {m.group(1) for e in trace.events() for m in [re.search(r"k_score_pair<\d+, \d+, (\d+)>", e.name)] if m}
+    assert len(names) == 1, [e.name for e in trace.events()]
+    return int(names.pop())
+
+
 @pytest.mark.parametrize("R,G,lens", [(1, 4, [700]), (4, 8, [513, 1]), (5, 4, [511, 0, 64, 63]), (12, 4, [1024, 2049]), (12, 8, [4095]), (13, 4, [300, 65]),
                                       (15, 2, [600]), (16, 4, [4100, 7]), (17, 8, [900, 130]), (20, 4, [1537]), (21, 8, [2500, 511, 0, 1024]),
                                       (21, 4, [97] * 9), (11, 4, [700, 40, 2100, 0, 333, 512, 1])])
@@ -37,8 +53,20 @@ def test_levels_around_sets(gpu, oracle, R, G, lens):  # noqa: F811
     check(gpu, oracle, R, G, 2, lens)
 
 
-# Launches that are cut into three passes of 512 tokens per workgroup (in 8, 4, 2 and 1 groups of slices): whole and partly filled last ones.
-@pytest.mark.parametrize("R,G,Hkv,lens", [(12, 4, 8, [513, 512, 511, 514, 513]), (21, 4, 8, [4500]), (14, 4, 8, [1537] * 5), (21, 8, 8, [1536, 1537, 1535, 1600, 1537]),
-                                          (21, 4, 16, [8400]), (11, 2, 16, [17500])])
-def test_three_passes(gpu, oracle, R, G, Hkv, lens):  # noqa: F811
-    check(gpu, oracle, R, G, Hkv, lens)
+# Launches that are cut into three passes of 512 tokens per workgroup: whole and partly filled last ones.
+@pytest.mark.parametrize("R,G,Hkv,lens,groups", [(12, 4, 8, [513, 512, 511, 514, 513], 8), (21, 4, 8, [4500], 8), (14, 4, 8, [1537] * 5, 4),
+                                                 (21, 8, 8, [1536, 1537, 1535, 1600, 1537], 4), (21, 4, 16, [8400], 2), (11, 2, 16, [17500], 1)])
+def test_three_passes(gpu, oracle, R, G, Hkv, lens, groups):  # noqa: F811
+    check(gpu, oracle, R, G, Hkv, lens, (3, groups))
+
+
+# Workgroups that go through several slices, and every number of passes, for one and two groups of four heads and each number of sets.
+@pytest.mark.parametrize("R,G,Hkv,lens,cut", [
+    (11, 4, 8, [14000], (2, 2)), (11, 4, 8, [30000], (2, 1)), (12, 4, 8, [40000], (3, 1)), (11, 4, 8, [70001], (8, 1)),
+    (14, 4, 8, [20000], (2, 1)), (14, 4, 8, [45000], (4, 1)), (14, 4, 8, [90001], (6, 1)),
+    (21, 4, 8, [15000], (2, 2)), (21, 4, 8, [40001], (6, 2)), (21, 4, 8, [70000], (6, 1)), (21, 4, 8, [2500, 100, 511, 0, 1037] * 17, (6, 1)),
+    (11, 8, 8, [20000], (2, 1)), (11, 8, 8, [62001], (4, 1)), (11, 8, 8, [100000], (8, 1)),
+    (14, 8, 8, [12000], (2, 2)), (14, 8, 8, [40000], (4, 1)), (14, 8, 8, [90001], (6, 1)),
+    (21, 8, 8, [17000], (2, 1)), (21, 8, 8, [40000], (4, 1)), (21, 8, 8, [90000], (6, 1))])
+def test_several_slices(gpu, oracle, R, G, Hkv, lens, cut):  # noqa: F811
+    check(gpu, oracle, R, G, Hkv, lens, cut)
