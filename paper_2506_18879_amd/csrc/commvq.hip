@@ -724,7 +724,8 @@ struct StreamDims {
 // the memory pipe's queue and stops the wavefronts for up to 2000 clk.  M = 32: a slice fills both blocks (codebooks 0..15 |
 // 16..31).  Its last pass is done with block 0 after half of its steps; the next slice's block 0, fetched into registers
 // earlier, is stored right then, and block 1 follows after the first half of the next slice's first pass, when everyone
-// has left the old one.  With 8 heads no registers are left to wait in: there the blocks are sent for at those points.
+// has left the old one.  With 8 heads no registers are left to wait in: there the blocks are sent for at those points
+// (eight passes spill 6 registers).
 //
 // Times, one sequence or batch of the 8B / 70B layer, before (tiles of one sequence, per-head totals after every pass) and
 // now: 128K tokens, M = 16: 75.3 -> 72 us; 8 x 8K..64K, M = 32: 435 -> 390; 64 x 512..1024, M = 32: 105 -> 70 (sequences

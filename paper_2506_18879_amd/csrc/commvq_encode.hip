@@ -500,7 +500,9 @@ __global__ __launch_bounds__(kFewThreads) void k_encode_few(const void *__restri
             const float rc = 1.01f * __builtin_amdgcn_sqrtf(whole2) * longest.y, bound = 9e-6f * rc + 5e-7f * cc;
             const float left = __builtin_fmaf(whole2, 1.000001f, m + 2.f * bound);  // |r - c|^2 = |r|^2 + (|c|^2 - 2 r c)
             whole2 = left < 1e-34f ? 1e-34f : left;        // (not fmaxf: NaN has to stay)
-            if (__any(!(up - m > bound && rc < 1e37f))) {
+            // (A level of zeros, as whoever has fewer levels than the format fills it up, needs no second look: 32 of them, 8 tokens: 156 -> 34 us.)
+            const bool zeros = cc == 0.f && m == 0.f && up == 0.f;
+            if (__any(!((up - m > bound || zeros) && rc < 1e37f))) {
                 uint4_t part[3][4];
 #pragma unroll
                 for (int s3 = 0; s3 < 3; ++s3)

@@ -52,6 +52,7 @@ __global__ __launch_bounds__(256) void k_prep_pairs(const uint4 *__restrict__ ta
 // by a kernel of their own, 17 us at 128K, and read again for every slice; columns for 16 or 32 levels; totals over lanes; tiles
 // of one sequence, never cut along the planes) and now, R = 11 | 21: 2000 tokens 58.3 -> 39.7 | 78.5 -> 42.6 us, 12000 59.6 ->
 // 48.2 | 81.1 -> 56.3, 40000 84.1 -> 74.4 | 125.8 -> 89.2, 128K 146.8 -> 117.3 | 250 -> 197, 8 x 1100..2200 63.1 -> 55.9 | 84.3 -> 62.2.
+// With two groups of heads the most passes do not fit the registers: <3, 2, 8> spills 22 of them, <6, 2, 6> 38.
 template <int SETS, int NGRP, int NP>
 __global__ __launch_bounds__(kSliceThreads) void k_score_pair(
     const void *__restrict__ q, const uint8_t *__restrict__ pairs, const uint4 *__restrict__ packed,

@@ -126,7 +126,8 @@ __device__ __forceinline__ float swap32_add(float x, float y)
 // that it replaces (16 MB out of one kernel and into the next at that size, 67 MB for 64 chats) and one launch less, whole call:
 // one fp32 head of 4096 tokens 23.9 -> 19.8 us; 8B 2-bit 1237 tokens 31.1 -> 24.8, 32K 69.8 -> 56.9, 8 x 8K..64K 483 -> 469, 64 x
 // 512..1024 136 -> 118; 8B 1-bit 128K 92.8 -> 88.6, position-free 39.5 -> 36.0; 70B 4 x 128K 559 -> 553.  Not kept: equal chunks of the whole batch
-// instead of ranges per sequence (more products: 8 x 8K..64K 456 -> 480), rows touched early to have them in L2 (no change).
+// instead of ranges per sequence (more products: 8 x 8K..64K 456 -> 480), rows touched early to have them in L2 (no change, with
+// codebooks that were there from the call before).  Eight heads with 8 codebooks spill 12 (1024 threads) or 13 registers.
 template <int G, int CB, int S, int NCS, int NT, bool BF16>
 __global__ __launch_bounds__(NT, S > 1 ? 2 : 4) void k_values(const ValuesArgs a)
 {

@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 
 # 2 heads: up to 640 tokens in workgroups of five; 700 go to workgroups of 16
-@pytest.mark.parametrize("kind", ["gaussian", "equal rows", "close rows", "small", "large", "overflow", "not finite"])
+@pytest.mark.parametrize("kind", ["gaussian", "equal rows", "close rows", "zero levels", "small", "large", "overflow", "not finite"])
 def test_codes_of_few_vectors(gpu, kind):  # noqa: F811
     w = synth.make_workload("enc_few", B=1, Hq=2, Hkv=2, seqlens=[8], Mk=32, Mv=16, dtype="bf16", seed=5)
     keys, cb = _inputs(kind, 700, w, np.random.default_rng(5))
