@@ -584,7 +584,8 @@ __global__ __launch_bounds__(kFewThreads) void k_encode_few(const void *__restri
 // wavefronts with an image each, 147.
 // Where rows have twins (a trained codebook with merged codewords) the screen decides nothing.  A wavefront that has had to repeat every tile for five
 // tokens, of one level or of several, takes the next 15 levels without a screen, and 31 after each further try.  Every row with a twin, 32 levels:
-// 265 -> 168 us (all three parts throughout: 168); a tenth of the rows: 234 -> 204 (178).
+// 259 -> 165 us (all three parts throughout: 168); a tenth of the rows: 234 -> 183 (178).  The next residual is split without need in those levels:
+// a branch around it costs the codebooks without twins 3 us.
 constexpr int kManyThreads = 512, kManyTokens = 128;
 constexpr int kManyNorms = 2 * kErImg * 16;              // [2][256] -|c|^2 / 2
 constexpr int kManyWhole = kManyNorms + 2 * kK * 4;        // [2][256] |c|^2
@@ -833,14 +834,12 @@ __global__ __launch_bounds__(kManyThreads, 2) void k_encode_many(const void *__r
                 res[8 * kc + 2 * i + 1] -= bf16_hi(ws[i]);
             }
         }
-        if (!plain) {
-            if (searched) {
-                whole2 = 0.f;
+        split();
+        if (searched && !plain) {
+            whole2 = 0.f;
 #pragma unroll
-                for (int i = 0; i < 32; ++i) whole2 = __builtin_fmaf(res[i], res[i], whole2);
-                whole2 = sum4(whole2) * 1.0001f + 1e-34f;
-            }
-            split();
+            for (int i = 0; i < 32; ++i) whole2 = __builtin_fmaf(res[i], res[i], whole2);
+            whole2 = sum4(whole2) * 1.0001f + 1e-34f;
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's rows of level l + 1 have landed
         __syncthreads();                                   // ... and everybody's, and level l is no longer read
