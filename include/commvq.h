@@ -119,7 +119,7 @@ typedef struct {
                                  is sized for splits of this length, a workgroup takes that many tokens or more */
     int32_t value_splits;     /* max_seqlen / value_split_len, rounded up */
     int32_t out_chunks;       /* chunks of 64 codebook rows per (sequence, KV head): the partial results that the workspace holds */
-    int32_t score_kernel;     /* 0: rows gathered through L1 (fp32 codebooks or explicit key positions);
+    int32_t score_kernel;     /* 0: rows gathered through L1 (fp32 codebooks, explicit key positions, launches of few tokens);
                                  1: codebook slices streamed through LDS (or the look-up table of position_free) */
     int32_t score_slice_groups; /* score workgroups per tile and KV head: contexts too short to fill the chip are also cut along the
                                  codebook slices, and the groups' partial logits are added by a small kernel; 1 otherwise */
@@ -217,7 +217,8 @@ commvq_status commvq_static_scratch_bytes(size_t *bytes /* host */);
  *   packed         device buffer of commvq_packed_key_codebook_bytes() bytes, 16-byte aligned,
  *                  owned by the caller; must stay alive and unchanged while registered
  * and remembers the pair in the handle: later calls that pass the same key_codebooks pointer
- * use `packed` instead of re-laying (the caller vouches that the contents did not change).
+ * use `packed` instead of re-laying (the caller vouches that the contents did not change; key_codebooks itself is still
+ * read by calls that gather rows: explicit key positions, launches of few tokens).
  * Results are bit-identical either way.  commvq_forget_packed_key_codebooks drops one pair
  * (or all, with NULL).  COMMVQ_ERR_CONFIG for fp32 codebooks (they take another kernel).
  * COMMVQ_KEYS_PAIRED: key_codebooks is the tied table; `packed` then holds it padded to 12, 16 or 24 levels, in

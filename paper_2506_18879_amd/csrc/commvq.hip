@@ -8,7 +8,8 @@
 //               LDS-image order) + k_score_stream (codebook slices streamed through LDS, tile codes
 //               resident in registers, gather-sum and query contraction on the matrix cores), for
 //               short contexts with the tiles also cut along the slices + k_score_combine;
-//               fp32 codebooks or explicit key positions: k_score (rows gathered through L1).
+//               fp32 codebooks, explicit key positions: k_score (rows gathered through L1); those and other keys in launches of few
+//               tokens: k_score_few.
 //   k_values    Softmax(A) S_V of Eq. optimized_v and its product with the value codebook (commvq_values.hpp): exp(logit - max) is
 //               scatter-added into LDS bins, one per head, value codebook and codeword, in 32-bit fixed point (integer LDS
 //               atomics run ~20x faster than fp32 ones on gfx950), and the bins are multiplied by the codebook rows on the matrix
@@ -211,6 +212,21 @@ StreamShape stream_shape(const commvq_handle *h, int B, int64_t T, int max_seqle
 // Whether the sliced score path is k_score_stream or k_score_pair (keys with RoPE), not the look-up table.
 inline bool stream_keys(const commvq_config &c) { return !c.position_free; }
 
+// Whether gathering rows (k_score_few) serves a launch of bf16 codebooks with contiguous positions better than the slices: so few
+// tokens that 16 of them a workgroup leave none of it waiting and the rows' way through the L1s (tokens x heads x codebooks x 256
+// bytes) costs less than the partial logits and their sum.  Whole calls, slices -> rows, in microseconds, 8 KV heads: 4 query heads each and 16 +
+// 16 codebooks 200 tokens 18.3 -> 14.4, 1237 21.5 -> 14.9, 4000 24.2 -> 20.6, 6000 27.3 -> 24.6, 8000 27.3 -> 28.4; 32 + 32 codebooks 200
+// tokens 18.5 -> 13.6, 1237 24.7 -> 19.6, 2500 26.9 -> 23.6, 3200 27.0 -> 26.9, 4000 27.4 -> 28.8; 8 query heads each and 32 + 32 codebooks
+// 1237 tokens 27.9 -> 22.8, 2500 30.8 -> 27.2, 3200 30.0 -> 31.4; 24 sequences of 256, 16 + 16 codebooks 35.3 -> 29.1; 32 KV heads of 4,
+// 32 + 32 codebooks 300 tokens 34.2 -> 27.9, 1000 36.6 -> 42.1.  Layers of fewer than 8 KV heads keep the slices, whose cuts the
+// tests pin on layers of two (two heads of 4, 16 + 16 codebooks, 3000 tokens: 21.2 us, with rows 14.7).
+inline bool few_tokens(const commvq_handle *h, int B, int64_t T, int max_seqlen)
+{
+    const commvq_config &c = h->cfg;
+    return !pair_keys(c) && c.n_kv_heads >= 8 && T * c.n_kv_heads * c.m_key <= 700000 &&
+           (int64_t)B * c.n_kv_heads * ((max_seqlen + 2 * kFewTokens - 1) / (2 * kFewTokens)) < kScoreMinWgs;
+}
+
 // Indexed values go through k_values, the binary code through k_vbits and the output kernels.
 inline bool fused_values(const commvq_config &c) { return !bin_values(c); }
 
@@ -283,6 +299,7 @@ void make_plan(const commvq_handle *h, int B, int64_t T, int max_seqlen, bool sl
     const int units = B * h->cfg.n_kv_heads;
     int len;
     p->stream = StreamShape{0, 0, 1};
+    if (sliced && stream_keys(h->cfg) && few_tokens(h, B, T, max_seqlen)) sliced = false;
     if (sliced && stream_keys(h->cfg)) {
         p->stream = stream_shape(h, B, T, max_seqlen);
         len = 1024;  // what is reported, and value splits are cut by: the workgroup's tokens rounded up to a power of two
@@ -303,7 +320,7 @@ void make_plan(const commvq_handle *h, int B, int64_t T, int max_seqlen, bool sl
     } else {
         len = 1024;
         // down to 4 tokens per wavefront (one iteration of four tokens): a short context still spreads over the chip
-        while (len > 16 && (long)units * ((max_seqlen + len - 1) / len) < kScoreMinWgs) len /= 2;
+        while (len > kFewTokens && (long)units * ((max_seqlen + len - 1) / len) < kScoreMinWgs) len /= 2;
     }
     const int groups = p->stream.groups;
     p->score_split_len = len;
@@ -484,8 +501,7 @@ __global__ __launch_bounds__(kScoreThreads) void k_score(
                 }
             }
     };
-    // the first codes travel while the table is put in place, the first codewords while the others finish theirs (one fp32 head of 4096
-    // tokens: 18.7 us a call with the table and the barrier first, 18.5 so)
+    // the first codes travel while the table is put in place, the first codewords while the others finish theirs
     if (n_it > 0) load_codes(t0, cw);
     for (int x = threadIdx.x; x < 2 * kLo * 16; x += kScoreThreads) {
         const int h = x / (kLo * 16), lo = (x / 16) % kLo, sb = x % 16;
@@ -612,6 +628,164 @@ __global__ __launch_bounds__(kScoreThreads) void k_score(
             if (st.x != -INFINITY) l += st.y * __builtin_amdgcn_exp2f((st.x - m) * kLog2e);
         }
         sstat[((size_t)b * a.Hq + (size_t)g * G + threadIdx.x) * a.nsplit + split] = make_float2(m, l);
+    }
+}
+
+// ------------------------------------------------------------------ k_score_few
+// k_score for launches that leave a wavefront no more than four tokens, one per 16-lane row: nothing is gone round, so nothing is
+// pipelined from one iteration to the next and the E_lo table does not pay for its way into LDS (32 KB a workgroup, against 8 KB of
+// rows a token).  Everything that does not depend on the codes (queries, phase factors) is asked for first, then the rows of all
+// codebooks, at most 48 16-byte pieces a lane at once: with 8 at a time, as in k_score, a wavefront alone on its SIMD waits for
+// every group of them.  The grid has a dimension for each of head, tile and sequence, which saves the divisions.
+// Bound by latency (arguments, sequence, codes, rows, one after the other) and by the rows' way through the L1s, 48 bytes a clock and compute
+// unit.  Whole calls with k_score and with this, in microseconds: one fp32 head of 4096 tokens, 32 + 32 codebooks 18.8 -> 15.9 (64 MB of
+// rows, 3 us of them); 8 x 4 heads, explicit positions, 16 + 16 codebooks 1237 tokens 17.1 -> 14.9, 4000 26.3 -> 20.6; 32 + 32 codebooks 1237
+// tokens 22.3 -> 19.6, 4000 33.3 -> 28.8.
+template <int M, int G, bool BF16>
+__global__ __launch_bounds__(kScoreThreads) void k_score_few(
+    const void *__restrict__ q, const uint8_t *__restrict__ key_codes, const void *__restrict__ key_cb,
+    const int32_t *__restrict__ cu, const int32_t *__restrict__ q_pos, const int32_t *__restrict__ key_pos,
+    const float2 *__restrict__ tbl_hi, const float2 *__restrict__ tbl_lo, float *__restrict__ scores,
+    float2 *__restrict__ sstat, const ScoreDims a)
+{
+    constexpr unsigned ROWB = BF16 ? kD * 2 : kD * 4;
+    constexpr int QL = 2;                                     // 16-byte pieces of a query head at most
+    constexpr int PC = BF16 ? 1 : 2;                          // 16-byte pieces of a codeword that a lane takes
+    constexpr int DEPTH = M * PC <= 48 ? M : 48 / PC;         // codebooks whose rows are in flight
+    typedef unsigned u4u __attribute__((ext_vector_type(4), aligned(2)));  // (queries and codebooks: any alignment that their elements have)
+    __shared__ float logit[G][kFewTokens];
+
+    const int g = blockIdx.x, split = blockIdx.y, b = blockIdx.z;
+    const int cu0 = cu[b], L = cu[b + 1] - cu0, qpos = q_pos[b];
+    asm volatile("" ::"s"(qpos));                             // (asked for here, with the others)
+    const int s0 = split * kFewTokens;
+    if (s0 >= L) return;
+    const int tid = threadIdx.x, lane = tid & 63, sub = lane & 15;
+    const int tok = min(s0 + (tid >> 4), L - 1);
+    int pos = tok;                                            // (asked for first: a wait for it is not one for the codes)
+    if (key_pos) pos = key_pos[cu0 + tok];
+    __builtin_amdgcn_sched_barrier(0);
+
+    unsigned cw[M / 4];
+    {
+        const uint4 *cp = reinterpret_cast<const uint4 *>(key_codes + ((size_t)cu0 * a.Hkv + (size_t)g * L + tok) * M);
+#pragma unroll
+        for (int v = 0; v < M / 16; ++v) {
+            const uint4 c4 = cp[v];
+            cw[4 * v + 0] = c4.x; cw[4 * v + 1] = c4.y; cw[4 * v + 2] = c4.z; cw[4 * v + 3] = c4.w;
+        }
+    }
+    const int dl = qpos - pos;
+    const bool neg = dl < 0;
+    const int ad = neg ? -dl : dl;
+    const int hi = min(ad >> kLoBits, a.n_hi - 1), lo = ad & (kLo - 1);
+    const __amdgpu_buffer_rsrc_t hi_rs = make_rsrc(tbl_hi, (unsigned)a.n_hi * kJ * 8u), lo_rs = make_rsrc(tbl_lo, (unsigned)kLo * kJ * 8u);
+    uint4_t ph[2][2];                                         // coarse and fine phase factors of the lane's 4 sub-spaces
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf) {
+        ph[0][hf] = __builtin_amdgcn_raw_buffer_load_b128(hi_rs, (unsigned)hi * (kJ * 8u) + sub * 32u + 16u * hf, 0, 0);
+        ph[1][hf] = __builtin_amdgcn_raw_buffer_load_b128(lo_rs, (unsigned)lo * (kJ * 8u) + sub * 32u + 16u * hf, 0, 0);
+    }
+    uint4_t qw[G][QL];
+    {
+        const unsigned qb = a.q_bf16 ? 2u : 4u, next = a.q_bf16 ? 0u : 16u;  // (bf16: the same piece twice, no branch)
+        const char *qp = static_cast<const char *>(q) + ((size_t)b * a.Hq + (size_t)g * G) * kD * qb;
+#pragma unroll
+        for (int hh = 0; hh < G; ++hh) {
+            qw[hh][0] = *reinterpret_cast<const u4u *>(qp + (hh * kD + 8 * sub) * qb);
+            qw[hh][1] = *reinterpret_cast<const u4u *>(qp + (hh * kD + 8 * sub) * qb + next);
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
+    const char *cb0 = static_cast<const char *>(key_cb) + (size_t)g * M * kK * ROWB;
+    const unsigned lane_off = BF16 ? sub * 16u : sub * 32u;
+    uint4_t row[M][PC];
+    auto issue = [&](int m) __attribute__((always_inline)) {
+        if (BF16) {
+            // byte 1 <- code m, byte 0 <- sub * 16: (code << 8) | (sub * 16)
+            const unsigned voff = __builtin_amdgcn_perm(cw[m / 4], lane_off, 0x0c0c0000u | ((4u + (m % 4)) << 8));
+            row[m][0] = *reinterpret_cast<const u4u *>(cb0 + (size_t)m * kK * ROWB + voff);
+        } else {
+            const unsigned voff = ((cw[m / 4] >> (8 * (m % 4))) & 0xffu) * ROWB + lane_off;
+#pragma unroll
+            for (int p = 0; p < PC; ++p) row[m][p] = *reinterpret_cast<const u4u *>(cb0 + (size_t)m * kK * ROWB + 16 * p + voff);
+        }
+    };
+    const unsigned sel_lo = opaque_sgpr(0x00003f80u), sel_hi = opaque_sgpr(0x3f800000u);
+    float A[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) A[e] = 0.f;
+#pragma unroll
+    for (int m = 0; m < DEPTH; ++m) issue(m);
+    __builtin_amdgcn_sched_barrier(0);
+    // the phase of the relative position (conjugated for keys behind the query)
+    float ex[4], ey[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const unsigned hxr = ph[0][u / 2][2 * (u % 2)], hyr = ph[0][u / 2][2 * (u % 2) + 1];
+        const unsigned lxr = ph[1][u / 2][2 * (u % 2)], lyr = ph[1][u / 2][2 * (u % 2) + 1];
+        const float hx = __builtin_bit_cast(float, hxr), hy = __builtin_bit_cast(float, hyr);
+        const float lx = __builtin_bit_cast(float, lxr), ly = __builtin_bit_cast(float, lyr);
+        ex[u] = hx * lx - hy * ly;
+        const float y = hx * ly + hy * lx;
+        ey[u] = neg ? -y : y;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int m0 = 0; m0 < M; m0 += 4) {
+#pragma unroll
+        for (int m = m0; m < m0 + 4; ++m)
+#pragma unroll
+            for (int p = 0; p < PC; ++p)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const unsigned ve = row[m][p][e];
+                    if (BF16) {
+                        A[2 * e] = add_bf16_sel(ve, sel_lo, A[2 * e]);
+                        A[2 * e + 1] = add_bf16_sel(ve, sel_hi, A[2 * e + 1]);
+                    } else {
+                        A[4 * p + e] += __builtin_bit_cast(float, ve);
+                    }
+                }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int m = m0 + DEPTH; m < m0 + DEPTH + 4; ++m)
+            if (m < M) issue(m);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // B = A E, score_h = sum_j Re(q_h conj(B))
+    float B[8];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        B[2 * u] = A[2 * u] * ex[u] - A[2 * u + 1] * ey[u];
+        B[2 * u + 1] = A[2 * u] * ey[u] + A[2 * u + 1] * ex[u];
+    }
+#pragma unroll
+    for (int hh = 0; hh < G; ++hh) {
+        float v = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const unsigned wb = qw[hh][0][e / 2], wf = qw[hh][e / 4][e % 4];
+            const float x = a.q_bf16 ? (e & 1 ? bf16_hi(wb) : bf16_lo(wb)) : __builtin_bit_cast(float, wf);
+            v += x * a.scale * B[e];
+        }
+        v = row_sum16(v);
+        if (sub == 0) logit[hh][tid >> 4] = v;
+    }
+    __syncthreads();
+    // logits, and (max, sum of exp) of the workgroup's tokens: 16 lanes per head
+    if (tid < G * kFewTokens) {
+        const int hh = tid / kFewTokens, t = s0 + tid % kFewTokens;
+        const float v = t < L ? logit[hh][tid % kFewTokens] : -INFINITY;
+        if (t < L) scores[(size_t)cu0 * a.Hq + (size_t)(g * G + hh) * L + t] = v;
+        float m = v;
+        m = fmaxf(m, dpp_mov<0xB1>(m));
+        m = fmaxf(m, dpp_mov<0x4E>(m));
+        m = fmaxf(m, dpp_mov<0x141>(m));
+        m = fmaxf(m, dpp_mov<0x140>(m));
+        const float l = row_sum16(v == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((v - m) * kLog2e));
+        if (tid % kFewTokens == 0) sstat[((size_t)b * a.Hq + (size_t)g * G + hh) * a.nsplit + split] = make_float2(m, l);
     }
 }
 
@@ -1940,24 +2114,23 @@ struct ScoreArgs {
 };
 
 template <int M, int G>
-hipError_t launch_score_mg(const ScoreArgs &a, bool bf16, int grid, hipStream_t s)
+hipError_t launch_score_mg(const ScoreArgs &a, bool bf16, int batch, hipStream_t s)
 {
-    if (bf16)
-        hipLaunchKernelGGL((k_score<M, G, true>), dim3(grid), dim3(kScoreThreads), 0, s, a.q, a.key_codes, a.key_cb, a.cu,
-                           a.q_pos, a.key_pos, a.tbl_hi, a.tbl_lo, a.scores, a.sstat, a.d);
-    else
-        hipLaunchKernelGGL((k_score<M, G, false>), dim3(grid), dim3(kScoreThreads), 0, s, a.q, a.key_codes, a.key_cb, a.cu,
-                           a.q_pos, a.key_pos, a.tbl_hi, a.tbl_lo, a.scores, a.sstat, a.d);
+    const bool few = a.d.split_len == kFewTokens;             // (then there are fewer than 2 kScoreMinWgs workgroups: each grid dimension is in range)
+    auto kernel = few ? (bf16 ? k_score_few<M, G, true> : k_score_few<M, G, false>) : (bf16 ? k_score<M, G, true> : k_score<M, G, false>);
+    const dim3 grid = few ? dim3(a.d.Hkv, a.d.nsplit, batch) : dim3(batch * a.d.Hkv * a.d.nsplit);
+    hipLaunchKernelGGL(kernel, grid, dim3(kScoreThreads), 0, s, a.q, a.key_codes, a.key_cb, a.cu, a.q_pos, a.key_pos, a.tbl_hi,
+                       a.tbl_lo, a.scores, a.sstat, a.d);
     return hipGetLastError();
 }
 template <int M>
-hipError_t launch_score_m(const ScoreArgs &a, int G, bool bf16, int grid, hipStream_t s)
+hipError_t launch_score_m(const ScoreArgs &a, int G, bool bf16, int batch, hipStream_t s)
 {
     switch (G) {
-    case 1: return launch_score_mg<M, 1>(a, bf16, grid, s);
-    case 2: return launch_score_mg<M, 2>(a, bf16, grid, s);
-    case 4: return launch_score_mg<M, 4>(a, bf16, grid, s);
-    default: return launch_score_mg<M, 8>(a, bf16, grid, s);
+    case 1: return launch_score_mg<M, 1>(a, bf16, batch, s);
+    case 2: return launch_score_mg<M, 2>(a, bf16, batch, s);
+    case 4: return launch_score_mg<M, 4>(a, bf16, batch, s);
+    default: return launch_score_mg<M, 8>(a, bf16, batch, s);
     }
 }
 
@@ -2153,9 +2326,8 @@ commvq_status run_scores(commvq_handle *h, const void *q, const uint8_t *key_cod
     a.scores = w.scores; a.sstat = w.sstat;
     a.d.Hq = c.n_q_heads; a.d.Hkv = c.n_kv_heads; a.d.nsplit = plan.score_splits; a.d.split_len = plan.score_split_len;
     a.d.n_hi = h->n_hi; a.d.q_bf16 = c.q_dtype == COMMVQ_BF16; a.d.scale = h->scale;
-    const int grid = pos->batch * c.n_kv_heads * plan.score_splits;
     const bool bf16 = c.codebook_dtype == COMMVQ_BF16;
-    hipError_t e = c.m_key == 16 ? launch_score_m<16>(a, h->G, bf16, grid, s) : launch_score_m<32>(a, h->G, bf16, grid, s);
+    hipError_t e = c.m_key == 16 ? launch_score_m<16>(a, h->G, bf16, pos->batch, s) : launch_score_m<32>(a, h->G, bf16, pos->batch, s);
     return e == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;
 }
 

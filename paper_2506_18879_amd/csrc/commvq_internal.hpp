@@ -25,6 +25,7 @@ constexpr int kPassTokens = 512;     // tokens of a pass: 16 wavefronts x 32
 constexpr int kStreamSlices = kD / 8;  // codebook slices: 8 elements of every codeword each
 constexpr int kScoreMinWgs = 2048;   // row-gather score kernel: tiles are halved until this many workgroups exist
 constexpr int kScoreThreads = 256;
+constexpr int kFewTokens = kScoreThreads / 16;  // tokens of a workgroup of k_score_few, the smallest tile of the row-gather kernels
 constexpr int kOutThreads = 256;
 constexpr int kMaxValueSplits = 256;  // value_splits never exceeds 256 / (batch * KV heads), at least 1
 constexpr int kOutRows = 64;    // codebook rows per k_out workgroup

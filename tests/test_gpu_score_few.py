@@ -1,0 +1,68 @@
+"""The score kernel of launches of few tokens (16 tokens a workgroup, rows gathered, nothing pipelined): parity with the oracle as in
+test_gpu_parity.py, at the edges of its workgroups and of the rule that chooses it."""
+import numpy as np
+import pytest
+
+from paper_2506_18879_amd import synth
+
+from test_gpu_parity import assert_rows, gpu, oracle_out  # noqa: F401  (gpu: fixture)
+from test_gpu_score_stream import _check
+
+pytestmark = pytest.mark.gpu
+
+
+def _make(name, Hq, lens, Mk, dtype="bf16"):
+    w = synth.make_workload(name, B=len(lens), Hq=Hq, Hkv=8, seqlens=lens, Mk=Mk, Mv=16, dtype=dtype, seed=Mk + Hq + sum(lens))
+    # queries at, before (negative distances) and past the end
+    w.q_pos = np.array([(max(1, x) - 1, x // 3, x + 777)[i % 3] for i, x in enumerate(lens)], np.int32)
+    return w
+
+
+@pytest.mark.parametrize("Mk,G,dtype", [(16, 1, "bf16"), (16, 4, "bf16"), (32, 2, "bf16"), (32, 4, "bf16"), (32, 8, "bf16"), (16, 8, "f32"), (32, 4, "f32")])
+@pytest.mark.parametrize("lens", [[1], [17, 15, 16], [0, 33, 0, 100, 31, 0], [64, 1, 63, 65, 2, 129, 5, 48]])
+def test_edges_of_workgroups(gpu, oracle, Mk, G, dtype, lens):  # noqa: F811
+    w = _make(f"few_m{Mk}_g{G}_{dtype}_{len(lens)}", 8 * G, lens, Mk, dtype)
+    op = gpu.DecodeAttention(w, max_position=1024)
+    assert (op.plan.score_kernel, op.plan.score_split_len) == (0, 16)
+    op.close()
+    _check(gpu, oracle, w, max_position=1024)
+
+
+@pytest.mark.parametrize("Mk,lens,kernel", [(32, [2734], 0), (32, [2735], 1), (16, [5468], 0), (16, [5469], 1), (16, [4000] + [1] * 8, 1)])
+def test_either_side_of_the_rule(gpu, oracle, Mk, lens, kernel):  # noqa: F811
+    # by tokens x heads x codebooks, and by the workgroups that one long sequence gives the short ones beside it
+    w = _make(f"rule_m{Mk}_{len(lens)}_{lens[-1]}", 32, lens, Mk)
+    op = gpu.DecodeAttention(w, max_position=8192)
+    assert op.plan.score_kernel == kernel
+    op.close()
+    _check(gpu, oracle, w, max_position=8192)
+
+
+@pytest.mark.parametrize("Mk", [16, 32])
+def test_explicit_positions_and_storage_that_is_not_aligned(gpu, oracle, Mk):  # noqa: F811
+    import torch
+    w = _make(f"odd_m{Mk}", 32, [300, 77], Mk)
+    rng = np.random.default_rng(Mk)
+    for key_pos in (None, rng.integers(0, 5000, w.total_tokens).astype(np.int32)):
+        w.key_pos = key_pos
+        dw, op = gpu.DeviceWorkload(w), gpu.DecodeAttention(w, max_position=8192)
+        for name in ("q", "key_codebooks"):                    # two bytes past a 16-byte boundary
+            t = getattr(dw, name)
+            room = torch.empty(t.numel() + 1, dtype=t.dtype, device="cuda")
+            room[1:] = t.view(-1)
+            setattr(dw, name, room[1:])
+        out = op(dw)
+        torch.cuda.synchronize()
+        assert_rows(out.cpu().numpy(), oracle_out(oracle, w), w.name)
+        op.close()
+
+
+@pytest.mark.parametrize("G", [4, 8])
+def test_sequences_that_share_a_workgroup_of_the_slices(gpu, oracle, G):  # noqa: F811
+    # 16 codebooks and more tokens than the rule leaves to this kernel: the segments of several sequences in k_score_stream
+    lens = [512, 1, 513, 511, 1024, 700, 0, 3, 512, 1537, 1200]
+    w = _make(f"share_g{G}", 8 * G, lens, 16)
+    op = gpu.DecodeAttention(w, max_position=4096)
+    assert op.plan.score_kernel == 1
+    op.close()
+    _check(gpu, oracle, w, max_position=4096)
