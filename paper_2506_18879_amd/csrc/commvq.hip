@@ -1751,6 +1751,7 @@ struct OutArgs {
     int Hq, Hkv, nvsplit, vsplit_len, nchunk, Mv;
     int batch;
     int per_split;  // partial results per value split (k_values); 0: nchunk in all
+    Divisor by_hq;
 };
 
 // Second half of the binary value code (indexed values: k_values).  Bins row r of a KV head is code bit c = vbits_code_bit(r),
@@ -2033,22 +2034,38 @@ __global__ __launch_bounds__(kD * kFinalParts) void k_out_final(OutArgs a)
     __shared__ float l_s;
     __shared__ float part[kFinalParts][kD];
     const int bh = blockIdx.x;
-    const int b = bh / a.Hq;
-    const int e = threadIdx.x % kD, q = threadIdx.x / kD;
+    const int b = quotient(bh, a.by_hq);
+    const int e = threadIdx.x % kD, q = __builtin_amdgcn_readfirstlane(threadIdx.x / kD);
+    const int rows = a.per_split ? a.nvsplit * a.per_split : a.nchunk;
+    const float *pp = a.partial + (size_t)bh * rows * kD + e, *lp = a.lsum + (size_t)bh * a.nvsplit;
+    // What the longest sequence has of exp-sums and of the first partial results is asked for before this sequence's length is known:
+    // that, they and they again one after the other are 0.8 us.
+    constexpr int AHEAD = 16;
+    const float l0 = (int)threadIdx.x < min(a.nvsplit, 64) ? lp[threadIdx.x] : 0.f;
+    float ahead[AHEAD];
+#pragma unroll
+    for (int i = 0; i < AHEAD; i += 4)
+        if (i == 0 || q + i * kFinalParts < rows) {
+#pragma unroll
+            for (int k = i; k < i + 4; ++k) ahead[k] = pp[(size_t)min(q + k * kFinalParts, rows - 1) * kD];
+        }
+    __builtin_amdgcn_sched_barrier(0);
     const int L = a.cu[b + 1] - a.cu[b];
     const int nvs = min((L + a.vsplit_len - 1) / a.vsplit_len, a.nvsplit);
-    const int rows = a.per_split ? a.nvsplit * a.per_split : a.nchunk, n = a.per_split ? nvs * a.per_split : a.nchunk;
-    const float *pp = a.partial + (size_t)bh * rows * kD + e;
-    float s = 0.f;
-#pragma unroll 16
-    for (int c = q; c < n; c += kFinalParts) s += pp[(size_t)c * kD];
-    part[q][e] = s;
+    const int n = a.per_split ? nvs * a.per_split : a.nchunk;
     if (threadIdx.x < 64) {
-        float l = 0.f;
-        for (int v = threadIdx.x; v < nvs; v += 64) l += a.lsum[(size_t)bh * a.nvsplit + v];
+        float l = (int)threadIdx.x < nvs ? l0 : 0.f;
+        for (int v = threadIdx.x + 64; v < nvs; v += 64) l += lp[v];
         l = wave_sum(l);
         if (threadIdx.x == 0) l_s = l;
     }
+    float s = 0.f;
+#pragma unroll
+    for (int k = 0; k < AHEAD; ++k)
+        if (q + k * kFinalParts < n) s += ahead[k];
+#pragma unroll 16
+    for (int c = q + AHEAD * kFinalParts; c < n; c += kFinalParts) s += pp[(size_t)c * kD];
+    part[q][e] = s;
     __syncthreads();
     if (q == 0) {
         float t = part[0][e];
@@ -2371,6 +2388,8 @@ commvq_status run_values(commvq_handle *h, const uint8_t *val_codes, const void 
     a.ranges = plan.values.ranges; a.range_len = plan.values.range_len; a.span = plan.values.span;
     a.spans = (a.range_len + a.span - 1) / a.span;
     a.batch = pos->batch; a.ncg = c.m_val / plan.values.books; a.mode = mode;
+    a.by_hkv = divisor(a.Hkv); a.by_ncg = divisor(a.ncg); a.by_batch = divisor(a.batch); a.by_span = divisor(a.span);
+    a.split_shift = __builtin_ctz(a.split_len);             // (statistics tiles are powers of two)
     hipError_t e;
     const bool bf16 = c.codebook_dtype == COMMVQ_BF16;
     switch (h->G) {
@@ -2388,7 +2407,7 @@ commvq_status run_values_final(commvq_handle *h, const commvq_positions *pos, co
     OutArgs a = {};
     a.cu = pos->cu_seqlens; a.lsum = w.lsum; a.partial = w.partial; a.out = out;
     a.Hq = h->cfg.n_q_heads; a.Hkv = h->cfg.n_kv_heads; a.nvsplit = plan.values.ranges; a.vsplit_len = plan.values.range_len;
-    a.per_split = h->cfg.m_val / plan.values.books; a.batch = pos->batch;
+    a.per_split = h->cfg.m_val / plan.values.books; a.batch = pos->batch; a.by_hq = divisor(a.Hq);
     hipLaunchKernelGGL(k_out_final, dim3(pos->batch * h->cfg.n_q_heads), dim3(kD * kFinalParts), 0, s, a);
     return hipGetLastError() == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;
 }
@@ -2417,7 +2436,7 @@ commvq_status run_output(commvq_handle *h, const void *val_cb, const commvq_posi
     a.partial = w.partial; a.out = out;
     a.Hq = c.n_q_heads; a.Hkv = c.n_kv_heads;
     a.nvsplit = plan.value_splits; a.vsplit_len = plan.value_split_len;
-    a.nchunk = plan.out_chunks; a.Mv = val_books(c); a.batch = pos->batch; a.per_split = 0;
+    a.nchunk = plan.out_chunks; a.Mv = val_books(c); a.batch = pos->batch; a.per_split = 0; a.by_hq = divisor(a.Hq);
     const int grid = pos->batch * c.n_kv_heads * plan.out_chunks;
     const bool bf16 = c.codebook_dtype == COMMVQ_BF16;
     hipError_t e;

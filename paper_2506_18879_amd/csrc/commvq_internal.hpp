@@ -39,6 +39,20 @@ typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
+// Quotients of workgroup indices by numbers that the host knows: a multiplication instead of the 40 dependent instructions of a
+// division, which every wavefront would run before its first load.  With s = ceil(log2 d) and m = floor(2^(31 + s) / d) + 1 the
+// product n m / 2^(31 + s) is n / d and less than 1 / d more for every n below 2^31, so that its whole part is the quotient.
+struct Divisor {
+    unsigned mul, shift;
+};
+inline Divisor divisor(unsigned d)
+{
+    unsigned s = 0;
+    while (s < 31 && 1u << s < d) ++s;
+    return Divisor{(unsigned)(((uint64_t)1 << (31 + s)) / d + 1), s};
+}
+__host__ __device__ inline int quotient(int n, Divisor d) { return (int)((unsigned)(((uint64_t)(2u * (unsigned)n) * d.mul) >> 32) >> d.shift); }
+
 }  // namespace
 
 struct commvq_handle {
@@ -142,9 +156,12 @@ struct RangeStats {
 #pragma unroll
         for (int i = 0; i < 4; ++i) first[i] = lane + 64 * i < ns ? st[lane + 64 * i] : make_float2(-INFINITY, 0.f);
     }
+    // (the sequence's own ns and tb, which may be less than what was asked for)
     __device__ __forceinline__ void finish(const float2 *st, int ns, int ta, int tb, int split_len, int v0, int lane, float &mx, float &l, float &lown) const
     {
-        mx = fmaxf(fmaxf(first[0].x, first[1].x), fmaxf(first[2].x, first[3].x));
+        mx = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) mx = fmaxf(mx, lane + 64 * i < ns ? first[i].x : -INFINITY);
         for (int k = lane + 256; k < ns; k += 64) mx = fmaxf(mx, st[k].x);
         mx = wave_max(mx);
         l = lown = 0.f;

@@ -52,6 +52,8 @@ struct ValuesArgs {
     int Hq, Hkv, M;
     int nsplit, split_len;    // statistics tiles of the score stage
     int batch, ncg;
+    Divisor by_hkv, by_ncg, by_batch, by_span;
+    int split_shift;          // log2 split_len
     int ranges, range_len;    // token ranges of a sequence (S > 1: one)
     int span, spans;          // tokens of a range that share a fixed-point unit (S > 1: all); spans of a range
     int mode;                 // 0: everything; 1: up to the bins, which go to memory; 2: from there on
@@ -119,10 +121,13 @@ __device__ __forceinline__ float swap32_add(float x, float y)
 // registers, column 8 n + t of lane n for tile t, so the codebook needs no other layout.  fp32 rows are multiplied by vector
 // instructions, four columns per lane.
 //
-// What bounds it, by variants with a part left out, 128K tokens of the 8B layer at 16 codebooks (21 us): 5.6 until the first token is
-// worked on (4.7 of them the launch after a kernel that leaves 17 MB of dirty lines), 8 for the tokens (the atomics alone are
-// 6.7 at 8.2 lanes a clock), 7.6 for the product (512 KiB of rows through the L1 of every compute unit, at 27 to 64
-// bytes a clock; 4 codebooks a workgroup halve that and double the exponentials).  The bins' way through memory
+// What bounds it, by clocks at the phases' ends, 128K tokens of the 8B layer at 16 codebooks (16 us in the workgroups, and the launch
+// after a kernel that leaves 17 MB of dirty lines): 2 until the first token is worked on, 10.8 for the tokens (the atomics alone are
+// 7.3 at 8.2 lanes a clock, the vector instructions of four wavefronts as much), 0.4 for the copies' sums, 1.3 for the rows of the product,
+// 1.2 for the digits and 0.5 for the wavefronts' sums.  The statistics are asked for before the sequence's length is known and ahead of
+// the tokens, and the workgroup's indices take no division: with both behind the length the phase before the tokens was 3.1 us (whole
+// calls, with the same change to k_out_final: 8B 2-bit 1237 tokens 19.8 -> 18.5, 1-bit 128K 86.6 -> 84.3, position-free 36.8 -> 34.3, one
+// fp32 head of 4096 tokens 16.9 -> 15.0).  The bins' way through memory
 // that it replaces (16 MB out of one kernel and into the next at that size, 67 MB for 64 chats) and one launch less, whole call:
 // one fp32 head of 4096 tokens 23.9 -> 19.8 us; 8B 2-bit 1237 tokens 31.1 -> 24.8, 32K 69.8 -> 56.9, 8 x 8K..64K 483 -> 469, 64 x
 // 512..1024 136 -> 118; 8B 1-bit 128K 92.8 -> 88.6, position-free 39.5 -> 36.0; 70B 4 x 128K 559 -> 553.  Not kept: equal chunks of the whole batch
@@ -153,30 +158,43 @@ __global__ __launch_bounds__(NT, S > 1 ? 2 : 4) void k_values(const ValuesArgs a
     float *const span_s = per_s + S * G, *const own_s = span_s + spans * S * G;  // [span] units per 1; exp-sum
     float *red = reinterpret_cast<float *>(lds);           // [NW][S][G][COLS]
 
-    int id = blockIdx.x;
-    const int g = id % a.Hkv;                              // (head = index mod Hkv: with 8 KV heads an XCD serves one head)
-    id /= a.Hkv;
-    const int cg = id % a.ncg;
-    id /= a.ncg;
-    const int cs = id % NCS, grp = id / NCS;
+    const int id0 = blockIdx.x, id1 = quotient(id0, a.by_hkv), id2 = quotient(id1, a.by_ncg);
+    const int g = id0 - id1 * a.Hkv;                       // (head = index mod Hkv: with 8 KV heads an XCD serves one head)
+    const int cg = id1 - id2 * a.ncg;
+    const int cs = id2 % NCS, grp = id2 / NCS;
+    const int rng = S == 1 ? quotient(grp, a.by_batch) : 0, b0 = S == 1 ? grp - rng * a.batch : grp * S;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    // The statistics that the wavefront looks at first are asked for before anything that takes the sequence's length (which
+    // is on its way meanwhile), as many as a sequence of the longest length has.
+    const int first = rng * a.range_len;                   // first token (S > 1: 0)
+    auto job_stats = [&](int job, int &v0) -> const float2 * __attribute__((always_inline)) {
+        v0 = first + (SPANS ? job / (S * G) * a.span : 0);
+        return a.sstat + ((size_t)min(b0 + job / G % S, a.batch - 1) * a.Hq + (size_t)g * G + job % G) * a.nsplit;
+    };
+    RangeStats stats;
+    if (a.mode != 2 && wave < spans * (S * G)) {
+        int v0;
+        const float2 *st = job_stats(wave, v0);
+        stats.request(st, a.nsplit, v0 >> a.split_shift, min((v0 + a.span + a.split_len - 1) >> a.split_shift, a.nsplit), lane);
+    }
+    __builtin_amdgcn_sched_barrier(0);
 
     const int mshift = a.M == 32 ? 5 : 4;                  // (16 or 32 codebooks)
     int sb[S], sv0[S], sv1[S], sL[S], scu[S];              // sequence, first and last token + 1, length, offset of the slots
     bool any = false;
 #pragma unroll
     for (int s = 0; s < S; ++s) {
-        const int b = S == 1 ? grp % a.batch : grp * S + s;
+        const int b = b0 + s;
         sb[s] = b < a.batch ? b : 0;
         scu[s] = a.cu[sb[s]];
         sL[s] = a.cu[sb[s] + 1] - scu[s];
-        sv0[s] = S == 1 ? grp / a.batch * a.range_len : 0;
+        sv0[s] = first;
         sv1[s] = S == 1 ? min(sv0[s] + a.range_len, sL[s]) : b < a.batch ? sL[s] : 0;
         any |= sv0[s] < sv1[s];
     }
     if (!any) return;
-    const int rng = S == 1 ? grp / a.batch : 0;
 
     // the first tokens' codes and logits
     // (buffer loads: one offset per lane, reads past the sequence return zeros)
@@ -207,7 +225,7 @@ __global__ __launch_bounds__(NT, S > 1 ? 2 : 4) void k_values(const ValuesArgs a
     for (int x = tid; x < S * SLOT / 16; x += NT) reinterpret_cast<uint4 *>(lds)[x] = make_uint4(0u, 0u, 0u, 0u);
 
     // (maximum of the sequence, exp-sum) of every span, slot and head
-    const int live = spans > 1 ? (sv1[0] - sv0[0] + a.span - 1) / a.span : 1;  // spans that have tokens
+    const int live = spans > 1 ? quotient(sv1[0] - sv0[0] + a.span - 1, a.by_span) : 1;  // spans that have tokens
     for (int job = wave; job < live * (S * G); job += NW) {
         const int s = job / G % S, hh = job % G, span = job / (S * G);
         int b = 0, v0 = 0, v1 = 0, L = 0;
@@ -215,21 +233,17 @@ __global__ __launch_bounds__(NT, S > 1 ? 2 : 4) void k_values(const ValuesArgs a
         for (int k = 0; k < S; ++k)
             if (s == k) { b = sb[k]; v0 = sv0[k]; v1 = sv1[k]; L = sL[k]; }
         if (v0 >= v1) continue;
-        if constexpr (SPANS) {
-            v0 += span * a.span;
-            v1 = min(v1, v0 + a.span);
-        }
+        const float2 *st = job_stats(job, v0);
+        if constexpr (SPANS) v1 = min(v1, v0 + a.span);
         const size_t at = ((size_t)b * a.Hq + (size_t)g * G + hh) * a.ranges + rng;
         if (a.mode == 2) {
             if (lane == 0 && span == 0) unit_s[job] = a.vscale[at];
             continue;
         }
-        const int ns = min((L + a.split_len - 1) / a.split_len, a.nsplit);
-        const float2 *st = a.sstat + ((size_t)b * a.Hq + (size_t)g * G + hh) * a.nsplit;
+        const int ns = min((L + a.split_len - 1) >> a.split_shift, a.nsplit);
         // the exp-sum l of all tiles that the span touches bounds every bin; what it reports towards the softmax denominator is lown
-        const int ta = v0 / a.split_len, tb = min((v1 + a.split_len - 1) / a.split_len, ns);
-        RangeStats stats;
-        stats.request(st, ns, ta, tb, lane);
+        const int ta = v0 >> a.split_shift, tb = min((v1 + a.split_len - 1) >> a.split_shift, ns);
+        if (job != wave) stats.request(st, ns, ta, tb, lane);
         float mx, l, lown;
         stats.finish(st, ns, ta, tb, a.split_len, v0, lane, mx, l, lown);
         if (lane == 0) {
