@@ -141,6 +141,21 @@ __device__ __forceinline__ void lds_dma16(const void *base_uniform, unsigned off
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_byte_addr_uniform), "v"(offset), "s"(base_uniform) : "memory");
 }
 
+// Raw buffer descriptor over [base, base + bytes): loads take a per-lane byte offset plus a
+// wave-uniform (scalar) byte offset, and reads past the end return zero instead of faulting.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *base, unsigned bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
+}
+
+// Stores that do not stay in the writer's L2.  What a kernel leaves there is written back once it has ended, before the next
+// one begins: for results of megabytes (logits, bins, partial sums) several microseconds in which nothing else runs, and the
+// next kernel's workgroups, on all eight L2s, read them from memory either way.  Whole calls, kept -> written through: 8B
+// layer at 128K 85.5 -> 83.9 us, paired keys and binary values 116.8 -> 113.3, 32K at 2 bits 57.7 -> 56.5, 70B 4 x 128K 544.5 -> 539.2.
+constexpr int kThrough = 16;  // cache policy of the buffer instructions: visible to the whole GPU
+__device__ __forceinline__ void store_through(uint4_t v, __amdgpu_buffer_rsrc_t r, unsigned offset) { __builtin_amdgcn_raw_buffer_store_b128(v, r, offset, 0, kThrough); }
+__device__ __forceinline__ void store_through(float v, __amdgpu_buffer_rsrc_t r, unsigned offset) { __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, offset, 0, kThrough); }
+
 // Softmax statistics of one head over tokens v0 .. of a sequence, by a wavefront, from the (max, sum of exp(logit - max)) of the ns
 // score tiles of split_len tokens: the maximum of the sequence, the exp-sum of the tiles ta .. tb - 1 that the range touches, and
 // of those that BEGIN inside it (a tile shared by two ranges is counted once).  Every load is requested before

@@ -485,15 +485,13 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_pair(
             for (int h = 0; h < 4; ++h) {
                 if (4 * x + h >= G) break;
                 const float4 w = *reinterpret_cast<const float4 *>(stg + ((h * NP + wp) * 8 + (rel >> kLoBits)) * 68 + (rel & (kLo - 1)));
-                float *dst = dst0 + (size_t)c0 * a.Hq + (size_t)(g * G + 4 * x + h) * L + tok;
-                if (tok + 3 < L) {
-                    typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));  // L need not be a multiple of 4
-                    const f4u ww = {w.x, w.y, w.z, w.w};
-                    *reinterpret_cast<f4u *>(dst) = ww;
+                const __amdgpu_buffer_rsrc_t row = make_rsrc(dst0 + (size_t)c0 * a.Hq + (size_t)(g * G + 4 * x + h) * L, (unsigned)L * 4u);
+                if (tok + 3 < L) {                            // (rows begin at any multiple of 4 bytes)
+                    store_through(__builtin_bit_cast(uint4_t, w), row, (unsigned)tok * 4u);
                 } else {
-                    if (tok < L) dst[0] = w.x;
-                    if (tok + 1 < L) dst[1] = w.y;
-                    if (tok + 2 < L) dst[2] = w.z;
+                    if (tok < L) store_through(w.x, row, (unsigned)tok * 4u);
+                    if (tok + 1 < L) store_through(w.y, row, (unsigned)tok * 4u + 4u);
+                    if (tok + 2 < L) store_through(w.z, row, (unsigned)tok * 4u + 8u);
                 }
                 if (a.groups == 1) {
                     const float w0 = tok < L ? w.x : -INFINITY, w1 = tok + 1 < L ? w.y : -INFINITY;

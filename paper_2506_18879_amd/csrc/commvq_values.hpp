@@ -68,13 +68,6 @@ __device__ __forceinline__ int fresh_lane()
     return l;
 }
 
-// Raw buffer descriptor over [base, base + bytes): loads take a per-lane byte offset plus a
-// wave-uniform (scalar) byte offset, and reads past the end return zero instead of faulting.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *base, unsigned bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
-}
-
 // x in whole units (numbers on [0, 2^32)): rounded to nearest, NaN to 0.
 __device__ __forceinline__ unsigned whole_units(float x, float per)
 {

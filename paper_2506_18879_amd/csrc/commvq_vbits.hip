@@ -210,6 +210,9 @@ __global__ __launch_bounds__(kVbThreads) void k_vbits(VbitsArgs a)
 
     // digits -> integer bins [Nc rows][G] per (sequence, KV head, range); row 128 W + 16 p + n for the wavefront's W-th
     // run of 128 code bits (vbits_code_bit gives the code bit of a row): the 16 lanes of a pass store 16 consecutive rows
+    // (the bins of the workgroup's 16 heads, all ranges: 64 MB at most)
+    const __amdgpu_buffer_rsrc_t own = make_rsrc(a.bins + (size_t)(b * a.Hkv + h0 / a.G) * a.nvsplit * ((size_t)a.G * a.Nc),
+                                                 (unsigned)kVbitsHeads * (unsigned)a.nvsplit * (unsigned)a.Nc * 4u);
 #pragma unroll
     for (int p = 0; p < 8; ++p) {
         const size_t row = (size_t)(128 * (cg * (kVbitsCols / 128) + wave) + 16 * p + n);
@@ -226,8 +229,8 @@ __global__ __launch_bounds__(kVbThreads) void k_vbits(VbitsArgs a)
         if ((a.G & 3) == 0) {
             if (h < a.Hq) {
                 const int g = h / a.G, hh = h % a.G;
-                unsigned *dst = a.bins + ((size_t)(b * a.Hkv + g) * a.nvsplit + vs) * ((size_t)a.G * a.Nc) + row * a.G + hh;
-                *reinterpret_cast<uint4 *>(dst) = make_uint4(val[0], val[1], val[2], val[3]);
+                store_through(uint4_t{val[0], val[1], val[2], val[3]}, own,
+                              ((unsigned)(((g - h0 / a.G) * a.nvsplit + vs) * a.G) * (unsigned)a.Nc + (unsigned)row * a.G + hh) * 4u);
             }
         } else {
 #pragma unroll
