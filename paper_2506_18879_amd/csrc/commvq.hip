@@ -822,6 +822,7 @@ struct SliceDims {
 // (no static LDS), but the compiler only learns that after instruction selection: a read through the array's
 // base costs one "add 0" per read.
 typedef __attribute__((address_space(3))) const uint4_t *lds_u4_ptr;
+typedef __attribute__((address_space(3))) const uint2_t *lds_u2_ptr;
 __device__ __forceinline__ uint4_t lds_read_b128(unsigned byte_addr) { return *reinterpret_cast<lds_u4_ptr>(byte_addr); }
 
 // Workgroup barrier that waits for nothing by itself: the caller has waited for what the others may rely on (LDS
@@ -879,33 +880,33 @@ struct StreamDims {
 //     The LDS reads of a group of steps are issued right after the matrix instructions that consumed the
 //     group's registers, so the first reads of the next pass travel while this pass is finished.
 //  2. Each lane rotates its two (x, y) sub-spaces by the coarse phase factor of its token.
-//  3. Contraction with the queries, two passes at a time: the two lanes of a token hold half of its 8 elements each, so
-//     an exchange of 16-lane rows between the passes of a pair (4 v_permlane16_swap) gives the even lane all 8 elements of
-//     its token of the even pass and the odd lane those of its token of the odd pass.  Eight chained
-//     v_mfma_f32_4x4x1_16b_f32 per group of 4 heads (in a block of 4 lanes, lane i supplies q'[head i][element], every lane
-//     its own element) then add the slice's whole contribution to the accumulators of 4 heads: nothing is left to add or
-//     exchange per head, where totals over the token's lanes per pass took 6 (G = 4) to 12 (G = 8) vector instructions.
-// What bounds it: SIMD issue.  With four wavefronts on a SIMD a sparse MFMA takes 17 clk of it, a 4x4x1 one 9, a row swap 9,
-// a byte permute 5, a rotation's multiplication or addition 3 (micro-benchmark), and they add up; a pass is 4 (8) + 4 (8) +
-// 2 + 8 (16) + 8 of these for M = 16 (32) and 4 heads = 200 (300) clk at 2.4 GHz, and the compute unit's LDS needs 4.35 clk
-// for each of the M / 2 + 1 16-byte reads of its 16 wavefronts, 157 (296) per SIMD.  Measured per slice of 8 passes: 7700
-// clk at 2.14 GHz against 5700 for M = 16, 13200 against 9800 for M = 32; the rest is the switch of slices and what the
-// latencies of one wavefront's chain leave open.  A wavefront that is behind issues first (s_setprio by pass): waves that ran
-// ahead left the last ones alone on their SIMD before each barrier (C3 74.5 -> 73.4 us, 8 heads 487 -> 475).
+//  3. Contraction with the queries.  The two lanes of a token hold half of its 8 elements each.  Logits are sums over
+//     elements, so each lane keeps the sum of its own half for all slices, and the two meet once, at the write-out: four chained
+//     v_mfma_f32_4x4x1_16b_f32 (in a block of 4 lanes, lane i supplies q'[head i][element], every lane its own element) add a
+//     pass's whole contribution to the accumulators of 4 heads, and the query operand is folded for 4 elements instead of 8.  They run between
+//     the steps of the next pass.  With two groups of heads (8) there are no registers for accumulators of every pass: there
+//     an exchange of 16-lane rows between the passes of a pair (4 v_permlane16_swap) gives the even lane all 8 elements of its
+//     token of the even pass and the odd lane those of the odd pass, and eight chained instructions per group follow.  For 4 heads
+//     that, and the next slice of M = 32 through registers that the halves need: 128K tokens, M = 16 82.5 against 80.2 us a call, 8 x
+//     8K..64K, M = 32 457 against 434, 32K 55.7 against 54.4, 64 x 512..1024 115 against 110; rms error of the logits against 64 bits
+//     1.25e-7 and 1.06e-7 (M = 16), 1.58e-7 and 1.25e-7 (M = 32).
+// What bounds it: LDS and SIMD issue.  With four wavefronts on a SIMD a sparse MFMA takes 17 clk of it, a 4x4x1 one 9, a row swap 9,
+// a byte permute 5, a rotation's multiplication or addition 3 to 4 (micro-benchmark), and they add up; a pass is 4 (8) + 5 + 8 (16)
+// + 8 of these for M = 16 (32) and 4 heads = 180 (290) clk, and the compute unit's LDS needs 4.35 clk for each of the M / 2 + 1
+// 16-byte reads of its 16 wavefronts and 8 for each KiB of the next slice, 173 (332) per SIMD and pass.  Measured per pass: 223 (398) clk, at
+// 2.2 GHz; the rest is the switch of slices and what the latencies of one wavefront's chain leave open.  (With 8 heads 440 for M = 32.)
+// A wavefront that is behind issues first (s_setprio by pass), pass by pass in the last ones: waves that run ahead leave the last ones
+// alone on their SIMD before each barrier (one level per two passes instead: 8 x 8K..64K 458.5 us, 454.2 so; 128K 82.8 and 82.0).
 //
 // Slices.  M = 16: the two 64 KiB blocks take slices in turn, the next one travels (memory -> LDS, no registers)
 // while the current one is worked on: one barrier per slice.  Its sends are spread over the passes, since a burst fills
 // the memory pipe's queue and stops the wavefronts for up to 2000 clk.  M = 32: a slice fills both blocks (codebooks 0..15 |
-// 16..31).  Its last pass is done with block 0 after half of its steps; the next slice's block 0, fetched into registers
-// earlier, is stored right then, and block 1 follows after the first half of the next slice's first pass, when everyone
-// has left the old one.  With 8 heads no registers are left to wait in: there the blocks are sent for at those points
-// (eight passes spill 6 registers).
+// 16..31).  Its last pass is done with block 0 after half of its steps and with block 1 at its end; the next slice's are sent for
+// right then, and block 1 is waited for after the first half of the next slice's first pass.  (Block 1 sent for behind the barrier between the
+// slices, which saves one: 8 x 8K..64K 437 -> 443.)  8 heads with M = 32 and eight passes spill 6 registers.
 //
-// Times, one sequence or batch of the 8B / 70B layer, before (tiles of one sequence, per-head totals after every pass) and
-// now: 128K tokens, M = 16: 75.3 -> 72 us; 8 x 8K..64K, M = 32: 435 -> 390; 64 x 512..1024, M = 32: 105 -> 70 (sequences
-// share workgroups); 4 x 128K, M = 32, 8 heads: 548 -> 475.  Not kept: three or four steps of reads in flight instead of two
-// (spills, or no change); M = 32 as two sweeps of 16 codebooks with the gather sums carried in registers, which
-// allows double buffering but only 4 to 6 passes (8 heads: 549 us, 4 heads: 403).
+// Not kept: three or four steps of reads in flight instead of two (no change, or spills); M = 32 as two sweeps of 16 codebooks with the
+// gather sums carried in registers, which allows double buffering but only 4 to 6 passes (8 heads: 549 us instead of 475).
 //
 // Short contexts: a launch may cut every tile along the slices as well (StreamDims::groups workgroups per
 // tile); each then writes partial logits, which k_score_combine adds.
@@ -920,8 +921,7 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_stream(
     constexpr int NST = 4 * NB;                               // gather steps (sparse matrix instructions) per pass
     const int G = NGRP == 2 ? 8 : a.G;                        // query heads of the KV head; NGRP groups of 4, padded with zero queries
     constexpr int NBUF = 2;                                   // gather steps whose LDS reads are in flight
-    constexpr bool STAGE = M == 32 && NGRP == 1;              // next slice through registers (8 heads leave none)
-    constexpr bool DELAY = M == 16 && NGRP == 1;              // a pair's rest runs between the steps of the next pass (else: no registers)
+    constexpr bool HALF = NGRP == 1;                          // logits in two halves, each of the elements that a lane has (8 heads: no registers)
     extern __shared__ __attribute__((aligned(16))) uint4 tab[];
 
     int id = blockIdx.x;
@@ -1141,35 +1141,26 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_stream(
     }
 
     constexpr int NPAIR = (NP + 1) / 2;
-    floatx4_t sc[NPAIR][NGRP];                               // pair k: 4 heads of the lane's token of pass 2 k + par
+    // HALF: 4 heads of the lane's token of pass p, from the lane's half of the elements; else 4 heads of its token of pass 2 k + par
+    constexpr int NV = HALF ? NP : NPAIR;
+    floatx4_t sc[NV][NGRP];
 #pragma unroll
-    for (int k = 0; k < NPAIR; ++k)
+    for (int k = 0; k < NV; ++k)
 #pragma unroll
         for (int x = 0; x < NGRP; ++x) sc[k][x] = floatx4_t{0.f, 0.f, 0.f, 0.f};
 
     float zero = 0.f;
     asm volatile("" : "+v"(zero));
     uint4_t v[NBUF][2];
-    float qrow[NGRP][8];                                      // q' of the slice: head 4 x + n % 4, the 8 elements
+    float qrow[NGRP][HALF ? 4 : 8];                                      // q' of the slice: head 4 x + n % 4, the 8 elements
     unsigned ehi_at = 0u;                                     // LDS address of the lane's coarse factor in pass 0's rows
     // where the lane finds its fine and coarse factor of pass 0's sequence, from the start of a buffer: bits 0..15, 16..31
     unsigned at0;
     {
         const int D0 = qd[0], D1 = qd[NP > 1 ? 1 : 0], ln = fresh_lane(), fl = 4 * wave + (ln >> 2 & 3), Dl = ln >> 4 & 1 ? D1 : D0;
         const int row = ((D0 - fl) >> kLoBits) - ((D0 + 1) >> kLoBits) + 8 - (ln & 3) - 4 * (ln >> 5);
-        at0 = (unsigned)((Dl - fl) & (kLo - 1)) * 16u | (unsigned)(kAuxHi + 2 * row + (ln >> 4 & 1)) << 20;
+        at0 = (unsigned)(HALF ? ((D0 - fl) & (kLo - 1)) + (ln >> 4 & 1) * kLo : (Dl - fl) & (kLo - 1)) * 16u | (unsigned)(kAuxHi + 2 * row + (ln >> 4 & 1)) << 20;
     }
-    uint4_t stage[4];                                         // STAGE: the thread's pieces of a block on their way to LDS
-    auto fetch_block = [&](int sl, int blk) {
-        const uint4_t *p = reinterpret_cast<const uint4_t *>(src + ((size_t)sl * NB + blk) * kBlockBytes) + (wave * 64 + fresh_lane());
-#pragma unroll
-        for (int j = 0; j < 4; ++j) stage[j] = p[j * kSliceThreads];
-    };
-    auto store_block = [&](int blk) {
-        uint4_t *p = reinterpret_cast<uint4_t *>(tab) + blk * (kBlockBytes / 16) + (wave * 64 + fresh_lane());
-#pragma unroll
-        for (int j = 0; j < 4; ++j) p[j * kSliceThreads] = stage[j];
-    };
     for (int sl = s_begin; sl < s_end; ++sl) {
         const bool more = sl + 1 < s_end;
         const int buf = sl & 1;
@@ -1196,11 +1187,44 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_stream(
                 v[(p * NST + st) % NBUF][ab] = lds_read_b128(__builtin_amdgcn_perm(ccall[p][ab][blk], xreg[st % 4], psel));
         };
         // q' = q conj(E_lo) for the pair of passes k (Re(conj(q) a E_hi E_lo) = Re(conj(q') a E_hi))
-        auto fold = [&](int k) {
+        // HALF: for pass k, the lane's 4 elements
+        auto fold = [&](int k) __attribute__((always_inline)) {
             const int ln = fresh_lane(), odd = ln >> 4 & 1;
             unsigned lo = aux0 + (at0 & 0xffffu);
+            if constexpr (HALF) {
+                if (k > 0) lo = aux0 + (unsigned)(((qd[k] - 4 * wave - (ln >> 2 & 3)) & (kLo - 1)) + odd * kLo) * 16u;
+                const uint4_t e = lds_read_b128(lo);
+                const int h = ln & 3;
+                const unsigned at = aux0 + (unsigned)(kAuxQ + (k * G + h) * (a.q_bf16 ? 1 : 2)) * 16u + odd * (a.q_bf16 ? 8u : 16u);
+                float qv[4];
+                if (a.q_bf16) {
+                    const uint2_t w = *reinterpret_cast<lds_u2_ptr>(at);
+#pragma unroll
+                    for (int r = 0; r < 2; ++r) {
+                        const unsigned u = w[r];
+                        qv[2 * r] = bf16_lo(u);
+                        qv[2 * r + 1] = bf16_hi(u);
+                    }
+                } else {
+                    const uint4_t w = lds_read_b128(at);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const unsigned u = w[r];
+                        qv[r] = __builtin_bit_cast(float, u);
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const unsigned lxr = e[2 * u], lyr = e[2 * u + 1];
+                    const float lx = __builtin_bit_cast(float, lxr), ly = __builtin_bit_cast(float, lyr);
+                    const float qx = qv[2 * u], qy = qv[2 * u + 1];
+                    qrow[0][2 * u] = h >= G ? 0.f : qx * lx + qy * ly;
+                    qrow[0][2 * u + 1] = h >= G ? 0.f : qy * lx - qx * ly;
+                }
+                return;
+            }
             if (k > 0) {
-                const int d0 = qd[2 * k], d1 = qd[2 * k + 1 < NP ? 2 * k + 1 : 2 * k], D = odd ? d1 : d0;
+                const int d0 = qd[2 * k % NP], d1 = qd[2 * k + 1 < NP ? 2 * k + 1 : 2 * k % NP], D = odd ? d1 : d0;
                 lo = aux0 + (unsigned)((D - 4 * wave - (ln >> 2 & 3)) & (kLo - 1)) * 16u;
             }
             const uint4_t e0 = lds_read_b128(lo), e1 = lds_read_b128(lo + kLo * 16u);
@@ -1250,6 +1274,19 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_stream(
             val[2 * u] = ax * ex - ay * ey;
             val[2 * u + 1] = ax * ey + ay * ex;
         };
+        // 2. and 3. for pass p, in NST parts that run between the steps of the next pass
+        float val[4];
+        auto finish_half = [&](auto pc, const floatx4_t &acc, const uint4_t &eh, int st) __attribute__((always_inline)) {
+            constexpr int p = decltype(pc)::value;
+            if (st == 0) {
+                rotate(0, acc, eh, val);
+                rotate(1, acc, eh, val);
+            } else {
+#pragma unroll
+                for (int r = (st - 1) * 4 / (NST - 1); r < st * 4 / (NST - 1); ++r)
+                    sc[HALF ? p : 0][0] = __builtin_amdgcn_mfma_f32_4x4x1f32(qrow[0][r], val[r], sc[HALF ? p : 0][0], 0, 0, 0);
+            }
+        };
         floatx4_t acc_e, acc_o;                               // gather sums of the pair's even and odd pass
         uint4_t eh_e, eh_o;                                   // their coarse phase factors
         float xy[8];                                          // even pass: rotated elements in 0..3; then the lane's 8 elements
@@ -1277,7 +1314,8 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_stream(
         auto pass = [&](auto pc, floatx4_t &acc, uint4_t &eh, auto part) __attribute__((always_inline)) {
             constexpr int p = decltype(pc)::value;
             __builtin_amdgcn_sched_barrier(0);
-            __builtin_amdgcn_s_setprio(3 - p * 4 / NP);       // (wavefronts that are behind go first)
+            // (wavefronts that are behind go first; pass by pass towards the barrier, where a last one would be alone on its SIMD)
+            __builtin_amdgcn_s_setprio(p < NP - 4 ? 3 : p < NP - 2 ? 2 : NP - 1 - p);
             if (p == 0) ehi_at = aux0 + (at0 >> 16);
             else if (__builtin_expect(chg >> p & 1u, 0)) hi_row(qd[p]);
             eh = lds_read_b128(ehi_at + (unsigned)(p * 2 * kHiRows * 16));
@@ -1290,7 +1328,6 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_stream(
                         if (p == j * (NP - 1) / 5) send_part(sl + 1, 0, buf ^ 1, j);
                 }
                 if (p == (M == 16 ? 4 * (NP - 1) / 5 : (NP - 1) / 3)) send_aux(sl + 1, buf ^ 1);
-                if (STAGE && p == (NP - 1) / 2) fetch_block(sl + 1, 0);
             }
             // (cleared by a small matrix instruction: the compiler makes five moves of a vector of zeros)
             acc = __builtin_amdgcn_mfma_f32_4x4x1f32(zero, zero, floatx4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
@@ -1301,14 +1338,7 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_stream(
                 acc = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(selv, __builtin_bit_cast(bf16x16_t, both), acc, (int)sidx, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
                 if (M == 32 && p == 0 && st + NBUF == 4) {
-                    // block 1 of this slice: what was fetched during the last pass of the slice before can be put in place now
-                    // that everyone has left that slice; or what was sent for has arrived
-                    if (STAGE && sl > s_begin) {
-                        store_block(1);
-                        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                    } else {
-                        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                    }
+                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // block 1 of this slice has arrived
                     bare_barrier();
                 }
                 if (st + NBUF < NST) issue(p, st + NBUF);
@@ -1317,14 +1347,9 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_stream(
                 if (M == 32 && p == NP - 1 && st == 3 && more) {
                     // everyone has read the last pieces of block 0: the next slice's may come
                     bare_barrier();
-                    if (STAGE) {
-                        store_block(0);
-                        fetch_block(sl + 1, 1);
-                    } else {
-                        send_block(sl + 1, 0, 0);
-                    }
+                    send_block(sl + 1, 0, 0);
                 }
-                if (M == 32 && !STAGE && p == NP - 1 && st == 7 && more) {
+                if (M == 32 && p == NP - 1 && st == 7 && more) {
                     bare_barrier();
                     send_block(sl + 1, 1, 1);
                 }
@@ -1334,7 +1359,7 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_stream(
         };
         auto pair = [&](auto kc) __attribute__((always_inline)) {
             constexpr int k = decltype(kc)::value;
-            pass(std::integral_constant<int, 2 * k>{}, acc_e, eh_e, [&](int st) { if (DELAY && k > 0) finish(k > 0 ? k - 1 : 0, st); });
+            pass(std::integral_constant<int, 2 * k>{}, acc_e, eh_e, [](int) {});
             if (k == 0 || (chg >> (2 * k - 1) & 7u)) fold(k);
             if constexpr (2 * k + 1 < NP) {
                 pass(std::integral_constant<int, 2 * k + 1>{}, acc_o, eh_o, [&](int st) { if (st < 2) rotate(st, acc_e, eh_e, xy); });
@@ -1344,17 +1369,40 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_stream(
                 acc_o = floatx4_t{0.f, 0.f, 0.f, 0.f};
                 eh_o = uint4_t{0u, 0u, 0u, 0u};
             }
-            if (!DELAY || k == NPAIR - 1) {
 #pragma unroll
-                for (int st = 0; st < NST; ++st) finish(k, st);
+            for (int st = 0; st < NST; ++st) finish(k, st);
+        };
+        // (even and odd passes' sums and factors in turn)
+        auto half = [&](auto pc) __attribute__((always_inline)) {
+            constexpr int p = decltype(pc)::value;
+            if constexpr (p < NP) {
+                typedef std::integral_constant<int, (p > 0 ? p - 1 : 0)> before;
+                if constexpr (p % 2 == 0) pass(pc, acc_e, eh_e, [&](int st) { if (p > 0) finish_half(before{}, acc_o, eh_o, st); });
+                else pass(pc, acc_o, eh_o, [&](int st) { finish_half(before{}, acc_e, eh_e, st); });
+                if (p == 0 || (chg >> p & 1u)) fold(p);
+                if constexpr (p == NP - 1) {
+#pragma unroll
+                    for (int st = 0; st < NST; ++st) finish_half(pc, p % 2 ? acc_o : acc_e, p % 2 ? eh_o : eh_e, st);
+                }
             }
         };
 #pragma unroll
         for (int st = 0; st < NBUF; ++st) issue(0, st);
-        pair(std::integral_constant<int, 0>());
-        if constexpr (NPAIR > 1) pair(std::integral_constant<int, (NPAIR > 1 ? 1 : 0)>());
-        if constexpr (NPAIR > 2) pair(std::integral_constant<int, (NPAIR > 2 ? 2 : 0)>());
-        if constexpr (NPAIR > 3) pair(std::integral_constant<int, (NPAIR > 3 ? 3 : 0)>());
+        if constexpr (HALF) {
+            half(std::integral_constant<int, 0>());
+            half(std::integral_constant<int, 1>());
+            half(std::integral_constant<int, 2>());
+            half(std::integral_constant<int, 3>());
+            half(std::integral_constant<int, 4>());
+            half(std::integral_constant<int, 5>());
+            half(std::integral_constant<int, 6>());
+            half(std::integral_constant<int, 7>());
+        } else {
+            pair(std::integral_constant<int, 0>());
+            if constexpr (NPAIR > 1) pair(std::integral_constant<int, (NPAIR > 1 ? 1 : 0)>());
+            if constexpr (NPAIR > 2) pair(std::integral_constant<int, (NPAIR > 2 ? 2 : 0)>());
+            if constexpr (NPAIR > 3) pair(std::integral_constant<int, (NPAIR > 3 ? 3 : 0)>());
+        }
     }
 
     // Write-out.  A wavefront's tokens are scattered over the pass (4 fine positions x 8 coarse rows), so the logits of
@@ -1375,8 +1423,10 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_stream(
         for (int k = 0; k < NPAIR; ++k)
             if (2 * k < np) {
 #pragma unroll
-                for (int h = 0; h < 4; ++h)
-                    if (2 * k + wpar < NP) stg[((h * NP + 2 * k + wpar) * 8 + wrow) * 68 + wf] = sc[k][x][h] * a.scale;
+                for (int h = 0; h < 4; ++h) {
+                    const float v = HALF ? swap16_add(sc[2 * k % NV][x][h], 2 * k + 1 < NP ? sc[(2 * k + 1) % NV][x][h] : 0.f) : sc[k][x][h];
+                    if (2 * k + wpar < NP) stg[((h * NP + 2 * k + wpar) * 8 + wrow) * 68 + wf] = v * a.scale;
+                }
             }
         __syncthreads();
         if (wp < np) {

@@ -31,8 +31,7 @@ __global__ __launch_bounds__(256) void k_prep_pairs(const uint4 *__restrict__ ta
     packed[t] = v;
 }
 
-// Score kernel for paired-code keys: k_score_stream (which see for tokens, segments, the contraction of pairs of passes and the
-// write-out) with another gather.  Differences:
+// Score kernel for paired-code keys: k_score_stream (which see for tokens, segments, the contraction and the write-out) with another gather.  Differences:
 //   * A slice = 4 planes of 8 elements of every centre of every level, SETS sets of four levels: a set is 64 rows (centre
 //     index) of 16 bank columns, 4 of them per plane.  A plane takes the place of a slice there: four rounds per slice.
 //   * Lanes n with the same n / 4 = j work on plane i ^ j in round i.  The four lanes of a token are (a | b) x half: in step (s, st)
@@ -47,8 +46,9 @@ __global__ __launch_bounds__(256) void k_prep_pairs(const uint4 *__restrict__ ta
 //     (Buffer loads check each dword against the end of the stream by itself.)
 //   * Phase factors and queries of a slice (four times those of one plane) come through registers, requested in the last
 //     round of the slice before.
-// What bounds it: SIMD issue as there, 6 (12) sparse matrix instructions, 12 (24) byte permutes, 4 query products, 2 row swaps
-// and a rotation of 8 per 32 tokens and plane for R = 11 (21) and 4 heads.  Whole calls with binary values, before (index bytes unpacked
+// What bounds it: SIMD issue and LDS as there, 6 (12) sparse matrix instructions, 12 (24) byte permutes, 5 products and a rotation of 8
+// per 32 tokens and plane for R = 11 (21) and 4 heads (with the exchange of rows instead of logits in halves: paper's 1-bit setting at 128K
+// 112.4 us a call, 107.7 so).  Whole calls with binary values, before (index bytes unpacked
 // by a kernel of their own, 17 us at 128K, and read again for every slice; columns for 16 or 32 levels; totals over lanes; tiles
 // of one sequence, never cut along the planes) and now, R = 11 | 21: 2000 tokens 58.3 -> 39.7 | 78.5 -> 42.6 us, 12000 59.6 ->
 // 48.2 | 81.1 -> 56.3, 40000 84.1 -> 74.4 | 125.8 -> 89.2, 128K 146.8 -> 117.3 | 250 -> 197, 8 x 1100..2200 63.1 -> 55.9 | 84.3 -> 62.2.
@@ -64,7 +64,7 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_pair(
     constexpr bool TWO = SETS == 3;                           // slices in two LDS buffers in turn, else in one
     const int G = NGRP == 2 ? 8 : a.G;                        // query heads of the KV head; NGRP groups of 4, padded with zero queries
     constexpr int NBUF = 2;                                   // gather steps whose LDS reads are in flight
-    constexpr bool DELAY = NGRP == 1 && SETS == 3;            // a pair's rest runs between the steps of the next pass (else: no registers)
+    constexpr bool HALF = NGRP == 1;                          // logits in two halves, each of the elements that a lane has (8 heads: no registers)
     constexpr int CC = SETS == 3 ? 3 : SETS;                  // dwords of a lane's index bytes per pass
     constexpr int RAW = SETS == 3 ? 5 : SETS == 4 ? 7 : 8;    // dwords that hold a record at any byte offset
     // LDS: slice buffers at 0 (and 64 KiB), [8 parts][64 positions] fine factors, queries, coarse factors [pass][9 rows][8 parts, padded
@@ -279,16 +279,18 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_pair(
     const bf16x8_t selv = __builtin_bit_cast(bf16x8_t, sel);
 
     constexpr int NPAIR = (NP + 1) / 2;
-    floatx4_t sc[NPAIR][NGRP];                               // pair k: 4 heads of the lane's token of pass 2 k + par
+    // HALF: 4 heads of the lane's token of pass p, from the lane's half of the elements; else 4 heads of its token of pass 2 k + par
+    constexpr int NV = HALF ? NP : NPAIR;
+    floatx4_t sc[NV][NGRP];
 #pragma unroll
-    for (int k = 0; k < NPAIR; ++k)
+    for (int k = 0; k < NV; ++k)
 #pragma unroll
         for (int x = 0; x < NGRP; ++x) sc[k][x] = floatx4_t{0.f, 0.f, 0.f, 0.f};
 
     float zero = 0.f;
     asm volatile("" : "+v"(zero));
     uint4_t v[NBUF][2];
-    float qrow[NGRP][8];                                      // q' of the plane: head 4 x + n % 4, the 8 elements
+    float qrow[NGRP][HALF ? 4 : 8];                                      // q' of the plane: head 4 x + n % 4, the 8 elements
     unsigned ehi_at = 0u;                                     // LDS address of the lane's coarse factor in pass 0's rows
     // the lane's row among the coarse factors of a pass whose first token is D away from its query, and its part in round 0
     auto hi_row = [&](int D, int i) {
@@ -333,9 +335,42 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_pair(
             }
         };
         // q' = q conj(E_lo) for the pair of passes k (Re(conj(q) a E_hi E_lo) = Re(conj(q') a E_hi))
-        auto fold = [&](int k) {
+        // HALF: for pass k, the lane's 4 elements
+        auto fold = [&](int k) __attribute__((always_inline)) {
             const int ln = fresh_lane(), odd = ln >> 4 & 1, j = ln >> 2 & 3, pl = i ^ j;
-            const int d0 = qd[2 * k], d1 = qd[2 * k + 1 < NP ? 2 * k + 1 : 2 * k], D = odd ? d1 : d0;
+            if constexpr (HALF) {
+                const unsigned lo = (unsigned)ELO_AT + (unsigned)((2 * pl + odd) * kLo + ((qd[k] - 4 * wave - j) & (kLo - 1))) * 16u;
+                const uint4_t e = lds_read_b128(lo);
+                const int h = ln & 3;
+                const unsigned at = (unsigned)Q_AT + (unsigned)((k * G + h) * per + (a.q_bf16 ? pl : 2 * pl)) * 16u + odd * (a.q_bf16 ? 8u : 16u);
+                float qv[4];
+                if (a.q_bf16) {
+                    const uint2_t w = *reinterpret_cast<lds_u2_ptr>(at);
+#pragma unroll
+                    for (int r = 0; r < 2; ++r) {
+                        const unsigned u = w[r];
+                        qv[2 * r] = bf16_lo(u);
+                        qv[2 * r + 1] = bf16_hi(u);
+                    }
+                } else {
+                    const uint4_t w = lds_read_b128(at);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const unsigned u = w[r];
+                        qv[r] = __builtin_bit_cast(float, u);
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const unsigned lxr = e[2 * u], lyr = e[2 * u + 1];
+                    const float lx = __builtin_bit_cast(float, lxr), ly = __builtin_bit_cast(float, lyr);
+                    const float qx = qv[2 * u], qy = qv[2 * u + 1];
+                    qrow[0][2 * u] = h >= G ? 0.f : qx * lx + qy * ly;
+                    qrow[0][2 * u + 1] = h >= G ? 0.f : qy * lx - qx * ly;
+                }
+                return;
+            }
+            const int d0 = qd[2 * k % NP], d1 = qd[2 * k + 1 < NP ? 2 * k + 1 : 2 * k % NP], D = odd ? d1 : d0;
             const unsigned lo = (unsigned)ELO_AT + (unsigned)(2 * pl * kLo + ((D - 4 * wave - j) & (kLo - 1))) * 16u;
             const uint4_t e0 = lds_read_b128(lo), e1 = lds_read_b128(lo + kLo * 16u);
 #pragma unroll
@@ -378,6 +413,19 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_pair(
             val[2 * u] = ax * ex - ay * ey;
             val[2 * u + 1] = ax * ey + ay * ex;
         };
+        // 2. and 3. for pass p, in NST parts that run between the steps of the next pass
+        float val[4];
+        auto finish_half = [&](auto pc, const floatx4_t &acc, const uint4_t &eh, int st) __attribute__((always_inline)) {
+            constexpr int p = decltype(pc)::value;
+            if (st == 0) {
+                rotate(0, acc, eh, val);
+                rotate(1, acc, eh, val);
+            } else {
+#pragma unroll
+                for (int r = (st - 1) * 4 / (NST - 1); r < st * 4 / (NST - 1); ++r)
+                    sc[HALF ? p : 0][0] = __builtin_amdgcn_mfma_f32_4x4x1f32(qrow[0][r], val[r], sc[HALF ? p : 0][0], 0, 0, 0);
+            }
+        };
         floatx4_t acc_e, acc_o;                               // gather sums of the pair's even and odd pass
         uint4_t eh_e, eh_o;                                   // their coarse phase factors
         float xy[8];                                          // even pass: rotated elements in 0..3; then the lane's 8 elements
@@ -405,7 +453,8 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_pair(
         auto pass = [&](auto pc, floatx4_t &acc, uint4_t &eh, auto part) __attribute__((always_inline)) {
             constexpr int p = decltype(pc)::value;
             __builtin_amdgcn_sched_barrier(0);
-            __builtin_amdgcn_s_setprio(3 - p * 4 / NP);       // (wavefronts that are behind go first)
+            // (wavefronts that are behind go first; pass by pass towards the barrier, where a last one would be alone on its SIMD)
+            __builtin_amdgcn_s_setprio(p < NP - 4 ? 3 : p < NP - 2 ? 2 : NP - 1 - p);
             if (p == 0 || __builtin_expect(chg >> p & 1u, 0)) hi_row(qd[p], i);
             eh = lds_read_b128(ehi_at + (unsigned)(p * kHiRows * HROW * 16));
             // the next slice sets out spread over this one's rounds; its phase factors and queries in the last round
@@ -430,7 +479,7 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_pair(
         };
         auto pair = [&](auto kc) __attribute__((always_inline)) {
             constexpr int k = decltype(kc)::value;
-            pass(std::integral_constant<int, 2 * k>{}, acc_e, eh_e, [&](int st) { if (DELAY && k > 0) finish(k > 0 ? k - 1 : 0, st); });
+            pass(std::integral_constant<int, 2 * k>{}, acc_e, eh_e, [](int) {});
             if (k == 0 || (chg >> (2 * k - 1) & 7u)) fold(k);
             if constexpr (2 * k + 1 < NP) {
                 pass(std::integral_constant<int, 2 * k + 1>{}, acc_o, eh_o, [&](int st) { if (st < 2) rotate(st, acc_e, eh_e, xy); });
@@ -440,17 +489,40 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_pair(
                 acc_o = floatx4_t{0.f, 0.f, 0.f, 0.f};
                 eh_o = uint4_t{0u, 0u, 0u, 0u};
             }
-            if (!DELAY || k == NPAIR - 1) {
 #pragma unroll
-                for (int st = 0; st < NST; ++st) finish(k, st);
+            for (int st = 0; st < NST; ++st) finish(k, st);
+        };
+        // (even and odd passes' sums and factors in turn)
+        auto half = [&](auto pc) __attribute__((always_inline)) {
+            constexpr int p = decltype(pc)::value;
+            if constexpr (p < NP) {
+                typedef std::integral_constant<int, (p > 0 ? p - 1 : 0)> before;
+                if constexpr (p % 2 == 0) pass(pc, acc_e, eh_e, [&](int st) { if (p > 0) finish_half(before{}, acc_o, eh_o, st); });
+                else pass(pc, acc_o, eh_o, [&](int st) { finish_half(before{}, acc_e, eh_e, st); });
+                if (p == 0 || (chg >> p & 1u)) fold(p);
+                if constexpr (p == NP - 1) {
+#pragma unroll
+                    for (int st = 0; st < NST; ++st) finish_half(pc, p % 2 ? acc_o : acc_e, p % 2 ? eh_o : eh_e, st);
+                }
             }
         };
 #pragma unroll
         for (int st = 0; st < NBUF; ++st) issue(0, st);
-        pair(std::integral_constant<int, 0>());
-        if constexpr (NPAIR > 1) pair(std::integral_constant<int, (NPAIR > 1 ? 1 : 0)>());
-        if constexpr (NPAIR > 2) pair(std::integral_constant<int, (NPAIR > 2 ? 2 : 0)>());
-        if constexpr (NPAIR > 3) pair(std::integral_constant<int, (NPAIR > 3 ? 3 : 0)>());
+        if constexpr (HALF) {
+            half(std::integral_constant<int, 0>());
+            half(std::integral_constant<int, 1>());
+            half(std::integral_constant<int, 2>());
+            half(std::integral_constant<int, 3>());
+            half(std::integral_constant<int, 4>());
+            half(std::integral_constant<int, 5>());
+            half(std::integral_constant<int, 6>());
+            half(std::integral_constant<int, 7>());
+        } else {
+            pair(std::integral_constant<int, 0>());
+            if constexpr (NPAIR > 1) pair(std::integral_constant<int, (NPAIR > 1 ? 1 : 0)>());
+            if constexpr (NPAIR > 2) pair(std::integral_constant<int, (NPAIR > 2 ? 2 : 0)>());
+            if constexpr (NPAIR > 3) pair(std::integral_constant<int, (NPAIR > 3 ? 3 : 0)>());
+        }
     }
     }
 
@@ -472,8 +544,10 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_pair(
         for (int k = 0; k < NPAIR; ++k)
             if (2 * k < np) {
 #pragma unroll
-                for (int h = 0; h < 4; ++h)
-                    if (2 * k + wpar < NP) stg[((h * NP + 2 * k + wpar) * 8 + wrow) * 68 + wf] = sc[k][x][h] * a.scale;
+                for (int h = 0; h < 4; ++h) {
+                    const float v = HALF ? swap16_add(sc[2 * k % NV][x][h], 2 * k + 1 < NP ? sc[(2 * k + 1) % NV][x][h] : 0.f) : sc[k][x][h];
+                    if (2 * k + wpar < NP) stg[((h * NP + 2 * k + wpar) * 8 + wrow) * 68 + wf] = v * a.scale;
+                }
             }
         __syncthreads();
         if (wp < np) {
