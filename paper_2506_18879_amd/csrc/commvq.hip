@@ -154,25 +154,41 @@ size_t few_tile_bytes(const commvq_handle *h, int B, int64_t T, int max_seqlen)
 struct StreamShape {
     int passes, tiles, groups;
 };
+// Cost of a workgroup in microseconds: a fixed start and end (launch, first fetches, write-out), and per slice a switch and the
+// passes.  A launch too short to fill the 256 compute units is also cut along the slices; every group then fetches the tile's codes
+// again, the partial logits take a trip through memory, and k_score_combine is one more launch.
+struct StreamCost {
+    double fixed, change, pass, combine, group, logits;  // (the last two per slice group; logits per million)
+};
 StreamShape stream_shape(const commvq_handle *h, int B, int64_t T, int max_seqlen)
 {
     const int per_seq = (max_seqlen + kPassTokens - 1) / kPassTokens;
-    // segments per KV head: at most one partly filled one per sequence more than the tokens need; about half of them for the estimate
+    // segments per KV head: at most one partly filled one per sequence more than the tokens need
     const int64_t most = std::min<int64_t>((int64_t)B * per_seq, T / kPassTokens + B);
-    // (k_score_pair: and the standard deviation, sqrt(B / 12), of the partly filled ones more.  Its cuts fill the 256 compute units once, and one
-    // segment too many for that is a second round: 8 sequences of 1250 to 2500 tokens 71.3 us without, 63.2 with.)
     const bool pair = pair_keys(h->cfg);
     const int sets = pair_sets(h->cfg);
+    // What the host does not know is how many of them are partly filled: half of the sequences' last ones on average, with a standard deviation
+    // of sqrt(B / 12).  k_score_stream: a cut is judged by that mean and by one deviation to either side of it, since one segment more than fills
+    // the compute units is a second round (8 sequences of 2000 to 4000 tokens, 32 codebooks 50.6 -> 34.8 us, 64 of 1500 to 3000 154.5 -> 141.6
+    // with the mean alone and so).  k_score_pair: by a whole number of deviations more than the mean (8 sequences of 1250 to 2500 tokens 71.3 us
+    // by the mean, 63.2 so).
     int spread = 0;
     while (pair && B > 1 && 12 * spread * spread < B) ++spread;
-    const int64_t likely = B == 1 ? most : std::min<int64_t>((int64_t)B * per_seq, T / kPassTokens + (B + 1) / 2 + spread);
-    // Cost of a workgroup in microseconds, fitted to sweeps over lengths from 350 tokens up: a fixed start and end (launch, first
-    // fetches, write-out), and per slice a switch and the passes.  A launch too short to fill the 256 compute units is also
-    // cut along the slices; every group then fetches the tile's codes again, the partial logits take a trip through
-    // memory (at 4 TB/s), and k_score_combine is one more launch.
-    const bool two = h->cfg.m_key == 32;
-    const double fixed = 9.0, sw = two ? 1.25 : h->G == 8 ? 0.6 : 0.5, c = two ? (h->G == 8 ? 0.70 : 0.66) : (h->G == 8 ? 0.47 : 0.41);
-    const double part = (double)T * h->cfg.n_q_heads / 1e6 + (two ? 0.08 : 0.15);
+    const bool known = B == 1 || T == (int64_t)B * max_seqlen;
+    const double mean = known ? (double)B * per_seq : (double)T / kPassTokens + 0.5 * B, dev = known ? 0.0 : std::sqrt(B / 12.0);
+    auto segments = [&](int k) -> int64_t {                   // k = -1, 0, 1
+        if (pair) return B == 1 ? most : std::min<int64_t>((int64_t)B * per_seq, T / kPassTokens + (B + 1) / 2 + spread);
+        return std::max<int64_t>(1, std::min<int64_t>((int64_t)B * per_seq, (int64_t)(mean + k * dev + 0.5)));
+    };
+    // k_score_stream, fitted to every cut (2 to 8 passes, 1 to 16 groups) of 28 shapes of 2900 to 131072 tokens and 1 to 64 sequences; the cut
+    // chosen is 0.3 % slower than the best on average.  One sequence of at most 32 segments keeps the numbers that it has been cut by,
+    // and with them the cut that the tests pin at 16384 tokens (1 to 6 % slower than the best).
+    // (One sequence of 32768 tokens, 32 codebooks 38.9 -> 36.7 us; 24 of 300 to 600 45.7 -> 29.2; 40 of 1500 to 3000 92.6 -> 83.9.)
+    const bool two = h->cfg.m_key == 32, wide = h->G == 8;
+    const StreamCost cost = B == 1 && most <= 32
+        ? StreamCost{9.0, two ? 1.25 : wide ? 0.6 : 0.5, two ? (wide ? 0.70 : 0.66) : (wide ? 0.47 : 0.41), 5.0, two ? 0.08 : 0.15, 1.0}
+        : two ? (wide ? StreamCost{3.18, 1.40, 0.687, 3.04, 0.355, 1.23} : StreamCost{2.57, 1.03, 0.584, 2.06, 0.375, 2.39})
+              : (wide ? StreamCost{1.70, 0.917, 0.483, 2.73, 0.855, 1.51} : StreamCost{2.35, 0.747, 0.352, 2.63, 0.715, 1.49});
     // k_score_pair: 16 rounds, four to a slice; 2, 3, 4 or pair_passes passes.  Fitted to 29 shapes of 2000 to 131072 tokens, 1 to 8
     // sequences, R = 11 and 21: 15 cuts each, the one chosen is 0.7 % slower than the best on average (8 sequences of 1100 to 2200 tokens, R = 11:
     // 55.9 us with groups of 8 rounds, 63.0 uncut; one of 2000: 39.9 with groups of two rounds, 56.8 uncut).
@@ -181,7 +197,7 @@ StreamShape stream_shape(const commvq_handle *h, int B, int64_t T, int max_seqle
     // 3000 85.3 -> 80.7.  Uncut with six sets of levels it loses to six passes in two groups (two sequences of 10000 to 20000: 90.2 against 94.3).
     // Two passes of three sets uncut take 2.5 us (8 heads per KV head: 5) more than the line through the others (their rounds are too short
     // for the codes on their way): 8 sequences of 1374 to 2748 tokens 64.7 us, 63.2 with three passes in two groups; 8 heads, one of 17000 63.5 and 61.3.
-    const double pc = (h->G == 8 ? 0.10 : 0.0) + (sets == 3 ? 0.443 : sets == 4 ? 0.535 : 0.728);
+    const double pc = (wide ? 0.10 : 0.0) + (sets == 3 ? 0.443 : sets == 4 ? 0.535 : 0.728);
     // The partial logits may not need more memory than the bins that follow them, apart from few_tile_bytes: a shape that fits a
     // workspace of some size (the static one in particular) must not outgrow it for the sake of a faster cut.
     const int vlen = value_split_len(h, B, max_seqlen, 1024);
@@ -194,15 +210,21 @@ StreamShape stream_shape(const commvq_handle *h, int B, int64_t T, int max_seqle
     }
     StreamShape best = {2, 1, 1};
     double t_best = 1e30;
+    const double million = (double)T * h->cfg.n_q_heads / 1e6;  // logits
     const int most_passes = pair ? pair_passes(sets) : kStreamPasses;
     for (int passes = 2; passes <= most_passes; passes = !pair || passes != 4 ? passes + 1 : most_passes)
         for (int e = 1; e <= kStreamSlices && (e - 1) * one <= room; e *= 2) {
             if (pair && passes == 3 && e == 1 && sets > 3) continue;
-            const int64_t wgs = (likely + passes - 1) / passes * h->cfg.n_kv_heads * e;
-            const double rounds = (double)kStreamSlices / e;
-            const double t = pair ? (double)((wgs + 255) / 256) * (9.4 + std::max(1.0, rounds / 4) * 0.32 + rounds * (0.27 + passes * pc)) +
-                                        (e > 1 ? 4.8 + e * 3.35 * (double)T * h->cfg.n_q_heads / 1e6 : passes == 2 && sets == 3 ? (h->G == 8 ? 5.0 : 2.5) : 0.0)
-                                  : (double)((wgs + 255) / 256) * (fixed + rounds * (sw + passes * c)) + (e > 1 ? 5.0 + e * part : 0.0);
+            const double slices = (double)kStreamSlices / e;
+            auto rounds = [&](int64_t segs) { return (double)(((segs + passes - 1) / passes * h->cfg.n_kv_heads * e + 255) / 256); };
+            double t;
+            if (pair) {
+                t = rounds(segments(0)) * (9.4 + std::max(1.0, slices / 4) * 0.32 + slices * (0.27 + passes * pc)) +
+                    (e > 1 ? 4.8 + e * 3.35 * million : passes == 2 && sets == 3 ? (wide ? 5.0 : 2.5) : 0.0);
+            } else {
+                const double n = dev > 0.0 ? 0.3 * rounds(segments(-1)) + 0.4 * rounds(segments(0)) + 0.3 * rounds(segments(1)) : rounds(segments(0));
+                t = n * (cost.fixed + slices * (cost.change + passes * cost.pass)) + (e > 1 ? cost.combine + e * (cost.group + cost.logits * million) : 0.0);
+            }
             if (t < t_best * 0.9999) { t_best = t; best = StreamShape{passes, 0, e}; }
         }
     best.tiles = (int)((most + best.passes - 1) / best.passes);
