@@ -1829,123 +1829,127 @@ struct OutArgs {
 // Workgroup = (sequence, KV head, chunk of codebook rows): sums the chunk's bins over the
 // context splits (fixed point -> fp32 with each split's unit), then multiplies them with the
 // chunk's value-codebook rows (Eq. optimized_v).
-template <int G, bool BF16>
-__global__ __launch_bounds__(kOutThreads) void k_out(OutArgs a)
+// Bound by latency: bins, units and (1024 threads) codebook rows are asked for together and ahead of the sequence's length.  Launches
+// of at most a workgroup per compute unit take 1024 threads, so that 128 splits' bins are one round of loads and not four: 9.8 -> 6.5 us at
+// 128K tokens, whole calls of the 8B layer 128K 106.6 -> 103.4 us, 9001 tokens 43.8 -> 42.1, 2048 code bits of 36000 81.9 -> 79.4.
+// Larger launches have a second workgroup to fill such a wait: 3 x 9000 tokens, 1024 bits (384 workgroups) 62.3 -> 60.5 with 256
+// threads, 63.0 with 1024; 2048 bits (768) 74.0 -> 72.5, 76.5; 3 x 43000 185.7 -> 183.3, with 1024 a hundredth slower than before.
+template <int G, bool BF16, int NT>
+__global__ __launch_bounds__(NT) void k_out(OutArgs a)
 {
+    static_assert(kOutRows == 64, "a lane per row");
+    constexpr int NW = NT / 64;                                     // wavefronts: each takes every NW-th split
+    constexpr int HG = NT == 1024 && G >= 4 ? 4 : 1, RG = NW / HG;  // product: HG groups of heads, RG groups of rows
+    constexpr int HPG = G / HG, NCR = kOutRows / RG;                // heads and codebook rows of a wavefront
+    constexpr int AT = G <= 4 || NT == 1024 ? 8 : 4;                // splits whose bins are in flight
+    constexpr bool EARLY = BF16 && NT == 1024;                      // codebook rows asked for ahead of the bins' sums
     __shared__ float wsum[G][kOutRows];
-    __shared__ float red[kOutThreads / 64][G][kD];
-    __shared__ float scl[G][kMaxValueSplits];                       // value of one fixed-point unit, per head and split
-    __shared__ float part[kOutThreads / kOutRows][kOutRows][G];     // sums over every fourth split
+    __shared__ float red[RG][G][kD];
+    __shared__ __attribute__((aligned(16))) float part[NW][kOutRows][G];
     int id = blockIdx.x;
     const int chunk = id % a.nchunk;
     id /= a.nchunk;
     const int g = id % a.Hkv;
     const int b = id / a.Hkv;
-    const int L = a.cu[b + 1] - a.cu[b];
-    const int nvs = min((L + a.vsplit_len - 1) / a.vsplit_len, a.nvsplit);
     const int MK = a.Mv * kK;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    // bins: [split][K][Mv][G]; the chunk's 64 rows are kOutRows / Mv consecutive codewords of every codebook, one
-    // contiguous run of 64 * G bins per split; local row r = (codeword - first) * Mv + codebook.  A thread reads
-    // the G bins of its row with one vector load and takes every fourth split.
-    constexpr int NSG = kOutThreads / kOutRows;
-    constexpr int NCR = kOutRows / (kOutThreads / 64);  // codebook rows per wavefront
-    const int r1 = tid % kOutRows, sg = tid / kOutRows;
-    const unsigned *src = a.bins + (size_t)(b * a.Hkv + g) * a.nvsplit * G * MK + (size_t)(chunk * kOutRows + r1) * G;
-    auto load_bins = [&](int v, unsigned(&bv)[G]) {
-        const unsigned *pv = src + (size_t)v * G * MK;
-        if (G >= 4) {
+    // bins: [split][rows][G]: one contiguous run of 64 * G bins per split, the G bins of its row in one load per lane.  The splits
+    // that the longest sequence has are asked for before this one's length is known.
+    const unsigned *src = a.bins + (size_t)(b * a.Hkv + g) * a.nvsplit * G * MK + (size_t)(chunk * kOutRows + lane) * G;
+    const float *units = a.vscale + ((size_t)b * a.Hq + (size_t)g * G + lane % G) * a.nvsplit;
+    unsigned bv[AT][G];
+    float unit = 0.f;                                               // lane k G + h: of head h in the k-th of the splits
+    auto request = [&](int v0) __attribute__((always_inline)) {
+        unit = units[min(v0 + lane / G % AT * NW, a.nvsplit - 1)];
 #pragma unroll
-            for (int q4 = 0; q4 < G / 4; ++q4) {
-                const uint4 t4 = reinterpret_cast<const uint4 *>(pv)[q4];
-                bv[4 * q4 + 0] = t4.x; bv[4 * q4 + 1 < G ? 4 * q4 + 1 : 0] = t4.y; bv[4 * q4 + 2 < G ? 4 * q4 + 2 : 0] = t4.z; bv[4 * q4 + 3 < G ? 4 * q4 + 3 : 0] = t4.w;
+        for (int k = 0; k < AT; ++k) {
+            if (v0 + k * NW >= a.nvsplit) break;
+            const unsigned *pv = src + (size_t)(v0 + k * NW) * G * MK;
+            if (G >= 4) {
+#pragma unroll
+                for (int q4 = 0; q4 < G / 4; ++q4) {
+                    const uint4 t4 = reinterpret_cast<const uint4 *>(pv)[q4];
+                    bv[k][4 * q4] = t4.x; bv[k][(4 * q4 + 1) % G] = t4.y; bv[k][(4 * q4 + 2) % G] = t4.z; bv[k][(4 * q4 + 3) % G] = t4.w;
+                }
+            } else if (G == 2) {
+                const uint2 t2 = *reinterpret_cast<const uint2 *>(pv);
+                bv[k][0] = t2.x; bv[k][G - 1] = t2.y;
+            } else {
+                bv[k][0] = pv[0];
             }
-        } else if (G == 2) {
-            const uint2 t2 = *reinterpret_cast<const uint2 *>(pv);
-            bv[0] = t2.x; bv[G - 1] = t2.y;
-        } else {
-            bv[0] = pv[0];
         }
     };
-    // a wavefront takes a quarter of the codebooks and the chunk's codewords of each: runs of consecutive rows
-    const int cpc = kOutRows / a.Mv, mpw = a.Mv / (kOutThreads / 64);  // codewords per chunk, codebooks per wavefront
-    auto load_row = [&](int i) -> float2 {
-        const int m = wave * mpw + i / cpc, cl = i % cpc;
-        const size_t row = (size_t)vbits_code_bit(chunk * kOutRows + cl * a.Mv + m) * a.Hkv + g;
+    const int rg = wave % RG, hg = wave / RG;
+    auto load_row = [&](int i) __attribute__((always_inline)) -> float2 {
+        const size_t row = (size_t)vbits_code_bit(chunk * kOutRows + rg * NCR + i) * a.Hkv + g;
         if (BF16) {
             const unsigned v = static_cast<const unsigned *>(a.val_cb)[row * kJ + lane];
-            return make_float2(bf16_lo(v), bf16_hi(v));
+            return make_float2(__builtin_bit_cast(float, v), 0.f);
         }
         return static_cast<const float2 *>(a.val_cb)[row * kJ + lane];
     };
-    for (int x = tid; x < G * nvs; x += kOutThreads)
-        scl[x / nvs][x % nvs] = a.vscale[((size_t)b * a.Hq + (size_t)g * G + x / nvs) * a.nvsplit + x % nvs];
-    __syncthreads();
-    {
-        float s[G];
+    request(wave);
+    float2 rows[NCR];
+    if (EARLY) {
 #pragma unroll
-        for (int hh = 0; hh < G; ++hh) s[hh] = 0.f;
-        // eight splits' bins in flight where a thread has that many and the registers allow, else four (same order of
-        // additions either way)
-        int v = sg;
-        if (G <= 4 && nvs >= 8 * NSG) {
-            for (; v + 7 * NSG < nvs; v += 8 * NSG) {
-                unsigned bv[8][G];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) load_bins(v + k * NSG, bv[k]);
-#pragma unroll
-                for (int k = 0; k < 8; ++k)
-#pragma unroll
-                    for (int hh = 0; hh < G; ++hh) s[hh] += (float)bv[k][hh] * scl[hh][v + k * NSG];
-            }
-        }
-#pragma unroll 4
-        for (; v < nvs; v += NSG) {
-            unsigned bv[G];
-            load_bins(v, bv);
-#pragma unroll
-            for (int hh = 0; hh < G; ++hh) s[hh] += (float)bv[hh] * scl[hh][v];
-        }
-#pragma unroll
-        for (int hh = 0; hh < G; ++hh) part[sg][r1][hh] = s[hh];
+        for (int i = 0; i < NCR; ++i) rows[i] = load_row(i);
     }
+    __builtin_amdgcn_sched_barrier(0);
+    const int L = a.cu[b + 1] - a.cu[b];
+    const int nvs = min((L + a.vsplit_len - 1) / a.vsplit_len, a.nvsplit);
+    float s[G];
+#pragma unroll
+    for (int hh = 0; hh < G; ++hh) s[hh] = 0.f;
+    for (int v = wave; v < nvs; v += AT * NW) {
+        if (v != wave) request(v);
+#pragma unroll
+        for (int k = 0; k < AT; ++k) {
+            if (v + k * NW >= nvs) break;
+#pragma unroll
+            for (int hh = 0; hh < G; ++hh)
+                s[hh] += (float)bv[k][hh] * __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, unit), k * G + hh));
+        }
+    }
+#pragma unroll
+    for (int hh = 0; hh < G; ++hh) part[wave][lane][hh] = s[hh];
     __syncthreads();
-    for (int x = tid; x < G * kOutRows; x += kOutThreads) {
+    for (int x = tid; x < G * kOutRows; x += NT) {
         const int hh = x % G, r = x / G;
-        float s = 0.f;
+        float t = 0.f;
 #pragma unroll
-        for (int q = 0; q < NSG; ++q) s += part[q][r][hh];
-        wsum[hh][r] = s;
+        for (int q = 0; q < NW; ++q) t += part[q][r][hh];
+        wsum[hh][r] = t;
     }
     __syncthreads();
-    float2 acc[G];
+    // (the wavefront's row loads are requested together)
+    if (!EARLY) {
 #pragma unroll
-    for (int hh = 0; hh < G; ++hh) acc[hh] = make_float2(0.f, 0.f);
-    // (unrolled: the wavefront's 16 row loads are requested together)
+        for (int i = 0; i < NCR; ++i) rows[i] = load_row(i);
+    }
+    float2 acc[HPG];
+#pragma unroll
+    for (int hh = 0; hh < HPG; ++hh) acc[hh] = make_float2(0.f, 0.f);
 #pragma unroll
     for (int i = 0; i < NCR; ++i) {
-        const int m = wave * mpw + i / cpc, cl = i % cpc;
-        const int r = cl * a.Mv + m;
-        const float2 c = load_row(i);
+        const unsigned u = __builtin_bit_cast(unsigned, rows[i].x);
+        const float2 c = BF16 ? make_float2(bf16_lo(u), bf16_hi(u)) : rows[i];
 #pragma unroll
-        for (int hh = 0; hh < G; ++hh) {
-            const float w = wsum[hh][r];
+        for (int hh = 0; hh < HPG; ++hh) {
+            const float w = wsum[hg * HPG + hh][rg * NCR + i];
             acc[hh].x += w * c.x;
             acc[hh].y += w * c.y;
         }
     }
 #pragma unroll
-    for (int hh = 0; hh < G; ++hh) {
-        red[wave][hh][2 * lane] = acc[hh].x;
-        red[wave][hh][2 * lane + 1] = acc[hh].y;
-    }
+    for (int hh = 0; hh < HPG; ++hh) *reinterpret_cast<float2 *>(&red[rg][hg * HPG + hh][2 * lane]) = acc[hh];
     __syncthreads();
-    for (int x = tid; x < G * kD; x += kOutThreads) {
+    for (int x = tid; x < G * kD; x += NT) {
         const int hh = x / kD, e = x % kD;
-        float s = 0.f;
-        for (int w = 0; w < kOutThreads / 64; ++w) s += red[w][hh][e];
-        a.partial[(((size_t)b * a.Hq + (size_t)g * G + hh) * a.nchunk + chunk) * kD + e] = s;
+        float t = 0.f;
+#pragma unroll
+        for (int w = 0; w < RG; ++w) t += red[w][hh][e];
+        a.partial[(((size_t)b * a.Hq + (size_t)g * G + hh) * a.nchunk + chunk) * kD + e] = t;
     }
 }
 
@@ -2224,8 +2228,13 @@ hipError_t launch_score_m(const ScoreArgs &a, int G, bool bf16, int batch, hipSt
 template <int G>
 hipError_t launch_out_g(const OutArgs &a, bool bf16, int grid, hipStream_t s)
 {
-    if (bf16) hipLaunchKernelGGL((k_out<G, true>), dim3(grid), dim3(kOutThreads), 0, s, a);
-    else hipLaunchKernelGGL((k_out<G, false>), dim3(grid), dim3(kOutThreads), 0, s, a);
+    if (grid <= 256) {
+        if (bf16) hipLaunchKernelGGL((k_out<G, true, 1024>), dim3(grid), dim3(1024), 0, s, a);
+        else hipLaunchKernelGGL((k_out<G, false, 1024>), dim3(grid), dim3(1024), 0, s, a);
+    } else {
+        if (bf16) hipLaunchKernelGGL((k_out<G, true, kOutThreads>), dim3(grid), dim3(kOutThreads), 0, s, a);
+        else hipLaunchKernelGGL((k_out<G, false, kOutThreads>), dim3(grid), dim3(kOutThreads), 0, s, a);
+    }
     return hipGetLastError();
 }
 

@@ -27,7 +27,6 @@ constexpr int kScoreMinWgs = 2048;   // row-gather score kernel: tiles are halve
 constexpr int kScoreThreads = 256;
 constexpr int kFewTokens = kScoreThreads / 16;  // tokens of a workgroup of k_score_few, the smallest tile of the row-gather kernels
 constexpr int kOutThreads = 256;
-constexpr int kMaxValueSplits = 256;  // value_splits never exceeds 256 / (batch * KV heads), at least 1
 constexpr int kOutRows = 64;    // codebook rows per k_out workgroup
 constexpr int kOutMfmaRows = 256;   // codebook rows per k_out_mfma workgroup (batched output stage)
 constexpr int kOutMfmaMinRows = 16;  // batch * (query heads per KV head) from which the batched output kernel is used
