@@ -125,7 +125,9 @@ __device__ __forceinline__ float swap32_add(float x, float y)
 // one fp32 head of 4096 tokens 23.9 -> 19.8 us; 8B 2-bit 1237 tokens 31.1 -> 24.8, 32K 69.8 -> 56.9, 8 x 8K..64K 483 -> 469, 64 x
 // 512..1024 136 -> 118; 8B 1-bit 128K 92.8 -> 88.6, position-free 39.5 -> 36.0; 70B 4 x 128K 559 -> 553.  Not kept: equal chunks of the whole batch
 // instead of ranges per sequence (more products: 8 x 8K..64K 456 -> 480), rows touched early to have them in L2 (no change, with
-// codebooks that were there from the call before).  Eight heads with 8 codebooks spill 12 (1024 threads) or 13 registers.
+// codebooks that were there from the call before).  Eight heads with 8 codebooks take the k-steps in
+// a loop: unrolled, the sums move from register to register and 9 of them spill (4 x 128K 498.5 -> 494.7 us, 6 x 15000..30000 152.8 -> 150.2, 40 x
+// 1500..3000 184.1 -> 179.5).
 template <int G, int CB, int S, int NCS, int NT, bool BF16>
 __global__ __launch_bounds__(NT, S > 1 ? 2 : 4) void k_values(const ValuesArgs a)
 {
@@ -476,7 +478,7 @@ __global__ __launch_bounds__(NT, S > 1 ? 2 : 4) void k_values(const ValuesArgs a
                 for (int x = 0; x < NX; ++x)
 #pragma unroll
                     for (int t = 0; t < NCT; ++t) acc[s][x][t] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
+#pragma unroll NX == 2 && CB == 8 && S == 1 ? 1 : KS
             for (int j = 0; j < KS; ++j) {
                 if (RB == 2 && j + 1 < KS) load_rows(j + 1, R[(j + 1) % RB]);
                 bf16x8_t A[S][NX];
