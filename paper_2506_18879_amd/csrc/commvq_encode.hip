@@ -861,19 +861,25 @@ __global__ __launch_bounds__(kManyThreads, 2) void k_encode_many(const void *__r
 // Four wavefronts, one per SIMD: 4 / RS sets of 32 tokens.  The RS wavefronts of a set share the rows a of the scan (and
 // compute only their part of P); residual, split and Q are each wavefront's own: handing them round through LDS, with
 // eight wavefronts and the residuals split between two, cost more than it saved (8.9 us a level at RS = 1's sizes).
-// A level takes 8.2 us with RS = 1 (128 tokens), 6.1 (2) and 5.1 (4), of which a row of the scan is 50 ns: two matrix
+// A level takes 7.9 us with RS = 1 (128 tokens), 6.0 (2) and 5.1 (4), of which a row of the scan is 50 ns: two matrix
 // instructions (64 clk) and 21 vector ones (90 clk) that hide in each other only where they alternate in the program, so
-// the order is fixed below (left to the compiler: 90 ns).  32768 vectors, 21 levels: 179 us, 8192 vectors 113; with the
+// the order is fixed below (left to the compiler: 90 ns).  32768 vectors, 21 levels: 167 us, 8192 vectors 109; with the
 // scan's sums on the vector unit and cross terms read per 16 tokens 258 and 165.
 //   32 x 32 operands: lane (n, h) supplies row / token n and elements 8 h .. + 7 of a chunk of 16 (scan: 4 h .. + 3 of 8)
 //   32 x 32 result  : lane (n, h) receives, in register i, row 8 (i / 4) + 4 h + i % 4 for token n
-// A level's tables do not depend on the residual: they are fetched into registers one level ahead.
+// A level's tables do not depend on the residual: rows, cross terms and norms of the next level travel from memory straight into the other of
+// two buffers while this one is searched; what is made of them (i C, the terms' parts) takes the place of the last level's.  Through registers
+// they were 33 of 256 for the whole level, 16 of which spilled, and one LDS write more: keys at 21 levels and values at 16 of 4000
+// tokens 247.6 -> 238.7 us, 300 tokens 137.6 -> 132.8; keys at 11 levels, 1000 tokens 93.7 -> 90.7, 2500 160.2 -> 154.4.  (Addresses made anew
+// at every level instead of held: 244.1, 139.9, 94.7, 160.9.  512 registers: the compiler moves half of them to and fro, 314.)
 constexpr int kEpThreads = 256;
-constexpr int kEpRows = 0;                          // [C | i C][64] rows of 256 bytes, piece x of row t in slot x xor (t mod 16)
-constexpr int kEpParts = 2 * 64 * 256;              // [64 a][64 b] x0, x1, x2, 0 of the cross terms, 8 bytes each
-constexpr int kEpCross = kEpParts + 4096 * 8;       // [64 a][64 b] cross terms, float4 x of row a in slot x xor (a mod 16)
-constexpr int kEpNorms = kEpCross + 4096 * 4;       // [64]
-constexpr int kEpMin = kEpNorms + 64 * 4;           // [4 wavefronts][32 tokens] minimum, its row and that row's U
+constexpr int kEpImage = 64 * 256;                  // C and the cross terms, of two levels in turn: 64 rows of 256 bytes, 16-byte piece x of row t in
+constexpr int kEpRows = 0;                          // slot x xor (t mod 16)
+constexpr int kEpTurned = 2 * kEpImage;             // i C, likewise
+constexpr int kEpParts = kEpTurned + kEpImage;      // [64 a][64 b] x0, x1, x2, 0 of the cross terms, 8 bytes each
+constexpr int kEpCross = kEpParts + 4096 * 8;
+constexpr int kEpNorms = kEpCross + 2 * kEpImage;   // [2][64]
+constexpr int kEpMin = kEpNorms + 2 * 64 * 4;           // [4 wavefronts][32 tokens] minimum, its row and that row's U
 constexpr int kEpChosen = kEpMin + 4 * 32 * 16;     // [tokens][32 levels][2]
 constexpr int ep_lds(int rs) { return kEpChosen + 128 / rs * 64; }
 static_assert(ep_lds(1) <= 163840, "LDS of a compute unit");
@@ -886,7 +892,6 @@ __global__ __launch_bounds__(kEpThreads, 2) void k_encode_pairs(const void *__re
 {
     extern __shared__ __attribute__((aligned(16))) uint4 ep_mem[];
     char *lds = reinterpret_cast<char *>(ep_mem);
-    float *nrm = reinterpret_cast<float *>(lds + kEpNorms);
     uint8_t *chosen = reinterpret_cast<uint8_t *>(lds + kEpChosen);
     constexpr int kSets = 4 / RS, kTiles = RS == 1 ? 2 : 1, kPairs = 32 / RS;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -894,10 +899,8 @@ __global__ __launch_bounds__(kEpThreads, 2) void k_encode_pairs(const void *__re
     const int set = wave % kSets, rs = wave / kSets;
     const int a0 = 64 / RS * rs;  // the wavefront's first row a; its tile of P begins at a0 & 32
     const int g = blockIdx.x % a.Hkv;
-    const int tl = set * 32 + n;
-    const long long tok = (long long)(blockIdx.x / a.Hkv) * (32 * kSets) + tl;
-    const size_t tokc = (size_t)(tok < n_tokens ? tok : n_tokens - 1);
     float res[8][8];  // dimensions 16 kc + 8 h .. + 7
+    const size_t tokc = (size_t)min((long long)(blockIdx.x / a.Hkv) * (32 * kSets) + set * 32 + n, (long long)n_tokens - 1);
 #pragma unroll
     for (int kc = 0; kc < 8; ++kc) {
         const size_t i = (tokc * a.Hkv + g) * kD + 16 * kc + 8 * h;
@@ -911,31 +914,29 @@ __global__ __launch_bounds__(kEpThreads, 2) void k_encode_pairs(const void *__re
             for (int e = 0; e < 8; ++e) res[kc][e] = static_cast<const float *>(keys)[i + e];
         }
     }
-    uint4 prow[4];
-    float4 pcross[4];
-    float pnorm = 0.f;
     auto fetch_level = [&](int l) {
         const size_t level = (size_t)g * a.levels + l;
 #pragma unroll
         for (int x = 0; x < 4; ++x) {
-            prow[x] = cb[level * 64 * 16 + x * 256 + tid];
-            pcross[x] = reinterpret_cast<const float4 *>(cross + level * 4096)[x * 256 + tid];
+            const int p0 = (wave * 4 + x) * 64, p = p0 + lane, t = p >> 4, at = (t * 16 + ((p ^ t) & 15)) * 16;
+            lds_dma16(cb + level * 64 * 16, (unsigned)at, (unsigned)(kEpRows + (l & 1) * kEpImage + p0 * 16));
+            lds_dma16(cross + level * 4096, (unsigned)at, (unsigned)(kEpCross + (l & 1) * kEpImage + p0 * 16));
         }
-        if (tid < 64) pnorm = norms[level * 64 + tid];
+        if (wave == 0 && fresh_lane() < 16) lds_dma16(norms + level * 64, (unsigned)fresh_lane() * 16u, (unsigned)(kEpNorms + (l & 1) * 256));
     };
-    auto park_level = [&]() {
+    auto park_level = [&](int l) {
+        const char *rows = lds + kEpRows + (l & 1) * kEpImage, *terms = lds + kEpCross + (l & 1) * kEpImage;
 #pragma unroll
         for (int x = 0; x < 4; ++x) {
-            const int p = x * 256 + tid, t = p >> 4, slot = (p ^ t) & 15;  // row t, piece / float4 p mod 16
-            uint4 *dst = reinterpret_cast<uint4 *>(lds + kEpRows + t * 256 + slot * 16);
-            dst[0] = prow[x];
-            const unsigned w[4] = {prow[x].x, prow[x].y, prow[x].z, prow[x].w};
+            const int p = x * 256 + tid, t = p >> 4;
+            const uint4 row = *reinterpret_cast<const uint4 *>(rows + p * 16);
+            const unsigned w[4] = {row.x, row.y, row.z, row.w};
             unsigned r[4];  // (x, y) -> (-y, x)
 #pragma unroll
             for (int e = 0; e < 4; ++e) r[e] = __builtin_amdgcn_alignbit(w[e], w[e], 16) ^ 0x8000u;
-            dst[64 * 16] = make_uint4(r[0], r[1], r[2], r[3]);
-            *reinterpret_cast<float4 *>(lds + kEpCross + t * 256 + slot * 16) = pcross[x];
-            const float xv[4] = {pcross[x].x, pcross[x].y, pcross[x].z, pcross[x].w};
+            *reinterpret_cast<uint4 *>(lds + kEpTurned + p * 16) = make_uint4(r[0], r[1], r[2], r[3]);
+            const float4 term = *reinterpret_cast<const float4 *>(terms + (t * 16 + ((p ^ t) & 15)) * 16);
+            const float xv[4] = {term.x, term.y, term.z, term.w};
             unsigned pr[8];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -950,16 +951,19 @@ __global__ __launch_bounds__(kEpThreads, 2) void k_encode_pairs(const void *__re
             pd[0] = make_uint4(pr[0], pr[1], pr[2], pr[3]);
             pd[1] = make_uint4(pr[4], pr[5], pr[6], pr[7]);
         }
-        if (tid < 64) nrm[tid] = pnorm;
     };
     // three ones along k in the lanes of the lower half, nothing in the upper: every cross term enters once
     const uint2_t ones_bits = h ? uint2_t{0u, 0u} : uint2_t{0x3f803f80u, 0x3f80u};
     const shortx4_t ones = __builtin_bit_cast(shortx4_t, ones_bits);
     fetch_level(0);
     for (int l = 0; l < a.levels; ++l) {
-        __syncthreads();  // the previous level's tables are no longer read
-        park_level();
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's part of the level has landed
+        __syncthreads();                                   // ... and everybody's, and the previous level's tables are no longer read
+        park_level(l);
+        if (l + 1 < a.levels) fetch_level(l + 1);
         __syncthreads();
+        const char *const img = lds + kEpRows + (l & 1) * kEpImage, *const terms = lds + kEpCross + (l & 1) * kEpImage;
+        const float *const nrm = reinterpret_cast<const float *>(lds + kEpNorms + (l & 1) * 256);
         floatx16_t P[kTiles], V[2];
 #pragma unroll
         for (int t = 0; t < kTiles; ++t) P[t] = floatx16_t{0.f};
@@ -981,8 +985,8 @@ __global__ __launch_bounds__(kEpThreads, 2) void k_encode_pairs(const void *__re
             bf16x8_t A[kTiles + 2];
 #pragma unroll
             for (int t = 0; t < kTiles + 2; ++t) {
-                const int row = (t < kTiles ? (RS == 1 ? 32 * t : (a0 & 32)) : 64 + 32 * (t - kTiles)) + n;
-                const uint4 pc = *reinterpret_cast<const uint4 *>(lds + kEpRows + row * 256 + ((2 * kc + h) ^ (n & 15)) * 16);
+                const int row = (t < kTiles ? (RS == 1 ? 32 * t : (a0 & 32)) : 32 * (t - kTiles)) + n;
+                const uint4 pc = *reinterpret_cast<const uint4 *>((t < kTiles ? img : lds + kEpTurned) + row * 256 + ((2 * kc + h) ^ (n & 15)) * 16);
                 const uint4_t pv = {pc.x, pc.y, pc.z, pc.w};
                 A[t] = __builtin_bit_cast(bf16x8_t, pv);
             }
@@ -994,7 +998,6 @@ __global__ __launch_bounds__(kEpThreads, 2) void k_encode_pairs(const void *__re
                     d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[t], __builtin_bit_cast(bf16x8_t, part[s3]), d, 0, 0, 0);
                 }
         }
-        if (l + 1 < a.levels) fetch_level(l + 1);
         float U[kPairs];  // of row a0 + 8 (i / 4) + 4 h + i % 4
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
@@ -1080,7 +1083,7 @@ __global__ __launch_bounds__(kEpThreads, 2) void k_encode_pairs(const void *__re
             ubest = m.z;
         }
         // stage two: the partner b of row ca, the lowest of those whose whole cost is the least.  (V + X alone would tell apart
-        // costs that are equal in fp32, and give a vector another code than k_encode_one does; it would save 3 of 179 us.)
+        // costs that are equal in fp32, and give a vector another code than k_encode_one does; it would save 3 us of 179.)
         float bestb = INFINITY;
         int cb2 = 0;
 #pragma unroll
@@ -1088,7 +1091,7 @@ __global__ __launch_bounds__(kEpThreads, 2) void k_encode_pairs(const void *__re
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int b0 = 32 * t + 8 * q + 4 * h;
-                const float4 x4 = *reinterpret_cast<const float4 *>(lds + kEpCross + ca * 256 + (((b0 >> 2) ^ ca) & 15) * 16);
+                const float4 x4 = *reinterpret_cast<const float4 *>(terms + ca * 256 + (((b0 >> 2) ^ ca) & 15) * 16);
                 const float xv[4] = {x4.x, x4.y, x4.z, x4.w};
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
@@ -1097,13 +1100,13 @@ __global__ __launch_bounds__(kEpThreads, 2) void k_encode_pairs(const void *__re
                 }
             }
         min2_halves(bestb, cb2);
-        if (h == 0 && rs == 0) { chosen[(tl * 32 + l) * 2] = (uint8_t)ca; chosen[(tl * 32 + l) * 2 + 1] = (uint8_t)cb2; }
+        if (h == 0 && rs == 0) { chosen[((set * 32 + n) * 32 + l) * 2] = (uint8_t)ca; chosen[((set * 32 + n) * 32 + l) * 2 + 1] = (uint8_t)cb2; }
         // residual -= C[a] + i C[b]
 #pragma unroll
         for (int kc = 0; kc < 8; ++kc) {
             const int piece = 2 * kc + h;
-            const uint4 pa = *reinterpret_cast<const uint4 *>(lds + kEpRows + ca * 256 + (piece ^ (ca & 15)) * 16);
-            const uint4 pb = *reinterpret_cast<const uint4 *>(lds + kEpRows + (64 + cb2) * 256 + (piece ^ (cb2 & 15)) * 16);
+            const uint4 pa = *reinterpret_cast<const uint4 *>(img + ca * 256 + (piece ^ (ca & 15)) * 16);
+            const uint4 pb = *reinterpret_cast<const uint4 *>(lds + kEpTurned + cb2 * 256 + (piece ^ (cb2 & 15)) * 16);
             const unsigned wa[4] = {pa.x, pa.y, pa.z, pa.w}, wb[4] = {pb.x, pb.y, pb.z, pb.w};
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -1113,9 +1116,11 @@ __global__ __launch_bounds__(kEpThreads, 2) void k_encode_pairs(const void *__re
         }
     }
     __syncthreads();
+    const int last_lane = fresh_lane(), tl = set * 32 + (last_lane & 31);
+    const long long tok = (long long)(blockIdx.x / a.Hkv) * (32 * kSets) + tl;
     if (tok < n_tokens) {
         uint8_t *dst = out + tok * a.token_stride + (long long)g * a.head_stride;
-        for (int byte = 2 * rs + h; byte < a.record_bytes; byte += 2 * RS) {
+        for (int byte = 2 * rs + (last_lane >> 5); byte < a.record_bytes; byte += 2 * RS) {
             unsigned v = 0;
             for (int r = (8 * byte) / 12; r < a.levels && 12 * r < 8 * byte + 8; ++r) {
                 const unsigned pr = (unsigned)chosen[(tl * 32 + r) * 2] | (unsigned)chosen[(tl * 32 + r) * 2 + 1] << 6;
@@ -1377,7 +1382,7 @@ commvq_status encode_pairs(const void *keys, const void *cb, const float *norms,
                            int n_tokens, hipStream_t s)
 {
     // As in encode_rows: full rounds of one workgroup per compute unit go to RS = 1, and the rest to what needs one round.
-    // 21 levels of 8 heads take 113 us with RS = 4 (up to 1024 tokens), 132 (2; 2048), 179 (1; 4096).  A workgroup per
+    // 21 levels of 8 heads take 109 us with RS = 4 (up to 1024 tokens), 125 (2; 2048), 167 (1; 4096).  A workgroup per
     // vector takes 33 to 46 us while the vectors fit the chip, two workgroups per compute unit.
     const int64_t round = 128 * (int64_t)std::max(1, 256 / d.Hkv);
     const int full = (int)(n_tokens / round * round), rest = n_tokens - full;

@@ -59,15 +59,6 @@ struct ValuesArgs {
     int mode;                 // 0: everything; 1: up to the bins, which go to memory; 2: from there on
 };
 
-// The lane's index, made anew wherever it is asked for: what depends on it is then neither hoisted out of a loop nor kept in
-// registers (or spilled) across it.
-__device__ __forceinline__ int fresh_lane()
-{
-    int l;
-    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
-    return l;
-}
-
 // x in whole units (numbers on [0, 2^32)): rounded to nearest, NaN to 0.
 __device__ __forceinline__ unsigned whole_units(float x, float per)
 {
