@@ -861,9 +861,9 @@ __global__ __launch_bounds__(kManyThreads, 2) void k_encode_many(const void *__r
 // Four wavefronts, one per SIMD: 4 / RS sets of 32 tokens.  The RS wavefronts of a set share the rows a of the scan (and
 // compute only their part of P); residual, split and Q are each wavefront's own: handing them round through LDS, with
 // eight wavefronts and the residuals split between two, cost more than it saved (8.9 us a level at RS = 1's sizes).
-// A level takes 7.9 us with RS = 1 (128 tokens), 6.0 (2) and 5.1 (4), of which a row of the scan is 50 ns: two matrix
+// A level takes 7.5 us with RS = 1 (128 tokens), 5.8 (2) and 4.9 (4), of which a row of the scan is 45 ns: two matrix
 // instructions (64 clk) and 21 vector ones (90 clk) that hide in each other only where they alternate in the program, so
-// the order is fixed below (left to the compiler: 90 ns).  32768 vectors, 21 levels: 167 us, 8192 vectors 109; with the
+// the order is fixed below (left to the compiler: 90 ns).  32768 vectors, 21 levels: 160 us, 8192 vectors 103; with the
 // scan's sums on the vector unit and cross terms read per 16 tokens 258 and 165.
 //   32 x 32 operands: lane (n, h) supplies row / token n and elements 8 h .. + 7 of a chunk of 16 (scan: 4 h .. + 3 of 8)
 //   32 x 32 result  : lane (n, h) receives, in register i, row 8 (i / 4) + 4 h + i % 4 for token n
@@ -872,6 +872,9 @@ __global__ __launch_bounds__(kManyThreads, 2) void k_encode_many(const void *__r
 // they were 33 of 256 for the whole level, 16 of which spilled, and one LDS write more: keys at 21 levels and values at 16 of 4000
 // tokens 247.6 -> 238.7 us, 300 tokens 137.6 -> 132.8; keys at 11 levels, 1000 tokens 93.7 -> 90.7, 2500 160.2 -> 154.4.  (Addresses made anew
 // at every level instead of held: 244.1, 139.9, 94.7, 160.9.  512 registers: the compiler moves half of them to and fro, 314.)
+// With a wait that the compiler had put into every level for the keys loaded ahead of them, and so for all of the next level's tables, 2 to 4 us
+// more (300 tokens 130.8 -> 126.3, 1000 90.1 -> 87.6, 4000 235.6 -> 233.0); with the scan's operands read one row ahead instead of two another
+// 7 at 4000 tokens (238.7 -> 231.7), 2 at 300.
 constexpr int kEpThreads = 256;
 constexpr int kEpImage = 64 * 256;                  // C and the cross terms, of two levels in turn: 64 rows of 256 bytes, 16-byte piece x of row t in
 constexpr int kEpRows = 0;                          // slot x xor (t mod 16)
@@ -956,6 +959,8 @@ __global__ __launch_bounds__(kEpThreads, 2) void k_encode_pairs(const void *__re
     const uint2_t ones_bits = h ? uint2_t{0u, 0u} : uint2_t{0x3f803f80u, 0x3f80u};
     const shortx4_t ones = __builtin_bit_cast(shortx4_t, ones_bits);
     fetch_level(0);
+    // (the keys: the compiler would wait for them in the loop, in every level, and with them for what is on its way for the next)
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
     for (int l = 0; l < a.levels; ++l) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's part of the level has landed
         __syncthreads();                                   // ... and everybody's, and the previous level's tables are no longer read
@@ -1030,12 +1035,12 @@ __global__ __launch_bounds__(kEpThreads, 2) void k_encode_pairs(const void *__re
             const float low = __builtin_bit_cast(float, opaque_sgpr(0xff800000u));
             auto least = [&](float x, float y) { return __builtin_amdgcn_fmed3f(x, y, low); };
             floatx16_t D[2][2];
-            uint2_t x0 = xs[0], x1 = xs[32];
+            uint2_t x[2][2] = {{xs[0], xs[32]}, {xs[row_of(1) * 64], xs[row_of(1) * 64 + 32]}};  // (two rows ahead: the LDS takes longer than one)
             float half[2] = {0.f, 0.f}, m0 = 0.f, m1 = 0.f;
 #pragma unroll
             for (int k = 0; k <= 2 * kPairs; ++k) {
                 const int cur = k & 1, old = cur ^ 1;
-                if (k < 2 * kPairs) D[cur][0] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(__builtin_bit_cast(shortx4_t, x0), ones, V[0], 0, 0, 0);
+                if (k < 2 * kPairs) D[cur][0] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(__builtin_bit_cast(shortx4_t, x[cur][0]), ones, V[0], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
                 if (k > 0) {
                     m0 = least(D[old][0][0], D[old][0][1]);
@@ -1044,8 +1049,8 @@ __global__ __launch_bounds__(kEpThreads, 2) void k_encode_pairs(const void *__re
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 if (k < 2 * kPairs) {
-                    D[cur][1] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(__builtin_bit_cast(shortx4_t, x1), ones, V[1], 0, 0, 0);
-                    if (k + 1 < 2 * kPairs) { x0 = xs[row_of(k + 1) * 64]; x1 = xs[row_of(k + 1) * 64 + 32]; }
+                    D[cur][1] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(__builtin_bit_cast(shortx4_t, x[cur][1]), ones, V[1], 0, 0, 0);
+                    if (k + 2 < 2 * kPairs) { x[cur][0] = xs[row_of(k + 2) * 64]; x[cur][1] = xs[row_of(k + 2) * 64 + 32]; }
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 if (k > 0) {
@@ -1382,7 +1387,7 @@ commvq_status encode_pairs(const void *keys, const void *cb, const float *norms,
                            int n_tokens, hipStream_t s)
 {
     // As in encode_rows: full rounds of one workgroup per compute unit go to RS = 1, and the rest to what needs one round.
-    // 21 levels of 8 heads take 109 us with RS = 4 (up to 1024 tokens), 125 (2; 2048), 167 (1; 4096).  A workgroup per
+    // 21 levels of 8 heads take 103 us with RS = 4 (up to 1024 tokens), 118 (2; 2048), 160 (1; 4096).  A workgroup per
     // vector takes 33 to 46 us while the vectors fit the chip, two workgroups per compute unit.
     const int64_t round = 128 * (int64_t)std::max(1, 256 / d.Hkv);
     const int full = (int)(n_tokens / round * round), rest = n_tokens - full;
