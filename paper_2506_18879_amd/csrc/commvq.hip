@@ -149,6 +149,23 @@ size_t few_tile_bytes(const commvq_handle *h, int B, int64_t T, int max_seqlen)
     return cut > 1 ? (size_t)cut * logit_bytes(h, T) : 0;
 }
 
+// Where the value stage's arrays begin (carve): `shared` is the end of the partial logits, `parts` their size, `packed` what the score stage
+// has behind them.
+inline size_t value_stage_at(size_t shared, size_t parts, size_t packed, size_t few, size_t value)
+{
+    const size_t apart = few ? few + std::min(packed, value) : 0;
+    return shared - (parts > apart ? parts - apart : 0);
+}
+
+// Tokens of a workgroup of the row-gather kernels.
+int gather_split_len(int units, int max_seqlen)
+{
+    int len = 1024;
+    // down to 4 tokens per wavefront (one iteration of four tokens): a short context still spreads over the chip
+    while (len > kFewTokens && (long)units * ((max_seqlen + len - 1) / len) < kScoreMinWgs) len /= 2;
+    return len;
+}
+
 // How k_score_stream cuts a launch: `passes` segments of 512 tokens per workgroup, `tiles` workgroups per KV head, each of
 // them once per slice group.
 struct StreamShape {
@@ -203,11 +220,21 @@ StreamShape stream_shape(const commvq_handle *h, int B, int64_t T, int max_seqle
     const int vlen = value_split_len(h, B, max_seqlen, 1024);
     const size_t one = logit_bytes(h, T);
     const size_t value = value_stage_bytes(h, B, (size_t)(max_seqlen + vlen - 1) / vlen);
-    size_t room = value + few_tile_bytes(h, B, T, max_seqlen);
+    const size_t few = few_tile_bytes(h, B, T, max_seqlen);
+    size_t room = value + few;
     if (pair) {  // no more than the shape has needed with unpacked indices, or 32 MB in all
         const size_t rest = one + packed_key_bytes(h->cfg) + align_up((size_t)B * h->cfg.n_q_heads * per_seq * 8, 256), small = (size_t)32 << 20;
         room = std::max({pair_room(h->cfg, T), value - std::min(value, packed_key_bytes(h->cfg)), small - std::min(small, rest)});
     }
+    // Nor may a shape outgrow the static array that fits it uncut (behind the partial logits lies the re-laid codebook, too: 40 sequences of up
+    // to 29503 tokens, 707107 in all, one query head each: 47 MB uncut, 62 in two groups).
+    const int gather = gather_split_len(B * h->cfg.n_kv_heads, max_seqlen);
+    const size_t stats = align_up((size_t)B * h->cfg.n_q_heads * std::max(per_seq, (max_seqlen + gather - 1) / gather) * 8, 256);
+    auto bytes = [&](size_t parts) {
+        const size_t shared = stats + one + parts, packed = packed_key_bytes(h->cfg);
+        return std::max(shared + packed, value_stage_at(shared, parts, packed, few, value) + value);
+    };
+    const size_t most_bytes = std::max(bytes(0), kStaticScratchBytes);
     StreamShape best = {2, 1, 1};
     double t_best = 1e30;
     const double million = (double)T * h->cfg.n_q_heads / 1e6;  // logits
@@ -215,6 +242,7 @@ StreamShape stream_shape(const commvq_handle *h, int B, int64_t T, int max_seqle
     for (int passes = 2; passes <= most_passes; passes = !pair || passes != 4 ? passes + 1 : most_passes)
         for (int e = 1; e <= kStreamSlices && (e - 1) * one <= room; e *= 2) {
             if (pair && passes == 3 && e == 1 && sets > 3) continue;
+            if (!pair && bytes((e - 1) * one) > most_bytes) continue;
             const double slices = (double)kStreamSlices / e;
             auto rounds = [&](int64_t segs) { return (double)(((segs + passes - 1) / passes * h->cfg.n_kv_heads * e + 255) / 256); };
             double t;
@@ -340,9 +368,7 @@ void make_plan(const commvq_handle *h, int B, int64_t T, int max_seqlen, bool sl
             if (t < best * 0.9999) { best = t; len = 1024 * tpt; }
         }
     } else {
-        len = 1024;
-        // down to 4 tokens per wavefront (one iteration of four tokens): a short context still spreads over the chip
-        while (len > kFewTokens && (long)units * ((max_seqlen + len - 1) / len) < kScoreMinWgs) len /= 2;
+        len = gather_split_len(units, max_seqlen);
     }
     const int groups = p->stream.groups;
     p->score_split_len = len;
@@ -386,8 +412,7 @@ void carve(const commvq_handle *h, int B, int64_t T, int max_seqlen, void *base,
     w->packed = bf16 && !c.position_free ? reinterpret_cast<uint4 *>(take(packed_key_bytes(c) / 4)) : nullptr;
     w->lut = c.position_free ? take(heads * c.m_key * kK) : nullptr;
     const size_t score_end = off, value_bytes = value_stage_bytes(h, B, vsplits);
-    const size_t few = few_tile_bytes(h, B, T, max_seqlen), apart = few ? few + std::min(score_end - shared, value_bytes) : 0;
-    off = shared - (parts > apart ? parts - apart : 0);
+    off = value_stage_at(shared, parts, score_end - shared, few_tile_bytes(h, B, T, max_seqlen), value_bytes);
     w->vscale = take(heads * vsplits);
     w->lsum = take(heads * vsplits);
     w->bins = reinterpret_cast<unsigned *>(take(heads * vsplits * rows));

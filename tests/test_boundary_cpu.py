@@ -310,6 +310,22 @@ def test_partial_logits_do_not_enlarge_the_workspace(planner, kw):
     assert cut > 20
 
 
+@pytest.mark.parametrize("B,T,L", [(40, 707107, 29503), (40, 682129, 34973), (24, 690000, 50000), (64, 500000, 20000)])
+def test_a_cut_does_not_outgrow_the_static_scratch(planner, B, T, L):
+    """One query head per KV head, so that the re-laid codebook and one set of logits together fill most of the array: whatever cut
+    the planner prefers, a shape that fits it uncut is accepted."""
+    h = planner(n_q_heads=8, m_key=32, m_val=16)
+    p = cv.commvq_plan_query(h, B, T, L)
+    up = lambda n: -(-n // 256) * 256
+    logits, stats = up(4 * T * 8), up(8 * B * 8 * -(-L // 512))
+    value = 2 * up(4 * B * 8 * p.value_splits) + up(4 * B * 8 * p.value_splits * 16 * 256) + up(4 * B * 8 * p.out_chunks * 128) + 8 * 16 * 256 * 256
+    uncut = logits + stats + max(8 * 32 * 256 * 256, value)
+    a = _call_args(h)
+    call = status_of(cv.commvq_decode_attn_static, h, a["q"], a["key_codes"], a["val_codes"], a["key_codebooks"], a["val_codebooks"],
+                     cv.binding.make_positions(B, _Buf(4096), _Buf(8192), None, T, L), a["out"])
+    assert uncut <= cv.commvq_static_scratch_bytes() and call == 6        # (a full handle would launch)
+
+
 @pytest.mark.parametrize("kw", [dict(m_key=16, m_val=16), dict(m_key=32, m_val=32), dict(n_q_heads=64, m_key=16, m_val=16)])
 def test_sixteen_chats_never_need_less_workspace_for_longer_contexts(planner, kw):
     h = planner(**kw)
