@@ -2229,10 +2229,16 @@ struct ScoreArgs {
     ScoreDims d;
 };
 
+// Tiles of 16 tokens go to k_score_few (there are then fewer than 2 kScoreMinWgs of them: each dimension of its grid is in range), except
+// fp32 rows of 32 codebooks with 4 or 8 heads, where it takes 256 registers, one wavefront per SIMD, which pays only while there is
+// about one workgroup per SIMD.  Whole calls in microseconds, k_score against it: 4 heads, 656 workgroups 28.5 and 28.1, 800 31.0 and
+// 32.1, 4000 78.1 and 85.4; 8 heads, 1500 63.0 and 61.6, 2000 69.9 and 70.2, 4000 104.5 and 108.5.  (1 and 2 heads, 16 codebooks and bf16:
+// faster with it by 4 to 30 % up to 4000.)
 template <int M, int G>
 hipError_t launch_score_mg(const ScoreArgs &a, bool bf16, int batch, hipStream_t s)
 {
-    const bool few = a.d.split_len == kFewTokens;             // (then there are fewer than 2 kScoreMinWgs workgroups: each grid dimension is in range)
+    const bool wide = !bf16 && M == 32 && G >= 4;
+    const bool few = a.d.split_len == kFewTokens && (!wide || batch * a.d.Hkv * a.d.nsplit <= (G == 4 ? 700 : 1800));
     auto kernel = few ? (bf16 ? k_score_few<M, G, true> : k_score_few<M, G, false>) : (bf16 ? k_score<M, G, true> : k_score<M, G, false>);
     const dim3 grid = few ? dim3(a.d.Hkv, a.d.nsplit, batch) : dim3(batch * a.d.Hkv * a.d.nsplit);
     hipLaunchKernelGGL(kernel, grid, dim3(kScoreThreads), 0, s, a.q, a.key_codes, a.key_cb, a.cu, a.q_pos, a.key_pos, a.tbl_hi,

@@ -1,5 +1,7 @@
 """The score kernel of launches of few tokens (16 tokens a workgroup, rows gathered, nothing pipelined): parity with the oracle as in
 test_gpu_parity.py, at the edges of its workgroups and of the rule that chooses it."""
+import re
+
 import numpy as np
 import pytest
 
@@ -36,6 +38,23 @@ def test_either_side_of_the_rule(gpu, oracle, Mk, lens, kernel):  # noqa: F811
     assert op.plan.score_kernel == kernel
     op.close()
     _check(gpu, oracle, w, max_position=8192)
+
+
+@pytest.mark.parametrize("Mk,G,tokens,kernel", [(32, 4, 1392, "k_score_few"), (32, 4, 1393, "k_score"), (32, 8, 3600, "k_score_few"), (32, 8, 3601, "k_score"),
+                                                (32, 2, 3700, "k_score_few"), (16, 8, 3700, "k_score_few")])
+def test_fp32_rows_with_many_heads(gpu, oracle, Mk, G, tokens, kernel):  # noqa: F811
+    # 696 and 704, 1800 and 1808 workgroups of 16 tokens: tiles of four tokens a wavefront in both kernels
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    w = _make(f"wide_m{Mk}_g{G}_{tokens}", 8 * G, [tokens], Mk, "f32")
+    dw, op = gpu.DeviceWorkload(w), gpu.DecodeAttention(w, max_position=4096)
+    assert (op.plan.score_kernel, op.plan.score_split_len) == (0, 16)
+    with profile(activities=[ProfilerActivity.CUDA]) as trace:
+        op(dw)
+        torch.cuda.synchronize()
+    op.close()
+    assert {m.group(1) for e in trace.events() for m in [re.search(r"(k_score\w*)<", e.name)] if m} == {kernel}
+    _check(gpu, oracle, w, max_position=4096)
 
 
 @pytest.mark.parametrize("Mk", [16, 32])
