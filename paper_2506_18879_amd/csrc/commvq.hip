@@ -262,6 +262,19 @@ StreamShape stream_shape(const commvq_handle *h, int B, int64_t T, int max_seqle
 // Whether the sliced score path is k_score_stream or k_score_pair (keys with RoPE), not the look-up table.
 inline bool stream_keys(const commvq_config &c) { return !c.position_free; }
 
+// Whether up to 4 heads take k_score_stream's and k_score_pair's exchange of rows within a pair of passes, as 8 heads do, and not logits in
+// halves.  Halves save the exchange but fold the queries in every pass that begins another sequence where an exchanged pair does so
+// once, and a launch of one round is as slow as its slowest workgroup.  They lose for a batch with two passes a workgroup, and with an even number
+// of passes where most of them are a sequence of its own.  Whole calls in microseconds, halves and exchange: two passes, 24 sequences
+// of 750 to 1500 tokens, 16 codebooks 48.8 and 47.7, R = 11 54.2 and 52.3, 8 of 1750 to 3500 43.5 and 42.3, 49.2 and 46.9 (one sequence of 30000: 37.7 and
+// 39.4, 42.2 and 43.8); four passes, 64 of 280 to 560 71.2 and 68.7, 85.4 and 81.8 (40 of 550 to 1100: 65.4 and 65.9, 78.4 and 78.0; 16 of 2048 to 4096: 54.5
+// and 57.4, 66.2 and 68.9).  32 codebooks: no more than 0.9 either way with short sequences, else halves by 1 to 12.
+inline bool exchange_rows(const commvq_handle *h, const StreamShape &s, int B, int64_t T)
+{
+    if (h->G == 8 || B == 1 || (!pair_keys(h->cfg) && h->cfg.m_key == 32)) return false;
+    return (s.passes == 2 && s.groups == 1) || ((s.passes == 2 || s.passes == 4) && T <= (int64_t)B * kPassTokens);
+}
+
 // Whether gathering rows (k_score_few) serves a launch of bf16 codebooks with contiguous positions better than the slices: so few
 // tokens that 16 of them a workgroup leave none of it waiting and the rows' way through the L1s (tokens x heads x codebooks x 256
 // bytes) costs less than the partial logits and their sum.  Whole calls, slices -> rows, in microseconds, 8 KV heads: 4 query heads each and 16 +
@@ -957,7 +970,9 @@ struct StreamDims {
 //
 // Short contexts: a launch may cut every tile along the slices as well (StreamDims::groups workgroups per
 // tile); each then writes partial logits, which k_score_combine adds.
-template <int M, int NGRP, int NP>
+//
+// FORM: 1 up to 4 heads, logits in halves; 0 up to 4 heads, rows exchanged in pairs of passes (exchange_rows); 2 eight heads, likewise.
+template <int M, int FORM, int NP>
 __global__ __launch_bounds__(kSliceThreads) void k_score_stream(
     const void *__restrict__ q, const uint8_t *__restrict__ key_codes, const uint4 *__restrict__ packed,
     const int32_t *__restrict__ cu, const int32_t *__restrict__ q_pos, const float2 *__restrict__ tbl_hi,
@@ -966,9 +981,10 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_stream(
     constexpr int S = kStreamSlices;
     constexpr int NB = M / 16;                                // 64 KiB blocks per slice
     constexpr int NST = 4 * NB;                               // gather steps (sparse matrix instructions) per pass
+    constexpr int NGRP = FORM == 2 ? 2 : 1;
     const int G = NGRP == 2 ? 8 : a.G;                        // query heads of the KV head; NGRP groups of 4, padded with zero queries
     constexpr int NBUF = 2;                                   // gather steps whose LDS reads are in flight
-    constexpr bool HALF = NGRP == 1;                          // logits in two halves, each of the elements that a lane has (8 heads: no registers)
+    constexpr bool HALF = FORM == 1;                          // logits in two halves, each of the elements that a lane has (8 heads: no registers)
     extern __shared__ __attribute__((aligned(16))) uint4 tab[];
 
     int id = blockIdx.x;
@@ -2280,47 +2296,49 @@ struct StreamArgs {
     StreamDims d;
 };
 
-template <int M, int NGRP, int NP>
+template <int M, int FORM, int NP>
 hipError_t launch_stream_n(const StreamArgs &a, int grid, hipStream_t s)
 {
     static std::atomic<uint64_t> lds_ok{0};  // per instantiation and device
-    if (hipError_t e = allow_dynamic_lds(&k_score_stream<M, NGRP, NP>, kStreamLds, lds_ok); e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_score_stream<M, NGRP, NP>), dim3(grid), dim3(kSliceThreads), kStreamLds, s, a.q, a.key_codes,
+    if (hipError_t e = allow_dynamic_lds(&k_score_stream<M, FORM, NP>, kStreamLds, lds_ok); e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_score_stream<M, FORM, NP>), dim3(grid), dim3(kSliceThreads), kStreamLds, s, a.q, a.key_codes,
                        a.packed, a.cu, a.q_pos, a.tbl_hi, a.tbl_lo, a.scores, a.sstat, a.d);
     return hipGetLastError();
 }
-template <int M, int NGRP>
+template <int M, int FORM>
 hipError_t launch_stream_g(const StreamArgs &a, int passes, int grid, hipStream_t s)
 {
     switch (passes) {
-    case 2: return launch_stream_n<M, NGRP, 2>(a, grid, s);
-    case 3: return launch_stream_n<M, NGRP, 3>(a, grid, s);
-    case 4: return launch_stream_n<M, NGRP, 4>(a, grid, s);
-    case 5: return launch_stream_n<M, NGRP, 5>(a, grid, s);
-    case 6: return launch_stream_n<M, NGRP, 6>(a, grid, s);
-    case 7: return launch_stream_n<M, NGRP, 7>(a, grid, s);
-    default: return launch_stream_n<M, NGRP, 8>(a, grid, s);
+    case 2: return launch_stream_n<M, FORM, 2>(a, grid, s);
+    case 3: return launch_stream_n<M, FORM, 3>(a, grid, s);
+    case 4: return launch_stream_n<M, FORM, 4>(a, grid, s);
+    case 5: return launch_stream_n<M, FORM, 5>(a, grid, s);
+    case 6: return launch_stream_n<M, FORM, 6>(a, grid, s);
+    case 7: return launch_stream_n<M, FORM, 7>(a, grid, s);
+    default: return launch_stream_n<M, FORM, 8>(a, grid, s);
     }
 }
-hipError_t launch_stream(const StreamArgs &a, int M, int passes, int grid, hipStream_t s)
+hipError_t launch_stream(const StreamArgs &a, int M, int passes, bool exchange, int grid, hipStream_t s)
 {
+    if (exchange) return passes == 2 ? launch_stream_n<16, 0, 2>(a, grid, s) : launch_stream_n<16, 0, 4>(a, grid, s);
     if (M == 16) return a.d.G == 8 ? launch_stream_g<16, 2>(a, passes, grid, s) : launch_stream_g<16, 1>(a, passes, grid, s);
     return a.d.G == 8 ? launch_stream_g<32, 2>(a, passes, grid, s) : launch_stream_g<32, 1>(a, passes, grid, s);
 }
 
-template <int SETS, int NGRP, int NP>
+template <int SETS, int FORM, int NP>
 hipError_t launch_pair_n(const StreamArgs &a, int R, int PB, int grid, hipStream_t s)
 {
     static std::atomic<uint64_t> lds_ok{0};  // per instantiation and device
-    if (hipError_t e = allow_dynamic_lds(&k_score_pair<SETS, NGRP, NP>, kPairLds, lds_ok); e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_score_pair<SETS, NGRP, NP>), dim3(grid), dim3(kSliceThreads), kPairLds, s, a.q, a.key_codes,
+    if (hipError_t e = allow_dynamic_lds(&k_score_pair<SETS, FORM, NP>, kPairLds, lds_ok); e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_score_pair<SETS, FORM, NP>), dim3(grid), dim3(kSliceThreads), kPairLds, s, a.q, a.key_codes,
                        a.packed, a.cu, a.q_pos, a.tbl_hi, a.tbl_lo, a.scores, a.sstat, a.d, R, PB);
     return hipGetLastError();
 }
 template <int SETS>
-hipError_t launch_pair_s(const StreamArgs &a, int passes, int R, int PB, int grid, hipStream_t s)
+hipError_t launch_pair_s(const StreamArgs &a, int passes, bool exchange, int R, int PB, int grid, hipStream_t s)
 {
     constexpr int most = pair_passes(SETS);
+    if (exchange) return passes == 2 ? launch_pair_n<SETS, 0, 2>(a, R, PB, grid, s) : launch_pair_n<SETS, 0, 4>(a, R, PB, grid, s);
     if (a.d.G == 8) {
         if (passes == 2) return launch_pair_n<SETS, 2, 2>(a, R, PB, grid, s);
         if (passes == 3) return launch_pair_n<SETS, 2, 3>(a, R, PB, grid, s);
@@ -2332,13 +2350,13 @@ hipError_t launch_pair_s(const StreamArgs &a, int passes, int R, int PB, int gri
     if (passes == 4) return launch_pair_n<SETS, 1, 4>(a, R, PB, grid, s);
     return launch_pair_n<SETS, 1, most>(a, R, PB, grid, s);
 }
-hipError_t launch_pair(const StreamArgs &a, const commvq_config &c, int passes, int grid, hipStream_t s)
+hipError_t launch_pair(const StreamArgs &a, const commvq_config &c, int passes, bool exchange, int grid, hipStream_t s)
 {
     const int R = c.key_levels, PB = pair_record_bytes(c);
     switch (pair_sets(c)) {
-    case 3: return launch_pair_s<3>(a, passes, R, PB, grid, s);
-    case 4: return launch_pair_s<4>(a, passes, R, PB, grid, s);
-    default: return launch_pair_s<6>(a, passes, R, PB, grid, s);
+    case 3: return launch_pair_s<3>(a, passes, exchange, R, PB, grid, s);
+    case 4: return launch_pair_s<4>(a, passes, exchange, R, PB, grid, s);
+    default: return launch_pair_s<6>(a, passes, exchange, R, PB, grid, s);
     }
 }
 
@@ -2437,7 +2455,8 @@ commvq_status run_scores(commvq_handle *h, const void *q, const uint8_t *key_cod
         sa.d.nstat = stat_splits(h, plan, pos->max_seqlen);
         sa.d.part_stride = (long long)(logit_bytes(h, pos->total_tokens) / 4);
         const int grid = c.n_kv_heads * ss.tiles * ss.groups;
-        e = pair_keys(c) ? launch_pair(sa, c, ss.passes, grid, s) : launch_stream(sa, c.m_key, ss.passes, grid, s);
+        const bool exchange = exchange_rows(h, ss, pos->batch, pos->total_tokens);
+        e = pair_keys(c) ? launch_pair(sa, c, ss.passes, exchange, grid, s) : launch_stream(sa, c.m_key, ss.passes, exchange, grid, s);
         if (e == hipSuccess && ss.groups > 1) {
             const int ns = sa.d.nstat;
             hipLaunchKernelGGL(k_score_combine, dim3((unsigned)(pos->batch * c.n_q_heads * ns)), dim3(kCombineThreads), 0, s,

@@ -53,7 +53,7 @@ __global__ __launch_bounds__(256) void k_prep_pairs(const uint4 *__restrict__ ta
 // of one sequence, never cut along the planes) and now, R = 11 | 21: 2000 tokens 58.3 -> 39.7 | 78.5 -> 42.6 us, 12000 59.6 ->
 // 48.2 | 81.1 -> 56.3, 40000 84.1 -> 74.4 | 125.8 -> 89.2, 128K 146.8 -> 117.3 | 250 -> 197, 8 x 1100..2200 63.1 -> 55.9 | 84.3 -> 62.2.
 // With two groups of heads the most passes do not fit the registers: <3, 2, 8> spills 22 of them, <6, 2, 6> 38.
-template <int SETS, int NGRP, int NP>
+template <int SETS, int FORM, int NP>
 __global__ __launch_bounds__(kSliceThreads) void k_score_pair(
     const void *__restrict__ q, const uint8_t *__restrict__ pairs, const uint4 *__restrict__ packed,
     const int32_t *__restrict__ cu, const int32_t *__restrict__ q_pos, const float2 *__restrict__ tbl_hi,
@@ -62,9 +62,10 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_pair(
     constexpr int S = kPairSlices, PL = kPairPlanes;
     constexpr int NST = 2 * SETS;                             // gather steps (sparse matrix instructions) per pass
     constexpr bool TWO = SETS == 3;                           // slices in two LDS buffers in turn, else in one
+    constexpr int NGRP = FORM == 2 ? 2 : 1;                   // (FORM as for k_score_stream)
     const int G = NGRP == 2 ? 8 : a.G;                        // query heads of the KV head; NGRP groups of 4, padded with zero queries
     constexpr int NBUF = 2;                                   // gather steps whose LDS reads are in flight
-    constexpr bool HALF = NGRP == 1;                          // logits in two halves, each of the elements that a lane has (8 heads: no registers)
+    constexpr bool HALF = FORM == 1;
     constexpr int CC = SETS == 3 ? 3 : SETS;                  // dwords of a lane's index bytes per pass
     constexpr int RAW = SETS == 3 ? 5 : SETS == 4 ? 7 : 8;    // dwords that hold a record at any byte offset
     // LDS: slice buffers at 0 (and 64 KiB), [8 parts][64 positions] fine factors, queries, coarse factors [pass][9 rows][8 parts, padded
