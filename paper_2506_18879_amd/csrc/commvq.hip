@@ -1546,9 +1546,14 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_stream(
 // partial logits of the slice groups (Eq. new_attention's sum over the sub-spaces, split in `groups` parts).  One
 // workgroup per (sequence, query head, 1024 tokens): adds the parts in a fixed order, writes the logits (over the
 // first group's part) and the (max, sum of exp) of its 1024 tokens.
-constexpr int kCombineThreads = 256;
+// Bound by latency: all parts of all its tokens are requested at once, with no branch before, between or behind them.  (A branch per part and a round of
+// requests per 256 tokens went through 4 KB of instructions that had to be fetched on the way: whole calls in microseconds, so -> now, paired keys
+// R = 11: two KV heads of one 400 tokens 18.8 -> 17.7, 2000 20.1 -> 17.7, 8 x 4 heads 400 20.3 -> 19.2, 1000 21.8 -> 19.7, R = 21 4000 25.4 -> 24.6;
+// 32 codebooks, 8 x 4 heads 8000 27.6 -> 26.9, 32768 50.8 -> 50.6.)
+constexpr int kCombineThreads = 256, kCombineTokens = 1024;
+template <int GROUPS>
 __global__ __launch_bounds__(kCombineThreads) void k_score_combine(float *scores, float2 *__restrict__ sstat, const int32_t *__restrict__ cu,
-                                                                  int Hq, int nsplit, int tile_len, int groups, long long part_stride)
+                                                                  int Hq, int nsplit, long long part_stride)
 {
     __shared__ float red[kCombineThreads / 64];
     int id = blockIdx.x;
@@ -1556,33 +1561,30 @@ __global__ __launch_bounds__(kCombineThreads) void k_score_combine(float *scores
     id /= nsplit;
     const int h = id % Hq, b = id / Hq;
     const int cu0 = cu[b], L = cu[b + 1] - cu0;
-    const int t0 = tile * tile_len;
+    const int t0 = tile * kCombineTokens;
     if (t0 >= L) return;
-    const int t1 = min(t0 + tile_len, L);
-    const size_t row = (size_t)cu0 * Hq + (size_t)h * L;
-    constexpr int MAXV = 1024 / kCombineThreads;  // statistics tiles of 1024 tokens
-    float v[MAXV];
-    float mx = -INFINITY;
+    float *const row = scores + (size_t)cu0 * Hq + (size_t)h * L;
+    constexpr int MAXV = kCombineTokens / kCombineThreads;
+    float part[GROUPS][MAXV];                                 // (reads past the row return zero)
 #pragma unroll
-    for (int k = 0; k < MAXV; ++k) {
-        const int tok = t0 + k * kCombineThreads + (int)threadIdx.x;
-        v[k] = -INFINITY;
-        if (k * kCombineThreads < tile_len && tok < t1) {
-            // all parts requested at once (at most 16 slice groups), added in a fixed order
-            float pv[16];
+    for (int e = 0; e < GROUPS; ++e) {
+        const __amdgpu_buffer_rsrc_t r = make_rsrc(row + (size_t)e * part_stride, (unsigned)L * 4u);
 #pragma unroll
-            for (int e = 0; e < 16; ++e) pv[e] = e < groups ? scores[(size_t)e * part_stride + row + tok] : 0.f;
-            float acc = pv[0];
-#pragma unroll
-            for (int e = 1; e < 16; ++e) acc += pv[e];
-            v[k] = acc;
-            mx = fmaxf(mx, acc);
-        }
+        for (int k = 0; k < MAXV; ++k)
+            part[e][k] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (unsigned)(t0 + k * kCombineThreads + (int)threadIdx.x) * 4u, 0, 0));
     }
+    __builtin_amdgcn_sched_barrier(0);
+    float v[MAXV], mx = -INFINITY;
+    const __amdgpu_buffer_rsrc_t own = make_rsrc(row, (unsigned)L * 4u);
 #pragma unroll
-    for (int k = 0; k < MAXV; ++k) {  // over the first group's part, once nothing of it is wanted any more
+    for (int k = 0; k < MAXV; ++k) {                          // in a fixed order, over the first group's part
         const int tok = t0 + k * kCombineThreads + (int)threadIdx.x;
-        if (k * kCombineThreads < tile_len && tok < t1) store_through(v[k], make_rsrc(scores + row, (unsigned)L * 4u), (unsigned)tok * 4u);
+        float acc = part[0][k];
+#pragma unroll
+        for (int e = 1; e < GROUPS; ++e) acc += part[e][k];
+        v[k] = tok < L ? acc : -INFINITY;
+        mx = fmaxf(mx, v[k]);
+        if (tok < L) store_through(acc, own, (unsigned)tok * 4u);
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     mx = wave_max(mx);
@@ -2459,8 +2461,9 @@ commvq_status run_scores(commvq_handle *h, const void *q, const uint8_t *key_cod
         e = pair_keys(c) ? launch_pair(sa, c, ss.passes, exchange, grid, s) : launch_stream(sa, c.m_key, ss.passes, exchange, grid, s);
         if (e == hipSuccess && ss.groups > 1) {
             const int ns = sa.d.nstat;
-            hipLaunchKernelGGL(k_score_combine, dim3((unsigned)(pos->batch * c.n_q_heads * ns)), dim3(kCombineThreads), 0, s,
-                               w.scores, w.sstat, pos->cu_seqlens, c.n_q_heads, ns, stat_len(h, plan), ss.groups, sa.d.part_stride);
+            auto combine = ss.groups == 2 ? k_score_combine<2> : ss.groups == 4 ? k_score_combine<4> : ss.groups == 8 ? k_score_combine<8> : k_score_combine<16>;
+            hipLaunchKernelGGL(combine, dim3((unsigned)(pos->batch * c.n_q_heads * ns)), dim3(kCombineThreads), 0, s,
+                               w.scores, w.sstat, pos->cu_seqlens, c.n_q_heads, ns, sa.d.part_stride);
             e = hipGetLastError();
         }
         return e == hipSuccess ? COMMVQ_OK : COMMVQ_ERR_LAUNCH;

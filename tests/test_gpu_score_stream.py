@@ -52,6 +52,20 @@ def test_numbers_of_passes(gpu, oracle, Mk, heads, L):  # noqa: F811
                                             dtype="bf16", seed=L + Mk))
 
 
+def test_partial_logits_of_every_number_of_groups(gpu, oracle):  # noqa: F811
+    # sums of 2, 4, 8 and 16 groups' partial logits, for lengths around the 256 tokens of a round and the 1024 of a workgroup, empty sequences
+    seen = set()
+    for i, (Hkv, Mk, lens) in enumerate([(1, 32, [255]), (2, 32, [256, 0, 257]), (1, 16, [1023, 1024, 1025]), (2, 16, [700, 0, 1, 1300]), (8, 32, [5121, 511]),
+                                         (2, 16, [7000, 1, 6143]), (2, 32, [20001]), (8, 16, [9000]), (8, 16, [7000] * 3), (8, 32, [32768]), (4, 16, [9001] * 5)]):
+        w = synth.make_workload(f"parts_{i}", B=len(lens), Hq=4 * Hkv, Hkv=Hkv, seqlens=lens, Mk=Mk, Mv=16, dtype="bf16", seed=600 + i)
+        op = gpu.DecodeAttention(w)
+        if op.plan.score_kernel == 1:
+            seen.add(op.plan.score_slice_groups)
+        op.close()
+        _check(gpu, oracle, w)
+    assert {2, 4, 8, 16} <= seen, seen
+
+
 def test_query_that_is_not_16_byte_aligned(gpu, oracle):  # noqa: F811
     import torch
     w = synth.make_workload("odd_q", B=2, Hq=8, Hkv=2, seqlens=[900, 1300], Mk=16, Mv=16, dtype="bf16", seed=3)
