@@ -1,18 +1,17 @@
 """Paired keys at the numbers of levels where the score kernel's sets of four levels begin and end, with contexts around its passes and
 tiles and of several sequences: logits and outputs against the oracle as in test_gpu_parity.py."""
-import re
-
 import numpy as np
 import pytest
 
 from paper_2506_18879_amd import synth
 
 from test_gpu_parity import TOL_SCORE, assert_rows, gpu  # noqa: F401  (gpu: fixture)
+from test_gpu_score_stream import launched
 
 pytestmark = pytest.mark.gpu
 
 
-def check(gpu, oracle, R, G, Hkv, lens, cut=None):  # noqa: F811
+def check(gpu, oracle, R, G, Hkv, lens, cut=None, form=None):  # noqa: F811
     import torch
     w = synth.make_pair_workload(f"sets_R{R}_{len(lens)}", B=len(lens), Hq=Hkv * G, Hkv=Hkv, seqlens=lens, R=R, Mv=16, seed=40 + R + len(lens))
     dw, op = gpu.DeviceWorkload(w), gpu.DecodeAttention(w)
@@ -21,7 +20,8 @@ def check(gpu, oracle, R, G, Hkv, lens, cut=None):  # noqa: F811
     out = op(dw)
     torch.cuda.synchronize()
     if cut:                                                # (passes of 512 tokens, groups of slices)
-        assert (passes_of_score_kernel(op, dw), op.plan.score_slice_groups) == cut
+        _, launched_form, passes = launched(op, dw, "k_score_pair")
+        assert (passes, op.plan.score_slice_groups) == cut and form in (None, launched_form)
     keep = [i for i, n in enumerate(lens) if n > 0]        # (the oracle rejects empty sequences; their rows are zeros)
     kc = oracle.paired_as_indexed(w.key_codes, w.key_levels, w.cu_seqlens, w.Hkv)
     cu = np.concatenate([[0], np.cumsum([lens[i] for i in keep])]).astype(np.int32)
@@ -32,18 +32,6 @@ def check(gpu, oracle, R, G, Hkv, lens, cut=None):  # noqa: F811
     assert_rows(got[keep], ref, w.name)
     assert not np.delete(got, keep, axis=0).any()
     op.close()
-
-
-def passes_of_score_kernel(op, dw):
-    """The last template argument of the k_score_pair that a call launches."""
-    import torch
-    from torch.profiler import ProfilerActivity, profile
-    with profile(activities=[ProfilerActivity.CUDA]) as trace:
-        op(dw)
-        torch.cuda.synchronize()
-    names = {m.group(1) for e in trace.events() for m in [re.search(r"k_score_pair<\d+, \d+, (\d+)>", e.name)] if m}
-    assert len(names) == 1, [e.name for e in trace.events()]
-    return int(names.pop())
 
 
 @pytest.mark.parametrize("R,G,lens", [(1, 4, [700]), (4, 8, [513, 1]), (5, 4, [511, 0, 64, 63]), (12, 4, [1024, 2049]), (12, 8, [4095]), (13, 4, [300, 65]),
@@ -70,3 +58,12 @@ def test_three_passes(gpu, oracle, R, G, Hkv, lens, groups):  # noqa: F811
     (21, 8, 8, [17000], (2, 1)), (21, 8, 8, [40000], (4, 1)), (21, 8, 8, [90000], (6, 1))])
 def test_several_slices(gpu, oracle, R, G, Hkv, lens, cut):  # noqa: F811
     check(gpu, oracle, R, G, Hkv, lens, cut)
+
+
+# Batches of up to 4 heads that exchange rows in pairs of passes: uncut with two passes, short sequences with two and four, an empty
+# sequence at the beginning and at the end.
+@pytest.mark.parametrize("R,G,Hkv,B,longest,cut", [
+    (11, 1, 8, 50, 511, (2, 1)), (11, 4, 8, 26, 1300, (2, 1)), (11, 4, 16, 66, 255, (4, 1)), (11, 2, 8, 26, 300, (4, 4)),
+    (14, 4, 16, 26, 300, (2, 1)), (14, 2, 16, 66, 255, (4, 1)), (21, 4, 16, 26, 300, (2, 1)), (21, 4, 16, 66, 255, (4, 1)), (21, 1, 4, 26, 300, (4, 8))])
+def test_rows_exchanged_in_pairs_of_passes(gpu, oracle, R, G, Hkv, B, longest, cut):  # noqa: F811
+    check(gpu, oracle, R, G, Hkv, [0] + [longest - 97 * i % (longest // 2) for i in range(B - 2)] + [0], cut, form=0)

@@ -1,6 +1,7 @@
 """The slice-streaming score kernel where a workgroup's passes (512-token segments) belong to several sequences, and every
 number of passes a workgroup can have: parity with the oracle as in test_gpu_parity.py."""
 import dataclasses
+import re
 
 import numpy as np
 import pytest
@@ -27,14 +28,30 @@ def _check(gpu, oracle, w, **kw):
     op.close()
 
 
+def launched(op, dw, kernel):
+    """The template arguments (whole numbers) of the one kernel of that name that a call launches."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CUDA]) as trace:
+        op(dw)
+        torch.cuda.synchronize()
+    names = {m.group(1) for e in trace.events() for m in [re.search(kernel + r"<([\d, ]+)>", e.name)] if m}
+    assert len(names) == 1, [e.name for e in trace.events()]
+    return tuple(int(x) for x in names.pop().split(","))
+
+
 @pytest.mark.parametrize("Mk,G", [(16, 4), (16, 8), (32, 2), (32, 8)])
-@pytest.mark.parametrize("lens", [[512, 1, 513, 511, 1024, 700, 3, 512, 1537], [40, 2000, 512, 0, 1023, 9], [0, 700, 0, 0, 513, 100, 0]])
+@pytest.mark.parametrize("lens", [[512, 1, 513, 511, 1024, 700, 3, 512, 1537], [40, 2000, 512, 0, 1023, 9],
+                                  [0, 2700, 0, 0, 1513, 1300, 0]])
 def test_sequences_that_share_a_workgroup(gpu, oracle, Mk, G, lens):  # noqa: F811
     # boundaries between sequences at even and odd passes, queries at, before (negative distances) and past the end, an empty
     # sequence between two others, at the beginning and at the end
     w = synth.make_workload(f"share_m{Mk}_g{G}_{len(lens)}", B=len(lens), Hq=8 * G, Hkv=8, seqlens=lens, Mk=Mk, Mv=16,
                             dtype="bf16", seed=Mk + G + len(lens))
     w.q_pos = np.array([(max(1, x) - 1, x // 3, x + 777)[i % 3] for i, x in enumerate(lens)], np.int32)
+    op = gpu.DecodeAttention(w, max_position=4096)
+    assert op.plan.score_kernel == 1
+    op.close()
     _check(gpu, oracle, w, max_position=4096)
 
 
@@ -47,9 +64,37 @@ def test_more_sequences_than_one_round_of_the_segment_lookup(gpu, oracle, Mk):  
 @pytest.mark.parametrize("Mk", [16, 32])
 @pytest.mark.parametrize("heads,L", [(4, 20000), (4, 13000), (8, 20000), (8, 9000), (1, 33000)])
 def test_numbers_of_passes(gpu, oracle, Mk, heads, L):  # noqa: F811
-    # one KV head at lengths whose plans use different numbers of passes and slice groups
+    # one KV head at long lengths: two or three passes a workgroup, 4 to 16 slice groups
     _check(gpu, oracle, synth.make_workload(f"passes_m{Mk}_g{heads}_{L}", B=1, Hq=heads, Hkv=1, seqlens=[L], Mk=Mk, Mv=16,
                                             dtype="bf16", seed=L + Mk))
+
+
+# (M_k, query heads per KV head, KV heads, sequences, longest, passes, slice groups): every kernel that a plan can name, in batches whose workgroups go
+# through several slices.  Up to 4 heads: logits in halves, or rows exchanged in pairs of passes.
+HALVES, EXCHANGE, WIDE = 1, 0, 2
+
+
+@pytest.mark.parametrize("Mk,G,Hkv,B,longest,passes,groups,form", [
+    (16, 4, 8, 42, 700, 2, 1, EXCHANGE), (16, 2, 16, 42, 700, 4, 1, EXCHANGE), (16, 4, 8, 50, 514, 4, 2, EXCHANGE),
+    (16, 4, 16, 1, 14477, 2, 1, HALVES), (16, 2, 2, 26, 8193, 3, 1, HALVES), (16, 4, 8, 66, 900, 4, 1, HALVES), (16, 4, 16, 42, 771, 5, 1, HALVES),
+    (16, 1, 16, 66, 514, 6, 1, HALVES), (16, 4, 16, 66, 700, 7, 1, HALVES), (16, 2, 16, 66, 900, 8, 1, HALVES),
+    (16, 8, 16, 4, 1025, 2, 1, WIDE), (16, 8, 16, 50, 255, 3, 1, WIDE), (16, 8, 16, 66, 255, 4, 1, WIDE), (16, 8, 16, 42, 771, 5, 1, WIDE),
+    (16, 8, 16, 66, 514, 6, 1, WIDE), (16, 8, 16, 66, 700, 7, 1, WIDE), (16, 8, 16, 66, 900, 8, 1, WIDE),
+    (32, 2, 2, 42, 514, 2, 4, HALVES), (32, 4, 8, 18, 3000, 3, 1, HALVES), (32, 4, 16, 50, 514, 4, 1, HALVES), (32, 4, 16, 42, 771, 5, 1, HALVES),
+    (32, 1, 16, 66, 514, 6, 1, HALVES), (32, 4, 16, 66, 700, 7, 1, HALVES), (32, 2, 16, 66, 900, 8, 1, HALVES),
+    (32, 8, 16, 6, 511, 2, 1, WIDE), (32, 8, 16, 1, 16405, 3, 1, WIDE), (32, 8, 8, 26, 255, 3, 4, WIDE), (32, 8, 16, 26, 1300, 4, 1, WIDE),
+    (32, 8, 16, 42, 771, 5, 1, WIDE), (32, 8, 16, 66, 514, 6, 1, WIDE), (32, 8, 16, 66, 700, 7, 1, WIDE), (32, 8, 16, 66, 255, 8, 2, WIDE)])
+def test_every_number_of_passes(gpu, oracle, Mk, G, Hkv, B, longest, passes, groups, form):  # noqa: F811
+    # an empty sequence at the beginning and at the end, queries at, before (negative distances) and past the ends
+    lens = [longest] if B == 1 else [0] + [longest - 97 * i % (longest // 2) for i in range(B - 2)] + [0]
+    w = synth.make_workload(f"np{passes}_m{Mk}_g{G}_{B}", B=B, Hq=G * Hkv, Hkv=Hkv, seqlens=lens, Mk=Mk, Mv=16, dtype="bf16", seed=B + longest)
+    w.q_pos = np.array([(max(1, x) - 1, x // 3, x + 777)[i % 3] for i, x in enumerate(lens)], np.int32)
+    most = longest + 1024
+    dw, op = gpu.DeviceWorkload(w), gpu.DecodeAttention(w, max_position=most)
+    assert op.plan.score_slice_groups == groups
+    assert launched(op, dw, "k_score_stream") == (Mk, form, passes)
+    op.close()
+    _check(gpu, oracle, w, max_position=most)
 
 
 def test_partial_logits_of_every_number_of_groups(gpu, oracle):  # noqa: F811
