@@ -76,6 +76,39 @@ def test_explicit_positions_and_storage_that_is_not_aligned(gpu, oracle, Mk):  #
         op.close()
 
 
+@pytest.mark.parametrize("Mk,dtype", [(16, "bf16"), (32, "bf16"), (16, "f32"), (32, "f32")])
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+def test_infinities_and_nan_stay_where_they_are(gpu, Mk, dtype, bad):  # noqa: F811
+    # in an element of one query head: that head's logits; in one codeword of one KV head: those of the tokens that have it. All others keep their bits.
+    import torch
+    w = _make(f"bad_m{Mk}_{dtype}", 32, [200, 33], Mk, dtype)
+    dw, op = gpu.DeviceWorkload(w), gpu.DecodeAttention(w, max_position=1024)
+    assert (op.plan.score_kernel, op.plan.score_split_len) == (0, 16)
+    clean, out = op.scores(dw).clone(), op(dw).clone()
+    lens, code = np.diff(w.cu_seqlens), int(w.key_codes[0])    # first codebook of KV head 0: a codeword that a token has
+    heads = lambda x: [x[32 * c:32 * (c + n)].view(32, n) for c, n in zip(w.cu_seqlens[:-1], lens)]
+    tokens = [np.asarray(w.key_codes[8 * Mk * c:8 * Mk * (c + n)]).reshape(8, n, Mk)[0, :, 0] == code for c, n in zip(w.cu_seqlens[:-1], lens)]
+
+    dw.q.view(2, 32, 128)[1, 5, 77] = bad
+    s, got = op.scores(dw), op(dw)
+    for b, (x, y) in enumerate(zip(heads(s), heads(clean))):
+        for h in range(32):
+            assert not x[h].isfinite().any() if (b, h) == (1, 5) else torch.equal(x[h], y[h])
+    hit = torch.zeros((2, 32), dtype=torch.bool, device="cuda")
+    hit[1, 5] = True
+    assert torch.equal(got.view(2, 32, 128)[~hit], out.view(2, 32, 128)[~hit])
+
+    dw = gpu.DeviceWorkload(w)
+    dw.key_codebooks.view(8, Mk, 256, 128)[0, 0, code, 33] = bad
+    s, got = op.scores(dw), op(dw)
+    assert tokens[0].any() and not tokens[0].all()
+    for x, y, t in zip(heads(s), heads(clean), tokens):
+        t = torch.from_numpy(t).cuda()
+        assert not x[:4, t].isfinite().any() and torch.equal(x[:4, ~t], y[:4, ~t]) and torch.equal(x[4:], y[4:])
+    assert torch.equal(got.view(2, 32, 128)[:, 4:], out.view(2, 32, 128)[:, 4:])
+    op.close()
+
+
 @pytest.mark.parametrize("G", [4, 8])
 def test_sequences_that_share_a_workgroup_of_the_slices(gpu, oracle, G):  # noqa: F811
     # 16 codebooks and more tokens than the rule leaves to this kernel: the segments of several sequences in k_score_stream
