@@ -78,7 +78,7 @@ def check(gpu, oracle, w, regress=TOL_REGRESS, **kw):
 
 
 # ---------------------------------------------------------------- the score stage on its own
-@pytest.mark.parametrize("idx,L", [(1, 777), (2, 1500), (3, 1100), (5, 900)])
+@pytest.mark.parametrize("idx,L", [(1, 777), (2, 1500), (2, 6001), (3, 1100), (3, 7000), (5, 900), (5, 2100)])
 def test_scores_match_oracle_logits(gpu, oracle, idx, L):
     import torch
     w = synth.config(idx, max_len=L)
@@ -94,14 +94,15 @@ def test_scores_match_oracle_logits(gpu, oracle, idx, L):
 
 
 # ---------------------------------------------------------------- the five configurations, reduced lengths
-@pytest.mark.parametrize("idx,L", [(1, 4096), (2, 3000), (3, 5001), (4, 4099), (5, 2500)])
+@pytest.mark.parametrize("idx,L", [(1, 4096), (2, 3000), (3, 5001), (3, 7001), (4, 4099), (5, 2500)])
 def test_configs_reduced(gpu, oracle, idx, L):
     # several score/value splits and a ragged tail (lengths are not multiples of 64)
     check(gpu, oracle, synth.config(idx, max_len=L))
 
 
-def test_staged_entry_points_equal_fused_call(gpu):
-    w = synth.config(3, max_len=3000)
+@pytest.mark.parametrize("L", [3000, 7000])                 # rows gathered; slices
+def test_staged_entry_points_equal_fused_call(gpu, L):
+    w = synth.config(3, max_len=L)
     a = run_gpu(gpu, w)
     b = run_gpu(gpu, w, staged=True)
     # same kernels, same order; the bins are integer, so even the atomics are order-independent
@@ -111,9 +112,10 @@ def test_staged_entry_points_equal_fused_call(gpu):
 @pytest.mark.parametrize("idx", [3, 2, 6, 7])
 def test_prepacked_key_codebooks_give_identical_bits(gpu, idx):
     import torch
-    w = synth.config(idx, max_len=5000)     # index form with 16 / 32 codebooks, paired format with one / two level blocks
+    w = synth.config(idx, max_len=7000)     # index form with 16 / 32 codebooks, paired format with one / two level blocks
     dw = gpu.DeviceWorkload(w)
     op = gpu.DecodeAttention(w)
+    assert op.plan.score_kernel == 1        # (the kernels that read the packed copy)
     a = op(dw).clone()
     op.pack_key_codebooks(dw)
     b = op(dw).clone()
