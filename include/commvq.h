@@ -213,12 +213,15 @@ commvq_status commvq_static_scratch_bytes(size_t *bytes /* host */);
  * 256 / M_k elements (Eq. new_attention is evaluated slice by slice) and wants it in that order.
  * Without preparation every commvq_decode_attn call re-lays the codebook into its workspace
  * first (one extra read + write of the codebook).  commvq_pack_key_codebooks does it once:
- *   key_codebooks  [Hkv][M_k][K][d] bf16, as for commvq_decode_attn
+ *   key_codebooks  [Hkv][M_k][K][d] bf16, as for commvq_decode_attn; must stay alive and unchanged while registered
  *   packed         device buffer of commvq_packed_key_codebook_bytes() bytes, 16-byte aligned,
  *                  owned by the caller; must stay alive and unchanged while registered
  * and remembers the pair in the handle: later calls that pass the same key_codebooks pointer
- * use `packed` instead of re-laying (the caller vouches that the contents did not change; key_codebooks itself is still
- * read by calls that gather rows: explicit key positions, launches of few tokens).
+ * use `packed` instead of re-laying.
+ * BOTH BUFFERS ARE READ.  Calls that stream the slices (score_kernel 1 in commvq_plan_query's answer) read `packed` alone, calls
+ * that gather rows read key_codebooks alone: explicit key positions, and launches of few tokens (score_kernel 0), whose
+ * line depends on the layer and the batch and may move with the library's version.  A caller that gives key_codebooks back after
+ * packing, or overwrites it, has short contexts read freed or wrong memory: forget the pair first.
  * Results are bit-identical either way.  commvq_forget_packed_key_codebooks drops one pair
  * (or all, with NULL).  COMMVQ_ERR_CONFIG for fp32 codebooks (they take another kernel).
  * COMMVQ_KEYS_PAIRED: key_codebooks is the tied table; `packed` then holds it padded to 12, 16 or 24 levels, in

@@ -186,6 +186,7 @@ def commvq_packed_key_codebook_bytes(handle) -> int:
 
 
 def commvq_pack_key_codebooks(handle, key_codebooks, packed, stream: int = 0) -> None:
+    """Both tensors must stay alive and unchanged until the pair is forgotten: launches of few tokens read key_codebooks, others packed."""
     _check(load_library().commvq_pack_key_codebooks(handle, _ptr(key_codebooks), _ptr(packed), stream or None),
            "commvq_pack_key_codebooks")
 

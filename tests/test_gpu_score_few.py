@@ -76,6 +76,22 @@ def test_explicit_positions_and_storage_that_is_not_aligned(gpu, oracle, Mk):  #
         op.close()
 
 
+@pytest.mark.parametrize("Mk,tokens", [(16, 900), (16, 7000), (32, 900), (32, 7000)])
+def test_which_copy_of_registered_key_codebooks_is_read(gpu, Mk, tokens):  # noqa: F811
+    # few tokens: the caller's; slices: the packed one.  Each result is the same with the other copy cleared.
+    import torch
+    import paper_2506_18879_amd as cv
+    w = _make(f"copies_m{Mk}_{tokens}", 32, [tokens], Mk)
+    dw, op = gpu.DeviceWorkload(w), gpu.DecodeAttention(w, max_position=8192)
+    assert op.plan.score_kernel == (tokens > 5000)
+    want = op(dw).clone()
+    packed = torch.empty(cv.commvq_packed_key_codebook_bytes(op.handle), dtype=torch.uint8, device="cuda")
+    cv.commvq_pack_key_codebooks(op.handle, dw.key_codebooks, packed, op.stream_ptr())
+    (dw.key_codebooks if op.plan.score_kernel else packed).zero_()
+    assert torch.equal(op(dw), want)
+    op.close()
+
+
 @pytest.mark.parametrize("Mk,dtype", [(16, "bf16"), (32, "bf16"), (16, "f32"), (32, "f32")])
 @pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
 def test_infinities_and_nan_stay_where_they_are(gpu, Mk, dtype, bad):  # noqa: F811
