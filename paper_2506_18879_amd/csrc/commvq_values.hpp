@@ -528,17 +528,36 @@ __global__ __launch_bounds__(NT, S > 1 ? 2 : 4) void k_values(const ValuesArgs a
             for (int hh = 0; hh < G; ++hh)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) sum[hh][e] = 0.f;
-#pragma unroll 8
-            for (int r = 0; r < NR / RPL; ++r) {
+            typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+            auto row_at = [&](int r) __attribute__((always_inline)) { return *reinterpret_cast<const f4u *>(rows + (size_t)(wave * NR + r * RPL + rl) * kD); };
+            auto add_row = [&](int r, const f4u &c) __attribute__((always_inline)) {
                 const int row = wave * NR + r * RPL + rl, cb = row / kK, code = row % kK;
-                typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
-                const f4u c = *reinterpret_cast<const f4u *>(rows + (size_t)row * kD);
                 const unsigned char *at = lds + code * ROWB + cb * 8;
 #pragma unroll
                 for (int hh = 0; hh < G; ++hh) {
                     const float w = (float)*reinterpret_cast<const unsigned *>(at + hh / 2 * (CB * 8) + (hh & 1) * 4) * 0x1p-32f;
                     sum[hh][0] += w * c.x; sum[hh][1] += w * c.y; sum[hh][2] += w * c.z; sum[hh][3] += w * c.w;
                 }
+            };
+            if constexpr (G == 8 && NCS == 1) {
+                // Sixteen rows asked for at once: left to itself the compiler orders this loop for six wavefronts on a SIMD (there are four), and
+                // a wavefront waits for every row.  Whole calls in microseconds, so -> now: 16 x 8 heads, 40 sequences of 900 tokens 383.7 -> 353.4,
+                // 2 x 8 heads, 40 of 16927 559 -> 520, 4 x 8 heads, 3 of 265 37.8 -> 26.5.  (Fewer heads, or a quarter of the columns a
+                // workgroup: the loop is in that order already; eight at a time and a barrier 1 to 2 % slower.)
+                constexpr int AT = 16;
+                static_assert(NR / RPL % AT == 0, "whole groups of rows");
+#pragma unroll 1
+                for (int r = 0; r < NR / RPL; r += AT) {
+                    f4u c[AT];
+#pragma unroll
+                    for (int k = 0; k < AT; ++k) c[k] = row_at(r + k);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int k = 0; k < AT; ++k) add_row(r + k, c[k]);
+                }
+            } else {
+#pragma unroll 8
+                for (int r = 0; r < NR / RPL; ++r) add_row(r, row_at(r));
             }
 #pragma unroll
             for (int m = LPR; m < 64; m *= 2)
