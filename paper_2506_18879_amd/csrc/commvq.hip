@@ -234,7 +234,7 @@ StreamShape stream_shape(const commvq_handle *h, int B, int64_t T, int max_seqle
         const size_t shared = stats + one + parts, packed = packed_key_bytes(h->cfg);
         return std::max(shared + packed, value_stage_at(shared, parts, packed, few, value) + value);
     };
-    const size_t most_bytes = std::max(bytes(0), kStaticScratchBytes);
+    const size_t most_bytes = bytes(0) <= kStaticScratchBytes ? kStaticScratchBytes : SIZE_MAX;
     StreamShape best = {2, 1, 1};
     double t_best = 1e30;
     const double million = (double)T * h->cfg.n_q_heads / 1e6;  // logits

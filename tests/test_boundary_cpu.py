@@ -326,6 +326,14 @@ def test_a_cut_does_not_outgrow_the_static_scratch(planner, B, T, L):
     assert uncut <= cv.commvq_static_scratch_bytes() and call == 6        # (a full handle would launch)
 
 
+@pytest.mark.parametrize("kw,B,T,L", [(dict(n_q_heads=16, n_kv_heads=2, m_key=32, m_val=16), 64, 5506, 116), (dict(n_q_heads=64, m_key=32, m_val=16), 16, 6478, 690)])
+def test_shapes_beyond_the_static_scratch_are_cut_as_well(planner, kw, B, T, L):
+    """The array sets no limit where the value stage's bins alone exceed it."""
+    h = planner(**kw)
+    assert cv.commvq_workspace_bytes(h, B, T, L) > cv.commvq_static_scratch_bytes()
+    assert cv.commvq_plan_query(h, B, T, L).score_slice_groups > 1
+
+
 @pytest.mark.parametrize("kw", [dict(m_key=16, m_val=16), dict(m_key=32, m_val=32), dict(n_q_heads=64, m_key=16, m_val=16)])
 def test_sixteen_chats_never_need_less_workspace_for_longer_contexts(planner, kw):
     h = planner(**kw)
