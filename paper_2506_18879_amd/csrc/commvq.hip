@@ -191,11 +191,14 @@ StreamShape stream_shape(const commvq_handle *h, int B, int64_t T, int max_seqle
     // by the mean, 63.2 so).
     int spread = 0;
     while (pair && B > 1 && 12 * spread * spread < B) ++spread;
-    const bool known = B == 1 || T == (int64_t)B * max_seqlen;
+    // (k_score_stream: no fewer than the sequences, or a batch of short ones is taken for half of what it is.  Whole calls in microseconds, 64
+    // sequences of up to 233 tokens, 8 x 8 heads, 32 codebooks 120.8 -> 95.3; 2 x 8 heads, 64 of up to 116 48.2 -> 37.4; 8 x 4 heads, 57 of up to 307
+    // 101.9 -> 85.6, with 16 codebooks 50 of up to 270 66.2 -> 55.0.)
+    const bool known = B == 1 || per_seq == 1 || T == (int64_t)B * max_seqlen;
     const double mean = known ? (double)B * per_seq : (double)T / kPassTokens + 0.5 * B, dev = known ? 0.0 : std::sqrt(B / 12.0);
     auto segments = [&](int k) -> int64_t {                   // k = -1, 0, 1
         if (pair) return B == 1 ? most : std::min<int64_t>((int64_t)B * per_seq, T / kPassTokens + (B + 1) / 2 + spread);
-        return std::max<int64_t>(1, std::min<int64_t>((int64_t)B * per_seq, (int64_t)(mean + k * dev + 0.5)));
+        return std::max<int64_t>(B, std::min<int64_t>((int64_t)B * per_seq, (int64_t)(mean + k * dev + 0.5)));
     };
     // k_score_stream, fitted to every cut (2 to 8 passes, 1 to 16 groups) of 28 shapes of 2900 to 131072 tokens and 1 to 64 sequences; the cut
     // chosen is 0.3 % slower than the best on average.  One sequence of at most 32 segments keeps the numbers that it has been cut by,
@@ -206,6 +209,11 @@ StreamShape stream_shape(const commvq_handle *h, int B, int64_t T, int max_seqle
         ? StreamCost{9.0, two ? 1.25 : wide ? 0.6 : 0.5, two ? (wide ? 0.70 : 0.66) : (wide ? 0.47 : 0.41), 5.0, two ? 0.08 : 0.15, 1.0}
         : two ? (wide ? StreamCost{3.18, 1.40, 0.687, 3.04, 0.355, 1.23} : StreamCost{2.57, 1.03, 0.584, 2.06, 0.375, 2.39})
               : (wide ? StreamCost{1.70, 0.917, 0.483, 2.73, 0.855, 1.51} : StreamCost{2.35, 0.747, 0.352, 2.63, 0.715, 1.49});
+    // Launches of at most 64 segments x KV heads: one more slice group costs little there.  Fitted to every cut of 112 batches of 100 to 80000
+    // tokens, 1 to 64 sequences, 1 to 16 KV heads: the cut chosen is 0.5 % slower than the best on average, 2.9 % with the costs above for
+    // all (KV heads x query heads each, microseconds: 1 x 4, 3 sequences of up to 1025 tokens, 16 codebooks 23.5 -> 18.9; 2 x 4, 8 of up to 139, 32
+    // codebooks 21.5 -> 19.4; 1 x 8, 5 of up to 876 24.4 -> 22.0); with the line at 256 some of those beyond it are 3 to 5 % slower.
+    const double group = segments(0) * h->cfg.n_kv_heads <= 64 && !(B == 1 && most <= 32) ? (two ? 0.2 : 0.15) : cost.group;
     // k_score_pair: 16 rounds, four to a slice; 2, 3, 4 or pair_passes passes.  Fitted to 29 shapes of 2000 to 131072 tokens, 1 to 8
     // sequences, R = 11 and 21: 15 cuts each, the one chosen is 0.7 % slower than the best on average (8 sequences of 1100 to 2200 tokens, R = 11:
     // 55.9 us with groups of 8 rounds, 63.0 uncut; one of 2000: 39.9 with groups of two rounds, 56.8 uncut).
@@ -251,7 +259,7 @@ StreamShape stream_shape(const commvq_handle *h, int B, int64_t T, int max_seqle
                     (e > 1 ? 4.8 + e * 3.35 * million : passes == 2 && sets == 3 ? (wide ? 5.0 : 2.5) : 0.0);
             } else {
                 const double n = dev > 0.0 ? 0.3 * rounds(segments(-1)) + 0.4 * rounds(segments(0)) + 0.3 * rounds(segments(1)) : rounds(segments(0));
-                t = n * (cost.fixed + slices * (cost.change + passes * cost.pass)) + (e > 1 ? cost.combine + e * (cost.group + cost.logits * million) : 0.0);
+                t = n * (cost.fixed + slices * (cost.change + passes * cost.pass)) + (e > 1 ? cost.combine + e * (group + cost.logits * million) : 0.0);
             }
             if (t < t_best * 0.9999) { t_best = t; best = StreamShape{passes, 0, e}; }
         }

@@ -334,6 +334,15 @@ def test_shapes_beyond_the_static_scratch_are_cut_as_well(planner, kw, B, T, L):
     assert cv.commvq_plan_query(h, B, T, L).score_slice_groups > 1
 
 
+@pytest.mark.parametrize("Hq,Hkv,Mk,B,T,L,split,groups", [
+    (4, 1, 16, 5, 662, 165, 1024, 16), (8, 2, 32, 8, 838, 139, 1024, 16), (8, 1, 32, 5, 2719, 876, 1024, 16),  # little work: every group it can be cut into
+    (16, 2, 32, 64, 5506, 116, 2048, 8), (16, 4, 16, 40, 5036, 198, 2048, 4)])   # short sequences: a segment each, so one round of workgroups needs 4 and 3 passes
+def test_cuts_of_short_batches(planner, Hq, Hkv, Mk, B, T, L, split, groups):
+    h = planner(n_q_heads=Hq, n_kv_heads=Hkv, m_key=Mk, m_val=16)
+    p = cv.commvq_plan_query(h, B, T, L)
+    assert (p.score_kernel, p.score_split_len, p.score_slice_groups) == (1, split, groups)
+
+
 @pytest.mark.parametrize("kw", [dict(m_key=16, m_val=16), dict(m_key=32, m_val=32), dict(n_q_heads=64, m_key=16, m_val=16)])
 def test_sixteen_chats_never_need_less_workspace_for_longer_contexts(planner, kw):
     h = planner(**kw)

@@ -101,7 +101,7 @@ def test_partial_logits_of_every_number_of_groups(gpu, oracle):  # noqa: F811
     # sums of 2, 4, 8 and 16 groups' partial logits, for lengths around the 256 tokens of a round and the 1024 of a workgroup, empty sequences
     seen = set()
     for i, (Hkv, Mk, lens) in enumerate([(1, 32, [255]), (2, 32, [256, 0, 257]), (1, 16, [1023, 1024, 1025]), (2, 16, [700, 0, 1, 1300]), (8, 32, [5121, 511]),
-                                         (2, 16, [7000, 1, 6143]), (2, 32, [20001]), (8, 16, [9000]), (8, 16, [7000] * 3), (8, 32, [32768]), (4, 16, [9001] * 5)]):
+                                         (2, 16, [7000, 1, 6143]), (2, 32, [20001]), (8, 16, [9000]), (8, 16, [7000] * 3), (8, 32, [32768]), (4, 16, [9001] * 5), (8, 16, [1025, 256, 255] * 7)]):
         w = synth.make_workload(f"parts_{i}", B=len(lens), Hq=4 * Hkv, Hkv=Hkv, seqlens=lens, Mk=Mk, Mv=16, dtype="bf16", seed=600 + i)
         op = gpu.DecodeAttention(w)
         if op.plan.score_kernel == 1:
