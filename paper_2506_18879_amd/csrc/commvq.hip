@@ -276,11 +276,13 @@ inline bool stream_keys(const commvq_config &c) { return !c.position_free; }
 // of passes where most of them are a sequence of its own.  Whole calls in microseconds, halves and exchange: two passes, 24 sequences
 // of 750 to 1500 tokens, 16 codebooks 48.8 and 47.7, R = 11 54.2 and 52.3, 8 of 1750 to 3500 43.5 and 42.3, 49.2 and 46.9 (one sequence of 30000: 37.7 and
 // 39.4, 42.2 and 43.8); four passes, 64 of 280 to 560 71.2 and 68.7, 85.4 and 81.8 (40 of 550 to 1100: 65.4 and 65.9, 78.4 and 78.0; 16 of 2048 to 4096: 54.5
-// and 57.4, 66.2 and 68.9).  32 codebooks: no more than 0.9 either way with short sequences, else halves by 1 to 12.
+// and 57.4, 66.2 and 68.9).  Exchange against halves over every cut of 180 batches, on average: two passes in slice groups 0.98 to 0.99; short
+// sequences with four, six and eight 0.97 to 0.98, with an odd number 0.99 to 1.03; long ones with four and more 1.00 to 1.02.  32
+// codebooks: no more than 0.9 us either way with short sequences, else halves by 1 to 12.
 inline bool exchange_rows(const commvq_handle *h, const StreamShape &s, int B, int64_t T)
 {
     if (h->G == 8 || B == 1 || (!pair_keys(h->cfg) && h->cfg.m_key == 32)) return false;
-    return (s.passes == 2 && s.groups == 1) || ((s.passes == 2 || s.passes == 4) && T <= (int64_t)B * kPassTokens);
+    return s.passes == 2 || (s.passes % 2 == 0 && T <= (int64_t)B * kPassTokens);
 }
 
 // Whether gathering rows (k_score_few) serves a launch of bf16 codebooks with contiguous positions better than the slices: so few
@@ -2330,7 +2332,9 @@ hipError_t launch_stream_g(const StreamArgs &a, int passes, int grid, hipStream_
 }
 hipError_t launch_stream(const StreamArgs &a, int M, int passes, bool exchange, int grid, hipStream_t s)
 {
-    if (exchange) return passes == 2 ? launch_stream_n<16, 0, 2>(a, grid, s) : launch_stream_n<16, 0, 4>(a, grid, s);
+    if (exchange)
+        return passes == 2 ? launch_stream_n<16, 0, 2>(a, grid, s) : passes == 4 ? launch_stream_n<16, 0, 4>(a, grid, s)
+             : passes == 6 ? launch_stream_n<16, 0, 6>(a, grid, s) : launch_stream_n<16, 0, 8>(a, grid, s);
     if (M == 16) return a.d.G == 8 ? launch_stream_g<16, 2>(a, passes, grid, s) : launch_stream_g<16, 1>(a, passes, grid, s);
     return a.d.G == 8 ? launch_stream_g<32, 2>(a, passes, grid, s) : launch_stream_g<32, 1>(a, passes, grid, s);
 }
@@ -2348,7 +2352,9 @@ template <int SETS>
 hipError_t launch_pair_s(const StreamArgs &a, int passes, bool exchange, int R, int PB, int grid, hipStream_t s)
 {
     constexpr int most = pair_passes(SETS);
-    if (exchange) return passes == 2 ? launch_pair_n<SETS, 0, 2>(a, R, PB, grid, s) : launch_pair_n<SETS, 0, 4>(a, R, PB, grid, s);
+    if (exchange)
+        return passes == 2 ? launch_pair_n<SETS, 0, 2>(a, R, PB, grid, s) : passes == 4 ? launch_pair_n<SETS, 0, 4>(a, R, PB, grid, s)
+                                                                                        : launch_pair_n<SETS, 0, most>(a, R, PB, grid, s);
     if (a.d.G == 8) {
         if (passes == 2) return launch_pair_n<SETS, 2, 2>(a, R, PB, grid, s);
         if (passes == 3) return launch_pair_n<SETS, 2, 3>(a, R, PB, grid, s);

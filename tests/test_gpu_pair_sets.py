@@ -60,10 +60,11 @@ def test_several_slices(gpu, oracle, R, G, Hkv, lens, cut):  # noqa: F811
     check(gpu, oracle, R, G, Hkv, lens, cut)
 
 
-# Batches of up to 4 heads that exchange rows in pairs of passes: uncut with two passes, short sequences with two and four, an empty
+# Batches of up to 4 heads that exchange rows in pairs of passes: two passes, short sequences with every even number, an empty
 # sequence at the beginning and at the end.
 @pytest.mark.parametrize("R,G,Hkv,B,longest,cut", [
     (11, 1, 8, 50, 511, (2, 1)), (11, 4, 8, 26, 1300, (2, 1)), (11, 4, 16, 66, 255, (4, 1)), (11, 2, 8, 26, 300, (4, 4)),
-    (14, 4, 16, 26, 300, (2, 1)), (14, 2, 16, 66, 255, (4, 1)), (21, 4, 16, 26, 300, (2, 1)), (21, 4, 16, 66, 255, (4, 1)), (21, 1, 4, 26, 300, (4, 8))])
+    (14, 4, 16, 26, 300, (2, 1)), (14, 2, 16, 66, 255, (4, 1)), (21, 4, 16, 26, 300, (2, 1)), (21, 4, 16, 66, 255, (4, 1)), (21, 1, 4, 26, 300, (4, 8)),
+    (11, 2, 16, 74, 255, (8, 1)), (14, 2, 16, 18, 255, (6, 4)), (21, 2, 16, 18, 255, (6, 4))])
 def test_rows_exchanged_in_pairs_of_passes(gpu, oracle, R, G, Hkv, B, longest, cut):  # noqa: F811
     check(gpu, oracle, R, G, Hkv, [0] + [longest - 97 * i % (longest // 2) for i in range(B - 2)] + [0], cut, form=0)

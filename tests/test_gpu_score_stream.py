@@ -75,7 +75,7 @@ HALVES, EXCHANGE, WIDE = 1, 0, 2
 
 
 @pytest.mark.parametrize("Mk,G,Hkv,B,longest,passes,groups,form", [
-    (16, 4, 8, 42, 700, 2, 1, EXCHANGE), (16, 2, 16, 42, 700, 4, 1, EXCHANGE),
+    (16, 4, 8, 42, 700, 2, 1, EXCHANGE), (16, 2, 16, 42, 700, 4, 1, EXCHANGE), (16, 2, 16, 22, 255, 6, 4, EXCHANGE), (16, 2, 16, 30, 255, 8, 4, EXCHANGE),
     (16, 4, 16, 1, 14477, 2, 1, HALVES), (16, 2, 2, 18, 11000, 3, 1, HALVES), (16, 2, 8, 66, 900, 4, 1, HALVES), (16, 2, 16, 50, 600, 5, 1, HALVES),
     (16, 2, 16, 26, 800, 6, 2, HALVES), (16, 2, 16, 66, 700, 7, 1, HALVES), (16, 4, 16, 66, 900, 8, 1, HALVES),
     (16, 8, 8, 42, 600, 2, 1, WIDE), (16, 8, 8, 66, 514, 3, 1, WIDE), (16, 8, 16, 42, 600, 4, 1, WIDE), (16, 8, 16, 50, 600, 5, 1, WIDE),
