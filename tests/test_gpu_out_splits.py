@@ -6,7 +6,10 @@ Same bar as the other binary-value tests, 2e-5 of a row's largest element: fp32 
 import numpy as np
 import pytest
 
+from paper_2506_18879_amd import device, synth
+
 from test_gpu_binary_values import errors, gpu, make, oracle_out, run_gpu  # noqa: F401  (gpu: a fixture)
+from test_gpu_score_stream import _check, launched
 
 pytestmark = pytest.mark.gpu
 
@@ -25,3 +28,16 @@ def test_output_over_many_splits(gpu, oracle, Hq, Hkv, lens, Nc, dtype):  # noqa
     got = run_gpu(gpu, w)
     row, _ = errors(got, oracle_out(oracle, w))
     assert np.isfinite(got).all() and row <= 2e-5, row
+
+
+@pytest.mark.parametrize("Hq,Hkv,Mv,lens,ahead", [
+    (32, 8, 16, [300, 0, 40] * 7, 1), (64, 8, 16, [700] * 9, 1),                  # up to 4 rows: one a thread
+    (32, 8, 32, [1000, 0], 4), (32, 8, 16, [3500], 4), (32, 8, 16, [4097], 16),  # 8, 16 and 20
+    (4, 1, 16, [16384, 1, 0, 5000], 16), (4, 1, 16, [16385], 16), (4, 1, 32, [40000], 16)])  # 64 and more: the rest in a loop
+def test_rows_asked_for_ahead_of_the_length(gpu, oracle, Hq, Hkv, Mv, lens, ahead):  # noqa: F811
+    # indexed values: range and codebook group of a workgroup each have a row per head
+    w = synth.make_workload(f"ahead_{Hq}_{len(lens)}", B=len(lens), Hq=Hq, Hkv=Hkv, seqlens=lens, Mk=16, Mv=Mv, dtype="bf16", seed=Hq + sum(lens))
+    dw, op = device.DeviceWorkload(w), device.DecodeAttention(w)
+    assert launched(op, dw, "k_out_final") == (ahead,)
+    op.close()
+    _check(device, oracle, w)
