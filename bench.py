@@ -362,7 +362,8 @@ def main():
     score_flops = units * w.d * (w.Mk + 3 + 2 * G)
     achieved_tflops = score_flops / score_s / 1e12 if score_s > 0 else 0.0
     paired = w.key_format == "paired"
-    kname = "k_score_pair" if paired else ("k_score_stream" if w.dtype == "bf16" else "k_score")
+    slices = bool(op.plan.score_kernel)                        # else rows gathered: fp32 codebooks, launches of few tokens
+    kname = "k_score_pair" if paired else "k_score_stream" if slices else "k_score_few" if op.plan.score_split_len == 16 else "k_score"
     if args.position_free:
         kname = "k_score_lut"
     # HBM bytes per launch from rocprofv3 counter passes (FETCH_SIZE, WRITE_SIZE) of this same command: counters
@@ -386,7 +387,7 @@ def main():
     pieces = 2 * (12 if w.key_levels <= 12 else 16 if w.key_levels <= 16 else 24) if paired else w.Mk
     gather_bytes = units * pieces * w.d * esz
     gather_tbs = gather_bytes / score_s / 1e12 if score_s > 0 else 0.0
-    mfma_tflops = (gather_bytes / 16 / 64 * 16384) / score_s / 1e12 if (score_s > 0 and w.dtype == "bf16") else 0.0
+    mfma_tflops = (gather_bytes / 16 / 64 * 16384) / score_s / 1e12 if (score_s > 0 and slices) else 0.0
     mfma_peak = 2.0 * MFMA_BF16_PEAK_TFLOPS
     roofline = {"kernel": kname, "bound": "alu", "achieved": round(achieved_tflops, 3), "peak": FP32_PEAK_TFLOPS,
                 "unit": "TFLOP/s", "frac": round(achieved_tflops / FP32_PEAK_TFLOPS, 4), "traffic": traffic,
@@ -394,7 +395,8 @@ def main():
                 "kernel_ms": round(stage_ms[0], 5), "launches_averaged": n_prof,
                 "launches_sampled": ("every call of a separate eager run" if args.graph else
                                      f"every {args.stage_event_interval}th call of the timed region"),
-                "timed_region_includes": ("k_score_pair + k_score_combine" if paired and op.plan.score_slice_groups > 1 else "k_score_pair" if paired else
+                "timed_region_includes": (f"{kname} only" if not slices else
+                                          "k_score_pair + k_score_combine" if paired and op.plan.score_slice_groups > 1 else "k_score_pair" if paired else
                                           "k_score_stream + k_score_combine" if prepacked and op.plan.score_slice_groups > 1 else
                                           "k_score_stream only" if prepacked else "codebook re-layout (k_prep) + score kernel"),
                 "lds_gather_view": {"codeword_bytes_TBs": round(gather_tbs, 2), "peak_TBs": LDS_PEAK_TBS,

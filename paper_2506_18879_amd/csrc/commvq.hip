@@ -460,7 +460,6 @@ __device__ __forceinline__ float row_sum16(float v)
     return v + dpp_mov<0x140>(v);
 }
 
-
 // Score kernel.  A wavefront handles FOUR tokens per iteration, one per 16-lane row; lane
 // `sub` of a row owns sub-spaces 4*sub .. 4*sub+3 (elements 8*sub .. 8*sub+7), i.e. 16 bytes of
 // a bf16 codeword row, so one 16-byte-per-lane buffer load fetches four different codeword
@@ -499,7 +498,7 @@ __global__ __launch_bounds__(kScoreThreads) void k_score(
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     const int r = lane >> 4, sub = lane & 15;
-    const int wlen = a.split_len / (kScoreThreads / 64);  // 4, 8, 16, 32 or a multiple of 64 tokens per wavefront
+    const int wlen = a.split_len / (kScoreThreads / 64);  // 8, 16, 32 or a multiple of 64 tokens per wavefront (4: launch_score_mg)
     const int t0 = s0 + wave * wlen;
     const int t1 = min(min(t0 + wlen, s0 + a.split_len), L);
     const int n_it = t1 > t0 ? (t1 - t0 + 3) / 4 : 0;
@@ -1393,7 +1392,7 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_stream(
             else if (__builtin_expect(chg >> p & 1u, 0)) hi_row(qd[p]);
             eh = lds_read_b128(ehi_at + (unsigned)(p * 2 * kHiRows * 16));
             // What the next slice needs sets out spread over this one's passes (a burst of sends fills the memory pipe's queue and
-            // stops the wavefronts): its codebook (M = 16) or the registers' share of it, phase factors and queries
+            // stops the wavefronts): its codebook (M = 16; two blocks' are sent at the end of the last pass), phase factors and queries
             if (more) {
                 if (M == 16) {
 #pragma unroll
@@ -2264,7 +2263,8 @@ struct ScoreArgs {
 // fp32 rows of 32 codebooks with 4 or 8 heads, where it takes 256 registers, one wavefront per SIMD, which pays only while there is
 // about one workgroup per SIMD.  Whole calls in microseconds, k_score against it: 4 heads, 656 workgroups 28.5 and 28.1, 800 31.0 and
 // 32.1, 4000 78.1 and 85.4; 8 heads, 1500 63.0 and 61.6, 2000 69.9 and 70.2, 4000 104.5 and 108.5.  (1 and 2 heads, 16 codebooks and bf16:
-// faster with it by 4 to 30 % up to 4000.)
+// faster with it by 4 to 30 % up to 4000, which one KV head reaches at 65000 tokens: one fp32 head, 32 codebooks 8000 tokens 19.4 and 17.0,
+// 32000 43.4 and 37.1, 65000 75.6 and 64.3; 8 heads, 16 codebooks 65000 89.2 and 69.3; explicit positions, bf16, 4 heads, 16 codebooks 53.7 and 41.4.)
 template <int M, int G>
 hipError_t launch_score_mg(const ScoreArgs &a, bool bf16, int batch, hipStream_t s)
 {

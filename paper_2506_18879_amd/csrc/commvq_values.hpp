@@ -105,8 +105,9 @@ __device__ __forceinline__ float swap32_add(float x, float y)
 // registers, column 8 n + t of lane n for tile t, so the codebook needs no other layout.  fp32 rows are multiplied by vector
 // instructions, four columns per lane.
 //
-// What bounds it, by clocks at the phases' ends, 128K tokens of the 8B layer at 16 codebooks (16 us in the workgroups, and the launch
-// after a kernel that leaves 17 MB of dirty lines): 2 until the first token is worked on, 10.8 for the tokens (the atomics alone are
+// What bounds it, by clocks at the phases' ends, 128K tokens of the 8B layer at 16 codebooks (16 us in the workgroups of 20.4 under the
+// tracer, the rest is its launch and end; 20.9 while the score kernels left 17 MB of logits dirty in the L2s, which they now write
+// through): 2 until the first token is worked on, 10.8 for the tokens (the atomics alone are
 // 7.3 at 8.2 lanes a clock, the vector instructions of four wavefronts as much), 0.4 for the copies' sums, 1.3 for the rows of the product,
 // 1.2 for the digits and 0.5 for the wavefronts' sums.  The statistics are asked for before the sequence's length is known and ahead of
 // the tokens, and the workgroup's indices take no division: with both behind the length the phase before the tokens was 3.1 us (whole
