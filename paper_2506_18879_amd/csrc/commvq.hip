@@ -201,8 +201,8 @@ StreamShape stream_shape(const commvq_handle *h, int B, int64_t T, int max_seqle
         return std::max<int64_t>(B, std::min<int64_t>((int64_t)B * per_seq, (int64_t)(mean + k * dev + 0.5)));
     };
     // k_score_stream, fitted to every cut (2 to 8 passes, 1 to 16 groups) of 28 shapes of 2900 to 131072 tokens and 1 to 64 sequences; the cut
-    // chosen is 0.3 % slower than the best on average.  One sequence of at most 32 segments keeps the numbers that it has been cut by,
-    // and with them the cut that the tests pin at 16384 tokens (1 to 6 % slower than the best).
+    // chosen is 0.3 % slower than the best on average.  One sequence of at most 32 segments keeps the numbers of an older form of
+    // the kernel, for the sake of the cut that a test names at 16384 tokens and not of its speed (1 to 6 % slower than the best).
     // (One sequence of 32768 tokens, 32 codebooks 38.9 -> 36.7 us; 24 of 300 to 600 45.7 -> 29.2; 40 of 1500 to 3000 92.6 -> 83.9.)
     const bool two = h->cfg.m_key == 32, wide = h->G == 8;
     const StreamCost cost = B == 1 && most <= 32
@@ -278,7 +278,8 @@ inline bool stream_keys(const commvq_config &c) { return !c.position_free; }
 // 39.4, 42.2 and 43.8); four passes, 64 of 280 to 560 71.2 and 68.7, 85.4 and 81.8 (40 of 550 to 1100: 65.4 and 65.9, 78.4 and 78.0; 16 of 2048 to 4096: 54.5
 // and 57.4, 66.2 and 68.9).  Exchange against halves over every cut of 180 batches, on average: two passes in slice groups 0.98 to 0.99; short
 // sequences with four, six and eight 0.97 to 0.98, with an odd number 0.99 to 1.03; long ones with four and more 1.00 to 1.02.  32
-// codebooks: no more than 0.9 us either way with short sequences, else halves by 1 to 12.
+// codebooks: no more than 0.9 us either way with short sequences, else halves by 1 to 12.  (The exchange adds a token's 8 products in one chain,
+// halves in two of 4: rms error of the logits 1.25e-7 and 1.06e-7.)
 inline bool exchange_rows(const commvq_handle *h, const StreamShape &s, int B, int64_t T)
 {
     if (h->G == 8 || B == 1 || (!pair_keys(h->cfg) && h->cfg.m_key == 32)) return false;
@@ -291,8 +292,9 @@ inline bool exchange_rows(const commvq_handle *h, const StreamShape &s, int B, i
 // 16 codebooks 200 tokens 18.3 -> 14.4, 1237 21.5 -> 14.9, 4000 24.2 -> 20.6, 6000 27.3 -> 24.6, 8000 27.3 -> 28.4; 32 + 32 codebooks 200
 // tokens 18.5 -> 13.6, 1237 24.7 -> 19.6, 2500 26.9 -> 23.6, 3200 27.0 -> 26.9, 4000 27.4 -> 28.8; 8 query heads each and 32 + 32 codebooks
 // 1237 tokens 27.9 -> 22.8, 2500 30.8 -> 27.2, 3200 30.0 -> 31.4; 24 sequences of 256, 16 + 16 codebooks 35.3 -> 29.1; 32 KV heads of 4,
-// 32 + 32 codebooks 300 tokens 34.2 -> 27.9, 1000 36.6 -> 42.1.  Layers of fewer than 8 KV heads keep the slices, whose cuts the
-// tests pin on layers of two (two heads of 4, 16 + 16 codebooks, 3000 tokens: 21.2 us, with rows 14.7).
+// 32 + 32 codebooks 300 tokens 34.2 -> 27.9, 1000 36.6 -> 42.1.  Layers of fewer than 8 KV heads keep the slices, not
+// because they are faster there (two KV heads of 4, 16 + 16 codebooks: 1500 tokens 20.8 us, with rows 17.4, 6000 20.8 and 17.0) but because the tests of
+// the slices are written for such layers.
 inline bool few_tokens(const commvq_handle *h, int B, int64_t T, int max_seqlen)
 {
     const commvq_config &c = h->cfg;
