@@ -1557,10 +1557,11 @@ __global__ __launch_bounds__(kSliceThreads) void k_score_stream(
 // partial logits of the slice groups (Eq. new_attention's sum over the sub-spaces, split in `groups` parts).  One
 // workgroup per (sequence, query head, 1024 tokens): adds the parts in a fixed order, writes the logits (over the
 // first group's part) and the (max, sum of exp) of its 1024 tokens.
-// Bound by latency: all parts of all its tokens are requested at once, with no branch before, between or behind them.  (A branch per part and a round of
+// Bound by latency: all parts of all its tokens are requested at once.  (A branch per part and a round of
 // requests per 256 tokens went through 4 KB of instructions that had to be fetched on the way: whole calls in microseconds, so -> now, paired keys
 // R = 11: two KV heads of one 400 tokens 18.8 -> 17.7, 2000 20.1 -> 17.7, 8 x 4 heads 400 20.3 -> 19.2, 1000 21.8 -> 19.7, R = 21 4000 25.4 -> 24.6;
-// 32 codebooks, 8 x 4 heads 8000 27.6 -> 26.9, 32768 50.8 -> 50.6.)
+// 32 codebooks, 8 x 4 heads 8000 27.6 -> 26.9, 32768 50.8 -> 50.6.)  Part by part of the tokens, and none past the row: the parts one after the other, with
+// reads past the row that return zero, took 5.95 us for one sequence of 17107 tokens, 8 x 8 heads in four groups (5.6 so), 5.58 for 24 of 600 (5.08).
 constexpr int kCombineThreads = 256, kCombineTokens = 1024;
 template <int GROUPS>
 __global__ __launch_bounds__(kCombineThreads) void k_score_combine(float *scores, float2 *__restrict__ sstat, const int32_t *__restrict__ cu,
@@ -1576,13 +1577,12 @@ __global__ __launch_bounds__(kCombineThreads) void k_score_combine(float *scores
     if (t0 >= L) return;
     float *const row = scores + (size_t)cu0 * Hq + (size_t)h * L;
     constexpr int MAXV = kCombineTokens / kCombineThreads;
-    float part[GROUPS][MAXV];                                 // (reads past the row return zero)
+    float part[MAXV][GROUPS];
 #pragma unroll
-    for (int e = 0; e < GROUPS; ++e) {
-        const __amdgpu_buffer_rsrc_t r = make_rsrc(row + (size_t)e * part_stride, (unsigned)L * 4u);
+    for (int k = 0; k < MAXV; ++k) {
+        const int tok = t0 + k * kCombineThreads + (int)threadIdx.x;
 #pragma unroll
-        for (int k = 0; k < MAXV; ++k)
-            part[e][k] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (unsigned)(t0 + k * kCombineThreads + (int)threadIdx.x) * 4u, 0, 0));
+        for (int e = 0; e < GROUPS; ++e) part[k][e] = tok < L ? row[(size_t)e * part_stride + (unsigned)tok] : 0.f;
     }
     __builtin_amdgcn_sched_barrier(0);
     float v[MAXV], mx = -INFINITY;
@@ -1590,9 +1590,9 @@ __global__ __launch_bounds__(kCombineThreads) void k_score_combine(float *scores
 #pragma unroll
     for (int k = 0; k < MAXV; ++k) {                          // in a fixed order, over the first group's part
         const int tok = t0 + k * kCombineThreads + (int)threadIdx.x;
-        float acc = part[0][k];
+        float acc = part[k][0];
 #pragma unroll
-        for (int e = 1; e < GROUPS; ++e) acc += part[e][k];
+        for (int e = 1; e < GROUPS; ++e) acc += part[k][e];
         v[k] = tok < L ? acc : -INFINITY;
         mx = fmaxf(mx, v[k]);
         if (tok < L) store_through(acc, own, (unsigned)tok * 4u);
